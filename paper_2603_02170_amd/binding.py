@@ -1,6 +1,7 @@
-"""Thin ctypes binding of libsagebwd.so: argument marshalling only.
+"""Thin binding of libsagebwd.so: argument marshalling only.
 
-Every step of the path runs in the HIP library; PyTorch is used for device
+The three calls of the method go through the native module `_sage_host` (csrc/torch_host.cpp), the
+inspection hooks, the helpers and the probes through ctypes.  Every step of the path runs in the HIP library; PyTorch is used for device
 memory and the current stream.  There is no CPU fallback: if the library is
 missing or a call fails, an exception is raised.
 """
@@ -14,6 +15,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB = None
+_HOST = None
 
 SMOOTH_K = 1
 SMOOTH_Q = 2
@@ -124,6 +126,20 @@ def load_library():
     return lib
 
 
+def _host():
+    """The native host module (built with the library); raises if absent."""
+    global _HOST
+    if _HOST is None:
+        load_library()
+        try:
+            from . import _sage_host
+        except ImportError as e:
+            raise RuntimeError("_sage_host.so not usable: build it with `python -m paper_2603_02170_amd.build` "
+                               "(there is no fallback path)") from e
+        _HOST = _sage_host
+    return _HOST
+
+
 def sagebwd_strerror(status: int) -> str:
     return load_library().sagebwd_strerror(int(status)).decode()
 
@@ -150,6 +166,11 @@ def _stream():
 def _expect(t, dtype, shape, name):
     if t.dtype != dtype or tuple(t.shape) != tuple(shape) or not t.is_contiguous() or not t.is_cuda:
         raise ValueError(f"{name}: need contiguous cuda {dtype} {tuple(shape)}, got {t.dtype} {tuple(t.shape)}")
+
+
+def _expect_named(t, dtype, shape, name):
+    """The native module's way to raise: it found that `t` is not what the call needs."""
+    _expect(t, getattr(torch, dtype), shape, name)
 
 
 def workspace_bytes(p: SageParams, forward_only: bool = False) -> int:
@@ -221,23 +242,7 @@ def sagebwd_export_ds(p: SageParams, workspace, head: int):
 
 def sagebwd_fwd(Q, K, V, p: SageParams, workspace=None, O=None, LSE=None):
     """O, LSE = INT8 attention forward.  Allocates outputs / workspace when not given."""
-    shp, kshp = p.tensor_shape(), p.tensor_shape(kv=True)
-    lshp = (p.B, p.H, p.N)
-    _expect(Q, torch.bfloat16, shp, "Q")
-    for t, n in ((K, "K"), (V, "V")):
-        _expect(t, torch.bfloat16, kshp, n)
-    if workspace is None:
-        workspace = alloc_workspace(p, Q.device, forward_only=True)
-    if O is None:
-        O = torch.empty(shp, dtype=torch.bfloat16, device=Q.device)
-    if LSE is None:
-        LSE = torch.empty(lshp, dtype=torch.float32, device=Q.device)
-    _expect(O, torch.bfloat16, shp, "O")
-    _expect(LSE, torch.float32, lshp, "LSE")
-    cp = p.c()
-    _check(load_library().sagebwd_fwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(LSE), ctypes.byref(cp),
-                                      _ptr(workspace), workspace.numel(), _stream()), "sagebwd_fwd")
-    return O, LSE
+    return _host().fwd(Q, K, V, p, workspace, O, LSE)
 
 
 STATIC_SCRATCH_BYTES = 32 << 20
@@ -246,39 +251,12 @@ STATIC_SCRATCH_BYTES = 32 << 20
 def sagebwd_fwd_static(Q, K, V, p: SageParams, O, LSE):
     """The forward on the library's built-in scratch: the call allocates nothing, so the caller
     passes the outputs too."""
-    shp, kshp = p.tensor_shape(), p.tensor_shape(kv=True)
-    for t, n in ((Q, "Q"), (O, "O")):
-        _expect(t, torch.bfloat16, shp, n)
-    for t, n in ((K, "K"), (V, "V")):
-        _expect(t, torch.bfloat16, kshp, n)
-    _expect(LSE, torch.float32, (p.B, p.H, p.N), "LSE")
-    cp = p.c()
-    _check(load_library().sagebwd_fwd_static(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(LSE), ctypes.byref(cp),
-                                             _stream()), "sagebwd_fwd_static")
-    return O, LSE
+    return _host().fwd_static(Q, K, V, p, O, LSE)
 
 
 def sagebwd_bwd(Q, K, V, O, dO, LSE, p: SageParams, workspace=None, dQ=None, dK=None, dV=None):
     """dQ, dK, dV = INT8 attention backward."""
-    shp, kshp = p.tensor_shape(), p.tensor_shape(kv=True)
-    for t, n in ((Q, "Q"), (O, "O"), (dO, "dO")):
-        _expect(t, torch.bfloat16, shp, n)
-    for t, n in ((K, "K"), (V, "V")):
-        _expect(t, torch.bfloat16, kshp, n)
-    _expect(LSE, torch.float32, (p.B, p.H, p.N), "LSE")
-    if workspace is None:
-        workspace = alloc_workspace(p, Q.device)
-    outs = []
-    for t, n, sh in ((dQ, "dQ", shp), (dK, "dK", kshp), (dV, "dV", kshp)):
-        if t is None:
-            t = torch.empty(sh, dtype=torch.bfloat16, device=Q.device)
-        _expect(t, torch.bfloat16, sh, n)
-        outs.append(t)
-    cp = p.c()
-    _check(load_library().sagebwd_bwd(_ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(dO), _ptr(LSE), _ptr(outs[0]),
-                                      _ptr(outs[1]), _ptr(outs[2]), ctypes.byref(cp), _ptr(workspace),
-                                      workspace.numel(), _stream()), "sagebwd_bwd")
-    return tuple(outs)
+    return _host().bwd(Q, K, V, O, dO, LSE, p, workspace, dQ, dK, dV)
 
 
 TIMING_ALL = 31

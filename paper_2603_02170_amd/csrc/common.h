@@ -97,6 +97,12 @@ __device__ __forceinline__ void async_copy_4(const void* gsrc_lane, void* lds_ba
   __builtin_amdgcn_global_load_lds((gptr_t)gsrc_lane, (lptr_t)lds_base, 4, 0, 0);
 }
 
+// A wave-uniform value through the scalar cache: no vector-memory instruction and no register of 64 lanes.  (The
+// buffer must not be written by the same kernel.)
+__device__ __forceinline__ float scalar_load(const float* p) {
+  return *(const __attribute__((address_space(4))) float*)(uintptr_t)p;
+}
+
 // Immediate of `s_waitcnt vmcnt(n)` alone (the LDS / scalar and export counters are left at their
 // maxima = no wait): the six bits of n sit in bits 3:0 and 15:14.
 constexpr int vmcnt_only(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }

@@ -105,7 +105,9 @@ __device__ __forceinline__ void fwd_s_mfma(const int8_t* __restrict__ Kt, const 
 // The instruction stream is laid out by hand in chunks separated by scheduling barriers: each
 // chunk pairs one MFMA (and the LDS read of an operand two MFMAs ahead) with the vector work of
 // four logits or of sixteen output values, so that the matrix pipe and the LDS latency hide
-// under the vector instructions of the same wave.
+// under the vector instructions of the same wave.  `copy(k)` issues the k-th of this wave's global -> LDS
+// copies for a coming tile, one in every second slot: a wave issues such a copy in about 100 cycles when it
+// follows another one, so the five of a tile in one place stood for 500 of a tile's 2500 cycles.
 //
 // KV128 = numerics blocks of 128 keys: the per-token quantiser of P~ (Algorithm 1 line 9) then takes its row
 // max over both 64-key tiles of the block.  `pair` carries the other tile's row max in (INT_MIN / -inf if
@@ -114,8 +116,8 @@ struct PairMax {
   int i;      // integer domain (no Q-smoothing: both tiles of a block share the scale c)
   float f;    // log2 domain (Q-smoothing)
 };
-template <int D, bool QSMOOTH, bool MASK, bool NEXT, bool SBIAS, bool KV128 = false>
-__device__ __forceinline__ void fwd_tile(const int8_t* __restrict__ Knext, const int8_t* __restrict__ Vt,
+template <int D, bool QSMOOTH, bool MASK, bool NEXT, bool SBIAS, bool KV128 = false, class Copy>
+__device__ __forceinline__ void fwd_tile(const Copy& copy, const int8_t* __restrict__ Knext, const int8_t* __restrict__ Vt,
                                          const v4i (&qf)[D / 32], v16i (&sacc)[2], v16i (&snext)[2],
                                          float (&oacc)[D / 32][16], float& w_bias, float& m_ref, float& l_part,
                                          const float c, const float sv, const float* __restrict__ bias_row,
@@ -224,6 +226,7 @@ __device__ __forceinline__ void fwd_tile(const int8_t* __restrict__ Knext, const
     // priority over its SIMD neighbour, which is mostly in the matrix-heavy second half (measured: 5-7 %).
     if (sl == 0) __builtin_amdgcn_s_setprio(1);
     if (sl == 8) __builtin_amdgcn_s_setprio(0);
+    if (sl & 1) copy(sl >> 1);
     // LDS reads: V^ fragment of the MFMA two slots ahead
 #pragma unroll
     for (int m = 0; m < 2 * KS; m++)
@@ -330,9 +333,9 @@ __global__ void __launch_bounds__(64 * NW, (NW == 4 ? (D == 64 ? 3 : 2) : 1)) sa
   constexpr int QT = 32 * NW;                // queries per workgroup
 
   // Q-smoothing: the 64 logit biases of each wave's Q block and the tile's keys travel with the tile too
-  constexpr int BIAS_OFF = PAIR + 64;
+  constexpr int BIAS_OFF = PAIR;
   constexpr int SLOT = BIAS_OFF + (QSMOOTH ? NW * 256 : 0);
-  __shared__ __attribute__((aligned(16))) int8_t lds[4][SLOT];   // K^ | V^ | per-wave (s_K, s_V) | per-wave bias row
+  __shared__ __attribute__((aligned(16))) int8_t lds[4][SLOT];   // K^ | V^ | per-wave bias row
 
   // workgroup -> (head, query tile): a head's tiles share one XCD's L2; heaviest (last) query
   // tiles first under the causal mask, over sets of heads (see work_item)
@@ -384,19 +387,21 @@ __global__ void __launch_bounds__(64 * NW, (NW == 4 ? (D == 64 ? 3 : 2) : 1)) sa
 
   // Asynchronous copy of tile j (K^ fragments, then V^ fragments) into a ring slot; the
   // 1 KiB fragments are dealt round-robin to the waves.
+  constexpr int CPW = NFRAG / NW + (QSMOOTH ? 1 : 0);   // copies per wave and tile
+  static_assert(NFRAG % NW == 0, "every wave must issue the same number of copies");
+  auto copy_piece = [&](int j, int8_t* dst, int k) __attribute__((always_inline)) {
+    const int o = wave + NW * k;             // wave-uniform
+    if (k < NFRAG / NW) {
+      const int8_t* src = o < NFRAG / 2 ? KFh + (size_t)j * TILE_BYTES + o * 1024
+                                        : VTh + (size_t)j * TILE_BYTES + (o - NFRAG / 2) * 1024;
+      async_copy_16(src + lane * 16, dst + o * 1024);
+    } else if (QSMOOTH && k == NFRAG / NW) {
+      async_copy_4(bias_row + j * kBlock + lane, dst + BIAS_OFF + wave * 256);
+    }
+  };
   auto stage_load = [&](int j, int8_t* dst) {
 #pragma unroll
-    for (int k = 0; k < (NFRAG + NW - 1) / NW; k++) {
-      const int o = wave + NW * k;           // wave-uniform
-      if (o < NFRAG) {
-        const int8_t* src = o < NFRAG / 2 ? KFh + (size_t)j * TILE_BYTES + o * 1024
-                                          : VTh + (size_t)j * TILE_BYTES + (o - NFRAG / 2) * 1024;
-        async_copy_16(src + lane * 16, dst + o * 1024);
-      }
-    }
-    // the two block scales of the tile, one private copy per wave (lanes 0 and 1 carry them)
-    if (lane < 2) async_copy_4((lane == 0 ? sKh : sVh) + j, dst + PAIR + wave * 8);
-    if constexpr (QSMOOTH) async_copy_4(bias_row + j * kBlock + lane, dst + BIAS_OFF + wave * 256);
+    for (int k = 0; k < CPW; k++) copy_piece(j, dst, k);
   };
 
   int8_t* cur = &lds[0][0];
@@ -413,15 +418,13 @@ __global__ void __launch_bounds__(64 * NW, (NW == 4 ? (D == 64 ? 3 : 2) : 1)) sa
   // past the barrier that ended iteration j - 1, so nobody reads it any more); this wave forms
   // S_{j+1} from slot `nxt` and finishes tile j with V^ from slot `cur`; before the barrier at
   // the end it waits for the copies of tile j + 2 (issued one iteration earlier), while its copies
-  // of tile j + 3 stay in flight.  The block scales travel with the tiles, so the loop has no
-  // register-returning global loads whose waits would also drain the copies.  Every wave of
+  // of tile j + 3 stay in flight.  The block scales come one tile ahead through the scalar cache, so the
+  // loop has no register-returning vector loads whose waits would also drain the copies.  Every wave of
   // the workgroup runs n_tiles iterations (the barriers must match): its unmasked tiles, its last
   // tile, then iterations that only keep the ring moving.
-  constexpr int CPW = (NFRAG + NW - 1) / NW + (QSMOOTH ? 1 : 0);   // copies per wave and tile (every wave issues all of them)
-  static_assert(NFRAG % NW == 0, "every wave must issue the same number of copies");
   auto end_iter = [&](const bool issued) {
     if (issued) {
-      __builtin_amdgcn_s_waitcnt(0x0F70 | (CPW + 1));   // vmcnt: all but this iteration's copies
+      __builtin_amdgcn_s_waitcnt(vmcnt_only(CPW));   // vmcnt: all but this iteration's copies
       barrier_lds_only();
     } else {
       barrier_all_memory();
@@ -462,21 +465,23 @@ __global__ void __launch_bounds__(64 * NW, (NW == 4 ? (D == 64 ? 3 : 2) : 1)) sa
     // instead would cost 32 registers this kernel does not have).  The odd tile takes the even tile's own
     // row max, which fwd_tile leaves in `pm`.
     PairMax pm{INT_MIN, -INFINITY};
+    float sk = scalar_load(sKh), sv = scalar_load(sVh);     // scales of tile j
     auto partner_max = [&](const int jn, auto mask_tag) __attribute__((always_inline)) {
       constexpr bool MASKED = decltype(mask_tag)::value;
       v16i sT[2];
       fwd_s_mfma<D, SBIAS>(nxt, qf, sT, lane);      // tile jn = j + 1 sits in the next ring slot
-      const v2f scn = *(const v2f*)(nxt + PAIR + wave * 8);
       // (with SBIAS the accumulators hold B0 + s: the same order)
-      pm = tile_row_max<QSMOOTH, MASKED>(sT, cq * scn[0], (const float*)(nxt + BIAS_OFF + wave * 256), jn * kBlock, qlim, h);
+      pm = tile_row_max<QSMOOTH, MASKED>(sT, cq * scalar_load(sKh + jn), (const float*)(nxt + BIAS_OFF + wave * 256), jn * kBlock, qlim, h);
     };
     auto full_iter = [&](const int j, v16i (&sc)[2], v16i (&sn)[2]) __attribute__((always_inline)) {
       const bool issue = j + 3 < n_tiles;
-      if (issue) stage_load(j + 3, nx3);
-      const v2f sc2 = *(const v2f*)(cur + PAIR + wave * 8);
-      fwd_tile<D, QSMOOTH, false, true, SBIAS, KV128>(nxt, cur + TILE_BYTES, qf, sc, sn, oacc, w_bias, m_ref, l_part,
-                                        cq * sc2[0], sc2[1], (const float*)(cur + BIAS_OFF + wave * 256), j * kBlock, q, lane, h, &pm);
+      const float skn = scalar_load(sKh + j + 1), svn = scalar_load(sVh + j + 1);     // (j < last: tile j + 1 exists)
+      fwd_tile<D, QSMOOTH, false, true, SBIAS, KV128>([&](int k) __attribute__((always_inline)) { if (k < CPW && issue) copy_piece(j + 3, nx3, k); },
+                                        nxt, cur + TILE_BYTES, qf, sc, sn, oacc, w_bias, m_ref, l_part,
+                                        cq * sk, sv, (const float*)(cur + BIAS_OFF + wave * 256), j * kBlock, q, lane, h, &pm);
       if ((j & (kBiasPeriod - 1)) == kBiasPeriod - 1) unbias();
+      sk = skn;
+      sv = svn;
       end_iter(issue);
     };
     int j = 0;
@@ -497,10 +502,9 @@ __global__ void __launch_bounds__(64 * NW, (NW == 4 ? (D == 64 ? 3 : 2) : 1)) sa
     {
       const bool issue = j + 3 < n_tiles;
       if (issue) stage_load(j + 3, nx3);
-      const v2f sc2 = *(const v2f*)(cur + PAIR + wave * 8);
       // (the last tile always takes the masked path: without the causal mask it hides the keys past nvalid)
-      fwd_tile<D, QSMOOTH, true, false, SBIAS, KV128>(nxt, cur + TILE_BYTES, qf, sA, sB, oacc, w_bias, m_ref, l_part,
-                                        cq * sc2[0], sc2[1], (const float*)(cur + BIAS_OFF + wave * 256), j * kBlock, qlim, lane, h, &pm);
+      fwd_tile<D, QSMOOTH, true, false, SBIAS, KV128>([](int) {}, nxt, cur + TILE_BYTES, qf, sA, sB, oacc, w_bias, m_ref, l_part,
+                                        cq * sk, sv, (const float*)(cur + BIAS_OFF + wave * 256), j * kBlock, qlim, lane, h, &pm);
       end_iter(issue);
       j++;
     }
