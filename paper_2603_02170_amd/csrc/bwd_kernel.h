@@ -325,8 +325,9 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_kernel(BwdArgs args) {
   // One interval.  STEADY = all three phases are active and tile t is not on the diagonal: the
   // body is then free of branches, one basic block in which the compiler interleaves the three
   // independent phases (the LDS and MFMA latencies of one hide under the vector work of the others).
-  auto interval = [&](const int t, auto steady_tag) __attribute__((always_inline)) {
+  auto interval = [&](const int t, auto steady_tag, auto b_before_a_tag) __attribute__((always_inline)) {
     constexpr bool STEADY = decltype(steady_tag)::value;
+    constexpr bool B_BEFORE_A = decltype(b_before_a_tag)::value;
     const float sP_b = sP_q, sS_b = sS_q;      // scales of tile t - 2 (its phase Q ran in the last interval)
     const int ib = itop - ISTEP * (t - 2);     // Q blocks of the three tiles in flight
     const int iq = itop - ISTEP * (t - 1);
@@ -335,6 +336,50 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_kernel(BwdArgs args) {
     const bool act_q = STEADY || (t >= 1 && t - 1 < T && gvalid && (!CAUSAL || iq + sb >= j));
     const bool act_a = STEADY || (t < T && gvalid && (!CAUSAL || ia + sb >= j));
 
+    auto phase_b = [&]() __attribute__((always_inline)) {
+    // ---------------- phase B of tile t - 2: channel block cb ----------------
+    if (act_b) {
+      const BwdStageB<D>& st = stB[t & 1];
+      const BwdExchange& X = xch[grp][t & 1];
+      const float w_dv = sP_b * st.sc[1];
+      const float w_dk = sS_b * st.sc[0] * args.sm_scale;
+#pragma unroll
+      for (int tt = 0; tt < NPB; tt++) {
+        const int kbo = blk0 + tt;
+        v16i av, ak;
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+          av[r] = 0;
+          ak[r] = 0;
+        }
+#pragma unroll
+        for (int qs = 0; qs < 2; qs++) {
+          const v4i a1 = *(const v4i*)(st.dot + ((qs * KS + cb) * 64 + lane) * 16);
+          const v4i b1 = *(const v4i*)(X.pb + ((qs * 2 + kbo) * 64 + lane) * 16);
+          av = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, b1, av, 0, 0, 0);
+          const v4i a2 = *(const v4i*)(st.qt + ((qs * KS + cb) * 64 + lane) * 16);
+          const v4i b2 = *(const v4i*)(X.dsb + ((qs * 2 + kbo) * 64 + lane) * 16);
+          ak = __builtin_amdgcn_mfma_i32_32x32x32_i8(a2, b2, ak, 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+          dvacc[tt][r] = __builtin_fmaf((float)av[r], w_dv, dvacc[tt][r]);
+          dkacc[tt][r] = __builtin_fmaf((float)ak[r], w_dk, dkacc[tt][r]);
+        }
+        if constexpr (QSMOOTH) {
+          // dK_bias = (dS^T 1) mu_Q^T with the unquantised column sums of this tile
+          const float* cs2 = csum + ((grp * 3 + (t - 2) % 3) * 2) * 64;
+          const float csv = cs2[32 * kbo + ll] + cs2[64 + 32 * kbo + ll];
+#pragma unroll
+          for (int aa = 0; aa < 4; aa++) {
+            const v4f m4 = *(const v4f*)(st.muq + 32 * cb + 8 * aa + 4 * h);
+#pragma unroll
+            for (int b = 0; b < 4; b++) dkbias[tt][4 * aa + b] = __builtin_fmaf(csv, m4[b], dkbias[tt][4 * aa + b]);
+          }
+        }
+      }
+    }
+    };
     // operands of the coming intervals; the copies are issued in two batches so that the eight
     // waves do not queue up behind each other at the memory pipeline
     if (STEADY || t + 1 < T) load_A(ia - ISTEP, stA[(t + 1) & 1], std::false_type{});
@@ -437,6 +482,10 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_kernel(BwdArgs args) {
     }
 
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (B_BEFORE_A) {
+      phase_b();
+      __builtin_amdgcn_sched_barrier(0);
+    }
     // The two waves of a SIMD are wave w (first group) and w + 4 (second group); the arbiter favours the
     // older one, which then idles at the interval's barrier.  Raising the younger wave's priority for
     // its MFMA-dense phase evens the two out (measured: 2-3 % of the kernel).
@@ -512,48 +561,7 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_kernel(BwdArgs args) {
 
     __builtin_amdgcn_sched_barrier(0);
     if (STEADY) __builtin_amdgcn_s_setprio(0);
-    // ---------------- phase B of tile t - 2: channel block cb ----------------
-    if (act_b) {
-      const BwdStageB<D>& st = stB[t & 1];
-      const BwdExchange& X = xch[grp][t & 1];
-      const float w_dv = sP_b * st.sc[1];
-      const float w_dk = sS_b * st.sc[0] * args.sm_scale;
-#pragma unroll
-      for (int tt = 0; tt < NPB; tt++) {
-        const int kbo = blk0 + tt;
-        v16i av, ak;
-#pragma unroll
-        for (int r = 0; r < 16; r++) {
-          av[r] = 0;
-          ak[r] = 0;
-        }
-#pragma unroll
-        for (int qs = 0; qs < 2; qs++) {
-          const v4i a1 = *(const v4i*)(st.dot + ((qs * KS + cb) * 64 + lane) * 16);
-          const v4i b1 = *(const v4i*)(X.pb + ((qs * 2 + kbo) * 64 + lane) * 16);
-          av = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, b1, av, 0, 0, 0);
-          const v4i a2 = *(const v4i*)(st.qt + ((qs * KS + cb) * 64 + lane) * 16);
-          const v4i b2 = *(const v4i*)(X.dsb + ((qs * 2 + kbo) * 64 + lane) * 16);
-          ak = __builtin_amdgcn_mfma_i32_32x32x32_i8(a2, b2, ak, 0, 0, 0);
-        }
-#pragma unroll
-        for (int r = 0; r < 16; r++) {
-          dvacc[tt][r] = __builtin_fmaf((float)av[r], w_dv, dvacc[tt][r]);
-          dkacc[tt][r] = __builtin_fmaf((float)ak[r], w_dk, dkacc[tt][r]);
-        }
-        if constexpr (QSMOOTH) {
-          // dK_bias = (dS^T 1) mu_Q^T with the unquantised column sums of this tile
-          const float* cs2 = csum + ((grp * 3 + (t - 2) % 3) * 2) * 64;
-          const float csv = cs2[32 * kbo + ll] + cs2[64 + 32 * kbo + ll];
-#pragma unroll
-          for (int aa = 0; aa < 4; aa++) {
-            const v4f m4 = *(const v4f*)(st.muq + 32 * cb + 8 * aa + 4 * h);
-#pragma unroll
-            for (int b = 0; b < 4; b++) dkbias[tt][4 * aa + b] = __builtin_fmaf(csv, m4[b], dkbias[tt][4 * aa + b]);
-          }
-        }
-      }
-    }
+    if constexpr (!B_BEFORE_A) phase_b();
     barrier_all_memory();   // the interval's LDS traffic, copies and stores are complete
   };
   // steady intervals: t >= 2 (all three tiles exist), tile t above the diagonal and not the last row
@@ -561,9 +569,16 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_kernel(BwdArgs args) {
   // (under the mask: while Q block itop - ISTEP * t lies above the group's diagonal block j - sb)
   const int t_steady_end = (!gvalid || kvalid < 64) ? 0 : (CAUSAL ? min((itop + sb - j + ISTEP - 1) / ISTEP, T - 1) : T - 1);
   int t = 0;
-  for (; t < 2 && t < T + 2; t++) interval(t, std::false_type{});
-  for (; t < t_steady_end; t++) interval(t, std::true_type{});
-  for (; t < T + 2; t++) interval(t, std::false_type{});
+  for (; t < 2 && t < T + 2; t++) interval(t, std::false_type{}, std::false_type{});
+  // (the second group's waves take phase B before phase A: the two waves of a SIMD then do not reach the
+  // MFMA-dense phase at the same time.  Not with Q-smoothing, whose instantiation has no register to spare.)
+  using second_order = std::integral_constant<bool, !QSMOOTH>;
+  if (QSMOOTH || grp == 0) {
+    for (; t < t_steady_end; t++) interval(t, std::true_type{}, std::false_type{});
+  } else {
+    for (; t < t_steady_end; t++) interval(t, std::true_type{}, second_order{});
+  }
+  for (; t < T + 2; t++) interval(t, std::false_type{}, std::false_type{});
 
   if (!gvalid) return;
 
