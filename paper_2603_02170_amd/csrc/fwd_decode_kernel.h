@@ -1,0 +1,361 @@
+// Forward for at most 32 query rows per head that see every key (a decoding step against a cache).
+//
+// Such a call is bound by reading K and V: the products are nothing, and every key is used once, so
+// quantising K and V into a workspace and reading the codes back costs more than the rest together (two query
+// sequences of 32 heads against 8192 keys, d = 128: 109 us of pre-pass and 167 us of forward, the latter on 64
+// workgroups, where one pass over the 268 MB of K and V takes about 55 us at the rate of a large copy).  Here a
+// wave takes whole 64-key blocks straight from the caller's tensors: it loads a block of K in the order of
+// the F fragments, finds the block's scale, quantises in registers, forms the logits, and does the same with V,
+// whose fragments one MFMA against the identity turns from (lane = key) to (lane = channel), the operand form of
+// P^V^.  No LDS, no barrier and no traffic but K and V inside the loop.  The arithmetic is the pre-pass's and
+// sage_fwd_kernel's (FP32 decisions of psi included), so codes and scales are the same bits.
+//
+// Keys are split over waves (four to a workgroup, which meet in LDS) and workgroups (whose partial O, m, l a second
+// small kernel joins).
+#pragma once
+
+#include "common.h"
+#include "fwd_kernel.h"
+#include "prepass_kernels.h"
+
+namespace sage {
+
+struct DecodeArgs {
+  const unsigned short *Q, *K, *V;
+  RowView qview, kview;        // Q and O; K and V
+  const double* mean_part;     // K-smoothing: float64 column sums [BH, nchunk, D] or nullptr
+  int nchunk;
+  unsigned short* O;
+  float* LSE;                  // [BH, nq]
+  float* part;                 // partial O of every workgroup [BH, gridDim.x, 32, D] (rows < nq used), if more than one
+  v2f* part_ml;                // (m, l) [BH, gridDim.x, 32]
+  int nq, nk, nblk;            // query rows (<= 32), keys, key blocks
+  int blocks_per_wave;
+  float scale_log2e;
+};
+
+// psi of 16 values held as FP32: the rounding of prepass_quant_kernel (q = rne(x * r); |x * r| cannot exceed
+// 127 by more than an FP32 rounding step, so no clamp is needed), packed into four registers
+__device__ __forceinline__ v4i quantise_16(const float (&x)[16], const float r) {
+  v4i o;
+#pragma unroll
+  for (int w = 0; w < 4; w++) {
+    unsigned u[4];
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const float y = x[4 * w + e] * r;
+      u[e] = __float_as_uint(y + 12582912.0f);               // 1.5 * 2^23: rne(y) in the low mantissa bits
+    }
+    o[w] = (int)(__builtin_amdgcn_perm(u[1], u[0], 0x0c0c0400u) | __builtin_amdgcn_perm(u[3], u[2], 0x04000c0cu));
+  }
+  return o;
+}
+
+template <int D, bool KSMOOTH>
+__global__ void __launch_bounds__(256, 1) sage_fwd_decode_kernel(DecodeArgs args) {
+  constexpr int KS = D / 32;
+  __shared__ __attribute__((aligned(16))) float mu_s[D];
+  __shared__ __attribute__((aligned(16))) float xch[4 * KS * 4 * 64 * 4];    // partial O of the four waves
+  __shared__ v2f ml[4 * 32];
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int r32 = lane & 31, h = lane >> 5;
+  const int bh = blockIdx.y;
+
+  // this wave's fragments of a block: row 32 rb + r32, channels 32 s + 16 h .. + 16 (two 16-byte pieces)
+  struct Raw {
+    v8us v[2][KS][2];
+  };
+  auto load_block = [&](const unsigned short* src, const int j, Raw& x) __attribute__((always_inline)) {
+#pragma unroll
+    for (int rb = 0; rb < 2; rb++) {
+      const int row = min(64 * j + 32 * rb + r32, args.nk - 1);
+      const unsigned short* p = src + args.kview.row(bh, row) + 16 * h;
+#pragma unroll
+      for (int s = 0; s < KS; s++) {
+        x.v[rb][s][0] = *(const v8us*)(p + 32 * s);
+        x.v[rb][s][1] = *(const v8us*)(p + 32 * s + 8);
+      }
+    }
+  };
+  // values of one fragment (K: minus the mean), zero where the row does not exist
+  auto values = [&](const v8us (&raw)[2], const bool there, const float* mu, float (&x)[16]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 16; e++) x[e] = bf16_bits_to_float(raw[e >> 3][e & 7]);
+    if (mu != nullptr) {
+#pragma unroll
+      for (int w = 0; w < 4; w++) {
+        const v4f m = *(const v4f*)(mu + 4 * w);
+#pragma unroll
+        for (int e = 0; e < 4; e++) x[4 * w + e] = x[4 * w + e] - m[e];
+      }
+    }
+    if (!there) {
+#pragma unroll
+      for (int e = 0; e < 16; e++) x[e] = 0.f;
+    }
+  };
+  // codes of a block as F fragments; returns the block's scale
+  auto quantise_block = [&](const Raw& raw, const int j, const float* mu, v4i (&f)[2][KS]) __attribute__((always_inline)) {
+    float a = 0.f;
+#pragma unroll
+    for (int rb = 0; rb < 2; rb++) {
+      const bool there = 64 * j + 32 * rb + r32 < args.nk;
+#pragma unroll
+      for (int s = 0; s < KS; s++) {
+        float x[16];
+        values(raw.v[rb][s], there, mu == nullptr ? nullptr : mu + 32 * s + 16 * h, x);
+#pragma unroll
+        for (int e = 0; e < 16; e++) a = fmaxf(a, fabsf(x[e]));
+      }
+    }
+    a = wave_max_nonneg_f32(a);
+    const bool nz = a > 0.f;
+    const float r = nz ? 127.0f / a : 0.f;
+#pragma unroll
+    for (int rb = 0; rb < 2; rb++) {
+      const bool there = 64 * j + 32 * rb + r32 < args.nk;
+#pragma unroll
+      for (int s = 0; s < KS; s++) {
+        float x[16];
+        values(raw.v[rb][s], there, mu == nullptr ? nullptr : mu + 32 * s + 16 * h, x);
+        f[rb][s] = quantise_16(x, r);
+      }
+    }
+    return nz ? a / 127.0f : 0.f;
+  };
+
+  const int first = (blockIdx.x * 4 + wave) * args.blocks_per_wave;
+  const int end = min(first + args.blocks_per_wave, args.nblk);
+  Raw kr, vr;
+  load_block(args.K, min(first, args.nblk - 1), kr);
+  load_block(args.V, min(first, args.nblk - 1), vr);
+
+  // psi(Q): the rows of the one query block
+  v4i qf[KS];
+  float cq;
+  {
+    float a = 0.f;
+    v8us raw[KS][2];
+    const unsigned short* p = args.Q + args.qview.row(bh, min(r32, args.nq - 1)) + 16 * h;
+#pragma unroll
+    for (int s = 0; s < KS; s++) {
+      raw[s][0] = *(const v8us*)(p + 32 * s);
+      raw[s][1] = *(const v8us*)(p + 32 * s + 8);
+    }
+    const bool there = r32 < args.nq;
+#pragma unroll
+    for (int s = 0; s < KS; s++) {
+      float x[16];
+      values(raw[s], there, nullptr, x);
+#pragma unroll
+      for (int e = 0; e < 16; e++) a = fmaxf(a, fabsf(x[e]));
+    }
+    a = wave_max_nonneg_f32(a);
+    const bool nz = a > 0.f;
+    const float r = nz ? 127.0f / a : 0.f;
+#pragma unroll
+    for (int s = 0; s < KS; s++) {
+      float x[16];
+      values(raw[s], there, nullptr, x);
+      qf[s] = quantise_16(x, r);
+    }
+    cq = (nz ? a / 127.0f : 0.f) * args.scale_log2e;
+  }
+  if constexpr (KSMOOTH) {
+    // mu_K as prepass_quant_kernel forms it: chunk sums added in float64, divided by N, rounded once to FP32
+    if (t < D) {
+      double s = 0.0;
+      for (int k = 0; k < args.nchunk; k++) s += args.mean_part[((size_t)bh * args.nchunk + k) * D + t];
+      mu_s[t] = (float)(s / (double)args.nk);
+    }
+    __syncthreads();
+  }
+
+  // identity as the B operand of the transposing MFMA: lane (n, hh) holds k = 16 hh + t in byte t
+  v4i ident;
+#pragma unroll
+  for (int w = 0; w < 4; w++) {
+    unsigned u = 0;
+#pragma unroll
+    for (int e = 0; e < 4; e++) u |= (unsigned)((16 * h + 4 * w + e) == r32) << (8 * e);
+    ident[w] = (int)u;
+  }
+
+  float oacc[KS][16];
+#pragma unroll
+  for (int cb = 0; cb < KS; cb++)
+#pragma unroll
+    for (int r = 0; r < 16; r++) oacc[cb][r] = 0.f;
+  float w_bias = 0.f, m_ref = -INFINITY, l_part = 0.f;
+  auto unbias = [&]() __attribute__((always_inline)) {
+    const float corr = kBiasC0 * w_bias;
+#pragma unroll
+    for (int cb = 0; cb < KS; cb++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) oacc[cb][r] -= corr;
+    w_bias = 0.f;
+  };
+
+  for (int j = first; j < end; j++) {
+    v4i f[2][KS];
+    const float sk = quantise_block(kr, j, KSMOOTH ? mu_s : nullptr, f);
+    const int jn = min(j + 1, end - 1);
+    load_block(args.K, jn, kr);                              // the next block travels under this one's arithmetic
+    __builtin_amdgcn_sched_barrier(0);
+    v16i sacc[2];
+#pragma unroll
+    for (int kb = 0; kb < 2; kb++) {
+#pragma unroll
+      for (int r = 0; r < 16; r++) sacc[kb][r] = 0;
+#pragma unroll
+      for (int s = 0; s < KS; s++) sacc[kb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f[kb][s], qf[s], sacc[kb], 0, 0, 0);
+    }
+    const float c = cq * sk;
+    int mi[2] = {INT_MIN, INT_MIN};
+#pragma unroll
+    for (int kb = 0; kb < 2; kb++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) {
+        const int key = 64 * j + 32 * kb + 8 * (r >> 2) + 4 * h + (r & 3);
+        const int v = key < args.nk ? sacc[kb][r] : INT_MIN;
+        sacc[kb][r] = v;
+        mi[kb] = max(mi[kb], v);
+      }
+    const float mloc = (float)half_swap_max_i32(max(mi[0], mi[1])) * c;
+    if (__builtin_amdgcn_ballot_w64(mloc > m_ref + kTau) != 0) {
+      const float m_new = fmaxf(m_ref, mloc);
+      const float alpha = __builtin_amdgcn_exp2f(m_ref - m_new);
+      l_part *= alpha;
+      w_bias *= alpha;
+#pragma unroll
+      for (int cb = 0; cb < KS; cb++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) oacc[cb][r] *= alpha;
+      m_ref = m_new;
+    }
+    const float beta = __builtin_amdgcn_exp2f(mloc - m_ref);
+    const float off = kLog2_127 - mloc;
+    float psum[4] = {0.f, 0.f, 0.f, 0.f};
+    v4i pf[2];
+#pragma unroll
+    for (int kb = 0; kb < 2; kb++)
+#pragma unroll
+      for (int aa = 0; aa < 4; aa++) {
+        unsigned u = 0;
+#pragma unroll
+        for (int b = 0; b < 4; b++) {
+          const int v = sacc[kb][4 * aa + b];
+          const float xv = v == INT_MIN ? -INFINITY : __builtin_fmaf((float)v, c, off);
+          const float e = __builtin_amdgcn_exp2f(xv);
+          psum[b] += e;
+          u = __builtin_amdgcn_cvt_pk_u8_f32(e, b, u);
+        }
+        pf[kb][aa] = (int)u;
+      }
+    l_part = __builtin_fmaf(beta, (psum[0] + psum[1]) + (psum[2] + psum[3]), l_part);
+    __builtin_amdgcn_sched_barrier(0);
+    const float sv = quantise_block(vr, j, nullptr, f);
+    load_block(args.V, jn, vr);
+    __builtin_amdgcn_sched_barrier(0);
+    const float w = beta * sv * kTwo26;
+    w_bias += w;
+#pragma unroll
+    for (int cb = 0; cb < KS; cb++) {
+      v16i tt;
+#pragma unroll
+      for (int r = 0; r < 16; r++) tt[r] = kBiasBits;
+#pragma unroll
+      for (int kb = 0; kb < 2; kb++) {
+        v16i z;
+#pragma unroll
+        for (int r = 0; r < 16; r++) z[r] = 0;
+        const v16i tr = __builtin_amdgcn_mfma_i32_32x32x32_i8(f[kb][cb], ident, z, 0, 0, 0);
+        v4i va;
+#pragma unroll
+        for (int aa = 0; aa < 4; aa++)
+          va[aa] = (int)(__builtin_amdgcn_perm((unsigned)tr[4 * aa + 1], (unsigned)tr[4 * aa], 0x0c0c0400u) |
+                         __builtin_amdgcn_perm((unsigned)tr[4 * aa + 3], (unsigned)tr[4 * aa + 2], 0x04000c0cu));
+        tt = __builtin_amdgcn_mfma_i32_32x32x32_i8(va, pf[kb], tt, 0, 0, 0);
+      }
+#pragma unroll
+      for (int r = 0; r < 16; r++) oacc[cb][r] = __builtin_fmaf(__int_as_float(tt[r]), w, oacc[cb][r]);
+    }
+    if (((j - first) & (kBiasPeriod - 1)) == kBiasPeriod - 1) unbias();
+  }
+  unbias();
+
+  // ---- the four waves meet: wave s finishes channel block s ----
+  const float l_tot = half_swap_sum_f32(l_part);
+#pragma unroll
+  for (int cb = 0; cb < KS; cb++)
+#pragma unroll
+    for (int aa = 0; aa < 4; aa++)
+      *(v4f*)(xch + (((wave * KS + cb) * 4 + aa) * 64 + lane) * 4) =
+          v4f{oacc[cb][4 * aa], oacc[cb][4 * aa + 1], oacc[cb][4 * aa + 2], oacc[cb][4 * aa + 3]};
+  if (h == 0) ml[wave * 32 + r32] = v2f{m_ref, l_tot};
+  __syncthreads();
+  if (r32 >= args.nq) return;
+  v2f mls[4];
+  float m = -INFINITY;
+#pragma unroll
+  for (int s = 0; s < 4; s++) {
+    mls[s] = ml[s * 32 + r32];
+    m = fmaxf(m, mls[s][0]);
+  }
+  float l = 0.f, wgt[4];
+#pragma unroll
+  for (int s = 0; s < 4; s++) {
+    wgt[s] = __builtin_amdgcn_exp2f(mls[s][0] - m);          // 0 for a wave without blocks (the first wave always has one)
+    l = __builtin_fmaf(mls[s][1], wgt[s], l);
+  }
+  const bool whole = gridDim.x == 1;
+  const float inv_l = 1.0f / l;
+  if (wave < KS) {
+#pragma unroll
+    for (int aa = 0; aa < 4; aa++) {
+      v4f o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < 4; s++) {
+        const v4f x = *(const v4f*)(xch + (((s * KS + wave) * 4 + aa) * 64 + lane) * 4);
+#pragma unroll
+        for (int e = 0; e < 4; e++) o[e] = __builtin_fmaf(x[e], wgt[s], o[e]);
+      }
+      const int ch = 32 * wave + 8 * aa + 4 * h;
+      if (whole) {
+        v4us ob;
+#pragma unroll
+        for (int e = 0; e < 4; e++) ob[e] = float_to_bf16_bits(o[e] * inv_l);
+        *(v4us*)(args.O + args.qview.row(bh, r32) + ch) = ob;
+      } else {
+        *(v4f*)(args.part + (((size_t)bh * gridDim.x + blockIdx.x) * 32 + r32) * D + ch) = o;
+      }
+    }
+  }
+  if (wave == 0 && h == 0) {
+    if (whole) args.LSE[(size_t)bh * args.nq + r32] = (m + __builtin_amdgcn_logf(l) - kLog2_127) * kLn2;
+    else args.part_ml[((size_t)bh * gridDim.x + blockIdx.x) * 32 + r32] = v2f{m, l};
+  }
+}
+
+// Joins the workgroups' partial (O, m, l): one workgroup of D threads per (query, head).
+template <int D>
+__global__ void __launch_bounds__(D) sage_fwd_decode_join_kernel(DecodeArgs args, int nsplit) {
+  const int q = blockIdx.x, bh = blockIdx.y, ch = threadIdx.x;
+  const v2f* ml = args.part_ml + (size_t)bh * nsplit * 32 + q;
+  const float* part = args.part + ((size_t)bh * nsplit * 32 + q) * D + ch;
+  float m = -INFINITY;
+  for (int s = 0; s < nsplit; s++) m = fmaxf(m, ml[(size_t)s * 32][0]);
+  float l = 0.f, o = 0.f;
+#pragma unroll 4
+  for (int s = 0; s < nsplit; s++) {
+    const v2f e = ml[(size_t)s * 32];
+    const float w = __builtin_amdgcn_exp2f(e[0] - m);
+    l = __builtin_fmaf(e[1], w, l);
+    o = __builtin_fmaf(part[(size_t)s * 32 * D], w, o);
+  }
+  args.O[args.qview.row(bh, q) + ch] = float_to_bf16_bits(o * (1.0f / l));
+  if (ch == 0) args.LSE[(size_t)bh * args.nq + q] = (m + __builtin_amdgcn_logf(l) - kLog2_127) * kLn2;
+}
+
+}  // namespace sage

@@ -119,7 +119,7 @@ struct PairMax {
 template <int D, bool QSMOOTH, bool MASK, bool NEXT, bool SBIAS, bool KV128 = false, class Copy>
 __device__ __forceinline__ void fwd_tile(const Copy& copy, const int8_t* __restrict__ Knext, const int8_t* __restrict__ Vt,
                                          const v4i (&qf)[D / 32], v16i (&sacc)[2], v16i (&snext)[2],
-                                         float (&oacc)[D / 32][16], float& w_bias, float& m_ref, float& l_part,
+                                         float (&oacc)[D / 32][16], float& w_bias, float& m_ref, float (&l_part)[2],
                                          const float c, const float sv, const float* __restrict__ bias_row,
                                          const int k0, const int q, const int lane, const int h,
                                          PairMax* pair = nullptr) {
@@ -190,7 +190,8 @@ __device__ __forceinline__ void fwd_tile(const Copy& copy, const int8_t* __restr
   if (__builtin_amdgcn_ballot_w64(mloc > m_ref + kTau) != 0) {
     const float m_new = fmaxf(m_ref, mloc);
     const float alpha = __builtin_amdgcn_exp2f(m_ref - m_new);   // 0 on the first tile
-    l_part *= alpha;
+    l_part[0] *= alpha;
+    l_part[1] *= alpha;
     w_bias *= alpha;
 #pragma unroll
     for (int cb = 0; cb < KS; cb++)
@@ -276,11 +277,16 @@ __device__ __forceinline__ void fwd_tile(const Copy& copy, const int8_t* __restr
         u = __builtin_amdgcn_cvt_pk_u8_f32(e, b, u);
       }
       pf[kb][aa] = (int)u;
+      if (aa == 3) {
+        // (one sum per key block, which meet at the end: sage_fwd_pair_kernel has them in two waves)
+        l_part[kb] = __builtin_fmaf(beta, (psum[0] + psum[1]) + (psum[2] + psum[3]), l_part[kb]);
+        pin(l_part[kb]);
+#pragma unroll
+        for (int b = 0; b < 4; b++) psum[b] = 0.f;
+      }
     } else if (sl == 8) {
-      l_part = __builtin_fmaf(beta, (psum[0] + psum[1]) + (psum[2] + psum[3]), l_part);
       w = beta * sv * kTwo26;
       w_bias += w;
-      pin(l_part);
       pin(w);
       pin(w_bias);
     } else if (sl >= 10) {
@@ -383,7 +389,7 @@ __global__ void __launch_bounds__(64 * NW, (NW == 4 ? (D == 64 ? 3 : 2) : 1)) sa
     for (int r = 0; r < 16; r++) oacc[cb][r] = 0.f;
   float w_bias = 0.f;        // sum of the tile weights since the last bias subtraction (see the header)
   float m_ref = -INFINITY;   // log2 domain
-  float l_part = 0.f;        // this lane's share of sum(127 p) relative to m_ref
+  float l_part[2] = {0.f, 0.f};   // this lane's share of sum(127 p) relative to m_ref, per 32-key block of the tiles
 
   // Asynchronous copy of tile j (K^ fragments, then V^ fragments) into a ring slot; the
   // 1 KiB fragments are dealt round-robin to the waves.
@@ -451,7 +457,7 @@ __global__ void __launch_bounds__(64 * NW, (NW == 4 ? (D == 64 ? 3 : 2) : 1)) sa
   bool use_sbias = false;
   if constexpr (!QSMOOTH) {
     float smax = 0.f;
-    for (int jj = lane; jj < n_tiles; jj += 64) smax = fmaxf(smax, sKh[jj]);
+    for (int jj = lane; jj <= last; jj += 64) smax = fmaxf(smax, sKh[jj]);
     use_sbias = cq * wave_max_nonneg_f32(smax) < 1e-3f;
   }
   auto run = [&](auto sbias_tag) __attribute__((always_inline)) {
@@ -515,7 +521,7 @@ __global__ void __launch_bounds__(64 * NW, (NW == 4 ? (D == 64 ? 3 : 2) : 1)) sa
     }
     unbias();
     // ---- epilogue: O = O / l, L = m + log(l) (l carries a factor 127) ----
-    const float l_tot = half_swap_sum_f32(l_part);
+    const float l_tot = half_swap_sum_f32(l_part[0]) + half_swap_sum_f32(l_part[1]);
     const float inv_l = 1.0f / l_tot;
     if (q >= args.nq_valid) return;                    // a query row that does not exist
     unsigned short* Oh = args.O + args.oview.row(bh, q);
@@ -534,6 +540,585 @@ __global__ void __launch_bounds__(64 * NW, (NW == 4 ? (D == 64 ? 3 : 2) : 1)) sa
   // (each path runs to the end of the kernel, so that no register state has to be merged)
   if (__builtin_amdgcn_readfirstlane((int)use_sbias)) run(std::true_type{});
   else run(std::false_type{});
+}
+
+// ---- two waves per 32 queries ------------------------------------------------------------------------
+// sage_fwd_pair_kernel: the forward for calls that do not fill the machine (numerics blocks of 64 keys).  A
+// workgroup owns 32 * NQ queries and has 2 * NQ waves: wave (query group qw, half kb) takes the 32-key block kb
+// of every tile for the logits and the softmax, and half of the channels for O.  What the two waves of a query
+// group owe each other, the row max of their half tile and the P^ codes of it, goes through LDS,
+// software-pipelined over one barrier per tile: interval t finishes the softmax of tile t, adds tile t - 1 to O
+// and forms S of tile t + 1 with its half row max, so each finds the other wave's part of the interval before.
+//
+// Such calls take the time of one wave's chain of tiles: sage_fwd_kernel needs about 2450 cycles a tile with one
+// wave per SIMD, most of them the wave's own instruction issue (one vector instruction in about 4.8 cycles),
+// and half a tile takes little more than half of that.  The arithmetic of every value and its order are those of
+// sage_fwd_kernel, so both give the same bits and the choice may depend on how full the machine is.  (With
+// 128 registers, four waves per SIMD, this form was tried for full machines too: 925 us against 756 at
+// the headline shape.)
+template <int D, bool CAUSAL, bool QSMOOTH, int NQ>
+__global__ void __launch_bounds__(128 * NQ, 2) sage_fwd_pair_kernel(FwdArgs args) {
+  constexpr int KS = D / 32;
+  constexpr int CBW = KS / 2;                                  // channel blocks of O per wave
+  constexpr int NW = 2 * NQ;
+  constexpr int TILE_BYTES = 64 * D;
+  constexpr int PAIR = 2 * TILE_BYTES;
+  constexpr int NFRAG = PAIR / 1024;
+  constexpr int NBR = (NQ + 1) / 2;                            // Q blocks of the workgroup = bias rows
+  constexpr int SLOT = PAIR + (QSMOOTH ? NBR * 256 : 0);
+  constexpr int R = 3;
+  constexpr int CPW = NFRAG / NW + (QSMOOTH ? 1 : 0);          // copies per wave and slot
+  static_assert(NFRAG % NW == 0, "every wave must issue the same number of copies");
+  // (one LDS object: reads of a second one, which no asynchronous copy writes, would be made to wait for the copies in flight)
+  struct Lds {
+    int8_t ring[R * SLOT];                                     // slot p: K^ of tile p + 2 | V^ of tile p | biases of tile p + 2
+    int8_t pxch[2][NQ][2][1024];                               // [tile parity][query group][key block]: P^ as B operand
+    float mxch[2][NQ][2][32];                                  // [tile parity][query group][key block][query]: half row max (bits)
+  };
+  __shared__ __attribute__((aligned(16))) Lds L;
+  auto& ring = L.ring;
+  auto& pxch = L.pxch;
+  auto& mxch = L.mxch;
+
+  const WorkItem wi = work_item(blockIdx.x, args.n_qtiles, args.head_set);
+  const int bh = wi.head;
+  if (bh >= args.BH) return;
+  const int qt = args.n_qtiles - 1 - wi.item;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qw = wave >> 1, kb = wave & 1;
+  const int ql = lane & 31, h = lane >> 5;
+  const int N = args.N;
+  const int q0 = (qt * NQ + qw) * 32;
+  const int q = q0 + ql;
+  const bool there = q0 < args.Nq;                             // (the last workgroup may reach past the last block)
+  const int qlim = CAUSAL ? q + args.shift : args.nvalid - 1;
+  const int nblk = N / kBlock;
+  const int nqblk = args.Nq / kBlock;
+  const int qblk = there ? q0 / kBlock : nqblk - 1;
+
+  const int8_t* KFh = args.KF + (size_t)bh * N * D;
+  const int8_t* VTh = args.VT + (size_t)bh * N * D;
+  const float* sKh = args.sK + (size_t)bh * nblk;
+  const float* sVh = args.sV + (size_t)bh * nblk;
+  const int n_tiles = CAUSAL ? min((qt * NQ * 32 + NQ * 32 + args.shift + kBlock - 1) / kBlock, nblk) : nblk;
+  const int last = !there ? -1 : (CAUSAL ? (q0 + 31 + args.shift) / kBlock : nblk - 1);   // this wave's last tile
+
+  // copies of slot p (K^ of tile p + 2, V^ of tile p; clamped where there is no such tile: never read)
+  auto copy_piece = [&](int p, int8_t* dst, int k) __attribute__((always_inline)) {
+    if (k < NFRAG / NW) {
+      const int o = wave + NW * k;                             // wave-uniform
+      const int8_t* src = o < NFRAG / 2 ? KFh + (size_t)min(p + 2, nblk - 1) * TILE_BYTES + o * 1024
+                                        : VTh + (size_t)max(p, 0) * TILE_BYTES + (o - NFRAG / 2) * 1024;
+      async_copy_16(src + lane * 16, dst + o * 1024);
+    } else if (QSMOOTH && k == NFRAG / NW) {
+      // (every wave copies a row, so that all issue the same number: NBR rows, several waves each)
+      const int row = wave % NBR;
+      const int qb = min(qt * NBR + row, nqblk - 1);
+      async_copy_4(args.bias + ((size_t)bh * nqblk + qb) * N + min(p + 2, nblk - 1) * kBlock + lane, dst + PAIR + row * 256);
+    }
+  };
+  int8_t* rd = ring;                                           // slot t - 1
+  int8_t* mid = ring + SLOT;                                   // slot t
+  int8_t* wr = ring + 2 * SLOT;                                // slot t + 1
+#pragma unroll
+  for (int k = 0; k < CPW; k++) copy_piece(-1, rd, k);
+#pragma unroll
+  for (int k = 0; k < CPW; k++) copy_piece(0, mid, k);
+
+  v4i qf[KS];
+  {
+    const int8_t* p = args.QF + (size_t)bh * args.Nq * D + (size_t)(there ? q0 / 32 : 0) * KS * 1024 + lane * 16;
+#pragma unroll
+    for (int s = 0; s < KS; s++) qf[s] = *(const v4i*)(p + s * 1024);
+  }
+  const float cq = args.sQ[(size_t)bh * nqblk + qblk] * args.scale_log2e;
+
+  float oacc[CBW][16];
+#pragma unroll
+  for (int cb = 0; cb < CBW; cb++)
+#pragma unroll
+    for (int r = 0; r < 16; r++) oacc[cb][r] = 0.f;
+  float w_bias = 0.f, m_ref = -INFINITY, l_part = 0.f, w_prev = 0.f;
+
+  bool use_sbias = false;
+  if constexpr (!QSMOOTH) {
+    float smax = 0.f;
+    for (int jj = lane; jj <= last; jj += 64) smax = fmaxf(smax, sKh[jj]);
+    use_sbias = cq * wave_max_nonneg_f32(smax) < 1e-3f;
+  }
+  auto run = [&](auto sbias_tag) __attribute__((always_inline)) {
+    constexpr bool SBIAS = decltype(sbias_tag)::value;
+    float mown = 0.f;          // half row max of the tile in hand (bits)
+
+    // half row max of tile j (logits s; with Q-smoothing they become floats in the log2 domain), into LDS
+    auto half_max = [&](v16i& s, const int j, const float c, const float* bias_row, auto mask_tag) __attribute__((always_inline)) {
+      constexpr bool MASK = decltype(mask_tag)::value;
+      if constexpr (!QSMOOTH) {
+        int m[2] = {INT_MIN, INT_MIN};
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+          int v = s[r];
+          if constexpr (MASK) {
+            const int key = j * kBlock + 32 * kb + 8 * (r >> 2) + 4 * h + (r & 3);
+            v = key > qlim ? INT_MIN : v;
+            s[r] = v;
+          }
+          m[r >> 3] = max(m[r >> 3], v);
+        }
+        mown = __int_as_float(half_swap_max_i32(max(m[0], m[1])));
+      } else {
+        float m[2] = {-INFINITY, -INFINITY};
+#pragma unroll
+        for (int aa = 0; aa < 4; aa++) {
+          const v4f b4 = *(const v4f*)(bias_row + 32 * kb + 8 * aa + 4 * h);
+#pragma unroll
+          for (int b = 0; b < 4; b++) {
+            float v = __builtin_fmaf((float)s[4 * aa + b], c, b4[b]);
+            if constexpr (MASK) {
+              const int key = j * kBlock + 32 * kb + 8 * aa + 4 * h + b;
+              v = key > qlim ? -INFINITY : v;
+            }
+            s[4 * aa + b] = __float_as_int(v);
+            m[b & 1] = fmaxf(m[b & 1], v);
+          }
+        }
+        mown = half_swap_max_f32(fmaxf(m[0], m[1]));
+      }
+      mxch[j & 1][qw][kb][ql] = mown;
+    };
+    auto unbias = [&]() __attribute__((always_inline)) {
+      const float corr = kBiasC0 * w_bias;
+#pragma unroll
+      for (int cb = 0; cb < CBW; cb++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) oacc[cb][r] -= corr;
+      w_bias = 0.f;
+    };
+    // One interval.  PV / SM / SN: tile t - 1 is added to O, tile t quantised, the logits of tile t + 1 formed.  The
+    // vector work of the softmax runs over the matrix work of the other two (P^ does not depend on the running
+    // reference); the reference, which scales O, moves after tile t - 1 has been added, as in sage_fwd_kernel.
+    auto interval = [&](const int t, const bool issue, const float c, const float sv, const float cn, v16i& s, v16i& sn, auto pv_tag,
+                        auto sm_tag, auto sn_tag, auto mask_tag) __attribute__((always_inline)) {
+      constexpr bool PV = decltype(pv_tag)::value, SM = decltype(sm_tag)::value, SN = decltype(sn_tag)::value;
+      constexpr bool MASK = decltype(mask_tag)::value;
+      const int8_t* kl = rd + kb * KS * 1024 + lane * 16;
+      const int8_t* vl = rd + TILE_BYTES + kb * CBW * 1024 + lane * 16;
+      float mother = 0.f;
+      v4i ka[KS], va[2][CBW], p[2];
+      if constexpr (SM) mother = mxch[t & 1][qw][kb ^ 1][ql];
+      if constexpr (PV) {
+#pragma unroll
+        for (int k = 0; k < 2; k++) {
+          p[k] = *(const v4i*)(&pxch[(t - 1) & 1][qw][k][lane * 16]);
+#pragma unroll
+          for (int cb = 0; cb < CBW; cb++) va[k][cb] = *(const v4i*)(vl + (k * KS + cb) * 1024);
+        }
+      }
+      if constexpr (SN) {
+#pragma unroll
+        for (int k = 0; k < KS; k++) ka[k] = *(const v4i*)(kl + k * 1024);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      float mloc = 0.f, c_eff = 0.f, off = 0.f;
+      if constexpr (SM) {
+        float bmax_f = 0.f;
+        if constexpr (!QSMOOTH) {
+          const int mrow = max(__float_as_int(mown), __float_as_int(mother));
+          mloc = (float)(mrow - (SBIAS ? kBiasBits : 0)) * c;
+          if constexpr (SBIAS) bmax_f = __int_as_float(mrow);
+        } else {
+          mloc = fmaxf(mown, mother);
+        }
+        c_eff = SBIAS ? c * kTwo26 : c;
+        off = SBIAS ? __builtin_fmaf(-bmax_f, c_eff, kLog2_127) : kLog2_127 - mloc;
+      }
+      v16i tt[CBW];
+      float psum[4] = {0.f, 0.f, 0.f, 0.f};
+      v4i pf;
+#pragma unroll
+      for (int sl = 0; sl < 5; sl++) {
+        // matrix work, one slot behind the vector work (the LDS reads of the operands are under way until then): one
+        // step of S (D / 32 of them), one MFMA of P^V^ (2 * CBW)
+        if constexpr (SN) {
+          const int aa = sl - 1;
+          if (aa >= 0 && aa < KS) {
+            if (aa == 0) {
+              v16i z;
+#pragma unroll
+              for (int r = 0; r < 16; r++) z[r] = SBIAS ? kBiasBits : 0;
+              sn = __builtin_amdgcn_mfma_i32_32x32x32_i8(ka[0], qf[0], z, 0, 0, 0);
+            } else {
+              sn = __builtin_amdgcn_mfma_i32_32x32x32_i8(ka[aa], qf[aa], sn, 0, 0, 0);
+            }
+          }
+        }
+        if constexpr (PV) {
+          const int aa = sl - 1;
+          if (aa >= 0 && aa < 2 * CBW) {
+            const int k = aa / CBW, cb = aa % CBW;
+            if (k == 0) {
+              v16i b0;
+#pragma unroll
+              for (int r = 0; r < 16; r++) b0[r] = kBiasBits;
+              tt[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(va[0][cb], p[0], b0, 0, 0, 0);
+            } else {
+              tt[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(va[1][cb], p[1], tt[cb], 0, 0, 0);
+            }
+          }
+        }
+        if (sl < CPW && issue) copy_piece(t + 1, wr, sl);
+        if (SM && sl < 4) {
+          const int aa = sl;
+          unsigned u = 0;
+#pragma unroll
+          for (int b = 0; b < 4; b++) {
+            float xv;
+            if constexpr (!QSMOOTH) {
+              if constexpr (SBIAS) xv = __builtin_fmaf(__int_as_float(s[4 * aa + b]), c_eff, off);
+              else xv = __builtin_fmaf((float)s[4 * aa + b], c, off);
+              if constexpr (MASK) xv = s[4 * aa + b] == INT_MIN ? -INFINITY : xv;
+            } else {
+              xv = __int_as_float(s[4 * aa + b]) + off;
+            }
+            const float e = __builtin_amdgcn_exp2f(xv);
+            psum[b] += e;
+            pin(psum[b]);
+            u = __builtin_amdgcn_cvt_pk_u8_f32(e, b, u);
+          }
+          pf[aa] = (int)u;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int k = 5; k < CPW; k++)
+        if (issue) copy_piece(t + 1, wr, k);
+      if constexpr (SM) *(v4i*)(&pxch[t & 1][qw][kb][lane * 16]) = pf;
+      if constexpr (PV) {
+#pragma unroll
+        for (int cb = 0; cb < CBW; cb++)
+#pragma unroll
+          for (int r = 0; r < 16; r++) oacc[cb][r] = __builtin_fmaf(__int_as_float(tt[cb][r]), w_prev, oacc[cb][r]);
+        if (((t - 1) & (kBiasPeriod - 1)) == kBiasPeriod - 1) unbias();
+      }
+      if constexpr (SM) {
+        if (__builtin_amdgcn_ballot_w64(mloc > m_ref + kTau) != 0) {
+          const float m_new = fmaxf(m_ref, mloc);
+          const float alpha = __builtin_amdgcn_exp2f(m_ref - m_new);   // 0 on the first tile
+          l_part *= alpha;
+          w_bias *= alpha;
+#pragma unroll
+          for (int cb = 0; cb < CBW; cb++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) oacc[cb][r] *= alpha;
+          m_ref = m_new;
+        }
+        const float beta = __builtin_amdgcn_exp2f(mloc - m_ref);
+        l_part = __builtin_fmaf(beta, (psum[0] + psum[1]) + (psum[2] + psum[3]), l_part);
+        w_prev = beta * sv * kTwo26;
+        w_bias += w_prev;
+      }
+      if constexpr (SN) half_max(sn, t + 1, cn, (const float*)(rd + PAIR + (qw >> 1) * 256), mask_tag);
+      // the copies of slot t (issued one interval ago) have landed; this interval's stay in flight
+      if (issue) {
+        __builtin_amdgcn_s_waitcnt(vmcnt_only(CPW));
+        barrier_lds_only();
+      } else {
+        barrier_all_memory();
+      }
+      int8_t* x = rd;
+      rd = mid;
+      mid = wr;
+      wr = x;
+    };
+    using T = std::true_type;
+    using F = std::false_type;
+
+    // tile 0: logits straight from memory
+    v16i sA, sB;
+    float sk = scalar_load(sKh), sv = scalar_load(sVh);
+#pragma unroll
+    for (int r = 0; r < 16; r++) sA[r] = SBIAS ? kBiasBits : 0;
+#pragma unroll
+    for (int k = 0; k < KS; k++)
+      sA = __builtin_amdgcn_mfma_i32_32x32x32_i8(*(const v4i*)(KFh + (kb * KS + k) * 1024 + lane * 16), qf[k], sA, 0, 0, 0);
+    half_max(sA, 0, cq * sk, QSMOOTH ? args.bias + ((size_t)bh * nqblk + qblk) * N : nullptr, T{});
+    barrier_all_memory();
+
+    // interval t with the scales of tiles t (sk, sv) and t + 1 (fetched one interval ahead of their use)
+    auto step = [&](const int t, v16i& s, v16i& sn, auto pv_tag, auto sm_tag, auto sn_tag, auto mask_tag) __attribute__((always_inline)) {
+      const int jn = min(t + 1, nblk - 1);
+      const float skn = scalar_load(sKh + jn), svn = scalar_load(sVh + jn);
+      interval(t, t + 1 < n_tiles, cq * sk, sv, cq * skn, s, sn, pv_tag, sm_tag, sn_tag, mask_tag);
+      sk = skn;
+      sv = svn;
+    };
+    // (the masked forms leave visible keys as they are; a wave whose tiles are done keeps the ring moving)
+    int t = 0;
+    if (last >= 1) {
+      step(t++, sA, sB, F{}, T{}, T{}, T{});
+      for (; t + 2 < last; t += 2) {
+        step(t, sB, sA, T{}, T{}, T{}, F{});
+        step(t + 1, sA, sB, T{}, T{}, T{}, F{});
+      }
+      for (; t < last; t++) {
+        step(t, sB, sA, T{}, T{}, T{}, T{});
+        sB = sA;
+      }
+      step(t++, sB, sA, T{}, T{}, F{}, T{});
+      step(t++, sB, sA, T{}, F{}, F{}, F{});
+    } else if (last == 0) {
+      step(t++, sA, sB, F{}, T{}, F{}, T{});
+      step(t++, sA, sB, T{}, F{}, F{}, F{});
+    }
+    for (; t <= n_tiles; t++) step(t, sA, sB, F{}, F{}, F{}, F{});
+    unbias();
+  };
+  if (__builtin_amdgcn_readfirstlane((int)use_sbias)) run(std::true_type{});
+  else run(std::false_type{});
+
+  // ---- epilogue: O = O / l, L = m + log(l) (l carries a factor 127); the two halves of l meet in LDS ----
+  mxch[0][qw][kb][ql] = half_swap_sum_f32(l_part);
+  barrier_lds_only();
+  if (q >= args.nq_valid) return;                              // a query row that does not exist
+  const float l_tot = mxch[0][qw][0][ql] + mxch[0][qw][1][ql];
+  const float inv_l = 1.0f / l_tot;
+  unsigned short* Oh = args.O + args.oview.row(bh, q);
+#pragma unroll
+  for (int cb = 0; cb < CBW; cb++)
+#pragma unroll
+    for (int aa = 0; aa < 4; aa++) {
+      v4us o;
+#pragma unroll
+      for (int b = 0; b < 4; b++) o[b] = float_to_bf16_bits(oacc[cb][4 * aa + b] * inv_l);
+      *(v4us*)(Oh + 32 * (kb * CBW + cb) + 8 * aa + 4 * h) = o;
+    }
+  if (kb == 0 && h == 0) args.LSE[(size_t)bh * args.nq_valid + q] = (m_ref + __builtin_amdgcn_logf(l_tot) - kLog2_127) * kLn2;
+}
+
+// ---- few query rows against many keys ----------------------------------------------------------------
+// A workgroup of 8 waves = NQ groups of 32 queries x NS splits of the keys.  Every wave walks its own
+// contiguous range of the workgroup's KV tiles with the arithmetic of sage_fwd_kernel; the partial (O, m, l)
+// of the splits meet in LDS at the end, each split finishing a share of the channels.
+//
+// Where the queries alone do not fill the machine (chunked prefill, cross attention), the time is one wave's chain
+// of tiles, about 1.1 us each; splitting the keys shortens it NS times and puts two waves on every SIMD.  512
+// queries x 32 heads against 4096 keys, d = 128: 70 -> 36 us.  (On a full machine the merge and
+// the barrier over 8 waves cost 20 to 50 %.)  The order of the sums differs from sage_fwd_kernel's, which
+// is why square attention does not come here: a head of it gets the same bits alone and in any batch.
+//
+// Slot p of a split's ring holds K^ of its tile p + 1 and V^ of its tile p (what iteration p reads: the logits
+// of the next tile are formed under the softmax of this one); K^ of the first tile comes straight from memory.
+template <int D, bool CAUSAL, bool QSMOOTH, int NQ, int NS>
+__global__ void __launch_bounds__(512, 1) sage_fwd_split_kernel(FwdArgs args) {
+  constexpr int KS = D / 32;
+  constexpr int TILE_BYTES = 64 * D;
+  constexpr int PAIR = 2 * TILE_BYTES;
+  constexpr int NFRAG = PAIR / 1024;
+  constexpr int SLOT = PAIR + (QSMOOTH ? NQ * 256 : 0);
+  constexpr int R = NS * 4 * PAIR <= 128 * 1024 ? 4 : 2;       // ring slots per split
+  constexpr int CPW = NFRAG / NQ + (QSMOOTH ? 1 : 0);
+  static_assert(NQ * NS == 8 && NFRAG % NQ == 0, "8 waves, the same number of copies for each");
+  constexpr int RING = NS * R * SLOT;
+  constexpr int XCH = NQ * NS * KS * 4096;                     // partial O of every wave: [q][split][channel block] x 4 KiB
+  __shared__ __attribute__((aligned(16))) int8_t lds[RING > XCH ? RING : XCH];
+  __shared__ v2f ml[NQ * NS * 32];                             // (m, l) of every wave and query
+
+  const WorkItem wi = work_item(blockIdx.x, args.n_qtiles, args.head_set);
+  const int bh = wi.head;
+  if (bh >= args.BH) return;
+  const int qt = args.n_qtiles - 1 - wi.item;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qw = wave % NQ, g = wave / NQ;
+  const int ql = lane & 31, h = lane >> 5;
+  const int N = args.N;
+  const int q0 = (qt * NQ + qw) * 32;
+  const int q = q0 + ql;
+  const bool there = q0 < args.Nq;                             // (the last workgroup may reach past the last block)
+  const int qlim = CAUSAL ? q + args.shift : args.nvalid - 1;
+  const int nblk = N / kBlock;
+  const int nqblk = args.Nq / kBlock;
+  const int qblk = there ? q0 / kBlock : nqblk - 1;
+
+  const int8_t* KFh = args.KF + (size_t)bh * N * D;
+  const int8_t* VTh = args.VT + (size_t)bh * N * D;
+  const float* sKh = args.sK + (size_t)bh * nblk;
+  const float* sVh = args.sV + (size_t)bh * nblk;
+
+  // this workgroup's tiles, this split's share [a, b) of them, this wave's last tile
+  const int n_tiles = CAUSAL ? min((qt * NQ * 32 + NQ * 32 + args.shift + kBlock - 1) / kBlock, nblk) : nblk;
+  const int share = (n_tiles + NS - 1) / NS;
+  const int a = g * share, b = min(n_tiles, a + share), cnt = max(b - a, 0);
+  const int last = !there ? -1 : (CAUSAL ? min((q0 + 31 + args.shift) / kBlock, b - 1) : b - 1);
+  const int ac = min(a, nblk - 1);                             // (a split without tiles still reads in bounds)
+
+  v4i qf[KS];
+  {
+    const int8_t* p = args.QF + (size_t)bh * args.Nq * D + (size_t)(there ? q0 / 32 : 0) * KS * 1024 + lane * 16;
+#pragma unroll
+    for (int s = 0; s < KS; s++) qf[s] = *(const v4i*)(p + s * 1024);
+  }
+  const float cq = args.sQ[(size_t)bh * nqblk + qblk] * args.scale_log2e;
+  const float* bias_row = QSMOOTH ? args.bias + ((size_t)bh * nqblk + qblk) * N : nullptr;
+
+  float oacc[KS][16];
+#pragma unroll
+  for (int cb = 0; cb < KS; cb++)
+#pragma unroll
+    for (int r = 0; r < 16; r++) oacc[cb][r] = 0.f;
+  float w_bias = 0.f, m_ref = -INFINITY, l_part[2] = {0.f, 0.f};
+
+  int8_t* ring = lds + g * R * SLOT;
+  auto copy_piece = [&](int p, int k) __attribute__((always_inline)) {
+    int8_t* dst = ring + (p % R) * SLOT;
+    const int o = qw + NQ * k;
+    if (k < NFRAG / NQ) {
+      const int8_t* src = o < NFRAG / 2 ? KFh + (size_t)min(a + p + 1, nblk - 1) * TILE_BYTES + o * 1024
+                                        : VTh + (size_t)(a + p) * TILE_BYTES + (o - NFRAG / 2) * 1024;
+      async_copy_16(src + lane * 16, dst + o * 1024);
+    } else if (QSMOOTH && k == NFRAG / NQ) {
+      async_copy_4(bias_row + (a + p) * kBlock + lane, dst + PAIR + qw * 256);
+    }
+  };
+#pragma unroll
+  for (int p = 0; p < R - 1; p++)
+    if (p < cnt) {
+#pragma unroll
+      for (int k = 0; k < CPW; k++) copy_piece(p, k);
+    }
+  // end of iteration t: the copies of slot t + 1 have landed (those of younger slots stay in flight while new
+  // ones are still issued)
+  auto end_iter = [&](const bool issued) {
+    if (issued && R > 2) {
+      __builtin_amdgcn_s_waitcnt(vmcnt_only((R - 2) * CPW));
+      barrier_lds_only();
+    } else {
+      barrier_all_memory();
+    }
+  };
+  auto unbias = [&]() {
+    const float corr = kBiasC0 * w_bias;
+#pragma unroll
+    for (int cb = 0; cb < KS; cb++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) oacc[cb][r] -= corr;
+    w_bias = 0.f;
+  };
+  bool use_sbias = false;
+  if constexpr (!QSMOOTH) {
+    float smax = 0.f;
+    for (int jj = a + lane; jj < b; jj += 64) smax = fmaxf(smax, sKh[jj]);
+    use_sbias = cq * wave_max_nonneg_f32(smax) < 1e-3f;
+  }
+  auto run = [&](auto sbias_tag) __attribute__((always_inline)) {
+    constexpr bool SBIAS = decltype(sbias_tag)::value;
+    v16i sA[2], sB[2];
+    fwd_s_mfma<D, SBIAS>(KFh + (size_t)ac * TILE_BYTES, qf, sA, lane);
+    barrier_all_memory();                                      // the first slots have landed
+    float sk = scalar_load(sKh + ac), sv = scalar_load(sVh + ac);
+    auto full_iter = [&](const int t, v16i (&sc)[2], v16i (&sn)[2]) __attribute__((always_inline)) {
+      const bool issue = t + R - 1 < cnt;
+      const float skn = scalar_load(sKh + a + t + 1), svn = scalar_load(sVh + a + t + 1);
+      const int8_t* slot = ring + (t % R) * SLOT;
+      fwd_tile<D, QSMOOTH, false, true, SBIAS>([&](int k) __attribute__((always_inline)) { if (k < CPW && issue) copy_piece(t + R - 1, k); },
+                                               slot, slot + TILE_BYTES, qf, sc, sn, oacc, w_bias, m_ref, l_part, cq * sk, sv,
+                                               (const float*)(slot + PAIR + qw * 256), (a + t) * kBlock, q, lane, h);
+      if ((t & (kBiasPeriod - 1)) == kBiasPeriod - 1) unbias();
+      sk = skn;
+      sv = svn;
+      end_iter(issue);
+    };
+    int t = 0;
+    for (; a + t + 1 < last; t += 2) {
+      full_iter(t, sA, sB);
+      full_iter(t + 1, sB, sA);
+    }
+    if (a + t < last) {
+      full_iter(t, sA, sB);
+#pragma unroll
+      for (int kb = 0; kb < 2; kb++) sA[kb] = sB[kb];
+      t++;
+    }
+    if (a + t <= last) {
+      // the wave's last tile takes the masked path (which leaves visible keys as they are)
+      const bool issue = t + R - 1 < cnt;
+      if (issue) {
+#pragma unroll
+        for (int k = 0; k < CPW; k++) copy_piece(t + R - 1, k);
+      }
+      const int8_t* slot = ring + (t % R) * SLOT;
+      fwd_tile<D, QSMOOTH, true, false, SBIAS>([](int) {}, slot, slot + TILE_BYTES, qf, sA, sB, oacc, w_bias, m_ref, l_part, cq * sk, sv,
+                                               (const float*)(slot + PAIR + qw * 256), (a + t) * kBlock, qlim, lane, h);
+      end_iter(issue);
+      t++;
+    }
+    for (; t < share; t++) {                                   // (every wave of the workgroup meets `share` barriers)
+      const bool issue = t + R - 1 < cnt;
+      if (issue) {
+#pragma unroll
+        for (int k = 0; k < CPW; k++) copy_piece(t + R - 1, k);
+      }
+      end_iter(issue);
+    }
+    unbias();
+  };
+  if (__builtin_amdgcn_readfirstlane((int)use_sbias)) run(std::true_type{});
+  else run(std::false_type{});
+
+  // ---- the splits meet: split s finishes the channel blocks cb with cb % NS == s (the ring is drained: the last
+  // iterations issue nothing and wait for everything) ----
+  const float l_tot = half_swap_sum_f32(l_part[0]) + half_swap_sum_f32(l_part[1]);
+  float* xch = (float*)lds;
+#pragma unroll
+  for (int cb = 0; cb < KS; cb++)
+    if (cb % NS != g) {
+#pragma unroll
+      for (int aa = 0; aa < 4; aa++)
+        *(v4f*)(xch + ((((qw * NS + g) * KS + cb) * 4 + aa) * 64 + lane) * 4) =
+            v4f{oacc[cb][4 * aa], oacc[cb][4 * aa + 1], oacc[cb][4 * aa + 2], oacc[cb][4 * aa + 3]};
+    }
+  if (h == 0) ml[(qw * NS + g) * 32 + ql] = v2f{m_ref, l_tot};
+  barrier_lds_only();
+  if (q >= args.nq_valid) return;
+  v2f mls[NS];
+  float m = -INFINITY;
+#pragma unroll
+  for (int s = 0; s < NS; s++) {
+    mls[s] = ml[(qw * NS + s) * 32 + ql];
+    m = fmaxf(m, mls[s][0]);
+  }
+  float l = 0.f, wgt[NS];
+#pragma unroll
+  for (int s = 0; s < NS; s++) {
+    wgt[s] = __builtin_amdgcn_exp2f(mls[s][0] - m);            // 0 for a split that saw no tile
+    l = __builtin_fmaf(mls[s][1], wgt[s], l);
+  }
+  const float inv_l = 1.0f / l;
+  unsigned short* Oh = args.O + args.oview.row(bh, q);
+#pragma unroll
+  for (int cb = 0; cb < KS; cb++)
+    if (cb % NS == g) {
+#pragma unroll
+      for (int aa = 0; aa < 4; aa++) {
+        v4f o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < NS; s++) {
+          v4f x;
+          if (s == g) x = v4f{oacc[cb][4 * aa], oacc[cb][4 * aa + 1], oacc[cb][4 * aa + 2], oacc[cb][4 * aa + 3]};
+          else x = *(const v4f*)(xch + ((((qw * NS + s) * KS + cb) * 4 + aa) * 64 + lane) * 4);
+#pragma unroll
+          for (int e = 0; e < 4; e++) o[e] = __builtin_fmaf(x[e], wgt[s], o[e]);
+        }
+        v4us ob;
+#pragma unroll
+        for (int e = 0; e < 4; e++) ob[e] = float_to_bf16_bits(o[e] * inv_l);
+        *(v4us*)(Oh + 32 * cb + 8 * aa + 4 * h) = ob;
+      }
+    }
+  if (g == 0 && h == 0) args.LSE[(size_t)bh * args.nq_valid + q] = (m + __builtin_amdgcn_logf(l) - kLog2_127) * kLn2;
 }
 
 }  // namespace sage

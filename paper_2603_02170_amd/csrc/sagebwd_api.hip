@@ -12,6 +12,7 @@
 #include "common.h"
 #include "prepass_kernels.h"
 #include "fwd_kernel.h"
+#include "fwd_decode_kernel.h"
 #include "bwd_kernel.h"
 #include "probe_kernels.h"
 
@@ -339,9 +340,36 @@ int prepass_for_backward(const void* Q, const void* K, const void* V, const void
 // that stages every K^/V^ tile once for twice as many queries).
 int pick_fwd_waves(int N) { return N % 128 == 0 ? 4 : 2; }
 
+// SIMDs of the machine: what a launch has to fill.
+constexpr int kSimds = 1024;
+
+// Few queries against many keys: split the keys inside the workgroup (sage_fwd_split_kernel) while 64-query
+// workgroups do not fill the CUs twice over and there are a few tiles for each split.
+bool use_fwd_split(const FwdArgs& a) {
+  return a.N >= 2 * a.Nq && a.N >= 8 * kBlock && (long long)a.BH * ((a.Nq + 63) / 64) <= kSimds / 2;
+}
+// At most one wave of sage_fwd_kernel (32 queries) per SIMD: two waves share them (sage_fwd_pair_kernel; same
+// bits).  Measured at d = 128, us: 256 waves 24 -> 20, 1024 waves 25.8 -> 21.2, 2048 waves 77 -> 75, 4096 waves 66 -> 79.
+bool use_fwd_pair(const FwdArgs& a) { return (long long)a.BH * ((a.Nq + 31) / 32) <= kSimds; }
+
+// the two forms for calls that do not fill the machine: 64 queries per workgroup
+template <int D, bool CAUSAL, bool QS>
+int launch_fwd_small(const FwdArgs& a, bool split, hipStream_t st) {
+  FwdArgs args = a;
+  args.n_qtiles = (a.Nq + 63) / 64;
+  args.head_set = head_set_for(args.n_qtiles, a.BH);
+  const int grid = grid_for(a.BH, args.n_qtiles);
+  if (split) sage_fwd_split_kernel<D, CAUSAL, QS, 2, 4><<<grid, 512, 0, st>>>(args);
+  else sage_fwd_pair_kernel<D, CAUSAL, QS, 2><<<grid, 256, 0, st>>>(args);
+  SAGE_LAUNCH_CHECK();
+  return SAGEBWD_OK;
+}
+
 // kv128: numerics blocks of 128 keys (the per-token quantiser of P~ takes its row max over two tiles)
 template <int D, bool CAUSAL, bool QS>
 int launch_fwd_nw(const FwdArgs& a, int nw, bool kv128, hipStream_t st) {
+  if (!kv128 && use_fwd_split(a)) return launch_fwd_small<D, CAUSAL, QS>(a, true, st);
+  if (!kv128 && use_fwd_pair(a)) return launch_fwd_small<D, CAUSAL, QS>(a, false, st);
   FwdArgs args = a;
   args.n_qtiles = a.Nq / (32 * nw);
   args.head_set = head_set_for(args.n_qtiles, a.BH);
@@ -393,10 +421,75 @@ int launch_bwd_dq(const DqArgs& a, bool causal, hipStream_t st) {
   return SAGEBWD_OK;
 }
 
-// The forward on a workspace that holds at least w.fwd_total bytes (arguments already validated).
+// K-mean chunk sums (K-smoothing) into the workspace
+template <int D>
+int launch_kmean(const void* K, const RowView& kview, const sagebwd_params& p, char* ws, const Workspace& w, const QkNorm& norm,
+                 hipStream_t st) {
+  kmean_partial_kernel<D><<<dim3(w.nchunk, p.B * p.H), 256, 0, st>>>((const unsigned short*)K, kview, (double*)(ws + w.kpart),
+                                                                     kv_len(p), w.nchunk, w.chunk_rows, norm);
+  SAGE_LAUNCH_CHECK();
+  return SAGEBWD_OK;
+}
+
+// One query block of at most 32 rows that sees every key, plain options: see fwd_decode_kernel.h.
+bool use_decode(const sagebwd_params& p) {
+  return p.N <= 32 && p.causal == 0 && !(p.smooth & SAGEBWD_SMOOTH_Q) && !(p.flags & SAGEBWD_FLAG_QK_NORM) && !big_blocks(p);
+}
+
+template <int D>
+int decode_impl(const void* Q, const void* K, const void* V, void* O, float* LSE, const sagebwd_params& p, char* ws, const Workspace& w,
+                hipStream_t st) {
+  const bool ks = (p.smooth & SAGEBWD_SMOOTH_K) != 0;
+  const int BH = p.B * p.H;
+  DecodeArgs a;
+  a.Q = (const unsigned short*)Q;
+  a.K = (const unsigned short*)K;
+  a.V = (const unsigned short*)V;
+  a.qview = caller_view(p, 1, p.N);
+  a.kview = caller_view(p, 1, kv_len(p));
+  a.mean_part = ks ? (const double*)(ws + w.kpart) : nullptr;
+  a.nchunk = w.nchunk;
+  a.O = (unsigned short*)O;
+  a.LSE = LSE;
+  a.nq = p.N;
+  a.nk = kv_len(p);
+  a.nblk = padded_rows(a.nk) / 64;
+  a.scale_log2e = logit_scale(p) * 1.4426950408889634f;
+  // one wave per SIMD (its registers hold the block in hand and the next one), each on as few blocks as that allows
+  a.blocks_per_wave = (int)(((long long)BH * a.nblk + kSimds - 1) / kSimds);
+  const int nsplit = (a.nblk + 4 * a.blocks_per_wave - 1) / (4 * a.blocks_per_wave);
+  // the workgroups' partial results lie where K^ would: a workgroup has at least four key blocks (4 * 64 * D bytes) unless
+  // it is the last of its head, and leaves at most 32 * (4 D + 8)
+  a.part_ml = (v2f*)(ws + w.KF);
+  a.part = (float*)(ws + w.KF + align_up((size_t)BH * nsplit * 32 * sizeof(v2f)));
+  if (ks) {
+    ScopedTimer tm(SAGEBWD_KERNEL_PREPASS_FWD, st);
+    const int rc = launch_kmean<D>(K, a.kview, p, ws, w, QkNorm{nullptr, 0.f}, st);
+    if (rc != SAGEBWD_OK) return rc;
+  }
+  ScopedTimer tm(SAGEBWD_KERNEL_FWD, st);
+  if (ks) sage_fwd_decode_kernel<D, true><<<dim3(nsplit, BH), 256, 0, st>>>(a);
+  else sage_fwd_decode_kernel<D, false><<<dim3(nsplit, BH), 256, 0, st>>>(a);
+  SAGE_LAUNCH_CHECK();
+  if (nsplit > 1) {
+    sage_fwd_decode_join_kernel<D><<<dim3(p.N, BH), D, 0, st>>>(a, nsplit);
+    SAGE_LAUNCH_CHECK();
+  }
+  return SAGEBWD_OK;
+}
+
+// The forward on a workspace of `ws_bytes` (at least w.fwd_total; arguments already validated).
 int forward_impl(const void* Q, const void* K, const void* V, void* O, float* LSE, const sagebwd_params& p,
-                 char* ws, const Workspace& w, hipStream_t st) {
+                 char* ws, size_t ws_bytes, const Workspace& w, hipStream_t st) {
   int rc;
+  if (use_decode(p)) {
+    rc = p.d == 64 ? decode_impl<64>(Q, K, V, O, LSE, p, ws, w, st) : decode_impl<128>(Q, K, V, O, LSE, p, ws, w, st);
+    // the quantised tensors themselves are wanted only by a backward that shares them and by the inspection hooks, which
+    // take the workspace of sagebwd_bwd
+    if (rc != SAGEBWD_OK || ws_bytes < ((p.flags & SAGEBWD_FLAG_SHARE_QUANTIZED) ? w.fwd_total : w.total)) return rc;
+    ScopedTimer tm(SAGEBWD_KERNEL_PREPASS_FWD, st);
+    return p.d == 64 ? prepass_for_forward<64>(Q, K, V, p, ws, w, st) : prepass_for_forward<128>(Q, K, V, p, ws, w, st);
+  }
   {
     ScopedTimer tm(SAGEBWD_KERNEL_PREPASS_FWD, st);
     rc = p.d == 64 ? prepass_for_forward<64>(Q, K, V, p, ws, w, st) : prepass_for_forward<128>(Q, K, V, p, ws, w, st);
@@ -583,7 +676,7 @@ int sagebwd_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE
     return SAGEBWD_INVALID_ARG;
   const Workspace w = make_layout(*params);
   if (workspace_bytes < w.fwd_total) return SAGEBWD_WORKSPACE_TOO_SMALL;
-  return forward_impl(Q, K, V, O, LSE, *params, (char*)workspace, w, (hipStream_t)stream);
+  return forward_impl(Q, K, V, O, LSE, *params, (char*)workspace, workspace_bytes, w, (hipStream_t)stream);
 }
 
 int sagebwd_fwd_static(const void* Q, const void* K, const void* V, void* O, float* LSE,
@@ -600,7 +693,7 @@ int sagebwd_fwd_static(const void* Q, const void* K, const void* V, void* O, flo
   // every byte of the forward's workspace that a kernel reads is written earlier in the same call
   // (the pre-pass fills all operand rows, the missing ones of a partial block as zero codes), so nothing
   // the previous call left in the array has to be cleared
-  return forward_impl(Q, K, V, O, LSE, *params, ws, w, (hipStream_t)stream);
+  return forward_impl(Q, K, V, O, LSE, *params, ws, w.fwd_total, w, (hipStream_t)stream);
 }
 
 int sagebwd_bwd(const void* Q, const void* K, const void* V, const void* O, const void* dO,

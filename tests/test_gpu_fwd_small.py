@@ -1,0 +1,89 @@
+"""The forward's forms for calls that do not fill the machine, at the sizes where each can go wrong."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2603_02170_amd import binding, synth
+
+from gpu_common import check_close, check_lse, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+def _inputs(B, H, Nq, Nk, d, normed=False, q_offset=False):
+    Q = synth.gaussian_inputs(Nq, d, sigma_qk=1.5, seed=11 * Nq + Nk, heads=B * H)[0]
+    _, K, V, _ = synth.gaussian_inputs(Nk, d, sigma_qk=1.5, seed=Nk + d, heads=B * H)
+    Q, K, V = (t.reshape(B, H, t.shape[2], d) for t in (Q, K, V))
+    if normed:      # unit RMS: small logit scales, the conversion-free logits
+        Q, K = (torch.nn.functional.rms_norm(t.float(), (d,)).to(torch.bfloat16) for t in (Q, K))
+    if q_offset:
+        Q = (Q.float() + torch.linspace(-2, 2, d)).to(torch.bfloat16)
+    return Q, K, V
+
+
+def _against_oracle(Q, K, V, p, heads):
+    lay = (lambda t: t.permute(0, 2, 1, 3).contiguous()) if p.token_major else (lambda t: t)
+    O, L = binding.sagebwd_fwd(*(lay(t).cuda() for t in (Q, K, V)), p)
+    torch.cuda.synchronize()
+    O, L = to_np(lay(O)), L.cpu().numpy()
+    for b, h in heads:
+        Or, Lr = oracle.forward_head(*(to_np(t[b, h]) for t in (Q, K, V)), causal=p.causal, k_smooth=p.k_smooth, q_smooth=p.q_smooth)
+        check_close(f"O[{b},{h}]", O[b, h], Or)
+        check_lse(f"LSE[{b},{h}]", L[b, h], Lr)
+
+
+# one key, one block, a partial block, one workgroup of four waves and just past it, many workgroups with a ragged end,
+# 1 to 32 query rows, one wave with several blocks
+@pytest.mark.parametrize("B,H,Nq,Nk,d,k_smooth,token_major", [
+    (1, 2, 1, 1, 128, True, False), (1, 2, 1, 64, 64, True, False), (1, 3, 5, 200, 64, False, True), (1, 2, 32, 256, 128, True, False),
+    (1, 2, 3, 257, 128, True, False), (2, 3, 7, 2049, 64, True, True), (1, 1, 31, 8192, 128, True, False), (8, 32, 1, 640, 128, True, False)])
+def test_decode(B, H, Nq, Nk, d, k_smooth, token_major):
+    Q, K, V = _inputs(B, H, Nq, Nk, d)
+    p = binding.SageParams(B, H, Nq, d, causal=False, k_smooth=k_smooth, Nkv=Nk, token_major=token_major)
+    _against_oracle(Q, K, V, p, {(0, 0), (B - 1, H - 1)})
+
+
+def test_decode_leaves_the_quantised_tensors_for_those_who_can_read_them():
+    """Codes and scales after a forward on the full workspace, and a backward that shares them."""
+    Q, K, V = (t.cuda() for t in _inputs(1, 2, 9, 200, 64))
+    p = binding.SageParams(1, 2, 9, 64, causal=False, Nkv=200)
+    ws, ws2 = binding.alloc_workspace(p), binding.alloc_workspace(p)
+    O, L = binding.sagebwd_fwd(Q, K, V, p, ws)
+    binding.sagebwd_quantize(Q, K, V, p, ws2)
+    for which in (binding.TENSOR_Q, binding.TENSOR_K, binding.TENSOR_V):
+        for a, b in zip(binding.sagebwd_export_quantized(p, ws, which), binding.sagebwd_export_quantized(p, ws2, which)):
+            assert torch.equal(a, b), which
+    dO = torch.ones_like(O)
+    ref = binding.sagebwd_bwd(Q, K, V, O, dO, L, p)
+    ps = binding.SageParams(1, 2, 9, 64, causal=False, Nkv=200, share_quantized=True)
+    wss = binding.alloc_workspace(ps)
+    Os, Ls = binding.sagebwd_fwd(Q, K, V, ps, wss)
+    assert torch.equal(O, Os) and torch.equal(L, Ls)
+    for a, b in zip(ref, binding.sagebwd_bwd(Q, K, V, Os, dO, Ls, ps, wss)):
+        assert torch.equal(a, b)
+
+
+# eight tiles for four splits, a number of tiles the splits do not divide, splits without a tile under the mask, a last
+# workgroup that reaches past the queries, both ring depths, Q-smoothing's biases in the ring
+@pytest.mark.parametrize("Nq,Nk,d,causal,q_smooth", [(64, 512, 128, False, False), (100, 868, 64, True, False), (192, 580, 128, False, True),
+                                                     (33, 609, 64, False, True), (256, 1024, 128, True, False), (64, 4160, 128, True, True)])
+def test_split_keys(Nq, Nk, d, causal, q_smooth):
+    Q, K, V = _inputs(1, 2, Nq, Nk, d, normed=not q_smooth, q_offset=q_smooth)
+    _against_oracle(Q, K, V, binding.SageParams(1, 2, Nq, d, causal=causal, q_smooth=q_smooth, Nkv=Nk), {(0, 0), (0, 1)})
+
+
+# one tile, two, a partial last block, the corrections of the bias every eight tiles, the conversion-free logits and the
+# converting ones: a head alone (two waves per 32 queries) and in a call that fills the machine (one wave)
+@pytest.mark.parametrize("N,d,causal,normed,q_smooth", [(64, 128, True, True, False), (128, 64, False, False, False), (200, 128, True, True, False),
+                                                        (577, 64, True, True, False), (640, 128, False, True, False), (320, 128, True, False, True)])
+def test_two_waves_per_query_group_give_the_same_bits(N, d, causal, normed, q_smooth):
+    heads = -(-1024 // (-(-N // 32))) + 8
+    Q, K, V = (t.cuda() for t in _inputs(1, heads, N, N, d, normed=normed, q_offset=q_smooth))
+    O, L = binding.sagebwd_fwd(Q, K, V, binding.SageParams(1, heads, N, d, causal=causal, q_smooth=q_smooth))
+    p1 = binding.SageParams(1, 1, N, d, causal=causal, q_smooth=q_smooth)
+    for h in (0, heads - 1):
+        O1, L1 = binding.sagebwd_fwd(*(t[:, h:h + 1].contiguous() for t in (Q, K, V)), p1)
+        torch.cuda.synchronize()
+        assert torch.equal(O1[0, 0], O[0, h]) and torch.equal(L1[0, 0], L[0, h]), h
+    assert np.isfinite(to_np(O)).all()
