@@ -39,12 +39,12 @@ __device__ __forceinline__ float bf16_bits_to_float(unsigned short u) {
   return __uint_as_float(((unsigned)u) << 16);
 }
 
-// round-to-nearest-even float -> bf16 bits (finite inputs; NaN kept quiet)
+// round-to-nearest-even float -> bf16 bits (one conversion instruction for two values; NaN kept quiet)
 __device__ __forceinline__ unsigned short float_to_bf16_bits(float f) {
-  unsigned u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (unsigned short)((u >> 16) | 0x40);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (unsigned short)(u >> 16);
+  const __bf16 b = (__bf16)f;
+  unsigned short u;
+  __builtin_memcpy(&u, &b, 2);
+  return u;
 }
 
 // max over the two 32-lane halves of a wave, result in every lane

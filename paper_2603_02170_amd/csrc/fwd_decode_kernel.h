@@ -34,23 +34,6 @@ struct DecodeArgs {
   float scale_log2e;
 };
 
-// psi of 16 values held as FP32: the rounding of prepass_quant_kernel (q = rne(x * r); |x * r| cannot exceed
-// 127 by more than an FP32 rounding step, so no clamp is needed), packed into four registers
-__device__ __forceinline__ v4i quantise_16(const float (&x)[16], const float r) {
-  v4i o;
-#pragma unroll
-  for (int w = 0; w < 4; w++) {
-    unsigned u[4];
-#pragma unroll
-    for (int e = 0; e < 4; e++) {
-      const float y = x[4 * w + e] * r;
-      u[e] = __float_as_uint(y + 12582912.0f);               // 1.5 * 2^23: rne(y) in the low mantissa bits
-    }
-    o[w] = (int)(__builtin_amdgcn_perm(u[1], u[0], 0x0c0c0400u) | __builtin_amdgcn_perm(u[3], u[2], 0x04000c0cu));
-  }
-  return o;
-}
-
 template <int D, bool KSMOOTH>
 __global__ void __launch_bounds__(256, 1) sage_fwd_decode_kernel(DecodeArgs args) {
   constexpr int KS = D / 32;
@@ -112,6 +95,7 @@ __global__ void __launch_bounds__(256, 1) sage_fwd_decode_kernel(DecodeArgs args
     a = wave_max_nonneg_f32(a);
     const bool nz = a > 0.f;
     const float r = nz ? 127.0f / a : 0.f;
+    const bool plain = __builtin_amdgcn_readfirstlane((int)(r < INFINITY));
 #pragma unroll
     for (int rb = 0; rb < 2; rb++) {
       const bool there = 64 * j + 32 * rb + r32 < args.nk;
@@ -119,7 +103,8 @@ __global__ void __launch_bounds__(256, 1) sage_fwd_decode_kernel(DecodeArgs args
       for (int s = 0; s < KS; s++) {
         float x[16];
         values(raw.v[rb][s], there, mu == nullptr ? nullptr : mu + 32 * s + 16 * h, x);
-        f[rb][s] = quantise_16(x, r);
+        f[rb][s] = quantise_16<false>(x, r);
+        if (!plain) f[rb][s] = quantise_16(x, r);
       }
     }
     return nz ? a / 127.0f : 0.f;

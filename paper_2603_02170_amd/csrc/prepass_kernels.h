@@ -117,6 +117,26 @@ __global__ void fill_zero_f32_kernel(float* __restrict__ p, size_t n) {
   for (; i < n; i += stride) p[i] = 0.f;
 }
 
+// The rounding of psi on 16 values held as FP32: q = rne(x * r) clamped to +-127 (needed only where r = 127 / max|x|
+// overflows: blocks of the smallest numbers), packed into four registers.  x * r is rounded to FP32 before the addition that takes it to an integer, so the
+// codes are those of rintf.
+template <bool CLAMP = true>
+__device__ __forceinline__ v4i quantise_16(const float (&x)[16], const float r) {
+  v4i o;
+#pragma unroll
+  for (int w = 0; w < 4; w++) {
+    unsigned u[4];
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      float y = x[4 * w + e] * r;
+      if constexpr (CLAMP) y = __builtin_amdgcn_fmed3f(y, -127.f, 127.f);
+      u[e] = __float_as_uint(y + 12582912.0f);               // 1.5 * 2^23: rne(y) in the low mantissa bits
+    }
+    o[w] = (int)(__builtin_amdgcn_perm(u[1], u[0], 0x0c0c0400u) | __builtin_amdgcn_perm(u[3], u[2], 0x04000c0cu));
+  }
+  return o;
+}
+
 // ---- psi on one 64-row block (of a numerics block of 64 or 128 rows) -------------
 struct QuantJob {
   const unsigned short* src;   // bf16, rows addressed through `view`
@@ -148,127 +168,105 @@ struct QuantJobs {
 // -L*log2(e) = -inf (P = 0 in the backward).  The grid's x extent covers the longest job.
 //
 // SUB = 64-row blocks per numerics block (Algorithm 1 leaves B_q, B_kv free): 1, or 2 for blocks of 128 rows.
-// A workgroup always writes ONE 64-row block; with SUB = 2 it also reads the other half of its numerics
-// block (its "partner") and takes the block mean and the absmax over both, so that the two workgroups of a
-// numerics block arrive at the same scale (and mean) without exchanging anything, and store it once per
-// 64-row block: the attention kernels index scales, means and bias rows by 64-row block whatever the
-// numerics block is.
+// A workgroup takes one numerics block; its scale (and block mean) is stored once per 64-row block: the
+// attention kernels index scales, means and bias rows by 64-row block whatever the numerics block is.
 template <int D, int SUB>
 __global__ void __launch_bounds__(256) prepass_quant_kernel(QuantJobs jobs) {
+  constexpr int ROWS = SUB * kBlock;
   constexpr int CPR = D / 16;            // 16-channel chunks per row
-  constexpr int NCH = 64 * CPR / 256;    // chunks per thread (1 for D=64, 2 for D=128)
-  constexpr int NTF = 4 * D / 256;       // TF chunks per thread
+  constexpr int NCH = ROWS * CPR / 256;  // chunks per thread
+  constexpr int NTF = ROWS / 16 * D / 256;   // TF chunks per thread
   static_assert(SUB == 1 || SUB == 2, "numerics blocks of 64 or 128 rows");
-  __shared__ __attribute__((aligned(16))) int8_t tile[64 * D];
+  __shared__ __attribute__((aligned(16))) int8_t tile[ROWS * D];
   __shared__ float colbuf[64 * D / 4];   // used by the block mean only (16 rows at a time)
   __shared__ float mu_s[D];
+  __shared__ double sumsq[ROWS];         // QK-norm: the rows' sums of squares, then their factors
   __shared__ float wmax[4];
 
   const QuantJob jb = jobs.job[blockIdx.z];
   const int t = threadIdx.x;
-  const int blk = blockIdx.x, bh = blockIdx.y;
+  const int blk = blockIdx.x * SUB, bh = blockIdx.y;                        // first 64-row block
   const int N = jb.N, Np = jb.Np;
   const RowView view = jb.view;
   const int nblk = Np / kBlock;
   if (blk >= nblk) return;
+  const int nsub = min(SUB, nblk - blk);                                    // 64-row blocks of the workspace here
   const size_t tile_off = view.row(bh, (size_t)blk * kBlock);               // in the caller's tensors
-  const int rows_here = min(kBlock, N - blk * kBlock);                      // rows of this block that exist
-  // the partner block (SUB = 2): the other 64 rows of this numerics block, possibly past the end
-  const int pblk = blk ^ 1;
-  const int rows_partner = SUB == 2 ? max(0, min(kBlock, N - pblk * kBlock)) : 0;
+  const int rows_here = min(ROWS, N - blk * kBlock);                        // rows of this block that exist
 
-  // rows of 64-row block `b` (the first `rows` of them exist) as FP32, 16 channels per chunk
-  auto load_rows = [&](float (&v)[NCH][16], const int b, const int rows) {
-    const size_t off = view.row(bh, (size_t)b * kBlock);
+  // the rows as FP32, 16 channels per chunk: chunk c = t + 256 it is (row c / CPR, channels 16 (c % CPR) ..)
+  float x[NCH][16];
 #pragma unroll
-    for (int it = 0; it < NCH; it++) {
-      const int c = t + 256 * it;
-      const int row = c / CPR, ch = c % CPR;
-      v8us lo = {0, 0, 0, 0, 0, 0, 0, 0}, hi = {0, 0, 0, 0, 0, 0, 0, 0};
-      if (row < rows) {
-        const unsigned short* p = jb.src + off + (size_t)row * view.row_stride + ch * 16;
-        lo = *(const v8us*)p;
-        hi = *(const v8us*)(p + 8);
-      }
-#pragma unroll
-      for (int e = 0; e < 8; e++) {
-        v[it][e] = bf16_bits_to_float(lo[e]);
-        v[it][8 + e] = bf16_bits_to_float(hi[e]);
-      }
+  for (int it = 0; it < NCH; it++) {
+    const int c = t + 256 * it;
+    const int row = c / CPR, ch = c % CPR;
+    v8us lo = {0, 0, 0, 0, 0, 0, 0, 0}, hi = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (row < rows_here) {
+      const unsigned short* p = jb.src + tile_off + (size_t)row * view.row_stride + ch * 16;
+      lo = *(const v8us*)p;
+      hi = *(const v8us*)(p + 8);
     }
-  };
-  // QK-norm of the rows held in `v`: the CPR threads of a row (consecutive lanes) share its sum of squares
-  auto qk_normalise = [&](float (&v)[NCH][16], const int rows, unsigned short* out_rows) {
+#pragma unroll
+    for (int e = 0; e < 8; e++) {
+      x[it][e] = bf16_bits_to_float(lo[e]);
+      x[it][8 + e] = bf16_bits_to_float(hi[e]);
+    }
+  }
+
+  if (jb.norm.gamma != nullptr) {
+    // QK-norm: the CPR threads of a row (consecutive lanes) form its sum of squares; one thread per row then takes
+    // the float64 root and quotient (in every thread of the row they cost more than all the rest of this kernel:
+    // B2 H16 N2048 d128 with blocks of 128, 57 us before, and the partner block was normalised twice)
 #pragma unroll
     for (int it = 0; it < NCH; it++) {
       const int c = t + 256 * it;
-      const int row = c / CPR, ch = c % CPR;
       double ss = 0.0;
 #pragma unroll
-      for (int e = 0; e < 16; e++) ss += (double)(v[it][e] * v[it][e]);
+      for (int e = 0; e < 16; e++) ss += (double)(x[it][e] * x[it][e]);
 #pragma unroll
       for (int off = 1; off < CPR; off <<= 1) ss += __shfl_xor(ss, off, 64);
-      if (row < rows) {
-        const float rs = qknorm_rscale(ss, D, jb.norm.eps);
-        const float* g = jb.norm.gamma + ch * 16;
+      if (c % CPR == 0) sumsq[c / CPR] = ss;
+    }
+    __syncthreads();
+    if (t < ROWS) sumsq[t] = (double)qknorm_rscale(sumsq[t], D, jb.norm.eps);
+    __syncthreads();
+    unsigned short* out = jb.norm_out != nullptr ? jb.norm_out + ((size_t)bh * Np + (size_t)blk * kBlock) * D : nullptr;
 #pragma unroll
-        for (int e = 0; e < 16; e++) v[it][e] = qknorm_apply(v[it][e], rs, g[e]);
+    for (int it = 0; it < NCH; it++) {
+      const int c = t + 256 * it;
+      const int row = c / CPR, ch = c % CPR;
+      const float rs = (float)sumsq[row];
+      const float* g = jb.norm.gamma + ch * 16;
+      // (rows that do not exist are zero and stay zero; their factor 1 / sqrt(eps) is infinite for eps = 0)
+      if (row < rows_here) {
+#pragma unroll
+        for (int e = 0; e < 16; e++) x[it][e] = qknorm_apply(x[it][e], rs, g[e]);
       }
-      if (out_rows != nullptr) {
+      if (out != nullptr && row < nsub * kBlock) {
         v8us lo, hi;
 #pragma unroll
         for (int e = 0; e < 8; e++) {
-          lo[e] = float_to_bf16_bits(v[it][e]);        // exact: the values are bf16 already (zero in missing rows)
-          hi[e] = float_to_bf16_bits(v[it][8 + e]);
+          lo[e] = float_to_bf16_bits(x[it][e]);        // exact: the values are bf16 already (zero in missing rows)
+          hi[e] = float_to_bf16_bits(x[it][8 + e]);
         }
-        unsigned short* o = out_rows + (size_t)row * D + ch * 16;
+        unsigned short* o = out + (size_t)row * D + ch * 16;
         *(v8us*)o = lo;
         *(v8us*)(o + 8) = hi;
       }
     }
-  };
-  // v -= mu_s on the rows that exist
-  auto subtract_mu = [&](float (&v)[NCH][16], const int rows) {
+  }
+
+  // x -= mu_s on the rows that exist
+  auto subtract_mu = [&]() {
 #pragma unroll
     for (int it = 0; it < NCH; it++) {
       const int row = (t + 256 * it) / CPR, ch = (t + 256 * it) % CPR;
-      if (row < rows) {
+      if (row < rows_here) {
 #pragma unroll
-        for (int e = 0; e < 16; e++) v[it][e] = v[it][e] - mu_s[ch * 16 + e];
+        for (int e = 0; e < 16; e++) x[it][e] = x[it][e] - mu_s[ch * 16 + e];
       }
     }
   };
-  // float64 column sums of the rows held in `v` (zeros where a row does not exist), thread t < D taking
-  // channel t; in 4 passes of 16 rows through `colbuf` to bound LDS
-  auto add_column_sums = [&](const float (&v)[NCH][16], double& part) {
-    for (int pass = 0; pass < 4; pass++) {
-      __syncthreads();
-#pragma unroll
-      for (int it = 0; it < NCH; it++) {
-        const int c = t + 256 * it;
-        const int row = c / CPR, ch = c % CPR;
-        if (row / 16 == pass) {
-#pragma unroll
-          for (int e = 0; e < 16; e++) colbuf[(row % 16) * D + ch * 16 + e] = v[it][e];
-        }
-      }
-      __syncthreads();
-      if (t < D) {
-        for (int r = 0; r < 16; r++) part += (double)colbuf[r * D + t];
-      }
-    }
-  };
-
-  float x[NCH][16];
-  float xp[SUB == 2 ? NCH : 1][16];      // the partner's rows (SUB = 2)
-  load_rows(x, blk, rows_here);
-  if constexpr (SUB == 2) load_rows(xp, pblk, rows_partner);
-
-  if (jb.norm.gamma != nullptr) {
-    qk_normalise(x, rows_here,
-                 jb.norm_out != nullptr ? jb.norm_out + ((size_t)bh * Np + (size_t)blk * kBlock) * D : nullptr);
-    if constexpr (SUB == 2) qk_normalise(xp, rows_partner, nullptr);
-  }
 
   // delta = rowsum(dO o O), FP32 (not part of the bit-exact contract)
   if (jb.O != nullptr) {
@@ -291,11 +289,11 @@ __global__ void __launch_bounds__(256) prepass_quant_kernel(QuantJobs jobs) {
 #pragma unroll
       for (int off = 1; off < CPR; off <<= 1) acc += __shfl_xor(acc, off, 64);
       // stored negated: the backward starts the dP accumulators from -delta (dP - delta in one chain)
-      if (ch == 0) jb.delta[(size_t)bh * Np + (size_t)blk * kBlock + row] = -acc;
+      if (ch == 0 && row < nsub * kBlock) jb.delta[(size_t)bh * Np + (size_t)blk * kBlock + row] = -acc;
     }
   }
 
-  if (jb.lse != nullptr && t < 64) {
+  if (jb.lse != nullptr && t < nsub * kBlock) {
     const size_t row = (size_t)blk * kBlock + t;
     jb.nl2[(size_t)bh * Np + row] = t < rows_here ? -jb.lse[(size_t)bh * N + row] * 1.4426950408889634f : -INFINITY;
   }
@@ -310,23 +308,36 @@ __global__ void __launch_bounds__(256) prepass_quant_kernel(QuantJobs jobs) {
       if (blk == 0) jb.mu_head_out[(size_t)bh * D + t] = m;
     }
     __syncthreads();
-    subtract_mu(x, rows_here);
-    if constexpr (SUB == 2) subtract_mu(xp, rows_partner);
+    subtract_mu();
   }
 
   if (jb.mu_block_out != nullptr) {
-    // block mean over the rows of the numerics block that exist: float64 sum (exact for bf16 data), one rounding
-    double part = 0.0;   // thread t < D accumulates channel t
-    add_column_sums(x, part);
-    if constexpr (SUB == 2) add_column_sums(xp, part);
+    // block mean over the rows of the numerics block that exist: float64 column sums (exact for bf16 data; zeros where
+    // a row does not exist), thread t < D taking channel t, 16 rows at a time through `colbuf`; one rounding
+    double part = 0.0;
+    for (int pass = 0; pass < ROWS / 16; pass++) {
+      __syncthreads();
+#pragma unroll
+      for (int it = 0; it < NCH; it++) {
+        const int c = t + 256 * it;
+        const int row = c / CPR, ch = c % CPR;
+        if (row / 16 == pass) {
+#pragma unroll
+          for (int e = 0; e < 16; e++) colbuf[(row % 16) * D + ch * 16 + e] = x[it][e];
+        }
+      }
+      __syncthreads();
+      if (t < D) {
+        for (int r = 0; r < 16; r++) part += (double)colbuf[r * D + t];
+      }
+    }
     if (t < D) {
-      const float m = (float)(part / (double)(rows_here + rows_partner));
+      const float m = (float)(part / (double)rows_here);
       mu_s[t] = m;
-      jb.mu_block_out[((size_t)bh * nblk + blk) * D + t] = m;
+      for (int k = 0; k < nsub; k++) jb.mu_block_out[((size_t)bh * nblk + blk + k) * D + t] = m;
     }
     __syncthreads();
-    subtract_mu(x, rows_here);
-    if constexpr (SUB == 2) subtract_mu(xp, rows_partner);
+    subtract_mu();
   }
 
   // block absmax
@@ -335,12 +346,6 @@ __global__ void __launch_bounds__(256) prepass_quant_kernel(QuantJobs jobs) {
   for (int it = 0; it < NCH; it++)
 #pragma unroll
     for (int e = 0; e < 16; e++) a = fmaxf(a, fabsf(x[it][e]));
-  if constexpr (SUB == 2) {
-#pragma unroll
-    for (int it = 0; it < NCH; it++)
-#pragma unroll
-      for (int e = 0; e < 16; e++) a = fmaxf(a, fabsf(xp[it][e]));
-  }
   a = wave_max_nonneg_f32(a);
   if ((t & 63) == 0) wmax[t >> 6] = a;
   __syncthreads();
@@ -348,27 +353,16 @@ __global__ void __launch_bounds__(256) prepass_quant_kernel(QuantJobs jobs) {
   const bool nz = a > 0.f;
   const float s = nz ? a / 127.0f : 0.f;
   const float r = nz ? 127.0f / a : 0.f;
-  if (t == 0) jb.scale[(size_t)bh * nblk + blk] = s;
+  if (t < nsub) jb.scale[(size_t)bh * nblk + blk + t] = s;
 
   const size_t frag_base = ((size_t)bh * (Np / 32) + (size_t)blk * 2) * (D / 32) * 1024;
 #pragma unroll
   for (int it = 0; it < NCH; it++) {
     const int c = t + 256 * it;
     const int row = c / CPR, ch = c % CPR;
-    v4i packed;
-#pragma unroll
-    for (int w = 0; w < 4; w++) {
-      unsigned u = 0;
-#pragma unroll
-      for (int e = 0; e < 4; e++) {
-        float y = __builtin_rintf(x[it][4 * w + e] * r);
-        y = fminf(fmaxf(y, -127.f), 127.f);
-        u |= ((unsigned)((int)y) & 0xffu) << (8 * e);
-      }
-      packed[w] = (int)u;
-    }
+    const v4i packed = quantise_16(x[it], r);
     if (jb.outTF != nullptr) *(v4i*)(tile + row * D + ch * 16) = packed;
-    if (jb.outF != nullptr) {
+    if (jb.outF != nullptr && row < nsub * kBlock) {
       const int rb = row / 32, sstep = ch / 2, h = ch % 2;
       const int lane = (row % 32) + 32 * h;
       *(v4i*)(jb.outF + frag_base + ((size_t)(rb * (D / 32) + sstep) * 64 + lane) * 16) = packed;
@@ -380,6 +374,7 @@ __global__ void __launch_bounds__(256) prepass_quant_kernel(QuantJobs jobs) {
     for (int it = 0; it < NTF; it++) {
       const int c = t + 256 * it;            // (rb, cb, lane)
       const int lane = c % 64, cb = (c / 64) % (D / 32), rb = c / (64 * (D / 32));
+      if (rb >= 2 * nsub) break;             // (whole waves)
       const int col = 32 * cb + (lane % 32), h = lane / 32;
       v4i packed;
 #pragma unroll

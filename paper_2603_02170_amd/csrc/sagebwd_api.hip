@@ -304,7 +304,7 @@ int run_prepass(const void* Q, const void* K, const void* V, const void* dO, con
       }
       if (np == 0) continue;
       if (sub == 1) prepass_quant_kernel<D, 1><<<dim3(nblk_max, BH, np), 256, 0, st>>>(part);
-      else prepass_quant_kernel<D, 2><<<dim3(nblk_max, BH, np), 256, 0, st>>>(part);
+      else prepass_quant_kernel<D, 2><<<dim3((nblk_max + 1) / 2, BH, np), 256, 0, st>>>(part);
       SAGE_LAUNCH_CHECK();
     }
   }
