@@ -94,8 +94,8 @@ __global__ void __launch_bounds__(256, 1) sage_fwd_decode_kernel(DecodeArgs args
     }
     a = wave_max_nonneg_f32(a);
     const bool nz = a > 0.f;
-    const float r = nz ? 127.0f / a : 0.f;
-    const bool plain = __builtin_amdgcn_readfirstlane((int)(r < INFINITY));
+    // (kept finite: psi then needs no clamp)
+    const float r = nz ? fminf(127.0f / a, 3.402823466e38f) : 0.f;
 #pragma unroll
     for (int rb = 0; rb < 2; rb++) {
       const bool there = 64 * j + 32 * rb + r32 < args.nk;
@@ -104,7 +104,6 @@ __global__ void __launch_bounds__(256, 1) sage_fwd_decode_kernel(DecodeArgs args
         float x[16];
         values(raw.v[rb][s], there, mu == nullptr ? nullptr : mu + 32 * s + 16 * h, x);
         f[rb][s] = quantise_16<false>(x, r);
-        if (!plain) f[rb][s] = quantise_16(x, r);
       }
     }
     return nz ? a / 127.0f : 0.f;

@@ -40,23 +40,15 @@ __device__ __forceinline__ float qknorm_apply(float x, float r, float g) {
   return bf16_bits_to_float(float_to_bf16_bits((x * r) * g));
 }
 
-// ---- K mean, stage 1: float64 column sums of a chunk of rows -----------------------
-// (bf16 data of ordinary range sum exactly in float64, so the result does not depend on the order
-// or on the chunk size.)  Stage 2, the sum over the chunks, the division by N and the one rounding to
-// FP32, runs at the start of every workgroup that quantises a block of K (prepass_quant_kernel).
+// Float64 column sums of `rows` rows at `base`, over the 256 threads of a workgroup: thread t adds the rows
+// t / TPR, t / TPR + RPP, ... of its 8 channels 8 (t % TPR) .. into acc.
+// (bf16 data of ordinary range sum exactly in float64, so the result does not depend on the order.)
 template <int D>
-__global__ void __launch_bounds__(256) kmean_partial_kernel(const unsigned short* __restrict__ K, RowView view,
-                                                            double* __restrict__ kpart, int N,
-                                                            int nchunk, int chunk_rows, QkNorm norm) {
+__device__ __forceinline__ void column_sums(const unsigned short* __restrict__ base, const size_t row_stride, const int rows,
+                                            const QkNorm& norm, double (&acc)[8]) {
   constexpr int TPR = D / 8;          // threads per row, 8 channels (16 bytes) each
   constexpr int RPP = 256 / TPR;      // rows per pass
-  __shared__ double red[256][8];
   const int t = threadIdx.x;
-  const int chunk = blockIdx.x, bh = blockIdx.y;
-  const int row0 = chunk * chunk_rows;
-  const int rows = min(chunk_rows, N - row0);
-  const unsigned short* base = K + view.row(bh, row0);
-  double acc[8];
 #pragma unroll
   for (int e = 0; e < 8; e++) acc[e] = 0.0;
   const int tr = t / TPR, tc = t % TPR;
@@ -69,7 +61,7 @@ __global__ void __launch_bounds__(256) kmean_partial_kernel(const unsigned short
     for (int r0 = 0; r0 < rows; r0 += RPP) {      // whole passes: the shuffles need every lane
       r = r0 + tr;
       v8us v = {0, 0, 0, 0, 0, 0, 0, 0};
-      if (r < rows) v = *(const v8us*)(base + (size_t)r * view.row_stride + tc * 8);
+      if (r < rows) v = *(const v8us*)(base + (size_t)r * row_stride + tc * 8);
       double ss = 0.0;
 #pragma unroll
       for (int e = 0; e < 8; e++) {
@@ -84,23 +76,40 @@ __global__ void __launch_bounds__(256) kmean_partial_kernel(const unsigned short
         for (int e = 0; e < 8; e++) acc[e] += (double)qknorm_apply(bf16_bits_to_float(v[e]), rs, g[e]);
       }
     }
-    r = rows;   // nothing left for the plain loops below
+    return;
   }
   // four independent 16-byte loads in flight per thread
   for (; r + 3 * RPP < rows; r += 4 * RPP) {
     v8us v[4];
 #pragma unroll
-    for (int u = 0; u < 4; u++) v[u] = *(const v8us*)(base + (size_t)(r + u * RPP) * view.row_stride + tc * 8);
+    for (int u = 0; u < 4; u++) v[u] = *(const v8us*)(base + (size_t)(r + u * RPP) * row_stride + tc * 8);
 #pragma unroll
     for (int u = 0; u < 4; u++)
 #pragma unroll
       for (int e = 0; e < 8; e++) acc[e] += (double)bf16_bits_to_float(v[u][e]);
   }
   for (; r < rows; r += RPP) {
-    v8us v = *(const v8us*)(base + (size_t)r * view.row_stride + tc * 8);
+    v8us v = *(const v8us*)(base + (size_t)r * row_stride + tc * 8);
 #pragma unroll
     for (int e = 0; e < 8; e++) acc[e] += (double)bf16_bits_to_float(v[e]);
   }
+}
+
+// ---- K mean, stage 1: float64 column sums of a chunk of rows -----------------------
+// Stage 2, the sum over the chunks, the division by N and the one rounding to
+// FP32, runs at the start of every workgroup that quantises a block of K (prepass_quant_kernel).
+template <int D>
+__global__ void __launch_bounds__(256) kmean_partial_kernel(const unsigned short* __restrict__ K, RowView view,
+                                                            double* __restrict__ kpart, int N,
+                                                            int nchunk, int chunk_rows, QkNorm norm) {
+  constexpr int TPR = D / 8;
+  constexpr int RPP = 256 / TPR;
+  __shared__ double red[256][8];
+  const int t = threadIdx.x;
+  const int chunk = blockIdx.x, bh = blockIdx.y;
+  const int row0 = chunk * chunk_rows;
+  double acc[8];
+  column_sums<D>(K + view.row(bh, row0), view.row_stride, min(chunk_rows, N - row0), norm, acc);
 #pragma unroll
   for (int e = 0; e < 8; e++) red[t][e] = acc[e];
   __syncthreads();
@@ -110,6 +119,10 @@ __global__ void __launch_bounds__(256) kmean_partial_kernel(const unsigned short
     kpart[((size_t)bh * nchunk + chunk) * D + t] = s;
   }
 }
+
+// Heads this short are summed by every workgroup that quantises a block of K, each for itself, without the launch of
+// stage 1: 512 rows of d = 128 cost a workgroup about 1.7 us, a launch about 3.
+inline bool mean_inline(int N, int D) { return (long long)N * D <= 65536; }
 
 __global__ void fill_zero_f32_kernel(float* __restrict__ p, size_t n) {
   size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
@@ -149,6 +162,7 @@ struct QuantJob {
   const double* mean_part;     // K-smoothing: float64 column sums [BH, nchunk, D] of the whole head; the
                                // mean (sum / N, rounded once to FP32) is subtracted from every row.  Else nullptr
   int nchunk;
+  int mean_inline;             // K-smoothing of a short head: no chunk sums, the workgroup sums the head itself
   float* mu_head_out;          // [BH, D]: where block 0 of each head stores that mean
   float* mu_block_out;         // [BH, N/64, D]: if set, the block mean is computed, stored and subtracted
   const unsigned short* O;     // bf16 [BH, N, D] or nullptr: delta = rowsum(src o O)
@@ -170,7 +184,9 @@ struct QuantJobs {
 // SUB = 64-row blocks per numerics block (Algorithm 1 leaves B_q, B_kv free): 1, or 2 for blocks of 128 rows.
 // A workgroup takes one numerics block; its scale (and block mean) is stored once per 64-row block: the
 // attention kernels index scales, means and bias rows by 64-row block whatever the numerics block is.
-template <int D, int SUB>
+// INLINE_MEAN: the K job sums its head itself (jobs of a short K; an instantiation of its own, since the summing loop costs
+// the registers that the long ones' occupancy needs).
+template <int D, int SUB, bool INLINE_MEAN>
 __global__ void __launch_bounds__(256) prepass_quant_kernel(QuantJobs jobs) {
   constexpr int ROWS = SUB * kBlock;
   constexpr int CPR = D / 16;            // 16-channel chunks per row
@@ -178,7 +194,7 @@ __global__ void __launch_bounds__(256) prepass_quant_kernel(QuantJobs jobs) {
   constexpr int NTF = ROWS / 16 * D / 256;   // TF chunks per thread
   static_assert(SUB == 1 || SUB == 2, "numerics blocks of 64 or 128 rows");
   __shared__ __attribute__((aligned(16))) int8_t tile[ROWS * D];
-  __shared__ float colbuf[64 * D / 4];   // used by the block mean only (16 rows at a time)
+  __shared__ __attribute__((aligned(16))) float colbuf[64 * D / 4];   // used by the block mean only (16 rows at a time)
   __shared__ float mu_s[D];
   __shared__ double sumsq[ROWS];         // QK-norm: the rows' sums of squares, then their factors
   __shared__ float wmax[4];
@@ -298,11 +314,27 @@ __global__ void __launch_bounds__(256) prepass_quant_kernel(QuantJobs jobs) {
     jb.nl2[(size_t)bh * Np + row] = t < rows_here ? -jb.lse[(size_t)bh * N + row] * 1.4426950408889634f : -INFINITY;
   }
 
-  if (jb.mean_part != nullptr) {
+  if (INLINE_MEAN && jb.mean_inline) {
+    double acc[8];
+    column_sums<D>(jb.src + view.row(bh, 0), view.row_stride, N, jb.norm, acc);
+    // the rows of a wave meet in its first D / 8 lanes, the waves in colbuf
+    double* red = (double*)colbuf;               // [wave][D]
+    static_assert(4 * D * sizeof(double) <= sizeof(colbuf), "four waves' sums");
+#pragma unroll
+    for (int e = 0; e < 8; e++) {
+#pragma unroll
+      for (int off = D / 8; off < 64; off <<= 1) acc[e] += __shfl_xor(acc[e], off, 64);
+      if ((t & 63) < D / 8) red[(t >> 6) * D + 8 * (t & 63) + e] = acc[e];
+    }
+    __syncthreads();
+  }
+  if ((INLINE_MEAN && jb.mean_inline) || jb.mean_part != nullptr) {
     // mu_K: the chunk sums of the head, added in float64, divided by N, rounded once to FP32
     if (t < D) {
       double s = 0.0;
-      for (int k = 0; k < jb.nchunk; k++) s += jb.mean_part[((size_t)bh * jb.nchunk + k) * D + t];
+      const double* red = (const double*)colbuf;
+      if (INLINE_MEAN && jb.mean_inline) s = (red[t] + red[D + t]) + (red[2 * D + t] + red[3 * D + t]);
+      else for (int k = 0; k < jb.nchunk; k++) s += jb.mean_part[((size_t)bh * jb.nchunk + k) * D + t];
       const float m = (float)(s / (double)N);
       mu_s[t] = m;
       if (blk == 0) jb.mu_head_out[(size_t)bh * D + t] = m;

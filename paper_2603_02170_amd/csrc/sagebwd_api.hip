@@ -218,6 +218,16 @@ struct ScopedTimer {
   } while (0)
 
 // ---- pre-pass ---------------------------------------------------------------
+// K-mean chunk sums (K-smoothing) into the workspace
+template <int D>
+int launch_kmean(const void* K, const RowView& kview, const sagebwd_params& p, char* ws, const Workspace& w, const QkNorm& norm,
+                 hipStream_t st) {
+  kmean_partial_kernel<D><<<dim3(w.nchunk, p.B * p.H), 256, 0, st>>>((const unsigned short*)K, kview, (double*)(ws + w.kpart),
+                                                                     kv_len(p), w.nchunk, w.chunk_rows, norm);
+  SAGE_LAUNCH_CHECK();
+  return SAGEBWD_OK;
+}
+
 // want_qk: smooth and quantise Q and K (F layouts; with want_tf also the backward's TF layouts);
 // want_v: quantise V; dO != nullptr: quantise dO and form delta and -L*log2(e).
 template <int D>
@@ -230,13 +240,14 @@ int run_prepass(const void* Q, const void* K, const void* V, const void* dO, con
   const RowView qview = caller_view(p, 1, Nq), kview = caller_view(p, 1, Nk);     // in bf16 elements
   float* muK = (float*)(ws + w.muK);
   const bool qkn = (p.flags & SAGEBWD_FLAG_QK_NORM) != 0;
+  const bool inline_mean = ks && mean_inline(Nk, D);
   const QkNorm norm_q{qkn ? p.qk_gamma_q : nullptr, p.qk_norm_eps}, norm_k{qkn ? p.qk_gamma_k : nullptr, p.qk_norm_eps};
   if (want_qk) {
     if (ks) {
-      kmean_partial_kernel<D><<<dim3(w.nchunk, BH), 256, 0, st>>>((const unsigned short*)K, kview,
-                                                                   (double*)(ws + w.kpart), Nk, w.nchunk, w.chunk_rows,
-                                                                   norm_k);
-      SAGE_LAUNCH_CHECK();
+      if (!inline_mean) {
+        const int rc = launch_kmean<D>(K, kview, p, ws, w, norm_k, st);
+        if (rc != SAGEBWD_OK) return rc;
+      }
     } else {
       fill_zero_f32_kernel<<<(BH * D + 255) / 256, 256, 0, st>>>(muK, (size_t)BH * D);
       SAGE_LAUNCH_CHECK();
@@ -255,7 +266,8 @@ int run_prepass(const void* Q, const void* K, const void* V, const void* dO, con
     jobs.job[nj].outF = (int8_t*)(ws + w.KF);
     jobs.job[nj].outTF = want_tf ? (int8_t*)(ws + w.KT) : nullptr;
     jobs.job[nj].scale = (float*)(ws + w.sK);
-    jobs.job[nj].mean_part = ks ? (const double*)(ws + w.kpart) : nullptr;
+    jobs.job[nj].mean_part = ks && !inline_mean ? (const double*)(ws + w.kpart) : nullptr;
+    jobs.job[nj].mean_inline = inline_mean;
     jobs.job[nj].nchunk = w.nchunk;
     jobs.job[nj].mu_head_out = muK;
     jobs.job[nj].norm = norm_k;
@@ -303,8 +315,14 @@ int run_prepass(const void* Q, const void* K, const void* V, const void* dO, con
         if ((jobs.job[k].q_like ? block_q(p) : block_kv(p)) / 64 == sub) part.job[np++] = jobs.job[k];
       }
       if (np == 0) continue;
-      if (sub == 1) prepass_quant_kernel<D, 1><<<dim3(nblk_max, BH, np), 256, 0, st>>>(part);
-      else prepass_quant_kernel<D, 2><<<dim3((nblk_max + 1) / 2, BH, np), 256, 0, st>>>(part);
+      const dim3 grid((nblk_max + sub - 1) / sub, BH, np);
+      if (sub == 1) {
+        if (want_qk && inline_mean) prepass_quant_kernel<D, 1, true><<<grid, 256, 0, st>>>(part);
+        else prepass_quant_kernel<D, 1, false><<<grid, 256, 0, st>>>(part);
+      } else {
+        if (want_qk && inline_mean) prepass_quant_kernel<D, 2, true><<<grid, 256, 0, st>>>(part);
+        else prepass_quant_kernel<D, 2, false><<<grid, 256, 0, st>>>(part);
+      }
       SAGE_LAUNCH_CHECK();
     }
   }
@@ -421,19 +439,12 @@ int launch_bwd_dq(const DqArgs& a, bool causal, hipStream_t st) {
   return SAGEBWD_OK;
 }
 
-// K-mean chunk sums (K-smoothing) into the workspace
-template <int D>
-int launch_kmean(const void* K, const RowView& kview, const sagebwd_params& p, char* ws, const Workspace& w, const QkNorm& norm,
-                 hipStream_t st) {
-  kmean_partial_kernel<D><<<dim3(w.nchunk, p.B * p.H), 256, 0, st>>>((const unsigned short*)K, kview, (double*)(ws + w.kpart),
-                                                                     kv_len(p), w.nchunk, w.chunk_rows, norm);
-  SAGE_LAUNCH_CHECK();
-  return SAGEBWD_OK;
-}
-
-// One query block of at most 32 rows that sees every key, plain options: see fwd_decode_kernel.h.
+// One query block of at most 32 rows that sees every key, plain options: see fwd_decode_kernel.h.  (Its kernel is long, and
+// with a short cache few workgroups share the cost of fetching its instructions: 9 heads against 384 keys took 21 us with
+// codes in the workspace, 23 this way.)
 bool use_decode(const sagebwd_params& p) {
-  return p.N <= 32 && p.causal == 0 && !(p.smooth & SAGEBWD_SMOOTH_Q) && !(p.flags & SAGEBWD_FLAG_QK_NORM) && !big_blocks(p);
+  const int nblk = padded_rows(kv_len(p)) / 64;
+  return (nblk >= 16 || (long long)p.B * p.H * nblk >= kSimds) && p.N <= 32 && p.causal == 0 && !(p.smooth & SAGEBWD_SMOOTH_Q) && !(p.flags & SAGEBWD_FLAG_QK_NORM) && !big_blocks(p);
 }
 
 template <int D>

@@ -37,7 +37,7 @@ def _against_oracle(Q, K, V, p, heads):
 # 1 to 32 query rows, one wave with several blocks
 @pytest.mark.parametrize("B,H,Nq,Nk,d,k_smooth,token_major", [
     (1, 2, 1, 1, 128, True, False), (1, 2, 1, 64, 64, True, False), (1, 3, 5, 200, 64, False, True), (1, 2, 32, 256, 128, True, False),
-    (1, 2, 3, 257, 128, True, False), (2, 3, 7, 2049, 64, True, True), (1, 1, 31, 8192, 128, True, False), (8, 32, 1, 640, 128, True, False)])
+    (1, 2, 3, 257, 128, True, False), (2, 3, 7, 2049, 64, True, True), (1, 1, 31, 8192, 128, True, False), (8, 32, 1, 640, 128, True, False), (1, 2, 9, 1024, 128, True, False), (1, 2, 2, 1023, 64, False, True)])
 def test_decode(B, H, Nq, Nk, d, k_smooth, token_major):
     Q, K, V = _inputs(B, H, Nq, Nk, d)
     p = binding.SageParams(B, H, Nq, d, causal=False, k_smooth=k_smooth, Nkv=Nk, token_major=token_major)
