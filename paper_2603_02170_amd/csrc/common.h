@@ -140,24 +140,26 @@ struct RowView {
 // are then the lightest of several heads, not of one.  That shortens the tail of short-sequence
 // launches (13 % of the step at N = 2048); at N = 8192 the compute kernels lose 2 % to it (several
 // heads' operands compete for the L2), so they take one head at a time there.
-// Other head counts are laid out densely, head after head: no workgroup is without
-// work (it would still queue for a whole workgroup's LDS and wave slots before it could exit) and a
-// single head spreads over all XCDs instead of one.
+// Other head counts are laid out densely over the XCDs: no workgroup is without work (it would still queue for a whole
+// workgroup's LDS and wave slots before it could exit) and a single head spreads over all XCDs instead of one.
+// Short sequences take the items heaviest first over ALL heads (head after head, the heaviest items of the
+// last heads start last: the backward of 36 heads of N = 1777 took half as long again as its work), longer ones over
+// sets of up to four heads, as above.
 struct WorkItem {
   int head, item;
 };
-// head_set > 0: that many heads of an XCD per set; head_set < 0: the dense layout (written as a set of
-// one head on a machine of one XCD, so that the mapping below stays one formula)
+// > 0: that many heads of an XCD per set; < 0: the dense layout, sets of that many heads (on a machine of one XCD, so to
+// speak, so that the mapping below stays one formula).  A set divides the heads evenly.
 __host__ __device__ inline int head_set_for(int items, int heads, bool always = false) {
-  if (heads % 8 != 0) return -1;
-  const int per_xcd = heads / 8;
-  int hs = (always || items <= 32) ? 4 : 1;
-  while (hs > 1 && per_xcd % hs != 0) hs >>= 1;
-  return hs;
+  const bool dense = heads % 8 != 0;
+  const int pool = dense ? heads : heads / 8;
+  int hs = dense && items <= 32 ? pool : (always || dense || items <= 32) ? 4 : 1;
+  while (pool % hs != 0) hs--;
+  return dense ? -hs : hs;
 }
 __host__ __device__ inline int grid_for(int heads, int items) { return heads * items; }
 __device__ inline WorkItem work_item(int block, int items, int head_set) {
-  const int xcds = head_set < 0 ? 1 : 8, hs = head_set < 0 ? 1 : head_set;
+  const int xcds = head_set < 0 ? 1 : 8, hs = head_set < 0 ? -head_set : head_set;
   const int xcd = block % xcds, slot = block / xcds;
   const int hset = slot / (items * hs), rem = slot % (items * hs);
   return WorkItem{xcd + xcds * (hset * hs + rem % hs), rem / hs};

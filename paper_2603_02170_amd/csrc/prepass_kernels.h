@@ -124,12 +124,6 @@ __global__ void __launch_bounds__(256) kmean_partial_kernel(const unsigned short
 // stage 1: 512 rows of d = 128 cost a workgroup about 1.7 us, a launch about 3.
 inline bool mean_inline(int N, int D) { return (long long)N * D <= 65536; }
 
-__global__ void fill_zero_f32_kernel(float* __restrict__ p, size_t n) {
-  size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-  const size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (; i < n; i += stride) p[i] = 0.f;
-}
-
 // The rounding of psi on 16 values held as FP32: q = rne(x * r) clamped to +-127 (needed only where r = 127 / max|x|
 // overflows: blocks of the smallest numbers), packed into four registers.  x * r is rounded to FP32 before the addition that takes it to an integer, so the
 // codes are those of rintf.
@@ -342,6 +336,9 @@ __global__ void __launch_bounds__(256) prepass_quant_kernel(QuantJobs jobs) {
     __syncthreads();
     subtract_mu();
   }
+
+  if (jb.mu_head_out != nullptr && !(INLINE_MEAN && jb.mean_inline) && jb.mean_part == nullptr && blk == 0 && t < D)
+    jb.mu_head_out[(size_t)bh * D + t] = 0.f;                               // no K-smoothing: the mean that was subtracted
 
   if (jb.mu_block_out != nullptr) {
     // block mean over the rows of the numerics block that exist: float64 column sums (exact for bf16 data; zeros where

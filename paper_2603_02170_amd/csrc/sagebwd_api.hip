@@ -243,14 +243,9 @@ int run_prepass(const void* Q, const void* K, const void* V, const void* dO, con
   const bool inline_mean = ks && mean_inline(Nk, D);
   const QkNorm norm_q{qkn ? p.qk_gamma_q : nullptr, p.qk_norm_eps}, norm_k{qkn ? p.qk_gamma_k : nullptr, p.qk_norm_eps};
   if (want_qk) {
-    if (ks) {
-      if (!inline_mean) {
-        const int rc = launch_kmean<D>(K, kview, p, ws, w, norm_k, st);
-        if (rc != SAGEBWD_OK) return rc;
-      }
-    } else {
-      fill_zero_f32_kernel<<<(BH * D + 255) / 256, 256, 0, st>>>(muK, (size_t)BH * D);
-      SAGE_LAUNCH_CHECK();
+    if (ks && !inline_mean) {
+      const int rc = launch_kmean<D>(K, kview, p, ws, w, norm_k, st);
+      if (rc != SAGEBWD_OK) return rc;
     }
   }
   QuantJobs jobs;
