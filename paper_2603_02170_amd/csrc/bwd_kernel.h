@@ -606,6 +606,340 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_kernel(BwdArgs args) {
   }
 }
 
+// ---- one KV block per workgroup ------------------------------------------------------------------------
+// sage_bwd_single_kernel (numerics blocks of 64 x 64).  The kernel above gives each group of four waves a KV block and all
+// three phases; one of its intervals takes about 4850 cycles, and a call with few heads takes the time of one
+// workgroup's chain of intervals.  Here the eight waves share ONE KV block and divide the phases: waves 0-3 ("front") run
+// phases Q and A, waves 4-7 ("back") issue every copy and run phase B, so an interval takes about 2700 cycles for half as
+// many tiles, and twice as many workgroups share the work.  Each SIMD has one wave of either kind.  The arithmetic of
+// every value and its order are those of sage_bwd_kernel, so both give the same bits.
+// Measured, backward kernel in us: 8 heads of N = 1000 d = 128: 43 -> 28; 4 heads of 4096: 131 -> 78; 32 heads of 2048: 89 -> 103
+// (a full machine pays for staging the Q side once per KV block instead of once per two).  At d = 64 two of these workgroups
+// fit a CU (120 registers, 81 KB of LDS), four waves to a SIMD: 64 heads of N = 8192: 1772 -> 1598.
+//
+// The front waves hold V in registers (no accumulators there), and the phases' operands come two intervals ahead in three
+// stages each: a back wave waits for the copies of the interval before, and a front wave (whose only global memory
+// operations are the stores of psi(dS)) for none.
+template <int D>
+struct BwdStageA1 {           // operands of phase A for one Q block
+  int8_t qf[64 * D];          // Q^  F fragments
+  int8_t dof[128 * D];        // bf16 dO as A fragments, XOR-swizzled slots (see BwdStageA)
+  float nl2[64];              // -L * log2(e)
+  float dl[64];               // -delta
+  float bias[64];             // Q-smoothing logit bias of this Q block for the workgroup's 64 keys
+};
+template <int D>
+struct BwdStageB1 {           // operands of phase B for one Q block
+  int8_t qt[64 * D];          // Q^  TF fragments
+  int8_t dot[64 * D];         // dO^ TF fragments
+  float muq[D];               // Q-smoothing block mean
+};
+
+template <int D, bool CAUSAL, bool QSMOOTH>
+__global__ void __launch_bounds__(512, 1) sage_bwd_single_kernel(BwdArgs args) {
+  constexpr int KS = D / 32;     // INT8 k-steps over d; channel blocks
+  constexpr int KB = D / 16;     // bf16 k-steps over d
+  constexpr int NPB = KS / 2;    // 32-row blocks per wave in phase B
+  constexpr int TILE = 64 * D;
+  constexpr int NF = TILE / 1024;
+  struct Lds {
+    BwdStageA1<D> stA[3];
+    BwdStageB1<D> stB[3];
+    BwdExchange xch[2];                             // [tile parity]
+    unsigned red[2][4][2];                          // [tile parity][wave][max P, max |dS|] as bit patterns
+    float scl[2][2];                                // [tile parity][s_P, s_dS]
+    float csum[QSMOOTH ? 3 * 2 * 64 : 1];           // [tile % 3][q half][key]: column sums of dS
+  };
+  __shared__ __attribute__((aligned(16))) Lds L;
+
+  const int N = args.N;
+  const int nblk = N / kBlock;        // KV blocks
+  const int nqblk = args.Nq / kBlock; // Q blocks
+  const int sb = CAUSAL ? args.shift_blocks : 0;
+  const WorkItem wi = work_item(blockIdx.x, nblk, args.head_set);
+  const int hl = wi.head;
+  if (hl >= args.BH) return;
+  const int bh = args.bh0 + hl;
+  const int j = wi.item;              // small j = most Q blocks under the causal mask: scheduled first
+  const int kvalid = min(64, args.nvalid - 64 * j);
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool front = wave < 4;
+  const int w4 = wave & 3;
+  const int ll = lane & 31, h = lane >> 5;
+  const int qb = w4 >> 1, kb = w4 & 1;                     // phase A quadrant
+  const int cb = (D == 128) ? w4 : (w4 & 1);               // phase B channel block
+  const int blk0 = (D == 128) ? 0 : (w4 >> 1);             // phase B first 32-row block
+
+  const size_t qhead = (size_t)bh * args.Nq * D;
+  const size_t rs = args.cv.row_stride, rsq = args.cvq.row_stride;
+  const size_t chead = args.cv.row(bh, 0), cqhead = args.cvq.row(bh, 0);
+  const float* sQh = args.sQ + (size_t)bh * nqblk;
+  const float* sdOh = args.sdO + (size_t)bh * nqblk;
+  const int itop = nqblk - 1;
+  const int i_first = CAUSAL ? max(j - sb, 0) : 0;
+  const int T = itop - i_first + 1;                        // tile t = Q block itop - t (at least one: the diagonal)
+
+  // One of this wave's copies for Q block i (back waves): phase A's fragments are dealt to the four waves, then phase B's.
+  // (Blocks past the last tile repeat it: every interval issues the same copies, so that they can be counted.)
+  auto copy_A = [&](int i, BwdStageA1<D>& st, auto last_tag) __attribute__((always_inline)) {
+    constexpr bool LAST = decltype(last_tag)::value;       // Q block i may be the partial last one
+    const size_t toff = qhead + (size_t)i * TILE;
+#pragma unroll
+    for (int k = 0; k < 3 * NF / 4; k++) {
+      const int o = w4 + 4 * k;
+      if (4 * k < NF) {
+        async_copy_16(args.QF + toff + o * 1024 + lane * 16, st.qf + o * 1024);
+      } else {
+        const int f = o - NF;
+        const int rb = f / KB, sst = f % KB;
+        const unsigned orig = lane ^ (sst & 7);
+        int row = 64 * i + 32 * rb + (int)(orig & 31);
+        if constexpr (LAST) row = min(row, args.nq_valid - 1);
+        async_copy_16(args.dO + cqhead + (size_t)row * rsq + 16 * sst + 8 * (orig >> 5), st.dof + f * 1024);
+      }
+    }
+    const float* vsrc = ((w4 & 1) ? args.delta : args.nL2) + (size_t)bh * args.Nq + 64 * i;
+    async_copy_4(vsrc + lane, (w4 & 1) ? st.dl : st.nl2);
+    if constexpr (QSMOOTH) async_copy_4(args.bias + ((size_t)bh * nqblk + i) * N + 64 * j + lane, st.bias);
+  };
+  auto copy_B = [&](int i, BwdStageB1<D>& st) __attribute__((always_inline)) {
+    const size_t toff = qhead + (size_t)i * TILE;
+#pragma unroll
+    for (int k = 0; k < 2 * NF / 4; k++) {
+      const int o = w4 + 4 * k;
+      if (4 * k < NF) async_copy_16(args.QT + toff + o * 1024 + lane * 16, st.qt + o * 1024);
+      else async_copy_16(args.dOT + toff + (o - NF) * 1024 + lane * 16, st.dot + (o - NF) * 1024);
+    }
+    if constexpr (QSMOOTH) {
+      const int part = D == 128 ? (w4 & 1) * 64 : 0;
+      async_copy_4(args.muQ + ((size_t)bh * nqblk + i) * D + part + lane, st.muq + part);
+    }
+  };
+  constexpr int COPIES = 5 * NF / 4 + 1 + (QSMOOTH ? 2 : 0);   // per back wave and interval
+  static_assert(NF % 4 == 0 && COPIES < 64, "fragments dealt evenly; vmcnt has six bits");
+
+  if (!front) {
+    copy_A(itop, L.stA[0], std::true_type{});
+    copy_A(max(itop - 1, i_first), L.stA[1], std::true_type{});
+  }
+
+  if (front) {
+    // ================= front waves: phases Q and A, quadrant (qb, kb) =================
+    __builtin_amdgcn_s_setprio(1);     // (the longer chain of the two; 2 to 5 % where workgroups share a CU)
+    const float sKj = args.sK[(size_t)bh * nblk + j];
+    v4i kfr[KS];
+    v8bf vb[KB];
+    {
+      const int8_t* p = args.KF + (size_t)bh * N * D + ((size_t)(2 * j + kb) * KS) * 1024 + lane * 16;
+#pragma unroll
+      for (int s = 0; s < KS; s++) kfr[s] = *(const v4i*)(p + s * 1024);
+      // (a key row that does not exist re-reads the last one that does: its P is masked to zero)
+      const unsigned short* pv = args.V + chead + (size_t)min(64 * j + 32 * kb + ll, args.nvalid - 1) * rs + 8 * h;
+#pragma unroll
+      for (int s = 0; s < KB; s++) vb[s] = *(const v8bf*)(pv + 16 * s);
+    }
+    float p[16], ds[16];           // P and dS of the tile between its phases A and Q
+    v4i qa[KS];
+    v8bf da[KB];
+    auto read_A = [&](const int t) __attribute__((always_inline)) {
+      const BwdStageA1<D>& st = L.stA[t % 3];
+#pragma unroll
+      for (int s = 0; s < KB; s++) {
+        if (s % 2 == 0) qa[s / 2] = *(const v4i*)(st.qf + ((qb * KS + s / 2) * 64 + lane) * 16);
+        da[s] = *(const v8bf*)(st.dof + ((qb * KB + s) * 64 + (lane ^ (s & 7))) * 16);
+      }
+    };
+    auto phase_Q = [&](const int t) __attribute__((always_inline)) {   // tile t
+      BwdExchange& X = L.xch[t & 1];
+      const unsigned(&R)[4][2] = L.red[t & 1];
+      const unsigned pu = max(max(R[0][0], R[1][0]), max(R[2][0], R[3][0]));
+      const unsigned du = max(max(R[0][1], R[1][1]), max(R[2][1], R[3][1]));
+      const float pm = __uint_as_float(pu), dm = __uint_as_float(du);
+      const float rP = pm > 0.f ? 127.0f * __builtin_amdgcn_rcpf(pm) : 0.f;
+      const float rS = dm > 0.f ? 127.0f * __builtin_amdgcn_rcpf(dm) : 0.f;
+      const float sP = pm * (1.0f / 127.0f), sS = dm * (1.0f / 127.0f);
+      v4i pf, df;
+#pragma unroll
+      for (int aa = 0; aa < 4; aa++) {
+        unsigned ub[4];
+#pragma unroll
+        for (int b = 0; b < 4; b++) ub[b] = __float_as_uint(__builtin_fmaf(ds[4 * aa + b], rS, kRoundMagic));
+        df[aa] = (int)(__builtin_amdgcn_perm(ub[1], ub[0], 0x0c0c0400u) | __builtin_amdgcn_perm(ub[3], ub[2], 0x04000c0cu));
+      }
+#pragma unroll
+      for (int aa = 0; aa < 4; aa++) {
+        unsigned up = 0;
+#pragma unroll
+        for (int b = 0; b < 4; b++) up = __builtin_amdgcn_cvt_pk_u8_f32(p[4 * aa + b] * rP, b, up);
+        pf[aa] = (int)up;
+      }
+      *(v4i*)(X.pb + ((qb * 2 + kb) * 64 + lane) * 16) = pf;
+      *(v4i*)(X.dsb + ((qb * 2 + kb) * 64 + lane) * 16) = df;
+      L.scl[t & 1][0] = sP;        // (the same values from every lane)
+      L.scl[t & 1][1] = sS;
+      const size_t tile = ((size_t)hl * nqblk + (itop - t)) * args.ds_pitch + j;
+      *(v4i*)(args.dSq + tile * 4096 + ((qb * 2 + kb) * 64 + lane) * 16) = df;
+      args.sdS[tile] = sS;
+    };
+    // (the operands of the products, qa and da, have been read)
+    auto phase_A = [&](const int t, const float sq, auto mask_tag) __attribute__((always_inline)) {
+      constexpr bool MASK = decltype(mask_tag)::value;
+      const BwdStageA1<D>& st = L.stA[t % 3];
+      v16i sacc;
+      v16f dp;
+      const float* dl = st.dl + 32 * qb + 4 * h;
+      if constexpr (QSMOOTH) {
+#pragma unroll
+        for (int r = 0; r < 16; r++) dp[r] = 0.f;
+      } else {
+#pragma unroll
+        for (int aa = 0; aa < 4; aa++) {
+          const v4f d4 = *(const v4f*)(dl + 8 * aa);
+#pragma unroll
+          for (int b = 0; b < 4; b++) dp[4 * aa + b] = d4[b];
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < 16; r++) sacc[r] = 0;
+#pragma unroll
+      for (int s = 0; s < KB; s++) {
+        if (s % 2 == 0) sacc = __builtin_amdgcn_mfma_i32_32x32x32_i8(qa[s / 2], kfr[s / 2], sacc, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(da[s], vb[s], dp, 0, 0, 0);
+      }
+      const float c = sq * sKj * args.scale_log2e;
+      float bias_l = 0.f;
+      if constexpr (QSMOOTH) bias_l = st.bias[32 * kb + ll];
+      const int ia = itop - t;
+      float pm, dm, cs;
+      if constexpr (MASK)
+        bwd_quadrant<true, QSMOOTH>(sacc, dp, st.nl2 + 32 * qb + 4 * h, dl, c, bias_l, 32 * qb + 4 * h, 32 * kb + ll, CAUSAL && ia + sb == j,
+                                    kvalid, p, ds, pm, dm, cs);
+      else
+        bwd_quadrant<false, QSMOOTH>(sacc, dp, st.nl2 + 32 * qb + 4 * h, dl, c, bias_l, 0, 0, false, 64, p, ds, pm, dm, cs);
+      pm = wave_max_nonneg_f32(pm);
+      dm = wave_max_nonneg_f32(dm);
+      L.red[t & 1][w4][0] = __float_as_uint(pm);
+      L.red[t & 1][w4][1] = __float_as_uint(dm);
+      if constexpr (QSMOOTH) {
+        cs = half_swap_sum_f32(cs);
+        if (h == 0) L.csum[((t % 3) * 2 + qb) * 64 + 32 * kb + ll] = cs;
+      }
+    };
+    barrier_all_memory();
+    float sq = scalar_load(sQh + itop);
+    // unmasked tiles: 0 .. t_plain - 1
+    const int t_plain = kvalid < 64 ? 0 : (CAUSAL && i_first + sb == j ? T - 1 : T);
+    for (int t = 0; t < T + 2; t++) {
+      const float sqn = scalar_load(sQh + max(itop - t - 1, i_first));
+      if (t >= 1 && t < t_plain) {
+        read_A(t);
+        phase_Q(t - 1);
+        phase_A(t, sq, std::false_type{});
+      } else {
+        if (t >= 1 && t <= T) phase_Q(t - 1);
+        if (t < T) {
+          read_A(t);
+          phase_A(t, sq, std::true_type{});      // (the masked form leaves unmasked entries as they are)
+        }
+      }
+      sq = sqn;
+      barrier_lds_only();
+    }
+    return;
+  }
+
+  // ================= back waves: the copies, phase B, channel block cb =================
+  v16f dvacc[NPB], dkacc[NPB], dkbias[QSMOOTH ? NPB : 1];
+#pragma unroll
+  for (int t = 0; t < NPB; t++)
+#pragma unroll
+    for (int r = 0; r < 16; r++) {
+      dvacc[t][r] = 0.f;
+      dkacc[t][r] = 0.f;
+      if constexpr (QSMOOTH) dkbias[t][r] = 0.f;
+    }
+  barrier_all_memory();
+  float sq0 = 0.f, sd0 = 0.f, sq1 = 0.f, sd1 = 0.f;          // s_Q, s_dO of tiles t - 2 and t - 1
+  for (int t = 0; t < T + 2; t++) {
+    const int in = max(itop - t, i_first);
+    copy_A(max(itop - t - 2, i_first), L.stA[(t + 2) % 3], std::false_type{});
+    copy_B(in, L.stB[t % 3]);
+    const float sqn = scalar_load(sQh + in), sdn = scalar_load(sdOh + in);
+    if (t >= 2) {
+      const BwdStageB1<D>& st = L.stB[(t - 2) % 3];
+      const BwdExchange& X = L.xch[t & 1];
+      const float w_dv = L.scl[t & 1][0] * sd0;
+      const float w_dk = L.scl[t & 1][1] * sq0 * args.sm_scale;
+#pragma unroll
+      for (int tt = 0; tt < NPB; tt++) {
+        const int kbo = blk0 + tt;
+        v16i av, ak;
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+          av[r] = 0;
+          ak[r] = 0;
+        }
+#pragma unroll
+        for (int qs = 0; qs < 2; qs++) {
+          const v4i a1 = *(const v4i*)(st.dot + ((qs * KS + cb) * 64 + lane) * 16);
+          const v4i b1 = *(const v4i*)(X.pb + ((qs * 2 + kbo) * 64 + lane) * 16);
+          av = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, b1, av, 0, 0, 0);
+          const v4i a2 = *(const v4i*)(st.qt + ((qs * KS + cb) * 64 + lane) * 16);
+          const v4i b2 = *(const v4i*)(X.dsb + ((qs * 2 + kbo) * 64 + lane) * 16);
+          ak = __builtin_amdgcn_mfma_i32_32x32x32_i8(a2, b2, ak, 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+          dvacc[tt][r] = __builtin_fmaf((float)av[r], w_dv, dvacc[tt][r]);
+          dkacc[tt][r] = __builtin_fmaf((float)ak[r], w_dk, dkacc[tt][r]);
+        }
+        if constexpr (QSMOOTH) {
+          const float* cs2 = L.csum + (((t - 2) % 3) * 2) * 64;
+          const float csv = cs2[32 * kbo + ll] + cs2[64 + 32 * kbo + ll];
+#pragma unroll
+          for (int aa = 0; aa < 4; aa++) {
+            const v4f m4 = *(const v4f*)(st.muq + 32 * cb + 8 * aa + 4 * h);
+#pragma unroll
+            for (int b = 0; b < 4; b++) dkbias[tt][4 * aa + b] = __builtin_fmaf(csv, m4[b], dkbias[tt][4 * aa + b]);
+          }
+        }
+      }
+    }
+    sq0 = sq1;
+    sd0 = sd1;
+    sq1 = sqn;
+    sd1 = sdn;
+    __builtin_amdgcn_s_waitcnt(vmcnt_only(COPIES));          // the copies of the interval before have landed
+    barrier_lds_only();
+  }
+  // ---- write dV, dK (bf16) ----
+#pragma unroll
+  for (int t = 0; t < NPB; t++) {
+    const int key = 64 * j + 32 * (blk0 + t) + ll;
+    unsigned short* pv = args.dV + chead + (size_t)key * rs + 32 * cb + 4 * h;
+    unsigned short* pk = args.dK + chead + (size_t)key * rs + 32 * cb + 4 * h;
+#pragma unroll
+    for (int aa = 0; aa < 4; aa++) {
+      v4us ov, ok;
+#pragma unroll
+      for (int b = 0; b < 4; b++) {
+        float kv = dkacc[t][4 * aa + b];
+        if constexpr (QSMOOTH) kv = __builtin_fmaf(dkbias[t][4 * aa + b], args.sm_scale, kv);
+        ov[b] = float_to_bf16_bits(dvacc[t][4 * aa + b]);
+        ok[b] = float_to_bf16_bits(kv);
+      }
+      if (key < args.nvalid) {
+        *(v4us*)(pv + 8 * aa) = ov;
+        *(v4us*)(pk + 8 * aa) = ok;
+      }
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(vmcnt_only(0));                 // (the copies past the last tile land before the LDS is given up)
+}
+
 // ---------------------------------------------------------------------------------
 // dQ_i = sum_j (dS^_ij K^_j) * s_dS(i,j) * s_K(j) * sm_scale        (Algorithm 2, the dQ line)
 // A = the stored psi(dS) fragments, transposed here, B = K^ in TF layout.

@@ -353,8 +353,8 @@ int prepass_for_backward(const void* Q, const void* K, const void* V, const void
 // that stages every K^/V^ tile once for twice as many queries).
 int pick_fwd_waves(int N) { return N % 128 == 0 ? 4 : 2; }
 
-// SIMDs of the machine: what a launch has to fill.
-constexpr int kSimds = 1024;
+// CUs and SIMDs of the machine: what a launch has to fill.
+constexpr int kCus = 256, kSimds = 1024;
 
 // Few queries against many keys: split the keys inside the workgroup (sage_fwd_split_kernel) while 64-query
 // workgroups do not fill the CUs twice over and there are a few tiles for each split.
@@ -417,6 +417,31 @@ int launch_bwd(const BwdArgs& a, bool causal, bool qs, hipStream_t st) {
   } else {
     if (qs) sage_bwd_kernel<D, false, true, MODE, KV128><<<grid, 512, 0, st>>>(args);
     else sage_bwd_kernel<D, false, false, MODE, KV128><<<grid, 512, 0, st>>>(args);
+  }
+  SAGE_LAUNCH_CHECK();
+  return SAGEBWD_OK;
+}
+
+// One KV block per workgroup (sage_bwd_single_kernel; same bits): while its workgroups are given out in one round (without the
+// mask, where a second round costs as much as the first) or two (with it, where the second is the lighter); at d = 64,
+// where two of its workgroups share a CU (not with Q-smoothing, which needs more registers), at every size but the
+// causal walks of one or two Q blocks (256 heads of N = 128: 14.9 us, 14.6 the other way).
+bool use_bwd_single(const BwdArgs& a, int d, bool causal, bool qs) {
+  if ((long long)a.BH * (a.N / 64) <= (causal ? 2 * kCus : kCus)) return true;
+  return d == 64 && !qs && !(causal && a.Nq <= 128);
+}
+template <int D>
+int launch_bwd_single(const BwdArgs& a, bool causal, bool qs, hipStream_t st) {
+  const int nblk = a.N / 64;
+  BwdArgs args = a;
+  args.head_set = head_set_for(nblk, a.BH);
+  const int grid = grid_for(a.BH, nblk);
+  if (causal) {
+    if (qs) sage_bwd_single_kernel<D, true, true><<<grid, 512, 0, st>>>(args);
+    else sage_bwd_single_kernel<D, true, false><<<grid, 512, 0, st>>>(args);
+  } else {
+    if (qs) sage_bwd_single_kernel<D, false, true><<<grid, 512, 0, st>>>(args);
+    else sage_bwd_single_kernel<D, false, false><<<grid, 512, 0, st>>>(args);
   }
   SAGE_LAUNCH_CHECK();
   return SAGEBWD_OK;
@@ -775,7 +800,10 @@ int sagebwd_bwd(const void* Q, const void* K, const void* V, const void* O, cons
     {
       ScopedTimer tm(SAGEBWD_KERNEL_BWD, st);
       const bool causal = params->causal != 0;
-      if (!big) {
+      if (!big && use_bwd_single(a, d, causal, qs)) {
+        rc = d == 64 ? launch_bwd_single<64>(a, causal, qs, st) : launch_bwd_single<128>(a, causal, qs, st);
+        if (rc != SAGEBWD_OK) return rc;
+      } else if (!big) {
         rc = d == 64 ? launch_bwd<64, kBwdFused>(a, causal, qs, st) : launch_bwd<128, kBwdFused>(a, causal, qs, st);
         if (rc != SAGEBWD_OK) return rc;
       } else if (block_q(*params) == 64) {
