@@ -154,7 +154,10 @@ constexpr int kBwdFused = 0, kBwdMaxOnly = 1, kBwdPairedRows = 2;
 // tile does not exist in an interval, above the diagonal or past the last KV block, contributes zeros); 64 x 128
 // blocks therefore need one sweep only.
 template <int D, bool CAUSAL, bool QSMOOTH, int MODE = kBwdFused, bool KV128 = false>
-__global__ void __launch_bounds__(512, 1) sage_bwd_kernel(BwdArgs args) {
+__global__ void __launch_bounds__(512, MODE == kBwdMaxOnly ? 4 : 1) sage_bwd_kernel(BwdArgs args) {
+  // kBwdMaxOnly has no accumulators and no phase B: V stays in registers, the buffers of phase B go, and two workgroups
+  // share a CU (52 KB of LDS, 128 registers)
+  constexpr bool VREG = MODE == kBwdMaxOnly;
   constexpr int ISTEP = MODE == kBwdMaxOnly ? 2 : 1;     // Q blocks between two tiles of the walk
   constexpr int KS = D / 32;     // INT8 k-steps over d; channel blocks
   constexpr int KB = D / 16;     // bf16 k-steps over d
@@ -166,17 +169,17 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_kernel(BwdArgs args) {
   // then makes reads of buffers that no asynchronous copy ever writes wait for all copies in flight.
   struct Lds {
     BwdStageA<D> stA[2];
-    BwdStageB<D> stB[2];
-    BwdExchange xch[2][2];                          // [group][tile parity]
-    int8_t vst[2][2 * D * 64];                      // [group]: bf16 V_j as B fragments (key block, 16-channel step)
+    __attribute__((aligned(16))) int8_t stB_bytes[VREG ? 16 : 2 * sizeof(BwdStageB<D>)];
+    __attribute__((aligned(16))) int8_t xch_bytes[VREG ? 16 : 4 * sizeof(BwdExchange)];   // [group][tile parity]
+    int8_t vst[VREG ? 1 : 2][VREG ? 16 : 2 * D * 64];   // [group]: bf16 V_j as B fragments (key block, 16-channel step)
     unsigned red[2][2][4][2];                       // [group][tile parity][wave][max P, max |dS|] as bit patterns
     float csum[QSMOOTH ? 2 * 3 * 2 * 64 : 1];       // [group][tile % 3][q half][key]: column sums of dS
     float tmx[MODE == kBwdPairedRows ? 2 * 2 * 64 : 1];   // [tile parity][group][even lanes: max P, odd lanes: max |dS|]
   };
   __shared__ __attribute__((aligned(16))) Lds L;
   auto& stA = L.stA;
-  auto& stB = L.stB;
-  auto& xch = L.xch;
+  auto& stB = *(BwdStageB<D>(*)[2])L.stB_bytes;
+  auto& xch = *(BwdExchange(*)[2][2])L.xch_bytes;
   auto& vst = L.vst;
   auto& red = L.red;
   auto& csum = L.csum;
@@ -226,8 +229,14 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_kernel(BwdArgs args) {
   // step s), lane (key, half) holding V[key][16 s + 8 half .. + 8]; 16 fragments (d = 128) dealt
   // to the group's 4 waves.  Keeping it in registers instead would cost 32 of them, which the
   // prefetch of the streamed operands needs more.
+  v8bf vreg[VREG ? KB : 1];
+  if constexpr (VREG) {
+    const unsigned short* pv = args.V + chead + (size_t)min(64 * jc + 32 * kb + ll, args.nvalid - 1) * rs + 8 * h;
 #pragma unroll
-  for (int k = 0; k < (2 * KB + 3) / 4; k++) {
+    for (int s = 0; s < KB; s++) vreg[s] = *(const v8bf*)(pv + 16 * s);
+  }
+#pragma unroll
+  for (int k = 0; k < (VREG ? 0 : (2 * KB + 3) / 4); k++) {
     const int f = w4 + 4 * k;
     if (f < 2 * KB) {
       const int fkb = f / KB, fs = f % KB;
@@ -498,11 +507,12 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_kernel(BwdArgs args) {
       v4i qa[KS];
       v8bf da[KB], vb[KB];
       const int8_t* qfp = st.qf + (qb * KS * 64 + lane) * 16;
-      const int8_t* vbp = vst[grp] + (kb * KB * 64 + lane) * 16;
+      const int8_t* vbp = vst[VREG ? 0 : grp] + (kb * KB * 64 + lane) * 16;
       auto ld = [&](int s) {
         if (s % 2 == 0) qa[s / 2] = *(const v4i*)(qfp + (s / 2) * 1024);
         da[s] = *(const v8bf*)(st.dof + ((qb * KB + s) * 64 + (lane ^ (s & 7))) * 16);
-        vb[s] = *(const v8bf*)(vbp + s * 1024);
+        if constexpr (VREG) vb[s] = vreg[s];
+        else vb[s] = *(const v8bf*)(vbp + s * 1024);
       };
       ld(0);
       ld(1);
