@@ -1,5 +1,5 @@
 """SageBwd hot path for MI355X (gfx950): fused INT8 attention forward and
-backward behind a C-ABI library, with a thin ctypes binding."""
+backward behind a C-ABI library, with a thin binding."""
 from .binding import (  # noqa: F401
     SageParams,
     lib_path,
