@@ -645,6 +645,21 @@ struct BwdStageB1 {           // operands of phase B for one Q block
   float muq[D];               // Q-smoothing block mean
 };
 
+
+// The Q blocks such a workgroup walks, from the last one down: tile t = Q block itop - t, t = 0 .. T - 1.  Interval t
+// copies the operands of phase A of tile t + 2 and of phase B of tile t, past the last tile that one again (never used):
+// every interval issues the same copies, so that they can be counted.  (Host code too: a test goes through every index.)
+struct SingleWalk {
+  int itop, i_first, T;
+  __host__ __device__ SingleWalk(int nqblk, int first) : itop(nqblk - 1), i_first(first), T(nqblk - first) {}
+  __host__ __device__ int at(int t) const { return itop - t > i_first ? itop - t : i_first; }   // Q block of tile t
+  // The partial last Q block is copied by the two first copies, which clamp each row (dO_row_clamped).  The copies inside
+  // the loop do not clamp, and a walk of one tile would repeat that very block there: it repeats the block's first row.
+  __host__ __device__ int loop_row_step() const { return T > 1 ? 1 : 0; }
+};
+// Row of dO that the copy of query row `row` reads: a row that does not exist re-reads the last one that does.
+__host__ __device__ inline int dO_row_clamped(int row, int nq_valid) { return row < nq_valid ? row : nq_valid - 1; }
+
 template <int D, bool CAUSAL, bool QSMOOTH>
 __global__ void __launch_bounds__(512, 1) sage_bwd_single_kernel(BwdArgs args) {
   constexpr int KS = D / 32;     // INT8 k-steps over d; channel blocks
@@ -688,12 +703,11 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_single_kernel(BwdArgs args) {
   const size_t chead = args.cv.row(bh, 0), cqhead = args.cvq.row(bh, 0);
   const float* sQh = args.sQ + (size_t)bh * nqblk;
   const float* sdOh = args.sdO + (size_t)bh * nqblk;
-  const int itop = nqblk - 1;
-  const int i_first = CAUSAL ? max(j - sb, 0) : 0;
-  const int T = itop - i_first + 1;                        // tile t = Q block itop - t (at least one: the diagonal)
+  const SingleWalk walk(nqblk, CAUSAL ? max(j - sb, 0) : 0);   // (at least one tile: the diagonal)
+  const int itop = walk.itop, i_first = walk.i_first, T = walk.T;
+  const size_t rsq_loop = rsq * walk.loop_row_step();
 
-  // One of this wave's copies for Q block i (back waves): phase A's fragments are dealt to the four waves, then phase B's.
-  // (Blocks past the last tile repeat it: every interval issues the same copies, so that they can be counted.)
+  // This wave's copies for Q block i (back waves): phase A's fragments are dealt to the four waves, then phase B's.
   auto copy_A = [&](int i, BwdStageA1<D>& st, auto last_tag) __attribute__((always_inline)) {
     constexpr bool LAST = decltype(last_tag)::value;       // Q block i may be the partial last one
     const size_t toff = qhead + (size_t)i * TILE;
@@ -706,9 +720,9 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_single_kernel(BwdArgs args) {
         const int f = o - NF;
         const int rb = f / KB, sst = f % KB;
         const unsigned orig = lane ^ (sst & 7);
-        int row = 64 * i + 32 * rb + (int)(orig & 31);
-        if constexpr (LAST) row = min(row, args.nq_valid - 1);
-        async_copy_16(args.dO + cqhead + (size_t)row * rsq + 16 * sst + 8 * (orig >> 5), st.dof + f * 1024);
+        const int r = 32 * rb + (int)(orig & 31);
+        const size_t row = LAST ? (size_t)dO_row_clamped(64 * i + r, args.nq_valid) * rsq : (size_t)(64 * i) * rsq + r * rsq_loop;
+        async_copy_16(args.dO + cqhead + row + 16 * sst + 8 * (orig >> 5), st.dof + f * 1024);
       }
     }
     const float* vsrc = ((w4 & 1) ? args.delta : args.nL2) + (size_t)bh * args.Nq + 64 * i;
@@ -733,7 +747,7 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_single_kernel(BwdArgs args) {
 
   if (!front) {
     copy_A(itop, L.stA[0], std::true_type{});
-    copy_A(max(itop - 1, i_first), L.stA[1], std::true_type{});
+    copy_A(walk.at(1), L.stA[1], std::true_type{});
   }
 
   if (front) {
@@ -874,8 +888,8 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_single_kernel(BwdArgs args) {
   barrier_all_memory();
   float sq0 = 0.f, sd0 = 0.f, sq1 = 0.f, sd1 = 0.f;          // s_Q, s_dO of tiles t - 2 and t - 1
   for (int t = 0; t < T + 2; t++) {
-    const int in = max(itop - t, i_first);
-    copy_A(max(itop - t - 2, i_first), L.stA[(t + 2) % 3], std::false_type{});
+    const int in = walk.at(t);
+    copy_A(walk.at(t + 2), L.stA[(t + 2) % 3], std::false_type{});
     copy_B(in, L.stB[t % 3]);
     const float sqn = scalar_load(sQh + in), sdn = scalar_load(sdOh + in);
     if (t >= 2) {
