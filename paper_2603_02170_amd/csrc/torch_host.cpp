@@ -326,6 +326,14 @@ struct SageAttentionBackward : torch::autograd::Node {
   }
 };
 
+// A tensor whose data alone is not what the caller asked about: a dual tensor of forward-mode AD (its tangent would be
+// dropped, which reads as a zero derivative), or one wrapped by a torch.func transform.
+bool is_transformed(const Tensor& t) {
+  constexpr c10::DispatchKeySet wrappers({c10::DispatchKey::FuncTorchBatched, c10::DispatchKey::BatchedNestedTensor,
+                                          c10::DispatchKey::FuncTorchGradWrapper});
+  return torch::autograd::isFwGradDefined(t) || t.key_set().has_any(wrappers);
+}
+
 // attention(Q, K, V, causal, k_smooth, q_smooth, sm_scale, token_major, share_quantized) -> (O, LSE)
 PyObject* py_attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
   HANDLE_TH_ERRORS
@@ -333,6 +341,11 @@ PyObject* py_attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
   for (int k = 0; k < 3; k++) {
     if (!THPVariable_Check(a[k])) {
       PyErr_SetString(PyExc_TypeError, "sage_attention: Q, K, V are tensors");
+      return nullptr;
+    }
+    if (is_transformed(THPVariable_Unpack(a[k]))) {
+      PyErr_SetString(PyExc_NotImplementedError,
+                      "sage_attention has no forward-mode derivative and no rule for torch.func transforms (vmap, grad, jvp, ...)");
       return nullptr;
     }
   }
