@@ -54,8 +54,15 @@ struct Params {
   std::array<int64_t, 3> lse_shape() const { return {c.B, c.H, c.N}; }
 };
 
-bool read_int(PyObject* o, PyObject* name, int32_t* out) {
+// (the conversions of SageParams.c(): the sizes have to be integers, the other numbers go through int() and float())
+PyObject* get_int(PyObject* o, PyObject* name) {
   PyObject* v = PyObject_GetAttr(o, name);
+  if (v == nullptr || PyLong_CheckExact(v)) return v;
+  PyObject* i = PyNumber_Long(v);
+  Py_DECREF(v);
+  return i;
+}
+bool take_int32(PyObject* v, int32_t* out) {      // (takes the reference)
   if (v == nullptr) return false;
   const long long x = PyLong_AsLongLong(v);
   Py_DECREF(v);
@@ -63,8 +70,10 @@ bool read_int(PyObject* o, PyObject* name, int32_t* out) {
   *out = (int32_t)x;
   return true;
 }
+bool read_size(PyObject* o, PyObject* name, int32_t* out) { return take_int32(PyObject_GetAttr(o, name), out); }
+bool read_int(PyObject* o, PyObject* name, int32_t* out) { return take_int32(get_int(o, name), out); }
 bool read_u64(PyObject* o, PyObject* name, uint64_t* out) {
-  PyObject* v = PyObject_GetAttr(o, name);
+  PyObject* v = get_int(o, name);
   if (v == nullptr) return false;
   *out = PyLong_AsUnsignedLongLongMask(v);
   Py_DECREF(v);
@@ -73,9 +82,12 @@ bool read_u64(PyObject* o, PyObject* name, uint64_t* out) {
 bool read_float(PyObject* o, PyObject* name, float* out) {
   PyObject* v = PyObject_GetAttr(o, name);
   if (v == nullptr) return false;
-  *out = (float)PyFloat_AsDouble(v);
+  PyObject* f = PyNumber_Float(v);
   Py_DECREF(v);
-  return !PyErr_Occurred();
+  if (f == nullptr) return false;
+  *out = (float)PyFloat_AS_DOUBLE(f);
+  Py_DECREF(f);
+  return true;
 }
 bool read_bool(PyObject* o, PyObject* name, bool* out) {
   PyObject* v = PyObject_GetAttr(o, name);
@@ -107,15 +119,14 @@ bool read_gain(PyObject* o, PyObject* name, int32_t d, const float** out) {
 bool read_params(PyObject* o, Params& p) {
   const Names& n = g_names;
   sagebwd_params& c = p.c;
-  bool causal, ks, qs, tm, share;
+  bool ks, qs, tm, share;
   c.reserved = 0;
-  if (!read_int(o, n.B, &c.B) || !read_int(o, n.H, &c.H) || !read_int(o, n.N, &c.N) || !read_int(o, n.d, &c.d) ||
-      !read_bool(o, n.causal, &causal) || !read_bool(o, n.k_smooth, &ks) || !read_bool(o, n.q_smooth, &qs) ||
+  if (!read_size(o, n.B, &c.B) || !read_size(o, n.H, &c.H) || !read_size(o, n.N, &c.N) || !read_size(o, n.d, &c.d) ||
+      !read_int(o, n.causal, &c.causal) || !read_bool(o, n.k_smooth, &ks) || !read_bool(o, n.q_smooth, &qs) ||
       !read_float(o, n.sm_scale, &c.sm_scale) || !read_bool(o, n.token_major, &tm) || !read_bool(o, n.share_quantized, &share) ||
       !read_u64(o, n.scratch_budget, &c.scratch_budget) || !read_int(o, n.bq, &c.bq) || !read_int(o, n.bkv, &c.bkv) ||
       !read_int(o, n.Nkv, &c.Nkv) || !read_gain(o, n.qk_gamma_q, c.d, &c.qk_gamma_q) || !read_gain(o, n.qk_gamma_k, c.d, &c.qk_gamma_k))
     return false;
-  c.causal = causal;
   c.smooth = (ks ? SAGEBWD_SMOOTH_K : 0) | (qs ? SAGEBWD_SMOOTH_Q : 0);
   c.layout = tm ? SAGEBWD_LAYOUT_BNHD : SAGEBWD_LAYOUT_BHND;
   c.flags = (share ? SAGEBWD_FLAG_SHARE_QUANTIZED : 0) | (c.qk_gamma_q != nullptr ? SAGEBWD_FLAG_QK_NORM : 0);
@@ -349,13 +360,16 @@ PyObject* py_attention(PyObject*, PyObject* const* a, Py_ssize_t n) {
       return nullptr;
     }
   }
-  int flag[5];
-  const int at_arg[5] = {3, 4, 5, 7, 8};
-  for (int k = 0; k < 5; k++)
+  int flag[4];
+  const int at_arg[4] = {4, 5, 7, 8};
+  for (int k = 0; k < 4; k++)
     if ((flag[k] = PyObject_IsTrue(a[at_arg[k]])) < 0) return nullptr;
-  const double sm_scale = PyFloat_AsDouble(a[6]);
-  if (PyErr_Occurred()) return nullptr;
-  const bool causal = flag[0], ks = flag[1], qs = flag[2], tm = flag[3], share = flag[4];
+  const bool ks = flag[0], qs = flag[1], tm = flag[2], share = flag[3];
+  int32_t causal;
+  if (!take_int32(PyNumber_Long(a[3]), &causal)) return nullptr;
+  THPObjectPtr scale(PyNumber_Float(a[6]));
+  if (!scale) return nullptr;
+  const double sm_scale = PyFloat_AS_DOUBLE(scale.get());
   const Tensor inQ = THPVariable_Unpack(a[0]), inK = THPVariable_Unpack(a[1]), inV = THPVariable_Unpack(a[2]);
   if (inQ.dim() != 4 || inK.dim() != 4) {
     PyErr_SetString(PyExc_ValueError, "sage_attention: Q, K, V need four dimensions");

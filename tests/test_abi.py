@@ -4,7 +4,9 @@ import ctypes
 import os
 import re
 
+import numpy as np
 import pytest
+import torch
 
 from paper_2603_02170_amd import binding
 from paper_2603_02170_amd.binding import SageParams
@@ -149,3 +151,21 @@ def test_probes_reject_bad_arguments_on_the_host(lib):
     assert lib.sagebwd_probe_stream(1, fake, None, 100, 1, fake, None, ctypes.byref(ms)) == INVALID          # not 16-byte pieces
     assert lib.sagebwd_probe_stream(1, ctypes.c_void_p(4100), None, 4096, 1, fake, None, ctypes.byref(ms)) == INVALID   # misaligned
     assert lib.sagebwd_probe_stream(3, fake, fake, 4096, 1, fake, None, ctypes.byref(ms)) == INVALID
+
+
+def test_numbers_of_the_parameters_are_converted_as_the_structure_converts_them(lib):
+    """The native module reads SageParams attribute by attribute: what SageParams.c() converts with int() and float() it
+    has to take, what ctypes refuses it has to refuse.  (CPU tensors: the tensor checks come after the parameters.)"""
+    x = [torch.zeros(1, 1, 64, 64, dtype=torch.bfloat16) for _ in range(3)]
+    for kw in (dict(scratch_budget=4e9), dict(bq=64.0, bkv=128.0), dict(Nkv=64.0), dict(causal=np.bool_(True)), dict(causal=1.0),
+               dict(sm_scale="0.125"), dict(sm_scale=np.float32(0.5)), dict(B=np.int64(1))):
+        p = SageParams(**{**dict(B=1, H=1, N=64, d=64), **kw})
+        p.c()
+        with pytest.raises(ValueError, match="need contiguous cuda"):
+            binding.sagebwd_fwd(*x, p)
+    for kw in (dict(N=64.0), dict(causal=None), dict(scratch_budget=None), dict(sm_scale=None)):
+        p = SageParams(**{**dict(B=1, H=1, N=64, d=64), **kw})
+        with pytest.raises(TypeError):
+            p.c()
+        with pytest.raises(TypeError):
+            binding.sagebwd_fwd(*x, p)

@@ -47,3 +47,11 @@ def test_autograd_wrapper_in_a_training_step():
             W.grad = None
         losses.append(float(loss.detach()))
     assert losses[-1] < 0.97 * losses[0], losses
+
+
+def test_a_causal_flag_that_is_neither_0_nor_1_is_refused():
+    x = [torch.zeros(1, 1, 64, 64, dtype=torch.bfloat16, device="cuda") for _ in range(3)]
+    for call in (lambda: sage_attention(*x, causal=2), lambda: binding.sagebwd_fwd(*x, binding.SageParams(1, 1, 64, 64, causal=2))):
+        with pytest.raises(binding.SageError) as e:
+            call()
+        assert e.value.status == -1
