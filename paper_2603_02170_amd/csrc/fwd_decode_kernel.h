@@ -7,8 +7,9 @@
 // wave takes whole 64-key blocks straight from the caller's tensors: it loads a block of K in the order of
 // the F fragments, finds the block's scale, quantises in registers, forms the logits, and does the same with V,
 // whose fragments one MFMA against the identity turns from (lane = key) to (lane = channel), the operand form of
-// P^V^.  No LDS, no barrier and no traffic but K and V inside the loop.  The arithmetic is the pre-pass's and
-// sage_fwd_kernel's (FP32 decisions of psi included), so codes and scales are the same bits.
+// P^V^.  No LDS, no barrier and no traffic but K and V inside the loop.  psi is the pre-pass's function (quantise_16, clamp
+// and factor included), so codes and scales are the same bits for every input, NaN and blocks whose 127 / max|x| overflows
+// among them; the logits are formed as in sage_fwd_kernel's converting path.
 //
 // Keys are split over waves (four to a workgroup, which meet in LDS) and workgroups (whose partial O, m, l a second
 // small kernel joins).
@@ -61,8 +62,9 @@ __global__ void __launch_bounds__(256, 1) sage_fwd_decode_kernel(DecodeArgs args
       }
     }
   };
-  // values of one fragment (K: minus the mean), zero where the row does not exist
-  auto values = [&](const v8us (&raw)[2], const bool there, const float* mu, float (&x)[16]) __attribute__((always_inline)) {
+  // Values of one fragment (K: minus the mean).  A row that does not exist holds the last one that does, which changes no
+  // maximum of its block; its key is masked, its query not stored.
+  auto values = [&](const v8us (&raw)[2], const float* mu, float (&x)[16]) __attribute__((always_inline)) {
 #pragma unroll
     for (int e = 0; e < 16; e++) x[e] = bf16_bits_to_float(raw[e >> 3][e & 7]);
     if (mu != nullptr) {
@@ -73,37 +75,30 @@ __global__ void __launch_bounds__(256, 1) sage_fwd_decode_kernel(DecodeArgs args
         for (int e = 0; e < 4; e++) x[4 * w + e] = x[4 * w + e] - m[e];
       }
     }
-    if (!there) {
-#pragma unroll
-      for (int e = 0; e < 16; e++) x[e] = 0.f;
-    }
   };
   // codes of a block as F fragments; returns the block's scale
   auto quantise_block = [&](const Raw& raw, const int j, const float* mu, v4i (&f)[2][KS]) __attribute__((always_inline)) {
     float a = 0.f;
 #pragma unroll
     for (int rb = 0; rb < 2; rb++) {
-      const bool there = 64 * j + 32 * rb + r32 < args.nk;
 #pragma unroll
       for (int s = 0; s < KS; s++) {
         float x[16];
-        values(raw.v[rb][s], there, mu == nullptr ? nullptr : mu + 32 * s + 16 * h, x);
+        values(raw.v[rb][s], mu == nullptr ? nullptr : mu + 32 * s + 16 * h, x);
 #pragma unroll
         for (int e = 0; e < 16; e++) a = fmaxf(a, fabsf(x[e]));
       }
     }
     a = wave_max_nonneg_f32(a);
     const bool nz = a > 0.f;
-    // (kept finite: psi then needs no clamp)
-    const float r = nz ? fminf(127.0f / a, 3.402823466e38f) : 0.f;
+    const float r = nz ? 127.0f / a : 0.f;
 #pragma unroll
     for (int rb = 0; rb < 2; rb++) {
-      const bool there = 64 * j + 32 * rb + r32 < args.nk;
 #pragma unroll
       for (int s = 0; s < KS; s++) {
         float x[16];
-        values(raw.v[rb][s], there, mu == nullptr ? nullptr : mu + 32 * s + 16 * h, x);
-        f[rb][s] = quantise_16<false>(x, r);
+        values(raw.v[rb][s], mu == nullptr ? nullptr : mu + 32 * s + 16 * h, x);
+        f[rb][s] = quantise_16(x, r);
       }
     }
     return nz ? a / 127.0f : 0.f;
@@ -127,11 +122,10 @@ __global__ void __launch_bounds__(256, 1) sage_fwd_decode_kernel(DecodeArgs args
       raw[s][0] = *(const v8us*)(p + 32 * s);
       raw[s][1] = *(const v8us*)(p + 32 * s + 8);
     }
-    const bool there = r32 < args.nq;
 #pragma unroll
     for (int s = 0; s < KS; s++) {
       float x[16];
-      values(raw[s], there, nullptr, x);
+      values(raw[s], nullptr, x);
 #pragma unroll
       for (int e = 0; e < 16; e++) a = fmaxf(a, fabsf(x[e]));
     }
@@ -141,7 +135,7 @@ __global__ void __launch_bounds__(256, 1) sage_fwd_decode_kernel(DecodeArgs args
 #pragma unroll
     for (int s = 0; s < KS; s++) {
       float x[16];
-      values(raw[s], there, nullptr, x);
+      values(raw[s], nullptr, x);
       qf[s] = quantise_16(x, r);
     }
     cq = (nz ? a / 127.0f : 0.f) * args.scale_log2e;

@@ -124,10 +124,9 @@ __global__ void __launch_bounds__(256) kmean_partial_kernel(const unsigned short
 // stage 1: 512 rows of d = 128 cost a workgroup about 1.7 us, a launch about 3.
 inline bool mean_inline(int N, int D) { return (long long)N * D <= 65536; }
 
-// The rounding of psi on 16 values held as FP32: q = rne(x * r) clamped to +-127 (needed only where r = 127 / max|x|
-// overflows: blocks of the smallest numbers), packed into four registers.  x * r is rounded to FP32 before the addition that takes it to an integer, so the
+// The rounding of psi on 16 values held as FP32: q = rne(x * r) clamped to +-127 (which matters where r = 127 / max|x|
+// overflows, blocks of the smallest numbers, and for NaN: both become codes), packed into four registers.  x * r is rounded to FP32 before the addition that takes it to an integer, so the
 // codes are those of rintf.
-template <bool CLAMP = true>
 __device__ __forceinline__ v4i quantise_16(const float (&x)[16], const float r) {
   v4i o;
 #pragma unroll
@@ -135,8 +134,7 @@ __device__ __forceinline__ v4i quantise_16(const float (&x)[16], const float r) 
     unsigned u[4];
 #pragma unroll
     for (int e = 0; e < 4; e++) {
-      float y = x[4 * w + e] * r;
-      if constexpr (CLAMP) y = __builtin_amdgcn_fmed3f(y, -127.f, 127.f);
+      const float y = __builtin_amdgcn_fmed3f(x[4 * w + e] * r, -127.f, 127.f);
       u[e] = __float_as_uint(y + 12582912.0f);               // 1.5 * 2^23: rne(y) in the low mantissa bits
     }
     o[w] = (int)(__builtin_amdgcn_perm(u[1], u[0], 0x0c0c0400u) | __builtin_amdgcn_perm(u[3], u[2], 0x04000c0cu));

@@ -87,3 +87,54 @@ def test_two_waves_per_query_group_give_the_same_bits(N, d, causal, normed, q_sm
         torch.cuda.synchronize()
         assert torch.equal(O1[0, 0], O[0, h]) and torch.equal(L1[0, 0], L[0, h]), h
     assert np.isfinite(to_np(O)).all()
+
+
+def _from_the_stored_codes(p, Q, K, V):
+    """The forward in float64 from the codes and scales that the pre-pass stores (its quantiser of P~ included)."""
+    ws = binding.alloc_workspace(p)
+    binding.sagebwd_quantize(Q, K, V, p, ws)
+    (q, sq), (k, sk), (v, sv) = ([t.cpu().numpy().astype(np.float64) for t in binding.sagebwd_export_quantized(p, ws, w)]
+                                 for w in (binding.TENSOR_Q, binding.TENSOR_K, binding.TENSOR_V))
+    nk, nblk = p.kv_len, k.shape[2] // 64
+    O = np.zeros((p.B, p.H, p.N, p.d))
+    for b in range(p.B):
+        for h in range(p.H):
+            o = l = 0.0
+            for j in range(nblk):
+                sl = slice(64 * j, min(64 * j + 64, nk))
+                s = q[b, h, :p.N] @ k[b, h, sl].T * (sq[b, h, 0] * sk[b, h, j] / np.sqrt(p.d))
+                m = s.max(1, keepdims=True)
+                e = 127.0 * np.exp(s - m)
+                w = np.exp(m)                                   # (logits of this test are small)
+                o = o + w * sv[b, h, j] * (np.rint(e) @ v[b, h, sl])
+                l = l + w * e.sum(1, keepdims=True)
+            O[b, h] = o / l
+    return O
+
+
+# what a value that is not a number, an infinite factor 127 / max|x| or a block of zeros becomes is the pre-pass's choice
+# (a code within +-127): a decoding step, which keeps its codes in registers, has to take the same one
+@pytest.mark.parametrize("what", ["plain", "nan_v", "nan_k", "nan_q", "tiny_v", "tiny_some_v", "zero_v"])
+@pytest.mark.parametrize("Nq", [5, 40])       # a decoding step; the same through the workspace
+def test_codes_of_exceptional_blocks(what, Nq):
+    Q, K, V = (t.clone() for t in _inputs(1, 2, Nq, 1100, 64, normed=True))
+    if what == "nan_v":
+        V[0, :, 70:80, 3] = float("nan")
+    elif what == "nan_k":
+        K[0, :, 130, 7] = float("nan")
+    elif what == "nan_q":
+        Q[0, :, 1, 9] = float("nan")
+    elif what == "tiny_v":
+        V = (V.float() * 2.0 ** -126).to(torch.bfloat16)        # 127 / max|v| is infinite
+        V[..., 5] = 0
+    elif what == "tiny_some_v":
+        V[0, :, 64:128] = (V[0, :, 64:128].float() * 2.0 ** -126).to(torch.bfloat16)
+    elif what == "zero_v":
+        V[0, :, 64:640] = 0
+    Q, K, V = (t.cuda() for t in (Q, K, V))
+    p = binding.SageParams(1, 2, Nq, 64, causal=False, k_smooth=False, Nkv=1100)
+    O, _ = binding.sagebwd_fwd(Q, K, V, p)
+    ref = _from_the_stored_codes(p, Q, K, V)
+    O = O.float().cpu().numpy().astype(np.float64)
+    # bf16 rounding is 2^-9 of a value; single codes of P~ may fall to the other side of a step
+    assert np.linalg.norm(O - ref) <= 6e-3 * np.linalg.norm(ref), np.linalg.norm(O - ref) / np.linalg.norm(ref)
