@@ -564,11 +564,11 @@ __global__ void __launch_bounds__(128 * NQ, 2) sage_fwd_pair_kernel(FwdArgs args
   constexpr int TILE_BYTES = 64 * D;
   constexpr int PAIR = 2 * TILE_BYTES;
   constexpr int NFRAG = PAIR / 1024;
-  constexpr int NBR = (NQ + 1) / 2;                            // Q blocks of the workgroup = bias rows
-  constexpr int SLOT = PAIR + (QSMOOTH ? NBR * 256 : 0);
+  constexpr int SLOT = PAIR + (QSMOOTH ? 256 : 0);             // (one Q block = one bias row per workgroup)
   constexpr int R = 3;
   constexpr int CPW = NFRAG / NW + (QSMOOTH ? 1 : 0);          // copies per wave and slot
   static_assert(NFRAG % NW == 0, "every wave must issue the same number of copies");
+  static_assert(NQ * 32 == kBlock, "a workgroup is one Q block: rows of the workspace tensors come in whole blocks");
   // (one LDS object: reads of a second one, which no asynchronous copy writes, would be made to wait for the copies in flight)
   struct Lds {
     int8_t ring[R * SLOT];                                     // slot p: K^ of tile p + 2 | V^ of tile p | biases of tile p + 2
@@ -592,18 +592,17 @@ __global__ void __launch_bounds__(128 * NQ, 2) sage_fwd_pair_kernel(FwdArgs args
   const int N = args.N;
   const int q0 = (qt * NQ + qw) * 32;
   const int q = q0 + ql;
-  const bool there = q0 < args.Nq;                             // (the last workgroup may reach past the last block)
   const int qlim = CAUSAL ? q + args.shift : args.nvalid - 1;
   const int nblk = N / kBlock;
   const int nqblk = args.Nq / kBlock;
-  const int qblk = there ? q0 / kBlock : nqblk - 1;
+  const int qblk = q0 / kBlock;
 
   const int8_t* KFh = args.KF + (size_t)bh * N * D;
   const int8_t* VTh = args.VT + (size_t)bh * N * D;
   const float* sKh = args.sK + (size_t)bh * nblk;
   const float* sVh = args.sV + (size_t)bh * nblk;
-  const int n_tiles = CAUSAL ? min((qt * NQ * 32 + NQ * 32 + args.shift + kBlock - 1) / kBlock, nblk) : nblk;
-  const int last = !there ? -1 : (CAUSAL ? (q0 + 31 + args.shift) / kBlock : nblk - 1);   // this wave's last tile
+  const int n_tiles = CAUSAL ? (qt * NQ * 32 + NQ * 32 + args.shift) / kBlock : nblk;
+  const int last = n_tiles - 1;                                // (the diagonal block of every wave, with the mask)
 
   // copies of slot p (K^ of tile p + 2, V^ of tile p; clamped where there is no such tile: never read)
   auto copy_piece = [&](int p, int8_t* dst, int k) __attribute__((always_inline)) {
@@ -613,10 +612,8 @@ __global__ void __launch_bounds__(128 * NQ, 2) sage_fwd_pair_kernel(FwdArgs args
                                         : VTh + (size_t)max(p, 0) * TILE_BYTES + (o - NFRAG / 2) * 1024;
       async_copy_16(src + lane * 16, dst + o * 1024);
     } else if (QSMOOTH && k == NFRAG / NW) {
-      // (every wave copies a row, so that all issue the same number: NBR rows, several waves each)
-      const int row = wave % NBR;
-      const int qb = min(qt * NBR + row, nqblk - 1);
-      async_copy_4(args.bias + ((size_t)bh * nqblk + qb) * N + min(p + 2, nblk - 1) * kBlock + lane, dst + PAIR + row * 256);
+      // (every wave copies the row, so that all issue the same number)
+      async_copy_4(args.bias + ((size_t)bh * nqblk + qblk) * N + min(p + 2, nblk - 1) * kBlock + lane, dst + PAIR);
     }
   };
   int8_t* rd = ring;                                           // slot t - 1
@@ -629,7 +626,7 @@ __global__ void __launch_bounds__(128 * NQ, 2) sage_fwd_pair_kernel(FwdArgs args
 
   v4i qf[KS];
   {
-    const int8_t* p = args.QF + (size_t)bh * args.Nq * D + (size_t)(there ? q0 / 32 : 0) * KS * 1024 + lane * 16;
+    const int8_t* p = args.QF + (size_t)bh * args.Nq * D + (size_t)(q0 / 32) * KS * 1024 + lane * 16;
 #pragma unroll
     for (int s = 0; s < KS; s++) qf[s] = *(const v4i*)(p + s * 1024);
   }
@@ -819,7 +816,7 @@ __global__ void __launch_bounds__(128 * NQ, 2) sage_fwd_pair_kernel(FwdArgs args
         w_prev = beta * sv * kTwo26;
         w_bias += w_prev;
       }
-      if constexpr (SN) half_max(sn, t + 1, cn, (const float*)(rd + PAIR + (qw >> 1) * 256), mask_tag);
+      if constexpr (SN) half_max(sn, t + 1, cn, (const float*)(rd + PAIR), mask_tag);
       // the copies of slot t (issued one interval ago) have landed; this interval's stay in flight
       if (issue) {
         __builtin_amdgcn_s_waitcnt(vmcnt_only(CPW));
@@ -854,7 +851,7 @@ __global__ void __launch_bounds__(128 * NQ, 2) sage_fwd_pair_kernel(FwdArgs args
       sk = skn;
       sv = svn;
     };
-    // (the masked forms leave visible keys as they are; a wave whose tiles are done keeps the ring moving)
+    // (the masked forms leave visible keys as they are)
     int t = 0;
     if (last >= 1) {
       step(t++, sA, sB, F{}, T{}, T{}, T{});
@@ -868,11 +865,10 @@ __global__ void __launch_bounds__(128 * NQ, 2) sage_fwd_pair_kernel(FwdArgs args
       }
       step(t++, sB, sA, T{}, T{}, F{}, T{});
       step(t++, sB, sA, T{}, F{}, F{}, F{});
-    } else if (last == 0) {
+    } else {
       step(t++, sA, sB, F{}, T{}, F{}, T{});
       step(t++, sA, sB, T{}, F{}, F{}, F{});
     }
-    for (; t <= n_tiles; t++) step(t, sA, sB, F{}, F{}, F{}, F{});
     unbias();
   };
   if (__builtin_amdgcn_readfirstlane((int)use_sbias)) run(std::true_type{});
@@ -920,6 +916,7 @@ __global__ void __launch_bounds__(512, 1) sage_fwd_split_kernel(FwdArgs args) {
   constexpr int R = NS * 4 * PAIR <= 128 * 1024 ? 4 : 2;       // ring slots per split
   constexpr int CPW = NFRAG / NQ + (QSMOOTH ? 1 : 0);
   static_assert(NQ * NS == 8 && NFRAG % NQ == 0, "8 waves, the same number of copies for each");
+  static_assert(NQ * 32 == kBlock, "a workgroup is one Q block: rows of the workspace tensors come in whole blocks");
   constexpr int RING = NS * R * SLOT;
   constexpr int XCH = NQ * NS * KS * 4096;                     // partial O of every wave: [q][split][channel block] x 4 KiB
   __shared__ __attribute__((aligned(16))) int8_t lds[RING > XCH ? RING : XCH];
@@ -937,27 +934,26 @@ __global__ void __launch_bounds__(512, 1) sage_fwd_split_kernel(FwdArgs args) {
   const int N = args.N;
   const int q0 = (qt * NQ + qw) * 32;
   const int q = q0 + ql;
-  const bool there = q0 < args.Nq;                             // (the last workgroup may reach past the last block)
   const int qlim = CAUSAL ? q + args.shift : args.nvalid - 1;
   const int nblk = N / kBlock;
   const int nqblk = args.Nq / kBlock;
-  const int qblk = there ? q0 / kBlock : nqblk - 1;
+  const int qblk = q0 / kBlock;
 
   const int8_t* KFh = args.KF + (size_t)bh * N * D;
   const int8_t* VTh = args.VT + (size_t)bh * N * D;
   const float* sKh = args.sK + (size_t)bh * nblk;
   const float* sVh = args.sV + (size_t)bh * nblk;
 
-  // this workgroup's tiles, this split's share [a, b) of them, this wave's last tile
-  const int n_tiles = CAUSAL ? min((qt * NQ * 32 + NQ * 32 + args.shift + kBlock - 1) / kBlock, nblk) : nblk;
+  // this workgroup's tiles, this split's share [a, b) of them (none for the last splits of some counts), its last tile
+  const int n_tiles = CAUSAL ? (qt * NQ * 32 + NQ * 32 + args.shift) / kBlock : nblk;
   const int share = (n_tiles + NS - 1) / NS;
   const int a = g * share, b = min(n_tiles, a + share), cnt = max(b - a, 0);
-  const int last = !there ? -1 : (CAUSAL ? min((q0 + 31 + args.shift) / kBlock, b - 1) : b - 1);
+  const int last = b - 1;
   const int ac = min(a, nblk - 1);                             // (a split without tiles still reads in bounds)
 
   v4i qf[KS];
   {
-    const int8_t* p = args.QF + (size_t)bh * args.Nq * D + (size_t)(there ? q0 / 32 : 0) * KS * 1024 + lane * 16;
+    const int8_t* p = args.QF + (size_t)bh * args.Nq * D + (size_t)(q0 / 32) * KS * 1024 + lane * 16;
 #pragma unroll
     for (int s = 0; s < KS; s++) qf[s] = *(const v4i*)(p + s * 1024);
   }
@@ -1043,7 +1039,7 @@ __global__ void __launch_bounds__(512, 1) sage_fwd_split_kernel(FwdArgs args) {
       t++;
     }
     if (a + t <= last) {
-      // the wave's last tile takes the masked path (which leaves visible keys as they are)
+      // the split's last tile takes the masked path (which leaves visible keys as they are)
       const bool issue = t + R - 1 < cnt;
       if (issue) {
 #pragma unroll
@@ -1055,7 +1051,7 @@ __global__ void __launch_bounds__(512, 1) sage_fwd_split_kernel(FwdArgs args) {
       end_iter(issue);
       t++;
     }
-    for (; t < share; t++) {                                   // (every wave of the workgroup meets `share` barriers)
+    for (; t < share; t++) {                                   // (a shorter split: every wave meets `share` barriers)
       const bool issue = t + R - 1 < cnt;
       if (issue) {
 #pragma unroll

@@ -369,7 +369,7 @@ bool use_fwd_pair(const FwdArgs& a) { return (long long)a.BH * ((a.Nq + 31) / 32
 template <int D, bool CAUSAL, bool QS>
 int launch_fwd_small(const FwdArgs& a, bool split, hipStream_t st) {
   FwdArgs args = a;
-  args.n_qtiles = (a.Nq + 63) / 64;
+  args.n_qtiles = a.Nq / 64;
   args.head_set = head_set_for(args.n_qtiles, a.BH);
   const int grid = grid_for(a.BH, args.n_qtiles);
   if (split) sage_fwd_split_kernel<D, CAUSAL, QS, 2, 4><<<grid, 512, 0, st>>>(args);
