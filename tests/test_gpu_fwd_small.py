@@ -33,21 +33,25 @@ def _against_oracle(Q, K, V, p, heads):
         check_lse(f"LSE[{b},{h}]", L[b, h], Lr)
 
 
-# one key, one block, a partial block, one workgroup of four waves and just past it, many workgroups with a ragged end,
-# 1 to 32 query rows, one wave with several blocks
+# Short caches, which the forms with codes in the workspace serve: one key, one block, a partial block, four blocks and just
+# past them.  The kernel without (from 16 blocks on, or 1024 blocks over all heads): its shortest cache and one key less, one
+# workgroup per head and many with a ragged end, one key, 1 to 32 query rows, waves with several blocks and without any.
 @pytest.mark.parametrize("B,H,Nq,Nk,d,k_smooth,token_major", [
     (1, 2, 1, 1, 128, True, False), (1, 2, 1, 64, 64, True, False), (1, 3, 5, 200, 64, False, True), (1, 2, 32, 256, 128, True, False),
-    (1, 2, 3, 257, 128, True, False), (2, 3, 7, 2049, 64, True, True), (1, 1, 31, 8192, 128, True, False), (8, 32, 1, 640, 128, True, False), (1, 2, 9, 1024, 128, True, False), (1, 2, 2, 1023, 64, False, True)])
+    (1, 2, 3, 257, 128, True, False), (2, 3, 7, 2049, 64, True, True), (1, 1, 31, 8192, 128, True, False), (8, 32, 1, 640, 128, True, False), (1, 2, 9, 1024, 128, True, False), (1, 2, 2, 1023, 64, False, True),
+    (1, 2, 4, 961, 128, True, False), (1, 2, 4, 960, 128, True, False), (32, 32, 1, 1, 64, True, False), (16, 32, 5, 100, 128, False, True),
+    (4, 32, 32, 1100, 64, True, False), (1, 1, 32, 20000, 64, True, False)])
 def test_decode(B, H, Nq, Nk, d, k_smooth, token_major):
     Q, K, V = _inputs(B, H, Nq, Nk, d)
     p = binding.SageParams(B, H, Nq, d, causal=False, k_smooth=k_smooth, Nkv=Nk, token_major=token_major)
     _against_oracle(Q, K, V, p, {(0, 0), (B - 1, H - 1)})
 
 
-def test_decode_leaves_the_quantised_tensors_for_those_who_can_read_them():
+@pytest.mark.parametrize("Nk", [200, 1100])       # codes in the workspace; a decoding step
+def test_decode_leaves_the_quantised_tensors_for_those_who_can_read_them(Nk):
     """Codes and scales after a forward on the full workspace, and a backward that shares them."""
-    Q, K, V = (t.cuda() for t in _inputs(1, 2, 9, 200, 64))
-    p = binding.SageParams(1, 2, 9, 64, causal=False, Nkv=200)
+    Q, K, V = (t.cuda() for t in _inputs(1, 2, 9, Nk, 64))
+    p = binding.SageParams(1, 2, 9, 64, causal=False, Nkv=Nk)
     ws, ws2 = binding.alloc_workspace(p), binding.alloc_workspace(p)
     O, L = binding.sagebwd_fwd(Q, K, V, p, ws)
     binding.sagebwd_quantize(Q, K, V, p, ws2)
@@ -56,7 +60,7 @@ def test_decode_leaves_the_quantised_tensors_for_those_who_can_read_them():
             assert torch.equal(a, b), which
     dO = torch.ones_like(O)
     ref = binding.sagebwd_bwd(Q, K, V, O, dO, L, p)
-    ps = binding.SageParams(1, 2, 9, 64, causal=False, Nkv=200, share_quantized=True)
+    ps = binding.SageParams(1, 2, 9, 64, causal=False, Nkv=Nk, share_quantized=True)
     wss = binding.alloc_workspace(ps)
     Os, Ls = binding.sagebwd_fwd(Q, K, V, ps, wss)
     assert torch.equal(O, Os) and torch.equal(L, Ls)
@@ -64,10 +68,11 @@ def test_decode_leaves_the_quantised_tensors_for_those_who_can_read_them():
         assert torch.equal(a, b)
 
 
-# eight tiles for four splits, a number of tiles the splits do not divide, splits without a tile under the mask, a last
-# workgroup that reaches past the queries, both ring depths, Q-smoothing's biases in the ring
+# eight tiles for four splits, a number of tiles the splits do not divide, nine tiles (the last split gets none) with and
+# without the mask, query rows that do not exist, both ring depths, Q-smoothing's biases in the ring
 @pytest.mark.parametrize("Nq,Nk,d,causal,q_smooth", [(64, 512, 128, False, False), (100, 868, 64, True, False), (192, 580, 128, False, True),
-                                                     (33, 609, 64, False, True), (256, 1024, 128, True, False), (64, 4160, 128, True, True)])
+                                                     (33, 609, 64, False, True), (256, 1024, 128, True, False), (64, 4160, 128, True, True),
+                                                     (64, 576, 128, True, False), (40, 530, 64, False, False), (64, 576, 64, True, True)])
 def test_split_keys(Nq, Nk, d, causal, q_smooth):
     Q, K, V = _inputs(1, 2, Nq, Nk, d, normed=not q_smooth, q_offset=q_smooth)
     _against_oracle(Q, K, V, binding.SageParams(1, 2, Nq, d, causal=causal, q_smooth=q_smooth, Nkv=Nk), {(0, 0), (0, 1)})
