@@ -23,8 +23,8 @@
  *     sagebwd_fwd / sagebwd_bwd may be recorded under stream capture and replayed.
  *   - Return value: SAGEBWD_OK (0) or a negative sagebwd_status.  Arguments are
  *     validated on the host before anything is launched; on error nothing runs.
- *   - Numerics blocks are B_q = B_kv = 64 (one FP32 scale per 64 rows x d channels); Algorithm 1
- *     takes both as inputs, sagebwd_params carries them, other values are SAGEBWD_UNSUPPORTED_SHAPE.
+ *   - Numerics blocks are B_q = B_kv = 64 (one FP32 scale per 64 rows x d channels) unless sagebwd_params
+ *     says 128 for either; other values are SAGEBWD_UNSUPPORTED_SHAPE.
  *   - Bit-exact contract: the stored INT8 tensors Q^, K^, V^, dO^, their scales and the smoothing
  *     means equal the paper's definitions evaluated in FP32 bit for bit.  The quantisers inside
  *     the attention loops (P^ of the forward, psi(P) and psi(dS) of the backward) depend on the
@@ -200,6 +200,21 @@ int sagebwd_export_ds(const sagebwd_params* params, const void* workspace, size_
  * Writes O bf16 [B,H,N,d] and LSE float32 [B,H,N].  LSE is the log-sum-exp of the
  * SMOOTHED logits (it differs from the unsmoothed one by a per-row constant) and is
  * meant to be handed back to sagebwd_bwd unchanged.
+ *
+ * Which bits a head gets.  Every call repeats itself bit for bit, and every (b, h) is computed from its own
+ * tensors.  Where the keys are fewer than twice the queries (rows counted in blocks of 64; square attention among
+ * them), and with numerics blocks of 128 keys, a head gets the same bits alone, in any batch, and on any shard of the
+ * heads.  With at least twice as many keys as queries, or at most 32 queries without the mask, the division of the
+ * keys over waves depends on B*H: sums over the keys then run in another order (and the logits may be formed by the
+ * biased or by the converting path), so that O agrees between calls of different B*H to its bf16 rounding and LSE to
+ * about 1e-4.  sagebwd_bwd, given the same O and LSE, returns the same bits in every case.
+ *
+ * A decoding step (at most 32 queries, no mask, numerics blocks of 64, neither Q-smoothing nor QK-norm, at least 961
+ * keys or 1024 key blocks over all heads) needs no quantised tensors in memory, and writes none where no later call could
+ * read them: that is, where workspace_bytes is below *bwd_bytes of sagebwd_workspace_bytes (with
+ * SAGEBWD_FLAG_SHARE_QUANTIZED, where the forward's own need holds what the backward reads, it always writes them).
+ * On a workspace of the full size it runs the whole pre-pass behind itself, for the export hooks, which about doubles
+ * its time: a caller that only decodes passes a workspace of *fwd_bytes.
  */
 int sagebwd_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE,
                 const sagebwd_params* params, void* workspace, size_t workspace_bytes,

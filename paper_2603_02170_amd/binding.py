@@ -183,6 +183,9 @@ def workspace_bytes(p: SageParams, forward_only: bool = False) -> int:
 
 
 def alloc_workspace(p: SageParams, device="cuda", forward_only: bool = False):
+    """A workspace for every call or, with forward_only, for sagebwd_fwd alone.  A caller that only decodes passes
+    forward_only: on the full size a decoding step also writes the quantised tensors, which about doubles its time
+    (see sagebwd_fwd in the header)."""
     return torch.empty(workspace_bytes(p, forward_only), dtype=torch.uint8, device=device)
 
 
@@ -241,7 +244,7 @@ def sagebwd_export_ds(p: SageParams, workspace, head: int):
 
 
 def sagebwd_fwd(Q, K, V, p: SageParams, workspace=None, O=None, LSE=None):
-    """O, LSE = INT8 attention forward.  Allocates outputs / workspace when not given."""
+    """O, LSE = INT8 attention forward.  Allocates outputs / workspace (of the forward's own size) when not given."""
     return _host().fwd(Q, K, V, p, workspace, O, LSE)
 
 

@@ -94,6 +94,27 @@ def test_two_waves_per_query_group_give_the_same_bits(N, d, causal, normed, q_sm
     assert np.isfinite(to_np(O)).all()
 
 
+# More keys than queries: the division of the keys over waves depends on how many heads the call has.  Then O differs by
+# at most its two bf16 roundings (2^-9 each) in the 2-norm, and LSE by what the biased logits cost (1e7 c 2^-24 in log2
+# units, c about 1e-4 for such inputs).  Fewer than twice as many keys: the same bits.
+@pytest.mark.parametrize("heads,Nq,Nk,d,causal,same", [(64, 1, 8192, 128, False, False), (128, 512, 1100, 128, False, False), (128, 128, 576, 64, True, False),
+                                                       (1024, 20, 64, 64, False, False), (64, 512, 960, 128, True, True), (70, 100, 150, 64, False, True)])
+def test_a_head_alone_and_in_a_batch(heads, Nq, Nk, d, causal, same):
+    Q, K, V = (t.cuda() for t in _inputs(1, heads, Nq, Nk, d, normed=True))
+    O, L = binding.sagebwd_fwd(Q, K, V, binding.SageParams(1, heads, Nq, d, causal=causal, Nkv=Nk))
+    again = binding.sagebwd_fwd(Q, K, V, binding.SageParams(1, heads, Nq, d, causal=causal, Nkv=Nk))
+    assert torch.equal(O, again[0]) and torch.equal(L, again[1])
+    for h in (0, heads - 1):
+        O1, L1 = binding.sagebwd_fwd(*(t[:, h:h + 1].contiguous() for t in (Q, K, V)), binding.SageParams(1, 1, Nq, d, causal=causal, Nkv=Nk))
+        torch.cuda.synchronize()
+        if same:
+            assert torch.equal(O1[0, 0], O[0, h]) and torch.equal(L1[0, 0], L[0, h])
+        else:
+            a, b = O[0, h].double(), O1[0, 0].double()
+            assert float((a - b).norm()) <= 2 ** -8 * float(b.norm())
+            assert float((L[0, h] - L1[0, 0]).abs().max()) <= 1e-4
+
+
 def _from_the_stored_codes(p, Q, K, V):
     """The forward in float64 from the codes and scales that the pre-pass stores (its quantiser of P~ included)."""
     ws = binding.alloc_workspace(p)
