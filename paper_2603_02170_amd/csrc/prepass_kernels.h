@@ -120,9 +120,14 @@ __global__ void __launch_bounds__(256) kmean_partial_kernel(const unsigned short
   }
 }
 
-// Heads this short are summed by every workgroup that quantises a block of K, each for itself, without the launch of
-// stage 1: 512 rows of d = 128 cost a workgroup about 1.7 us, a launch about 3.
-inline bool mean_inline(int N, int D) { return (long long)N * D <= 65536; }
+// Short heads are summed by every workgroup that quantises a block of K, each for itself, without the launch of stage 1:
+// what that launch costs (about 2 us) against what one workgroup reads (N * D) and what all of them read.  Forward calls,
+// us without -> with: 1 head, d = 128, N = 512: 17.8 -> 17.4, 768: 20.9 -> 21.2; in millions of elements read by all, 64
+// heads of 256 (8.4): 18.5 -> 17.2, 64 of 320 (13.1): 20.0 -> 19.8, 32 of 512 (16.8): 21.7 -> 22.1, 128 of 384 (38): 31.9 ->
+// 37.2, 128 of 512 (67): 37.9 -> 49.6; d = 64, 48 of 512 (12.6): 18.8 -> 18.2, 128 of 384 (18.9): 23.6 -> 24.4.
+inline bool mean_inline(int heads, int N, int D) {
+  return (long long)N * D <= 65536 && (long long)heads * ((N + kBlock - 1) / kBlock) * N * D <= (14 << 20);
+}
 
 // The rounding of psi on 16 values held as FP32: q = rne(x * r) clamped to +-127 (which matters where r = 127 / max|x|
 // overflows, blocks of the smallest numbers, and for NaN: both become codes), packed into four registers.  x * r is rounded to FP32 before the addition that takes it to an integer, so the

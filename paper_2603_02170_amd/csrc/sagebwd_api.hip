@@ -240,7 +240,7 @@ int run_prepass(const void* Q, const void* K, const void* V, const void* dO, con
   const RowView qview = caller_view(p, 1, Nq), kview = caller_view(p, 1, Nk);     // in bf16 elements
   float* muK = (float*)(ws + w.muK);
   const bool qkn = (p.flags & SAGEBWD_FLAG_QK_NORM) != 0;
-  const bool inline_mean = ks && mean_inline(Nk, D);
+  const bool inline_mean = ks && mean_inline(BH, Nk, D);
   const QkNorm norm_q{qkn ? p.qk_gamma_q : nullptr, p.qk_norm_eps}, norm_k{qkn ? p.qk_gamma_k : nullptr, p.qk_norm_eps};
   if (want_qk) {
     if (ks && !inline_mean) {
