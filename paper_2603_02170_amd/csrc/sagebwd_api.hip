@@ -356,13 +356,20 @@ int pick_fwd_waves(int N) { return N % 128 == 0 ? 4 : 2; }
 // CUs and SIMDs of the machine: what a launch has to fill.
 constexpr int kCus = 256, kSimds = 1024;
 
-// Few queries against many keys: split the keys inside the workgroup (sage_fwd_split_kernel) while 64-query
-// workgroups do not fill the CUs twice over and there are a few tiles for each split.
+// Few queries against many keys: split the keys inside the workgroup (sage_fwd_split_kernel) where there are a few tiles
+// for each split, while there is a CU for each 64-query workgroup (its LDS takes a whole one), and for two rounds of
+// them where the chains are long and several workgroups share a head's keys.  Whole calls, d = 128, us with one chain
+// per query -> split: 256 workgroups: 512 x 1024 29.1 -> 25.7, 512 x 4096 82.7 -> 66.9, 128 x 8192 299 -> 285, 64 x 1024
+// 67.6 -> 67.2; 320 to 512: 512 x 1024 35.2 -> 38.5, 512 x 2048 58.2 -> 59.2, 128 x 8192 442 -> 461, 512 x 4096 119 -> 116,
+// 512 x 8192 235 -> 228; 768: 512 x 4096 170 -> 175.
 bool use_fwd_split(const FwdArgs& a) {
-  return a.N >= 2 * a.Nq && a.N >= 8 * kBlock && (long long)a.BH * ((a.Nq + 63) / 64) <= kSimds / 2;
+  const long long wgs = (long long)a.BH * (a.Nq / 64);
+  return a.N >= 2 * a.Nq && a.N >= 8 * kBlock && (wgs <= kCus || (wgs <= 2 * kCus && a.N >= 64 * kBlock && a.Nq >= 8 * kBlock));
 }
 // At most one wave of sage_fwd_kernel (32 queries) per SIMD: two waves share them (sage_fwd_pair_kernel; same
-// bits).  Measured at d = 128, us: 256 waves 24 -> 20, 1024 waves 25.8 -> 21.2, 2048 waves 77 -> 75, 4096 waves 66 -> 79.
+// bits).  Whole calls at d = 128, us: with the mask N = 1024, 256 waves 30.2 -> 26.0, 1024 waves 35.2 -> 31.2, 1280 42.1 ->
+// 40.1, 3072 61.8 -> 66.5; N = 4096, 1024 waves 84.1 -> 67.7, 1280 88.0 -> 84.1; without it N = 1024, 1024 waves 35.7 -> 35.3,
+// 1280 42.2 -> 49.1; at d = 64, N = 4096, 1024 waves 67.2 -> 51.3, 1280 69.9 -> 77.2.
 bool use_fwd_pair(const FwdArgs& a) { return (long long)a.BH * ((a.Nq + 31) / 32) <= kSimds; }
 
 // the two forms for calls that do not fill the machine: 64 queries per workgroup
