@@ -429,12 +429,19 @@ int launch_bwd(const BwdArgs& a, bool causal, bool qs, hipStream_t st) {
   return SAGEBWD_OK;
 }
 
-// One KV block per workgroup (sage_bwd_single_kernel; same bits): while its workgroups are given out in one round (without the
-// mask, where a second round costs as much as the first) or two (with it, where the second is the lighter); at d = 64,
-// where two of its workgroups share a CU (not with Q-smoothing, which needs more registers), at every size but the
-// causal walks of one or two Q blocks (256 heads of N = 128: 14.9 us, 14.6 the other way).
+// One KV block per workgroup (sage_bwd_single_kernel; same bits): while its workgroups are given out in one round, or in two
+// where the second is much the lighter (square calls with the mask, walks long enough for that to outweigh what every
+// workgroup pays for filling its pipeline); at d = 64, where two of its workgroups share a CU (not with Q-smoothing, which
+// needs more registers), at every size but the causal walks of one or two Q blocks.  Whole backward calls, us with two KV
+// blocks per workgroup -> with one.  d = 128 with the mask: N = 1024, 256 blocks 60.7 -> 47.1, 512 63.3 -> 57.5, 576 64.8 ->
+// 68.7; N = 4096, 512 blocks 182 -> 141, 640 186 -> 198; 510 blocks of N = 640 50.3 -> 50.7, 380 47.8 -> 44.0; 504 of N = 576
+// 46.9 -> 51.3; N = 256, 256 blocks 30.4 -> 26.3, 384 33.0 -> 35.4; 64 x 1024, 384 blocks 32.0 -> 37.3; 512 x 4096 79.5 -> 85.0.
+// Without: N = 1024, 256 blocks 60.1 -> 49.5, 320 61.2 -> 71.7.  d = 64 with Q-smoothing and the mask: 512 blocks of N = 512
+// 37.4 -> 33.4, 384 of N = 256 26.5 -> 26.2, 512 27.8 -> 29.3; d = 64: 256 heads of N = 128 21.3 -> 21.9, of N = 192 34.6 -> 31.2.
 bool use_bwd_single(const BwdArgs& a, int d, bool causal, bool qs) {
-  if ((long long)a.BH * (a.N / 64) <= (causal ? 2 * kCus : kCus)) return true;
+  const long long blocks = (long long)a.BH * (a.N / 64);
+  const bool lighter_second = causal && a.N == a.Nq && a.N >= (d == 64 ? 8 : 10) * kBlock;
+  if (blocks <= kCus || (lighter_second && blocks <= 2 * kCus)) return true;
   return d == 64 && !qs && !(causal && a.Nq <= 128);
 }
 template <int D>
