@@ -209,8 +209,8 @@ int sagebwd_export_ds(const sagebwd_params* params, const void* workspace, size_
  * biased or by the converting path), so that O agrees between calls of different B*H to its bf16 rounding and LSE to
  * about 1e-4.  sagebwd_bwd, given the same O and LSE, returns the same bits in every case.
  *
- * A decoding step (at most 32 queries, no mask, numerics blocks of 64, neither Q-smoothing nor QK-norm, at least 961
- * keys or 1024 key blocks over all heads) needs no quantised tensors in memory, and writes none where no later call could
+ * A decoding step (at most 32 queries, no mask, numerics blocks of 64, neither Q-smoothing nor QK-norm, more than a
+ * thousand keys or enough heads) needs no quantised tensors in memory, and writes none where no later call could
  * read them: that is, where workspace_bytes is below *bwd_bytes of sagebwd_workspace_bytes (with
  * SAGEBWD_FLAG_SHARE_QUANTIZED, where the forward's own need holds what the backward reads, it always writes them).
  * On a workspace of the full size it runs the whole pre-pass behind itself, for the export hooks, which about doubles

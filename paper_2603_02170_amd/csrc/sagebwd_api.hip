@@ -474,11 +474,15 @@ int launch_bwd_dq(const DqArgs& a, bool causal, hipStream_t st) {
 }
 
 // One query block of at most 32 rows that sees every key, plain options: see fwd_decode_kernel.h.  (Its kernel is long, and
-// with a short cache few workgroups share the cost of fetching its instructions: 9 heads against 384 keys took 21 us with
-// codes in the workspace, 23 this way.)
+// with a short cache few workgroups share the cost of fetching its instructions.)  Whole calls, us with codes in the workspace
+// -> this way.  d = 128: 1 head, 20 key blocks 21.9 -> 23.7, 24 24.0 -> 24.4, 32 27.7 -> 25.9; 16 heads, 16 blocks 22.3 -> 22.8, 24
+// 27.4 -> 25.7; blocks over all heads: 48 heads of 12 (576) 23.0 -> 24.5, 64 of 12 (768) 24.8 -> 24.8, 128 of 6 (768) 28.0 ->
+// 23.3, 256 of 4 (1024) 27.0 -> 20.9.  d = 64: 1 head, 12 blocks 14.5 -> 16.2 (2 heads), 16 16.4 -> 15.7, 32 24.1 -> 20.1; 64 heads
+// of 6 (384) 15.1 -> 15.3, of 8 (512) 17.4 -> 15.6, 256 of 2 (512) 12.6 -> 11.6.
 bool use_decode(const sagebwd_params& p) {
   const int nblk = padded_rows(kv_len(p)) / 64;
-  return (nblk >= 16 || (long long)p.B * p.H * nblk >= kSimds) && p.N <= 32 && p.causal == 0 && !(p.smooth & SAGEBWD_SMOOTH_Q) && !(p.flags & SAGEBWD_FLAG_QK_NORM) && !big_blocks(p);
+  const bool long_enough = nblk >= (p.d == 64 ? 16 : 24) || (long long)p.B * p.H * nblk >= (p.d == 64 ? 512 : 768);
+  return long_enough && p.N <= 32 && p.causal == 0 && !(p.smooth & SAGEBWD_SMOOTH_Q) && !(p.flags & SAGEBWD_FLAG_QK_NORM) && !big_blocks(p);
 }
 
 template <int D>

@@ -34,12 +34,14 @@ def _against_oracle(Q, K, V, p, heads):
 
 
 # Short caches, which the forms with codes in the workspace serve: one key, one block, a partial block, four blocks and just
-# past them.  The kernel without (from 16 blocks on, or 1024 blocks over all heads): its shortest cache and one key less, one
-# workgroup per head and many with a ragged end, one key, 1 to 32 query rows, waves with several blocks and without any.
+# past them.  The kernel without (from 16 blocks on at d = 64 and 24 at d = 128, or 512 and 768 blocks over all heads): its
+# shortest caches and one key less, one workgroup per head and many with a ragged end, one key, 1 to 32 query rows, waves
+# with several blocks and without any.
 @pytest.mark.parametrize("B,H,Nq,Nk,d,k_smooth,token_major", [
     (1, 2, 1, 1, 128, True, False), (1, 2, 1, 64, 64, True, False), (1, 3, 5, 200, 64, False, True), (1, 2, 32, 256, 128, True, False),
     (1, 2, 3, 257, 128, True, False), (2, 3, 7, 2049, 64, True, True), (1, 1, 31, 8192, 128, True, False), (8, 32, 1, 640, 128, True, False), (1, 2, 9, 1024, 128, True, False), (1, 2, 2, 1023, 64, False, True),
-    (1, 2, 4, 961, 128, True, False), (1, 2, 4, 960, 128, True, False), (32, 32, 1, 1, 64, True, False), (16, 32, 5, 100, 128, False, True),
+    (1, 2, 4, 961, 64, True, False), (1, 2, 4, 960, 64, True, False), (1, 2, 4, 1473, 128, True, False), (1, 2, 4, 1472, 128, False, False),
+    (32, 32, 1, 1, 64, True, False), (16, 32, 5, 100, 128, False, True),
     (4, 32, 32, 1100, 64, True, False), (1, 1, 32, 20000, 64, True, False)])
 def test_decode(B, H, Nq, Nk, d, k_smooth, token_major):
     Q, K, V = _inputs(B, H, Nq, Nk, d)
