@@ -22,9 +22,9 @@ INT8_PEAK_TOPS = 5000.0     # MI355X dense INT8 MFMA peak (published)
 HBM_PEAK_GBS = 8000.0       # MI355X HBM3E peak (published)
 
 # HBM bytes per launch at the headline workload.  NOT measured in this run: taken from the committed
-# rocprofv3 FETCH_SIZE / WRITE_SIZE runs summarised in profiles/hbm_traffic_headline_fwd_bwd.txt
+# rocprofv3 FETCH_SIZE / WRITE_SIZE runs summarised in profiles/hbm_traffic_cases.txt
 # (scaled by the copy-kernel calibration stated there).
-PROFILED_TRAFFIC_BYTES = {"headline": {"bwd": 3.5082e9, "fwd": 3.382e8, "bwd_dq": 2.656e9}}
+PROFILED_TRAFFIC_BYTES = {"headline": {"bwd": 3.5265e9, "fwd": 3.381e8, "bwd_dq": 2.6568e9}}
 
 
 def work_ops(w, fwd=True, bwd=True, matmuls=None):

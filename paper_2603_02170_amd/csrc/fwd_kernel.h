@@ -106,8 +106,8 @@ __device__ __forceinline__ void fwd_s_mfma(const int8_t* __restrict__ Kt, const 
 // chunk pairs one MFMA (and the LDS read of an operand two MFMAs ahead) with the vector work of
 // four logits or of sixteen output values, so that the matrix pipe and the LDS latency hide
 // under the vector instructions of the same wave.  `copy(k)` issues the k-th of this wave's global -> LDS
-// copies for a coming tile, one in every second slot: a wave issues such a copy in about 100 cycles when it
-// follows another one, so the five of a tile in one place stood for 500 of a tile's 2500 cycles.
+// copies for a coming tile, one in every second slot: alone a wave issues such a copy in 12 cycles, but the CU takes
+// one in 16, and four copies of each of its eight waves in one place hold every wave for about 200 of a tile's 3000 cycles.
 //
 // KV128 = numerics blocks of 128 keys: the per-token quantiser of P~ (Algorithm 1 line 9) then takes its row
 // max over both 64-key tiles of the block.  `pair` carries the other tile's row max in (INT_MIN / -inf if
@@ -550,10 +550,12 @@ __global__ void __launch_bounds__(64 * NW, (NW == 4 ? (D == 64 ? 3 : 2) : 1)) sa
 // software-pipelined over one barrier per tile: interval t finishes the softmax of tile t, adds tile t - 1 to O
 // and forms S of tile t + 1 with its half row max, so each finds the other wave's part of the interval before.
 //
-// Such calls take the time of one wave's chain of tiles: sage_fwd_kernel needs about 2450 cycles a tile with one
-// wave per SIMD, most of them the wave's own instruction issue (one vector instruction in about 4.8 cycles),
-// and half a tile takes little more than half of that.  The arithmetic of every value and its order are those of
-// sage_fwd_kernel, so both give the same bits and the choice may depend on how full the machine is.  (With
+// Such calls take the time of one wave's chain of tiles: with one wave per SIMD sage_fwd_kernel needs 1.02 us for
+// each further tile (2 heads of N = 4096 against 8 of N = 1024, same pre-pass), most of it the wave's own instruction
+// issue (one vector instruction in about 4.8 cycles).  Half a tile per wave takes 0.77 us: less than half of the
+// instructions are saved (row statistics are formed twice), and the interval is a chain of its own, from the other
+// wave's row max in LDS through exp2 and packing to the next one.  The arithmetic of every value and its order are
+// those of sage_fwd_kernel, so both give the same bits and the choice may depend on how full the machine is.  (With
 // 128 registers, four waves per SIMD, this form was tried for full machines too: 925 us against 756 at
 // the headline shape.)
 template <int D, bool CAUSAL, bool QSMOOTH, int NQ>
@@ -899,10 +901,15 @@ __global__ void __launch_bounds__(128 * NQ, 2) sage_fwd_pair_kernel(FwdArgs args
 // of the splits meet in LDS at the end, each split finishing a share of the channels.
 //
 // Where the queries alone do not fill the machine (chunked prefill, cross attention), the time is one wave's chain
-// of tiles, about 1.1 us each; splitting the keys shortens it NS times and puts two waves on every SIMD.  512
-// queries x 32 heads against 4096 keys, d = 128: 70 -> 36 us.  (On a full machine the merge and
-// the barrier over 8 waves cost 20 to 50 %.)  The order of the sums differs from sage_fwd_kernel's, which
-// is why square attention does not come here: a head of it gets the same bits alone and in any batch.
+// of tiles, about 1 us each; splitting the keys shortens it NS times and puts two waves on every SIMD.  512
+// queries x 32 heads against 4096 keys, d = 128: 70 -> 34 us.  (On a full machine the merge and
+// the barrier over 8 waves make it the slower form by 5 to 15 %.)  The order of the sums differs from
+// sage_fwd_kernel's, which is why square attention does not come here: a head of it gets the same bits alone and in
+// any batch.
+//
+// At d = 128 the ring has two slots per split, so every iteration waits for all of its copies; four would not fit beside
+// four splits.  (The instantiations without Q-smoothing keep 17 registers in scratch there, written before the tile loop
+// and read after it.)
 //
 // Slot p of a split's ring holds K^ of its tile p + 1 and V^ of its tile p (what iteration p reads: the logits
 // of the next tile are formed under the softmax of this one); K^ of the first tile comes straight from memory.

@@ -66,3 +66,23 @@ def test_forward_kernels_fit_their_occupancy(kernels):
             assert k["vgpr"] <= 256 and k["scratch"] <= scratch and 2 * k["lds"] <= 160 * 1024, k
         for k in _pick(kernels, "sage_fwd_kernel", "ILi64E", kv128):
             assert k["vgpr"] <= 168 and k["scratch"] <= scratch and 3 * k["lds"] <= 160 * 1024, k
+
+
+def test_the_forms_for_calls_that_do_not_fill_the_machine(kernels):
+    # one wave per SIMD of four-wave workgroups and two: registers only, nothing in scratch
+    for k in _pick(kernels, "sage_fwd_pair_kernel"):
+        assert k["scratch"] == 0 and k["vgpr"] <= 256 and 2 * k["lds"] <= 160 * 1024, k
+    # eight waves and most of the LDS of a CU; at d = 128 without Q-smoothing some registers are parked outside the tile loop
+    for k in _pick(kernels, "sage_fwd_split_kernel"):
+        assert k["scratch"] <= 96 and k["vgpr"] <= 256 and k["lds"] <= 160 * 1024, k
+    for bits in (("ILi64E",), ("ILi128ELb0ELb1E",), ("ILi128ELb1ELb1E",)):
+        assert all(k["scratch"] == 0 for k in _pick(kernels, "sage_fwd_split_kernel", *bits)), bits
+    # one wave per SIMD: the whole register file, no scratch
+    for k in _pick(kernels, "sage_fwd_decode_kernel"):
+        assert k["scratch"] == 0 and k["vgpr"] <= 512 and k["lds"] <= 160 * 1024, k
+    # one KV block per workgroup: two workgroups per CU at d = 64 without Q-smoothing
+    for k in _pick(kernels, "sage_bwd_single_kernel"):
+        assert k["scratch"] == 0 and k["vgpr"] <= 256 and k["lds"] <= 160 * 1024, k
+    for bits in ("ILi64ELb1ELb0E", "ILi64ELb0ELb0E"):
+        for k in _pick(kernels, "sage_bwd_single_kernel", bits):
+            assert k["vgpr"] <= 128 and 2 * k["lds"] <= 160 * 1024, k
