@@ -57,7 +57,7 @@ struct Params {
 // (the conversions of SageParams.c(): the sizes have to be integers, the other numbers go through int() and float())
 PyObject* get_int(PyObject* o, PyObject* name) {
   PyObject* v = PyObject_GetAttr(o, name);
-  if (v == nullptr || PyLong_CheckExact(v)) return v;
+  if (v == nullptr || PyLong_CheckExact(v) || PyBool_Check(v)) return v;
   PyObject* i = PyNumber_Long(v);
   Py_DECREF(v);
   return i;
