@@ -193,7 +193,6 @@ __global__ void __launch_bounds__(512, MODE == kBwdMaxOnly ? 4 : 1) sage_bwd_ker
   const int npair = (nblk + 1) / 2;
   const WorkItem wi = work_item(gidx, npair, args.head_set);
   const int hl = wi.head;             // head within this launch
-  if (hl >= args.BH) return;
   const int bh = args.bh0 + hl;
   const int jp = wi.item;             // small jp = most Q blocks under the causal mask: scheduled first
 
@@ -683,7 +682,6 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_single_kernel(BwdArgs args) {
   const int sb = CAUSAL ? args.shift_blocks : 0;
   const WorkItem wi = work_item(blockIdx.x, nblk, args.head_set);
   const int hl = wi.head;
-  if (hl >= args.BH) return;
   const int bh = args.bh0 + hl;
   const int j = wi.item;              // small j = most Q blocks under the causal mask: scheduled first
   const int kvalid = min(64, args.nvalid - 64 * j);
@@ -705,7 +703,7 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_single_kernel(BwdArgs args) {
   const float* sdOh = args.sdO + (size_t)bh * nqblk;
   const SingleWalk walk(nqblk, CAUSAL ? max(j - sb, 0) : 0);   // (at least one tile: the diagonal)
   const int itop = walk.itop, i_first = walk.i_first, T = walk.T;
-  const size_t rsq_loop = rsq * walk.loop_row_step();
+  const size_t rsq_loop = walk.loop_row_step() ? rsq : 0;
 
   // This wave's copies for Q block i (back waves): phase A's fragments are dealt to the four waves, then phase B's.
   auto copy_A = [&](int i, BwdStageA1<D>& st, auto last_tag) __attribute__((always_inline)) {
@@ -1023,7 +1021,6 @@ __global__ void __launch_bounds__(256, 3) sage_bwd_dq_kernel(DqArgs args) {
   const int npair = (nqblk + 1) / 2;
   const WorkItem wi = work_item(g, npair, args.head_set);
   const int hl = wi.head;
-  if (hl >= args.BH) return;
   const int bh = args.bh0 + hl;
   const int i0 = 2 * (npair - 1 - wi.item);            // longest rows first under the causal mask
   const int tid = threadIdx.x;

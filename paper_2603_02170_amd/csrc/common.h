@@ -157,8 +157,10 @@ __host__ __device__ inline int head_set_for(int items, int heads, bool always = 
   while (pool % hs != 0) hs--;
   return dense ? -hs : hs;
 }
+// The grid is heads * items workgroups, each of which has a (head, item) of its own (a test goes through them on the host): a
+// kernel needs no check of its head, and without one the loads of its arguments need not wait for the mapping.
 __host__ __device__ inline int grid_for(int heads, int items) { return heads * items; }
-__device__ inline WorkItem work_item(int block, int items, int head_set) {
+__host__ __device__ inline WorkItem work_item(int block, int items, int head_set) {
   const int xcds = head_set < 0 ? 1 : 8, hs = head_set < 0 ? -head_set : head_set;
   const int xcd = block % xcds, slot = block / xcds;
   const int hset = slot / (items * hs), rem = slot % (items * hs);

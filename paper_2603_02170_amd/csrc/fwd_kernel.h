@@ -347,7 +347,6 @@ __global__ void __launch_bounds__(64 * NW, (NW == 4 ? (D == 64 ? 3 : 2) : 1)) sa
   // tiles first under the causal mask, over sets of heads (see work_item)
   const WorkItem wi = work_item(blockIdx.x, args.n_qtiles, args.head_set);
   const int bh = wi.head;
-  if (bh >= args.BH) return;
   const int qt = args.n_qtiles - 1 - wi.item;
 
   const int tid = threadIdx.x;
@@ -584,7 +583,6 @@ __global__ void __launch_bounds__(128 * NQ, 2) sage_fwd_pair_kernel(FwdArgs args
 
   const WorkItem wi = work_item(blockIdx.x, args.n_qtiles, args.head_set);
   const int bh = wi.head;
-  if (bh >= args.BH) return;
   const int qt = args.n_qtiles - 1 - wi.item;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -931,7 +929,6 @@ __global__ void __launch_bounds__(512, 1) sage_fwd_split_kernel(FwdArgs args) {
 
   const WorkItem wi = work_item(blockIdx.x, args.n_qtiles, args.head_set);
   const int bh = wi.head;
-  if (bh >= args.BH) return;
   const int qt = args.n_qtiles - 1 - wi.item;
   const int tid = threadIdx.x;
   const int lane = tid & 63;

@@ -1,11 +1,35 @@
-// Every row of dO and every Q block that the staging copies of sage_bwd_single_kernel read, over all small shapes, from the
-// index functions the kernel itself uses.  Prints the first access that lies outside the tensor and returns 1.
+// Every row of dO and every Q block that the staging copies of sage_bwd_single_kernel read, over all small shapes, and the
+// (head, item) of every workgroup, from the index functions the kernels themselves use.  Prints the first access that lies
+// outside the tensor, or the first workgroup without a (head, item) of its own, and returns 1.
 #include <stdio.h>
+
+#include <vector>
 
 #include "common.h"
 #include "bwd_kernel.h"
 
+int every_workgroup_has_its_own_work() {
+  for (int heads = 1; heads <= 272; heads++)
+    for (int items = 1; items <= 68; items++)
+      for (int always = 0; always < 2; always++) {
+        const int set = sage::head_set_for(items, heads, always != 0), grid = sage::grid_for(heads, items);
+        std::vector<char> taken(heads * items, 0);
+        for (int b = 0; b < grid; b++) {
+          const sage::WorkItem w = sage::work_item(b, items, set);
+          const bool inside = w.head >= 0 && w.head < heads && w.item >= 0 && w.item < items;
+          if (!inside || taken[w.head * items + w.item]) {
+            printf("heads %d items %d set %d: workgroup %d has head %d item %d\n", heads, items, set, b, w.head, w.item);
+            return 1;
+          }
+          taken[w.head * items + w.item] = 1;
+        }
+        if (grid != heads * items) return printf("heads %d items %d: grid %d\n", heads, items, grid), 1;
+      }
+  return 0;
+}
+
 int main() {
+  if (every_workgroup_has_its_own_work()) return 1;
   long long copies = 0;
   for (int causal = 0; causal < 2; causal++)
     for (int nq = 1; nq <= 330; nq++)
