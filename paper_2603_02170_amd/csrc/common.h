@@ -149,11 +149,18 @@ struct WorkItem {
   int head, item;
 };
 // > 0: that many heads of an XCD per set; < 0: the dense layout, sets of that many heads (on a machine of one XCD, so to
-// speak, so that the mapping below stays one formula).  A set divides the heads evenly.
+// speak, so that the mapping below stays one formula).  A set divides the heads evenly; where four do not divide an XCD's heads,
+// short sequences take the next larger number that does, or all of them (five heads one at a time left the last head's heaviest items to the end:
+// calls with the mask, forward and backward in us, 40 heads of N = 1024 43 + 90 -> 39 + 65, of 2048 84 + 196 -> 73 + 167, 56 of 4096 276 + 808 -> 258 + 764).
 __host__ __device__ inline int head_set_for(int items, int heads, bool always = false) {
   const bool dense = heads % 8 != 0;
   const int pool = dense ? heads : heads / 8;
   int hs = dense && items <= 32 ? pool : (always || dense || items <= 32) ? 4 : 1;
+  if (items <= 32 && pool % hs != 0 && pool > hs) {
+    hs = 8;
+    while (pool % hs != 0) hs--;
+    if (hs < 3 && pool < 32) hs = pool;
+  }
   while (pool % hs != 0) hs--;
   return dense ? -hs : hs;
 }
