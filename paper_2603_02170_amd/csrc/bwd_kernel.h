@@ -14,6 +14,8 @@
 //            tile: dV^T += dO^^T P^, dK^T += Q^^T dS^ (accumulated in FP32 registers with the
 //            per-tile scales).
 // The phases are software-pipelined over ONE workgroup barrier per tile (see the kernel).
+// sage_bwd_single_kernel and sage_bwd_wide_kernel divide the same arithmetic over the waves in other ways, for calls with few KV
+// blocks and with many.
 // A second kernel (sage_bwd_dq_kernel) owns two Q blocks per workgroup and forms
 //   dQ_i = sum_j s_dS(i,j) s_K(j) sm_scale * (dS^_ij K^_j)
 // from the stored INT8 tiles: a plain scaled INT8 GEMM with no atomics, so dQ is
@@ -960,6 +962,406 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_single_kernel(BwdArgs args) {
     }
   }
   __builtin_amdgcn_s_waitcnt(vmcnt_only(0));                 // (the copies past the last tile land before the LDS is given up)
+}
+
+// ---- four KV blocks per workgroup ----------------------------------------------------------------------
+// sage_bwd_wide_kernel (d = 128).  The kernel above divides every tile between four waves twice over: a quadrant of S and dP
+// each, then a channel block of dV and dK each, with psi(P) and psi(dS) handed over through LDS in between.  Here a wave owns 32
+// KEYS: it forms S and dP of all 64 queries of a tile against them, and the quantised P and dS, one key per lane, are the B
+// operands of its own dV and dK as they stand.  Two waves share a KV block and exchange the two tile maxima, nothing else; eight
+// waves hold four KV blocks and share every staged Q block.  Against sage_bwd_kernel, per 64 x 64 tile: 100 instead of 128 KB of
+// operands read from LDS and none written to it, half the staging copies, half the barriers, and 298 instead of 336 vector instructions per
+// 32 x 32 piece.  The values, their order and so the bits are the same.
+//
+// Of a wave's 256 registers 128 hold dV and dK of its keys, 12 hold K^ (its last fragment lies in LDS: with 16 the allocator put
+// one into scratch, whose reload waits for the copies in flight), and 64 carry P and dS from one interval to the next (psi needs
+// the maxima of the whole tile).  The interval's products are laid out by hand, one between two scheduling barriers with the
+// vector work that runs beside it, LDS operands two or three products ahead:
+//   psi of the last tile  |  16 products of its dV, dK; beside them the INT32 -> FP32 updates of the product before, and
+//   between those of dK the 8 products of S of this tile  |  16 products of dP; beside them P of this tile  |  dS, maxima
+// The masked form of an interval (the first one, the diagonal, a partial KV block, the last one) has the same shape: it forms
+// everything and masks what does not exist, because branches around its phases cost the allocator its registers as well (K^ in
+// scratch: slower than the kernel above).
+//
+// Measured (us, two KV blocks per workgroup -> four): 64 heads of N = 2048 with the mask 206 -> 157, 32 of 4096 358 -> 273, 64 of
+// 8192 2657 -> 2030; 8 heads of 8192 without 632 -> 468.  Steps on the way, the last of these shapes: K^ out of scratch 566 -> 498;
+// dO copied as whole rows 488 -> 485; the copies dealt to the products instead of issued at the head of the interval, row statistics and
+// exp2 one product ahead 485 -> 465; the younger wave of a SIMD first in phase B 462 -> 452.
+// What bounds it: of about 7000 cycles an interval the vector instructions of a SIMD's two waves (1192, at 2.4 to 8.4 each) take
+// 4300 and the 80 products 2560 of the matrix pipe; the rest is chains (psi, the end of dS) that two waves do not cover.
+template <int D>
+struct BwdStageA4 {           // operands of phase A for one Q block
+  int8_t qf[64 * D];          // Q^  F fragments
+  int8_t dof[128 * D];        // bf16 dO, row by row; 16-byte piece c of row r in slot c ^ (r & 15) of the row
+  float nl2[64];              // -L * log2(e)
+  float dl[64];               // -delta
+};
+
+template <int D, bool CAUSAL, int MODE = kBwdFused, bool KV128 = false>
+__global__ void __launch_bounds__(512, 1) sage_bwd_wide_kernel(BwdArgs args) {
+  static_assert(D == 128 && MODE != kBwdMaxOnly, "");
+  constexpr int KS = D / 32;       // INT8 k-steps over d; channel blocks
+  constexpr int KB = D / 16;       // bf16 k-steps over d
+  constexpr int TILE = 64 * D;     // bytes of one INT8 tile
+  constexpr int NF = TILE / 1024;  // 1 KiB fragments per INT8 tile
+  constexpr int PPR = D / 8, RPF = 64 / PPR;   // 16-byte pieces of a bf16 row, rows per 1 KiB
+  static_assert(NF == 8 && PPR == 16, "copies: one fragment of each kind per wave");
+  struct Lds {
+    BwdStageA4<D> stA[2];
+    int8_t stB[2][2][TILE];        // [buffer][Q^, dO^]: TF fragments
+    int8_t kst[8][1024];           // [wave]: the last of the KS fragments of K^ of its 32 keys (the others stay in registers)
+    int8_t vst[8][32 * D * 2];     // [wave]: bf16 V of the wave's 32 keys as B fragments; at the end its dV, dK rows
+    unsigned red[2][8][2];         // [tile parity][wave][max P, max |dS|] as bit patterns
+  };
+  __shared__ __attribute__((aligned(256))) Lds L;
+
+  const int N = args.N;
+  const int nblk = N / kBlock;          // KV blocks
+  const int nqblk = args.Nq / kBlock;   // Q blocks
+  const int sb = CAUSAL ? args.shift_blocks : 0;
+  const WorkItem wi = work_item(blockIdx.x, (nblk + 3) / 4, args.head_set);
+  const int hl = wi.head;               // head within this launch
+  const int bh = args.bh0 + hl;
+  const int j0 = 4 * wi.item;           // small = most Q blocks under the causal mask: scheduled first
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ll = lane & 31, h = lane >> 5;
+  const int kb = wave & 1;                        // 32-key half of the KV block
+  const int j = j0 + (wave >> 1);
+  const bool valid = j < nblk;
+  const int jc = valid ? j : nblk - 1;            // clamped: a wave without a block still loads in bounds
+  const int kvalid = min(64, args.nvalid - 64 * jc);
+
+  const size_t qhead = (size_t)bh * args.Nq * D;
+  const size_t rs = args.cv.row_stride, rsq = args.cvq.row_stride;
+  const size_t chead = args.cv.row(bh, 0), cqhead = args.cvq.row(bh, 0);
+  const float sKj = scalar_load(args.sK + (size_t)bh * nblk + jc);
+  const float* sQh = args.sQ + (size_t)bh * nqblk;
+  const float* sdOh = args.sdO + (size_t)bh * nqblk;
+  // the walk: tile t is Q block itop - t, t = 0 .. T - 1 (at least one: the diagonal)
+  const SingleWalk walk(nqblk, CAUSAL ? max(j0 - sb, 0) : 0);
+  const int itop = walk.itop, T = walk.T;
+  const size_t rsq_loop = walk.loop_row_step() ? rsq : 0;
+
+  unsigned lane16 = lane * 16;
+  // dO: this lane's piece of a fragment of four rows, in bytes (the wave copies fragments `wave` and `wave + 8`: rows 4 wave + ..
+  // of either half)
+  unsigned dO_lane = (unsigned)((lane / PPR) * 2 * rsq_loop + ((lane ^ (RPF * wave + lane / PPR)) & (PPR - 1)) * 16);
+  v4i kfr[KS - 1];
+  {
+    const int8_t* p = args.KF + (size_t)bh * N * D + ((size_t)(2 * jc + kb) * KS) * 1024 + lane16;
+#pragma unroll
+    for (int s = 0; s < KS - 1; s++) kfr[s] = *(const v4i*)(p + s * 1024);
+    async_copy_16(p + (KS - 1) * 1024, L.kst[wave]);
+    // (a key row that does not exist re-reads the last one that does: its P is masked to zero)
+    const unsigned short* pv = args.V + chead + (size_t)min(64 * jc + 32 * kb + ll, args.nvalid - 1) * rs + 8 * h;
+#pragma unroll
+    for (int s = 0; s < KB; s++) async_copy_16(pv + 16 * s, L.vst[wave] + s * 1024);
+  }
+  // the operands of phase A of tile 0: Q block itop may be the partial last one, so each row of dO is clamped
+  {
+    BwdStageA4<D>& st = L.stA[0];
+    async_copy_16(args.QF + qhead + (size_t)itop * TILE + wave * 1024 + lane16, st.qf + wave * 1024);
+#pragma unroll
+    for (int f = wave; f < 2 * NF; f += 8) {
+      const int r = RPF * f + lane / PPR;
+      async_copy_16(args.dO + cqhead + (size_t)dO_row_clamped(64 * itop + r, args.nq_valid) * rsq + 8 * ((lane ^ r) & (PPR - 1)),
+                    st.dof + f * 1024);
+    }
+    async_copy_4(((wave & 1) ? args.delta : args.nL2) + (size_t)bh * args.Nq + 64 * itop + lane, (wave & 1) ? st.dl : st.nl2);
+  }
+
+  v16f dvacc[KS], dkacc[KS];
+  float p[2][16], ds[2][16];     // [q half] P and dS of the wave's 64 x 32 piece of a tile, between its two intervals
+#pragma unroll
+  for (int r = 0; r < 16; r++) {
+#pragma unroll
+    for (int t = 0; t < KS; t++) dvacc[t][r] = dkacc[t][r] = 0.f;
+    p[0][r] = p[1][r] = ds[0][r] = ds[1][r] = 0.f;
+  }
+  // maxima as bit patterns (non-negative floats order like theirs), kept in scalar registers
+  int own_p = 0, own_d = 0;                                               // the wave's own, of that piece
+  int prev_p = 0, prev_d = 0;                                             // kBwdPairedRows: the last tile's
+  float sq = scalar_load(sQh + itop), sd = scalar_load(sdOh + itop);      // s_Q, s_dO of tile t
+  float sq1 = 0.f, sd1 = 0.f;                                             // ... of tile t - 1
+  const unsigned dO_read = (unsigned)(uintptr_t)(lptr_t)L.stA[0].dof + ll * 2 * D + ((h ^ ll) & (PPR - 1)) * 16;
+  barrier_all_memory();
+
+  // Interval t: psi, dV, dK of tile t - 1; S, dP, P, dS of tile t; copies of phase A's operands of tile t + 1 and of phase B's of
+  // tile t (past the last tile that one again, never used).  One barrier at its end.
+  auto interval = [&](const int t, auto mask_tag) __attribute__((always_inline)) {
+    constexpr bool MASK = decltype(mask_tag)::value;
+    const int iq = itop - (t - 1), ia = itop - t;
+    const bool act_q = !MASK || (t >= 1 && valid && (!CAUSAL || iq + sb >= j));
+    const bool act_a = !MASK || (t < T && valid && (!CAUSAL || ia + sb >= j));
+    asm volatile("" : "+v"(lane16), "+v"(dO_lane));     // (keeps their extension to 64 bits out of registers)
+    const BwdStageA4<D>& st = L.stA[t & 1];
+    const int8_t* stq = L.stB[(t - 1) & 1][0] + lane16;
+    const int8_t* stdo = L.stB[(t - 1) & 1][1] + lane16;
+    const int8_t* qfp = st.qf + lane16;
+    const int8_t* vbp = L.vst[wave] + lane16;
+    const unsigned dofp = dO_read + (t & 1) * (unsigned)sizeof(BwdStageA4<D>);
+    const unsigned(&R)[8][2] = L.red[(t - 1) & 1];
+    unsigned pu, du;                                    // the other waves' maxima of the numerics block
+    if constexpr (KV128) {
+      const int g = wave & 4;
+      pu = max(max(R[g][0], R[g + 1][0]), max(R[g + 2][0], R[g + 3][0]));
+      du = max(max(R[g][1], R[g + 1][1]), max(R[g + 2][1], R[g + 3][1]));
+    } else {
+      pu = R[wave ^ 1][0];
+      du = R[wave ^ 1][1];
+    }
+    // copy `part` of this wave's six
+    const int in = walk.at(t + 1), ic = walk.at(t);
+    auto copy_part = [&](int part) __attribute__((always_inline)) {
+      BwdStageA4<D>& sa = L.stA[(t + 1) & 1];
+      int8_t(&sbuf)[2][TILE] = L.stB[t & 1];
+      const size_t toff = qhead + (size_t)in * TILE + wave * 1024, coff = qhead + (size_t)ic * TILE + wave * 1024;
+      if (part == 0) copy_16(uniform(args.QF + toff) + lane16, sa.qf + wave * 1024);
+      if (part == 1 || part == 2) {
+        const int f = wave + 8 * (part - 1);
+        copy_16(uniform(args.dO + cqhead + (size_t)(64 * in) * rsq + (size_t)(RPF * f) * rsq_loop) + dO_lane, sa.dof + f * 1024);
+      }
+      if (part == 3)
+        copy_4(uniform(((wave & 1) ? args.delta : args.nL2) + (size_t)bh * args.Nq + 64 * in) + (lane16 >> 2), (wave & 1) ? sa.dl : sa.nl2);
+      if (part == 4) copy_16(uniform(args.QT + coff) + lane16, sbuf[0] + wave * 1024);
+      if (part == 5) copy_16(uniform(args.dOT + coff) + lane16, sbuf[1] + wave * 1024);
+    };
+    const float sqn = scalar_load(sQh + in), sdn = scalar_load(sdOh + in);
+    __builtin_amdgcn_sched_barrier(0);
+    if (!MASK || act_a || act_q) {
+      // ---------------- psi of tile t - 1 ----------------
+      pu = max(pu, (unsigned)own_p);
+      du = max(du, (unsigned)own_d);
+      if constexpr (MODE == kBwdPairedRows) {
+        // the other Q block of the numerics block: below (iq odd: the stored maxima of tile (iq - 1, j), and of its neighbour
+        // in the 128-key block, where those tiles exist) or above (iq even: the last interval's)
+        const unsigned bp = pu, bd = du;
+        if (iq & 1) {
+          const int jm = KV128 ? (jc & ~1) : jc;
+          const float* tm = args.tmax + 2 * (((size_t)hl * nqblk + iq - 1) * args.ds_pitch + jm);
+          if (!CAUSAL || jm <= iq - 1 + sb) {
+            pu = max(pu, __float_as_uint(scalar_load(tm)));
+            du = max(du, __float_as_uint(scalar_load(tm + 1)));
+          }
+          if (KV128 && jm + 1 < nblk && (!CAUSAL || jm + 1 <= iq - 1 + sb)) {
+            pu = max(pu, __float_as_uint(scalar_load(tm + 2)));
+            du = max(du, __float_as_uint(scalar_load(tm + 3)));
+          }
+        } else if (iq + 1 < nqblk) {
+          pu = max(pu, (unsigned)prev_p);
+          du = max(du, (unsigned)prev_d);
+        }
+        prev_p = __builtin_amdgcn_readfirstlane((int)bp);
+        prev_d = __builtin_amdgcn_readfirstlane((int)bd);
+      }
+      if (MASK && !act_q) pu = du = 0u;       // (the first interval: no tile, nothing written to those maxima yet)
+      const float bpm = __uint_as_float(pu), bdm = __uint_as_float(du);
+      // the per-tile scales of P and dS are internal (never stored bit-exactly): 127/a via rcp
+      const float rP = bpm > 0.f ? 127.0f * __builtin_amdgcn_rcpf(bpm) : 0.f;
+      const float rS = bdm > 0.f ? 127.0f * __builtin_amdgcn_rcpf(bdm) : 0.f;
+      const float sP = bpm * (1.0f / 127.0f), sS = bdm * (1.0f / 127.0f);
+      v4i pf[2], df[2];            // [q half]: B operands of dV, dK, one key per lane
+#pragma unroll
+      for (int qh = 0; qh < 2; qh++)
+#pragma unroll
+        for (int aa = 0; aa < 4; aa++) {
+          unsigned up = 0;
+#pragma unroll
+          for (int b = 0; b < 4; b++) up = __builtin_amdgcn_cvt_pk_u8_f32(p[qh][4 * aa + b] * rP, b, up);
+          pf[qh][aa] = (int)up;
+        }
+#pragma unroll
+      for (int qh = 0; qh < 2; qh++)
+#pragma unroll
+        for (int aa = 0; aa < 4; aa++) {
+          unsigned ub[4];
+#pragma unroll
+          for (int b = 0; b < 4; b++) ub[b] = __float_as_uint(__builtin_fmaf(ds[qh][4 * aa + b], rS, kRoundMagic));
+          df[qh][aa] = (int)(__builtin_amdgcn_perm(ub[1], ub[0], 0x0c0c0400u) | __builtin_amdgcn_perm(ub[3], ub[2], 0x04000c0cu));
+        }
+      const float w_dv = sP * sd1;
+      const float w_dk = sS * sq1 * args.sm_scale;
+      if (!MASK || act_q) {
+        // fragments (q half, kb) of the tile, as sage_bwd_kernel stores them
+        const size_t tile = ((size_t)hl * nqblk + iq) * args.ds_pitch + j;
+        const gbytes_t dst = uniform(args.dSq + tile * 4096 + kb * 1024) + lane16;
+        *(__attribute__((address_space(1))) v4i*)dst = df[0];
+        *(__attribute__((address_space(1))) v4i*)(dst + 2048) = df[1];
+        args.sdS[tile] = sS;       // (the same value from every lane)
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      // ---------------- dV, dK of tile t - 1 (phase B), S of tile t ----------------
+      // Products u = 0 .. KS - 1: dV of channel block u, u = KS .. 2 KS - 1: dK of block u - KS, two steps each; those of dK have two
+      // products of S (q half s / KS, step s % KS) between them: psi(P) is dead by then.
+      first_for_younger_waves<1>(wave);
+      struct Slot {
+        int u, k, s;               // step k of product u, or (k < 0) product s of S
+      };
+      constexpr int NM = 6 * KS;
+      auto slot = [](int m) constexpr {
+        if (m < 2 * KS) return Slot{m / 2, m % 2, 0};
+        const int n = m - 2 * KS;
+        return n % 2 == 0 ? Slot{KS + n / 4, (n / 2) % 2, 0} : Slot{KS + n / 4, -1, n / 2};
+      };
+      v16i res[2], sacc[2], zero;
+      v4i op[4], klast;
+#pragma unroll
+      for (int r = 0; r < 16; r++) zero[r] = 0;
+      auto read_op = [&](int m) __attribute__((always_inline)) {
+        const Slot sl = slot(m);
+        op[m % 4] = sl.k >= 0 ? *(const v4i*)((sl.u < KS ? stdo : stq) + (sl.k * KS + sl.u % KS) * 1024) : *(const v4i*)(qfp + sl.s * 1024);
+      };
+      auto update = [&](int u, int r0, int r1) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = r0; r < r1; r++) {
+          if (u >= KS) dkacc[u % KS][r] = __builtin_fmaf((float)res[u & 1][r], w_dk, dkacc[u % KS][r]);
+          else dvacc[u][r] = __builtin_fmaf((float)res[u & 1][r], w_dv, dvacc[u][r]);
+        }
+      };
+#pragma unroll
+      for (int m = 0; m < 3; m++) read_op(m);
+#pragma unroll
+      for (int m = 0; m < NM; m++) {
+        const Slot sl = slot(m);
+        if (m + 3 < NM) read_op(m + 3);
+        if (sl.k < 0 && sl.s % KS == KS - 2) klast = *(const v4i*)(L.kst[wave] + lane16);
+        if (sl.k >= 0)
+          res[sl.u & 1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(op[m % 4], sl.u < KS ? pf[sl.k] : df[sl.k], sl.k == 0 ? zero : res[sl.u & 1], 0, 0, 0);
+        else
+          sacc[sl.s / KS] = __builtin_amdgcn_mfma_i32_32x32x32_i8(op[m % 4], sl.s % KS == KS - 1 ? klast : kfr[sl.s % KS], sl.s % KS == 0 ? zero : sacc[sl.s / KS], 0, 0, 0);
+        if (sl.u > 0 && sl.u < KS) update(sl.u - 1, 8 * (m % 2), 8 * (m % 2) + 8);
+        if (sl.u >= KS) update(sl.u - 1, 4 * (m % 4), 4 * (m % 4) + 4);
+        if (m % 3 == 1 && m / 3 < 6) copy_part(m / 3);     // (dealt out: the waves do not queue up at the memory pipeline)
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      first_for_younger_waves<0>(wave);
+      // ---------------- dP, P, dS of tile t ----------------
+      const float c = sq * sKj * args.scale_log2e;
+      v16f dp[2];
+      v8bf da[3], vb[2];
+      v4f l4[2];
+      auto read_dO = [&](int m) __attribute__((always_inline)) {     // product m: q half m % 2, step m / 2
+        da[m % 3] = *(const __attribute__((address_space(3))) v8bf*)(uintptr_t)((dofp ^ ((m / 2) * 32)) + (m & 1) * 64 * D);
+      };
+      auto read_V = [&](int s) __attribute__((always_inline)) { vb[s % 2] = *(const v8bf*)(vbp + s * 1024); };
+      auto read_L = [&](int g) __attribute__((always_inline)) { l4[g & 1] = *(const v4f*)(st.nl2 + 4 * h + 32 * (g >> 2) + 8 * (g & 3)); };
+      float pm = 0.f, dm = 0.f;
+      // masked: the rows of the tile below klow + 4 h (under the diagonal), or all 64 of a key or of a tile that does not exist
+      const int klow = !act_a || 32 * kb + ll >= kvalid ? 64 : CAUSAL && ia + sb == j ? 32 * kb + ll - 4 * h : -64;
+      // P of element e (q half e / 16, register e % 16 = query 8 (r / 4) + 4 h + r % 4 of it), in three steps that run one product apart
+      auto form_x = [&](int e) __attribute__((always_inline)) {
+        p[e >> 4][e & 15] = __builtin_fmaf((float)sacc[e >> 4][e & 15], c, l4[(e >> 2) & 1][e & 3]);
+      };
+      auto form_p = [&](int e) __attribute__((always_inline)) {
+        const int qh = e >> 4, r = e & 15;
+        const float pv = __builtin_amdgcn_exp2f(p[qh][r]);
+        p[qh][r] = MASK && 32 * qh + 2 * (r & ~3) + (r & 3) < klow ? 0.f : pv;
+      };
+      auto form_max = [&](int e) __attribute__((always_inline)) { pm = fmaxf(fmaxf(p[e >> 4][e & 15], p[e >> 4][(e & 15) + 1]), pm); };
+      read_V(0);
+      read_dO(0);
+      read_dO(1);
+      read_L(0);
+      // dS = P o (dP - delta): the chains start from -delta of the rows a lane's registers hold
+      auto read_delta = [&](int qh) __attribute__((always_inline)) {
+#pragma unroll
+        for (int aa = 0; aa < 4; aa++) {
+          const v4f d4 = *(const v4f*)(st.dl + 32 * qh + 4 * h + 8 * aa);
+#pragma unroll
+          for (int b = 0; b < 4; b++) dp[qh][4 * aa + b] = d4[b];
+        }
+      };
+      read_delta(0);
+      __builtin_amdgcn_sched_barrier(0);
+      update(2 * KS - 1, 0, 16);         // (while those reads are under way; its operands' registers go to the second chain)
+      __builtin_amdgcn_sched_barrier(0);
+      read_delta(1);
+#pragma unroll
+      for (int m = 0; m < 2 * KB; m++) {
+        if (m + 2 < 2 * KB) read_dO(m + 2);
+        if (m % 2 == 0 && m / 2 + 1 < KB) {
+          read_V(m / 2 + 1);
+          read_L(m / 2 + 1);
+        }
+        dp[m & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(da[m % 3], vb[(m / 2) % 2], dp[m & 1], 0, 0, 0);
+        if (m >= 2) form_max(2 * m - 4);
+        if (m >= 1) {
+          form_p(2 * m - 2);
+          form_p(2 * m - 1);
+        }
+        form_x(2 * m);
+        form_x(2 * m + 1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      form_max(28);
+      form_p(30);
+      form_p(31);
+      form_max(30);
+#pragma unroll
+      for (int qh = 0; qh < 2; qh++)
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+#pragma unroll
+          for (int b = r; b < r + 2; b++) {
+            ds[qh][b] = p[qh][b] * dp[qh][b];
+            if constexpr (MASK) ds[qh][b] = act_a ? ds[qh][b] : 0.f;   // (no tile: nothing, whatever the stage holds)
+          }
+          dm = fmaxf(fmaxf(fabsf(ds[qh][r]), fabsf(ds[qh][r + 1])), dm);
+        }
+      own_p = __builtin_amdgcn_readfirstlane(__float_as_int(wave_max_nonneg_f32(pm)));
+      own_d = __builtin_amdgcn_readfirstlane(__float_as_int(wave_max_nonneg_f32(dm)));
+      L.red[t & 1][wave][0] = (unsigned)own_p;     // (the same pair from every lane)
+      L.red[t & 1][wave][1] = (unsigned)own_d;
+    } else {
+#pragma unroll
+      for (int part = 0; part < 6; part++) copy_part(part);
+      if constexpr (KV128) L.red[t & 1][wave][0] = L.red[t & 1][wave][1] = 0u;   // nothing for the neighbour's block maxima
+    }
+    sq1 = sq;
+    sd1 = sd;
+    sq = sqn;
+    sd = sdn;
+    barrier_all_memory();   // the interval's LDS traffic, copies and stores are complete
+  };
+  // unmasked intervals: both tiles exist in full, tile t above the diagonal
+  const int t_steady_end = !valid || kvalid < 64 ? 0 : CAUSAL ? min(itop + sb - j, T - 1) : T - 1;
+  // the first interval, the unmasked ones, the others (written so that the masked form is there once)
+#pragma clang loop unroll(disable)
+  for (int t = 0; t <= T;) {
+    interval(t++, std::true_type{});
+#pragma clang loop unroll(disable)
+    for (; t < t_steady_end; t++) interval(t, std::false_type{});
+  }
+
+  if (!valid) return;
+  // ---- write dV, then dK (bf16): through the wave's own V stage (nobody else reads it), so that whole rows leave.  Piece c of row
+  // r lies in slot c ^ (r & 15) of its row. ----
+  int8_t* stg = L.vst[wave];
+  const int key0 = 64 * j + 32 * kb;
+#pragma unroll
+  for (int which = 0; which < 2; which++) {
+    const v16f(&acc)[KS] = which == 0 ? dvacc : dkacc;
+    unsigned short* out = (which == 0 ? args.dV : args.dK) + chead;
+#pragma unroll
+    for (int cb = 0; cb < KS; cb++)
+#pragma unroll
+      for (int aa = 0; aa < 4; aa++) {
+        v4us o;
+#pragma unroll
+        for (int b = 0; b < 4; b++) o[b] = float_to_bf16_bits(acc[cb][4 * aa + b]);
+        *(v4us*)(stg + ll * 2 * D + (((4 * cb + aa) ^ ll) & (PPR - 1)) * 16 + 8 * h) = o;
+      }
+    // (one wave: its LDS operations complete in order)
+#pragma unroll
+    for (int k = 0; k < 32 / RPF; k++) {
+      const int r = RPF * k + lane / PPR;
+      const v8us piece = *(const v8us*)(stg + r * 2 * D + ((lane ^ r) & (PPR - 1)) * 16);
+      if (key0 + r < args.nvalid) *(v8us*)(out + (size_t)(key0 + r) * rs + 8 * (lane % PPR)) = piece;
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------------

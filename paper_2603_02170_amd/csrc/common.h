@@ -97,6 +97,28 @@ __device__ __forceinline__ void async_copy_4(const void* gsrc_lane, void* lds_ba
   __builtin_amdgcn_global_load_lds((gptr_t)gsrc_lane, (lptr_t)lds_base, 4, 0, 0);
 }
 
+// A wave-uniform address as the compiler must take it: in scalar registers, so that an access adds 32 bits of lane offset to it
+// (left alone it keeps 64-bit sums of base and lane in vector registers).
+typedef __attribute__((address_space(1))) char* gbytes_t;
+__device__ __forceinline__ gbytes_t uniform(const void* p) {
+  gbytes_t g = (gbytes_t)p;
+  asm("" : "+s"(g));
+  return g;
+}
+__device__ __forceinline__ void copy_16(gbytes_t gsrc_lane, void* lds_base) {
+  __builtin_amdgcn_global_load_lds((gptr_t)gsrc_lane, (lptr_t)lds_base, 16, 0, 0);
+}
+__device__ __forceinline__ void copy_4(gbytes_t gsrc_lane, void* lds_base) {
+  __builtin_amdgcn_global_load_lds((gptr_t)gsrc_lane, (lptr_t)lds_base, 4, 0, 0);
+}
+
+// Issue priority P for waves 4 to 7 of a workgroup of eight: where two waves share a SIMD the arbiter favours the older one.
+// (The branch is inside the assembly: the code around it stays one basic block for the scheduler and the register allocator.)
+template <int P>
+__device__ __forceinline__ void first_for_younger_waves(int wave) {
+  asm volatile("s_cmp_lt_u32 %0, 4\n\ts_cbranch_scc1 .Lolder%=\n\ts_setprio %1\n.Lolder%=:" ::"s"(wave), "n"(P) : "scc");
+}
+
 // A wave-uniform value through the scalar cache: no vector-memory instruction and no register of 64 lanes.  (The
 // buffer must not be written by the same kernel.)
 __device__ __forceinline__ float scalar_load(const float* p) {

@@ -1,0 +1,50 @@
+"""The backward with four KV blocks per workgroup gives the bits of the forms that a head alone takes."""
+import pytest
+import torch
+
+from paper_2603_02170_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+
+# one to five KV blocks (workgroups with idle waves), one Q block and more, whole and partial last blocks of either side, the mask
+# with and without a shift (the diagonal of the four blocks lies in different intervals), numerics blocks of 128 in either direction
+# (pairs of blocks of which one does not exist, is not visible, or lies in the next workgroup; odd and even Q block counts)
+@pytest.mark.parametrize("bq,bkv", [(0, 0), (64, 128), (128, 64), (128, 128)])
+@pytest.mark.parametrize("Nq,Nk,causal", [(64, 64, True), (1, 100, False), (50, 600, False), (100, 228, True), (256, 256, True), (300, 300, True),
+                                          (640, 640, True), (200, 321, False), (448, 70, False), (64, 512, True), (130, 450, True)])
+def test_four_kv_blocks_per_workgroup_give_the_same_bits(Nq, Nk, causal, bq, bkv):
+    d, nblk = 128, -(-Nk // 64)
+    heads = 1024 // nblk + 9            # more than 256 workgroups of four blocks and 768 blocks in all
+    g = torch.Generator(device="cuda").manual_seed(1000 * Nq + Nk)
+    rand = lambda n, s: (torch.randn((1, heads, n, d), generator=g, device="cuda") * s).to(torch.bfloat16)
+    Q, K, V, dO = rand(Nq, 1.5), rand(Nk, 1.5), rand(Nk, 1.0), rand(Nq, 1.0)
+    kw = dict(causal=causal, Nkv=Nk, bq=bq, bkv=bkv)
+    p, p1 = binding.SageParams(1, heads, Nq, d, **kw), binding.SageParams(1, 1, Nq, d, **kw)
+    O, L = binding.sagebwd_fwd(Q, K, V, p)
+    many = binding.sagebwd_bwd(Q, K, V, O, dO, L, p)
+    for h in (0, heads // 2, heads - 1):
+        sl = slice(h, h + 1)
+        one = binding.sagebwd_bwd(*(t[:, sl].contiguous() for t in (Q, K, V, O, dO)), L[:, sl].contiguous(), p1)
+        torch.cuda.synchronize()
+        for a, b, name in zip(many, one, ("dQ", "dK", "dV")):
+            assert torch.isfinite(b.float()).all()
+            assert torch.equal(a[:, sl], b), (h, name)
+
+
+@pytest.mark.parametrize("Nq,Nk,causal", [(200, 321, False), (640, 640, True), (1, 100, False)])
+def test_token_major_tensors(Nq, Nk, causal):
+    heads, d = 1024 // (-(-Nk // 64)) + 9, 128
+    g = torch.Generator(device="cuda").manual_seed(Nq + Nk)
+    rand = lambda n: torch.randn((1, heads, n, d), generator=g, device="cuda").to(torch.bfloat16)
+    Q, K, V, dO = rand(Nq), rand(Nk), rand(Nk), rand(Nq)
+    got = []
+    for tm in (False, True):
+        p = binding.SageParams(1, heads, Nq, d, causal=causal, Nkv=Nk, token_major=tm)
+        q, k, v, do = (t.transpose(1, 2).contiguous() if tm else t for t in (Q, K, V, dO))
+        O, L = binding.sagebwd_fwd(q, k, v, p)
+        grads = binding.sagebwd_bwd(q, k, v, O, do, L, p)
+        torch.cuda.synchronize()
+        got.append([t.transpose(1, 2) if tm else t for t in grads])
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
