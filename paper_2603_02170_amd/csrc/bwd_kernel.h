@@ -96,12 +96,11 @@ struct BwdExchange {          // per group of 4 waves and tile parity
   int8_t dsb[4096];           // psi(dS) B fragments
 };
 
-// phase A element-wise work of one quadrant (`dp` holds dP - delta, or dP with -delta passed in `dl`); MASK = some entries of the tile are masked: query row
+// phase A element-wise work of one quadrant (`dp` holds dP - delta); MASK = some entries of the tile are masked: query row
 // qrow0 + 8 aa + b of the tile sees key column kcol only up to column klim_row (the row itself on
 // the causal diagonal, 63 elsewhere) and only if the key exists (kcol < kvalid)
 template <bool MASK, bool QSMOOTH>
-__device__ __forceinline__ void bwd_quadrant(const v16i& sacc, const v16f& dp, const float* __restrict__ nl2,
-                                             const float* __restrict__ dl, const float c, const float bias_l,
+__device__ __forceinline__ void bwd_quadrant(const v16i& sacc, const v16f& dp, const float* __restrict__ nl2, const float c, const float bias_l,
                                              const int qrow0, const int kcol, const bool diag, const int kvalid,
                                              float (&p)[16], float (&ds)[16], float& pm, float& dm, float& cs) {
   float pm2[2] = {0.f, 0.f}, dm2[2] = {0.f, 0.f};
@@ -109,16 +108,13 @@ __device__ __forceinline__ void bwd_quadrant(const v16i& sacc, const v16f& dp, c
 #pragma unroll
   for (int aa = 0; aa < 4; aa++) {
     const v4f l4 = *(const v4f*)(nl2 + 8 * aa);
-    v4f d4 = {0.f, 0.f, 0.f, 0.f};
-    if constexpr (QSMOOTH) d4 = *(const v4f*)(dl + 8 * aa);     // -delta
 #pragma unroll
     for (int b = 0; b < 4; b++) {
       const int r = 4 * aa + b;
       const float off = QSMOOTH ? bias_l + l4[b] : l4[b];
       float pv = __builtin_amdgcn_exp2f(__builtin_fmaf((float)sacc[r], c, off));
       if constexpr (MASK) pv = ((diag && (qrow0 + 8 * aa + b) < kcol) || kcol >= kvalid) ? 0.f : pv;
-      // (without Q-smoothing the dP accumulators started from -delta)
-      const float dsv = QSMOOTH ? pv * (dp[r] + d4[b]) : pv * dp[r];
+      const float dsv = pv * dp[r];
       p[r] = pv;
       ds[r] = dsv;
       pm2[aa & 1] = fmaxf(pm2[aa & 1], pv);
@@ -128,6 +124,14 @@ __device__ __forceinline__ void bwd_quadrant(const v16i& sacc, const v16f& dp, c
   }
   pm = fmaxf(pm2[0], pm2[1]);
   dm = fmaxf(dm2[0], dm2[1]);
+}
+
+// Q-smoothing: dK_bias = (dS^T 1) mu_Q^T with the unquantised column sums of a tile, on the FP32 matrix instruction (contraction
+// over two) straight into the accumulators of dK, before the tile's own products are added: rows = channels, one key per lane, the two
+// lane halves' sums are the two terms: `cs` = (this lane half's sum over the first 32 rows of the Q block + over the second) * sm_scale.
+// (As 16 FMAs into accumulators of their own it took 16 more registers per 32 x 32 block of dK and a read of mu_Q per four channels.)
+__device__ __forceinline__ v16f add_dk_bias(const v16f& dk, const float muq, const float cs) {
+  return __builtin_amdgcn_mfma_f32_32x32x2f32(muq, cs, dk, 0, 0, 0);
 }
 
 // Schedule.  The tiles of a group (Q blocks i = nblk-1 .. i_first against its KV block) go
@@ -175,7 +179,7 @@ __global__ void __launch_bounds__(512, MODE == kBwdMaxOnly ? 4 : 1) sage_bwd_ker
     __attribute__((aligned(16))) int8_t xch_bytes[VREG ? 16 : 4 * sizeof(BwdExchange)];   // [group][tile parity]
     int8_t vst[VREG ? 1 : 2][VREG ? 16 : 2 * D * 64];   // [group]: bf16 V_j as B fragments (key block, 16-channel step)
     unsigned red[2][2][4][2];                       // [group][tile parity][wave][max P, max |dS|] as bit patterns
-    float csum[QSMOOTH ? 2 * 3 * 2 * 64 : 1];       // [group][tile % 3][q half][key]: column sums of dS
+    float csum[QSMOOTH ? 2 * 3 * 2 * 2 * 64 : 1];   // [group][tile % 3][q half][lane half][key]: column sums of dS
     float tmx[MODE == kBwdPairedRows ? 2 * 2 * 64 : 1];   // [tile parity][group][even lanes: max P, odd lanes: max |dS|]
   };
   __shared__ __attribute__((aligned(16))) Lds L;
@@ -247,14 +251,13 @@ __global__ void __launch_bounds__(512, MODE == kBwdMaxOnly ? 4 : 1) sage_bwd_ker
     }
   }
 
-  v16f dvacc[NPB], dkacc[NPB], dkbias[QSMOOTH ? NPB : 1];
+  v16f dvacc[NPB], dkacc[NPB];
 #pragma unroll
   for (int t = 0; t < NPB; t++)
 #pragma unroll
     for (int r = 0; r < 16; r++) {
       dvacc[t][r] = 0.f;
       dkacc[t][r] = 0.f;
-      if constexpr (QSMOOTH) dkbias[t][r] = 0.f;
     }
 
   const int i_first = CAUSAL ? max(2 * jp - sb, 0) : 0;
@@ -356,6 +359,10 @@ __global__ void __launch_bounds__(512, MODE == kBwdMaxOnly ? 4 : 1) sage_bwd_ker
 #pragma unroll
       for (int tt = 0; tt < NPB; tt++) {
         const int kbo = blk0 + tt;
+        if constexpr (QSMOOTH) {
+          const float* cs = csum + ((grp * 3 + (t - 2) % 3) * 4 + h) * 64 + 32 * kbo + ll;
+          dkacc[tt] = add_dk_bias(dkacc[tt], st.muq[32 * cb + ll], (cs[0] + cs[128]) * args.sm_scale);
+        }
         v16i av, ak;
 #pragma unroll
         for (int r = 0; r < 16; r++) {
@@ -375,17 +382,6 @@ __global__ void __launch_bounds__(512, MODE == kBwdMaxOnly ? 4 : 1) sage_bwd_ker
         for (int r = 0; r < 16; r++) {
           dvacc[tt][r] = __builtin_fmaf((float)av[r], w_dv, dvacc[tt][r]);
           dkacc[tt][r] = __builtin_fmaf((float)ak[r], w_dk, dkacc[tt][r]);
-        }
-        if constexpr (QSMOOTH) {
-          // dK_bias = (dS^T 1) mu_Q^T with the unquantised column sums of this tile
-          const float* cs2 = csum + ((grp * 3 + (t - 2) % 3) * 2) * 64;
-          const float csv = cs2[32 * kbo + ll] + cs2[64 + 32 * kbo + ll];
-#pragma unroll
-          for (int aa = 0; aa < 4; aa++) {
-            const v4f m4 = *(const v4f*)(st.muq + 32 * cb + 8 * aa + 4 * h);
-#pragma unroll
-            for (int b = 0; b < 4; b++) dkbias[tt][4 * aa + b] = __builtin_fmaf(csv, m4[b], dkbias[tt][4 * aa + b]);
-          }
         }
       }
     }
@@ -521,19 +517,12 @@ __global__ void __launch_bounds__(512, MODE == kBwdMaxOnly ? 4 : 1) sage_bwd_ker
       v16f dp;
       // dS = P o (dP - delta): the dP chain starts from -delta of the rows this lane's registers hold
       // (register 4a + b = query 8a + 4h + b of the quadrant), which saves the subtraction per entry.
-      // (Not with Q-smoothing: that instantiation has no register to spare, and anything that lengthens
-      // a live range there ends in a scratch access inside the loop, whose wait drains the staging copies.)
-      if constexpr (QSMOOTH) {
+      const float* dl = st.dl + 32 * qb + 4 * h;
 #pragma unroll
-        for (int r = 0; r < 16; r++) dp[r] = 0.f;
-      } else {
-        const float* dl = st.dl + 32 * qb + 4 * h;
+      for (int aa = 0; aa < 4; aa++) {
+        const v4f d4 = *(const v4f*)(dl + 8 * aa);
 #pragma unroll
-        for (int aa = 0; aa < 4; aa++) {
-          const v4f d4 = *(const v4f*)(dl + 8 * aa);
-#pragma unroll
-          for (int b = 0; b < 4; b++) dp[4 * aa + b] = d4[b];
-        }
+        for (int b = 0; b < 4; b++) dp[4 * aa + b] = d4[b];
       }
 #pragma unroll
       for (int r = 0; r < 16; r++) sacc[r] = 0;
@@ -551,19 +540,16 @@ __global__ void __launch_bounds__(512, MODE == kBwdMaxOnly ? 4 : 1) sage_bwd_ker
       const float* nl2 = st.nl2 + 32 * qb + 4 * h;
       float pm, dm, cs;
       if (!STEADY && ((CAUSAL && ia + sb == j) || kvalid < 64))
-        bwd_quadrant<true, QSMOOTH>(sacc, dp, nl2, st.dl + 32 * qb + 4 * h, c, bias_l, 32 * qb + 4 * h, 32 * kb + ll, CAUSAL && ia + sb == j, kvalid,
+        bwd_quadrant<true, QSMOOTH>(sacc, dp, nl2, c, bias_l, 32 * qb + 4 * h, 32 * kb + ll, CAUSAL && ia + sb == j, kvalid,
                                     p, ds, pm, dm, cs);
       else
-        bwd_quadrant<false, QSMOOTH>(sacc, dp, nl2, st.dl + 32 * qb + 4 * h, c, bias_l, 0, 0, false, 64, p, ds, pm, dm, cs);
+        bwd_quadrant<false, QSMOOTH>(sacc, dp, nl2, c, bias_l, 0, 0, false, 64, p, ds, pm, dm, cs);
       pm = wave_max_nonneg_f32(pm);
       dm = wave_max_nonneg_f32(dm);
       // every lane stores the same pair (one LDS write, no branch)
       red[grp][t & 1][w4][0] = __float_as_uint(pm);
       red[grp][t & 1][w4][1] = __float_as_uint(dm);
-      if constexpr (QSMOOTH) {
-        cs = half_swap_sum_f32(cs);
-        if (h == 0) csum[((grp * 3 + t % 3) * 2 + qb) * 64 + 32 * kb + ll] = cs;
-      }
+      if constexpr (QSMOOTH) csum[((grp * 3 + t % 3) * 4 + 2 * qb + h) * 64 + 32 * kb + ll] = cs;
     } else if constexpr (KV128) {
       // no tile for this group in this interval: nothing for the other group's block maxima
       red[grp][t & 1][w4][0] = 0u;
@@ -582,12 +568,11 @@ __global__ void __launch_bounds__(512, MODE == kBwdMaxOnly ? 4 : 1) sage_bwd_ker
   int t = 0;
   for (; t < 2 && t < T + 2; t++) interval(t, std::false_type{}, std::false_type{});
   // (the second group's waves take phase B before phase A: the two waves of a SIMD then do not reach the
-  // MFMA-dense phase at the same time.  Not with Q-smoothing, whose instantiation has no register to spare.)
-  using second_order = std::integral_constant<bool, !QSMOOTH>;
-  if (QSMOOTH || grp == 0) {
+  // MFMA-dense phase at the same time)
+  if (grp == 0) {
     for (; t < t_steady_end; t++) interval(t, std::true_type{}, std::false_type{});
   } else {
-    for (; t < t_steady_end; t++) interval(t, std::true_type{}, second_order{});
+    for (; t < t_steady_end; t++) interval(t, std::true_type{}, std::true_type{});
   }
   for (; t < T + 2; t++) interval(t, std::false_type{}, std::false_type{});
 
@@ -604,10 +589,8 @@ __global__ void __launch_bounds__(512, MODE == kBwdMaxOnly ? 4 : 1) sage_bwd_ker
       v4us ov, ok;
 #pragma unroll
       for (int b = 0; b < 4; b++) {
-        float kv = dkacc[t][4 * aa + b];
-        if constexpr (QSMOOTH) kv = __builtin_fmaf(dkbias[t][4 * aa + b], args.sm_scale, kv);
         ov[b] = float_to_bf16_bits(dvacc[t][4 * aa + b]);
-        ok[b] = float_to_bf16_bits(kv);
+        ok[b] = float_to_bf16_bits(dkacc[t][4 * aa + b]);
       }
       if (key < args.nvalid) {
         *(v4us*)(pv + 8 * aa) = ov;
@@ -674,7 +657,7 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_single_kernel(BwdArgs args) {
     BwdExchange xch[2];                             // [tile parity]
     unsigned red[2][4][2];                          // [tile parity][wave][max P, max |dS|] as bit patterns
     float scl[2][2];                                // [tile parity][s_P, s_dS]
-    float csum[QSMOOTH ? 3 * 2 * 64 : 1];           // [tile % 3][q half][key]: column sums of dS
+    float csum[QSMOOTH ? 3 * 2 * 2 * 64 : 1];       // [tile % 3][q half][lane half][key]: column sums of dS
   };
   __shared__ __attribute__((aligned(16))) Lds L;
 
@@ -768,8 +751,20 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_single_kernel(BwdArgs args) {
     float p[16], ds[16];           // P and dS of the tile between its phases A and Q
     v4i qa[KS];
     v8bf da[KB];
+    v16f dp;                       // starts from -delta, becomes dP - delta
+    auto read_delta = [&](const int t) __attribute__((always_inline)) {
+      const float* dl = L.stA[t % 3].dl + 32 * qb + 4 * h;
+#pragma unroll
+      for (int aa = 0; aa < 4; aa++) {
+        const v4f d4 = *(const v4f*)(dl + 8 * aa);
+#pragma unroll
+        for (int b = 0; b < 4; b++) dp[4 * aa + b] = d4[b];
+      }
+    };
     auto read_A = [&](const int t) __attribute__((always_inline)) {
       const BwdStageA1<D>& st = L.stA[t % 3];
+      // (with Q-smoothing a CU holds one of these workgroups whatever the registers: -delta is read ahead as well, 3 % at d = 64)
+      if constexpr (QSMOOTH) read_delta(t);
 #pragma unroll
       for (int s = 0; s < KB; s++) {
         if (s % 2 == 0) qa[s / 2] = *(const v4i*)(st.qf + ((qb * KS + s / 2) * 64 + lane) * 16);
@@ -813,19 +808,7 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_single_kernel(BwdArgs args) {
       constexpr bool MASK = decltype(mask_tag)::value;
       const BwdStageA1<D>& st = L.stA[t % 3];
       v16i sacc;
-      v16f dp;
-      const float* dl = st.dl + 32 * qb + 4 * h;
-      if constexpr (QSMOOTH) {
-#pragma unroll
-        for (int r = 0; r < 16; r++) dp[r] = 0.f;
-      } else {
-#pragma unroll
-        for (int aa = 0; aa < 4; aa++) {
-          const v4f d4 = *(const v4f*)(dl + 8 * aa);
-#pragma unroll
-          for (int b = 0; b < 4; b++) dp[4 * aa + b] = d4[b];
-        }
-      }
+      if constexpr (!QSMOOTH) read_delta(t);
 #pragma unroll
       for (int r = 0; r < 16; r++) sacc[r] = 0;
 #pragma unroll
@@ -839,18 +822,15 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_single_kernel(BwdArgs args) {
       const int ia = itop - t;
       float pm, dm, cs;
       if constexpr (MASK)
-        bwd_quadrant<true, QSMOOTH>(sacc, dp, st.nl2 + 32 * qb + 4 * h, dl, c, bias_l, 32 * qb + 4 * h, 32 * kb + ll, CAUSAL && ia + sb == j,
+        bwd_quadrant<true, QSMOOTH>(sacc, dp, st.nl2 + 32 * qb + 4 * h, c, bias_l, 32 * qb + 4 * h, 32 * kb + ll, CAUSAL && ia + sb == j,
                                     kvalid, p, ds, pm, dm, cs);
       else
-        bwd_quadrant<false, QSMOOTH>(sacc, dp, st.nl2 + 32 * qb + 4 * h, dl, c, bias_l, 0, 0, false, 64, p, ds, pm, dm, cs);
+        bwd_quadrant<false, QSMOOTH>(sacc, dp, st.nl2 + 32 * qb + 4 * h, c, bias_l, 0, 0, false, 64, p, ds, pm, dm, cs);
       pm = wave_max_nonneg_f32(pm);
       dm = wave_max_nonneg_f32(dm);
       L.red[t & 1][w4][0] = __float_as_uint(pm);
       L.red[t & 1][w4][1] = __float_as_uint(dm);
-      if constexpr (QSMOOTH) {
-        cs = half_swap_sum_f32(cs);
-        if (h == 0) L.csum[((t % 3) * 2 + qb) * 64 + 32 * kb + ll] = cs;
-      }
+      if constexpr (QSMOOTH) L.csum[((t % 3) * 4 + 2 * qb + h) * 64 + 32 * kb + ll] = cs;
     };
     barrier_all_memory();
     float sq = scalar_load(sQh + itop);
@@ -876,19 +856,28 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_single_kernel(BwdArgs args) {
   }
 
   // ================= back waves: the copies, phase B, channel block cb =================
-  v16f dvacc[NPB], dkacc[NPB], dkbias[QSMOOTH ? NPB : 1];
+  v16f dvacc[NPB], dkacc[NPB];
 #pragma unroll
   for (int t = 0; t < NPB; t++)
 #pragma unroll
     for (int r = 0; r < 16; r++) {
       dvacc[t][r] = 0.f;
       dkacc[t][r] = 0.f;
-      if constexpr (QSMOOTH) dkbias[t][r] = 0.f;
     }
   barrier_all_memory();
   float sq0 = 0.f, sd0 = 0.f, sq1 = 0.f, sd1 = 0.f;          // s_Q, s_dO of tiles t - 2 and t - 1
   for (int t = 0; t < T + 2; t++) {
     const int in = walk.at(t);
+    // the terms of dK_bias of tile t - 2 are read ahead of the copies, whose issue takes longer than the reads
+    float muq = 0.f, cs[NPB] = {};
+    if (QSMOOTH && t >= 2) {
+      muq = L.stB[(t - 2) % 3].muq[32 * cb + ll];
+#pragma unroll
+      for (int tt = 0; tt < NPB; tt++) {
+        const float* c2 = L.csum + (((t - 2) % 3) * 4 + h) * 64 + 32 * (blk0 + tt) + ll;
+        cs[tt] = (c2[0] + c2[128]) * args.sm_scale;
+      }
+    }
     copy_A(walk.at(t + 2), L.stA[(t + 2) % 3], std::false_type{});
     copy_B(in, L.stB[t % 3]);
     const float sqn = scalar_load(sQh + in), sdn = scalar_load(sdOh + in);
@@ -897,6 +886,10 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_single_kernel(BwdArgs args) {
       const BwdExchange& X = L.xch[t & 1];
       const float w_dv = L.scl[t & 1][0] * sd0;
       const float w_dk = L.scl[t & 1][1] * sq0 * args.sm_scale;
+      if constexpr (QSMOOTH) {
+#pragma unroll
+        for (int tt = 0; tt < NPB; tt++) dkacc[tt] = add_dk_bias(dkacc[tt], muq, cs[tt]);
+      }
 #pragma unroll
       for (int tt = 0; tt < NPB; tt++) {
         const int kbo = blk0 + tt;
@@ -920,16 +913,6 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_single_kernel(BwdArgs args) {
           dvacc[tt][r] = __builtin_fmaf((float)av[r], w_dv, dvacc[tt][r]);
           dkacc[tt][r] = __builtin_fmaf((float)ak[r], w_dk, dkacc[tt][r]);
         }
-        if constexpr (QSMOOTH) {
-          const float* cs2 = L.csum + (((t - 2) % 3) * 2) * 64;
-          const float csv = cs2[32 * kbo + ll] + cs2[64 + 32 * kbo + ll];
-#pragma unroll
-          for (int aa = 0; aa < 4; aa++) {
-            const v4f m4 = *(const v4f*)(st.muq + 32 * cb + 8 * aa + 4 * h);
-#pragma unroll
-            for (int b = 0; b < 4; b++) dkbias[tt][4 * aa + b] = __builtin_fmaf(csv, m4[b], dkbias[tt][4 * aa + b]);
-          }
-        }
       }
     }
     sq0 = sq1;
@@ -950,10 +933,8 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_single_kernel(BwdArgs args) {
       v4us ov, ok;
 #pragma unroll
       for (int b = 0; b < 4; b++) {
-        float kv = dkacc[t][4 * aa + b];
-        if constexpr (QSMOOTH) kv = __builtin_fmaf(dkbias[t][4 * aa + b], args.sm_scale, kv);
         ov[b] = float_to_bf16_bits(dvacc[t][4 * aa + b]);
-        ok[b] = float_to_bf16_bits(kv);
+        ok[b] = float_to_bf16_bits(dkacc[t][4 * aa + b]);
       }
       if (key < args.nvalid) {
         *(v4us*)(pv + 8 * aa) = ov;
@@ -997,7 +978,7 @@ struct BwdStageA4 {           // operands of phase A for one Q block
   float dl[64];               // -delta
 };
 
-template <int D, bool CAUSAL, int MODE = kBwdFused, bool KV128 = false>
+template <int D, bool CAUSAL, bool QSMOOTH, int MODE = kBwdFused, bool KV128 = false>
 __global__ void __launch_bounds__(512, 1) sage_bwd_wide_kernel(BwdArgs args) {
   static_assert(D == 128 && MODE != kBwdMaxOnly, "");
   constexpr int KS = D / 32;       // INT8 k-steps over d; channel blocks
@@ -1012,6 +993,8 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_wide_kernel(BwdArgs args) {
     int8_t kst[8][1024];           // [wave]: the last of the KS fragments of K^ of its 32 keys (the others stay in registers)
     int8_t vst[8][32 * D * 2];     // [wave]: bf16 V of the wave's 32 keys as B fragments; at the end its dV, dK rows
     unsigned red[2][8][2];         // [tile parity][wave][max P, max |dS|] as bit patterns
+    float bias[QSMOOTH ? 2 : 1][QSMOOTH ? 4 : 1][QSMOOTH ? 64 : 1];   // [buffer][KV block][key]: logit bias of a Q block
+    float muq[QSMOOTH ? 2 : 1][QSMOOTH ? D : 1];                      // [buffer]: its mean
   };
   __shared__ __attribute__((aligned(256))) Lds L;
 
@@ -1071,6 +1054,10 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_wide_kernel(BwdArgs args) {
                     st.dof + f * 1024);
     }
     async_copy_4(((wave & 1) ? args.delta : args.nL2) + (size_t)bh * args.Nq + 64 * itop + lane, (wave & 1) ? st.dl : st.nl2);
+    if constexpr (QSMOOTH) {
+      async_copy_4(args.bias + ((size_t)bh * nqblk + itop) * N + 64 * jc + lane, L.bias[0][wave >> 1]);
+      if (tid < D) L.muq[1][tid] = 0.f;     // (interval 0 multiplies it by sums of zero)
+    }
   }
 
   v16f dvacc[KS], dkacc[KS];
@@ -1083,10 +1070,10 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_wide_kernel(BwdArgs args) {
   }
   // maxima as bit patterns (non-negative floats order like theirs), kept in scalar registers
   int own_p = 0, own_d = 0;                                               // the wave's own, of that piece
+  float cs = 0.f;                                                         // Q-smoothing: sm_scale * column sum of dS (see add_dk_bias)
   int prev_p = 0, prev_d = 0;                                             // kBwdPairedRows: the last tile's
   float sq = scalar_load(sQh + itop), sd = scalar_load(sdOh + itop);      // s_Q, s_dO of tile t
   float sq1 = 0.f, sd1 = 0.f;                                             // ... of tile t - 1
-  const unsigned dO_read = (unsigned)(uintptr_t)(lptr_t)L.stA[0].dof + ll * 2 * D + ((h ^ ll) & (PPR - 1)) * 16;
   barrier_all_memory();
 
   // Interval t: psi, dV, dK of tile t - 1; S, dP, P, dS of tile t; copies of phase A's operands of tile t + 1 and of phase B's of
@@ -1096,13 +1083,15 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_wide_kernel(BwdArgs args) {
     const int iq = itop - (t - 1), ia = itop - t;
     const bool act_q = !MASK || (t >= 1 && valid && (!CAUSAL || iq + sb >= j));
     const bool act_a = !MASK || (t < T && valid && (!CAUSAL || ia + sb >= j));
-    asm volatile("" : "+v"(lane16), "+v"(dO_lane));     // (keeps their extension to 64 bits out of registers)
+    // (opaque: their extension to 64 bits and what is derived from the lane are formed here and not kept in registers)
+    asm volatile("" : "+v"(lane16), "+v"(dO_lane));
+    const int ll = (lane16 >> 4) & 31, h = lane16 >> 9;
     const BwdStageA4<D>& st = L.stA[t & 1];
     const int8_t* stq = L.stB[(t - 1) & 1][0] + lane16;
     const int8_t* stdo = L.stB[(t - 1) & 1][1] + lane16;
     const int8_t* qfp = st.qf + lane16;
     const int8_t* vbp = L.vst[wave] + lane16;
-    const unsigned dofp = dO_read + (t & 1) * (unsigned)sizeof(BwdStageA4<D>);
+    const unsigned dofp = (unsigned)(uintptr_t)(lptr_t)st.dof + ll * 2 * D + ((h ^ ll) & (PPR - 1)) * 16;
     const unsigned(&R)[8][2] = L.red[(t - 1) & 1];
     unsigned pu, du;                                    // the other waves' maxima of the numerics block
     if constexpr (KV128) {
@@ -1113,7 +1102,8 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_wide_kernel(BwdArgs args) {
       pu = R[wave ^ 1][0];
       du = R[wave ^ 1][1];
     }
-    // copy `part` of this wave's six
+    // copy `part` of this wave's six (eight)
+    constexpr int PARTS = QSMOOTH ? 8 : 6;
     const int in = walk.at(t + 1), ic = walk.at(t);
     auto copy_part = [&](int part) __attribute__((always_inline)) {
       BwdStageA4<D>& sa = L.stA[(t + 1) & 1];
@@ -1128,6 +1118,10 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_wide_kernel(BwdArgs args) {
         copy_4(uniform(((wave & 1) ? args.delta : args.nL2) + (size_t)bh * args.Nq + 64 * in) + (lane16 >> 2), (wave & 1) ? sa.dl : sa.nl2);
       if (part == 4) copy_16(uniform(args.QT + coff) + lane16, sbuf[0] + wave * 1024);
       if (part == 5) copy_16(uniform(args.dOT + coff) + lane16, sbuf[1] + wave * 1024);
+      // (the same values from both waves of a block, from four of the eight)
+      if (QSMOOTH && part == 6) copy_4(uniform(args.bias + ((size_t)bh * nqblk + in) * N + 64 * jc) + (lane16 >> 2), L.bias[(t + 1) & 1][wave >> 1]);
+      if (QSMOOTH && part == 7)
+        copy_4(uniform(args.muQ + ((size_t)bh * nqblk + ic) * D + 64 * (wave & 1)) + (lane16 >> 2), L.muq[t & 1] + 64 * (wave & 1));
     };
     const float sqn = scalar_load(sQh + in), sdn = scalar_load(sdOh + in);
     __builtin_amdgcn_sched_barrier(0);
@@ -1232,9 +1226,11 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_wide_kernel(BwdArgs args) {
           res[sl.u & 1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(op[m % 4], sl.u < KS ? pf[sl.k] : df[sl.k], sl.k == 0 ? zero : res[sl.u & 1], 0, 0, 0);
         else
           sacc[sl.s / KS] = __builtin_amdgcn_mfma_i32_32x32x32_i8(op[m % 4], sl.s % KS == KS - 1 ? klast : kfr[sl.s % KS], sl.s % KS == 0 ? zero : sacc[sl.s / KS], 0, 0, 0);
+        if (QSMOOTH && m % 2 == 0 && m < 2 * KS)
+          dkacc[m / 2] = add_dk_bias(dkacc[m / 2], L.muq[(t - 1) & 1][16 * m + ll], cs);
         if (sl.u > 0 && sl.u < KS) update(sl.u - 1, 8 * (m % 2), 8 * (m % 2) + 8);
         if (sl.u >= KS) update(sl.u - 1, 4 * (m % 4), 4 * (m % 4) + 4);
-        if (m % 3 == 1 && m / 3 < 6) copy_part(m / 3);     // (dealt out: the waves do not queue up at the memory pipeline)
+        if (m % 3 == 1 && m / 3 < PARTS) copy_part(m / 3);     // (dealt out: the waves do not queue up at the memory pipeline)
         __builtin_amdgcn_sched_barrier(0);
       }
       first_for_younger_waves<0>(wave);
@@ -1242,18 +1238,28 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_wide_kernel(BwdArgs args) {
       const float c = sq * sKj * args.scale_log2e;
       v16f dp[2];
       v8bf da[3], vb[2];
-      v4f l4[2];
       auto read_dO = [&](int m) __attribute__((always_inline)) {     // product m: q half m % 2, step m / 2
         da[m % 3] = *(const __attribute__((address_space(3))) v8bf*)(uintptr_t)((dofp ^ ((m / 2) * 32)) + (m & 1) * 64 * D);
       };
       auto read_V = [&](int s) __attribute__((always_inline)) { vb[s % 2] = *(const v8bf*)(vbp + s * 1024); };
-      auto read_L = [&](int g) __attribute__((always_inline)) { l4[g & 1] = *(const v4f*)(st.nl2 + 4 * h + 32 * (g >> 2) + 8 * (g & 3)); };
+      // -L log2e, LE elements at a time (with Q-smoothing there is no register for four)
+      constexpr int LE = QSMOOTH ? 2 : 4;
+      typedef float vle __attribute__((ext_vector_type(LE)));
+      vle lst[2];
+      auto read_L = [&](int g) __attribute__((always_inline)) {
+        const int e = g * LE;
+        lst[g & 1] = *(const vle*)(st.nl2 + 4 * h + 32 * (e >> 4) + 8 * ((e >> 2) & 3) + (e & 3));
+      };
       float pm = 0.f, dm = 0.f;
       // masked: the rows of the tile below klow + 4 h (under the diagonal), or all 64 of a key or of a tile that does not exist
-      const int klow = !act_a || 32 * kb + ll >= kvalid ? 64 : CAUSAL && ia + sb == j ? 32 * kb + ll - 4 * h : -64;
+      // (in scalars first: as a choice of three it became branches around the products)
+      const int kv = act_a ? kvalid : 0, off = CAUSAL && ia + sb == j ? 32 * kb : -128;
+      const int klow = 32 * kb + ll >= kv ? 64 : ll - 4 * h + off;
       // P of element e (q half e / 16, register e % 16 = query 8 (r / 4) + 4 h + r % 4 of it), in three steps that run one product apart
+      const float bias_l = QSMOOTH ? L.bias[t & 1][wave >> 1][32 * kb + ll] : 0.f;
       auto form_x = [&](int e) __attribute__((always_inline)) {
-        p[e >> 4][e & 15] = __builtin_fmaf((float)sacc[e >> 4][e & 15], c, l4[(e >> 2) & 1][e & 3]);
+        const float l = lst[(e / LE) & 1][e % LE];
+        p[e >> 4][e & 15] = __builtin_fmaf((float)sacc[e >> 4][e & 15], c, QSMOOTH ? bias_l + l : l);
       };
       auto form_p = [&](int e) __attribute__((always_inline)) {
         const int qh = e >> 4, r = e & 15;
@@ -1282,10 +1288,8 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_wide_kernel(BwdArgs args) {
 #pragma unroll
       for (int m = 0; m < 2 * KB; m++) {
         if (m + 2 < 2 * KB) read_dO(m + 2);
-        if (m % 2 == 0 && m / 2 + 1 < KB) {
-          read_V(m / 2 + 1);
-          read_L(m / 2 + 1);
-        }
+        if (m % 2 == 0 && m / 2 + 1 < KB) read_V(m / 2 + 1);
+        if (2 * m % LE == 0 && 2 * m + LE < 32) read_L(2 * m / LE + 1);
         dp[m & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(da[m % 3], vb[(m / 2) % 2], dp[m & 1], 0, 0, 0);
         if (m >= 2) form_max(2 * m - 4);
         if (m >= 1) {
@@ -1311,13 +1315,22 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_wide_kernel(BwdArgs args) {
           }
           dm = fmaxf(fmaxf(fabsf(ds[qh][r]), fabsf(ds[qh][r + 1])), dm);
         }
+      if constexpr (QSMOOTH) {
+        float cs0 = 0.f, cs1 = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+          cs0 += ds[0][r];
+          cs1 += ds[1][r];
+        }
+        cs = (cs0 + cs1) * args.sm_scale;
+      }
       own_p = __builtin_amdgcn_readfirstlane(__float_as_int(wave_max_nonneg_f32(pm)));
       own_d = __builtin_amdgcn_readfirstlane(__float_as_int(wave_max_nonneg_f32(dm)));
       L.red[t & 1][wave][0] = (unsigned)own_p;     // (the same pair from every lane)
       L.red[t & 1][wave][1] = (unsigned)own_d;
     } else {
 #pragma unroll
-      for (int part = 0; part < 6; part++) copy_part(part);
+      for (int part = 0; part < PARTS; part++) copy_part(part);
       if constexpr (KV128) L.red[t & 1][wave][0] = L.red[t & 1][wave][1] = 0u;   // nothing for the neighbour's block maxima
     }
     sq1 = sq;

@@ -461,8 +461,8 @@ int launch_bwd_single(const BwdArgs& a, bool causal, bool qs, hipStream_t st) {
   return SAGEBWD_OK;
 }
 
-// Four KV blocks per workgroup (sage_bwd_wide_kernel; same bits): d = 128 without Q-smoothing, once the machine would be given two
-// rounds of workgroups with two blocks each.  An interval of it serves twice the blocks in 1.5 times the time, so a call that fits one
+// Four KV blocks per workgroup (sage_bwd_wide_kernel; same bits): d = 128 (Q-smoothing with numerics blocks of 64), once the machine would be given
+// two rounds of workgroups with two blocks each.  An interval of it serves twice the blocks in 1.5 times the time, so a call that fits one
 // round of those loses.  Backward kernel, us with two KV blocks -> with four.  Walks of about one length (no mask, or at least four
 // times as many keys as queries): 512 blocks of N = 1024 47.0 -> 59.6, of 8192 285 -> 373, 528 of N = 512 50.9 -> 38.4, 544 of N = 2048 139 -> 106, 640 of
 // N = 8192 529 -> 385, 1536 of N = 4096 438 -> 438 (three rounds against two), 2048 602 -> 475; 512 x 4096 with the mask, 512 blocks 31.3
@@ -470,21 +470,22 @@ int launch_bwd_single(const BwdArgs& a, bool causal, bool qs, hipStream_t st) {
 // CUs: 192 of N = 896 41.8 -> 53.0, 224 of N = 1024 57.7 -> 60.5, 256 of N = 2048 91.5 -> 107, of 8192 329 -> 409; 264 of N = 1536 91.8 -> 86.7,
 // 288 of N = 2048 118 -> 111, 320 128 -> 112; 272 of N = 4096 188 -> 207, 288 208 -> 217, 320 225 -> 214 and of N = 8192 528 -> 393.  Up to
 // eight blocks a walk is mostly fill and drain: 576 blocks of N = 384 27.2 -> 29.0, 768 36.2 -> 30.4, of N = 512 39.9 -> 35.9, of N = 192 30.4 -> 21.9.
-bool use_bwd_wide(const BwdArgs& a, int d, bool causal, bool qs) {
-  if (d != 128 || qs) return false;
+// With Q-smoothing the lines are the same (whole backward: 64 heads of N = 8192 with the mask 3437 -> 2827, of 2048 272 -> 233, of 1024 without 128 -> 109).
+bool use_bwd_wide(const BwdArgs& a, int d, bool causal, bool qs, bool big) {
+  if (d != 128 || (qs && big)) return false;
   const long long nblk = a.N / kBlock, blocks = a.BH * nblk;
   if (!causal || a.N >= 4 * a.Nq) return blocks > 2 * kCus;
   const long long wgs = a.BH * ((nblk + 3) / 4);
   return wgs > (nblk <= 32 ? kCus : kCus * 6 / 5) || (nblk <= 8 && blocks >= 3 * kCus);
 }
-template <int MODE, bool KV128 = false>
+template <bool QSMOOTH, int MODE, bool KV128 = false>
 int launch_bwd_wide(const BwdArgs& a, bool causal, hipStream_t st) {
   const int nquad = (a.N / 64 + 3) / 4;
   BwdArgs args = a;
   args.head_set = head_set_for(nquad, a.BH);
   const int grid = grid_for(a.BH, nquad);
-  if (causal) sage_bwd_wide_kernel<128, true, MODE, KV128><<<grid, 512, 0, st>>>(args);
-  else sage_bwd_wide_kernel<128, false, MODE, KV128><<<grid, 512, 0, st>>>(args);
+  if (causal) sage_bwd_wide_kernel<128, true, QSMOOTH, MODE, KV128><<<grid, 512, 0, st>>>(args);
+  else sage_bwd_wide_kernel<128, false, QSMOOTH, MODE, KV128><<<grid, 512, 0, st>>>(args);
   SAGE_LAUNCH_CHECK();
   return SAGEBWD_OK;
 }
@@ -858,16 +859,16 @@ int sagebwd_bwd(const void* Q, const void* K, const void* V, const void* O, cons
   q.Nq = Nqp;
   q.shift_blocks = shift_blocks;
   q.sm_scale = a.sm_scale;
-  const bool even_walks = params->causal == 0 && d == 128 && !qs;     // (the workgroups of sage_bwd_wide_kernel)
+  const bool even_walks = params->causal == 0 && d == 128 && !(qs && big);     // (the workgroups of sage_bwd_wide_kernel)
   for (int h0 = 0, nh = 0; h0 < BH; h0 += nh) {
     nh = even_walks ? heads_of_group(w.heads_per_group, BH - h0, (Nkp / 64 + 3) / 4) : BH - h0 < w.heads_per_group ? BH - h0 : w.heads_per_group;
     a.bh0 = q.bh0 = h0;
     a.BH = q.BH = nh;
     {
       ScopedTimer tm(SAGEBWD_KERNEL_BWD, st);
-      const bool causal = params->causal != 0, wide = use_bwd_wide(a, d, causal, qs);
+      const bool causal = params->causal != 0, wide = use_bwd_wide(a, d, causal, qs, big);
       if (!big && wide) {
-        rc = launch_bwd_wide<kBwdFused>(a, causal, st);
+        rc = qs ? launch_bwd_wide<true, kBwdFused>(a, causal, st) : launch_bwd_wide<false, kBwdFused>(a, causal, st);
         if (rc != SAGEBWD_OK) return rc;
       } else if (!big && use_bwd_single(a, d, causal, qs)) {
         rc = d == 64 ? launch_bwd_single<64>(a, causal, qs, st) : launch_bwd_single<128>(a, causal, qs, st);
@@ -877,7 +878,7 @@ int sagebwd_bwd(const void* Q, const void* K, const void* V, const void* O, cons
         if (rc != SAGEBWD_OK) return rc;
       } else if (block_q(*params) == 64) {
         // 64 x 128: the numerics block is the pair of tiles a workgroup holds at once
-        rc = wide ? launch_bwd_wide<kBwdFused, true>(a, causal, st)
+        rc = wide ? launch_bwd_wide<false, kBwdFused, true>(a, causal, st)
              : d == 64 ? launch_bwd<64, kBwdFused, true>(a, causal, qs, st) : launch_bwd<128, kBwdFused, true>(a, causal, qs, st);
         if (rc != SAGEBWD_OK) return rc;
       } else {
@@ -887,7 +888,7 @@ int sagebwd_bwd(const void* Q, const void* K, const void* V, const void* O, cons
         rc = d == 64 ? launch_bwd<64, kBwdMaxOnly>(a, causal, qs, st) : launch_bwd<128, kBwdMaxOnly>(a, causal, qs, st);
         if (rc != SAGEBWD_OK) return rc;
         if (wide)
-          rc = block_kv(*params) == 128 ? launch_bwd_wide<kBwdPairedRows, true>(a, causal, st) : launch_bwd_wide<kBwdPairedRows>(a, causal, st);
+          rc = block_kv(*params) == 128 ? launch_bwd_wide<false, kBwdPairedRows, true>(a, causal, st) : launch_bwd_wide<false, kBwdPairedRows>(a, causal, st);
         else if (block_kv(*params) == 128)
           rc = d == 64 ? launch_bwd<64, kBwdPairedRows, true>(a, causal, qs, st) : launch_bwd<128, kBwdPairedRows, true>(a, causal, qs, st);
         else

@@ -89,7 +89,6 @@ def test_the_forms_for_calls_that_do_not_fill_the_machine(kernels):
 
 
 def test_backward_with_four_kv_blocks_keeps_its_operands_in_registers(kernels):
-    # two waves per SIMD and 157 KB of LDS; the numerics blocks of 128 may park a few registers outside their loops
+    # two waves per SIMD and 157 KB of LDS
     for k in _pick(kernels, "sage_bwd_wide_kernel"):
-        assert k["scratch"] <= 32 and k["vgpr"] <= 256 and k["lds"] <= 160 * 1024, k
-    assert all(k["scratch"] == 0 for k in _pick(kernels, "sage_bwd_wide_kernel", "ELi0ELb0EEEv"))
+        assert k["scratch"] == 0 and k["vgpr"] <= 256 and k["lds"] <= 160 * 1024, k
