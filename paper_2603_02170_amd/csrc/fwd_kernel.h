@@ -331,7 +331,7 @@ __device__ __forceinline__ PairMax tile_row_max(const v16i (&s)[2], const float 
 }
 
 template <int D, bool CAUSAL, bool QSMOOTH, int NW, bool KV128 = false>
-__global__ void __launch_bounds__(64 * NW, (NW == 4 ? (D == 64 ? 3 : 2) : 1)) sage_fwd_kernel(FwdArgs args) {
+__global__ void __launch_bounds__(64 * NW, D == 64 ? 3 : 2) sage_fwd_kernel(FwdArgs args) {
   constexpr int KS = D / 32;                 // k-steps of Q K^T; also channel blocks of O
   constexpr int TILE_BYTES = 64 * D;         // one K^ or V^ tile of 64 keys
   constexpr int PAIR = 2 * TILE_BYTES;       // K^ tile | V^ tile
@@ -354,8 +354,13 @@ __global__ void __launch_bounds__(64 * NW, (NW == 4 ? (D == 64 ? 3 : 2) : 1)) sa
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ql = lane & 31, h = lane >> 5;
   const int N = args.N;
-  const int q0 = qt * QT + 32 * wave;        // first query of this wave
-  const int q = q0 + ql;
+  // First query of this wave.  The last workgroup of an odd number of Q blocks has two waves without queries: they read the
+  // last rows that exist, take part in the copies and the barriers, form one tile and store nothing.  (Workgroups of 64
+  // queries served such calls before: half the waves to share a staged tile, and 6 heads of N = 22028, blocks of 128, took 998 us where N = 22016 took 677; now 705.)
+  const int q0w = qt * QT + 32 * wave;
+  const bool has_rows = q0w < args.Nq;
+  const int q0 = has_rows ? q0w : args.Nq - 32;
+  const int q = q0w + ql;
   // last visible key of this lane's query: under the causal mask the query's own position among the
   // keys (a query row that does not exist may see keys that do not exist: it is dropped anyway), else
   // the last key
@@ -378,8 +383,8 @@ __global__ void __launch_bounds__(64 * NW, (NW == 4 ? (D == 64 ? 3 : 2) : 1)) sa
   const float cq = args.sQ[(size_t)bh * nqblk + q0 / kBlock] * args.scale_log2e;
   const float* bias_row = QSMOOTH ? args.bias + ((size_t)bh * nqblk + q0 / kBlock) * N : nullptr;
 
-  const int n_tiles = CAUSAL ? (qt * QT + QT + args.shift) / kBlock : nblk;   // barrier count, uniform in the workgroup
-  const int last = CAUSAL ? (q0 + 31 + args.shift) / kBlock : nblk - 1;       // this wave's last tile (masked if causal)
+  const int n_tiles = CAUSAL ? min((qt * QT + QT + args.shift) / kBlock, nblk) : nblk;   // barrier count, uniform in the workgroup
+  const int last = !has_rows ? 0 : CAUSAL ? (q0 + 31 + args.shift) / kBlock : nblk - 1;   // this wave's last tile (masked if causal)
 
   float oacc[KS][16];
 #pragma unroll

@@ -347,12 +347,6 @@ int prepass_for_backward(const void* Q, const void* K, const void* V, const void
   return run_prepass<D>(Q, K, V, dO, O, LSE, p, ws, w, !reuse, true, false, st);
 }
 
-// Waves per forward workgroup (32 queries each).  Four, with two (d = 128) or three (d = 64)
-// workgroups per CU: the waves that share a SIMD then belong to different workgroups and do not
-// wait at each other's barriers (measured 7 % faster than one 8-wave workgroup per CU, although
-// that stages every K^/V^ tile once for twice as many queries).
-int pick_fwd_waves(int N) { return N % 128 == 0 ? 4 : 2; }
-
 // CUs and SIMDs of the machine: what a launch has to fill.
 constexpr int kCus = 256, kSimds = 1024;
 
@@ -385,31 +379,29 @@ int launch_fwd_small(const FwdArgs& a, bool split, hipStream_t st) {
   return SAGEBWD_OK;
 }
 
-// kv128: numerics blocks of 128 keys (the per-token quantiser of P~ takes its row max over two tiles)
+// Full machines: workgroups of four waves (32 queries each), two (d = 128) or three (d = 64) per CU: the waves that share a SIMD
+// then belong to different workgroups and do not wait at each other's barriers (measured 7 % faster than one 8-wave workgroup per
+// CU, although that stages every K^/V^ tile once for twice as many queries).  kv128: numerics blocks of 128 keys (the per-token
+// quantiser of P~ takes its row max over two tiles).
+constexpr int kFwdWaves = 4;
 template <int D, bool CAUSAL, bool QS>
-int launch_fwd_nw(const FwdArgs& a, int nw, bool kv128, hipStream_t st) {
+int launch_fwd_form(const FwdArgs& a, bool kv128, hipStream_t st) {
   if (!kv128 && use_fwd_split(a)) return launch_fwd_small<D, CAUSAL, QS>(a, true, st);
   if (!kv128 && use_fwd_pair(a)) return launch_fwd_small<D, CAUSAL, QS>(a, false, st);
   FwdArgs args = a;
-  args.n_qtiles = a.Nq / (32 * nw);
+  args.n_qtiles = (a.Nq + 32 * kFwdWaves - 1) / (32 * kFwdWaves);
   args.head_set = head_set_for(args.n_qtiles, a.BH);
   const int grid = grid_for(a.BH, args.n_qtiles);
-  if (kv128) {
-    if (nw == 4) sage_fwd_kernel<D, CAUSAL, QS, 4, true><<<grid, 256, 0, st>>>(args);
-    else sage_fwd_kernel<D, CAUSAL, QS, 2, true><<<grid, 128, 0, st>>>(args);
-  } else {
-    if (nw == 4) sage_fwd_kernel<D, CAUSAL, QS, 4><<<grid, 256, 0, st>>>(args);
-    else sage_fwd_kernel<D, CAUSAL, QS, 2><<<grid, 128, 0, st>>>(args);
-  }
+  if (kv128) sage_fwd_kernel<D, CAUSAL, QS, kFwdWaves, true><<<grid, 64 * kFwdWaves, 0, st>>>(args);
+  else sage_fwd_kernel<D, CAUSAL, QS, kFwdWaves><<<grid, 64 * kFwdWaves, 0, st>>>(args);
   SAGE_LAUNCH_CHECK();
   return SAGEBWD_OK;
 }
 
 template <int D>
 int launch_fwd(const FwdArgs& a, bool causal, bool qs, bool kv128, hipStream_t st) {
-  const int nw = pick_fwd_waves(a.Nq);
-  if (causal) return qs ? launch_fwd_nw<D, true, true>(a, nw, kv128, st) : launch_fwd_nw<D, true, false>(a, nw, kv128, st);
-  return qs ? launch_fwd_nw<D, false, true>(a, nw, kv128, st) : launch_fwd_nw<D, false, false>(a, nw, kv128, st);
+  if (causal) return qs ? launch_fwd_form<D, true, true>(a, kv128, st) : launch_fwd_form<D, true, false>(a, kv128, st);
+  return qs ? launch_fwd_form<D, false, true>(a, kv128, st) : launch_fwd_form<D, false, false>(a, kv128, st);
 }
 
 template <int D, int MODE, bool KV128 = false>
