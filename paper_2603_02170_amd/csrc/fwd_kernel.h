@@ -25,8 +25,7 @@
 // result is unchanged because O/l and m + log l do not depend on the reference chosen.
 //
 // INT32 -> FP32 without a conversion instruction: the P^V^ accumulators start from the bit
-// pattern B0 of the float C0 = 1/(2 pi) (an inline constant of the ISA; the compiler keeps the
-// splat in 16 registers because several MFMAs start from it).  B0's mantissa leaves more than 2^20 codes to either end of its binade, so for
+// pattern B0 of the float C0 = 1/(2 pi) (an inline constant of the ISA, see mfma_from_bias).  B0's mantissa leaves more than 2^20 codes to either end of its binade, so for
 // every possible sum |a| <= 64 * 127 * 127 the bits B0 + a read as the float C0 + a * 2^-26
 // exactly.  The FP32 accumulators take w * 2^26 * (C0 + a * 2^-26) with ONE fused multiply-add
 // per value and so carry the bias C0 * 2^26 * sum(w), the same for every channel of a query;
@@ -77,6 +76,18 @@ constexpr int kBiasPeriod = 8;                // tiles between two subtractions 
 // Keeps the computation of `v` where it is written: without a use at this point the compiler
 // sinks the vector work of a chunk past the scheduling barriers into the next basic block.
 __device__ __forceinline__ void pin(float& v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void pin_i(int& v) { asm volatile("" : "+v"(v)); }
+
+// The product that starts a chain from B0.  As assembly, because the compiler folds the inline constant into one product
+// only and makes a splat of 16 registers for several: with it the loop of sage_fwd_kernel formed the splat anew in every tile (8 vector and 16 scalar
+// instructions) and had no register to spare (256 and 17 parked; now 251; 16 heads of N = 8192 350 -> 337 us).  The compiler does not see a matrix instruction here, so
+// the waits around one are written out: two states after a vector write of an operand, two before the next product of the chain
+// reads the result as its C (which is the only thing that ever reads it).
+__device__ __forceinline__ v16i mfma_from_bias(const v4i& a, const v4i& b) {
+  v16i d;
+  asm("s_nop 1\n\tv_mfma_i32_32x32x32_i8 %0, %1, %2, 0.15915494\n\ts_nop 1" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
 
 // S^T accumulators of one 64-key tile (two 32-key blocks), interleaved so that consecutive
 // MFMAs are independent.
@@ -109,6 +120,10 @@ __device__ __forceinline__ void fwd_s_mfma(const int8_t* __restrict__ Kt, const 
 // copies for a coming tile, one in every second slot: alone a wave issues such a copy in 12 cycles, but the CU takes
 // one in 16, and four copies of each of its eight waves in one place hold every wave for about 200 of a tile's 3000 cycles.
 //
+// CARRY = the row max of this tile's logits was taken under the last tile's output update and comes in `carried` (over the two lane
+// halves); that of the next tile, unmasked, goes out there.  It takes a chain of some 20 dependent instructions out of the
+// tile's head (2 to 3 % of the kernel).  The exponents of a slot are formed in the slot before (another 2 to 3 %).
+//
 // KV128 = numerics blocks of 128 keys: the per-token quantiser of P~ (Algorithm 1 line 9) then takes its row
 // max over both 64-key tiles of the block.  `pair` carries the other tile's row max in (INT_MIN / -inf if
 // the other tile has no visible key) and this tile's own row max out.
@@ -116,13 +131,13 @@ struct PairMax {
   int i;      // integer domain (no Q-smoothing: both tiles of a block share the scale c)
   float f;    // log2 domain (Q-smoothing)
 };
-template <int D, bool QSMOOTH, bool MASK, bool NEXT, bool SBIAS, bool KV128 = false, class Copy>
+template <int D, bool QSMOOTH, bool MASK, bool NEXT, bool SBIAS, bool KV128 = false, bool CARRY = false, class Copy>
 __device__ __forceinline__ void fwd_tile(const Copy& copy, const int8_t* __restrict__ Knext, const int8_t* __restrict__ Vt,
                                          const v4i (&qf)[D / 32], v16i (&sacc)[2], v16i (&snext)[2],
                                          float (&oacc)[D / 32][16], float& w_bias, float& m_ref, float (&l_part)[2],
                                          const float c, const float sv, const float* __restrict__ bias_row,
                                          const int k0, const int q, const int lane, const int h,
-                                         PairMax* pair = nullptr) {
+                                         PairMax* pair = nullptr, int* carried = nullptr) {
   constexpr int KS = D / 32;
   constexpr int NSM = 2 * KS;    // MFMAs of the next tile's logits; MFMA m = (k-step m / 2, key block m % 2)
   const int8_t* kl = Knext + lane * 16;
@@ -141,21 +156,26 @@ __device__ __forceinline__ void fwd_tile(const Copy& copy, const int8_t* __restr
   float bmax_f = 0.f;   // SBIAS: the row max as the float its bits spell
   if constexpr (!QSMOOTH) {
     // the scale is one positive scalar per tile, so the row max can be taken on the integers
-    int mi[2] = {INT_MIN, INT_MIN};
+    int mrow;
+    if constexpr (CARRY) {
+      mrow = *carried;
+    } else {
+      int mi[2] = {INT_MIN, INT_MIN};
 #pragma unroll
-    for (int kb = 0; kb < 2; kb++)
+      for (int kb = 0; kb < 2; kb++)
 #pragma unroll
-      for (int r = 0; r < 16; r++) {
-        int v = sacc[kb][r];
-        if constexpr (MASK) {
-          const int key = k0 + 32 * kb + 8 * (r >> 2) + 4 * h + (r & 3);
-          v = key > q ? INT_MIN : v;
-          sacc[kb][r] = v;
+        for (int r = 0; r < 16; r++) {
+          int v = sacc[kb][r];
+          if constexpr (MASK) {
+            const int key = k0 + 32 * kb + 8 * (r >> 2) + 4 * h + (r & 3);
+            v = key > q ? INT_MIN : v;
+            sacc[kb][r] = v;
+          }
+          mi[kb] = max(mi[kb], v);
         }
-        mi[kb] = max(mi[kb], v);
-      }
     // (with SBIAS the accumulators hold B0 + s: the same order, and B0 + s never is INT_MIN)
-    int mrow = half_swap_max_i32(max(mi[0], mi[1]));
+      mrow = half_swap_max_i32(max(mi[0], mi[1]));
+    }
     if constexpr (KV128) {
       const int own = mrow;
       mrow = max(mrow, pair->i);
@@ -207,6 +227,24 @@ __device__ __forceinline__ void fwd_tile(const Copy& copy, const int8_t* __restr
   // scales c for which that is far below the half code that would carry 127 to 128).
   const float c_eff = SBIAS ? c * kTwo26 : c;
   const float off = SBIAS ? __builtin_fmaf(-bmax_f, c_eff, kLog2_127) : kLog2_127 - mloc;
+  // exponents of a group of four logits (group g: key block g / 4, registers 4 (g % 4) ..), formed one slot ahead of their exp2
+  float xn[4];
+  auto form_x = [&](int g) __attribute__((always_inline)) {
+    const int kb = g >> 2, aa = g & 3;
+#pragma unroll
+    for (int b = 0; b < 4; b++) {
+      float xv;
+      if constexpr (!QSMOOTH) {
+        if constexpr (SBIAS) xv = __builtin_fmaf(__int_as_float(sacc[kb][4 * aa + b]), c_eff, off);
+        else xv = __builtin_fmaf((float)sacc[kb][4 * aa + b], c, off);
+        if constexpr (MASK) xv = sacc[kb][4 * aa + b] == INT_MIN ? -INFINITY : xv;
+      } else {
+        xv = x[kb][4 * aa + b] + off;
+      }
+      xn[b] = xv;
+    }
+  };
+  form_x(0);
   __builtin_amdgcn_sched_barrier(0);
 
   // ---- slots 0..7: P^ = rne(127 exp(S - rowmax)) for four logits each, packed as the B operand;
@@ -219,7 +257,9 @@ __device__ __forceinline__ void fwd_tile(const Copy& copy, const int8_t* __restr
   v16i t[KS];
   float psum[4] = {0.f, 0.f, 0.f, 0.f};
   float w = 0.f;
+  int nmax[2] = {INT_MIN, INT_MIN};
   constexpr int NSLOT = 10 + 2 * KS;
+  static_assert(NSLOT >= 14, "the next tile's row max takes slots 8 to 13");
   auto pv_slot = [&](int m) { return m < KS ? 4 + m : 8 + (m - KS); };   // slot of P^V^ MFMA m = (kb, cb)
 #pragma unroll
   for (int sl = 0; sl < NSLOT; sl++) {
@@ -239,8 +279,8 @@ __device__ __forceinline__ void fwd_tile(const Copy& copy, const int8_t* __restr
         if (sl < 2) {
           v16i z;
 #pragma unroll
-          for (int r = 0; r < 16; r++) z[r] = SBIAS ? kBiasBits : 0;
-          snext[sl & 1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ka[sl % 3], qf[sl >> 1], z, 0, 0, 0);
+          for (int r = 0; r < 16; r++) z[r] = 0;
+          snext[sl & 1] = SBIAS ? mfma_from_bias(ka[sl % 3], qf[sl >> 1]) : __builtin_amdgcn_mfma_i32_32x32x32_i8(ka[sl % 3], qf[sl >> 1], z, 0, 0, 0);
         } else {
           snext[sl & 1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ka[sl % 3], qf[sl >> 1], snext[sl & 1], 0, 0, 0);
         }
@@ -250,10 +290,7 @@ __device__ __forceinline__ void fwd_tile(const Copy& copy, const int8_t* __restr
     for (int m = 0; m < 2 * KS; m++)
       if (pv_slot(m) == sl) {
         if (m < KS) {
-          v16i b0;
-#pragma unroll
-          for (int r = 0; r < 16; r++) b0[r] = kBiasBits;
-          t[m] = __builtin_amdgcn_mfma_i32_32x32x32_i8(va[m & 3], pf[0], b0, 0, 0, 0);
+          t[m] = mfma_from_bias(va[m & 3], pf[0]);
         }
         else t[m - KS] = __builtin_amdgcn_mfma_i32_32x32x32_i8(va[m & 3], pf[1], t[m - KS], 0, 0, 0);
       }
@@ -261,30 +298,47 @@ __device__ __forceinline__ void fwd_tile(const Copy& copy, const int8_t* __restr
     if (sl < 8) {
       const int kb = sl >> 2, aa = sl & 3;
       unsigned u = 0;
+      float e[4];
+#pragma unroll
+      for (int b = 0; b < 4; b++) e[b] = __builtin_amdgcn_exp2f(xn[b]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (sl < 7) form_x(sl + 1);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int b = 0; b < 4; b++) {
-        float xv;
-        if constexpr (!QSMOOTH) {
-          if constexpr (SBIAS) xv = __builtin_fmaf(__int_as_float(sacc[kb][4 * aa + b]), c_eff, off);
-          else xv = __builtin_fmaf((float)sacc[kb][4 * aa + b], c, off);
-          if constexpr (MASK) xv = sacc[kb][4 * aa + b] == INT_MIN ? -INFINITY : xv;
-        } else {
-          xv = x[kb][4 * aa + b] + off;
-        }
-        const float e = __builtin_amdgcn_exp2f(xv);
-        psum[b] += e;
+        psum[b] = aa == 0 ? e[b] : psum[b] + e[b];
         pin(psum[b]);
-        u = __builtin_amdgcn_cvt_pk_u8_f32(e, b, u);
+        u = __builtin_amdgcn_cvt_pk_u8_f32(e[b], b, u);
       }
       pf[kb][aa] = (int)u;
       if (aa == 3) {
         // (one sum per key block, which meet at the end: sage_fwd_pair_kernel has them in two waves)
         l_part[kb] = __builtin_fmaf(beta, (psum[0] + psum[1]) + (psum[2] + psum[3]), l_part[kb]);
         pin(l_part[kb]);
-#pragma unroll
-        for (int b = 0; b < 4; b++) psum[b] = 0.f;
       }
-    } else if (sl == 8) {
+    }
+    if constexpr (NEXT && CARRY) {
+      if (sl == 8) nmax[0] = max(max(snext[0][0], snext[0][1]), snext[0][2]);
+      if (sl == 9) {
+#pragma unroll
+        for (int r = 3; r < 15; r += 2) nmax[0] = max(max(snext[0][r], snext[0][r + 1]), nmax[0]);
+        pin_i(nmax[0]);
+      }
+      if (sl >= 10 && sl < 13) {
+        if (sl == 10) nmax[1] = max(snext[1][0], snext[0][15]);
+#pragma unroll
+        for (int r = 1; r < 15; r += 2)
+          if ((r < 5 ? 10 : r < 11 ? 11 : 12) == sl) nmax[1] = max(max(snext[1][r], snext[1][r + 1]), nmax[1]);
+        if (sl == 12) nmax[0] = max(max(snext[1][15], nmax[0]), nmax[1]);
+        pin_i(nmax[1]);
+        pin_i(nmax[0]);
+      }
+      if (sl == 13) {
+        *carried = half_swap_max_i32(nmax[0]);
+        pin_i(*carried);
+      }
+    }
+    if (sl == 8) {
       w = beta * sv * kTwo26;
       w_bias += w;
       pin(w);
@@ -398,16 +452,14 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 3 : 2) sage_fwd_kernel(FwdA
   // Asynchronous copy of tile j (K^ fragments, then V^ fragments) into a ring slot; the
   // 1 KiB fragments are dealt round-robin to the waves.
   constexpr int CPW = NFRAG / NW + (QSMOOTH ? 1 : 0);   // copies per wave and tile
+  unsigned lane16 = lane * 16;
   static_assert(NFRAG % NW == 0, "every wave must issue the same number of copies");
+  static_assert(NFRAG / 2 % NW == 0, "a copy is of K^ for every wave, or of V^");
   auto copy_piece = [&](int j, int8_t* dst, int k) __attribute__((always_inline)) {
     const int o = wave + NW * k;             // wave-uniform
-    if (k < NFRAG / NW) {
-      const int8_t* src = o < NFRAG / 2 ? KFh + (size_t)j * TILE_BYTES + o * 1024
-                                        : VTh + (size_t)j * TILE_BYTES + (o - NFRAG / 2) * 1024;
-      async_copy_16(src + lane * 16, dst + o * 1024);
-    } else if (QSMOOTH && k == NFRAG / NW) {
-      async_copy_4(bias_row + j * kBlock + lane, dst + BIAS_OFF + wave * 256);
-    }
+    if (k < NFRAG / 2 / NW) copy_16(uniform(KFh + (size_t)j * TILE_BYTES + o * 1024) + lane16, dst + o * 1024);
+    else if (k < NFRAG / NW) copy_16(uniform(VTh + (size_t)j * TILE_BYTES + (o - NFRAG / 2) * 1024) + lane16, dst + o * 1024);
+    else if (QSMOOTH && k == NFRAG / NW) copy_4(uniform(bias_row + j * kBlock) + (lane16 >> 2), dst + BIAS_OFF + wave * 256);
   };
   auto stage_load = [&](int j, int8_t* dst) {
 #pragma unroll
@@ -428,17 +480,14 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 3 : 2) sage_fwd_kernel(FwdA
   // past the barrier that ended iteration j - 1, so nobody reads it any more); this wave forms
   // S_{j+1} from slot `nxt` and finishes tile j with V^ from slot `cur`; before the barrier at
   // the end it waits for the copies of tile j + 2 (issued one iteration earlier), while its copies
-  // of tile j + 3 stay in flight.  The block scales come one tile ahead through the scalar cache, so the
+  // of tile j + 3 stay in flight (past the last tile that one again, never read: without a branch around each copy the tile
+  // is one basic block, 1 to 3 % of the kernel).  The block scales come one tile ahead through the scalar cache, so the
   // loop has no register-returning vector loads whose waits would also drain the copies.  Every wave of
   // the workgroup runs n_tiles iterations (the barriers must match): its unmasked tiles, its last
   // tile, then iterations that only keep the ring moving.
-  auto end_iter = [&](const bool issued) {
-    if (issued) {
-      __builtin_amdgcn_s_waitcnt(vmcnt_only(CPW));   // vmcnt: all but this iteration's copies
-      barrier_lds_only();
-    } else {
-      barrier_all_memory();
-    }
+  auto end_iter = [&]() {
+    __builtin_amdgcn_s_waitcnt(vmcnt_only(CPW));   // vmcnt: all but this iteration's copies
+    barrier_lds_only();
     int8_t* t = cur;
     cur = nxt;
     nxt = nx2;
@@ -483,16 +532,20 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 3 : 2) sage_fwd_kernel(FwdA
       // (with SBIAS the accumulators hold B0 + s: the same order)
       pm = tile_row_max<QSMOOTH, MASKED>(sT, cq * scalar_load(sKh + jn), (const float*)(nxt + BIAS_OFF + wave * 256), jn * kBlock, qlim, h);
     };
+    constexpr bool CARRY = !QSMOOTH && !KV128;
+    int carried = INT_MIN;
+    if constexpr (CARRY) carried = tile_row_max<false, false>(sA, 0.f, nullptr, 0, 0, h).i;
     auto full_iter = [&](const int j, v16i (&sc)[2], v16i (&sn)[2]) __attribute__((always_inline)) {
-      const bool issue = j + 3 < n_tiles;
+      const int jl = min(j + 3, n_tiles - 1);
+      asm volatile("" : "+v"(lane16));
       const float skn = scalar_load(sKh + j + 1), svn = scalar_load(sVh + j + 1);     // (j < last: tile j + 1 exists)
-      fwd_tile<D, QSMOOTH, false, true, SBIAS, KV128>([&](int k) __attribute__((always_inline)) { if (k < CPW && issue) copy_piece(j + 3, nx3, k); },
+      fwd_tile<D, QSMOOTH, false, true, SBIAS, KV128, CARRY>([&](int k) __attribute__((always_inline)) { if (k < CPW) copy_piece(jl, nx3, k); },
                                         nxt, cur + TILE_BYTES, qf, sc, sn, oacc, w_bias, m_ref, l_part,
-                                        cq * sk, sv, (const float*)(cur + BIAS_OFF + wave * 256), j * kBlock, q, lane, h, &pm);
+                                        cq * sk, sv, (const float*)(cur + BIAS_OFF + wave * 256), j * kBlock, q, lane, h, &pm, &carried);
       if ((j & (kBiasPeriod - 1)) == kBiasPeriod - 1) unbias();
       sk = skn;
       sv = svn;
-      end_iter(issue);
+      end_iter();
     };
     int j = 0;
     for (; j + 1 < last; j += 2) {
@@ -510,19 +563,18 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 3 : 2) sage_fwd_kernel(FwdA
       j++;
     }
     {
-      const bool issue = j + 3 < n_tiles;
-      if (issue) stage_load(j + 3, nx3);
+      stage_load(min(j + 3, n_tiles - 1), nx3);
       // (the last tile always takes the masked path: without the causal mask it hides the keys past nvalid)
       fwd_tile<D, QSMOOTH, true, false, SBIAS, KV128>([](int) {}, nxt, cur + TILE_BYTES, qf, sA, sB, oacc, w_bias, m_ref, l_part,
                                         cq * sk, sv, (const float*)(cur + BIAS_OFF + wave * 256), j * kBlock, qlim, lane, h, &pm);
-      end_iter(issue);
+      end_iter();
       j++;
     }
     for (; j < n_tiles; j++) {
-      const bool issue = j + 3 < n_tiles;
-      if (issue) stage_load(j + 3, nx3);
-      end_iter(issue);
+      stage_load(min(j + 3, n_tiles - 1), nx3);
+      end_iter();
     }
+    __builtin_amdgcn_s_waitcnt(vmcnt_only(0));     // (the copies past the last tile land before the LDS is given up)
     unbias();
     // ---- epilogue: O = O / l, L = m + log(l) (l carries a factor 127) ----
     const float l_tot = half_swap_sum_f32(l_part[0]) + half_swap_sum_f32(l_part[1]);
@@ -911,8 +963,7 @@ __global__ void __launch_bounds__(128 * NQ, 2) sage_fwd_pair_kernel(FwdArgs args
 // any batch.
 //
 // At d = 128 the ring has two slots per split, so every iteration waits for all of its copies; four would not fit beside
-// four splits.  (The instantiations without Q-smoothing keep 17 registers in scratch there, written before the tile loop
-// and read after it.)
+// four splits.
 //
 // Slot p of a split's ring holds K^ of its tile p + 1 and V^ of its tile p (what iteration p reads: the logits
 // of the next tile are formed under the softmax of this one); K^ of the first tile comes straight from memory.
@@ -956,7 +1007,7 @@ __global__ void __launch_bounds__(512, 1) sage_fwd_split_kernel(FwdArgs args) {
   // this workgroup's tiles, this split's share [a, b) of them (none for the last splits of some counts), its last tile
   const int n_tiles = CAUSAL ? (qt * NQ * 32 + NQ * 32 + args.shift) / kBlock : nblk;
   const int share = (n_tiles + NS - 1) / NS;
-  const int a = g * share, b = min(n_tiles, a + share), cnt = max(b - a, 0);
+  const int a = g * share, b = min(n_tiles, a + share);
   const int last = b - 1;
   const int ac = min(a, nblk - 1);                             // (a split without tiles still reads in bounds)
 
@@ -977,27 +1028,23 @@ __global__ void __launch_bounds__(512, 1) sage_fwd_split_kernel(FwdArgs args) {
   float w_bias = 0.f, m_ref = -INFINITY, l_part[2] = {0.f, 0.f};
 
   int8_t* ring = lds + g * R * SLOT;
+  unsigned lane16 = lane * 16;
+  static_assert(NFRAG / 2 % NQ == 0, "a copy is of K^ for every wave, or of V^");
+  // (slots past the split's tiles are filled with tiles that exist and never read: every iteration issues the same copies)
   auto copy_piece = [&](int p, int k) __attribute__((always_inline)) {
     int8_t* dst = ring + (p % R) * SLOT;
     const int o = qw + NQ * k;
-    if (k < NFRAG / NQ) {
-      const int8_t* src = o < NFRAG / 2 ? KFh + (size_t)min(a + p + 1, nblk - 1) * TILE_BYTES + o * 1024
-                                        : VTh + (size_t)(a + p) * TILE_BYTES + (o - NFRAG / 2) * 1024;
-      async_copy_16(src + lane * 16, dst + o * 1024);
-    } else if (QSMOOTH && k == NFRAG / NQ) {
-      async_copy_4(bias_row + (a + p) * kBlock + lane, dst + PAIR + qw * 256);
-    }
+    if (k < NFRAG / 2 / NQ) copy_16(uniform(KFh + (size_t)min(a + p + 1, nblk - 1) * TILE_BYTES + o * 1024) + lane16, dst + o * 1024);
+    else if (k < NFRAG / NQ) copy_16(uniform(VTh + (size_t)min(a + p, nblk - 1) * TILE_BYTES + (o - NFRAG / 2) * 1024) + lane16, dst + o * 1024);
+    else if (QSMOOTH && k == NFRAG / NQ) copy_4(uniform(bias_row + min(a + p, nblk - 1) * kBlock) + (lane16 >> 2), dst + PAIR + qw * 256);
   };
 #pragma unroll
   for (int p = 0; p < R - 1; p++)
-    if (p < cnt) {
 #pragma unroll
-      for (int k = 0; k < CPW; k++) copy_piece(p, k);
-    }
-  // end of iteration t: the copies of slot t + 1 have landed (those of younger slots stay in flight while new
-  // ones are still issued)
-  auto end_iter = [&](const bool issued) {
-    if (issued && R > 2) {
+    for (int k = 0; k < CPW; k++) copy_piece(p, k);
+  // end of iteration t: the copies of slot t + 1 have landed (those of younger slots stay in flight)
+  auto end_iter = [&]() {
+    if constexpr (R > 2) {
       __builtin_amdgcn_s_waitcnt(vmcnt_only((R - 2) * CPW));
       barrier_lds_only();
     } else {
@@ -1024,17 +1071,20 @@ __global__ void __launch_bounds__(512, 1) sage_fwd_split_kernel(FwdArgs args) {
     fwd_s_mfma<D, SBIAS>(KFh + (size_t)ac * TILE_BYTES, qf, sA, lane);
     barrier_all_memory();                                      // the first slots have landed
     float sk = scalar_load(sKh + ac), sv = scalar_load(sVh + ac);
+    constexpr bool CARRY = !QSMOOTH;
+    int carried = INT_MIN;
+    if constexpr (CARRY) carried = tile_row_max<false, false>(sA, 0.f, nullptr, 0, 0, h).i;
     auto full_iter = [&](const int t, v16i (&sc)[2], v16i (&sn)[2]) __attribute__((always_inline)) {
-      const bool issue = t + R - 1 < cnt;
+      asm volatile("" : "+v"(lane16));
       const float skn = scalar_load(sKh + a + t + 1), svn = scalar_load(sVh + a + t + 1);
       const int8_t* slot = ring + (t % R) * SLOT;
-      fwd_tile<D, QSMOOTH, false, true, SBIAS>([&](int k) __attribute__((always_inline)) { if (k < CPW && issue) copy_piece(t + R - 1, k); },
+      fwd_tile<D, QSMOOTH, false, true, SBIAS, false, CARRY>([&](int k) __attribute__((always_inline)) { if (k < CPW) copy_piece(t + R - 1, k); },
                                                slot, slot + TILE_BYTES, qf, sc, sn, oacc, w_bias, m_ref, l_part, cq * sk, sv,
-                                               (const float*)(slot + PAIR + qw * 256), (a + t) * kBlock, q, lane, h);
+                                               (const float*)(slot + PAIR + qw * 256), (a + t) * kBlock, q, lane, h, nullptr, &carried);
       if ((t & (kBiasPeriod - 1)) == kBiasPeriod - 1) unbias();
       sk = skn;
       sv = svn;
-      end_iter(issue);
+      end_iter();
     };
     int t = 0;
     for (; a + t + 1 < last; t += 2) {
@@ -1049,32 +1099,26 @@ __global__ void __launch_bounds__(512, 1) sage_fwd_split_kernel(FwdArgs args) {
     }
     if (a + t <= last) {
       // the split's last tile takes the masked path (which leaves visible keys as they are)
-      const bool issue = t + R - 1 < cnt;
-      if (issue) {
 #pragma unroll
-        for (int k = 0; k < CPW; k++) copy_piece(t + R - 1, k);
-      }
+      for (int k = 0; k < CPW; k++) copy_piece(t + R - 1, k);
       const int8_t* slot = ring + (t % R) * SLOT;
       fwd_tile<D, QSMOOTH, true, false, SBIAS>([](int) {}, slot, slot + TILE_BYTES, qf, sA, sB, oacc, w_bias, m_ref, l_part, cq * sk, sv,
                                                (const float*)(slot + PAIR + qw * 256), (a + t) * kBlock, qlim, lane, h);
-      end_iter(issue);
+      end_iter();
       t++;
     }
     for (; t < share; t++) {                                   // (a shorter split: every wave meets `share` barriers)
-      const bool issue = t + R - 1 < cnt;
-      if (issue) {
 #pragma unroll
-        for (int k = 0; k < CPW; k++) copy_piece(t + R - 1, k);
-      }
-      end_iter(issue);
+      for (int k = 0; k < CPW; k++) copy_piece(t + R - 1, k);
+      end_iter();
     }
+    if constexpr (R > 2) barrier_all_memory();                 // (the ring is drained before it is used again)
     unbias();
   };
   if (__builtin_amdgcn_readfirstlane((int)use_sbias)) run(std::true_type{});
   else run(std::false_type{});
 
-  // ---- the splits meet: split s finishes the channel blocks cb with cb % NS == s (the ring is drained: the last
-  // iterations issue nothing and wait for everything) ----
+  // ---- the splits meet: split s finishes the channel blocks cb with cb % NS == s (the ring is drained) ----
   const float l_tot = half_swap_sum_f32(l_part[0]) + half_swap_sum_f32(l_part[1]);
   float* xch = (float*)lds;
 #pragma unroll
