@@ -606,6 +606,8 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 3 : 2) sage_fwd_kernel(FwdA
 // software-pipelined over one barrier per tile: interval t finishes the softmax of tile t, adds tile t - 1 to O
 // and forms S of tile t + 1 with its half row max, so each finds the other wave's part of the interval before.
 //
+// (Copies that every interval issues, past the last tile ones never read, the inline constant in the products and exponents
+// formed a slot ahead of their exp2: 2 heads of N = 4096 63.6 -> 59.1 us a call, 8 of N = 1000 25.6 -> 24.7.)
 // Such calls take the time of one wave's chain of tiles: with one wave per SIMD sage_fwd_kernel needs 1.02 us for
 // each further tile (2 heads of N = 4096 against 8 of N = 1024, same pre-pass), most of it the wave's own instruction
 // issue (one vector instruction in about 4.8 cycles).  Half a tile per wave takes 0.77 us: less than half of the
@@ -662,16 +664,15 @@ __global__ void __launch_bounds__(128 * NQ, 2) sage_fwd_pair_kernel(FwdArgs args
   const int last = n_tiles - 1;                                // (the diagonal block of every wave, with the mask)
 
   // copies of slot p (K^ of tile p + 2, V^ of tile p; clamped where there is no such tile: never read)
+  unsigned lane16 = lane * 16;
+  static_assert(NFRAG / 2 % NW == 0, "a copy is of K^ for every wave, or of V^");
   auto copy_piece = [&](int p, int8_t* dst, int k) __attribute__((always_inline)) {
-    if (k < NFRAG / NW) {
-      const int o = wave + NW * k;                             // wave-uniform
-      const int8_t* src = o < NFRAG / 2 ? KFh + (size_t)min(p + 2, nblk - 1) * TILE_BYTES + o * 1024
-                                        : VTh + (size_t)max(p, 0) * TILE_BYTES + (o - NFRAG / 2) * 1024;
-      async_copy_16(src + lane * 16, dst + o * 1024);
-    } else if (QSMOOTH && k == NFRAG / NW) {
-      // (every wave copies the row, so that all issue the same number)
-      async_copy_4(args.bias + ((size_t)bh * nqblk + qblk) * N + min(p + 2, nblk - 1) * kBlock + lane, dst + PAIR);
-    }
+    const int o = wave + NW * k;                               // wave-uniform
+    const int jk = min(p + 2, nblk - 1), jv = min(max(p, 0), nblk - 1);
+    if (k < NFRAG / 2 / NW) copy_16(uniform(KFh + (size_t)jk * TILE_BYTES + o * 1024) + lane16, dst + o * 1024);
+    else if (k < NFRAG / NW) copy_16(uniform(VTh + (size_t)jv * TILE_BYTES + (o - NFRAG / 2) * 1024) + lane16, dst + o * 1024);
+    // (every wave copies the row, so that all issue the same number)
+    else if (QSMOOTH && k == NFRAG / NW) copy_4(uniform(args.bias + ((size_t)bh * nqblk + qblk) * N + jk * kBlock) + (lane16 >> 2), dst + PAIR);
   };
   int8_t* rd = ring;                                           // slot t - 1
   int8_t* mid = ring + SLOT;                                   // slot t
@@ -753,10 +754,11 @@ __global__ void __launch_bounds__(128 * NQ, 2) sage_fwd_pair_kernel(FwdArgs args
     // One interval.  PV / SM / SN: tile t - 1 is added to O, tile t quantised, the logits of tile t + 1 formed.  The
     // vector work of the softmax runs over the matrix work of the other two (P^ does not depend on the running
     // reference); the reference, which scales O, moves after tile t - 1 has been added, as in sage_fwd_kernel.
-    auto interval = [&](const int t, const bool issue, const float c, const float sv, const float cn, v16i& s, v16i& sn, auto pv_tag,
+    auto interval = [&](const int t, const float c, const float sv, const float cn, v16i& s, v16i& sn, auto pv_tag,
                         auto sm_tag, auto sn_tag, auto mask_tag) __attribute__((always_inline)) {
       constexpr bool PV = decltype(pv_tag)::value, SM = decltype(sm_tag)::value, SN = decltype(sn_tag)::value;
       constexpr bool MASK = decltype(mask_tag)::value;
+      asm volatile("" : "+v"(lane16));
       const int8_t* kl = rd + kb * KS * 1024 + lane * 16;
       const int8_t* vl = rd + TILE_BYTES + kb * CBW * 1024 + lane * 16;
       float mother = 0.f;
@@ -788,6 +790,23 @@ __global__ void __launch_bounds__(128 * NQ, 2) sage_fwd_pair_kernel(FwdArgs args
         c_eff = SBIAS ? c * kTwo26 : c;
         off = SBIAS ? __builtin_fmaf(-bmax_f, c_eff, kLog2_127) : kLog2_127 - mloc;
       }
+      // exponents of four logits, formed one slot ahead of their exp2
+      float xn[4] = {0.f, 0.f, 0.f, 0.f};
+      auto form_x = [&](int aa) __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < 4; b++) {
+          float xv;
+          if constexpr (!QSMOOTH) {
+            if constexpr (SBIAS) xv = __builtin_fmaf(__int_as_float(s[4 * aa + b]), c_eff, off);
+            else xv = __builtin_fmaf((float)s[4 * aa + b], c, off);
+            if constexpr (MASK) xv = s[4 * aa + b] == INT_MIN ? -INFINITY : xv;
+          } else {
+            xv = __int_as_float(s[4 * aa + b]) + off;
+          }
+          xn[b] = xv;
+        }
+      };
+      if constexpr (SM) form_x(0);
       v16i tt[CBW];
       float psum[4] = {0.f, 0.f, 0.f, 0.f};
       v4i pf;
@@ -801,8 +820,8 @@ __global__ void __launch_bounds__(128 * NQ, 2) sage_fwd_pair_kernel(FwdArgs args
             if (aa == 0) {
               v16i z;
 #pragma unroll
-              for (int r = 0; r < 16; r++) z[r] = SBIAS ? kBiasBits : 0;
-              sn = __builtin_amdgcn_mfma_i32_32x32x32_i8(ka[0], qf[0], z, 0, 0, 0);
+              for (int r = 0; r < 16; r++) z[r] = 0;
+              sn = SBIAS ? mfma_from_bias(ka[0], qf[0]) : __builtin_amdgcn_mfma_i32_32x32x32_i8(ka[0], qf[0], z, 0, 0, 0);
             } else {
               sn = __builtin_amdgcn_mfma_i32_32x32x32_i8(ka[aa], qf[aa], sn, 0, 0, 0);
             }
@@ -813,41 +832,34 @@ __global__ void __launch_bounds__(128 * NQ, 2) sage_fwd_pair_kernel(FwdArgs args
           if (aa >= 0 && aa < 2 * CBW) {
             const int k = aa / CBW, cb = aa % CBW;
             if (k == 0) {
-              v16i b0;
-#pragma unroll
-              for (int r = 0; r < 16; r++) b0[r] = kBiasBits;
-              tt[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(va[0][cb], p[0], b0, 0, 0, 0);
+              tt[cb] = mfma_from_bias(va[0][cb], p[0]);
             } else {
               tt[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(va[1][cb], p[1], tt[cb], 0, 0, 0);
             }
           }
         }
-        if (sl < CPW && issue) copy_piece(t + 1, wr, sl);
+        if (sl < CPW) copy_piece(t + 1, wr, sl);
         if (SM && sl < 4) {
           const int aa = sl;
           unsigned u = 0;
+          float e[4];
+#pragma unroll
+          for (int b = 0; b < 4; b++) e[b] = __builtin_amdgcn_exp2f(xn[b]);
+          __builtin_amdgcn_sched_barrier(0);
+          if (aa < 3) form_x(aa + 1);
+          __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
           for (int b = 0; b < 4; b++) {
-            float xv;
-            if constexpr (!QSMOOTH) {
-              if constexpr (SBIAS) xv = __builtin_fmaf(__int_as_float(s[4 * aa + b]), c_eff, off);
-              else xv = __builtin_fmaf((float)s[4 * aa + b], c, off);
-              if constexpr (MASK) xv = s[4 * aa + b] == INT_MIN ? -INFINITY : xv;
-            } else {
-              xv = __int_as_float(s[4 * aa + b]) + off;
-            }
-            const float e = __builtin_amdgcn_exp2f(xv);
-            psum[b] += e;
+            psum[b] = aa == 0 ? e[b] : psum[b] + e[b];
             pin(psum[b]);
-            u = __builtin_amdgcn_cvt_pk_u8_f32(e, b, u);
+            u = __builtin_amdgcn_cvt_pk_u8_f32(e[b], b, u);
           }
           pf[aa] = (int)u;
         }
         __builtin_amdgcn_sched_barrier(0);
       }
 #pragma unroll
-      for (int k = 5; k < CPW; k++)
-        if (issue) copy_piece(t + 1, wr, k);
+      for (int k = 5; k < CPW; k++) copy_piece(t + 1, wr, k);
       if constexpr (SM) *(v4i*)(&pxch[t & 1][qw][kb][lane * 16]) = pf;
       if constexpr (PV) {
 #pragma unroll
@@ -875,12 +887,8 @@ __global__ void __launch_bounds__(128 * NQ, 2) sage_fwd_pair_kernel(FwdArgs args
       }
       if constexpr (SN) half_max(sn, t + 1, cn, (const float*)(rd + PAIR), mask_tag);
       // the copies of slot t (issued one interval ago) have landed; this interval's stay in flight
-      if (issue) {
-        __builtin_amdgcn_s_waitcnt(vmcnt_only(CPW));
-        barrier_lds_only();
-      } else {
-        barrier_all_memory();
-      }
+      __builtin_amdgcn_s_waitcnt(vmcnt_only(CPW));
+      barrier_lds_only();
       int8_t* x = rd;
       rd = mid;
       mid = wr;
@@ -904,7 +912,7 @@ __global__ void __launch_bounds__(128 * NQ, 2) sage_fwd_pair_kernel(FwdArgs args
     auto step = [&](const int t, v16i& s, v16i& sn, auto pv_tag, auto sm_tag, auto sn_tag, auto mask_tag) __attribute__((always_inline)) {
       const int jn = min(t + 1, nblk - 1);
       const float skn = scalar_load(sKh + jn), svn = scalar_load(sVh + jn);
-      interval(t, t + 1 < n_tiles, cq * sk, sv, cq * skn, s, sn, pv_tag, sm_tag, sn_tag, mask_tag);
+      interval(t, cq * sk, sv, cq * skn, s, sn, pv_tag, sm_tag, sn_tag, mask_tag);
       sk = skn;
       sv = svn;
     };
@@ -926,6 +934,7 @@ __global__ void __launch_bounds__(128 * NQ, 2) sage_fwd_pair_kernel(FwdArgs args
       step(t++, sA, sB, F{}, T{}, F{}, T{});
       step(t++, sA, sB, T{}, F{}, F{}, F{});
     }
+    __builtin_amdgcn_s_waitcnt(vmcnt_only(0));                 // (the copies past the last tile land before the LDS is given up)
     unbias();
   };
   if (__builtin_amdgcn_readfirstlane((int)use_sbias)) run(std::true_type{});
