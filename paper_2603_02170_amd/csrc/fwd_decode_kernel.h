@@ -141,10 +141,13 @@ __global__ void __launch_bounds__(256, 1) sage_fwd_decode_kernel(DecodeArgs args
     cq = (nz ? a / 127.0f : 0.f) * args.scale_log2e;
   }
   if constexpr (KSMOOTH) {
-    // mu_K as prepass_quant_kernel forms it: chunk sums added in float64, divided by N, rounded once to FP32
+    // mu_K as prepass_quant_kernel forms it: chunk sums added in float64 in the same order, divided by N, rounded once to FP32
+    double* red = (double*)xch;
+    head_sums<D>(args.mean_part + (size_t)bh * args.nchunk * D, args.nchunk, red);
     if (t < D) {
-      double s = 0.0;
-      for (int k = 0; k < args.nchunk; k++) s += args.mean_part[((size_t)bh * args.nchunk + k) * D + t];
+      double s = red[t];
+#pragma unroll
+      for (int g = 1; g < 256 / D; g++) s += red[g * D + t];
       mu_s[t] = (float)(s / (double)args.nk);
     }
     __syncthreads();

@@ -120,6 +120,29 @@ __global__ void __launch_bounds__(256) kmean_partial_kernel(const unsigned short
   }
 }
 
+// The chunk sums of a head, added by the 256 threads of a workgroup into red[256 / D][D] (whose rows the reader adds in
+// order): thread t takes channel t % D of every (256 / D)-th chunk, eight loads in flight.  The sum stands before all else
+// that a workgroup does with K, and each load waits for an L2 hit: with D threads adding one chunk after the other, a forward of 512
+// queries against 4096 keys, 32 heads, d = 128 took 67.3 us, this way 61.4.
+template <int D>
+__device__ __forceinline__ void head_sums(const double* __restrict__ part, const int nchunk, double* red) {
+  constexpr int GROUPS = 256 / D;
+  const int t = threadIdx.x;
+  part += t % D;
+  double s = 0.0;
+  int k = t / D;
+  for (; k + 7 * GROUPS < nchunk; k += 8 * GROUPS) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; u++) v[u] = part[(size_t)(k + u * GROUPS) * D];
+#pragma unroll
+    for (int u = 0; u < 8; u++) s += v[u];
+  }
+  for (; k < nchunk; k += GROUPS) s += part[(size_t)k * D];
+  red[t] = s;
+  __syncthreads();
+}
+
 // Short heads are summed by every workgroup that quantises a block of K, each for itself, without the launch of stage 1:
 // what that launch costs (about 2 us) against what one workgroup reads (N * D) and what all of them read.  Forward calls,
 // us without -> with: 1 head, d = 128, N = 512: 17.8 -> 17.4, 768: 20.9 -> 21.2; in millions of elements read by all, 64
@@ -326,12 +349,15 @@ __global__ void __launch_bounds__(256) prepass_quant_kernel(QuantJobs jobs) {
     __syncthreads();
   }
   if ((INLINE_MEAN && jb.mean_inline) || jb.mean_part != nullptr) {
-    // mu_K: the chunk sums of the head, added in float64, divided by N, rounded once to FP32
+    // mu_K: the float64 sum of the head, divided by N, rounded once to FP32
+    double* red = (double*)colbuf;
+    const bool inline_mean = INLINE_MEAN && jb.mean_inline;
+    if (!inline_mean) head_sums<D>(jb.mean_part + (size_t)bh * jb.nchunk * D, jb.nchunk, red);
     if (t < D) {
-      double s = 0.0;
-      const double* red = (const double*)colbuf;
-      if (INLINE_MEAN && jb.mean_inline) s = (red[t] + red[D + t]) + (red[2 * D + t] + red[3 * D + t]);
-      else for (int k = 0; k < jb.nchunk; k++) s += jb.mean_part[((size_t)bh * jb.nchunk + k) * D + t];
+      double s = red[t];
+#pragma unroll
+      for (int g = 1; g < (INLINE_MEAN ? 4 : 256 / D); g++)
+        if (inline_mean || g < 256 / D) s += red[g * D + t];
       const float m = (float)(s / (double)N);
       mu_s[t] = m;
       if (blk == 0) jb.mu_head_out[(size_t)bh * D + t] = m;

@@ -109,6 +109,18 @@ def test_prepass_bit_exact_sampled_heads_of_pretrain_shape():
     _run_case(Q, K, V, dO, params_for(w, B=3, H=1))
 
 
+# chunk sums of K (128 rows each at these sizes) shared by the 256 / d groups of threads, eight in flight: fewer than one
+# round of eight, exactly one, one more, a group that has one chunk more than another, two rounds and a rest
+@pytest.mark.parametrize("chunks,d", [(5, 128), (15, 128), (16, 128), (17, 128), (37, 128), (9, 64), (31, 64), (32, 64), (33, 64), (70, 64)])
+def test_prepass_mean_of_many_chunks_is_bit_exact(chunks, d):
+    g = torch.Generator().manual_seed(chunks)
+    Nk = 128 * chunks - 27
+    Q, dO = (torch.randn(1, 1, 40, d, generator=g).to(torch.bfloat16) for _ in range(2))
+    K, V = (torch.randn(1, 1, Nk, d, generator=g).to(torch.bfloat16) for _ in range(2))
+    K = (K.float() + torch.randn(1, 1, 1, d, generator=g) * 4).to(torch.bfloat16)
+    _run_case(Q, K, V, dO, binding.SageParams(1, 1, 40, d, causal=False, Nkv=Nk))
+
+
 @pytest.mark.parametrize("Nq,Nk,d,q_smooth", [(100, 300, 64, False), (320, 64, 128, True), (1, 200, 128, False)])
 def test_prepass_bit_exact_non_square(Nq, Nk, d, q_smooth):
     """Q, dO of N_q rows and K, V of N_kv rows: every tensor is smoothed and quantised over its own blocks."""
