@@ -13,6 +13,13 @@
 //
 // Keys are split over waves (four to a workgroup, which meet in LDS) and workgroups (whose partial O, m, l a second
 // small kernel joins).
+//
+// Two waves to a SIMD.  A wave alone gets a vector instruction out every 4.8 cycles and a block takes it about 2800, so one
+// wave per SIMD, with K and V both loaded a block ahead, was bound by issue as much as by memory (two sequences of 32 heads of
+// 8192 keys: 65 us of the call's 92).  For d = 128 two waves have room for one block of raw values each: V is loaded under the
+// logits into the registers that K has left, the next K under P^V^, values are formed twice (for the maximum and for
+// the codes) and not held, and lane-derived values are recomputed.  The call 92.4 -> 82.8 us (with the join below); 8 sequences of 32 heads of 4096 159 -> 148;
+// 32 heads of 8192, d = 64, 16 queries, four sequences 87 -> 75.
 #pragma once
 
 #include "common.h"
@@ -36,8 +43,9 @@ struct DecodeArgs {
 };
 
 template <int D, bool KSMOOTH>
-__global__ void __launch_bounds__(256, 1) sage_fwd_decode_kernel(DecodeArgs args) {
+__global__ void __launch_bounds__(256, 2) sage_fwd_decode_kernel(DecodeArgs args) {
   constexpr int KS = D / 32;
+  constexpr bool V_AHEAD = D == 64;          // registers for K and V a block ahead, in two waves per SIMD
   __shared__ __attribute__((aligned(16))) float mu_s[D];
   __shared__ __attribute__((aligned(16))) float xch[4 * KS * 4 * 64 * 4];    // partial O of the four waves
   __shared__ v2f ml[4 * 32];
@@ -50,7 +58,7 @@ __global__ void __launch_bounds__(256, 1) sage_fwd_decode_kernel(DecodeArgs args
   struct Raw {
     v8us v[2][KS][2];
   };
-  auto load_block = [&](const unsigned short* src, const int j, Raw& x) __attribute__((always_inline)) {
+  auto load_block = [&](const unsigned short* src, const int j, const int r32, const int h, Raw& x) __attribute__((always_inline)) {
 #pragma unroll
     for (int rb = 0; rb < 2; rb++) {
       const int row = min(64 * j + 32 * rb + r32, args.nk - 1);
@@ -64,10 +72,10 @@ __global__ void __launch_bounds__(256, 1) sage_fwd_decode_kernel(DecodeArgs args
   };
   // Values of one fragment (K: minus the mean).  A row that does not exist holds the last one that does, which changes no
   // maximum of its block; its key is masked, its query not stored.
-  auto values = [&](const v8us (&raw)[2], const float* mu, float (&x)[16]) __attribute__((always_inline)) {
+  auto values = [&](auto with_mean, const v8us (&raw)[2], const float* mu, float (&x)[16]) __attribute__((always_inline)) {
 #pragma unroll
     for (int e = 0; e < 16; e++) x[e] = bf16_bits_to_float(raw[e >> 3][e & 7]);
-    if (mu != nullptr) {
+    if constexpr (decltype(with_mean)::value) {
 #pragma unroll
       for (int w = 0; w < 4; w++) {
         const v4f m = *(const v4f*)(mu + 4 * w);
@@ -77,38 +85,49 @@ __global__ void __launch_bounds__(256, 1) sage_fwd_decode_kernel(DecodeArgs args
     }
   };
   // codes of a block as F fragments; returns the block's scale
-  auto quantise_block = [&](const Raw& raw, const int j, const float* mu, v4i (&f)[2][KS]) __attribute__((always_inline)) {
+  auto quantise_block = [&](auto with_mean, Raw& raw, const int h, v4i (&f)[2][KS]) __attribute__((always_inline)) {
     float a = 0.f;
+    int mu_at = 16 * h;
+    asm volatile("" : "+v"(mu_at));
 #pragma unroll
-    for (int rb = 0; rb < 2; rb++) {
+    for (int s = 0; s < KS; s++) {
 #pragma unroll
-      for (int s = 0; s < KS; s++) {
+      for (int rb = 0; rb < 2; rb++) {
         float x[16];
-        values(raw.v[rb][s], mu == nullptr ? nullptr : mu + 32 * s + 16 * h, x);
+        values(with_mean, raw.v[rb][s], mu_s + 32 * s + mu_at, x);
 #pragma unroll
         for (int e = 0; e < 16; e++) a = fmaxf(a, fabsf(x[e]));
       }
+      __builtin_amdgcn_sched_barrier(0);
     }
+    // the values are formed a second time below rather than held: raw, they take half the registers
+    asm volatile("" : "+v"(mu_at));
+#pragma unroll
+    for (int rb = 0; rb < 2; rb++)
+#pragma unroll
+      for (int s = 0; s < KS; s++) asm volatile("" : "+v"(raw.v[rb][s][0]), "+v"(raw.v[rb][s][1]));
     a = wave_max_nonneg_f32(a);
     const bool nz = a > 0.f;
     const float r = nz ? 127.0f / a : 0.f;
 #pragma unroll
-    for (int rb = 0; rb < 2; rb++) {
+    for (int s = 0; s < KS; s++) {
 #pragma unroll
-      for (int s = 0; s < KS; s++) {
+      for (int rb = 0; rb < 2; rb++) {
         float x[16];
-        values(raw.v[rb][s], mu == nullptr ? nullptr : mu + 32 * s + 16 * h, x);
+        values(with_mean, raw.v[rb][s], mu_s + 32 * s + mu_at, x);
         f[rb][s] = quantise_16(x, r);
       }
+      __builtin_amdgcn_sched_barrier(0);
     }
     return nz ? a / 127.0f : 0.f;
   };
 
   const int first = (blockIdx.x * 4 + wave) * args.blocks_per_wave;
   const int end = min(first + args.blocks_per_wave, args.nblk);
-  Raw kr, vr;
-  load_block(args.K, min(first, args.nblk - 1), kr);
-  load_block(args.V, min(first, args.nblk - 1), vr);
+  Raw kr, vr_ahead;
+  Raw& vr = V_AHEAD ? vr_ahead : kr;
+  load_block(args.K, min(first, args.nblk - 1), r32, h, kr);
+  if constexpr (V_AHEAD) load_block(args.V, min(first, args.nblk - 1), r32, h, vr);
 
   // psi(Q): the rows of the one query block
   v4i qf[KS];
@@ -125,7 +144,7 @@ __global__ void __launch_bounds__(256, 1) sage_fwd_decode_kernel(DecodeArgs args
 #pragma unroll
     for (int s = 0; s < KS; s++) {
       float x[16];
-      values(raw[s], nullptr, x);
+      values(std::false_type{}, raw[s], nullptr, x);
 #pragma unroll
       for (int e = 0; e < 16; e++) a = fmaxf(a, fabsf(x[e]));
     }
@@ -135,7 +154,7 @@ __global__ void __launch_bounds__(256, 1) sage_fwd_decode_kernel(DecodeArgs args
 #pragma unroll
     for (int s = 0; s < KS; s++) {
       float x[16];
-      values(raw[s], nullptr, x);
+      values(std::false_type{}, raw[s], nullptr, x);
       qf[s] = quantise_16(x, r);
     }
     cq = (nz ? a / 127.0f : 0.f) * args.scale_log2e;
@@ -178,11 +197,19 @@ __global__ void __launch_bounds__(256, 1) sage_fwd_decode_kernel(DecodeArgs args
     w_bias = 0.f;
   };
 
+  // counted anew for each block and behind the loop, so that nothing derived from it holds a register through it
+  auto lane_anew = []() __attribute__((always_inline)) {
+    int zero = 0;
+    asm volatile("" : "+s"(zero));
+    return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
+  };
   for (int j = first; j < end; j++) {
+    const int ln = lane_anew(), r32 = ln & 31, h = ln >> 5;
     v4i f[2][KS];
-    const float sk = quantise_block(kr, j, KSMOOTH ? mu_s : nullptr, f);
+    const float sk = quantise_block(std::integral_constant<bool, KSMOOTH>{}, kr, h, f);
     const int jn = min(j + 1, end - 1);
-    load_block(args.K, jn, kr);                              // the next block travels under this one's arithmetic
+    if constexpr (V_AHEAD) load_block(args.K, jn, r32, h, kr);       // what comes next travels under this block's arithmetic
+    else load_block(args.V, j, r32, h, vr);
     __builtin_amdgcn_sched_barrier(0);
     v16i sacc[2];
 #pragma unroll
@@ -236,16 +263,15 @@ __global__ void __launch_bounds__(256, 1) sage_fwd_decode_kernel(DecodeArgs args
       }
     l_part = __builtin_fmaf(beta, (psum[0] + psum[1]) + (psum[2] + psum[3]), l_part);
     __builtin_amdgcn_sched_barrier(0);
-    const float sv = quantise_block(vr, j, nullptr, f);
-    load_block(args.V, jn, vr);
+    const float sv = quantise_block(std::false_type{}, vr, h, f);
+    if constexpr (V_AHEAD) load_block(args.V, jn, r32, h, vr);
+    else load_block(args.K, jn, r32, h, kr);
     __builtin_amdgcn_sched_barrier(0);
     const float w = beta * sv * kTwo26;
     w_bias += w;
 #pragma unroll
     for (int cb = 0; cb < KS; cb++) {
       v16i tt;
-#pragma unroll
-      for (int r = 0; r < 16; r++) tt[r] = kBiasBits;
 #pragma unroll
       for (int kb = 0; kb < 2; kb++) {
         v16i z;
@@ -257,31 +283,34 @@ __global__ void __launch_bounds__(256, 1) sage_fwd_decode_kernel(DecodeArgs args
         for (int aa = 0; aa < 4; aa++)
           va[aa] = (int)(__builtin_amdgcn_perm((unsigned)tr[4 * aa + 1], (unsigned)tr[4 * aa], 0x0c0c0400u) |
                          __builtin_amdgcn_perm((unsigned)tr[4 * aa + 3], (unsigned)tr[4 * aa + 2], 0x04000c0cu));
-        tt = __builtin_amdgcn_mfma_i32_32x32x32_i8(va, pf[kb], tt, 0, 0, 0);
+        if (kb == 0) tt = mfma_from_bias(va, pf[kb]);
+        else tt = __builtin_amdgcn_mfma_i32_32x32x32_i8(va, pf[kb], tt, 0, 0, 0);
       }
 #pragma unroll
       for (int r = 0; r < 16; r++) oacc[cb][r] = __builtin_fmaf(__int_as_float(tt[r]), w, oacc[cb][r]);
+      if (cb & 1) __builtin_amdgcn_sched_barrier(0);
     }
     if (((j - first) & (kBiasPeriod - 1)) == kBiasPeriod - 1) unbias();
   }
   unbias();
 
   // ---- the four waves meet: wave s finishes channel block s ----
+  const int ln = lane_anew(), row = ln & 31, half = ln >> 5;
   const float l_tot = half_swap_sum_f32(l_part);
 #pragma unroll
   for (int cb = 0; cb < KS; cb++)
 #pragma unroll
     for (int aa = 0; aa < 4; aa++)
-      *(v4f*)(xch + (((wave * KS + cb) * 4 + aa) * 64 + lane) * 4) =
+      *(v4f*)(xch + (((wave * KS + cb) * 4 + aa) * 64 + ln) * 4) =
           v4f{oacc[cb][4 * aa], oacc[cb][4 * aa + 1], oacc[cb][4 * aa + 2], oacc[cb][4 * aa + 3]};
-  if (h == 0) ml[wave * 32 + r32] = v2f{m_ref, l_tot};
+  if (half == 0) ml[wave * 32 + row] = v2f{m_ref, l_tot};
   __syncthreads();
-  if (r32 >= args.nq) return;
+  if (row >= args.nq) return;
   v2f mls[4];
   float m = -INFINITY;
 #pragma unroll
   for (int s = 0; s < 4; s++) {
-    mls[s] = ml[s * 32 + r32];
+    mls[s] = ml[s * 32 + row];
     m = fmaxf(m, mls[s][0]);
   }
   float l = 0.f, wgt[4];
@@ -298,45 +327,73 @@ __global__ void __launch_bounds__(256, 1) sage_fwd_decode_kernel(DecodeArgs args
       v4f o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int s = 0; s < 4; s++) {
-        const v4f x = *(const v4f*)(xch + (((s * KS + wave) * 4 + aa) * 64 + lane) * 4);
+        const v4f x = *(const v4f*)(xch + (((s * KS + wave) * 4 + aa) * 64 + ln) * 4);
 #pragma unroll
         for (int e = 0; e < 4; e++) o[e] = __builtin_fmaf(x[e], wgt[s], o[e]);
       }
-      const int ch = 32 * wave + 8 * aa + 4 * h;
+      const int ch = 32 * wave + 8 * aa + 4 * half;
       if (whole) {
         v4us ob;
 #pragma unroll
         for (int e = 0; e < 4; e++) ob[e] = float_to_bf16_bits(o[e] * inv_l);
-        *(v4us*)(args.O + args.qview.row(bh, r32) + ch) = ob;
+        *(v4us*)(args.O + args.qview.row(bh, row) + ch) = ob;
       } else {
-        *(v4f*)(args.part + (((size_t)bh * gridDim.x + blockIdx.x) * 32 + r32) * D + ch) = o;
+        *(v4f*)(args.part + (((size_t)bh * gridDim.x + blockIdx.x) * 32 + row) * D + ch) = o;
       }
     }
   }
-  if (wave == 0 && h == 0) {
-    if (whole) args.LSE[(size_t)bh * args.nq + r32] = (m + __builtin_amdgcn_logf(l) - kLog2_127) * kLn2;
-    else args.part_ml[((size_t)bh * gridDim.x + blockIdx.x) * 32 + r32] = v2f{m, l};
+  if (wave == 0 && half == 0) {
+    if (whole) args.LSE[(size_t)bh * args.nq + row] = (m + __builtin_amdgcn_logf(l) - kLog2_127) * kLn2;
+    else args.part_ml[((size_t)bh * gridDim.x + blockIdx.x) * 32 + row] = v2f{m, l};
   }
 }
 
-// Joins the workgroups' partial (O, m, l): one workgroup of D threads per (query, head).
+// Joins the workgroups' partial (O, m, l): one workgroup of 256 threads per (query, head), D / 4 of them to a row of O.
+// Bound by latency: every thread has the loads of its rows in flight while the waves find m and l, each for itself.
+// (One thread per channel and all the rows in
+// turn: 1 head of 8192 keys, 32 partial results, 7 us more for the call; 16 heads of 8192 keys, 32 queries, 9 us.)
 template <int D>
-__global__ void __launch_bounds__(D) sage_fwd_decode_join_kernel(DecodeArgs args, int nsplit) {
-  const int q = blockIdx.x, bh = blockIdx.y, ch = threadIdx.x;
+__global__ void __launch_bounds__(256) sage_fwd_decode_join_kernel(DecodeArgs args, int nsplit) {
+  constexpr int LANES = D / 4, GROUPS = 256 / LANES;
+  __shared__ v4f sums[GROUPS][LANES];
+  const int q = blockIdx.x, bh = blockIdx.y, t = threadIdx.x, lane = t & 63;
+  const int g = t / LANES, c = t % LANES;
   const v2f* ml = args.part_ml + (size_t)bh * nsplit * 32 + q;
-  const float* part = args.part + ((size_t)bh * nsplit * 32 + q) * D + ch;
+  const float* part = args.part + ((size_t)bh * nsplit * 32 + q) * D + 4 * c;
   float m = -INFINITY;
-  for (int s = 0; s < nsplit; s++) m = fmaxf(m, ml[(size_t)s * 32][0]);
-  float l = 0.f, o = 0.f;
-#pragma unroll 4
-  for (int s = 0; s < nsplit; s++) {
+  for (int s = lane; s < nsplit; s += 64) m = fmaxf(m, ml[(size_t)s * 32][0]);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+  float l = 0.f;
+  for (int s = lane; s < nsplit; s += 64) {
     const v2f e = ml[(size_t)s * 32];
-    const float w = __builtin_amdgcn_exp2f(e[0] - m);
-    l = __builtin_fmaf(e[1], w, l);
-    o = __builtin_fmaf(part[(size_t)s * 32 * D], w, o);
+    l = __builtin_fmaf(e[1], __builtin_amdgcn_exp2f(e[0] - m), l);
   }
-  args.O[args.qview.row(bh, q) + ch] = float_to_bf16_bits(o * (1.0f / l));
-  if (ch == 0) args.LSE[(size_t)bh * args.nq + q] = (m + __builtin_amdgcn_logf(l) - kLog2_127) * kLn2;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off, 64);
+  v4f o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int s = g; s < nsplit; s += GROUPS) {
+    const float w = __builtin_amdgcn_exp2f(ml[(size_t)s * 32][0] - m);
+    const v4f x = *(const v4f*)(part + (size_t)s * 32 * D);
+#pragma unroll
+    for (int e = 0; e < 4; e++) o[e] = __builtin_fmaf(x[e], w, o[e]);
+  }
+  sums[g][c] = o;
+  __syncthreads();
+  if (g != 0) return;
+#pragma unroll
+  for (int k = 1; k < GROUPS; k++) {
+    const v4f x = sums[k][c];
+#pragma unroll
+    for (int e = 0; e < 4; e++) o[e] += x[e];
+  }
+  const float inv_l = 1.0f / l;
+  v4us ob;
+#pragma unroll
+  for (int e = 0; e < 4; e++) ob[e] = float_to_bf16_bits(o[e] * inv_l);
+  *(v4us*)(args.O + args.qview.row(bh, q) + 4 * c) = ob;
+  if (t == 0) args.LSE[(size_t)bh * args.nq + q] = (m + __builtin_amdgcn_logf(l) - kLog2_127) * kLn2;
 }
 
 }  // namespace sage

@@ -515,13 +515,13 @@ int launch_bwd_dq(const DqArgs& a, bool causal, hipStream_t st) {
 
 // One query block of at most 32 rows that sees every key, plain options: see fwd_decode_kernel.h.  (Its kernel is long, and
 // with a short cache few workgroups share the cost of fetching its instructions.)  Whole calls, us with codes in the workspace
-// -> this way.  d = 128: 1 head, 20 key blocks 21.9 -> 23.7, 24 24.0 -> 24.4, 32 27.7 -> 25.9; 16 heads, 16 blocks 22.3 -> 22.8, 24
-// 27.4 -> 25.7; blocks over all heads: 48 heads of 12 (576) 23.0 -> 24.5, 64 of 12 (768) 24.8 -> 24.8, 128 of 6 (768) 28.0 ->
-// 23.3, 256 of 4 (1024) 27.0 -> 20.9.  d = 64: 1 head, 12 blocks 14.5 -> 16.2 (2 heads), 16 16.4 -> 15.7, 32 24.1 -> 20.1; 64 heads
-// of 6 (384) 15.1 -> 15.3, of 8 (512) 17.4 -> 15.6, 256 of 2 (512) 12.6 -> 11.6.
+// -> this way.  d = 128: 1 head, 16 key blocks 18.5 -> 19.4, 20 20.3 -> 20.2, 24 22.3 -> 20.2; 16 heads, 12 blocks 18.7 -> 20.2, 16
+// 20.7 -> 20.1, 24 26.0 -> 21.0; blocks over all heads: 64 heads of 4 (256) 14.6 -> 16.3, 128 of 3 (384) 15.0 -> 16.0, 64 of 8 (512)
+// 19.8 -> 19.6, 256 of 2 (512) 15.2 -> 15.1, 48 of 12 (576) 22.3 -> 21.1, 256 of 4 (1024) 24.8 -> 19.1.  d = 64: 1 head, 12 blocks
+// 14.0 -> 14.7, 16 16.3 -> 14.9; 64 heads of 6 (384) 14.7 -> 15.2, of 8 (512) 15.9 -> 15.2, 256 of 1 8.6 -> 11.4, of 2 (512) 12.4 -> 11.5.
 bool use_decode(const sagebwd_params& p) {
   const int nblk = padded_rows(kv_len(p)) / 64;
-  const bool long_enough = nblk >= (p.d == 64 ? 16 : 24) || (long long)p.B * p.H * nblk >= (p.d == 64 ? 512 : 768);
+  const bool long_enough = nblk >= (p.d == 64 ? 16 : 20) || (long long)p.B * p.H * nblk >= 512;
   return long_enough && p.N <= 32 && p.causal == 0 && !(p.smooth & SAGEBWD_SMOOTH_Q) && !(p.flags & SAGEBWD_FLAG_QK_NORM) && !big_blocks(p);
 }
 
@@ -544,8 +544,8 @@ int decode_impl(const void* Q, const void* K, const void* V, void* O, float* LSE
   a.nk = kv_len(p);
   a.nblk = padded_rows(a.nk) / 64;
   a.scale_log2e = logit_scale(p) * 1.4426950408889634f;
-  // one wave per SIMD (its registers hold the block in hand and the next one), each on as few blocks as that allows
-  a.blocks_per_wave = (int)(((long long)BH * a.nblk + kSimds - 1) / kSimds);
+  // two waves per SIMD, each on as few blocks as that allows
+  a.blocks_per_wave = (int)(((long long)BH * a.nblk + 2 * kSimds - 1) / (2 * kSimds));
   const int nsplit = (a.nblk + 4 * a.blocks_per_wave - 1) / (4 * a.blocks_per_wave);
   // the workgroups' partial results lie where K^ would: a workgroup has at least four key blocks (4 * 64 * D bytes) unless
   // it is the last of its head, and leaves at most 32 * (4 D + 8)
@@ -561,7 +561,7 @@ int decode_impl(const void* Q, const void* K, const void* V, void* O, float* LSE
   else sage_fwd_decode_kernel<D, false><<<dim3(nsplit, BH), 256, 0, st>>>(a);
   SAGE_LAUNCH_CHECK();
   if (nsplit > 1) {
-    sage_fwd_decode_join_kernel<D><<<dim3(p.N, BH), D, 0, st>>>(a, nsplit);
+    sage_fwd_decode_join_kernel<D><<<dim3(p.N, BH), 256, 0, st>>>(a, nsplit);
     SAGE_LAUNCH_CHECK();
   }
   return SAGEBWD_OK;

@@ -77,7 +77,7 @@ def test_the_forms_for_calls_that_do_not_fill_the_machine(kernels):
         assert k["scratch"] <= 96 and k["vgpr"] <= 256 and k["lds"] <= 160 * 1024, k
     for bits in (("ILi64E",), ("ILi128ELb0ELb1E",), ("ILi128ELb1ELb1E",)):
         assert all(k["scratch"] == 0 for k in _pick(kernels, "sage_fwd_split_kernel", *bits)), bits
-    # one wave per SIMD: the whole register file, no scratch
+    # nothing in scratch
     for k in _pick(kernels, "sage_fwd_decode_kernel"):
         assert k["scratch"] == 0 and k["vgpr"] <= 512 and k["lds"] <= 160 * 1024, k
     # one KV block per workgroup: two workgroups per CU at d = 64 without Q-smoothing
@@ -86,6 +86,11 @@ def test_the_forms_for_calls_that_do_not_fill_the_machine(kernels):
     for bits in ("ILi64ELb1ELb0E", "ILi64ELb0ELb0E"):
         for k in _pick(kernels, "sage_bwd_single_kernel", bits):
             assert k["vgpr"] <= 128 and 2 * k["lds"] <= 160 * 1024, k
+
+
+def test_two_workgroups_of_the_decoding_kernel_share_a_cu(kernels):
+    for k in _pick(kernels, "sage_fwd_decode_kernel"):
+        assert k["vgpr"] <= 256 and 2 * k["lds"] <= 160 * 1024, k
 
 
 def test_backward_with_four_kv_blocks_keeps_its_operands_in_registers(kernels):
