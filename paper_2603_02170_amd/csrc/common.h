@@ -160,8 +160,8 @@ struct RowView {
 // an XCD are taken `head_set` at a time, and inside such a set the items go heaviest first over ALL its
 // heads (item 0 of every head, then item 1, ...): with the causal mask the last workgroups to start
 // are then the lightest of several heads, not of one.  That shortens the tail of short-sequence
-// launches (13 % of the step at N = 2048); at N = 8192 the compute kernels lose 2 % to it (several
-// heads' operands compete for the L2), so they take one head at a time there.
+// launches (13 % of the step at N = 2048); from more than 32 items a head on the forward and the backward with two KV blocks
+// per workgroup lose 2 % to it (several heads' operands compete for the L2), so they take one head at a time there.
 // Other head counts are laid out densely over the XCDs: no workgroup is without work (it would still queue for a whole
 // workgroup's LDS and wave slots before it could exit) and a single head spreads over all XCDs instead of one.
 // Short sequences take the items heaviest first over ALL heads (head after head, the heaviest items of the

@@ -474,7 +474,11 @@ template <bool QSMOOTH, int MODE, bool KV128 = false>
 int launch_bwd_wide(const BwdArgs& a, bool causal, hipStream_t st) {
   const int nquad = (a.N / 64 + 3) / 4;
   BwdArgs args = a;
-  args.head_set = head_set_for(nquad, a.BH);
+  // Sets of heads at every length under the mask: four blocks of a head share what an XCD's L2 serves, so four heads' operands do not
+  // crowd it, and the lightest workgroups of several heads end the launch.  Whole backward, us one head at a time -> in sets: 64 heads
+  // of N = 6144 1612 -> 1538, of 8192 2661 -> 2616, of 8256 2703 -> 2685, 24 of 10000 1527 -> 1472, 32 of 12288 2949 -> 2872, 16 of 16384 2482 -> 2490, 8 of
+  // 32768 6233 -> 6228.  Without the mask the rule of the other kernels (16 of 16384 4794 one at a time, 4820 in sets).
+  args.head_set = head_set_for(nquad, a.BH, causal);
   const int grid = grid_for(a.BH, nquad);
   if (causal) sage_bwd_wide_kernel<128, true, QSMOOTH, MODE, KV128><<<grid, 512, 0, st>>>(args);
   else sage_bwd_wide_kernel<128, false, QSMOOTH, MODE, KV128><<<grid, 512, 0, st>>>(args);
