@@ -24,7 +24,7 @@ HBM_PEAK_GBS = 8000.0       # MI355X HBM3E peak (published)
 # HBM bytes per launch at the headline workload.  NOT measured in this run: taken from the committed
 # rocprofv3 FETCH_SIZE / WRITE_SIZE runs summarised in profiles/hbm_traffic_cases.txt
 # (scaled by the copy-kernel calibration stated there).
-PROFILED_TRAFFIC_BYTES = {"headline": {"bwd": 3.5265e9, "fwd": 3.381e8, "bwd_dq": 2.6568e9}}
+PROFILED_TRAFFIC_BYTES = {"headline": {"bwd": 5.2341e9, "fwd": 3.381e8, "bwd_dq": 2.6339e9}}
 
 
 def work_ops(w, fwd=True, bwd=True, matmuls=None):
@@ -195,9 +195,10 @@ def main():
 
     peaks = measured_peaks(torch, binding)
     tops = work_ops(w) / (ms * 1e-3) / 1e12
-    # sage_bwd_kernel runs four of the five backward matmuls (S recompute, dV, dP, dK); the fifth (dQ)
+    # the backward kernel (sage_bwd_wide_kernel at the headline shape) runs four of the five backward matmuls (S recompute, dV, dP, dK); the fifth (dQ)
     # runs in sage_bwd_dq_kernel from the staged psi(dS) tiles
     bwd_ops = work_ops(w, matmuls=4)
+    bwd_kernel = "sage_bwd_wide_kernel" if w.d == 128 and w.N >= 1024 else "backward kernel (by shape)"
     fwd_ops = work_ops(w, bwd=False)
     bwd_tops = bwd_ops / (kern["bwd"] * 1e-3) / 1e12
     fwd_tops = fwd_ops / (kern["fwd"] * 1e-3) / 1e12
@@ -231,7 +232,7 @@ def main():
                           "mean HIP-event duration per launch over the timed region, every kernel bracketed",
         "measured_peaks": peaks,
         "pct_of_measured_int8_peak": 100.0 * tops / peaks["int8_mfma"]["value"],
-        "roofline": {"bound": "mfma", "kernel": "sage_bwd_kernel", "achieved": bwd_tops, "peak": INT8_PEAK_TOPS,
+        "roofline": {"bound": "mfma", "kernel": bwd_kernel, "achieved": bwd_tops, "peak": INT8_PEAK_TOPS,
                      "unit": "TOP/s", "frac": bwd_tops / INT8_PEAK_TOPS,
                      "traffic": traffic.get("bwd"),
                      "frac_of_mixed_roof": bwd_tops / (INT8_PEAK_TOPS * 0.8),
