@@ -14,7 +14,7 @@
 // Keys are split over waves (four to a workgroup, which meet in LDS) and workgroups (whose partial O, m, l a second
 // small kernel joins).
 //
-// Two waves to a SIMD.  A wave alone gets a vector instruction out every 4.8 cycles and a block takes it about 2800, so one
+// Two waves to a SIMD.  A wave alone gets a vector instruction out every 4.8 cycles and a block took it about 2800, so one
 // wave per SIMD, with K and V both loaded a block ahead, was bound by issue as much as by memory (two sequences of 32 heads of
 // 8192 keys: 65 us of the call's 92).  For d = 128 two waves have room for one block of raw values each: V is loaded under the
 // logits into the registers that K has left, the next K under P^V^, values are formed twice (for the maximum and for
@@ -220,16 +220,23 @@ __global__ void __launch_bounds__(256, 2) sage_fwd_decode_kernel(DecodeArgs args
       for (int s = 0; s < KS; s++) sacc[kb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f[kb][s], qf[s], sacc[kb], 0, 0, 0);
     }
     const float c = cq * sk;
+    // keys that do not exist: only the last block of a head has any (masking every block was 128 of its 2800 instructions: 128
+    // heads of 2048 keys, d = 64, 29.5 -> 28.4 us; 64 of 8192, d = 128, 82.6 -> 81.9)
+    const bool ragged = 64 * j + 64 > args.nk;
+    auto exists = [&](const int kb, const int r) __attribute__((always_inline)) {
+      return 64 * j + 32 * kb + 8 * (r >> 2) + 4 * h + (r & 3) < args.nk;
+    };
+    if (ragged) {
+#pragma unroll
+      for (int kb = 0; kb < 2; kb++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) sacc[kb][r] = exists(kb, r) ? sacc[kb][r] : INT_MIN;
+    }
     int mi[2] = {INT_MIN, INT_MIN};
 #pragma unroll
     for (int kb = 0; kb < 2; kb++)
 #pragma unroll
-      for (int r = 0; r < 16; r++) {
-        const int key = 64 * j + 32 * kb + 8 * (r >> 2) + 4 * h + (r & 3);
-        const int v = key < args.nk ? sacc[kb][r] : INT_MIN;
-        sacc[kb][r] = v;
-        mi[kb] = max(mi[kb], v);
-      }
+      for (int r = 0; r < 16; r++) mi[kb] = max(mi[kb], sacc[kb][r]);
     const float mloc = (float)half_swap_max_i32(max(mi[0], mi[1])) * c;
     if (__builtin_amdgcn_ballot_w64(mloc > m_ref + kTau) != 0) {
       const float m_new = fmaxf(m_ref, mloc);
@@ -244,6 +251,17 @@ __global__ void __launch_bounds__(256, 2) sage_fwd_decode_kernel(DecodeArgs args
     }
     const float beta = __builtin_amdgcn_exp2f(mloc - m_ref);
     const float off = kLog2_127 - mloc;
+    float xv[2][16];
+#pragma unroll
+    for (int kb = 0; kb < 2; kb++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) xv[kb][r] = __builtin_fmaf((float)sacc[kb][r], c, off);
+    if (ragged) {
+#pragma unroll
+      for (int kb = 0; kb < 2; kb++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) xv[kb][r] = exists(kb, r) ? xv[kb][r] : -INFINITY;
+    }
     float psum[4] = {0.f, 0.f, 0.f, 0.f};
     v4i pf[2];
 #pragma unroll
@@ -253,9 +271,7 @@ __global__ void __launch_bounds__(256, 2) sage_fwd_decode_kernel(DecodeArgs args
         unsigned u = 0;
 #pragma unroll
         for (int b = 0; b < 4; b++) {
-          const int v = sacc[kb][4 * aa + b];
-          const float xv = v == INT_MIN ? -INFINITY : __builtin_fmaf((float)v, c, off);
-          const float e = __builtin_amdgcn_exp2f(xv);
+          const float e = __builtin_amdgcn_exp2f(xv[kb][4 * aa + b]);
           psum[b] += e;
           u = __builtin_amdgcn_cvt_pk_u8_f32(e, b, u);
         }
