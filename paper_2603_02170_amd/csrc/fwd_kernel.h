@@ -408,8 +408,8 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 3 : 2) sage_fwd_kernel(FwdA
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ql = lane & 31, h = lane >> 5;
   const int N = args.N;
-  // First query of this wave.  The last workgroup of an odd number of Q blocks has two waves without queries: they read the
-  // last rows that exist, take part in the copies and the barriers, form one tile and store nothing.  (Workgroups of 64
+  // First query of this wave.  The last workgroup of an odd number of Q blocks has two waves without queries: they take part in
+  // the copies and the barriers, form nothing and store nothing (q0: rows that exist, for the loads of the prologue).  (Workgroups of 64
   // queries served such calls before: half the waves to share a staged tile, and 6 heads of N = 22028, blocks of 128, took 998 us where N = 22016 took 677; now 705.)
   const int q0w = qt * QT + 32 * wave;
   const bool has_rows = q0w < args.Nq;
@@ -438,7 +438,7 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 3 : 2) sage_fwd_kernel(FwdA
   const float* bias_row = QSMOOTH ? args.bias + ((size_t)bh * nqblk + q0 / kBlock) * N : nullptr;
 
   const int n_tiles = CAUSAL ? min((qt * QT + QT + args.shift) / kBlock, nblk) : nblk;   // barrier count, uniform in the workgroup
-  const int last = !has_rows ? 0 : CAUSAL ? (q0 + 31 + args.shift) / kBlock : nblk - 1;   // this wave's last tile (masked if causal)
+  const int last = CAUSAL ? (q0 + 31 + args.shift) / kBlock : nblk - 1;       // this wave's last tile (masked if causal)
 
   float oacc[KS][16];
 #pragma unroll
@@ -480,20 +480,37 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 3 : 2) sage_fwd_kernel(FwdA
   // past the barrier that ended iteration j - 1, so nobody reads it any more); this wave forms
   // S_{j+1} from slot `nxt` and finishes tile j with V^ from slot `cur`; before the barrier at
   // the end it waits for the copies of tile j + 2 (issued one iteration earlier), while its copies
-  // of tile j + 3 stay in flight (past the last tile that one again, never read: without a branch around each copy the tile
-  // is one basic block, 1 to 3 % of the kernel).  The block scales come one tile ahead through the scalar cache, so the
+  // of tile j + 3 stay in flight (from an unmasked iteration past the last tile that one again, never read: without a branch around
+  // each copy the tile is one basic block, 1 to 3 % of the kernel).  The block scales come one tile ahead through the scalar cache, so the
   // loop has no register-returning vector loads whose waits would also drain the copies.  Every wave of
   // the workgroup runs n_tiles iterations (the barriers must match): its unmasked tiles, its last
   // tile, then iterations that only keep the ring moving.
-  auto end_iter = [&]() {
-    __builtin_amdgcn_s_waitcnt(vmcnt_only(CPW));   // vmcnt: all but this iteration's copies
-    barrier_lds_only();
+  auto end_iter = [&](const bool issued) __attribute__((always_inline)) {
+    if (issued) {
+      __builtin_amdgcn_s_waitcnt(vmcnt_only(CPW));   // vmcnt: all but this iteration's copies
+      barrier_lds_only();
+    } else {
+      barrier_all_memory();
+    }
     int8_t* t = cur;
     cur = nxt;
     nxt = nx2;
     nx2 = nx3;
     nx3 = t;
   };
+  // An iteration after the wave's last tile.  From that tile on a copy is issued only where there is a tile, so the last wait of the
+  // workgroup is for everything and short calls copy no tile twice (numerics blocks of 128 keys also lose the registers that the clamped
+  // addresses held: 116 bytes of scratch -> 0).  With this and waves without queries that form nothing, forward calls in us: 2048 heads of
+  // N = 192, d = 64, 92.9 -> 90.3, 1100 of N = 40, d = 128, 31.7 -> 31.0, 4096 of N = 64 112.6 -> 111.2, 600 of N = 128 with blocks of 128 keys, d = 64, 27.6 -> 26.3.
+  auto keep_ring_moving = [&](const int j) {
+    const bool issue = j + 3 < n_tiles;
+    if (issue) stage_load(j + 3, nx3);
+    end_iter(issue);
+  };
+  if (!has_rows) {
+    for (int j = 0; j < n_tiles; j++) keep_ring_moving(j);
+    return;
+  }
   // subtracts the bias that the output accumulators carry (see the header)
   auto unbias = [&]() {
     const float corr = kBiasC0 * w_bias;
@@ -534,7 +551,7 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 3 : 2) sage_fwd_kernel(FwdA
     };
     constexpr bool CARRY = !QSMOOTH && !KV128;
     int carried = INT_MIN;
-    if constexpr (CARRY) carried = tile_row_max<false, false>(sA, 0.f, nullptr, 0, 0, h).i;
+    if (CARRY && last > 0) carried = tile_row_max<false, false>(sA, 0.f, nullptr, 0, 0, h).i;
     auto full_iter = [&](const int j, v16i (&sc)[2], v16i (&sn)[2]) __attribute__((always_inline)) {
       const int jl = min(j + 3, n_tiles - 1);
       asm volatile("" : "+v"(lane16));
@@ -545,7 +562,7 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 3 : 2) sage_fwd_kernel(FwdA
       if ((j & (kBiasPeriod - 1)) == kBiasPeriod - 1) unbias();
       sk = skn;
       sv = svn;
-      end_iter();
+      end_iter(true);
     };
     int j = 0;
     for (; j + 1 < last; j += 2) {
@@ -563,18 +580,15 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 3 : 2) sage_fwd_kernel(FwdA
       j++;
     }
     {
-      stage_load(min(j + 3, n_tiles - 1), nx3);
+      const bool issue = j + 3 < n_tiles;
+      if (issue) stage_load(j + 3, nx3);
       // (the last tile always takes the masked path: without the causal mask it hides the keys past nvalid)
       fwd_tile<D, QSMOOTH, true, false, SBIAS, KV128>([](int) {}, nxt, cur + TILE_BYTES, qf, sA, sB, oacc, w_bias, m_ref, l_part,
                                         cq * sk, sv, (const float*)(cur + BIAS_OFF + wave * 256), j * kBlock, qlim, lane, h, &pm);
-      end_iter();
+      end_iter(issue);
       j++;
     }
-    for (; j < n_tiles; j++) {
-      stage_load(min(j + 3, n_tiles - 1), nx3);
-      end_iter();
-    }
-    __builtin_amdgcn_s_waitcnt(vmcnt_only(0));     // (the copies past the last tile land before the LDS is given up)
+    for (; j < n_tiles; j++) keep_ring_moving(j);
     unbias();
     // ---- epilogue: O = O / l, L = m + log(l) (l carries a factor 127) ----
     const float l_tot = half_swap_sum_f32(l_part[0]) + half_swap_sum_f32(l_part[1]);

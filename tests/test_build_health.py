@@ -50,33 +50,28 @@ def test_backward_kernels_keep_their_loops_free_of_scratch(kernels):
             assert k["scratch"] == 0 and k["vgpr"] <= 256, (bits, k)
             assert k["lds"] <= 160 * 1024
     for k in _pick(kernels, "sage_bwd_kernel"):
-        assert k["scratch"] <= 64 and k["vgpr"] <= 256 and k["lds"] <= 160 * 1024, k
+        assert k["scratch"] <= 24 and k["vgpr"] <= 256 and k["lds"] <= 160 * 1024, k
     for k in _pick(kernels, "sage_bwd_dq_kernel"):
         # three workgroups of four waves per CU: 168 registers, a third of the LDS
         assert k["scratch"] == 0 and k["vgpr"] <= 168 and 3 * k["lds"] <= 160 * 1024, k
 
 
 def test_forward_kernels_fit_their_occupancy(kernels):
-    # four-wave workgroups, two per CU at d = 128 (256 registers) and three at d = 64 (168); the few
-    # registers kept in scratch are used before and after the tile loop only
-    # (the last template argument, Lb0E / Lb1E, selects numerics blocks of 64 / 128 keys; the latter keeps a pair
-    # of row maxima more and may park a few more registers)
-    for kv128, scratch in (("ELi4ELb0E", 80), ("ELi4ELb1E", 128)):
-        for k in _pick(kernels, "sage_fwd_kernel", "ILi128E", kv128):
-            assert k["vgpr"] <= 256 and k["scratch"] <= scratch and 2 * k["lds"] <= 160 * 1024, k
-        for k in _pick(kernels, "sage_fwd_kernel", "ILi64E", kv128):
-            assert k["vgpr"] <= 168 and k["scratch"] <= scratch and 3 * k["lds"] <= 160 * 1024, k
+    # four-wave workgroups, two per CU at d = 128 (256 registers) and three at d = 64 (168), nothing in scratch, with numerics
+    # blocks of 64 keys or 128
+    for k in _pick(kernels, "sage_fwd_kernel", "ILi128E"):
+        assert k["vgpr"] <= 256 and k["scratch"] == 0 and 2 * k["lds"] <= 160 * 1024, k
+    for k in _pick(kernels, "sage_fwd_kernel", "ILi64E"):
+        assert k["vgpr"] <= 168 and k["scratch"] == 0 and 3 * k["lds"] <= 160 * 1024, k
 
 
 def test_the_forms_for_calls_that_do_not_fill_the_machine(kernels):
     # one wave per SIMD of four-wave workgroups and two: registers only, nothing in scratch
     for k in _pick(kernels, "sage_fwd_pair_kernel"):
         assert k["scratch"] == 0 and k["vgpr"] <= 256 and 2 * k["lds"] <= 160 * 1024, k
-    # eight waves and most of the LDS of a CU; at d = 128 without Q-smoothing some registers are parked outside the tile loop
+    # eight waves and most of the LDS of a CU
     for k in _pick(kernels, "sage_fwd_split_kernel"):
-        assert k["scratch"] <= 96 and k["vgpr"] <= 256 and k["lds"] <= 160 * 1024, k
-    for bits in (("ILi64E",), ("ILi128ELb0ELb1E",), ("ILi128ELb1ELb1E",)):
-        assert all(k["scratch"] == 0 for k in _pick(kernels, "sage_fwd_split_kernel", *bits)), bits
+        assert k["scratch"] == 0 and k["vgpr"] <= 256 and k["lds"] <= 160 * 1024, k
     # nothing in scratch
     for k in _pick(kernels, "sage_fwd_decode_kernel"):
         assert k["scratch"] == 0 and k["vgpr"] <= 512 and k["lds"] <= 160 * 1024, k
