@@ -45,10 +45,12 @@ struct DecodeArgs {
 template <int D, bool KSMOOTH>
 __global__ void __launch_bounds__(256, 2) sage_fwd_decode_kernel(DecodeArgs args) {
   constexpr int KS = D / 32;
+  constexpr int Q_LDS = D == 128 ? 2 : 0;    // fragments of psi(Q), the same for all four waves, that lie in LDS: nothing is in scratch then
   constexpr bool V_AHEAD = D == 64;          // registers for K and V a block ahead, in two waves per SIMD
   __shared__ __attribute__((aligned(16))) float mu_s[D];
   __shared__ __attribute__((aligned(16))) float xch[4 * KS * 4 * 64 * 4];    // partial O of the four waves
   __shared__ v2f ml[4 * 32];
+  __shared__ v4i q_lds[Q_LDS ? 64 * Q_LDS : 1];                               // the last fragments of psi(Q)
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int r32 = lane & 31, h = lane >> 5;
@@ -159,6 +161,9 @@ __global__ void __launch_bounds__(256, 2) sage_fwd_decode_kernel(DecodeArgs args
     }
     cq = (nz ? a / 127.0f : 0.f) * args.scale_log2e;
   }
+  // (every wave writes the same values and reads only after its own writes)
+#pragma unroll
+  for (int s = 0; s < Q_LDS; s++) q_lds[64 * s + lane] = qf[KS - Q_LDS + s];
   if constexpr (KSMOOTH) {
     // mu_K as prepass_quant_kernel forms it: chunk sums added in float64 in the same order, divided by N, rounded once to FP32
     double* red = (double*)xch;
@@ -212,6 +217,8 @@ __global__ void __launch_bounds__(256, 2) sage_fwd_decode_kernel(DecodeArgs args
     else load_block(args.V, j, r32, h, vr);
     __builtin_amdgcn_sched_barrier(0);
     v16i sacc[2];
+#pragma unroll
+    for (int s = 0; s < Q_LDS; s++) qf[KS - Q_LDS + s] = q_lds[64 * s + ln];
 #pragma unroll
     for (int kb = 0; kb < 2; kb++) {
 #pragma unroll

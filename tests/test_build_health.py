@@ -14,6 +14,9 @@ from paper_2603_02170_amd import build
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
+_TEXT = []      # the assembly that `kernels` was read from
+
+
 @pytest.fixture(scope="module")
 def kernels():
     with tempfile.TemporaryDirectory() as tmp:
@@ -32,6 +35,7 @@ def kernels():
         info[name] = dict(vgpr=get(r"\.amdhsa_next_free_vgpr"), scratch=get(r"\.amdhsa_private_segment_fixed_size"),
                           lds=get(r"\.amdhsa_group_segment_fixed_size"))
     assert not re.search(r"\bv_pk_(fma|mul|add)_f32\b", text), "packed FP32 instructions must stay out of the build"
+    _TEXT.append(text)
     return info
 
 
@@ -92,3 +96,27 @@ def test_backward_with_four_kv_blocks_keeps_its_operands_in_registers(kernels):
     # two waves per SIMD and 157 KB of LDS
     for k in _pick(kernels, "sage_bwd_wide_kernel"):
         assert k["scratch"] == 0 and k["vgpr"] <= 256 and k["lds"] <= 160 * 1024, k
+
+
+def _registers(operands):
+    """Vector registers that an instruction names, as (first, last) ranges."""
+    return [(int(m[1]), int(m[2] or m[1])) for m in re.finditer(r"\bv\[?(\d+)(?::(\d+)\])?", operands)]
+
+
+def test_products_that_start_from_the_inline_constant_are_read_by_their_chain_only(kernels):
+    """mfma_from_bias is assembly that the compiler does not know for a matrix product: its result may not lie on its
+    operands' registers, and the first thing that touches it has to be the next product of the chain, with it as C."""
+    code = [line.split(";")[0].strip() for line in _TEXT[0].split("\n")]
+    code = [line for line in code if line and not (line.startswith(".") and not line.startswith(".LBB"))]
+    starts = [n for n, line in enumerate(code) if line.startswith("v_mfma") and "0.15915494" in line]
+    assert len(starts) > 100
+    overlaps = lambda a, b: a[0] <= b[1] and b[0] <= a[1]
+    for n in starts:
+        dst, *operands = _registers(code[n])
+        assert dst[1] - dst[0] == 15 and len(operands) == 2
+        assert not any(overlaps(dst, r) for r in operands), code[n]
+        for line in code[n + 1:]:
+            assert not line.startswith((".LBB", "s_cbranch", "s_branch", "s_endpgm")), (code[n], line)
+            if any(overlaps(dst, r) for r in _registers(line)):
+                assert line.startswith("v_mfma_i32_32x32x32_i8") and _registers(line)[3:] == [dst], (code[n], line)
+                break
