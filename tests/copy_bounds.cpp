@@ -1,4 +1,4 @@
-// Every row of dO and every Q block that the staging copies of sage_bwd_single_kernel read, over all small shapes, and the
+// Every row of dO and every Q block that the staging copies of sage_bwd_single_kernel read, over all small shapes, the rows that a decoding step reads, and the
 // (head, item) of every workgroup, from the index functions the kernels themselves use.  Prints the first access that lies
 // outside the tensor, or the first workgroup without a (head, item) of its own, and returns 1.
 #include <stdio.h>
@@ -28,8 +28,38 @@ int every_workgroup_has_its_own_work() {
   return 0;
 }
 
+// The loads of K of sage_fwd_decode_kernel: before the loop the wave's first block, in block j the one after it.
+int decoding_reads_every_block_once() {
+  for (int nk = 1; nk <= 700; nk++)
+    for (int per_wave = 1; per_wave <= 5; per_wave++) {
+      const int nblk = (nk + 63) / 64, waves = 4 * ((nblk + 4 * per_wave - 1) / (4 * per_wave));
+      std::vector<int> read(nk, 0);
+      for (int w = 0; w < waves; w++) {
+        const int first = w * per_wave, end = first + per_wave < nblk ? first + per_wave : nblk;
+        auto load = [&](int j, bool mine) {
+          std::vector<char> rows(nk, 0);
+          for (int r = 0; r < 64; r++) {
+            const int row = sage::decode_row(64 * j + r, mine, nk);
+            if (row < 0 || row >= nk) return false;
+            rows[row] = 1;
+            if (mine && 64 * j + r < nk && row != 64 * j + r) return false;
+          }
+          for (int r = 0; r < nk; r++) read[r] += rows[r];
+          return true;
+        };
+        bool fine = load(first, first < end);
+        for (int j = first; j < end; j++) fine = fine && load(j + 1, j + 1 < end);
+        if (!fine) return printf("decoding: %d keys, %d blocks per wave, wave %d\n", nk, per_wave, w), 1;
+      }
+      for (int r = 1; r < nk; r++)      // (row 0 stands in for the blocks that no wave has)
+        if (read[r] != 1) return printf("decoding: %d keys, %d blocks per wave: row %d read %d times\n", nk, per_wave, r, read[r]), 1;
+    }
+  return 0;
+}
+
 int main() {
   if (every_workgroup_has_its_own_work()) return 1;
+  if (decoding_reads_every_block_once()) return 1;
   long long copies = 0;
   for (int causal = 0; causal < 2; causal++)
     for (int nq = 1; nq <= 330; nq++)
