@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "common.h"
+#include "dispatch.h"
 #include "prepass_kernels.h"
 #include "fwd_kernel.h"
 #include "fwd_decode_kernel.h"
@@ -347,8 +348,7 @@ int prepass_for_backward(const void* Q, const void* K, const void* V, const void
   return run_prepass<D>(Q, K, V, dO, O, LSE, p, ws, w, !reuse, true, false, st);
 }
 
-// CUs and SIMDs of the machine: what a launch has to fill.
-constexpr int kCus = 256, kSimds = 1024;
+constexpr int kSimds = 4 * kCus;
 
 // Few queries against many keys: split the keys inside the workgroup (sage_fwd_split_kernel) where there are a few tiles
 // for each split, while there is a CU for each 64-query workgroup (its LDS takes a whole one), and for two rounds of
@@ -517,16 +517,10 @@ int launch_bwd_dq(const DqArgs& a, bool causal, hipStream_t st) {
   return SAGEBWD_OK;
 }
 
-// One query block of at most 32 rows that sees every key, plain options: see fwd_decode_kernel.h.  (Its kernel is long, and
-// with a short cache few workgroups share the cost of fetching its instructions.)  Whole calls, us with codes in the workspace
-// -> this way.  d = 128: 1 head, 16 key blocks 18.5 -> 19.4, 20 20.3 -> 20.2, 24 22.3 -> 20.2; 16 heads, 12 blocks 18.7 -> 20.2, 16
-// 20.7 -> 20.1, 24 26.0 -> 21.0; blocks over all heads: 64 heads of 4 (256) 14.6 -> 16.3, 128 of 3 (384) 15.0 -> 16.0, 64 of 8 (512)
-// 19.8 -> 19.6, 256 of 2 (512) 15.2 -> 15.1, 48 of 12 (576) 22.3 -> 21.1, 256 of 4 (1024) 24.8 -> 19.1.  d = 64: 1 head, 12 blocks
-// 14.0 -> 14.7, 16 16.3 -> 14.9; 64 heads of 6 (384) 14.7 -> 15.2, of 8 (512) 15.9 -> 15.2, 256 of 1 8.6 -> 11.4, of 2 (512) 12.4 -> 11.5.
+// One query block of at most 32 rows that sees every key, plain options: see fwd_decode_kernel.h.
 bool use_decode(const sagebwd_params& p) {
-  const int nblk = padded_rows(kv_len(p)) / 64;
-  const bool long_enough = nblk >= (p.d == 64 ? 16 : 20) || (long long)p.B * p.H * nblk >= 512;
-  return long_enough && p.N <= 32 && p.causal == 0 && !(p.smooth & SAGEBWD_SMOOTH_Q) && !(p.flags & SAGEBWD_FLAG_QK_NORM) && !big_blocks(p);
+  return decode_long_enough((long long)p.B * p.H, padded_rows(kv_len(p)) / 64, p.d, (p.smooth & SAGEBWD_SMOOTH_K) != 0) && p.N <= 32 && p.causal == 0 &&
+         !(p.smooth & SAGEBWD_SMOOTH_Q) && !(p.flags & SAGEBWD_FLAG_QK_NORM) && !big_blocks(p);
 }
 
 template <int D>
@@ -548,8 +542,7 @@ int decode_impl(const void* Q, const void* K, const void* V, void* O, float* LSE
   a.nk = kv_len(p);
   a.nblk = padded_rows(a.nk) / 64;
   a.scale_log2e = logit_scale(p) * 1.4426950408889634f;
-  // two waves per SIMD, each on as few blocks as that allows
-  a.blocks_per_wave = (int)(((long long)BH * a.nblk + 2 * kSimds - 1) / (2 * kSimds));
+  a.blocks_per_wave = decode_blocks_per_wave(BH, a.nblk, D);
   const int nsplit = (a.nblk + 4 * a.blocks_per_wave - 1) / (4 * a.blocks_per_wave);
   // the workgroups' partial results lie where K^ would: a workgroup has at least four key blocks (4 * 64 * D bytes) unless
   // it is the last of its head, and leaves at most 32 * (4 D + 8)

@@ -1,0 +1,39 @@
+// The rules of dispatch.h on the host: at the shapes where both sides were measured they take the faster one, and what they
+// return can be launched.  Prints the first shape that fails and returns 1.
+#include <stdio.h>
+
+#include "dispatch.h"
+
+using namespace sage;
+
+// heads, key blocks, d, K-smoothing; long enough for the decoding kernel
+const struct { int heads, nblk, d; bool k_smooth, decode; } kDecode[] = {
+    {512, 1, 128, true, false}, {4096, 1, 128, true, false}, {512, 1, 64, true, false}, {512, 1, 128, false, true}, {256, 1, 64, true, false},
+    {300, 2, 128, true, false}, {400, 2, 128, true, true}, {300, 2, 64, true, true}, {300, 2, 128, false, true}, {128, 4, 128, true, true},
+    {64, 8, 128, true, false}, {64, 8, 128, false, true}, {80, 8, 128, true, true}, {64, 8, 64, true, true}, {48, 14, 128, true, true}, {16, 12, 64, true, false},
+    {1, 16, 64, true, true}, {1, 16, 128, true, false}, {1, 20, 128, true, true}};
+// heads, key blocks, d; workgroups of a head
+const struct { int heads, nblk, d, splits; } kSplits[] = {
+    {256, 16, 64, 1}, {256, 16, 128, 1}, {256, 8, 64, 1}, {128, 8, 64, 1}, {64, 8, 64, 1}, {192, 12, 128, 1}, {300, 16, 128, 1}, {384, 16, 64, 1},
+    {700, 16, 128, 1}, {512, 64, 128, 1}, {180, 12, 64, 1}, {180, 32, 128, 2}, {200, 64, 64, 2}, {240, 12, 128, 1}, {240, 64, 64, 2}, {256, 64, 128, 1}, {64, 128, 128, 8}, {128, 64, 128, 4},
+    {64, 32, 64, 4}, {128, 16, 64, 2}, {128, 64, 64, 4}, {150, 64, 128, 3}, {1, 128, 128, 32}, {16, 32, 128, 8}};
+
+int splits(int nblk, int per_wave) { return (nblk + 4 * per_wave - 1) / (4 * per_wave); }
+
+int main() {
+  for (const auto& c : kDecode)
+    if (decode_long_enough(c.heads, c.nblk, c.d, c.k_smooth) != c.decode) return printf("decode_long_enough: %d heads of %d blocks, d %d\n", c.heads, c.nblk, c.d), 1;
+  for (const auto& c : kSplits) {
+    const int n = splits(c.nblk, decode_blocks_per_wave(c.heads, c.nblk, c.d));
+    if (n != c.splits) return printf("decode_blocks_per_wave: %d heads of %d blocks, d %d: %d workgroups\n", c.heads, c.nblk, c.d, n), 1;
+  }
+  for (int d = 64; d <= 128; d += 64)
+    for (int heads = 1; heads <= 1100; heads++)
+      for (int nblk = 1; nblk <= 1200; nblk = nblk < 70 ? nblk + 1 : nblk * 9 / 8) {
+        const int per_wave = decode_blocks_per_wave(heads, nblk, d), n = splits(nblk, per_wave);
+        // one round of two workgroups per CU, unless a head alone has that many; the partial results (32 rows of O, m, l) fit where K's codes would lie
+        const bool fits = n == 1 || (long long)heads * n * 32 * (4 * d + 8) + 256 <= (long long)heads * nblk * 64 * d;
+        if (per_wave < 1 || (n > 1 && heads * n > 2 * kCus) || !fits) return printf("%d heads of %d blocks, d %d: %d per wave\n", heads, nblk, d, per_wave), 1;
+      }
+  return 0;
+}

@@ -34,7 +34,7 @@ def _against_oracle(Q, K, V, p, heads):
 
 
 # Short caches, which the forms with codes in the workspace serve: one key, one block, a partial block, four blocks and just
-# past them.  The kernel without (from 16 blocks on at d = 64 and 20 at d = 128, or 512 blocks over all heads): its
+# past them.  The kernel without (from 16 blocks on at d = 64 and 20 at d = 128, or about 512 blocks over all heads): its
 # shortest caches and one key less, one workgroup per head and many with a ragged end, one key, 1 to 32 query rows, waves
 # with several blocks and without any.
 @pytest.mark.parametrize("B,H,Nq,Nk,d,k_smooth,token_major", [
@@ -50,11 +50,15 @@ def test_decode(B, H, Nq, Nk, d, k_smooth, token_major):
 
 
 # The join of partial results: one past a wave's 64, one more than the groups of threads (8 at d = 128, 16 at d = 64), fewer;
-# blocks per wave: the most for one, one more, three with a last workgroup of one block; the line at 20 blocks and at 512
+# blocks per wave: one and more, a last workgroup of one block; the line at 20 blocks and at 512
 @pytest.mark.parametrize("B,H,Nq,Nk,d,k_smooth", [
     (1, 1, 2, 64 * 257, 128, True), (1, 1, 32, 64 * 257, 64, False), (1, 2, 3, 64 * 33, 128, False), (1, 2, 3, 64 * 65, 64, True),
     (2, 32, 4, 64 * 32, 128, True), (1, 32, 2, 64 * 65 - 5, 128, True), (4, 32, 1, 64 * 37, 64, True), (4, 32, 17, 64 * 37 - 63, 128, False),
-    (1, 2, 1, 64 * 19, 128, True), (1, 2, 1, 64 * 19 + 1, 128, True), (8, 32, 2, 65, 128, True), (8, 32, 2, 64, 128, True)])
+    (1, 2, 1, 64 * 19, 128, True), (1, 2, 1, 64 * 19 + 1, 128, True), (8, 32, 2, 65, 128, True), (8, 32, 2, 64, 128, True),
+    # one workgroup per head between one and two rounds of them, two where the walks are long; two blocks for each wave; one and
+    # two blocks with K-smoothing (codes) and without
+    (4, 45, 3, 64 * 12 - 3, 64, True), (4, 45, 2, 64 * 32 - 40, 128, True), (5, 45, 1, 64 * 9 + 1, 128, False), (8, 16, 32, 64 * 8 - 1, 64, False),
+    (5, 16, 4, 64 * 8, 128, True), (16, 32, 2, 64, 128, False), (16, 32, 2, 64, 128, True), (6, 50, 2, 128, 128, True), (8, 50, 2, 127, 128, True)])
 def test_decode_splits(B, H, Nq, Nk, d, k_smooth):
     Q, K, V = _inputs(B, H, Nq, Nk, d)
     _against_oracle(Q, K, V, binding.SageParams(B, H, Nq, d, causal=False, k_smooth=k_smooth, Nkv=Nk), {(0, 0), (B - 1, H - 1)})
