@@ -48,4 +48,86 @@ inline int decode_blocks_per_wave(long long heads, int nblk, int d) {
   return d == 64 && blocks(1) <= 2 ? blocks(1) : blocks(2);
 }
 
+// ---- backward, d = 128: two KV blocks per workgroup (sage_bwd_kernel) or four (sage_bwd_wide_kernel) ----
+
+// CUs that take workgroups from a queue, one at a time each: when the last one is done, in the unit of the workgroups' times.
+class Queue {
+ public:
+  // `count` workgroups of `time` each, behind those already queued
+  void add(long long count, double time) {
+    total_ += count * time;
+    while (count > 0) {
+      const Level first = level_[0];              // the CUs that are free first
+      const long long n = count < first.cus ? count : first.cus;
+      if (n == first.cus) {
+        for (int k = 1; k < levels_; k++) level_[k - 1] = level_[k];
+        levels_--;
+      } else {
+        level_[0].cus -= n;
+      }
+      put(first.time + time, n);
+      count -= n;
+    }
+  }
+  // (a machine that runs dry speeds up: part of the estimate is the mean over the CUs)
+  double end() const { return 0.85 * level_[levels_ - 1].time + 0.15 * total_ / kCus; }
+
+ private:
+  struct Level {
+    double time;
+    long long cus;
+  };
+  void put(double time, long long cus) {
+    int k = levels_;
+    while (k > 0 && level_[k - 1].time > time) k--;
+    if (k > 0 && level_[k - 1].time == time) {
+      level_[k - 1].cus += cus;
+      return;
+    }
+    for (int m = levels_; m > k; m--) level_[m] = level_[m - 1];
+    level_[k] = {time, cus};
+    levels_++;
+  }
+  Level level_[kCus + 1] = {{0.0, kCus}};         // in order; every level has a CU
+  int levels_ = 1;
+  double total_ = 0.0;
+};
+
+// Both kernels run one workgroup per CU, heaviest first.  In units of an interval with two KV blocks, a workgroup with two takes its
+// walk and 5 for filling and draining, one with four 1.65 times its walk and 3; with at most half of its blocks there it takes 0.8 of
+// that (numbers fitted to 576 shapes: heads of 1 to 72 KV blocks, 400 to 3000 blocks in all, with the mask and without; the
+// choice then costs 0.1 % on average against the better side of each, at most 7 %).  Whole backward calls, us, two -> four.  Without
+// the mask: 32 heads of N = 1024 65.6 two (one round), 34 104 -> 85; 102 of 576 82.8 -> 92.5 (two rounds either way), 110 100.4 -> 97.2; 30 of 2112 206 -> 241, 16 of 4160 502 -> 470;
+// 520 of 64 38.1 -> 45.4, 140 of 256 51.5 -> 43.1, 170 of 320 62.5 -> 68.0.  With it: 34 of 2048 139.7 -> 143.8, 36 148.6 -> 145.6; 43 of 1344 92.3 -> 101.6, 60 121 -> 108; 20
+// of 3200 177 -> 202, 20 of 4096 284 -> 270; 520 of 64 40.4 -> 45.4, 216 of 192 45.0 -> 37.0.  Numerics blocks of 128 and Q-smoothing have the
+// same lines (34 of 2048, blocks of 64 x 128 140 -> 144, 128 x 64 179 -> 183, 128 x 128 180 -> 186; 36 151 -> 145, 189 -> 185, 191 -> 188).
+inline bool bwd_wide_is_faster(long long heads, int nblk, int nqblk, int shift_blocks, bool causal) {
+  // (one and two blocks leave half of the workgroup idle; one round of workgroups with two blocks each is never longer, nor a little more than
+  // one of short walks with the mask: 110 heads of 320 40.7 -> 42.8, 97 of 384 48.0 -> 46.5)
+  if (nblk <= 2 || heads * nblk <= (causal && nblk > 4 ? 9 * kCus / 4 : 2 * kCus)) return false;
+  // three: 272 heads 49.3 -> 55.6 with the mask, 300 without 59.7 -> 60.6, 480 79.6 -> 71.6, 520 88.2 -> 92.7, 573 99.1 -> 95.2
+  if (nblk == 3) return heads <= kCus || (heads - 1) % kCus >= 48;
+  const long long wgs = heads * ((nblk + 3) / 4);
+  if (wgs >= 4 * kCus) return true;
+  // walks of about one length: no mask, or few queries against many keys
+  const bool even = !causal || nblk >= 4 * nqblk;
+  // (long walks of all lengths: the longest one decides; 272 workgroups of N = 4096 188 -> 207, 304 270 -> 270, 320 225 -> 214)
+  if (!even && nblk > 64) return wgs > kCus * 6 / 5;
+  Queue two, four;
+  if (even) {
+    two.add(heads * (nblk / 2), nqblk + 5);
+    if (nblk % 2 != 0) two.add(heads, 0.8 * (nqblk + 5));
+    const int rest = nblk % 4;
+    four.add(heads * (nblk / 4 + (rest == 3)), 1.65 * (nqblk + 3));
+    if (rest == 1 || rest == 2) four.add(heads, 0.8 * 1.65 * (nqblk + 3));
+  } else {
+    auto walk = [&](int j) { return nqblk - (j > shift_blocks ? j - shift_blocks : 0); };
+    for (int j = 0; j < nblk; j += 2) two.add(heads, (nblk - j > 1 ? 1.0 : 0.8) * (walk(j) + 5));
+    for (int j = 0; j < nblk; j += 4) four.add(heads, (nblk - j > 2 ? 1.65 : 0.8 * 1.65) * (walk(j) + 3));
+  }
+  // (where both are near, the estimate is 2 % too good for two blocks with the mask, 35 heads of 2048 149 -> 146, 20 of 4096 284 -> 270, and 3 % for
+  // long walks without, 24 of 3776 528 -> 508, 16 of 4160 502 -> 470)
+  return four.end() < (!even ? 1.02 : nblk > 48 ? 1.03 : 1.0) * two.end();
+}
+
 }  // namespace sage

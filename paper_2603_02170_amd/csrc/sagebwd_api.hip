@@ -453,22 +453,9 @@ int launch_bwd_single(const BwdArgs& a, bool causal, bool qs, hipStream_t st) {
   return SAGEBWD_OK;
 }
 
-// Four KV blocks per workgroup (sage_bwd_wide_kernel; same bits): d = 128 (Q-smoothing with numerics blocks of 64), once the machine would be given
-// two rounds of workgroups with two blocks each.  An interval of it serves twice the blocks in 1.5 times the time, so a call that fits one
-// round of those loses.  Backward kernel, us with two KV blocks -> with four.  Walks of about one length (no mask, or at least four
-// times as many keys as queries): 512 blocks of N = 1024 47.0 -> 59.6, of 8192 285 -> 373, 528 of N = 512 50.9 -> 38.4, 544 of N = 2048 139 -> 106, 640 of
-// N = 8192 529 -> 385, 1536 of N = 4096 438 -> 438 (three rounds against two), 2048 602 -> 475; 512 x 4096 with the mask, 512 blocks 31.3
-// -> 38.5, 576 52.0 -> 38.0.  With the mask and walks of all lengths the longest one decides until there are more workgroups than
-// CUs: 192 of N = 896 41.8 -> 53.0, 224 of N = 1024 57.7 -> 60.5, 256 of N = 2048 91.5 -> 107, of 8192 329 -> 409; 264 of N = 1536 91.8 -> 86.7,
-// 288 of N = 2048 118 -> 111, 320 128 -> 112; 272 of N = 4096 188 -> 207, 288 208 -> 217, 320 225 -> 214 and of N = 8192 528 -> 393.  Up to
-// eight blocks a walk is mostly fill and drain: 576 blocks of N = 384 27.2 -> 29.0, 768 36.2 -> 30.4, of N = 512 39.9 -> 35.9, of N = 192 30.4 -> 21.9.
-// With Q-smoothing the lines are the same (whole backward: 64 heads of N = 8192 with the mask 3437 -> 2827, of 2048 272 -> 233, of 1024 without 128 -> 109).
+// Four KV blocks per workgroup (sage_bwd_wide_kernel; same bits): d = 128 (Q-smoothing with numerics blocks of 64).
 bool use_bwd_wide(const BwdArgs& a, int d, bool causal, bool qs, bool big) {
-  if (d != 128 || (qs && big)) return false;
-  const long long nblk = a.N / kBlock, blocks = a.BH * nblk;
-  if (!causal || a.N >= 4 * a.Nq) return blocks > 2 * kCus;
-  const long long wgs = a.BH * ((nblk + 3) / 4);
-  return wgs > (nblk <= 32 ? kCus : kCus * 6 / 5) || (nblk <= 8 && blocks >= 3 * kCus);
+  return d == 128 && !(qs && big) && bwd_wide_is_faster(a.BH, a.N / kBlock, a.Nq / kBlock, a.shift_blocks, causal);
 }
 template <bool QSMOOTH, int MODE, bool KV128 = false>
 int launch_bwd_wide(const BwdArgs& a, bool causal, hipStream_t st) {

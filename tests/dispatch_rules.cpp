@@ -18,6 +18,17 @@ const struct { int heads, nblk, d, splits; } kSplits[] = {
     {700, 16, 128, 1}, {512, 64, 128, 1}, {180, 12, 64, 1}, {180, 32, 128, 2}, {200, 64, 64, 2}, {240, 12, 128, 1}, {240, 64, 64, 2}, {256, 64, 128, 1}, {64, 128, 128, 8}, {128, 64, 128, 4},
     {64, 32, 64, 4}, {128, 16, 64, 2}, {128, 64, 64, 4}, {150, 64, 128, 3}, {1, 128, 128, 32}, {16, 32, 128, 8}};
 
+// square calls at d = 128: heads, KV blocks, mask; four KV blocks per workgroup measured faster (by 3 % and more on either side)
+const struct { int heads, nblk; bool causal, wide; } kBackward[] = {
+    {300, 1, true, false}, {520, 1, false, false}, {2048, 1, true, false}, {520, 2, false, false}, {216, 3, true, true}, {280, 3, true, false},
+    {480, 3, false, true}, {520, 3, false, false}, {140, 4, false, true}, {184, 4, true, true}, {200, 4, true, true}, {170, 5, false, false},
+    {130, 5, true, true}, {110, 5, true, false}, {17, 49, false, true}, {170, 6, false, false}, {130, 6, true, true}, {200, 6, false, true}, {102, 9, false, false}, {102, 9, true, true},
+    {86, 10, false, false}, {110, 10, false, true}, {73, 13, false, false}, {65, 13, true, false}, {80, 13, true, true}, {52, 17, true, false},
+    {62, 17, true, true}, {40, 18, false, true}, {52, 18, false, false}, {60, 18, false, true}, {43, 21, true, false}, {60, 21, true, true},
+    {43, 23, false, false}, {43, 23, true, false}, {40, 25, true, false}, {34, 32, true, false}, {64, 32, true, true}, {64, 32, false, true},
+    {30, 33, false, false}, {28, 33, false, true}, {28, 33, true, false}, {20, 50, true, false}, {17, 62, true, false}, {20, 64, true, true},
+    {32, 128, true, true}, {64, 128, false, true}};
+
 int splits(int nblk, int per_wave) { return (nblk + 4 * per_wave - 1) / (4 * per_wave); }
 
 int main() {
@@ -27,6 +38,8 @@ int main() {
     const int n = splits(c.nblk, decode_blocks_per_wave(c.heads, c.nblk, c.d));
     if (n != c.splits) return printf("decode_blocks_per_wave: %d heads of %d blocks, d %d: %d workgroups\n", c.heads, c.nblk, c.d, n), 1;
   }
+  for (const auto& c : kBackward)
+    if (bwd_wide_is_faster(c.heads, c.nblk, c.nblk, 0, c.causal) != c.wide) return printf("bwd_wide_is_faster: %d heads of %d blocks, mask %d\n", c.heads, c.nblk, c.causal), 1;
   for (int d = 64; d <= 128; d += 64)
     for (int heads = 1; heads <= 1100; heads++)
       for (int nblk = 1; nblk <= 1200; nblk = nblk < 70 ? nblk + 1 : nblk * 9 / 8) {
