@@ -93,10 +93,33 @@ class Queue {
   double total_ = 0.0;
 };
 
+// Walks of about one length: no mask, or few queries against many keys.
+inline bool even_walks(int nblk, int nqblk, bool causal) { return !causal || nblk >= 4 * nqblk; }
+
 // Both kernels run one workgroup per CU, heaviest first.  In units of an interval with two KV blocks, a workgroup with two takes its
 // walk and 5 for filling and draining, one with four 1.65 times its walk and 3; with at most half of its blocks there it takes 0.8 of
 // that (numbers fitted to 576 shapes: heads of 1 to 72 KV blocks, 400 to 3000 blocks in all, with the mask and without; the
-// choice then costs 0.1 % on average against the better side of each, at most 7 %).  Whole backward calls, us, two -> four.  Without
+// choice then costs 0.1 % on average against the better side of each, at most 7 %).
+struct BwdEstimate {
+  double two, four;
+};
+inline BwdEstimate bwd_estimate(long long heads, int nblk, int nqblk, int shift_blocks, bool causal) {
+  Queue two, four;
+  if (even_walks(nblk, nqblk, causal)) {
+    two.add(heads * (nblk / 2), nqblk + 5);
+    if (nblk % 2 != 0) two.add(heads, 0.8 * (nqblk + 5));
+    const int rest = nblk % 4;
+    four.add(heads * (nblk / 4 + (rest == 3)), 1.65 * (nqblk + 3));
+    if (rest == 1 || rest == 2) four.add(heads, 0.8 * 1.65 * (nqblk + 3));
+  } else {
+    auto walk = [&](int j) { return nqblk - (j > shift_blocks ? j - shift_blocks : 0); };
+    for (int j = 0; j < nblk; j += 2) two.add(heads, (nblk - j > 1 ? 1.0 : 0.8) * (walk(j) + 5));
+    for (int j = 0; j < nblk; j += 4) four.add(heads, (nblk - j > 2 ? 1.65 : 0.8 * 1.65) * (walk(j) + 3));
+  }
+  return {two.end(), four.end()};
+}
+
+// Four KV blocks per workgroup?  Whole backward calls, us, two -> four.  Without
 // the mask: 32 heads of N = 1024 65.6 two (one round), 34 104 -> 85; 102 of 576 82.8 -> 92.5 (two rounds either way), 110 100.4 -> 97.2; 30 of 2112 206 -> 241, 16 of 4160 502 -> 470;
 // 520 of 64 38.1 -> 45.4, 140 of 256 51.5 -> 43.1, 170 of 320 62.5 -> 68.0.  With it: 34 of 2048 139.7 -> 143.8, 36 148.6 -> 145.6; 43 of 1344 92.3 -> 101.6, 60 121 -> 108; 20
 // of 3200 177 -> 202, 20 of 4096 284 -> 270; 520 of 64 40.4 -> 45.4, 216 of 192 45.0 -> 37.0.  Numerics blocks of 128 and Q-smoothing have the
@@ -109,25 +132,37 @@ inline bool bwd_wide_is_faster(long long heads, int nblk, int nqblk, int shift_b
   if (nblk == 3) return heads <= kCus || (heads - 1) % kCus >= 48;
   const long long wgs = heads * ((nblk + 3) / 4);
   if (wgs >= 4 * kCus) return true;
-  // walks of about one length: no mask, or few queries against many keys
-  const bool even = !causal || nblk >= 4 * nqblk;
+  const bool even = even_walks(nblk, nqblk, causal);
   // (long walks of all lengths: the longest one decides; 272 workgroups of N = 4096 188 -> 207, 304 270 -> 270, 320 225 -> 214)
   if (!even && nblk > 64) return wgs > kCus * 6 / 5;
-  Queue two, four;
-  if (even) {
-    two.add(heads * (nblk / 2), nqblk + 5);
-    if (nblk % 2 != 0) two.add(heads, 0.8 * (nqblk + 5));
-    const int rest = nblk % 4;
-    four.add(heads * (nblk / 4 + (rest == 3)), 1.65 * (nqblk + 3));
-    if (rest == 1 || rest == 2) four.add(heads, 0.8 * 1.65 * (nqblk + 3));
-  } else {
-    auto walk = [&](int j) { return nqblk - (j > shift_blocks ? j - shift_blocks : 0); };
-    for (int j = 0; j < nblk; j += 2) two.add(heads, (nblk - j > 1 ? 1.0 : 0.8) * (walk(j) + 5));
-    for (int j = 0; j < nblk; j += 4) four.add(heads, (nblk - j > 2 ? 1.65 : 0.8 * 1.65) * (walk(j) + 3));
-  }
+  const BwdEstimate t = bwd_estimate(heads, nblk, nqblk, shift_blocks, causal);
   // (where both are near, the estimate is 2 % too good for two blocks with the mask, 35 heads of 2048 149 -> 146, 20 of 4096 284 -> 270, and 3 % for
   // long walks without, 24 of 3776 528 -> 508, 16 of 4160 502 -> 470)
-  return four.end() < (!even ? 1.02 : nblk > 48 ? 1.03 : 1.0) * two.end();
+  return t.four < (!even ? 1.02 : nblk > 48 ? 1.03 : 1.0) * t.two;
+}
+
+// Heads of the next group of a backward whose psi(dS) does not fit the scratch at once: `most` do, `left` are left.  Where all
+// workgroups run for about the same time a group takes whole rounds of them, so the size is the one with the shortest estimate in all,
+// the largest of those (32 heads of N = 32768 without the mask: 7 heads fill three and a half rounds of workgroups with four KV blocks and take 7.11 ms,
+// 6 take 5.54; the training step 6 % faster).  Beyond 32 rounds a part of one is 3 %.  `wide`: the call may take that form.
+inline int bwd_heads_of_group(int most, int left, int nblk, int nqblk, int shift_blocks, bool causal, bool wide) {
+  if (left <= most) return left;
+  if (!wide || !even_walks(nblk, nqblk, causal) || (long long)most * ((nblk + 3) / 4) > 32 * kCus) return most;
+  auto time = [&](int heads) {
+    if (heads == 0) return 0.0;
+    const BwdEstimate t = bwd_estimate(heads, nblk, nqblk, shift_blocks, causal);
+    return bwd_wide_is_faster(heads, nblk, nqblk, shift_blocks, causal) ? t.four : t.two;
+  };
+  int best = most;
+  double least = 0.0;
+  for (int h = most; h > most / 2 && h >= 1; h--) {
+    const double t = left / h * time(h) + time(left % h);
+    if (h == most || t < 0.99 * least) {
+      least = t;
+      best = h;
+    }
+  }
+  return best;
 }
 
 }  // namespace sage

@@ -473,25 +473,6 @@ int launch_bwd_wide(const BwdArgs& a, bool causal, hipStream_t st) {
   return SAGEBWD_OK;
 }
 
-// Heads of the next group of a backward whose psi(dS) does not fit the scratch at once: `most` do, `left` are left.  Where all
-// workgroups run for about the same time a group takes whole rounds of them, so the size is the one that takes the fewest in all,
-// the largest of those (32 heads of N = 32768, four KV blocks per workgroup, no mask: 7 heads fill three and a half rounds and take 7.11 ms,
-// 6 take 5.54; the training step 6 % faster).
-int heads_of_group(int most, int left, int wgs_per_head) {
-  if (left <= most) return left;
-  auto rounds = [&](int heads) { return ((long long)heads * wgs_per_head + kCus - 1) / kCus; };
-  int best = most;
-  long long least = 0;
-  for (int h = most; h > most / 2 && h >= 1; h--) {
-    const long long r = left / h * rounds(h) + rounds(left % h);
-    if (least == 0 || r < least) {
-      least = r;
-      best = h;
-    }
-  }
-  return best;
-}
-
 template <int D>
 int launch_bwd_dq(const DqArgs& a, bool causal, hipStream_t st) {
   const int npair = (a.Nq / 64 + 1) / 2;    // one workgroup per pair of Q blocks
@@ -835,9 +816,9 @@ int sagebwd_bwd(const void* Q, const void* K, const void* V, const void* O, cons
   q.Nq = Nqp;
   q.shift_blocks = shift_blocks;
   q.sm_scale = a.sm_scale;
-  const bool even_walks = params->causal == 0 && d == 128 && !(qs && big);     // (the workgroups of sage_bwd_wide_kernel)
+  const bool wide_form = d == 128 && !(qs && big);
   for (int h0 = 0, nh = 0; h0 < BH; h0 += nh) {
-    nh = even_walks ? heads_of_group(w.heads_per_group, BH - h0, (Nkp / 64 + 3) / 4) : BH - h0 < w.heads_per_group ? BH - h0 : w.heads_per_group;
+    nh = bwd_heads_of_group(w.heads_per_group, BH - h0, Nkp / 64, Nqp / 64, shift_blocks, params->causal != 0, wide_form);
     a.bh0 = q.bh0 = h0;
     a.BH = q.BH = nh;
     {

@@ -40,6 +40,19 @@ int main() {
   }
   for (const auto& c : kBackward)
     if (bwd_wide_is_faster(c.heads, c.nblk, c.nblk, 0, c.causal) != c.wide) return printf("bwd_wide_is_faster: %d heads of %d blocks, mask %d\n", c.heads, c.nblk, c.causal), 1;
+  // groups of heads: whole rounds where the walks are even (no mask, or few queries against many keys) and the workgroups have four
+  // blocks; else all that fit
+  if (bwd_heads_of_group(7, 32, 512, 512, 0, false, true) != 6 || bwd_heads_of_group(9, 16, 128, 128, 0, false, true) != 8 ||
+      bwd_heads_of_group(9, 16, 512, 64, 448, true, true) != 8 || bwd_heads_of_group(9, 16, 128, 128, 0, true, true) != 9 ||
+      bwd_heads_of_group(9, 16, 128, 128, 0, false, false) != 9 || bwd_heads_of_group(4, 9, 128, 128, 0, false, true) != 4 ||
+      bwd_heads_of_group(9, 7, 128, 128, 0, false, true) != 7)
+    return printf("bwd_heads_of_group\n"), 1;
+  for (int nblk = 1; nblk <= 600; nblk = nblk * 5 / 4 + 1)
+    for (int most = 1; most <= 70; most++)
+      for (int left = 1; left <= 150; left += 7) {
+        const int h = bwd_heads_of_group(most, left, nblk, nblk, 0, false, true);
+        if (h < 1 || h > most || h > left || (left > most && h <= most / 2)) return printf("bwd_heads_of_group: %d of %d, %d blocks: %d\n", most, left, nblk, h), 1;
+      }
   for (int d = 64; d <= 128; d += 64)
     for (int heads = 1; heads <= 1100; heads++)
       for (int nblk = 1; nblk <= 1200; nblk = nblk < 70 ? nblk + 1 : nblk * 9 / 8) {
