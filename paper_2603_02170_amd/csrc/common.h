@@ -172,8 +172,11 @@ struct WorkItem {
 };
 // > 0: that many heads of an XCD per set; < 0: the dense layout, sets of that many heads (on a machine of one XCD, so to
 // speak, so that the mapping below stays one formula).  A set divides the heads evenly; where four do not divide an XCD's heads,
-// short sequences take the next larger number that does, or all of them (five heads one at a time left the last head's heaviest items to the end:
-// calls with the mask, forward and backward in us, 40 heads of N = 1024 43 + 90 -> 39 + 65, of 2048 84 + 196 -> 73 + 167, 56 of 4096 276 + 808 -> 258 + 764).
+// short sequences take the largest number up to eight that does (five heads one at a time left the last head's heaviest items to the end:
+// calls with the mask, forward and backward in us, 40 heads of N = 1024 43 + 90 -> 39 + 65, of 2048 84 + 196 -> 73 + 167, 56 of 4096 276 + 808 -> 258 + 764;
+// nine heads have sets of three).  Where that is one or two, all of them, up to 31 heads and 768 items: 152 heads (19) of N = 512 55 + 100 -> 48 + 70, 248
+// (31) of 1024 163 + 381 -> 154 + 287; larger sets crowd the L2 (34 heads in sets of two -> all: N = 1024 164 + 323 -> 170 + 317, 2048 403 + 945 -> 421 + 980; 37 one at a
+// time -> all: 1024 190 + 407 -> 188 + 341, 2048 451 + 1084 -> 458 + 1064; 31 of 32 items, d = 64 and N = 2048, backward 667 -> 686).
 __host__ __device__ inline int head_set_for(int items, int heads, bool always = false) {
   const bool dense = heads % 8 != 0;
   const int pool = dense ? heads : heads / 8;
@@ -181,7 +184,7 @@ __host__ __device__ inline int head_set_for(int items, int heads, bool always = 
   if (items <= 32 && pool % hs != 0 && pool > hs) {
     hs = 8;
     while (pool % hs != 0) hs--;
-    if (hs < 3 && pool < 32) hs = pool;
+    if (hs < 3 && pool < 32 && pool * items <= 768) hs = pool;
   }
   while (pool % hs != 0) hs--;
   return dense ? -hs : hs;

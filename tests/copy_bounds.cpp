@@ -9,6 +9,10 @@
 #include "bwd_kernel.h"
 
 int every_workgroup_has_its_own_work() {
+  // sets of the heads of an XCD: four, the largest divisor up to eight, all of a few short ones
+  const int sets[][3] = {{4, 64, 4}, {4, 40, 5}, {4, 72, 3}, {16, 152, 19}, {16, 248, 31}, {32, 248, 1}, {4, 272, 2}, {4, 296, 1}, {33, 40, 1}};
+  for (const auto& c : sets)
+    if (sage::head_set_for(c[0], c[1]) != c[2]) return printf("items %d heads %d: set %d\n", c[0], c[1], sage::head_set_for(c[0], c[1])), 1;
   for (int heads = 1; heads <= 272; heads++)
     for (int items = 1; items <= 68; items++)
       for (int always = 0; always < 2; always++) {
