@@ -763,13 +763,15 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_single_kernel(BwdArgs args) {
     };
     auto read_A = [&](const int t) __attribute__((always_inline)) {
       const BwdStageA1<D>& st = L.stA[t % 3];
-      // (with Q-smoothing a CU holds one of these workgroups whatever the registers: -delta is read ahead as well, 3 % at d = 64)
-      if constexpr (QSMOOTH) read_delta(t);
+      // (with Q-smoothing a CU holds one of these workgroups whatever the registers: -delta is read ahead as well, 3 %; at d = 64 behind the
+      // operands, which the first products wait for: 16 heads of N = 2048 69.1 -> 68.4 us, 4 of 4096 107.3 -> 106.1, d = 128 78.0 -> 79.6)
+      if constexpr (QSMOOTH && D == 128) read_delta(t);
 #pragma unroll
       for (int s = 0; s < KB; s++) {
         if (s % 2 == 0) qa[s / 2] = *(const v4i*)(st.qf + ((qb * KS + s / 2) * 64 + lane) * 16);
         da[s] = *(const v8bf*)(st.dof + ((qb * KB + s) * 64 + (lane ^ (s & 7))) * 16);
       }
+      if constexpr (QSMOOTH && D == 64) read_delta(t);
     };
     auto phase_Q = [&](const int t) __attribute__((always_inline)) {   // tile t
       BwdExchange& X = L.xch[t & 1];
