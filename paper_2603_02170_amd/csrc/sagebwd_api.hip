@@ -379,23 +379,38 @@ int launch_fwd_small(const FwdArgs& a, bool split, hipStream_t st) {
   return SAGEBWD_OK;
 }
 
+// One Q block, or three under the mask: half or a quarter of the waves of such workgroups would have no queries.  Workgroups of two waves
+// then, at d = 64 (five fit a CU beside their rings, three of four waves; at d = 128 two of either) and once they are more than one round.
+// Whole calls, us, four waves -> two: 800 heads of N = 64 18.3 -> 16.1, 1100 22.7 -> 23.1, 1600 30.6 -> 28.8, 4096 60.4 -> 57.1; 300 heads of N = 192 with the mask
+// 22.7 -> 22.0, 350 24.8 -> 25.3, 400 29.2 -> 27.3, 2048 90.0 -> 85.5; blocks of 128 keys 4096 of 64 66.5 -> 63.1, 2048 of 192 94.6 -> 91.6.  Not with five blocks (1000
+// of N = 320 76.2 -> 78.4), more keys (2048 of 64 x 256 80.6 -> 81.3, 1300 55.3 -> 57.3) or Q-smoothing (2048 of 64 48.5 -> 50.0).
+bool use_fwd_two_waves(const FwdArgs& a, bool causal) {
+  return a.N == a.Nq && (a.Nq == 64 || (causal && a.Nq == 192)) && (long long)a.BH * ((a.Nq + 127) / 128) > 3 * kCus;
+}
+
 // Full machines: workgroups of four waves (32 queries each), two (d = 128) or three (d = 64) per CU: the waves that share a SIMD
 // then belong to different workgroups and do not wait at each other's barriers (measured 7 % faster than one 8-wave workgroup per
 // CU, although that stages every K^/V^ tile once for twice as many queries).  kv128: numerics blocks of 128 keys (the per-token
 // quantiser of P~ takes its row max over two tiles).
-constexpr int kFwdWaves = 4;
+template <int D, bool CAUSAL, bool QS, int NW>
+int launch_fwd_full(const FwdArgs& a, bool kv128, hipStream_t st) {
+  FwdArgs args = a;
+  args.n_qtiles = (a.Nq + 32 * NW - 1) / (32 * NW);
+  args.head_set = head_set_for(args.n_qtiles, a.BH);
+  const int grid = grid_for(a.BH, args.n_qtiles);
+  if (kv128) sage_fwd_kernel<D, CAUSAL, QS, NW, true><<<grid, 64 * NW, 0, st>>>(args);
+  else sage_fwd_kernel<D, CAUSAL, QS, NW><<<grid, 64 * NW, 0, st>>>(args);
+  SAGE_LAUNCH_CHECK();
+  return SAGEBWD_OK;
+}
 template <int D, bool CAUSAL, bool QS>
 int launch_fwd_form(const FwdArgs& a, bool kv128, hipStream_t st) {
   if (!kv128 && use_fwd_split(a)) return launch_fwd_small<D, CAUSAL, QS>(a, true, st);
   if (!kv128 && use_fwd_pair(a)) return launch_fwd_small<D, CAUSAL, QS>(a, false, st);
-  FwdArgs args = a;
-  args.n_qtiles = (a.Nq + 32 * kFwdWaves - 1) / (32 * kFwdWaves);
-  args.head_set = head_set_for(args.n_qtiles, a.BH);
-  const int grid = grid_for(a.BH, args.n_qtiles);
-  if (kv128) sage_fwd_kernel<D, CAUSAL, QS, kFwdWaves, true><<<grid, 64 * kFwdWaves, 0, st>>>(args);
-  else sage_fwd_kernel<D, CAUSAL, QS, kFwdWaves><<<grid, 64 * kFwdWaves, 0, st>>>(args);
-  SAGE_LAUNCH_CHECK();
-  return SAGEBWD_OK;
+  if constexpr (D == 64 && !QS) {
+    if (use_fwd_two_waves(a, CAUSAL)) return launch_fwd_full<D, CAUSAL, QS, 2>(a, kv128, st);
+  }
+  return launch_fwd_full<D, CAUSAL, QS, 4>(a, kv128, st);
 }
 
 template <int D>

@@ -25,3 +25,18 @@ def test_every_row_has_the_bits_of_a_call_on_a_head_alone(Nq, Nk, d, causal, q_s
         o, l = binding.sagebwd_fwd(*(t[:, sl].contiguous() for t in (Q, K, V)), p1)
         torch.cuda.synchronize()
         assert torch.isfinite(o.float()).all() and torch.equal(O[:, sl], o) and torch.equal(L[:, sl], l), h
+
+
+# one Q block and three at d = 64 with so many heads that workgroups of two waves serve them, one head fewer and more, a partial block
+@pytest.mark.parametrize("heads,N,causal,bkv", [(769, 64, True, 0), (768, 64, True, 0), (800, 33, False, 0), (800, 64, False, 128), (385, 192, True, 0),
+                                                (384, 192, True, 0), (400, 150, True, 0), (400, 192, True, 128), (400, 192, False, 0)])
+def test_short_heads_have_the_bits_of_a_call_on_a_head_alone(heads, N, causal, bkv):
+    g = torch.Generator(device="cuda").manual_seed(heads + N)
+    Q, K, V = (torch.randn((1, heads, N, 64), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    O, L = torch.full_like(Q, float("nan")), torch.full((1, heads, N), float("nan"), device="cuda")
+    binding.sagebwd_fwd(Q, K, V, binding.SageParams(1, heads, N, 64, causal=causal, bkv=bkv), None, O, L)
+    for h in (0, heads // 2, heads - 1):
+        sl = slice(h, h + 1)
+        o, l = binding.sagebwd_fwd(*(t[:, sl].contiguous() for t in (Q, K, V)), binding.SageParams(1, 1, N, 64, causal=causal, bkv=bkv))
+        torch.cuda.synchronize()
+        assert torch.isfinite(o.float()).all() and torch.equal(O[:, sl], o) and torch.equal(L[:, sl], l), h
