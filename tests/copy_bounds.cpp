@@ -1,4 +1,5 @@
-// Every row of dO and every Q block that the staging copies of sage_bwd_single_kernel read, over all small shapes, the rows that a decoding step reads, and the
+// Every row of dO and every Q block that the staging copies of sage_bwd_single_kernel and sage_bwd_wide_kernel read, over all small
+// shapes, the rows that a decoding step reads, and the
 // (head, item) of every workgroup, from the index functions the kernels themselves use.  Prints the first access that lies
 // outside the tensor, or the first workgroup without a (head, item) of its own, and returns 1.
 #include <stdio.h>
@@ -70,28 +71,34 @@ int main() {
       for (int nk = 1; nk <= 330; nk++) {
         if (causal && (nk < nq || (nk - nq) % 64 != 0)) continue;
         const int nqblk = (nq + 63) / 64, nkblk = (nk + 63) / 64, sb = causal ? (nk - nq) / 64 : 0;
-        for (int j = 0; j < nkblk; j++) {
-          const int first = causal ? (j - sb > 0 ? j - sb : 0) : 0;
-          const sage::SingleWalk walk(nqblk, first);
-          auto bad = [&](const char* what, int t, int row) {
-            printf("%s: Nq %d Nk %d causal %d KV block %d interval %d row %d\n", what, nq, nk, causal, j, t, row);
-            return 1;
-          };
-          if (walk.T < 1 || walk.at(0) != nqblk - 1 || walk.at(walk.T - 1) != first) return bad("walk", 0, 0);
-          for (int t = 0; t < 2; t++)                   // before the loop: tiles 0 and 1, rows clamped one by one
-            for (int r = 0; r < 64; r++, copies++) {
-              const int want = 64 * walk.at(t) + r, row = sage::dO_row_clamped(want, nq);
-              if (row < 0 || row >= nq || (want < nq && row != want)) return bad("first copies", t, row);
-            }
-          for (int t = 0; t < walk.T + 2; t++) {        // interval t: phase A of tile t + 2, phase B of tile t
-            if (walk.at(t) < 0 || walk.at(t) >= nqblk || (t < walk.T && walk.at(t) != nqblk - 1 - t)) return bad("phase B", t, 64 * walk.at(t));
-            for (int r = 0; r < 64; r++, copies++) {
-              const int row = 64 * walk.at(t + 2) + r * walk.loop_row_step();
-              if (row < 0 || row >= nq) return bad("phase A", t, row);
-              if (t + 2 < walk.T && row != 64 * (nqblk - 1 - t - 2) + r) return bad("phase A of a tile that is used", t, row);
+        // ahead: tiles copied before the loop, row by row clamped; interval t copies dO of tile t + ahead and the operands of phase B
+        // of tile t (one KV block per workgroup: T + 2 intervals, two tiles ahead; four: T + 1 and one)
+        for (int blocks = 1; blocks <= 4; blocks += 3)
+          for (int j = 0; j < nkblk; j += blocks) {
+            const int ahead = blocks == 1 ? 2 : 1;
+            const int first = causal ? (j - sb > 0 ? j - sb : 0) : 0;
+            const sage::SingleWalk walk(nqblk, first);
+            auto bad = [&](const char* what, int t, int row) {
+              printf("%s: Nq %d Nk %d causal %d KV block %d (%d per workgroup) interval %d row %d\n", what, nq, nk, causal, j, blocks, t, row);
+              return 1;
+            };
+            if (walk.T < 1 || walk.at(0) != nqblk - 1 || walk.at(walk.T - 1) != first) return bad("walk", 0, 0);
+            // (the workgroup's other blocks see no Q block below its first one)
+            if (causal && j + blocks - 1 < nkblk && first > (j + blocks - 1 - sb > 0 ? j + blocks - 1 - sb : 0)) return bad("first Q block", 0, 0);
+            for (int t = 0; t < ahead; t++)
+              for (int r = 0; r < 64; r++, copies++) {
+                const int want = 64 * walk.at(t) + r, row = sage::dO_row_clamped(want, nq);
+                if (row < 0 || row >= nq || (want < nq && row != want)) return bad("first copies", t, row);
+              }
+            for (int t = 0; t < walk.T + ahead; t++) {
+              if (walk.at(t) < 0 || walk.at(t) >= nqblk || (t < walk.T && walk.at(t) != nqblk - 1 - t)) return bad("phase B", t, 64 * walk.at(t));
+              for (int r = 0; r < 64; r++, copies++) {
+                const int row = 64 * walk.at(t + ahead) + r * walk.loop_row_step();
+                if (row < 0 || row >= nq) return bad("phase A", t, row);
+                if (t + ahead < walk.T && row != 64 * (nqblk - 1 - t - ahead) + r) return bad("phase A of a tile that is used", t, row);
+              }
             }
           }
-        }
       }
   printf("%lld rows\n", copies);
   return 0;

@@ -1,4 +1,4 @@
-"""The staging copies of the backward with one KV block per workgroup stay inside the caller's tensors, for every small
+"""The staging copies of the backward with one KV block per workgroup and with four stay inside the caller's tensors, for every small
 (N_q, N_kv) with and without the mask, and every workgroup of a launch has one (head, item) of its own: the kernels' own
 index functions, run on the host (no GPU needed)."""
 import os
