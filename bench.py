@@ -198,7 +198,9 @@ def main():
     # the backward kernel (sage_bwd_wide_kernel at the headline shape) runs four of the five backward matmuls (S recompute, dV, dP, dK); the fifth (dQ)
     # runs in sage_bwd_dq_kernel from the staged psi(dS) tiles
     bwd_ops = work_ops(w, matmuls=4)
-    bwd_kernel = "sage_bwd_wide_kernel" if w.d == 128 and w.N >= 1024 else "backward kernel (by shape)"
+    # (four rounds of its workgroups and more always take that kernel; below, the rule on sizes decides)
+    wide = w.d == 128 and w.B * w.H * -(-w.N // 256) >= 1024
+    bwd_kernel = "sage_bwd_wide_kernel" if wide else "backward kernel (by shape)"
     fwd_ops = work_ops(w, bwd=False)
     bwd_tops = bwd_ops / (kern["bwd"] * 1e-3) / 1e12
     fwd_tops = fwd_ops / (kern["fwd"] * 1e-3) / 1e12
