@@ -65,3 +65,18 @@ def test_groups_of_heads_without_the_mask(heads, N, fit):
     torch.cuda.synchronize()
     for a, b in zip(whole, parts):
         assert torch.equal(a, b)
+
+
+def test_gradients_into_tensors_that_are_not_16_byte_aligned():
+    """dK and dV leave in 16-byte pieces; a caller's tensors need not start at such an address."""
+    heads, N, d = 140, 256, 128
+    g = torch.Generator(device="cuda").manual_seed(5)
+    Q, K, V, dO = (torch.randn((1, heads, N, d), generator=g, device="cuda").to(torch.bfloat16) for _ in range(4))
+    p = binding.SageParams(1, heads, N, d, causal=False)
+    O, L = binding.sagebwd_fwd(Q, K, V, p)
+    want = binding.sagebwd_bwd(Q, K, V, O, dO, L, p)
+    shifted = [torch.empty(Q.numel() + 4, dtype=torch.bfloat16, device="cuda")[4:].view(Q.shape) for _ in range(3)]
+    got = binding.sagebwd_bwd(Q, K, V, O, dO, L, p, None, *shifted)
+    torch.cuda.synchronize()
+    for a, b, s in zip(got, want, shifted):
+        assert a.data_ptr() == s.data_ptr() and a.data_ptr() % 16 == 8 and torch.equal(a, b)
