@@ -7,16 +7,17 @@ from paper_2603_02170_amd import binding, synth
 pytestmark = pytest.mark.gpu
 
 
-# one to five KV blocks (workgroups with idle waves), one Q block and more, whole and partial last blocks of either side, the mask
+# three to ten KV blocks (workgroups with idle waves; also one and two, which the form with two blocks serves), one Q block and more, whole and partial last blocks of either side, the mask
 # with and without a shift (the diagonal of the four blocks lies in different intervals), numerics blocks of 128 in either direction
 # (pairs of blocks of which one does not exist, is not visible, or lies in the next workgroup; odd and even Q block counts)
 # and Q-smoothing (the bias of every block's keys, the sums for the bias branch of dK)
 @pytest.mark.parametrize("bq,bkv,q_smooth", [(0, 0, False), (0, 0, True), (64, 128, False), (128, 64, False), (128, 128, False)])
 @pytest.mark.parametrize("Nq,Nk,causal", [(64, 64, True), (1, 100, False), (50, 600, False), (100, 228, True), (256, 256, True), (300, 300, True),
-                                          (640, 640, True), (200, 321, False), (448, 70, False), (64, 512, True), (130, 450, True)])
+                                          (640, 640, True), (200, 321, False), (448, 70, False), (64, 512, True), (130, 450, True),
+                                          (192, 192, True), (1, 170, False), (64, 192, False), (448, 140, False)])
 def test_four_kv_blocks_per_workgroup_give_the_same_bits(Nq, Nk, causal, bq, bkv, q_smooth):
     d, nblk = 128, -(-Nk // 64)
-    heads = 1024 // nblk + 9            # more than 256 workgroups of four blocks and 768 blocks in all
+    heads = 1024 // nblk + 9            # enough for four blocks per workgroup from three KV blocks on (bwd_wide_is_faster)
     g = torch.Generator(device="cuda").manual_seed(1000 * Nq + Nk)
     rand = lambda n, s: (torch.randn((1, heads, n, d), generator=g, device="cuda") * s).to(torch.bfloat16)
     Q, K, V, dO = rand(Nq, 1.5), rand(Nk, 1.5), rand(Nk, 1.0), rand(Nq, 1.0)
