@@ -1058,7 +1058,6 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_wide_kernel(BwdArgs args) {
     async_copy_4(((wave & 1) ? args.delta : args.nL2) + (size_t)bh * args.Nq + 64 * itop + lane, (wave & 1) ? st.dl : st.nl2);
     if constexpr (QSMOOTH) {
       async_copy_4(args.bias + ((size_t)bh * nqblk + itop) * N + 64 * jc + lane, L.bias[0][wave >> 1]);
-      if (tid < D) L.muq[1][tid] = 0.f;     // (interval 0 multiplies it by sums of zero)
     }
   }
 
@@ -1078,13 +1077,16 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_wide_kernel(BwdArgs args) {
   float sq1 = 0.f, sd1 = 0.f;                                             // ... of tile t - 1
   barrier_all_memory();
 
-  // Interval t: psi, dV, dK of tile t - 1; S, dP, P, dS of tile t; copies of phase A's operands of tile t + 1 and of phase B's of
-  // tile t (past the last tile that one again, never used).  One barrier at its end.
-  auto interval = [&](const int t, auto mask_tag) __attribute__((always_inline)) {
+  // Interval t: psi, dV, dK of tile t - 1 (HAS_Q: not in interval 0); S, dP, P, dS of tile t and copies of phase A's operands of tile
+  // t + 1 (past the last tile that one again, never used) and of phase B's of tile t (HAS_A: not in interval T).  One barrier at its end.
+  auto interval = [&](const int t, auto mask_tag, auto q_tag, auto a_tag) __attribute__((always_inline)) {
     constexpr bool MASK = decltype(mask_tag)::value;
+    constexpr bool HAS_Q = decltype(q_tag)::value, HAS_A = decltype(a_tag)::value;
     const int iq = itop - (t - 1), ia = itop - t;
-    const bool act_q = !MASK || (t >= 1 && valid && (!CAUSAL || iq + sb >= j));
-    const bool act_a = !MASK || (t < T && valid && (!CAUSAL || ia + sb >= j));
+    // (the wave's tiles are the first ones of the walk; the comparisons with t hold wherever they are made: without them the compiler makes
+    // two loops of it, for waves with a block and without, and has no registers for them)
+    const bool act_q = HAS_Q && (!MASK || (t >= 1 && valid && (!CAUSAL || iq + sb >= j)));
+    const bool act_a = HAS_A && (!MASK || (t < T && valid && (!CAUSAL || ia + sb >= j)));
     // (opaque: their extension to 64 bits and what is derived from the lane are formed here and not kept in registers)
     asm volatile("" : "+v"(lane16), "+v"(dO_lane));
     const int ll = (lane16 >> 4) & 31, h = lane16 >> 9;
@@ -1129,64 +1131,66 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_wide_kernel(BwdArgs args) {
     __builtin_amdgcn_sched_barrier(0);
     if (!MASK || act_a || act_q) {
       // ---------------- psi of tile t - 1 ----------------
-      pu = max(pu, (unsigned)own_p);
-      du = max(du, (unsigned)own_d);
-      if constexpr (MODE == kBwdPairedRows) {
-        // the other Q block of the numerics block: below (iq odd: the stored maxima of tile (iq - 1, j), and of its neighbour
-        // in the 128-key block, where those tiles exist) or above (iq even: the last interval's)
-        const unsigned bp = pu, bd = du;
-        if (iq & 1) {
-          const int jm = KV128 ? (jc & ~1) : jc;
-          const float* tm = args.tmax + 2 * (((size_t)hl * nqblk + iq - 1) * args.ds_pitch + jm);
-          if (!CAUSAL || jm <= iq - 1 + sb) {
-            pu = max(pu, __float_as_uint(scalar_load(tm)));
-            du = max(du, __float_as_uint(scalar_load(tm + 1)));
-          }
-          if (KV128 && jm + 1 < nblk && (!CAUSAL || jm + 1 <= iq - 1 + sb)) {
-            pu = max(pu, __float_as_uint(scalar_load(tm + 2)));
-            du = max(du, __float_as_uint(scalar_load(tm + 3)));
-          }
-        } else if (iq + 1 < nqblk) {
-          pu = max(pu, (unsigned)prev_p);
-          du = max(du, (unsigned)prev_d);
-        }
-        prev_p = __builtin_amdgcn_readfirstlane((int)bp);
-        prev_d = __builtin_amdgcn_readfirstlane((int)bd);
-      }
-      if (MASK && !act_q) pu = du = 0u;       // (the first interval: no tile, nothing written to those maxima yet)
-      const float bpm = __uint_as_float(pu), bdm = __uint_as_float(du);
-      // the per-tile scales of P and dS are internal (never stored bit-exactly): 127/a via rcp
-      const float rP = bpm > 0.f ? 127.0f * __builtin_amdgcn_rcpf(bpm) : 0.f;
-      const float rS = bdm > 0.f ? 127.0f * __builtin_amdgcn_rcpf(bdm) : 0.f;
-      const float sP = bpm * (1.0f / 127.0f), sS = bdm * (1.0f / 127.0f);
       v4i pf[2], df[2];            // [q half]: B operands of dV, dK, one key per lane
-#pragma unroll
-      for (int qh = 0; qh < 2; qh++)
-#pragma unroll
-        for (int aa = 0; aa < 4; aa++) {
-          unsigned up = 0;
-#pragma unroll
-          for (int b = 0; b < 4; b++) up = __builtin_amdgcn_cvt_pk_u8_f32(p[qh][4 * aa + b] * rP, b, up);
-          pf[qh][aa] = (int)up;
+      float w_dv = 0.f, w_dk = 0.f;
+      if constexpr (HAS_Q) {
+        pu = max(pu, (unsigned)own_p);
+        du = max(du, (unsigned)own_d);
+        if constexpr (MODE == kBwdPairedRows) {
+          // the other Q block of the numerics block: below (iq odd: the stored maxima of tile (iq - 1, j), and of its neighbour
+          // in the 128-key block, where those tiles exist) or above (iq even: the last interval's)
+          const unsigned bp = pu, bd = du;
+          if (iq & 1) {
+            const int jm = KV128 ? (jc & ~1) : jc;
+            const float* tm = args.tmax + 2 * (((size_t)hl * nqblk + iq - 1) * args.ds_pitch + jm);
+            if (!CAUSAL || jm <= iq - 1 + sb) {
+              pu = max(pu, __float_as_uint(scalar_load(tm)));
+              du = max(du, __float_as_uint(scalar_load(tm + 1)));
+            }
+            if (KV128 && jm + 1 < nblk && (!CAUSAL || jm + 1 <= iq - 1 + sb)) {
+              pu = max(pu, __float_as_uint(scalar_load(tm + 2)));
+              du = max(du, __float_as_uint(scalar_load(tm + 3)));
+            }
+          } else if (iq + 1 < nqblk) {
+            pu = max(pu, (unsigned)prev_p);
+            du = max(du, (unsigned)prev_d);
+          }
+          prev_p = __builtin_amdgcn_readfirstlane((int)bp);
+          prev_d = __builtin_amdgcn_readfirstlane((int)bd);
         }
+        const float bpm = __uint_as_float(pu), bdm = __uint_as_float(du);
+        // the per-tile scales of P and dS are internal (never stored bit-exactly): 127/a via rcp
+        const float rP = bpm > 0.f ? 127.0f * __builtin_amdgcn_rcpf(bpm) : 0.f;
+        const float rS = bdm > 0.f ? 127.0f * __builtin_amdgcn_rcpf(bdm) : 0.f;
+        const float sP = bpm * (1.0f / 127.0f), sS = bdm * (1.0f / 127.0f);
 #pragma unroll
-      for (int qh = 0; qh < 2; qh++)
+        for (int qh = 0; qh < 2; qh++)
 #pragma unroll
-        for (int aa = 0; aa < 4; aa++) {
-          unsigned ub[4];
+          for (int aa = 0; aa < 4; aa++) {
+            unsigned up = 0;
 #pragma unroll
-          for (int b = 0; b < 4; b++) ub[b] = __float_as_uint(__builtin_fmaf(ds[qh][4 * aa + b], rS, kRoundMagic));
-          df[qh][aa] = (int)(__builtin_amdgcn_perm(ub[1], ub[0], 0x0c0c0400u) | __builtin_amdgcn_perm(ub[3], ub[2], 0x04000c0cu));
+            for (int b = 0; b < 4; b++) up = __builtin_amdgcn_cvt_pk_u8_f32(p[qh][4 * aa + b] * rP, b, up);
+            pf[qh][aa] = (int)up;
+          }
+#pragma unroll
+        for (int qh = 0; qh < 2; qh++)
+#pragma unroll
+          for (int aa = 0; aa < 4; aa++) {
+            unsigned ub[4];
+#pragma unroll
+            for (int b = 0; b < 4; b++) ub[b] = __float_as_uint(__builtin_fmaf(ds[qh][4 * aa + b], rS, kRoundMagic));
+            df[qh][aa] = (int)(__builtin_amdgcn_perm(ub[1], ub[0], 0x0c0c0400u) | __builtin_amdgcn_perm(ub[3], ub[2], 0x04000c0cu));
+          }
+        w_dv = sP * sd1;
+        w_dk = sS * sq1 * args.sm_scale;
+        if (!MASK || act_q) {
+          // fragments (q half, kb) of the tile, as sage_bwd_kernel stores them
+          const size_t tile = ((size_t)hl * nqblk + iq) * args.ds_pitch + j;
+          const gbytes_t dst = uniform(args.dSq + tile * 4096 + kb * 1024) + lane16;
+          *(__attribute__((address_space(1))) v4i*)dst = df[0];
+          *(__attribute__((address_space(1))) v4i*)(dst + 2048) = df[1];
+          args.sdS[tile] = sS;       // (the same value from every lane)
         }
-      const float w_dv = sP * sd1;
-      const float w_dk = sS * sq1 * args.sm_scale;
-      if (!MASK || act_q) {
-        // fragments (q half, kb) of the tile, as sage_bwd_kernel stores them
-        const size_t tile = ((size_t)hl * nqblk + iq) * args.ds_pitch + j;
-        const gbytes_t dst = uniform(args.dSq + tile * 4096 + kb * 1024) + lane16;
-        *(__attribute__((address_space(1))) v4i*)dst = df[0];
-        *(__attribute__((address_space(1))) v4i*)(dst + 2048) = df[1];
-        args.sdS[tile] = sS;       // (the same value from every lane)
       }
       __builtin_amdgcn_sched_barrier(0);
       // ---------------- dV, dK of tile t - 1 (phase B), S of tile t ----------------
@@ -1196,8 +1200,10 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_wide_kernel(BwdArgs args) {
       struct Slot {
         int u, k, s;               // step k of product u, or (k < 0) product s of S
       };
-      constexpr int NM = 6 * KS;
+      constexpr int NM = HAS_Q && HAS_A ? 6 * KS : HAS_Q ? 4 * KS : 2 * KS;
       auto slot = [](int m) constexpr {
+        if (!HAS_Q) return Slot{KS, -1, m};
+        if (!HAS_A) return Slot{m / 2, m % 2, 0};
         if (m < 2 * KS) return Slot{m / 2, m % 2, 0};
         const int n = m - 2 * KS;
         return n % 2 == 0 ? Slot{KS + n / 4, (n / 2) % 2, 0} : Slot{KS + n / 4, -1, n / 2};
@@ -1228,109 +1234,117 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_wide_kernel(BwdArgs args) {
           res[sl.u & 1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(op[m % 4], sl.u < KS ? pf[sl.k] : df[sl.k], sl.k == 0 ? zero : res[sl.u & 1], 0, 0, 0);
         else
           sacc[sl.s / KS] = __builtin_amdgcn_mfma_i32_32x32x32_i8(op[m % 4], sl.s % KS == KS - 1 ? klast : kfr[sl.s % KS], sl.s % KS == 0 ? zero : sacc[sl.s / KS], 0, 0, 0);
-        if (QSMOOTH && m % 2 == 0 && m < 2 * KS)
+        if (!HAS_Q && m < PARTS) copy_part(m);
+        if (QSMOOTH && HAS_Q && m % 2 == 0 && m < 2 * KS)
           dkacc[m / 2] = add_dk_bias(dkacc[m / 2], L.muq[(t - 1) & 1][16 * m + ll], cs);
-        if (sl.u > 0 && sl.u < KS) update(sl.u - 1, 8 * (m % 2), 8 * (m % 2) + 8);
-        if (sl.u >= KS) update(sl.u - 1, 4 * (m % 4), 4 * (m % 4) + 4);
-        if (m % 3 == 1 && m / 3 < PARTS) copy_part(m / 3);     // (dealt out: the waves do not queue up at the memory pipeline)
+        if (HAS_Q && sl.u > 0 && (sl.u < KS || !HAS_A)) update(sl.u - 1, 8 * (m % 2), 8 * (m % 2) + 8);
+        if (HAS_Q && HAS_A && sl.u >= KS) update(sl.u - 1, 4 * (m % 4), 4 * (m % 4) + 4);
+        if (HAS_Q && HAS_A && m % 3 == 1 && m / 3 < PARTS) copy_part(m / 3);     // (dealt out: the waves do not queue up at the memory pipeline)
         __builtin_amdgcn_sched_barrier(0);
       }
-      first_for_younger_waves<0>(wave);
-      // ---------------- dP, P, dS of tile t ----------------
-      const float c = sq * sKj * args.scale_log2e;
-      v16f dp[2];
-      v8bf da[3], vb[2];
-      auto read_dO = [&](int m) __attribute__((always_inline)) {     // product m: q half m % 2, step m / 2
-        da[m % 3] = *(const __attribute__((address_space(3))) v8bf*)(uintptr_t)((dofp ^ ((m / 2) * 32)) + (m & 1) * 64 * D);
-      };
-      auto read_V = [&](int s) __attribute__((always_inline)) { vb[s % 2] = *(const v8bf*)(vbp + s * 1024); };
-      // -L log2e, LE elements at a time (with Q-smoothing there is no register for four)
-      constexpr int LE = QSMOOTH ? 2 : 4;
-      typedef float vle __attribute__((ext_vector_type(LE)));
-      vle lst[2];
-      auto read_L = [&](int g) __attribute__((always_inline)) {
-        const int e = g * LE;
-        lst[g & 1] = *(const vle*)(st.nl2 + 4 * h + 32 * (e >> 4) + 8 * ((e >> 2) & 3) + (e & 3));
-      };
-      float pm = 0.f, dm = 0.f;
-      // masked: the rows of the tile below klow + 4 h (under the diagonal), or all 64 of a key or of a tile that does not exist
-      // (in scalars first: as a choice of three it became branches around the products)
-      const int kv = act_a ? kvalid : 0, off = CAUSAL && ia + sb == j ? 32 * kb : -128;
-      const int klow = 32 * kb + ll >= kv ? 64 : ll - 4 * h + off;
-      // P of element e (q half e / 16, register e % 16 = query 8 (r / 4) + 4 h + r % 4 of it), in three steps that run one product apart
-      const float bias_l = QSMOOTH ? L.bias[t & 1][wave >> 1][32 * kb + ll] : 0.f;
-      auto form_x = [&](int e) __attribute__((always_inline)) {
-        const float l = lst[(e / LE) & 1][e % LE];
-        p[e >> 4][e & 15] = __builtin_fmaf((float)sacc[e >> 4][e & 15], c, QSMOOTH ? bias_l + l : l);
-      };
-      auto form_p = [&](int e) __attribute__((always_inline)) {
-        const int qh = e >> 4, r = e & 15;
-        const float pv = __builtin_amdgcn_exp2f(p[qh][r]);
-        p[qh][r] = MASK && 32 * qh + 2 * (r & ~3) + (r & 3) < klow ? 0.f : pv;
-      };
-      auto form_max = [&](int e) __attribute__((always_inline)) { pm = fmaxf(fmaxf(p[e >> 4][e & 15], p[e >> 4][(e & 15) + 1]), pm); };
-      read_V(0);
-      read_dO(0);
-      read_dO(1);
-      read_L(0);
-      // dS = P o (dP - delta): the chains start from -delta of the rows a lane's registers hold
-      auto read_delta = [&](int qh) __attribute__((always_inline)) {
+      if constexpr (!HAS_A) {
+        update(2 * KS - 1, 0, 16);
+        first_for_younger_waves<0>(wave);
+      } else {
+        // ---------------- dP, P, dS of tile t ----------------
+        const float c = sq * sKj * args.scale_log2e;
+        v16f dp[2];
+        v8bf da[3], vb[2];
+        auto read_dO = [&](int m) __attribute__((always_inline)) {     // product m: q half m % 2, step m / 2
+          da[m % 3] = *(const __attribute__((address_space(3))) v8bf*)(uintptr_t)((dofp ^ ((m / 2) * 32)) + (m & 1) * 64 * D);
+        };
+        auto read_V = [&](int s) __attribute__((always_inline)) { vb[s % 2] = *(const v8bf*)(vbp + s * 1024); };
+        // -L log2e, LE elements at a time (with Q-smoothing there is no register for four)
+        constexpr int LE = QSMOOTH ? 2 : 4;
+        typedef float vle __attribute__((ext_vector_type(LE)));
+        vle lst[2];
+        auto read_L = [&](int g) __attribute__((always_inline)) {
+          const int e = g * LE;
+          lst[g & 1] = *(const vle*)(st.nl2 + 4 * h + 32 * (e >> 4) + 8 * ((e >> 2) & 3) + (e & 3));
+        };
+        float pm = 0.f, dm = 0.f;
+        // masked: the rows of the tile below klow + 4 h (under the diagonal), or all 64 of a key or of a tile that does not exist
+        // (in scalars first: as a choice of three it became branches around the products)
+        const int kv = act_a ? kvalid : 0, off = CAUSAL && ia + sb == j ? 32 * kb : -128;
+        const int klow = 32 * kb + ll >= kv ? 64 : ll - 4 * h + off;
+        // P of element e (q half e / 16, register e % 16 = query 8 (r / 4) + 4 h + r % 4 of it), in three steps that run one product apart
+        const float bias_l = QSMOOTH ? L.bias[t & 1][wave >> 1][32 * kb + ll] : 0.f;
+        auto form_x = [&](int e) __attribute__((always_inline)) {
+          const float l = lst[(e / LE) & 1][e % LE];
+          p[e >> 4][e & 15] = __builtin_fmaf((float)sacc[e >> 4][e & 15], c, QSMOOTH ? bias_l + l : l);
+        };
+        auto form_p = [&](int e) __attribute__((always_inline)) {
+          const int qh = e >> 4, r = e & 15;
+          const float pv = __builtin_amdgcn_exp2f(p[qh][r]);
+          p[qh][r] = MASK && 32 * qh + 2 * (r & ~3) + (r & 3) < klow ? 0.f : pv;
+        };
+        auto form_max = [&](int e) __attribute__((always_inline)) { pm = fmaxf(fmaxf(p[e >> 4][e & 15], p[e >> 4][(e & 15) + 1]), pm); };
+        read_V(0);
+        read_dO(0);
+        read_dO(1);
+        read_L(0);
+        // dS = P o (dP - delta): the chains start from -delta of the rows a lane's registers hold
+        auto read_delta = [&](int qh) __attribute__((always_inline)) {
 #pragma unroll
-        for (int aa = 0; aa < 4; aa++) {
-          const v4f d4 = *(const v4f*)(st.dl + 32 * qh + 4 * h + 8 * aa);
+          for (int aa = 0; aa < 4; aa++) {
+            const v4f d4 = *(const v4f*)(st.dl + 32 * qh + 4 * h + 8 * aa);
 #pragma unroll
-          for (int b = 0; b < 4; b++) dp[qh][4 * aa + b] = d4[b];
-        }
-      };
-      read_delta(0);
-      __builtin_amdgcn_sched_barrier(0);
-      update(2 * KS - 1, 0, 16);         // (while those reads are under way; its operands' registers go to the second chain)
-      __builtin_amdgcn_sched_barrier(0);
-      read_delta(1);
-#pragma unroll
-      for (int m = 0; m < 2 * KB; m++) {
-        if (m + 2 < 2 * KB) read_dO(m + 2);
-        if (m % 2 == 0 && m / 2 + 1 < KB) read_V(m / 2 + 1);
-        if (2 * m % LE == 0 && 2 * m + LE < 32) read_L(2 * m / LE + 1);
-        dp[m & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(da[m % 3], vb[(m / 2) % 2], dp[m & 1], 0, 0, 0);
-        if (m >= 2) form_max(2 * m - 4);
-        if (m >= 1) {
-          form_p(2 * m - 2);
-          form_p(2 * m - 1);
-        }
-        form_x(2 * m);
-        form_x(2 * m + 1);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      form_max(28);
-      form_p(30);
-      form_p(31);
-      form_max(30);
-#pragma unroll
-      for (int qh = 0; qh < 2; qh++)
-#pragma unroll
-        for (int r = 0; r < 16; r += 2) {
-#pragma unroll
-          for (int b = r; b < r + 2; b++) {
-            ds[qh][b] = p[qh][b] * dp[qh][b];
-            if constexpr (MASK) ds[qh][b] = act_a ? ds[qh][b] : 0.f;   // (no tile: nothing, whatever the stage holds)
+            for (int b = 0; b < 4; b++) dp[qh][4 * aa + b] = d4[b];
           }
-          dm = fmaxf(fmaxf(fabsf(ds[qh][r]), fabsf(ds[qh][r + 1])), dm);
-        }
-      if constexpr (QSMOOTH) {
-        float cs0 = 0.f, cs1 = 0.f;
+        };
+        read_delta(0);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (HAS_Q) update(2 * KS - 1, 0, 16);         // (while those reads are under way; its operands' registers go to the second chain)
+        __builtin_amdgcn_sched_barrier(0);
+        read_delta(1);
 #pragma unroll
-        for (int r = 0; r < 16; r++) {
-          cs0 += ds[0][r];
-          cs1 += ds[1][r];
+        for (int m = 0; m < 2 * KB; m++) {
+          if (m + 2 < 2 * KB) read_dO(m + 2);
+          if (m % 2 == 0 && m / 2 + 1 < KB) read_V(m / 2 + 1);
+          if (2 * m % LE == 0 && 2 * m + LE < 32) read_L(2 * m / LE + 1);
+          dp[m & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(da[m % 3], vb[(m / 2) % 2], dp[m & 1], 0, 0, 0);
+          // (first through most of dP too: its operands are read under the older wave's dK.  Dropped at product 0, 3, 7, 11, 16: 64 heads of N = 8192
+          // with the mask 1997, 1991, 1986, 1965, 2000 us)
+          if (m == 11) first_for_younger_waves<0>(wave);
+          if (m >= 2) form_max(2 * m - 4);
+          if (m >= 1) {
+            form_p(2 * m - 2);
+            form_p(2 * m - 1);
+          }
+          form_x(2 * m);
+          form_x(2 * m + 1);
+          __builtin_amdgcn_sched_barrier(0);
         }
-        cs = (cs0 + cs1) * args.sm_scale;
+        form_max(28);
+        form_p(30);
+        form_p(31);
+        form_max(30);
+#pragma unroll
+        for (int qh = 0; qh < 2; qh++)
+#pragma unroll
+          for (int r = 0; r < 16; r += 2) {
+#pragma unroll
+            for (int b = r; b < r + 2; b++) {
+              ds[qh][b] = p[qh][b] * dp[qh][b];
+              if constexpr (MASK) ds[qh][b] = act_a ? ds[qh][b] : 0.f;   // (no tile: nothing, whatever the stage holds)
+            }
+            dm = fmaxf(fmaxf(fabsf(ds[qh][r]), fabsf(ds[qh][r + 1])), dm);
+          }
+        if constexpr (QSMOOTH) {
+          float cs0 = 0.f, cs1 = 0.f;
+#pragma unroll
+          for (int r = 0; r < 16; r++) {
+            cs0 += ds[0][r];
+            cs1 += ds[1][r];
+          }
+          cs = (cs0 + cs1) * args.sm_scale;
+        }
+        own_p = __builtin_amdgcn_readfirstlane(__float_as_int(wave_max_nonneg_f32(pm)));
+        own_d = __builtin_amdgcn_readfirstlane(__float_as_int(wave_max_nonneg_f32(dm)));
+        L.red[t & 1][wave][0] = (unsigned)own_p;     // (the same pair from every lane)
+        L.red[t & 1][wave][1] = (unsigned)own_d;
       }
-      own_p = __builtin_amdgcn_readfirstlane(__float_as_int(wave_max_nonneg_f32(pm)));
-      own_d = __builtin_amdgcn_readfirstlane(__float_as_int(wave_max_nonneg_f32(dm)));
-      L.red[t & 1][wave][0] = (unsigned)own_p;     // (the same pair from every lane)
-      L.red[t & 1][wave][1] = (unsigned)own_d;
-    } else {
+    } else if constexpr (HAS_A) {
 #pragma unroll
       for (int part = 0; part < PARTS; part++) copy_part(part);
       if constexpr (KV128) L.red[t & 1][wave][0] = L.red[t & 1][wave][1] = 0u;   // nothing for the neighbour's block maxima
@@ -1339,17 +1353,21 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_wide_kernel(BwdArgs args) {
     sd1 = sd;
     sq = sqn;
     sd = sdn;
-    barrier_all_memory();   // the interval's LDS traffic, copies and stores are complete
+    if constexpr (HAS_A) barrier_all_memory();   // the interval's LDS traffic, copies and stores are complete
   };
   // unmasked intervals: both tiles exist in full, tile t above the diagonal
   const int t_steady_end = !valid || kvalid < 64 ? 0 : CAUSAL ? min(itop + sb - j, T - 1) : T - 1;
-  // the first interval, the unmasked ones, the others (written so that the masked form is there once)
+  // the first interval, the unmasked ones, the others (written so that their masked form is there once), the last one.  The first and
+  // the last are half an interval each: in the masked form, as they were, each wasted the other half (64 heads of N = 2048 with the mask 136.3 -> 129.2
+  // us, 32 of 4096 236 -> 228.5, 64 of 8192 1970 -> 1900, 8 of 8192 without 438 -> 429, the dP priority included).
+  interval(0, std::true_type{}, std::false_type{}, std::true_type{});
 #pragma clang loop unroll(disable)
-  for (int t = 0; t <= T;) {
-    interval(t++, std::true_type{});
+  for (int t = 1; t < T;) {
 #pragma clang loop unroll(disable)
-    for (; t < t_steady_end; t++) interval(t, std::false_type{});
+    for (; t < t_steady_end; t++) interval(t, std::false_type{}, std::true_type{}, std::true_type{});
+    if (t < T) interval(t++, std::true_type{}, std::true_type{}, std::true_type{});
   }
+  interval(T, std::true_type{}, std::true_type{}, std::false_type{});
 
   if (!valid) return;
   // ---- write dV, then dK (bf16): through the wave's own V stage (nobody else reads it), so that whole rows leave.  Piece c of row
