@@ -57,6 +57,7 @@ struct BwdArgs {
   int8_t* dSq;         // psi(dS) tiles [heads, N/64, ds_pitch, 4096]: the four quadrant fragments as phase Q forms them
   int ds_pitch;        // tiles per Q-block row of that array (>= N/64)
   float* sdS;          // their scales [heads, N/64, ds_pitch]
+  int stream_ds;       // the tiles are stored past the caches (see ds_traffic)
   float* tmax;         // B_q = 128: (max P, max |dS|) of the tiles of the even Q blocks [heads, N/64, ds_pitch][2], see MODE
   int bh0;             // first head of this launch (the scratch above is indexed from it)
   unsigned short* dK;  // bf16 [BH, N, D]
@@ -1183,12 +1184,12 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_wide_kernel(BwdArgs args) {
           }
         w_dv = sP * sd1;
         w_dk = sS * sq1 * args.sm_scale;
-        if (!MASK || act_q) {
+        // (act_q whenever act_a, so always; the branch decides a register either way: none is in scratch with it here and without it there)
+        if (MODE == kBwdPairedRows || !MASK || act_q) {
           // fragments (q half, kb) of the tile, as sage_bwd_kernel stores them
           const size_t tile = ((size_t)hl * nqblk + iq) * args.ds_pitch + j;
-          const gbytes_t dst = uniform(args.dSq + tile * 4096 + kb * 1024) + lane16;
-          *(__attribute__((address_space(1))) v4i*)dst = df[0];
-          *(__attribute__((address_space(1))) v4i*)(dst + 2048) = df[1];
+          const gbytes_t dst = uniform(args.dSq + tile * 4096 + kb * 1024);
+          store_pair<2048>(dst, lane16, df[0], df[1], args.stream_ds);
           args.sdS[tile] = sS;       // (the same value from every lane)
         }
       }
@@ -1392,7 +1393,7 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_wide_kernel(BwdArgs args) {
     for (int k = 0; k < 32 / RPF; k++) {
       const int r = RPF * k + lane / PPR;
       const v8us piece = *(const v8us*)(stg + r * 2 * D + ((lane ^ r) & (PPR - 1)) * 16);
-      if (key0 + r < args.nvalid) *(v8us*)(out + (size_t)(key0 + r) * rs + 8 * (lane % PPR)) = piece;
+      if (key0 + r < args.nvalid) stream_store((v8us*)(out + (size_t)(key0 + r) * rs + 8 * (lane % PPR)), piece);
     }
   }
 }
@@ -1413,6 +1414,7 @@ struct DqArgs {
   int nvalid;           // query rows >= nvalid do not exist
   int shift_blocks;     // causal: Q block i sees KV blocks j <= i + shift_blocks
   int head_set;         // heads per XCD whose work items are interleaved (see work_item)
+  int last_first;       // the last heads first: their tiles are still cached (see ds_traffic)
   float sm_scale;
 };
 
@@ -1431,11 +1433,13 @@ struct DqArgs {
 // registers.  Three workgroups share a CU: about 96 KiB of psi(dS) in flight per CU.
 // (Every lane takes part in the scale copy: a memory operation under a lane mask sits behind a branch,
 // and with a path that skips it the compiler stops counting the loads in flight and waits for all of
-// them before each use.)  Measured: the kernel runs at the speed of its psi(dS) stream alone (no
-// arithmetic, no K^ copies: 0.51 ms of 0.54 at the headline shape, about 4.4 TB/s, where a plain read
-// stream over the same bytes reaches 5.6 TB/s on this GPU); ring depths 3 to 7, two or three workgroups
-// per CU and non-temporal loads change nothing.
-template <int D, bool CAUSAL>
+// them before each use.)  Measured: the kernel runs nearly at the speed of its psi(dS) stream alone (no
+// arithmetic, no K^ copies: 0.51 ms of 0.54 for 64 heads of N = 8192 with the mask, where a plain read
+// stream over the same bytes reaches 5.6 TB/s on this GPU); ring depths 3 to 7 and two or three workgroups
+// per CU change nothing.  What did: psi(dS) stored and loaded past the caches (see ds_traffic), 538 -> 520 us, dQ, dK and dV stored past
+// them (what a kernel leaves dirty in the L2 is written back at its end) -> 506, and a subtraction in place of the conversion -> 491.
+// STREAM: psi(dS) is loaded past the caches.
+template <int D, bool CAUSAL, bool STREAM>
 __global__ void __launch_bounds__(256, 3) sage_bwd_dq_kernel(DqArgs args) {
   constexpr int KS = D / 32;               // channel blocks
   constexpr int TILE = 64 * D;             // bytes of one K^ tile
@@ -1455,7 +1459,7 @@ __global__ void __launch_bounds__(256, 3) sage_bwd_dq_kernel(DqArgs args) {
   const int sb = CAUSAL ? args.shift_blocks : 0;
   const int npair = (nqblk + 1) / 2;
   const WorkItem wi = work_item(g, npair, args.head_set);
-  const int hl = wi.head;
+  const int hl = args.last_first ? args.BH - 1 - wi.head : wi.head;
   const int bh = args.bh0 + hl;
   const int i0 = 2 * (npair - 1 - wi.item);            // longest rows first under the causal mask
   const int tid = threadIdx.x;
@@ -1482,8 +1486,8 @@ __global__ void __launch_bounds__(256, 3) sage_bwd_dq_kernel(DqArgs args) {
   auto load_ds = [&](int j, v4i (&a)[2]) __attribute__((always_inline)) {
     const int jc = j < j_last ? j : j_last;
     const int8_t* p = dsw + (size_t)jc * DSB;
-    a[0] = *(const v4i*)p;
-    a[1] = *(const v4i*)(p + 1024);
+    a[0] = STREAM ? stream_load((const v4i*)p) : *(const v4i*)p;
+    a[1] = STREAM ? stream_load((const v4i*)(p + 1024)) : *(const v4i*)(p + 1024);
   };
   auto load_k = [&](int j, int sl) __attribute__((always_inline)) {
     const int jc = j < n_j ? j : n_j - 1;
@@ -1558,13 +1562,11 @@ __global__ void __launch_bounds__(256, 3) sage_bwd_dq_kernel(DqArgs args) {
         for (int cb = 0; cb < KS; cb++) {
           const v4i b0 = *(const v4i*)(kp + cb * 1024 + lane * 16);
           const v4i b1 = *(const v4i*)(kp + (KS + cb) * 1024 + lane * 16);
-          v16i q;
-#pragma unroll
-          for (int r = 0; r < 16; r++) q[r] = 0;
-          q = __builtin_amdgcn_mfma_i32_32x32x32_i8(a0, b0, q, 0, 0, 0);
+          // (the sum less the bias is a 2^-26 exactly, and a subtraction takes half the time of a conversion)
+          v16i q = mfma_from_bias(a0, b0);
           q = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1, b1, q, 0, 0, 0);
 #pragma unroll
-          for (int r = 0; r < 16; r++) acc[cb][r] = __builtin_fmaf((float)q[r], w, acc[cb][r]);
+          for (int r = 0; r < 16; r++) acc[cb][r] = __builtin_fmaf(__int_as_float(q[r]) - kBiasC0, w, acc[cb][r]);
         }
       }
       load_ds(j + kStages, a[s]);
@@ -1587,14 +1589,14 @@ __global__ void __launch_bounds__(256, 3) sage_bwd_dq_kernel(DqArgs args) {
       for (int aa = 0; aa < 4; aa++)
 #pragma unroll
         for (int b = 0; b < 4; b++)
-          stg[(iq * 64 + 32 * qb + 8 * aa + 4 * h + b) * LDQ + 32 * cb + ll] = float_to_bf16_bits(acc[cb][4 * aa + b]);
+          stg[(iq * 64 + 32 * qb + 8 * aa + 4 * h + b) * LDQ + 32 * cb + ll] = float_to_bf16_bits(acc[cb][4 * aa + b] * kTwo26);
   }
   barrier_lds_only();
   constexpr int CPR = D / 8;                                   // 16-byte pieces per row
   for (int c = tid; c < 2 * 64 * CPR; c += 256) {
     const int qblk = c / (64 * CPR), row = (c / CPR) % 64, pc = c % CPR;
     if (i0 + qblk < nqblk && 64 * (i0 + qblk) + row < args.nvalid)
-      *(v8us*)(args.dQ + args.cv.row(bh, 64 * (i0 + qblk) + row) + 8 * pc) = *(const v8us*)(stg + (qblk * 64 + row) * LDQ + 8 * pc);
+      stream_store((v8us*)(args.dQ + args.cv.row(bh, 64 * (i0 + qblk) + row) + 8 * pc), *(const v8us*)(stg + (qblk * 64 + row) * LDQ + 8 * pc));
   }
 }
 

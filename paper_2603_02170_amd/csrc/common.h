@@ -85,6 +85,37 @@ __device__ __forceinline__ float wave_max_nonneg_f32(float v) {
   return __uint_as_float(u);
 }
 
+// Loads and stores of what passes through once and does not fit the caches: they are told to let go of it first.  For whole 16-byte pieces of
+// whole lines only: stores of 8 bytes that meet in the L2 otherwise, and loads of lines that another load takes the rest of, got slower (the
+// backward of 36 heads of N = 1777, d = 64, 55 -> 83 us, a decoding step 73 -> 95).
+template <class T>
+__device__ __forceinline__ T stream_load(const T* p) {
+  return __builtin_nontemporal_load(p);
+}
+template <class T>
+__device__ __forceinline__ void stream_store(T* p, const T& v) {
+  __builtin_nontemporal_store(v, p);
+}
+
+// INT32 sums that read as floats: accumulators that start from the bits of C0 = 1/(2 pi), an inline constant of the ISA, hold
+// C0 + a 2^-26 exactly for |a| < 2^20 (see fwd_kernel.h).
+constexpr int kBiasBits = 0x3E22F983;
+constexpr float kBiasC0 = 0.15915494309189532f;
+constexpr float kTwo26 = 67108864.0f;
+
+// The product that starts a chain from B0.  As assembly, because the compiler folds the inline constant into one product
+// only and makes a splat of 16 registers for several: with it the loop of sage_fwd_kernel formed the splat anew in every tile (8 vector and 16 scalar
+// instructions) and had no register to spare (256 and 17 parked; now 251; 16 heads of N = 8192 350 -> 337 us).  The compiler does not see a matrix instruction here, so
+// the waits around one are written out: two states after a vector write of an operand, two before the next product of the chain
+// reads the result as its C, which must be the only thing that ever reads it (a copy or a spill in between would read an unfinished
+// result), and the result is kept off its operands' registers, as the compiler keeps those of its own products of this size.  A test reads
+// both from the assembly of the build.
+__device__ __forceinline__ v16i mfma_from_bias(const v4i& a, const v4i& b) {
+  v16i d;
+  asm("s_nop 1\n\tv_mfma_i32_32x32x32_i8 %0, %1, %2, 0.15915494\n\ts_nop 1" : "=&v"(d) : "v"(a), "v"(b));
+  return d;
+}
+
 typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
 
@@ -104,6 +135,18 @@ __device__ __forceinline__ gbytes_t uniform(const void* p) {
   gbytes_t g = (gbytes_t)p;
   asm("" : "+s"(g));
   return g;
+}
+// Two 16-byte pieces per lane to base + lane_offset and OFFSET behind it, past the caches (as stream_store does) where `stream` is not 0.  The branch is inside the
+// assembly, as below, and the compiler would make one plain store of both sides.  It does not see stores here: the wait states in front are
+// for a base that a vector instruction wrote, the one behind for an overwrite of the data, and a wait for them has to be written out.
+template <int OFFSET>
+__device__ __forceinline__ void store_pair(gbytes_t base, unsigned lane_offset, const v4i& a, const v4i& b, int stream) {
+  asm volatile(
+      "s_nop 4\n\ts_cmp_eq_u32 %4, 0\n\ts_cbranch_scc1 .Lkeep%=\n\t"
+      "global_store_dwordx4 %0, %1, %3 nt\n\tglobal_store_dwordx4 %0, %2, %3 offset:%5 nt\n\ts_branch .Ldone%=\n"
+      ".Lkeep%=:\n\tglobal_store_dwordx4 %0, %1, %3\n\tglobal_store_dwordx4 %0, %2, %3 offset:%5\n"
+      ".Ldone%=:\n\ts_nop 1" ::"v"(lane_offset), "v"(a), "v"(b), "s"(base), "s"(stream), "n"(OFFSET)
+      : "scc", "memory");
 }
 __device__ __forceinline__ void copy_16(gbytes_t gsrc_lane, void* lds_base) {
   __builtin_amdgcn_global_load_lds((gptr_t)gsrc_lane, (lptr_t)lds_base, 16, 0, 0);

@@ -165,4 +165,21 @@ inline int bwd_heads_of_group(int most, int left, int nblk, int nqblk, int shift
   return best;
 }
 
+// psi(dS) of a launch on its way from the backward to the dQ kernel.  Up to 100 MB it is left to the caches.  From there on the dQ kernel
+// loads it past them, and takes the last heads first, whose tiles were written last: the memory-side cache (256 MB) holds part of them.  Beyond 400 MB that is
+// little and displaces what the two kernels read again, so that sage_bwd_wide_kernel stores past the caches too (and the heads come in order).  Whole
+// steps / dQ kernel, us: all through the caches -> loaded past them, last heads first -> stored past them.  40 heads of N = 2048, d = 64, 86 MB: dQ 23.1 -> 26.2; d =
+// 128: 44 of 2048, 95 MB, 225 / 35.4 -> 224 / 37.2; 64 of 2048, 139 MB, 307 / 52.4 -> 300 / 49.7; 32 of 4096, 273 MB, 498 / 87 -> 488 / 74 -> 488.5 / 84; 20 of 6144,
+// 382 MB, 705 / 140 -> 698 / 124 -> 696 / 130; 24 of 6144 838 / 141.5 -> 819 / 124.6 -> 818 / 127; 64 of 4096, 545 MB, 989 / 167 -> 973 / 145 -> 973 / 144; 64 of 8192,
+// 2164 MB, 3515 / 518 -> 3514 / 510 -> 3485 / 494.5; d = 64, whose kernel always stores through, 64 of 4096 792 / 162 -> 773 / 132.
+struct DsTraffic {
+  bool load_past, store_past;
+};
+inline DsTraffic ds_traffic(long long heads, int nblk, int nqblk, int shift_blocks, bool causal) {
+  long long tiles = (long long)nblk * nqblk;      // of a head
+  if (causal) tiles = (long long)nqblk * (shift_blocks + 1) + (long long)nqblk * (nqblk - 1) / 2;
+  const long long mb = heads * tiles * 4096 >> 20;
+  return {mb > 100, mb > 400};
+}
+
 }  // namespace sage

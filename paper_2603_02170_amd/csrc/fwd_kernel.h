@@ -68,28 +68,12 @@ struct FwdArgs {
 constexpr float kTau = 8.0f;
 constexpr float kLog2_127 = 6.98868468677216585f;
 constexpr float kLn2 = 0.69314718055994531f;
-constexpr int kBiasBits = 0x3E22F983;         // bit pattern of 1/(2 pi): an inline constant of the ISA
-constexpr float kBiasC0 = 0.15915494309189532f;
-constexpr float kTwo26 = 67108864.0f;
 constexpr int kBiasPeriod = 8;                // tiles between two subtractions of the accumulated bias
 
 // Keeps the computation of `v` where it is written: without a use at this point the compiler
 // sinks the vector work of a chunk past the scheduling barriers into the next basic block.
 __device__ __forceinline__ void pin(float& v) { asm volatile("" : "+v"(v)); }
 __device__ __forceinline__ void pin_i(int& v) { asm volatile("" : "+v"(v)); }
-
-// The product that starts a chain from B0.  As assembly, because the compiler folds the inline constant into one product
-// only and makes a splat of 16 registers for several: with it the loop of sage_fwd_kernel formed the splat anew in every tile (8 vector and 16 scalar
-// instructions) and had no register to spare (256 and 17 parked; now 251; 16 heads of N = 8192 350 -> 337 us).  The compiler does not see a matrix instruction here, so
-// the waits around one are written out: two states after a vector write of an operand, two before the next product of the chain
-// reads the result as its C, which must be the only thing that ever reads it (a copy or a spill in between would read an unfinished
-// result), and the result is kept off its operands' registers, as the compiler keeps those of its own products of this size.  A test reads
-// both from the assembly of the build.
-__device__ __forceinline__ v16i mfma_from_bias(const v4i& a, const v4i& b) {
-  v16i d;
-  asm("s_nop 1\n\tv_mfma_i32_32x32x32_i8 %0, %1, %2, 0.15915494\n\ts_nop 1" : "=&v"(d) : "v"(a), "v"(b));
-  return d;
-}
 
 // S^T accumulators of one 64-key tile (two 32-key blocks), interleaved so that consecutive
 // MFMAs are independent.

@@ -489,13 +489,18 @@ int launch_bwd_wide(const BwdArgs& a, bool causal, hipStream_t st) {
 }
 
 template <int D>
-int launch_bwd_dq(const DqArgs& a, bool causal, hipStream_t st) {
+int launch_bwd_dq(const DqArgs& a, bool causal, bool stream, hipStream_t st) {
   const int npair = (a.Nq / 64 + 1) / 2;    // one workgroup per pair of Q blocks
   DqArgs args = a;
   args.head_set = head_set_for(npair, a.BH, true);   // memory-bound: gains from head sets at every length
   const int grid = grid_for(a.BH, npair);
-  if (causal) sage_bwd_dq_kernel<D, true><<<grid, 256, 0, st>>>(args);
-  else sage_bwd_dq_kernel<D, false><<<grid, 256, 0, st>>>(args);
+  if (causal) {
+    if (stream) sage_bwd_dq_kernel<D, true, true><<<grid, 256, 0, st>>>(args);
+    else sage_bwd_dq_kernel<D, true, false><<<grid, 256, 0, st>>>(args);
+  } else {
+    if (stream) sage_bwd_dq_kernel<D, false, true><<<grid, 256, 0, st>>>(args);
+    else sage_bwd_dq_kernel<D, false, false><<<grid, 256, 0, st>>>(args);
+  }
   SAGE_LAUNCH_CHECK();
   return SAGEBWD_OK;
 }
@@ -836,9 +841,12 @@ int sagebwd_bwd(const void* Q, const void* K, const void* V, const void* O, cons
     nh = bwd_heads_of_group(w.heads_per_group, BH - h0, Nkp / 64, Nqp / 64, shift_blocks, params->causal != 0, wide_form);
     a.bh0 = q.bh0 = h0;
     a.BH = q.BH = nh;
+    const DsTraffic ds = ds_traffic(nh, Nkp / 64, Nqp / 64, shift_blocks, params->causal != 0);
+    const bool causal = params->causal != 0, wide = use_bwd_wide(a, d, causal, qs, big);
+    a.stream_ds = ds.store_past;
+    q.last_first = ds.load_past && !(wide && ds.store_past);
     {
       ScopedTimer tm(SAGEBWD_KERNEL_BWD, st);
-      const bool causal = params->causal != 0, wide = use_bwd_wide(a, d, causal, qs, big);
       if (!big && wide) {
         rc = qs ? launch_bwd_wide<true, kBwdFused>(a, causal, st) : launch_bwd_wide<false, kBwdFused>(a, causal, st);
         if (rc != SAGEBWD_OK) return rc;
@@ -870,7 +878,7 @@ int sagebwd_bwd(const void* Q, const void* K, const void* V, const void* O, cons
     }
     {
       ScopedTimer tm(SAGEBWD_KERNEL_BWD_DQ, st);
-      rc = d == 64 ? launch_bwd_dq<64>(q, params->causal != 0, st) : launch_bwd_dq<128>(q, params->causal != 0, st);
+      rc = d == 64 ? launch_bwd_dq<64>(q, causal, ds.load_past, st) : launch_bwd_dq<128>(q, causal, ds.load_past, st);
       if (rc != SAGEBWD_OK) return rc;
     }
   }

@@ -40,6 +40,13 @@ int main() {
   }
   for (const auto& c : kBackward)
     if (bwd_wide_is_faster(c.heads, c.nblk, c.nblk, 0, c.causal) != c.wide) return printf("bwd_wide_is_faster: %d heads of %d blocks, mask %d\n", c.heads, c.nblk, c.causal), 1;
+  // psi(dS) past the caches: heads, blocks, mask; loaded, stored
+  const struct { int heads, nblk; bool causal, load, store; } kTraffic[] = {{36, 28, true, false, false}, {44, 32, true, false, false}, {64, 32, true, true, false},
+      {16, 64, false, true, false}, {32, 64, true, true, false}, {64, 64, true, true, true}, {64, 128, true, true, true}, {1, 1, false, false, false}};
+  for (const auto& c : kTraffic) {
+    const DsTraffic t = ds_traffic(c.heads, c.nblk, c.nblk, 0, c.causal);
+    if (t.load_past != c.load || t.store_past != c.store) return printf("ds_traffic: %d heads of %d blocks, mask %d\n", c.heads, c.nblk, c.causal), 1;
+  }
   // groups of heads: whole rounds where the walks are even (no mask, or few queries against many keys) and the workgroups have four
   // blocks; else all that fit
   if (bwd_heads_of_group(7, 32, 512, 512, 0, false, true) != 6 || bwd_heads_of_group(9, 16, 128, 128, 0, false, true) != 8 ||
