@@ -168,6 +168,12 @@ __device__ __forceinline__ float scalar_load(const float* p) {
   return *(const __attribute__((address_space(4))) float*)(uintptr_t)p;
 }
 
+// Two neighbours.
+__device__ __forceinline__ v2f scalar_load2(const float* p) {
+  typedef v2f v2f_dword __attribute__((aligned(4)));
+  return *(const __attribute__((address_space(4))) v2f_dword*)(uintptr_t)p;
+}
+
 // Immediate of `s_waitcnt vmcnt(n)` alone (the LDS / scalar and export counters are left at their
 // maxima = no wait): the six bits of n sit in bits 3:0 and 15:14.
 constexpr int vmcnt_only(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }

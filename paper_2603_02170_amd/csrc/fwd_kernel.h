@@ -959,6 +959,398 @@ __global__ void __launch_bounds__(128 * NQ, 2) sage_fwd_pair_kernel(FwdArgs args
   if (kb == 0 && h == 0) args.LSE[(size_t)bh * args.nq_valid + q] = (m_ref + __builtin_amdgcn_logf(l_tot) - kLog2_127) * kLn2;
 }
 
+// ---- four waves per 32 queries -----------------------------------------------------------------------
+// sage_fwd_quad_kernel: the same for calls that leave half of the SIMDs idle even then.  A workgroup is one Q block, eight waves; the four waves of
+// 32 queries take TWO tiles at a time, wave (tile, key block) one 32-key block of the pair, and a quarter of O's channels each (d = 64: half of
+// them, twice over).  An interval is as long a chain as above and there are half as many.  The tiles of a pair are added to O one after the
+// other by every wave, and the sums of P of either key block in the order of the tiles, so the bits are those of the other two kernels: row maxima, P^ and
+// the sums of P go through LDS for that.
+//
+// What an interval (0.85 us) takes is each wave's own instruction stream and its waits.  The steps, 1 and 4 heads of N = 4096, whole calls, two waves per 32
+// queries 51.8, 56.6 us: four waves 44.9, 48.7; copies whose addresses are one scalar minimum away and scales loaded behind the first waits for
+// LDS (85 -> 35 scalar instructions an interval, and such a wait no longer waits for all) 42.7, 47.0; the operands of the coming interval's products read under the end of
+// this one 41.3, 45.5.  Others: 8 heads of N = 1000 23.4 -> 21.5, 16 of 1024 25.8 -> 23.7, 8 of 2048 without the mask 35.2 -> 30.9.
+template <int D, bool CAUSAL, bool QSMOOTH>
+__global__ void __launch_bounds__(512, 1) sage_fwd_quad_kernel(FwdArgs args) {
+  constexpr int KS = D / 32;
+  constexpr int NQ = 2, NW = 4 * NQ;
+  constexpr int TILE_BYTES = 64 * D;
+  constexpr int PAIR = 2 * TILE_BYTES;
+  constexpr int TF = TILE_BYTES / 1024;                        // fragments of a tile
+  constexpr int NFRAG = 2 * PAIR / 1024;
+  constexpr int SLOT = 2 * PAIR + (QSMOOTH ? 512 : 0);         // (one Q block = one bias row per workgroup)
+  constexpr int R = 3;
+  constexpr int CPW = NFRAG / NW + (QSMOOTH ? 1 : 0);          // copies per wave and slot
+  static_assert(NFRAG % NW == 0, "every wave must issue the same number of copies");
+  static_assert(NQ * 32 == kBlock, "a workgroup is one Q block: rows of the workspace tensors come in whole blocks");
+  // (one LDS object: reads of a second one, which no asynchronous copy writes, would be made to wait for the copies in flight)
+  struct Lds {
+    int8_t ring[R * SLOT];                                     // slot p: K^ of pair p + 2 | V^ of pair p | biases of pair p + 1
+    int8_t pxch[2][NQ][4][1024];                               // [parity of the pair][query group][key block]: P^ as B operand
+    float sxch[2][NQ][4][64];                                  // [..][lane]: the lane's sum of P
+    float mxch[2][NQ][4][32];                                  // [..][query]: row max over the key block (bits)
+  };
+  __shared__ __attribute__((aligned(16))) Lds L;
+  auto& ring = L.ring;
+  auto& pxch = L.pxch;
+  auto& mxch = L.mxch;
+  auto& sxch = L.sxch;
+
+  const WorkItem wi = work_item(blockIdx.x, args.n_qtiles, args.head_set);
+  const int bh = wi.head;
+  const int qt = args.n_qtiles - 1 - wi.item;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qw = wave >> 2, w4 = wave & 3;
+  const int tp = w4 >> 1, kb = w4 & 1;                         // tile of a pair, key block of it
+  const int cb = w4 % KS;                                      // channel block of O (d = 64: two waves form each)
+  const int ql = lane & 31, h = lane >> 5;
+  const int N = args.N;
+  const int q0 = (qt * NQ + qw) * 32;
+  const int q = q0 + ql;
+  const int qlim = CAUSAL ? q + args.shift : args.nvalid - 1;
+  const int nblk = N / kBlock;
+  const int nqblk = args.Nq / kBlock;
+  const int qblk = q0 / kBlock;
+
+  const int8_t* KFh = args.KF + (size_t)bh * N * D;
+  const int8_t* VTh = args.VT + (size_t)bh * N * D;
+  const float* sKh = args.sK + (size_t)bh * nblk;
+  const float* sVh = args.sV + (size_t)bh * nblk;
+  const int n_tiles = CAUSAL ? (qt * NQ * 32 + NQ * 32 + args.shift) / kBlock : nblk;
+  const int last = n_tiles - 1;                                // (the diagonal block of every wave, with the mask)
+  const int n_pairs = (n_tiles + 1) / 2;
+
+  // Copies of slot p: K^ of pair p + 2, V^ of pair p (from the last tile where there is no such tile: K^ is masked, V^ never used).  One lane offset serves
+  // all of a wave's copies, and a copy is a minimum and an addition of scalars away: the wave's own instruction stream is what such a call takes.
+  constexpr int KC = NFRAG / 2 / NW;                           // copies of K^ per wave and slot, as many of V^
+  static_assert(NFRAG / 2 % NW == 0 && (KC == 2 || TF == NW / 2), "a copy is of K^ for every wave, or of V^; of one tile");
+  const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc((void*)KFh, 0, N * D, 0x27000);
+  const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc((void*)VTh, 0, N * D, 0x27000);
+  unsigned lane_off = lane * 16 + (wave % TF) * 1024;
+  const int last_off = (nblk - 1) * TILE_BYTES;
+  auto copy_piece = [&](int p, int8_t* dst, int k) __attribute__((always_inline)) {
+    const int o = wave + NW * k;                               // wave-uniform
+    const int tile = KC == 2 ? k % KC : wave / TF;
+    if (k < KC) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(krs, (lptr_t)(dst + o * 1024), 16, lane_off, min((2 * p + 4 + tile) * TILE_BYTES, last_off), 0, 0);
+    } else if (k < 2 * KC) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(vrs, (lptr_t)(dst + o * 1024), 16, lane_off, min(max(2 * p + tile, 0) * TILE_BYTES, last_off), 0, 0);
+    } else if (QSMOOTH && k == 2 * KC) {
+      // (every wave copies a row, so that all issue the same number)
+      copy_4(uniform(args.bias + ((size_t)bh * nqblk + qblk) * N + min(max(2 * p + 2 + (wave & 1), 0), nblk - 1) * kBlock) + 4 * lane, dst + 2 * PAIR + (wave & 1) * 256);
+    }
+  };
+  int8_t* rd = ring + SLOT;                                    // slot t
+  int8_t* mid = ring + 2 * SLOT;                               // slot t + 1
+  int8_t* wr = ring;                                           // slot t + 2 (before: t - 1)
+#pragma unroll
+  for (int k = 0; k < CPW; k++) copy_piece(-1, wr, k);
+#pragma unroll
+  for (int k = 0; k < CPW; k++) copy_piece(0, rd, k);
+#pragma unroll
+  for (int k = 0; k < CPW; k++) copy_piece(1, mid, k);
+
+  v4i qf[KS];
+  {
+    const int8_t* p = args.QF + (size_t)bh * args.Nq * D + (size_t)(q0 / 32) * KS * 1024 + lane * 16;
+#pragma unroll
+    for (int s = 0; s < KS; s++) qf[s] = *(const v4i*)(p + s * 1024);
+  }
+  const float cq = args.sQ[(size_t)bh * nqblk + qblk] * args.scale_log2e;
+
+  float oacc[16];
+#pragma unroll
+  for (int r = 0; r < 16; r++) oacc[r] = 0.f;
+  float w_bias = 0.f, m_ref = -INFINITY, l_part = 0.f;
+  float m_prev[2] = {0.f, 0.f};                                // row maxima of the tiles of the pair that is to be added to O
+
+  bool use_sbias = false;
+  if constexpr (!QSMOOTH) {
+    float smax = 0.f;
+    for (int jj = lane; jj <= last; jj += 64) smax = fmaxf(smax, sKh[jj]);
+    use_sbias = cq * wave_max_nonneg_f32(smax) < 1e-3f;
+  }
+  auto run = [&](auto sbias_tag) __attribute__((always_inline)) {
+    constexpr bool SBIAS = decltype(sbias_tag)::value;
+    // row max over the wave's key block of tile j (logits s; with Q-smoothing they become floats in the log2 domain), into LDS
+    auto half_max = [&](v16i& s, const int pair, const float c, const float* bias_row, auto mask_tag) __attribute__((always_inline)) {
+      constexpr bool MASK = decltype(mask_tag)::value;
+      const int j = 2 * pair + tp;
+      float mown;
+      if constexpr (!QSMOOTH) {
+        int m[2] = {INT_MIN, INT_MIN};
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+          int v = s[r];
+          if constexpr (MASK) {
+            const int key = j * kBlock + 32 * kb + 8 * (r >> 2) + 4 * h + (r & 3);
+            v = key > qlim ? INT_MIN : v;
+            s[r] = v;
+          }
+          m[r >> 3] = max(m[r >> 3], v);
+        }
+        mown = __int_as_float(half_swap_max_i32(max(m[0], m[1])));
+      } else {
+        float m[2] = {-INFINITY, -INFINITY};
+#pragma unroll
+        for (int aa = 0; aa < 4; aa++) {
+          const v4f b4 = *(const v4f*)(bias_row + 32 * kb + 8 * aa + 4 * h);
+#pragma unroll
+          for (int b = 0; b < 4; b++) {
+            float v = __builtin_fmaf((float)s[4 * aa + b], c, b4[b]);
+            if constexpr (MASK) {
+              const int key = j * kBlock + 32 * kb + 8 * aa + 4 * h + b;
+              v = key > qlim ? -INFINITY : v;
+            }
+            s[4 * aa + b] = __float_as_int(v);
+            m[b & 1] = fmaxf(m[b & 1], v);
+          }
+        }
+        mown = half_swap_max_f32(fmaxf(m[0], m[1]));
+      }
+      mxch[pair & 1][qw][w4][ql] = mown;
+    };
+    auto unbias = [&]() __attribute__((always_inline)) {
+      const float corr = kBiasC0 * w_bias;
+#pragma unroll
+      for (int r = 0; r < 16; r++) oacc[r] -= corr;
+      w_bias = 0.f;
+    };
+    // The running reference for a tile of row max mloc, and the sum of its P; returns the weight of its P^V^.
+    auto take_tile = [&](const float mloc, const float psum, const float sv) __attribute__((always_inline)) {
+      if (__builtin_amdgcn_ballot_w64(mloc > m_ref + kTau) != 0) {
+        const float m_new = fmaxf(m_ref, mloc);
+        const float alpha = __builtin_amdgcn_exp2f(m_ref - m_new);     // 0 on the first tile
+        l_part *= alpha;
+        w_bias *= alpha;
+#pragma unroll
+        for (int r = 0; r < 16; r++) oacc[r] *= alpha;
+        m_ref = m_new;
+      }
+      const float beta = __builtin_amdgcn_exp2f(mloc - m_ref);
+      l_part = __builtin_fmaf(beta, psum, l_part);
+      const float w = beta * sv * kTwo26;
+      w_bias += w;
+      return w;
+    };
+    // scales of the tiles of pairs t (sk, sv) and t - 1 (svp).  (Two at a time; past the head's last tile it is whatever lies behind them in the
+    // workspace, which has the codes behind the scales, and multiplies masked logits or nothing.)
+    v2f sk = scalar_load2(sKh), sv = scalar_load2(sVh), svp = {0.f, 0.f};
+    // K^ of pair t + 1 and V^ of pair t - 1 for interval t, read under the end of the interval before
+    v4i ka[KS], va[2][2];
+    auto read_operands = [&](const int8_t* slot) __attribute__((always_inline)) {
+      const int8_t* kl = slot + tp * TILE_BYTES + kb * KS * 1024 + lane * 16;
+      const int8_t* vl = slot + PAIR + cb * 1024 + lane * 16;
+#pragma unroll
+      for (int k = 0; k < KS; k++) ka[k] = *(const v4i*)(kl + k * 1024);
+#pragma unroll
+      for (int k = 0; k < 2; k++)
+#pragma unroll
+        for (int u = 0; u < 2; u++) va[u][k] = *(const v4i*)(vl + u * TILE_BYTES + k * KS * 1024);
+    };
+    // One interval.  PV / SM / SN: pair t - 1 is added to O, tile after tile, pair t quantised, the logits of pair t + 1 formed.
+    auto interval = [&](const int t, v16i& s, v16i& sn, auto pv_tag, auto sm_tag, auto sn_tag, auto mask_tag) __attribute__((always_inline)) {
+      constexpr bool PV = decltype(pv_tag)::value, SM = decltype(sm_tag)::value, SN = decltype(sn_tag)::value;
+      constexpr bool MASK = decltype(mask_tag)::value;
+      asm volatile("" : "+v"(lane_off));
+      const float c[2] = {cq * sk[0], cq * sk[1]};
+      v2f skn = sk, svn = sv;
+      float mx[4], ps[2];
+      v4i p[2][2];
+      if constexpr (SM) {
+#pragma unroll
+        for (int k = 0; k < 4; k++) mx[k] = mxch[t & 1][qw][k][ql];
+      }
+      if constexpr (PV) {
+#pragma unroll
+        for (int u = 0; u < 2; u++) {
+          ps[u] = sxch[(t - 1) & 1][qw][2 * u + kb][lane];
+#pragma unroll
+          for (int k = 0; k < 2; k++) p[u][k] = *(const v4i*)(&pxch[(t - 1) & 1][qw][2 * u + k][lane * 16]);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      float m_pair[2] = {0.f, 0.f}, c_own = 0.f, c_eff = 0.f, off = 0.f;
+      if constexpr (SM) {
+        float bmax_f = 0.f;
+        c_own = tp ? c[1] : c[0];
+#pragma unroll
+        for (int u = 0; u < 2; u++) {
+          if constexpr (!QSMOOTH) {
+            const int mrow = max(__float_as_int(mx[2 * u]), __float_as_int(mx[2 * u + 1]));
+            m_pair[u] = (float)(mrow - (SBIAS ? kBiasBits : 0)) * c[u];
+            if constexpr (SBIAS) bmax_f = tp == u ? __int_as_float(mrow) : bmax_f;
+          } else {
+            m_pair[u] = fmaxf(mx[2 * u], mx[2 * u + 1]);
+          }
+        }
+        c_eff = SBIAS ? c_own * kTwo26 : c_own;
+        off = SBIAS ? __builtin_fmaf(-bmax_f, c_eff, kLog2_127) : kLog2_127 - (tp ? m_pair[1] : m_pair[0]);
+      }
+      // exponents of four logits, formed one slot ahead of their exp2
+      float xn[4] = {0.f, 0.f, 0.f, 0.f};
+      auto form_x = [&](int aa) __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < 4; b++) {
+          float xv;
+          if constexpr (!QSMOOTH) {
+            if constexpr (SBIAS) xv = __builtin_fmaf(__int_as_float(s[4 * aa + b]), c_eff, off);
+            else xv = __builtin_fmaf((float)s[4 * aa + b], c_own, off);
+            if constexpr (MASK) xv = s[4 * aa + b] == INT_MIN ? -INFINITY : xv;
+          } else {
+            xv = __int_as_float(s[4 * aa + b]) + off;
+          }
+          xn[b] = xv;
+        }
+      };
+      if constexpr (SM) form_x(0);
+      v16i tt[2];
+      float psum[4] = {0.f, 0.f, 0.f, 0.f};
+      v4i pf;
+#pragma unroll
+      for (int sl = 0; sl < 5; sl++) {
+        // matrix work: one step of S (D / 32 of them) and, a slot behind (P^ is under way until then), one product of P^V^
+        if constexpr (SN) {
+          const int aa = sl;
+          if (aa >= 0 && aa < KS) {
+            if (aa == 0) {
+              v16i z;
+#pragma unroll
+              for (int r = 0; r < 16; r++) z[r] = 0;
+              sn = SBIAS ? mfma_from_bias(ka[0], qf[0]) : __builtin_amdgcn_mfma_i32_32x32x32_i8(ka[0], qf[0], z, 0, 0, 0);
+            } else {
+              sn = __builtin_amdgcn_mfma_i32_32x32x32_i8(ka[aa], qf[aa], sn, 0, 0, 0);
+            }
+          }
+        }
+        if constexpr (PV) {
+          const int aa = sl - 1;
+          if (aa >= 0) {
+            const int k = aa / 2, u = aa % 2;
+            tt[u] = k == 0 ? mfma_from_bias(va[u][0], p[u][0]) : __builtin_amdgcn_mfma_i32_32x32x32_i8(va[u][1], p[u][1], tt[u], 0, 0, 0);
+          }
+        }
+        // (behind the first waits for LDS: scalar loads come back out of order, and with one under way every such wait is for all)
+        if (SN && sl == 1) {
+          skn = scalar_load2(sKh + 2 * t + 2);
+          svn = scalar_load2(sVh + 2 * t + 2);
+        }
+        if (sl < CPW) copy_piece(t + 2, wr, sl);
+        if (SM && sl < 4) {
+          const int aa = sl;
+          unsigned u = 0;
+          float e[4];
+#pragma unroll
+          for (int b = 0; b < 4; b++) e[b] = __builtin_amdgcn_exp2f(xn[b]);
+          __builtin_amdgcn_sched_barrier(0);
+          if (aa < 3) form_x(aa + 1);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int b = 0; b < 4; b++) {
+            psum[b] = aa == 0 ? e[b] : psum[b] + e[b];
+            pin(psum[b]);
+            u = __builtin_amdgcn_cvt_pk_u8_f32(e[b], b, u);
+          }
+          pf[aa] = (int)u;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int k = 5; k < CPW; k++) copy_piece(t + 2, wr, k);
+      read_operands(rd);
+      if constexpr (SN) half_max(sn, t + 1, cq * (tp ? skn[1] : skn[0]), (const float*)(rd + 2 * PAIR + tp * 256), mask_tag);
+      if constexpr (SM) {
+        *(v4i*)(&pxch[t & 1][qw][w4][lane * 16]) = pf;
+        sxch[t & 1][qw][w4][lane] = (psum[0] + psum[1]) + (psum[2] + psum[3]);
+      }
+      if constexpr (PV) {
+        auto add = [&](const v16i& x, const float w) __attribute__((always_inline)) {
+#pragma unroll
+          for (int r = 0; r < 16; r++) oacc[r] = __builtin_fmaf(__int_as_float(x[r]), w, oacc[r]);
+        };
+        add(tt[0], take_tile(m_prev[0], ps[0], svp[0]));
+        if (!MASK || 2 * t - 1 <= last) {
+          add(tt[1], take_tile(m_prev[1], ps[1], svp[1]));
+          if (((2 * t - 1) & (kBiasPeriod - 1)) == kBiasPeriod - 1) unbias();
+        }
+      }
+      if constexpr (SM) {
+        m_prev[0] = m_pair[0];
+        m_prev[1] = m_pair[1];
+      }
+      // the copies of slot t + 1 (issued one interval ago) have landed; this interval's stay in flight
+      __builtin_amdgcn_s_waitcnt(vmcnt_only(CPW));
+      barrier_lds_only();
+      svp = sv;
+      sk = skn;
+      sv = svn;
+      int8_t* x = rd;
+      rd = mid;
+      mid = wr;
+      wr = x;
+    };
+    using T = std::true_type;
+    using F = std::false_type;
+
+    // pair 0: logits straight from memory
+    v16i sA, sB;
+    const int j0 = min(tp, nblk - 1);
+#pragma unroll
+    for (int r = 0; r < 16; r++) sA[r] = SBIAS ? kBiasBits : 0;
+#pragma unroll
+    for (int k = 0; k < KS; k++)
+      sA = __builtin_amdgcn_mfma_i32_32x32x32_i8(*(const v4i*)(KFh + (size_t)j0 * TILE_BYTES + (kb * KS + k) * 1024 + lane * 16), qf[k], sA, 0, 0, 0);
+    half_max(sA, 0, cq * (tp ? sk[1] : sk[0]), QSMOOTH ? args.bias + ((size_t)bh * nqblk + qblk) * N + j0 * kBlock : nullptr, T{});
+    barrier_all_memory();
+    read_operands(wr);
+    barrier_lds_only();        // (interval 0 copies there)
+
+    // (the masked forms leave visible keys as they are)
+    const int lp = n_pairs - 1;
+    int t = 0;
+    if (lp >= 1) {
+      interval(t++, sA, sB, F{}, T{}, T{}, T{});
+      for (; t + 2 < lp; t += 2) {
+        interval(t, sB, sA, T{}, T{}, T{}, F{});
+        interval(t + 1, sA, sB, T{}, T{}, T{}, F{});
+      }
+      for (; t < lp; t++) {
+        interval(t, sB, sA, T{}, T{}, T{}, T{});
+        sB = sA;
+      }
+      interval(t++, sB, sA, T{}, T{}, F{}, T{});
+      interval(t++, sB, sA, T{}, F{}, F{}, T{});
+    } else {
+      interval(t++, sA, sB, F{}, T{}, F{}, T{});
+      interval(t++, sA, sB, T{}, F{}, F{}, T{});
+    }
+    __builtin_amdgcn_s_waitcnt(vmcnt_only(0));                 // (the copies past the last tile land before the LDS is given up)
+    unbias();
+  };
+  if (__builtin_amdgcn_readfirstlane((int)use_sbias)) run(std::true_type{});
+  else run(std::false_type{});
+
+  // ---- epilogue: O = O / l, L = m + log(l) (l carries a factor 127); the two halves of l meet in LDS ----
+  mxch[0][qw][w4][ql] = half_swap_sum_f32(l_part);
+  barrier_lds_only();
+  if (q >= args.nq_valid) return;                              // a query row that does not exist
+  const float l_tot = mxch[0][qw][0][ql] + mxch[0][qw][1][ql];
+  const float inv_l = 1.0f / l_tot;
+  unsigned short* Oh = args.O + args.oview.row(bh, q);
+  if (w4 < KS) {
+#pragma unroll
+    for (int aa = 0; aa < 4; aa++) {
+      v4us o;
+#pragma unroll
+      for (int b = 0; b < 4; b++) o[b] = float_to_bf16_bits(oacc[4 * aa + b] * inv_l);
+      *(v4us*)(Oh + 32 * cb + 8 * aa + 4 * h) = o;
+    }
+  }
+  if (w4 == 0 && h == 0) args.LSE[(size_t)bh * args.nq_valid + q] = (m_ref + __builtin_amdgcn_logf(l_tot) - kLog2_127) * kLn2;
+}
+
 // ---- few query rows against many keys ----------------------------------------------------------------
 // A workgroup of 8 waves = NQ groups of 32 queries x NS splits of the keys.  Every wave walks its own
 // contiguous range of the workgroup's KV tiles with the arithmetic of sage_fwd_kernel; the partial (O, m, l)

@@ -366,14 +366,28 @@ bool use_fwd_split(const FwdArgs& a) {
 // 1280 42.2 -> 49.1; at d = 64, N = 4096, 1024 waves 67.2 -> 51.3, 1280 69.9 -> 77.2.
 bool use_fwd_pair(const FwdArgs& a) { return (long long)a.BH * ((a.Nq + 31) / 32) <= kSimds; }
 
-// the two forms for calls that do not fill the machine: 64 queries per workgroup
+// Four waves share them (sage_fwd_quad_kernel; same bits): while there is a CU for every 64 queries, and at d = 128 for some workgroups more where
+// the mask makes the second round much the lighter.  Not for a single tile.  Whole calls, us, two waves -> four: 256 workgroups, N = 1024 25.8 ->
+// 23.6, 128 14.2 -> 13.8, 64 9.0 -> 9.5 (d = 64, 200 workgroups); with the mask and d = 128: N = 1024, 320 workgroups 27.8 -> 26.9, 384 27.4 -> 28.8; 2048, 384 38.1 -> 34.7, 512
+// 38.5 -> 38.7; 4096, 384 57.0 -> 47.5, 512 57.8 -> 53.5 (Q-smoothing 74.5 -> 69.0), 640 (one wave) 74.5 -> 79.5; 16384, 512 174 -> 142, 768 243 -> 220; without it 3000, 282 54.9
+// -> 64.3; d = 64: 1024, 384 21.4 -> 23.4, 4096, 512 45.9 -> 46.1.  (A head's codes are addressed with 32 bits.)
+bool use_fwd_quad(const FwdArgs& a, int d, bool causal) {
+  const long long wgs = (long long)a.BH * (a.Nq / 64), nblk = a.N / kBlock;
+  if (nblk < 2 || (long long)a.N * d > (1ll << 30)) return false;
+  if (wgs <= kCus) return true;
+  return d == 128 && causal && a.N == a.Nq && wgs <= kCus + 4 * nblk && wgs <= 3 * kCus;
+}
+
+// the forms for calls that do not fill the machine: 64 queries per workgroup
+enum class FwdForm { pair, quad, split };
 template <int D, bool CAUSAL, bool QS>
-int launch_fwd_small(const FwdArgs& a, bool split, hipStream_t st) {
+int launch_fwd_small(const FwdArgs& a, FwdForm form, hipStream_t st) {
   FwdArgs args = a;
   args.n_qtiles = a.Nq / 64;
   args.head_set = head_set_for(args.n_qtiles, a.BH);
   const int grid = grid_for(a.BH, args.n_qtiles);
-  if (split) sage_fwd_split_kernel<D, CAUSAL, QS, 2, 4><<<grid, 512, 0, st>>>(args);
+  if (form == FwdForm::quad) sage_fwd_quad_kernel<D, CAUSAL, QS><<<grid, 512, 0, st>>>(args);
+  else if (form == FwdForm::split) sage_fwd_split_kernel<D, CAUSAL, QS, 2, 4><<<grid, 512, 0, st>>>(args);
   else sage_fwd_pair_kernel<D, CAUSAL, QS, 2><<<grid, 256, 0, st>>>(args);
   SAGE_LAUNCH_CHECK();
   return SAGEBWD_OK;
@@ -405,8 +419,9 @@ int launch_fwd_full(const FwdArgs& a, bool kv128, hipStream_t st) {
 }
 template <int D, bool CAUSAL, bool QS>
 int launch_fwd_form(const FwdArgs& a, bool kv128, hipStream_t st) {
-  if (!kv128 && use_fwd_split(a)) return launch_fwd_small<D, CAUSAL, QS>(a, true, st);
-  if (!kv128 && use_fwd_pair(a)) return launch_fwd_small<D, CAUSAL, QS>(a, false, st);
+  if (!kv128 && use_fwd_split(a)) return launch_fwd_small<D, CAUSAL, QS>(a, FwdForm::split, st);
+  if (!kv128 && use_fwd_quad(a, D, CAUSAL)) return launch_fwd_small<D, CAUSAL, QS>(a, FwdForm::quad, st);
+  if (!kv128 && use_fwd_pair(a)) return launch_fwd_small<D, CAUSAL, QS>(a, FwdForm::pair, st);
   if constexpr (D == 64 && !QS) {
     if (use_fwd_two_waves(a, CAUSAL)) return launch_fwd_full<D, CAUSAL, QS, 2>(a, kv128, st);
   }

@@ -74,7 +74,7 @@ def test_the_forms_for_calls_that_do_not_fill_the_machine(kernels):
     for k in _pick(kernels, "sage_fwd_pair_kernel"):
         assert k["scratch"] == 0 and k["vgpr"] <= 256 and 2 * k["lds"] <= 160 * 1024, k
     # eight waves and most of the LDS of a CU
-    for k in _pick(kernels, "sage_fwd_split_kernel"):
+    for k in _pick(kernels, "sage_fwd_split_kernel") + _pick(kernels, "sage_fwd_quad_kernel"):
         assert k["scratch"] == 0 and k["vgpr"] <= 256 and k["lds"] <= 160 * 1024, k
     # nothing in scratch
     for k in _pick(kernels, "sage_fwd_decode_kernel"):
