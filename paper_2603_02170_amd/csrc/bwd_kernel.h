@@ -1600,4 +1600,206 @@ __global__ void __launch_bounds__(256, 3) sage_bwd_dq_kernel(DqArgs args) {
   }
 }
 
+// dQ of calls whose launch of the kernel above does not fill the machine: it then takes as long as its longest chain of stages, at about 0.7 us a stage, most of
+// it the latency of one wave's transposition, products and updates in turn.  Here a workgroup owns ONE Q block and takes two stages (KV blocks) an
+// interval; wave (row half, channel block of 32) owns 32 x 32 of dQ, eight waves at d = 128 and four at d = 64, and a fragment of psi(dS) is
+// transposed by one wave only, an interval ahead, and handed on through LDS: 0.4 us a stage.  (An interval first issues all its LDS reads and the
+// transposing product, and the loads behind them; with the transposition hoisted over the barrier of the interval before by the compiler, which then waited for every load in flight, a stage took
+// 0.5.)  Twice the copies of K^ of the kernel above are what a full machine pays.  The order of the sums is that of the kernel above: the same bits.
+// us, kernel above -> this one, with the mask: 8 heads of N = 4096 48.5 -> 25.5, 24 of 2048 28.6 -> 21.5, 6 of 9000 104 -> 69, 2 of 1368 21.0 -> 12.0, 6 of 4467, d = 64, 35.0 ->
+// 24.1; without: 6 of 2297 29.8 -> 16.5, 12 of 768 14.5 -> 9.3 (the rule: use_dq_split).
+template <int D, bool CAUSAL, bool STREAM>
+__global__ void __launch_bounds__(4 * D, D == 128 ? 4 : 2) sage_bwd_dq_split_kernel(DqArgs args) {
+  constexpr int KS = D / 32;               // channel blocks
+  constexpr int NW = 2 * KS;               // waves
+  constexpr int FW = 8 / NW;               // psi(dS) fragments of an interval that a wave transposes
+  constexpr int TILE = 64 * D;             // bytes of one K^ tile
+  constexpr int DSB = 4096;                // bytes of one psi(dS) tile
+  constexpr int NS = 3;                    // ring slots, of two stages each: two intervals run ahead
+  constexpr int KSLOT = 2 * TILE;          // two K^ tiles
+  constexpr int OPS = FW + 2;              // memory operations per wave and interval: psi(dS), K^ copies
+
+  struct Lds {
+    __attribute__((aligned(16))) int8_t ring[NS * KSLOT];
+    __attribute__((aligned(16))) int8_t frag[2][2 * DSB];     // [interval parity]: the transposed tiles
+  };
+  __shared__ __attribute__((aligned(16))) Lds L;
+
+  const int N = args.N;
+  const int nblk = N / kBlock;                         // KV blocks
+  const int nqblk = args.Nq / kBlock;                  // Q blocks
+  const WorkItem wi = work_item(blockIdx.x, nqblk, args.head_set);
+  const int hl = args.last_first ? args.BH - 1 - wi.head : wi.head;
+  const int bh = args.bh0 + hl;
+  const int i = nqblk - 1 - wi.item;                   // longest rows first under the causal mask
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ll = lane & 31, h = lane >> 5;
+  const int qb = wave / KS, cb = wave % KS;            // row half, channel block
+  const int n_j = CAUSAL ? min(i + args.shift_blocks + 1, nblk) : nblk;         // stages
+
+  const size_t row = ((size_t)hl * nqblk + i) * args.ds_pitch;
+  const int8_t* dsw = args.dSq + row * DSB + (wave & 3) * 1024;
+  const int8_t* kth = args.KT + (size_t)bh * N * D + wave * 1024;
+  const float *sds = args.sdS + row, *sks = args.sK + (size_t)bh * nblk;
+  const unsigned lane16 = lane * 16;
+
+  // Stages past the end are clamped (see sage_bwd_dq_kernel).
+  auto stage = [&](int j) { return j < n_j ? j : n_j - 1; };
+  // fragment wave + NW f of the interval's eight: four a stage
+  auto load_ds = [&](int m, v4i (&a)[FW]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int f = 0; f < FW; f++) {
+      const int j = stage(2 * m + (FW == 1 ? wave >> 2 : f));
+      const __attribute__((address_space(1))) v4i* p = (const __attribute__((address_space(1))) v4i*)(uniform(dsw + (size_t)j * DSB) + lane16);
+      a[f] = STREAM ? __builtin_nontemporal_load(p) : *p;
+    }
+  };
+  auto load_k = [&](int m, int sl) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < 2; k++)
+      copy_16(uniform(kth + (size_t)stage(2 * m + k) * TILE) + lane16, L.ring + sl * KSLOT + k * TILE + wave * 1024);
+  };
+
+  v16f acc;
+#pragma unroll
+  for (int r = 0; r < 16; r++) acc[r] = 0.f;
+
+  // (the transposing product: see sage_bwd_dq_kernel)
+  v4i tperm;
+#pragma unroll
+  for (int aa = 0; aa < 4; aa++) {
+    unsigned u = 0;
+#pragma unroll
+    for (int b = 0; b < 4; b++) u |= (unsigned)((8 * aa + 4 * h + b) == ll) << (8 * b);
+    tperm[aa] = (int)u;
+  }
+  auto transposed = [&](const v4i& f) __attribute__((always_inline)) {
+    v16i z;
+#pragma unroll
+    for (int r = 0; r < 16; r++) z[r] = 0;
+    return __builtin_amdgcn_mfma_i32_32x32x32_i8(f, tperm, z, 0, 0, 0);
+  };
+  auto hand_on = [&](const v16i (&tr)[FW], int parity) __attribute__((always_inline)) {
+#pragma unroll
+    for (int f = 0; f < FW; f++) {
+      v4i o;
+#pragma unroll
+      for (int aa = 0; aa < 4; aa++) {
+        const unsigned lo = __builtin_amdgcn_perm((unsigned)tr[f][4 * aa + 1], (unsigned)tr[f][4 * aa], 0x0c0c0400u);
+        const unsigned hi = __builtin_amdgcn_perm((unsigned)tr[f][4 * aa + 3], (unsigned)tr[f][4 * aa + 2], 0x04000c0cu);
+        o[aa] = (int)(lo | hi);
+      }
+      *(v4i*)(L.frag[parity] + (wave + NW * f) * 1024 + lane * 16) = o;
+    }
+  };
+  // s_dS s_K of the two stages of an interval, through the scalar cache, an interval ahead
+  v2f scale;
+  auto load_scale = [&](int m) __attribute__((always_inline)) {
+    const int j = stage(2 * m), j1 = stage(2 * m + 1);
+    scale[0] = scalar_load(sds + j) * scalar_load(sks + j) * args.sm_scale;
+    scale[1] = scalar_load(sds + j1) * scalar_load(sks + j1) * args.sm_scale;
+  };
+  // the operands of the interval's two products of each stage
+  struct Operands {
+    v4i a0[2], a1[2], b0[2], b1[2];
+  };
+  auto read = [&](int sl, int parity, Operands& x) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < 2; k++) {
+      const int8_t* ap = L.frag[parity] + k * DSB + qb * 2048 + lane * 16;
+      const int8_t* bp = L.ring + sl * KSLOT + k * TILE + cb * 1024 + lane * 16;
+      x.a0[k] = *(const v4i*)ap;
+      x.b0[k] = *(const v4i*)bp;
+      x.a1[k] = *(const v4i*)(ap + 1024);
+      x.b1[k] = *(const v4i*)(bp + KS * 1024);
+    }
+  };
+  auto add = [&](const v16i& q, float w) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < 16; r++) acc[r] = __builtin_fmaf(__int_as_float(q[r]) - kBiasC0, w, acc[r]);
+  };
+
+  v4i first[FW], a[2][FW];                 // a[m & 1]: the fragments of interval m
+  load_scale(0);
+  load_ds(0, first);
+#pragma unroll
+  for (int m = 0; m < 2; m++) {
+    load_ds(m + 1, a[(m + 1) & 1]);
+    load_k(m, m);
+    compiler_fence();                      // the waits below count operations in issue order
+  }
+  v16i tr[FW];
+#pragma unroll
+  for (int f = 0; f < FW; f++) tr[f] = transposed(first[f]);
+  hand_on(tr, 0);
+  __builtin_amdgcn_s_waitcnt(vmcnt_only(OPS));   // interval 0 has landed
+  barrier_lds_only();
+
+  // Interval m: transpose the fragments of interval m + 1, contract stages 2m and 2m + 1, start the loads of m + 3 and the copies of m + 2
+  // (into the slot of m - 1: every wave is past the barrier that ended it), wait for the copies of m + 1.
+  int sl = 0, m = 0;                       // slot of interval m
+  auto interval = [&](auto parity_tag) __attribute__((always_inline)) {
+    constexpr int P = decltype(parity_tag)::value;
+    Operands x;
+    read(sl, P, x);
+#pragma unroll
+    for (int f = 0; f < FW; f++) tr[f] = transposed(a[P ^ 1][f]);
+    __builtin_amdgcn_sched_barrier(0);
+    v16i q[2];
+    q[0] = mfma_from_bias(x.a0[0], x.b0[0]);
+    q[0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(x.a1[0], x.b1[0], q[0], 0, 0, 0);
+    hand_on(tr, P ^ 1);
+    load_ds(m + 3, a[P ^ 1]);
+    __builtin_amdgcn_sched_barrier(0);
+    q[1] = mfma_from_bias(x.a0[1], x.b0[1]);
+    q[1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(x.a1[1], x.b1[1], q[1], 0, 0, 0);
+    load_k(m + 2, sl == 0 ? NS - 1 : sl - 1);
+    __builtin_amdgcn_sched_barrier(0);
+    const v2f w = scale;
+    load_scale(m + 1);
+    add(q[0], w[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    add(q[1], w[1]);
+    __builtin_amdgcn_s_waitcnt(vmcnt_only(OPS));
+    barrier_lds_only();
+    __builtin_amdgcn_sched_barrier(0);
+    sl = sl == NS - 1 ? 0 : sl + 1;
+    m++;
+  };
+  const int pairs = n_j / 2;
+  while (m + 1 < pairs) {
+    interval(std::integral_constant<int, 0>{});
+    interval(std::integral_constant<int, 1>{});
+  }
+  auto last = [&](int parity) __attribute__((always_inline)) {
+    Operands x;
+    read(sl, parity, x);
+    v16i q = mfma_from_bias(x.a0[0], x.b0[0]);
+    add(__builtin_amdgcn_mfma_i32_32x32x32_i8(x.a1[0], x.b1[0], q, 0, 0, 0), scale[0]);
+  };
+  if (m < pairs) {
+    interval(std::integral_constant<int, 0>{});
+    if (n_j & 1) last(1);
+  } else if (n_j & 1) {
+    last(0);
+  }
+  barrier_all_memory();    // the clamped copies past the last stage have landed before the ring is reused
+  constexpr int LDQ = D + 8;                                   // padded row, in bf16 elements
+  static_assert(64 * LDQ * 2 <= NS * KSLOT, "the dQ staging must fit the ring");
+  unsigned short* stg = (unsigned short*)L.ring;               // [row][LDQ]
+#pragma unroll
+  for (int aa = 0; aa < 4; aa++)
+#pragma unroll
+    for (int b = 0; b < 4; b++) stg[(32 * qb + 8 * aa + 4 * h + b) * LDQ + 32 * cb + ll] = float_to_bf16_bits(acc[4 * aa + b] * kTwo26);
+  barrier_lds_only();
+  constexpr int CPR = D / 8;                                   // 16-byte pieces per row
+#pragma unroll
+  for (int k = 0; k < 64 * CPR / (64 * NW); k++) {
+    const int c = tid + 64 * NW * k, r = c / CPR, pc = c % CPR;
+    if (64 * i + r < args.nvalid) stream_store((v8us*)(args.dQ + args.cv.row(bh, 64 * i + r) + 8 * pc), *(const v8us*)(stg + r * LDQ + 8 * pc));
+  }
+}
+
 }  // namespace sage

@@ -182,4 +182,19 @@ inline DsTraffic ds_traffic(long long heads, int nblk, int nqblk, int shift_bloc
   return {mb > 100, mb > 400};
 }
 
+// dQ with one Q block per workgroup and its waves on channel blocks (sage_bwd_dq_split_kernel; same bits): while the other form's workgroups, of two Q blocks each, leave
+// much of the machine idle, which walks of all lengths do longer than even ones.  On fuller machines this kernel is still the faster, but its copies and LDS reads cost power
+// that the kernels around it then lack (32 heads of N = 2048: 30.7 -> 26.9, but the backward before it, the same code, 127.5 -> 131.7), so the line lies where the
+// whole training step gains.  Q blocks of all heads: step / dQ kernel, us, two Q blocks per workgroup -> one.  With the mask, d = 128: 512 (N = 2048) 124 / 28 -> 114 / 17, 752
+// (3000) 206 / 38 -> 197 / 27, 768 (2048) 159 / 29 -> 155 / 22, 896 (4096) 279.7 / 52 -> 281.5 / 47, 960 (1500) 149.3 / 24 -> 150.5 / 22, 1024 (4096) 302 / 53 -> 305 / 45; longer
+// walks, 846 (9000) 555 / 105 -> 543 / 71, 1536 (8192) 760 / 152 -> 740 / 123, 2000 (16000) 1497 / 243 -> 1520 / 251; d = 64: 640 (2500) 125 / 23 -> 120 / 17, 768 (2048) 110.5 / 20 -> 109.5
+// / 16, 1008 (1777) 117 / 19 -> 119 / 18.  Without: 512 (2048) 153 / 28 -> 152 / 22.5, (4096) 264.5 / 49 -> 261.5 / 38.5, 640 (2048) 193 / 32 -> 199 / 31, (2500) 230.5 / 37 -> 236 / 36; d
+// = 64: 672 (1777) 135.3 / 20 -> 138 / 21.  One Q block a head leaves half of the other form idle at every size: 4000 heads of N = 64 329 / 40 -> 325 / 35.
+inline bool use_dq_split(long long heads, int nblk, int nqblk, bool causal) {
+  const long long blocks = heads * nqblk;
+  if (nqblk == 1) return true;
+  if (even_walks(nblk, nqblk, causal)) return blocks <= 2 * kCus;
+  return blocks <= (nqblk > 64 ? 6 : 3) * kCus;
+}
+
 }  // namespace sage

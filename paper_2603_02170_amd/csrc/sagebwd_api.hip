@@ -504,7 +504,24 @@ int launch_bwd_wide(const BwdArgs& a, bool causal, hipStream_t st) {
 }
 
 template <int D>
+int launch_bwd_dq_split(const DqArgs& a, bool causal, bool stream, hipStream_t st) {
+  const int nqblk = a.Nq / 64;
+  DqArgs args = a;
+  args.head_set = head_set_for(nqblk, a.BH, true);
+  const int grid = grid_for(a.BH, nqblk);
+  if (causal) {
+    if (stream) sage_bwd_dq_split_kernel<D, true, true><<<grid, 4 * D, 0, st>>>(args);
+    else sage_bwd_dq_split_kernel<D, true, false><<<grid, 4 * D, 0, st>>>(args);
+  } else {
+    if (stream) sage_bwd_dq_split_kernel<D, false, true><<<grid, 4 * D, 0, st>>>(args);
+    else sage_bwd_dq_split_kernel<D, false, false><<<grid, 4 * D, 0, st>>>(args);
+  }
+  SAGE_LAUNCH_CHECK();
+  return SAGEBWD_OK;
+}
+template <int D>
 int launch_bwd_dq(const DqArgs& a, bool causal, bool stream, hipStream_t st) {
+  if (use_dq_split(a.BH, a.N / 64, a.Nq / 64, causal)) return launch_bwd_dq_split<D>(a, causal, stream, st);
   const int npair = (a.Nq / 64 + 1) / 2;    // one workgroup per pair of Q blocks
   DqArgs args = a;
   args.head_set = head_set_for(npair, a.BH, true);   // memory-bound: gains from head sets at every length

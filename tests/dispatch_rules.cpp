@@ -47,6 +47,12 @@ int main() {
     const DsTraffic t = ds_traffic(c.heads, c.nblk, c.nblk, 0, c.causal);
     if (t.load_past != c.load || t.store_past != c.store) return printf("ds_traffic: %d heads of %d blocks, mask %d\n", c.heads, c.nblk, c.causal), 1;
   }
+  // dQ with one Q block per workgroup: heads, key blocks, Q blocks, mask
+  const struct { int heads, nblk, nqblk; bool causal, split; } kDq[] = {{1, 1, 1, true, true}, {5000, 3, 1, false, true}, {24, 32, 32, true, true}, {25, 32, 32, true, false},
+      {12, 64, 64, true, true}, {13, 64, 64, true, false}, {12, 128, 128, true, true}, {13, 128, 128, true, false}, {16, 32, 32, false, true}, {17, 32, 32, false, false},
+      {64, 64, 8, true, true}, {65, 64, 8, true, false}};
+  for (const auto& c : kDq)
+    if (use_dq_split(c.heads, c.nblk, c.nqblk, c.causal) != c.split) return printf("use_dq_split: %d heads of %d x %d blocks, mask %d\n", c.heads, c.nqblk, c.nblk, c.causal), 1;
   // groups of heads: whole rounds where the walks are even (no mask, or few queries against many keys) and the workgroups have four
   // blocks; else all that fit
   if (bwd_heads_of_group(7, 32, 512, 512, 0, false, true) != 6 || bwd_heads_of_group(9, 16, 128, 128, 0, false, true) != 8 ||

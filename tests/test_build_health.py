@@ -55,6 +55,11 @@ def test_backward_kernels_keep_their_loops_free_of_scratch(kernels):
             assert k["lds"] <= 160 * 1024
     for k in _pick(kernels, "sage_bwd_kernel"):
         assert k["scratch"] <= 24 and k["vgpr"] <= 256 and k["lds"] <= 160 * 1024, k
+    for k in _pick(kernels, "sage_bwd_dq_split_kernel", "ILi128E"):
+        # two workgroups of eight waves per CU
+        assert k["scratch"] == 0 and k["vgpr"] <= 128 and 2 * k["lds"] <= 160 * 1024, k
+    for k in _pick(kernels, "sage_bwd_dq_split_kernel", "ILi64E"):
+        assert k["scratch"] == 0 and k["vgpr"] <= 168 and 3 * k["lds"] <= 160 * 1024, k
     for k in _pick(kernels, "sage_bwd_dq_kernel"):
         # three workgroups of four waves per CU: 168 registers, a third of the LDS
         assert k["scratch"] == 0 and k["vgpr"] <= 168 and 3 * k["lds"] <= 160 * 1024, k
