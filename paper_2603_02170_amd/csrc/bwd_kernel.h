@@ -68,6 +68,7 @@ struct BwdArgs {
   int nq_valid;        // query rows >= nq_valid do not exist
   int shift_blocks;    // causal: Q block i sees KV blocks j <= i + shift_blocks ((N_kv - N_q) / 64), diagonal at equality
   int head_set;        // heads per XCD whose work items are interleaved (see work_item)
+  int fold_end;        // order of the first workgroups (see folded)
   float sm_scale;
   float scale_log2e;
 };
@@ -666,7 +667,7 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_single_kernel(BwdArgs args) {
   const int nblk = N / kBlock;        // KV blocks
   const int nqblk = args.Nq / kBlock; // Q blocks
   const int sb = CAUSAL ? args.shift_blocks : 0;
-  const WorkItem wi = work_item(blockIdx.x, nblk, args.head_set);
+  const WorkItem wi = work_item(D == 64 ? folded(blockIdx.x, args.fold_end) : blockIdx.x, nblk, args.head_set);
   const int hl = wi.head;
   const int bh = args.bh0 + hl;
   const int j = wi.item;              // small j = most Q blocks under the causal mask: scheduled first

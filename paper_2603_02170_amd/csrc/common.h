@@ -248,6 +248,22 @@ __host__ __device__ inline WorkItem work_item(int block, int items, int head_set
   return WorkItem{xcd + xcds * (hset * hs + rem % hs), rem / hs};
 }
 
+// Which of a launch's workgroups share a CU.  The first of an XCD go round its 32 CUs, heaviest first, so that a CU's second workgroup is its 33rd: with the mask the CU
+// with the heaviest first one gets the heaviest second one too, and a launch of about one round takes as long as that CU.  The second 32 (up to `end`) in reverse
+// order give every CU about the same.  us, heaviest first -> this way: forward, 32 heads of N = 2048 44.6 -> 42.4 (blocks of 128), 64 of 1024 29.1 -> 26.0, 8 of 8192 134 -> 123, 9
+// of 7000 119 -> 107; d = 64, 36 of 1777 28.6 -> 27.1, 12 of 8192 158 -> 118; backward, d = 64 (sage_bwd_single_kernel), 10 of 3000 64.5 -> 56.0, 6 of 4096 71.0
+// -> 68.3, 36 of 1777 56.7 -> 55.5.
+__host__ __device__ inline int folded(int block, int end) {
+  const int slot = block >> 3;
+  return slot >= 32 && slot < end ? (32 + end - 1 - slot) << 3 | (block & 7) : block;
+}
+// Up to `rounds` times the CUs, and some more where walks are long (forward, us: 12 heads of N = 6000, 564 workgroups, 104 -> 100.5; d = 64, 24 of 4096, 768, 62.2 -> 59.3, but 64 of 1500,
+// 768, 31.2 -> 32.1); launches of several rounds give out their workgroups as CUs get free.
+__host__ __device__ inline int fold_end(int grid, int items, int rounds) {
+  if (grid <= 256 || grid > (items >= 24 && rounds < 3 ? 3 : rounds) * 256) return 0;
+  return grid / 8 < 64 ? grid / 8 : 64;
+}
+
 // Row of K or V that a load of sage_fwd_decode_kernel for row `row` reads: a row that does not exist re-reads the last one that does (which changes no
 // maximum of its block), and all rows of a block that is not the wave's (`mine` false: the load ahead of a wave's last block) are one
 // row.  The loop stays without a branch, and no block is read twice (two sequences of 32 heads of 8192 keys, where that was an eighth of

@@ -62,6 +62,7 @@ struct FwdArgs {
   int shift;            // causal: query i sees keys k <= i + shift (N_kv - N_q, a multiple of 64)
   int n_qtiles;         // workgroups per head
   int head_set;         // heads per XCD whose work items are interleaved (see work_item)
+  int fold_end;         // order of the first workgroups (see folded)
   float scale_log2e;    // sm_scale * log2(e)
 };
 
@@ -385,7 +386,7 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 3 : 2) sage_fwd_kernel(FwdA
 
   // workgroup -> (head, query tile): a head's tiles share one XCD's L2; heaviest (last) query
   // tiles first under the causal mask, over sets of heads (see work_item)
-  const WorkItem wi = work_item(blockIdx.x, args.n_qtiles, args.head_set);
+  const WorkItem wi = work_item(folded(blockIdx.x, args.fold_end), args.n_qtiles, args.head_set);
   const int bh = wi.head;
   const int qt = args.n_qtiles - 1 - wi.item;
 
@@ -640,7 +641,7 @@ __global__ void __launch_bounds__(128 * NQ, 2) sage_fwd_pair_kernel(FwdArgs args
   auto& pxch = L.pxch;
   auto& mxch = L.mxch;
 
-  const WorkItem wi = work_item(blockIdx.x, args.n_qtiles, args.head_set);
+  const WorkItem wi = work_item(folded(blockIdx.x, args.fold_end), args.n_qtiles, args.head_set);
   const int bh = wi.head;
   const int qt = args.n_qtiles - 1 - wi.item;
   const int tid = threadIdx.x;
