@@ -567,6 +567,43 @@ __global__ void __launch_bounds__(256) qsmooth_bias_kernel(const unsigned short*
   }
 }
 
+// The same table for at most 16 Q blocks, where the kernel above has no Q blocks for two of its waves and half a tile of rows that do not exist for the others: wave w
+// forms 16 Q blocks x keys 16 w .. with 16x16x4 products, both operands straight from the tensors, without LDS or a barrier.  The contraction order is free,
+// so lane (row or column r, g = lane / 16) contracts channels 32 u + 8 g .. + 7 and the four lanes of a row read whole pieces of a line.  (Bound by latency, as the kernel
+// above is there.)  Whole forward calls, us: 8 heads of N = 512 23.0 -> 20.7; d = 64, 36 heads of 1024 the training step 88.9 -> 85.1.  From 17 Q blocks on the larger
+// products are the faster ones (32 heads of N = 2048 215.5 -> 216.4, 64 of 8192 with all tiles this way 172 -> 200 for the table).
+template <int D>
+__global__ void __launch_bounds__(256) qsmooth_bias_short_kernel(const unsigned short* __restrict__ K, RowView view,
+                                                                 const float* __restrict__ muK, const float* __restrict__ muQ,
+                                                                 float* __restrict__ bias, int N, int Np, int nqblk,
+                                                                 int causal_shift, float scale_log2e) {
+  constexpr int NV = D / 16;                     // 16-byte pieces of FP32 of a lane
+  const int kblk = blockIdx.x, bh = blockIdx.y;
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const int key = kblk * kBlock + 16 * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // first of the wave
+  const unsigned short* src = K + view.row(bh, min(key + r, N - 1)) + 8 * g;
+  const float* mk = muK + (size_t)bh * D + 8 * g;
+  const float* mq = muQ + ((size_t)bh * nqblk + min(r, nqblk - 1)) * D + 8 * g;              // Q blocks past the end repeat the last one (not stored)
+  v4f acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};                                 // two chains over alternate steps, summed at the end
+#pragma unroll
+  for (int v = 0; v < NV; v++) {
+    const v4us raw = *(const v4us*)(src + 32 * (v / 2) + 4 * (v % 2));
+    const v4f m = *(const v4f*)(mk + 32 * (v / 2) + 4 * (v % 2)), q = *(const v4f*)(mq + 32 * (v / 2) + 4 * (v % 2));
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const float k = key + r < N ? bf16_bits_to_float(raw[e]) - m[e] : 0.f;                 // keys that do not exist count as zero rows
+      acc[e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(k, q[e], acc[e & 1], 0, 0, 0);
+    }
+  }
+  // register e of lane (r, g): key 4 g + e of the wave, Q block r
+  if (r < nqblk && (causal_shift < 0 || kblk <= r + causal_shift)) {
+    v4f o;
+#pragma unroll
+    for (int e = 0; e < 4; e++) o[e] = (acc[0][e] + acc[1][e]) * scale_log2e;
+    *(v4f*)(bias + ((size_t)bh * nqblk + r) * Np + key + 4 * g) = o;
+  }
+}
+
 // ---- inspection: the psi(dS) tiles the backward left in its scratch, as a row-major [Np, Np] matrix ----
 // Tile (i, j) holds four 1 KiB fragments (32-query block qb, 32-key block kb): lane (key, half), byte
 // 4 a + b = psi(dS)[64 i + 32 qb + 8 a + 4 half + b][64 j + 32 kb + key] (a quantised accumulator quadrant

@@ -328,9 +328,14 @@ int run_prepass(const void* Q, const void* K, const void* V, const void* dO, con
     RowView dense;
     dense.H = p.H;
     dense.batch_stride = (size_t)p.H * Nkp * D; dense.head_stride = (size_t)Nkp * D; dense.row_stride = D;
-    qsmooth_bias_kernel<D><<<dim3(Nkp / 64, BH), 256, 0, st>>>(
-        qkn ? (const unsigned short*)(ws + w.Knorm) : (const unsigned short*)K, qkn ? dense : kview, muK,
-        (const float*)(ws + w.muQ), (float*)(ws + w.bias), Nk, Nkp, Nqp / 64, p.causal ? (Nk - Nq) / 64 : -1, sl2);
+    const unsigned short* keys = qkn ? (const unsigned short*)(ws + w.Knorm) : (const unsigned short*)K;
+    const RowView kv = qkn ? dense : kview;
+    const float* muQ = (const float*)(ws + w.muQ);
+    float* bias = (float*)(ws + w.bias);
+    const int shift = p.causal ? (Nk - Nq) / 64 : -1;
+    const dim3 bgrid(Nkp / 64, BH);
+    if (Nqp / 64 <= 16) qsmooth_bias_short_kernel<D><<<bgrid, 256, 0, st>>>(keys, kv, muK, muQ, bias, Nk, Nkp, Nqp / 64, shift, sl2);
+    else qsmooth_bias_kernel<D><<<bgrid, 256, 0, st>>>(keys, kv, muK, muQ, bias, Nk, Nkp, Nqp / 64, shift, sl2);
     SAGE_LAUNCH_CHECK();
   }
   return SAGEBWD_OK;
