@@ -199,7 +199,7 @@ __global__ void __launch_bounds__(512, MODE == kBwdMaxOnly ? 4 : 1) sage_bwd_ker
   const int nqblk = args.Nq / kBlock; // Q blocks
   const int sb = CAUSAL ? args.shift_blocks : 0;
   const int npair = (nblk + 1) / 2;
-  const WorkItem wi = work_item(gidx, npair, args.head_set);
+  const WorkItem wi = work_item(MODE == kBwdMaxOnly ? folded(gidx, args.fold_end) : gidx, npair, args.head_set);
   const int hl = wi.head;             // head within this launch
   const int bh = args.bh0 + hl;
   const int jp = wi.item;             // small jp = most Q blocks under the causal mask: scheduled first
@@ -568,7 +568,8 @@ __global__ void __launch_bounds__(512, MODE == kBwdMaxOnly ? 4 : 1) sage_bwd_ker
   // (under the mask: while Q block itop - ISTEP * t lies above the group's diagonal block j - sb)
   const int t_steady_end = (!gvalid || kvalid < 64) ? 0 : (CAUSAL ? min((itop + sb - j + ISTEP - 1) / ISTEP, T - 1) : T - 1);
   int t = 0;
-  for (; t < 2 && t < T + 2; t++) interval(t, std::false_type{}, std::false_type{});
+  constexpr int DRAIN = MODE == kBwdMaxOnly ? 1 : 2;       // phases behind A
+  for (; t < DRAIN && t < T + DRAIN; t++) interval(t, std::false_type{}, std::false_type{});
   // (the second group's waves take phase B before phase A: the two waves of a SIMD then do not reach the
   // MFMA-dense phase at the same time)
   if (grp == 0) {
@@ -576,7 +577,7 @@ __global__ void __launch_bounds__(512, MODE == kBwdMaxOnly ? 4 : 1) sage_bwd_ker
   } else {
     for (; t < t_steady_end; t++) interval(t, std::true_type{}, std::true_type{});
   }
-  for (; t < T + 2; t++) interval(t, std::false_type{}, std::false_type{});
+  for (; t < T + DRAIN; t++) interval(t, std::false_type{}, std::false_type{});
 
   if (!gvalid) return;
 

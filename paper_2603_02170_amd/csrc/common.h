@@ -252,7 +252,7 @@ __host__ __device__ inline WorkItem work_item(int block, int items, int head_set
 // with the heaviest first one gets the heaviest second one too, and a launch of about one round takes as long as that CU.  The second 32 (up to `end`) in reverse
 // order give every CU about the same.  us, heaviest first -> this way: forward, 32 heads of N = 2048 44.6 -> 42.4 (blocks of 128), 64 of 1024 29.1 -> 26.0, 8 of 8192 134 -> 123, 9
 // of 7000 119 -> 107; d = 64, 36 of 1777 28.6 -> 27.1, 12 of 8192 158 -> 118; backward, d = 64 (sage_bwd_single_kernel), 10 of 3000 64.5 -> 56.0, 6 of 4096 71.0
-// -> 68.3, 36 of 1777 56.7 -> 55.5.
+// -> 68.3, 36 of 1777 56.7 -> 55.5; the sweep for the maxima of blocks of 128 queries with the sweep behind it, 32 of 2048 126.2 -> 124.3, the whole step 225.3 -> 221.7, 24 of 1700 174 -> 165.
 __host__ __device__ inline int folded(int block, int end) {
   const int slot = block >> 3;
   return slot >= 32 && slot < end ? (32 + end - 1 - slot) << 3 | (block & 7) : block;

@@ -447,6 +447,7 @@ int launch_bwd(const BwdArgs& a, bool causal, bool qs, hipStream_t st) {
   BwdArgs args = a;
   args.head_set = head_set_for(npair, a.BH);
   const int grid = grid_for(a.BH, npair);
+  args.fold_end = causal && MODE == kBwdMaxOnly ? fold_end(grid, npair, 2) : 0;
   if (causal) {
     if (qs) sage_bwd_kernel<D, true, true, MODE, KV128><<<grid, 512, 0, st>>>(args);
     else sage_bwd_kernel<D, true, false, MODE, KV128><<<grid, 512, 0, st>>>(args);
