@@ -1417,8 +1417,14 @@ struct DqArgs {
   int shift_blocks;     // causal: Q block i sees KV blocks j <= i + shift_blocks
   int head_set;         // heads per XCD whose work items are interleaved (see work_item)
   int last_first;       // the last heads first: their tiles are still cached (see ds_traffic)
-  float sm_scale;
+  float sm_scale;       // times 2^13
 };
+
+// The INT32 sums arrive as a 2^-26 (mfma_from_bias).  Half of that is made up in the weights (sm_scale), half at the end, so that gradients as
+// large and as small as FP32 holds come out as with converted sums: with all of it at the end the sums of gradients below 2^-100 were
+// denormal.
+constexpr float kDqWeight = 8192.0f;
+static_assert(kDqWeight * kDqWeight == kTwo26, "the two halves");
 
 // A workgroup of 4 waves owns TWO Q blocks (128 queries) and walks the KV blocks j; wave (Q block, row half)
 // owns 32 query rows and ALL d channels.  A stored psi(dS) fragment holds one KEY per lane and 16 queries in
@@ -1591,7 +1597,7 @@ __global__ void __launch_bounds__(256, 3) sage_bwd_dq_kernel(DqArgs args) {
       for (int aa = 0; aa < 4; aa++)
 #pragma unroll
         for (int b = 0; b < 4; b++)
-          stg[(iq * 64 + 32 * qb + 8 * aa + 4 * h + b) * LDQ + 32 * cb + ll] = float_to_bf16_bits(acc[cb][4 * aa + b] * kTwo26);
+          stg[(iq * 64 + 32 * qb + 8 * aa + 4 * h + b) * LDQ + 32 * cb + ll] = float_to_bf16_bits(acc[cb][4 * aa + b] * kDqWeight);
   }
   barrier_lds_only();
   constexpr int CPR = D / 8;                                   // 16-byte pieces per row
@@ -1794,7 +1800,7 @@ __global__ void __launch_bounds__(4 * D, D == 128 ? 4 : 2) sage_bwd_dq_split_ker
 #pragma unroll
   for (int aa = 0; aa < 4; aa++)
 #pragma unroll
-    for (int b = 0; b < 4; b++) stg[(32 * qb + 8 * aa + 4 * h + b) * LDQ + 32 * cb + ll] = float_to_bf16_bits(acc[4 * aa + b] * kTwo26);
+    for (int b = 0; b < 4; b++) stg[(32 * qb + 8 * aa + 4 * h + b) * LDQ + 32 * cb + ll] = float_to_bf16_bits(acc[4 * aa + b] * kDqWeight);
   barrier_lds_only();
   constexpr int CPR = D / 8;                                   // 16-byte pieces per row
 #pragma unroll

@@ -876,7 +876,7 @@ int sagebwd_bwd(const void* Q, const void* K, const void* V, const void* O, cons
   q.N = Nkp;
   q.Nq = Nqp;
   q.shift_blocks = shift_blocks;
-  q.sm_scale = a.sm_scale;
+  q.sm_scale = a.sm_scale * kDqWeight;
   const bool wide_form = d == 128 && !(qs && big);
   for (int h0 = 0, nh = 0; h0 < BH; h0 += nh) {
     nh = bwd_heads_of_group(w.heads_per_group, BH - h0, Nkp / 64, Nqp / 64, shift_blocks, params->causal != 0, wide_form);
