@@ -24,7 +24,7 @@ HBM_PEAK_GBS = 8000.0       # MI355X HBM3E peak (published)
 # HBM bytes per launch at the headline workload.  NOT measured in this run: taken from the committed
 # rocprofv3 FETCH_SIZE / WRITE_SIZE runs summarised in profiles/hbm_traffic_cases.txt
 # (scaled by the copy-kernel calibration stated there).
-PROFILED_TRAFFIC_BYTES = {"headline": {"bwd": 5.2355e9, "fwd": 3.381e8, "bwd_dq": 2.6384e9}}
+PROFILED_TRAFFIC_BYTES = {"headline": {"bwd": 5.0164e9, "fwd": 3.381e8, "bwd_dq": 2.4924e9}}
 
 
 def work_ops(w, fwd=True, bwd=True, matmuls=None):
@@ -201,6 +201,8 @@ def main():
     # (four rounds of its workgroups and more always take that kernel; below, the rule on sizes decides)
     wide = w.d == 128 and w.B * w.H * -(-w.N // 256) >= 1024
     bwd_kernel = "sage_bwd_wide_kernel" if wide else "backward kernel (by shape)"
+    # (and more than 1536 Q blocks, more than one a head, the two-block form of dQ)
+    dq_kernel = "sage_bwd_dq_kernel" if w.N > 64 and w.B * w.H * -(-w.N // 64) > 1536 else "dQ kernel (by shape)"
     fwd_ops = work_ops(w, bwd=False)
     bwd_tops = bwd_ops / (kern["bwd"] * 1e-3) / 1e12
     fwd_tops = fwd_ops / (kern["fwd"] * 1e-3) / 1e12
@@ -246,7 +248,7 @@ def main():
         "roofline_fwd": {"bound": "mfma", "kernel": "sage_fwd_kernel", "achieved": fwd_tops, "peak": INT8_PEAK_TOPS,
                          "unit": "TOP/s", "frac": fwd_tops / INT8_PEAK_TOPS, "traffic": traffic.get("fwd"),
                          "frac_of_measured_peak": fwd_tops / peaks["int8_mfma"]["value"]},
-        "roofline_bwd_dq": {"bound": "hbm", "kernel": "sage_bwd_dq_kernel",
+        "roofline_bwd_dq": {"bound": "hbm", "kernel": dq_kernel,
                             "achieved": dq_bytes / (kern["bwd_dq"] * 1e-3) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                             "frac": dq_bytes / (kern["bwd_dq"] * 1e-3) / 1e9 / HBM_PEAK_GBS,
                             "traffic": traffic.get("bwd_dq"),
