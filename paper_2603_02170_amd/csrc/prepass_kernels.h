@@ -585,31 +585,34 @@ __global__ void __launch_bounds__(256) qsmooth_bias_kernel(const unsigned short*
 }
 
 // The same table for at most 16 Q blocks, where the kernel above has no Q blocks for two of its waves and half a tile of rows that do not exist for the others: wave w
-// forms 16 Q blocks x keys 16 w .. with 16x16x4 products, both operands straight from the tensors, without LDS or a barrier.  The contraction order is free,
-// so lane (row or column r, g = lane / 16) contracts channels 32 u + 8 g .. + 7 and the four lanes of a row read whole pieces of a line.  (Bound by latency, as the kernel
-// above is there.)  Whole forward calls, us: 8 heads of N = 512 23.0 -> 20.7; d = 64, 36 heads of 1024 the training step 88.9 -> 85.1.  From 17 Q blocks on the larger
-// products are the faster ones (32 heads of N = 2048 215.5 -> 216.4, 64 of 8192 with all tiles this way 172 -> 200 for the table).
+// forms 16 Q blocks x keys 16 w .. with 16x16x4 products, both operands straight from the tensors, without LDS or a barrier.  Step (v, p) contracts
+// channels 8 v + p + 0, 4, 2, 6 in the four lanes of a row, which is the order in which two steps of the kernel above do: the same bits, so that no logit falls to the other side of
+// a rounding.  The four lanes of a row read whole 16-byte pieces.  (Bound by latency, as the kernel
+// above is there.)  Whole calls, us, the kernel above -> this one: forward of 8 heads of N = 512 24.7 -> 23.6; training steps, 16 of
+// 1000 83.9 -> 74.5, d = 64, 13 of 1008 65.2 -> 59.9, 40 of 41 31.5 -> 29.4.  Its narrow loads cost more from two workgroups per CU on: forward of 200 heads of N = 256 (800
+// workgroups) 43.2 -> 44.2, d = 64, 34 of 448 against 1408 keys (748) 31.0 -> 32.0, the step of 54 of 648 (594) 101.3 -> 102.1; and from 17 Q blocks on the larger
+// products are the faster ones (32 heads of N = 2048 215.5 -> 216.4).
 template <int D>
 __global__ void __launch_bounds__(256) qsmooth_bias_short_kernel(const unsigned short* __restrict__ K, RowView view,
                                                                  const float* __restrict__ muK, const float* __restrict__ muQ,
                                                                  float* __restrict__ bias, int N, int Np, int nqblk,
                                                                  int causal_shift, float scale_log2e) {
-  constexpr int NV = D / 16;                     // 16-byte pieces of FP32 of a lane
   const int kblk = blockIdx.x, bh = blockIdx.y;
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const int c0 = 4 * (g & 1) + 2 * (g >> 1);     // first channel of the lane's in every eight
   const int key = kblk * kBlock + 16 * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);     // first of the wave
-  const unsigned short* src = K + view.row(bh, min(key + r, N - 1)) + 8 * g;
-  const float* mk = muK + (size_t)bh * D + 8 * g;
-  const float* mq = muQ + ((size_t)bh * nqblk + min(r, nqblk - 1)) * D + 8 * g;              // Q blocks past the end repeat the last one (not stored)
-  v4f acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};                                 // two chains over alternate steps, summed at the end
+  const unsigned short* src = K + view.row(bh, min(key + r, N - 1)) + c0;
+  const float* mk = muK + (size_t)bh * D + c0;
+  const float* mq = muQ + ((size_t)bh * nqblk + min(r, nqblk - 1)) * D + c0;                 // Q blocks past the end repeat the last one (not stored)
+  v4f acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};                                 // two chains over alternate channels, summed at the end
 #pragma unroll
-  for (int v = 0; v < NV; v++) {
-    const v4us raw = *(const v4us*)(src + 32 * (v / 2) + 4 * (v % 2));
-    const v4f m = *(const v4f*)(mk + 32 * (v / 2) + 4 * (v % 2)), q = *(const v4f*)(mq + 32 * (v / 2) + 4 * (v % 2));
+  for (int v = 0; v < D / 8; v++) {
+    const unsigned raw = *(const unsigned*)(src + 8 * v);
+    const v2f m = *(const v2f*)(mk + 8 * v), q = *(const v2f*)(mq + 8 * v);
 #pragma unroll
-    for (int e = 0; e < 4; e++) {
-      const float k = key + r < N ? bf16_bits_to_float(raw[e]) - m[e] : 0.f;                 // keys that do not exist count as zero rows
-      acc[e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(k, q[e], acc[e & 1], 0, 0, 0);
+    for (int p = 0; p < 2; p++) {
+      const float k = key + r < N ? bf16_bits_to_float((unsigned short)(raw >> (16 * p))) - m[p] : 0.f;      // keys that do not exist count as zero rows
+      acc[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(k, q[p], acc[p], 0, 0, 0);
     }
   }
   // register e of lane (r, g): key 4 g + e of the wave, Q block r
