@@ -668,7 +668,7 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_single_kernel(BwdArgs args) {
   const int nblk = N / kBlock;        // KV blocks
   const int nqblk = args.Nq / kBlock; // Q blocks
   const int sb = CAUSAL ? args.shift_blocks : 0;
-  const WorkItem wi = work_item(D == 64 ? folded(blockIdx.x, args.fold_end) : blockIdx.x, nblk, args.head_set);
+  const WorkItem wi = work_item(D == 64 && !QSMOOTH ? folded(blockIdx.x, args.fold_end) : blockIdx.x, nblk, args.head_set);
   const int hl = wi.head;
   const int bh = args.bh0 + hl;
   const int j = wi.item;              // small j = most Q blocks under the causal mask: scheduled first

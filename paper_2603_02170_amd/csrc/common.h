@@ -248,19 +248,25 @@ __host__ __device__ inline WorkItem work_item(int block, int items, int head_set
   return WorkItem{xcd + xcds * (hset * hs + rem % hs), rem / hs};
 }
 
-// Which of a launch's workgroups share a CU.  The first of an XCD go round its 32 CUs, heaviest first, so that a CU's second workgroup is its 33rd: with the mask the CU
-// with the heaviest first one gets the heaviest second one too, and a launch of about one round takes as long as that CU.  The second 32 (up to `end`) in reverse
-// order give every CU about the same.  us, heaviest first -> this way: forward, 32 heads of N = 2048 44.6 -> 42.4 (blocks of 128), 64 of 1024 29.1 -> 26.0, 8 of 8192 134 -> 123, 9
-// of 7000 119 -> 107; d = 64, 36 of 1777 28.6 -> 27.1, 12 of 8192 158 -> 118; backward, d = 64 (sage_bwd_single_kernel), 10 of 3000 64.5 -> 56.0, 6 of 4096 71.0
-// -> 68.3, 36 of 1777 56.7 -> 55.5; the sweep for the maxima of blocks of 128 queries with the sweep behind it, 32 of 2048 126.2 -> 124.3, the whole step 225.3 -> 221.7, 24 of 1700 174 -> 165.
+// Which of a launch's workgroups share a CU, for kernels of which two or more fit one.  The first of an XCD go round its 32
+// CUs, heaviest first, so that a CU's second workgroup is its 33rd: with the mask the CU with the heaviest first one gets the
+// heaviest second one too, and a launch of about one round takes as long as that CU.  The second 32 (up to `end`) in reverse
+// order give every CU about the same.  us, heaviest first -> this way: forward, 32 heads of N = 2048 44.6 -> 42.4 (blocks of
+// 128), 64 of 1024 29.1 -> 26.0, 8 of 8192 134 -> 123, 9 of 7000 119 -> 107; d = 64, 36 of 1777 28.6 -> 27.1, 12 of 8192 158 ->
+// 118; backward, d = 64 (sage_bwd_single_kernel), 10 of 3000 64.5 -> 56.0, 6 of 4096 71.0 -> 68.3, 36 of 1777 56.7 -> 55.5; the
+// sweep for the maxima of blocks of 128 queries with the sweep behind it, 32 of 2048 126.2 -> 124.3, the whole step 225.3 ->
+// 221.7, 24 of 1700 174 -> 165.
 __host__ __device__ inline int folded(int block, int end) {
   const int slot = block >> 3;
   return slot >= 32 && slot < end ? (32 + end - 1 - slot) << 3 | (block & 7) : block;
 }
-// Up to `rounds` times the CUs, and some more where walks are long (forward, us: 12 heads of N = 6000, 564 workgroups, 104 -> 100.5; d = 64, 24 of 4096, 768, 62.2 -> 59.3, but 64 of 1500,
-// 768, 31.2 -> 32.1); launches of several rounds give out their workgroups as CUs get free.
-__host__ __device__ inline int fold_end(int grid, int items, int rounds) {
-  if (grid <= 256 || grid > (items >= 24 && rounds < 3 ? 3 : rounds) * 256) return 0;
+// Up to `rounds` times the CUs, and some more where walks are long (forward, us: 12 heads of N = 6000, 564 workgroups, 104 ->
+// 100.5; d = 64, 24 of 4096, 768, 62.2 -> 59.3, but 64 of 1500, 768, 31.2 -> 32.1); launches of several rounds give out their
+// workgroups as CUs get free.  So does one of a kernel that has a CU to itself (per_cu = 1): the lightest of the first 32 is
+// done first and has to get the heaviest of the second (backward of d = 64 with Q-smoothing, us, this way -> heaviest first: 16
+// heads of N = 2048 57.5 -> 47.6, 8 of 4096 98.5 -> 80.5, 32 of 1024 36.3 -> 30.9, 40 of 700 28.5 -> 24.8).
+__host__ __device__ inline int fold_end(int grid, int items, int rounds, int per_cu) {
+  if (per_cu < 2 || grid <= 256 || grid > (items >= 24 && rounds < 3 ? 3 : rounds) * 256) return 0;
   return grid / 8 < 64 ? grid / 8 : 64;
 }
 

@@ -6,6 +6,11 @@ namespace sage {
 // CUs of the machine: what a launch has to fill (four SIMDs each).
 constexpr int kCus = 256;
 
+// Workgroups that fit a CU, of the kernels whose launches are folded (see common.h; a test reads registers and LDS from the build).
+inline int fwd_per_cu(int d) { return d == 64 ? 3 : 2; }          // sage_fwd_kernel; sage_fwd_pair_kernel: at least two
+constexpr int kMaxSweepPerCu = 2;                                 // sage_bwd_kernel, the sweep for the maxima
+inline int bwd_single_per_cu(int d, bool q_smooth) { return d == 64 && !q_smooth ? 2 : 1; }
+
 // ---- decoding: sage_fwd_decode_kernel -----------------------------------------------------------------
 // A query block of at most 32 rows that sees every key takes that kernel, which quantises K and V itself, instead of codes in the
 // workspace: with a long cache, or with many heads (its code is long, and with little work few workgroups share the cost of

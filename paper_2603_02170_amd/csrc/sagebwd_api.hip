@@ -391,7 +391,7 @@ int launch_fwd_small(const FwdArgs& a, FwdForm form, hipStream_t st) {
   args.n_qtiles = a.Nq / 64;
   args.head_set = head_set_for(args.n_qtiles, a.BH);
   const int grid = grid_for(a.BH, args.n_qtiles);
-  args.fold_end = CAUSAL ? fold_end(grid, args.n_qtiles, 2) : 0;
+  args.fold_end = CAUSAL && form == FwdForm::pair ? fold_end(grid, args.n_qtiles, 2, 2) : 0;      // (the other two have a CU to themselves)
   if (form == FwdForm::quad) sage_fwd_quad_kernel<D, CAUSAL, QS><<<grid, 512, 0, st>>>(args);
   else if (form == FwdForm::split) sage_fwd_split_kernel<D, CAUSAL, QS, 2, 4><<<grid, 512, 0, st>>>(args);
   else sage_fwd_pair_kernel<D, CAUSAL, QS, 2><<<grid, 256, 0, st>>>(args);
@@ -418,7 +418,7 @@ int launch_fwd_full(const FwdArgs& a, bool kv128, hipStream_t st) {
   args.n_qtiles = (a.Nq + 32 * NW - 1) / (32 * NW);
   args.head_set = head_set_for(args.n_qtiles, a.BH);
   const int grid = grid_for(a.BH, args.n_qtiles);
-  args.fold_end = CAUSAL ? fold_end(grid, args.n_qtiles, 2) : 0;
+  args.fold_end = CAUSAL ? fold_end(grid, args.n_qtiles, 2, fwd_per_cu(D)) : 0;
   if (kv128) sage_fwd_kernel<D, CAUSAL, QS, NW, true><<<grid, 64 * NW, 0, st>>>(args);
   else sage_fwd_kernel<D, CAUSAL, QS, NW><<<grid, 64 * NW, 0, st>>>(args);
   SAGE_LAUNCH_CHECK();
@@ -447,7 +447,7 @@ int launch_bwd(const BwdArgs& a, bool causal, bool qs, hipStream_t st) {
   BwdArgs args = a;
   args.head_set = head_set_for(npair, a.BH);
   const int grid = grid_for(a.BH, npair);
-  args.fold_end = causal && MODE == kBwdMaxOnly ? fold_end(grid, npair, 2) : 0;
+  args.fold_end = causal && MODE == kBwdMaxOnly ? fold_end(grid, npair, 2, kMaxSweepPerCu) : 0;
   if (causal) {
     if (qs) sage_bwd_kernel<D, true, true, MODE, KV128><<<grid, 512, 0, st>>>(args);
     else sage_bwd_kernel<D, true, false, MODE, KV128><<<grid, 512, 0, st>>>(args);
@@ -480,7 +480,7 @@ int launch_bwd_single(const BwdArgs& a, bool causal, bool qs, hipStream_t st) {
   BwdArgs args = a;
   args.head_set = head_set_for(nblk, a.BH);
   const int grid = grid_for(a.BH, nblk);
-  args.fold_end = causal && D == 64 ? fold_end(grid, nblk, 4) : 0;      // (two fit a CU at d = 64)
+  args.fold_end = causal ? fold_end(grid, nblk, 4, bwd_single_per_cu(D, qs)) : 0;
   if (causal) {
     if (qs) sage_bwd_single_kernel<D, true, true><<<grid, 512, 0, st>>>(args);
     else sage_bwd_single_kernel<D, true, false><<<grid, 512, 0, st>>>(args);

@@ -20,7 +20,7 @@ int every_workgroup_has_its_own_work() {
         const int set = sage::head_set_for(items, heads, always != 0), grid = sage::grid_for(heads, items);
         std::vector<char> taken(heads * items, 0);
         for (int b = 0; b < grid; b++) {
-          const sage::WorkItem w = sage::work_item(sage::folded(b, sage::fold_end(grid, items, 2 + 2 * always)), items, set);
+          const sage::WorkItem w = sage::work_item(sage::folded(b, sage::fold_end(grid, items, 2 + 2 * always, 2)), items, set);
           const bool inside = w.head >= 0 && w.head < heads && w.item >= 0 && w.item < items;
           if (!inside || taken[w.head * items + w.item]) {
             printf("heads %d items %d set %d: workgroup %d has head %d item %d\n", heads, items, set, b, w.head, w.item);

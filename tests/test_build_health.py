@@ -92,6 +92,19 @@ def test_the_forms_for_calls_that_do_not_fill_the_machine(kernels):
             assert k["vgpr"] <= 128 and 2 * k["lds"] <= 160 * 1024, k
 
 
+def test_workgroups_share_a_cu_as_the_order_of_their_launch_says(kernels):
+    # fwd_per_cu, kMaxSweepPerCu, bwd_single_per_cu: waves per SIMD by their registers (512, in eights), workgroups by that and by the LDS
+    def per_cu(k, waves):
+        return min(512 // (-(-k["vgpr"] // 8) * 8) * 4 // waves, 160 * 1024 // k["lds"])
+
+    for d, at_least in (("ILi64E", 3), ("ILi128E", 2)):
+        assert all(per_cu(k, 4) >= at_least for k in _pick(kernels, "sage_fwd_kernel", d))
+        assert all(per_cu(k, 4) >= 2 for k in _pick(kernels, "sage_fwd_pair_kernel", d))
+        assert all(per_cu(k, 8) == 2 for k in _pick(kernels, "sage_bwd_kernel", d, "ELi1ELb0EEEv"))
+    for bits, n in (("ILi64ELb1ELb0E", 2), ("ILi64ELb1ELb1E", 1), ("ILi128ELb1ELb0E", 1), ("ILi128ELb1ELb1E", 1)):
+        assert all(per_cu(k, 8) == n for k in _pick(kernels, "sage_bwd_single_kernel", bits))
+
+
 def test_two_workgroups_of_the_decoding_kernel_share_a_cu(kernels):
     for k in _pick(kernels, "sage_fwd_decode_kernel"):
         assert k["vgpr"] <= 256 and 2 * k["lds"] <= 160 * 1024, k
