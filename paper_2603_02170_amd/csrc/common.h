@@ -270,6 +270,26 @@ __host__ __device__ inline int fold_end(int grid, int items, int rounds, int per
   return grid / 8 < 64 ? grid / 8 : 64;
 }
 
+// Both that order and a kernel with a CU to itself whose second round is to be the lighter one count on the heaviest items being the
+// first of the whole launch, which sets of heads do not give: where a set begins, its heaviest items follow the lightest of the one
+// before, and in the last round they end the launch.  Such launches take the items heaviest first over all heads (of an XCD, or of the call in
+// the dense layout); few as their workgroups are, their heads do not crowd the L2.  us, in sets -> over all heads: forward (four waves per 32 queries), 7
+// heads of N = 4096 77.0 -> 50.2 (two waves 59.2), 5 of 6144 91.4 -> 66.1 (79.2), 5 of 8192 133.4 -> 110.1 (127.3), 9 of 3000 49.5 -> 42.9 (48.3); forward,
+// 7 of 7000 131 -> 110.6 (not folded 127), 11 of 7000 157.6 -> 135.5 (152.8); d = 64, 11 of 7000 125 -> 97.5 (115.5); training steps, d =
+// 64, 5 of 5000 195 -> 161 (173), 10 of 4096 193 -> 165 (185), 7 of 7000 345 -> 275 (333).
+__host__ __device__ inline int all_heads(int heads) { return heads % 8 != 0 ? -heads : heads / 8; }
+struct LaunchOrder {
+  int head_set, fold_end;
+};
+__host__ __device__ inline LaunchOrder folded_order(int heads, int items, int rounds, int per_cu) {
+  const int end = fold_end(grid_for(heads, items), items, rounds, per_cu);
+  return {end != 0 ? all_heads(heads) : head_set_for(items, heads), end};
+}
+// sage_fwd_quad_kernel under the mask: more than one round of one workgroup per CU (see use_fwd_quad)
+__host__ __device__ inline int quad_head_set(int heads, int items) {
+  return grid_for(heads, items) > 256 ? all_heads(heads) : head_set_for(items, heads);
+}
+
 // Row of K or V that a load of sage_fwd_decode_kernel for row `row` reads: a row that does not exist re-reads the last one that does (which changes no
 // maximum of its block), and all rows of a block that is not the wave's (`mine` false: the load ahead of a wave's last block) are one
 // row.  The loop stays without a branch, and no block is read twice (two sequences of 32 heads of 8192 keys, where that was an eighth of

@@ -389,9 +389,11 @@ template <int D, bool CAUSAL, bool QS>
 int launch_fwd_small(const FwdArgs& a, FwdForm form, hipStream_t st) {
   FwdArgs args = a;
   args.n_qtiles = a.Nq / 64;
-  args.head_set = head_set_for(args.n_qtiles, a.BH);
   const int grid = grid_for(a.BH, args.n_qtiles);
-  args.fold_end = CAUSAL && form == FwdForm::pair ? fold_end(grid, args.n_qtiles, 2, 2) : 0;      // (the other two have a CU to themselves)
+  // (the pair form's workgroups share a CU; the other two have one to themselves, the quad form's in up to three rounds under the mask)
+  const LaunchOrder order = folded_order(a.BH, args.n_qtiles, 2, CAUSAL && form == FwdForm::pair ? 2 : 1);
+  args.fold_end = order.fold_end;
+  args.head_set = CAUSAL && form == FwdForm::quad ? quad_head_set(a.BH, args.n_qtiles) : order.head_set;
   if (form == FwdForm::quad) sage_fwd_quad_kernel<D, CAUSAL, QS><<<grid, 512, 0, st>>>(args);
   else if (form == FwdForm::split) sage_fwd_split_kernel<D, CAUSAL, QS, 2, 4><<<grid, 512, 0, st>>>(args);
   else sage_fwd_pair_kernel<D, CAUSAL, QS, 2><<<grid, 256, 0, st>>>(args);
@@ -416,9 +418,10 @@ template <int D, bool CAUSAL, bool QS, int NW>
 int launch_fwd_full(const FwdArgs& a, bool kv128, hipStream_t st) {
   FwdArgs args = a;
   args.n_qtiles = (a.Nq + 32 * NW - 1) / (32 * NW);
-  args.head_set = head_set_for(args.n_qtiles, a.BH);
   const int grid = grid_for(a.BH, args.n_qtiles);
-  args.fold_end = CAUSAL ? fold_end(grid, args.n_qtiles, 2, fwd_per_cu(D)) : 0;
+  const LaunchOrder order = folded_order(a.BH, args.n_qtiles, 2, CAUSAL ? fwd_per_cu(D) : 1);
+  args.head_set = order.head_set;
+  args.fold_end = order.fold_end;
   if (kv128) sage_fwd_kernel<D, CAUSAL, QS, NW, true><<<grid, 64 * NW, 0, st>>>(args);
   else sage_fwd_kernel<D, CAUSAL, QS, NW><<<grid, 64 * NW, 0, st>>>(args);
   SAGE_LAUNCH_CHECK();
@@ -445,9 +448,10 @@ template <int D, int MODE, bool KV128 = false>
 int launch_bwd(const BwdArgs& a, bool causal, bool qs, hipStream_t st) {
   const int npair = (a.N / 64 + 1) / 2;     // one workgroup per pair of KV blocks
   BwdArgs args = a;
-  args.head_set = head_set_for(npair, a.BH);
   const int grid = grid_for(a.BH, npair);
-  args.fold_end = causal && MODE == kBwdMaxOnly ? fold_end(grid, npair, 2, kMaxSweepPerCu) : 0;
+  const LaunchOrder order = folded_order(a.BH, npair, 2, causal && MODE == kBwdMaxOnly ? kMaxSweepPerCu : 1);
+  args.head_set = order.head_set;
+  args.fold_end = order.fold_end;
   if (causal) {
     if (qs) sage_bwd_kernel<D, true, true, MODE, KV128><<<grid, 512, 0, st>>>(args);
     else sage_bwd_kernel<D, true, false, MODE, KV128><<<grid, 512, 0, st>>>(args);
@@ -478,9 +482,10 @@ template <int D>
 int launch_bwd_single(const BwdArgs& a, bool causal, bool qs, hipStream_t st) {
   const int nblk = a.N / 64;
   BwdArgs args = a;
-  args.head_set = head_set_for(nblk, a.BH);
   const int grid = grid_for(a.BH, nblk);
-  args.fold_end = causal ? fold_end(grid, nblk, 4, bwd_single_per_cu(D, qs)) : 0;
+  const LaunchOrder order = folded_order(a.BH, nblk, 4, causal ? bwd_single_per_cu(D, qs) : 1);
+  args.head_set = order.head_set;
+  args.fold_end = order.fold_end;
   if (causal) {
     if (qs) sage_bwd_single_kernel<D, true, true><<<grid, 512, 0, st>>>(args);
     else sage_bwd_single_kernel<D, true, false><<<grid, 512, 0, st>>>(args);

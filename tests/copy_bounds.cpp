@@ -4,6 +4,7 @@
 // outside the tensor, or the first workgroup without a (head, item) of its own, and returns 1.
 #include <stdio.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "common.h"
@@ -27,6 +28,12 @@ int every_workgroup_has_its_own_work() {
             return 1;
           }
           taken[w.head * items + w.item] = 1;
+        }
+        const sage::LaunchOrder order = sage::folded_order(heads, items, 2 + 2 * always, 2);
+        std::fill(taken.begin(), taken.end(), 0);
+        for (int b = 0; b < grid; b++) {
+          const sage::WorkItem w = sage::work_item(sage::folded(b, order.fold_end), items, order.head_set);
+          if (w.head < 0 || w.head >= heads || w.item < 0 || w.item >= items || taken[w.head * items + w.item]++) return printf("folded: heads %d items %d: workgroup %d\n", heads, items, b), 1;
         }
         if (grid != heads * items) return printf("heads %d items %d: grid %d\n", heads, items, grid), 1;
       }

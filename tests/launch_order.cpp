@@ -26,14 +26,38 @@ int end_of_launch(int heads, int nblk, int head_set, int fold) {
 int one_workgroup_per_cu_is_not_folded() {
   for (int nblk = 8; nblk <= 200; nblk++)
     for (int heads = 256 / nblk + 1; heads * nblk <= 512; heads++) {
-      const int set = head_set_for(nblk, heads), fold = fold_end(grid_for(heads, nblk), nblk, 4, bwd_single_per_cu(64, true));
-      const int launched = end_of_launch(heads, nblk, set, fold), heaviest_first = end_of_launch(heads, nblk, set, 0);
+      const LaunchOrder order = folded_order(heads, nblk, 4, bwd_single_per_cu(64, true));
+      const int launched = end_of_launch(heads, nblk, order.head_set, order.fold_end), heaviest_first = end_of_launch(heads, nblk, order.head_set, 0);
       if (launched > heaviest_first) return printf("%d heads of %d blocks: %d intervals, heaviest first %d\n", heads, nblk, launched, heaviest_first), 1;
     }
   return 0;
 }
 
+// Launches that count on it have the heaviest items first: in every XCD no item follows a lighter one.
+bool heaviest_first(int heads, int items, int head_set) {
+  int last[8] = {0};
+  for (int b = 0; b < grid_for(heads, items); b++) {
+    const int item = work_item(b, items, head_set).item;
+    if (item < last[b % 8]) return false;
+    last[b % 8] = item;
+  }
+  return true;
+}
+int launches_that_count_on_it_are_heaviest_first() {
+  for (int heads = 1; heads <= 128; heads++)
+    for (int items = 1; heads * items <= 1100; items++) {
+      for (int rounds = 2; rounds <= 4; rounds += 2)
+        for (int per_cu = 2; per_cu <= 3; per_cu++) {
+          const LaunchOrder order = folded_order(heads, items, rounds, per_cu);
+          if (order.fold_end != 0 && !heaviest_first(heads, items, order.head_set)) return printf("%d heads of %d items, up to %d rounds\n", heads, items, rounds), 1;
+        }
+      if (heads * items > 256 && !heaviest_first(heads, items, quad_head_set(heads, items))) return printf("second round of %d heads of %d items\n", heads, items), 1;
+    }
+  return 0;
+}
+
 int main() {
+  if (launches_that_count_on_it_are_heaviest_first()) return 1;
   if (one_workgroup_per_cu_is_not_folded()) return 1;
   return 0;
 }
