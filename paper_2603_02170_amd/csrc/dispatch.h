@@ -11,6 +11,27 @@ inline int fwd_per_cu(int d) { return d == 64 ? 3 : 2; }          // sage_fwd_ke
 constexpr int kMaxSweepPerCu = 2;                                 // sage_bwd_kernel, the sweep for the maxima
 inline int bwd_single_per_cu(int d, bool q_smooth) { return d == 64 && !q_smooth ? 2 : 1; }
 
+// ---- forward of few queries: two waves per 32 queries (sage_fwd_pair_kernel) or four (sage_fwd_quad_kernel) ----
+// Four while there is a CU for each workgroup of 64 queries, and at d = 128 for some more where the mask makes the second round
+// much the lighter.  An interval takes two key blocks: walks of few blocks gain with an even number of them and lose with an odd
+// one, more on fuller machines.  Whole calls, us, two waves -> four.
+// d = 128: 2 blocks, 128 workgroups 12.9 -> 12.3, 250 15.9 -> 15.4; 3, 126 14.6 -> 14.8; 4, 128 14.8 -> 14.3, 248 18.7 -> 18.3; 5, 125
+// 16.4 -> 16.9, 250 18.5 -> 19.2; 7, 245 20.9 -> 22.2; 6, 8 and 9, 60 and 128 1 to 3 % less, 250 1 to 3 % more; 10, 11 and 12, 60
+// to 250 1 to 7 % less; 16, 128 23.7 -> 21.6; 32, 224 36.6 -> 31.5.
+// d = 64: 2, 128 10.6 -> 10.5; 3, 126 11.9 -> 12.4; 4, 128 12.6 -> 12.0, 248 14.3 -> 14.5; 5, 250 14.7 -> 15.4; 7, 245 16.7 -> 17.9; 6
+// and 8 0 to 5 % more; 10, 1 to 4 % less; 11, 1 % more; 12, 1 to 3 % less; 16, 128 19.7 -> 18.8; 32, 224 29.9 -> 27.5.  One block: 9.0
+// -> 9.5.
+// More workgroups than CUs: 17 blocks and more, 289 29.2 -> 28.1, 323 29.6 -> 30.0; 24, 345 32.8 -> 31.7; 32, 384 38.5 -> 35.3; 64,
+// 448 59.2 -> 50.2, 512 58.3 -> 53.5, 640 (one wave) 74.5 -> 79.5; 128, 640 127 -> 110, 768 126 -> 126; 256, 768 228 -> 221; 12 to
+// 16, up to two a block more, 276 26.5 -> 26.4, 280 (14) 28.1 -> 25.6, 288 (16) 29.1 -> 27.2, but 300 (12) 26.9 -> 28.2, 304 (16)
+// 29.1 -> 29.7; 11, 275 25.6 -> 26.1; without the mask 47, 282 54.9 -> 64.3; d = 64: 16, 384 21.4 -> 23.4.
+inline bool fwd_quad_is_faster(long long heads, int nblk, int nqblk, int d, bool causal) {
+  const long long wgs = heads * nqblk;
+  if (wgs > kCus) return d == 128 && causal && nblk == nqblk && nblk >= 12 && wgs <= kCus + (nblk < 17 ? 2 : 4) * nblk && wgs <= 3 * kCus;
+  if (nblk >= 12 || nblk == 2 || nblk == 4 || nblk == 10) return true;
+  return d == 128 && (nblk == 11 || (wgs <= kCus / 2 && (nblk == 6 || nblk == 8 || nblk == 9)));
+}
+
 // ---- decoding: sage_fwd_decode_kernel -----------------------------------------------------------------
 // A query block of at most 32 rows that sees every key takes that kernel, which quantises K and V itself, instead of codes in the
 // workspace: with a long cache, or with many heads (its code is long, and with little work few workgroups share the cost of

@@ -371,16 +371,9 @@ bool use_fwd_split(const FwdArgs& a) {
 // 1280 42.2 -> 49.1; at d = 64, N = 4096, 1024 waves 67.2 -> 51.3, 1280 69.9 -> 77.2.
 bool use_fwd_pair(const FwdArgs& a) { return (long long)a.BH * ((a.Nq + 31) / 32) <= kSimds; }
 
-// Four waves share them (sage_fwd_quad_kernel; same bits): while there is a CU for every 64 queries, and at d = 128 for some workgroups more where
-// the mask makes the second round much the lighter.  Not for a single tile.  Whole calls, us, two waves -> four: 256 workgroups, N = 1024 25.8 ->
-// 23.6, 128 14.2 -> 13.8, 64 9.0 -> 9.5 (d = 64, 200 workgroups); with the mask and d = 128: N = 1024, 320 workgroups 27.8 -> 26.9, 384 27.4 -> 28.8; 2048, 384 38.1 -> 34.7, 512
-// 38.5 -> 38.7; 4096, 384 57.0 -> 47.5, 512 57.8 -> 53.5 (Q-smoothing 74.5 -> 69.0), 640 (one wave) 74.5 -> 79.5; 16384, 512 174 -> 142, 768 243 -> 220; without it 3000, 282 54.9
-// -> 64.3; d = 64: 1024, 384 21.4 -> 23.4, 4096, 512 45.9 -> 46.1.  (A head's codes are addressed with 32 bits.)
+// Four waves share them (sage_fwd_quad_kernel; same bits).  (A head's codes are addressed with 32 bits.)
 bool use_fwd_quad(const FwdArgs& a, int d, bool causal) {
-  const long long wgs = (long long)a.BH * (a.Nq / 64), nblk = a.N / kBlock;
-  if (nblk < 2 || (long long)a.N * d > (1ll << 30)) return false;
-  if (wgs <= kCus) return true;
-  return d == 128 && causal && a.N == a.Nq && wgs <= kCus + 4 * nblk && wgs <= 3 * kCus;
+  return (long long)a.N * d <= (1ll << 30) && fwd_quad_is_faster(a.BH, a.N / kBlock, a.Nq / kBlock, d, causal);
 }
 
 // the forms for calls that do not fill the machine: 64 queries per workgroup

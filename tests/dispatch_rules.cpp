@@ -40,6 +40,15 @@ int main() {
   }
   for (const auto& c : kBackward)
     if (bwd_wide_is_faster(c.heads, c.nblk, c.nblk, 0, c.causal) != c.wide) return printf("bwd_wide_is_faster: %d heads of %d blocks, mask %d\n", c.heads, c.nblk, c.causal), 1;
+  // four waves per 32 queries: heads, key blocks (as many Q blocks), d, mask
+  const struct { int heads, nblk, d; bool causal, quad; } kQuad[] = {{125, 2, 128, true, true}, {125, 2, 64, false, true}, {200, 1, 64, true, false}, {10, 3, 64, true, false},
+      {42, 3, 128, true, false}, {32, 4, 64, true, true}, {62, 4, 128, false, true}, {50, 5, 64, true, false}, {25, 5, 128, true, false}, {20, 6, 128, true, true}, {41, 6, 128, true, false},
+      {35, 7, 128, false, false}, {35, 7, 64, true, false}, {31, 8, 64, true, false}, {16, 8, 128, true, true}, {27, 9, 64, true, false}, {25, 10, 64, true, true}, {22, 11, 64, true, false},
+      {22, 11, 128, true, true}, {20, 12, 64, false, true}, {16, 16, 128, true, true}, {7, 32, 64, true, true}, {28, 9, 128, true, false}, {25, 11, 128, true, false}, {25, 12, 128, true, false},
+      {20, 14, 128, true, true}, {18, 16, 128, true, true}, {19, 16, 128, true, false}, {14, 24, 128, true, true}, {12, 32, 128, true, true}, {7, 64, 128, true, true}, {8, 64, 128, true, true},
+      {10, 64, 128, true, false}, {5, 128, 128, true, true}, {6, 47, 128, false, false}, {24, 16, 64, true, false}};
+  for (const auto& c : kQuad)
+    if (fwd_quad_is_faster(c.heads, c.nblk, c.nblk, c.d, c.causal) != c.quad) return printf("fwd_quad_is_faster: %d heads of %d blocks, d %d, mask %d\n", c.heads, c.nblk, c.d, c.causal), 1;
   // psi(dS) past the caches: heads, blocks, mask; loaded, stored
   const struct { int heads, nblk; bool causal, load, store; } kTraffic[] = {{36, 28, true, false, false}, {44, 32, true, false, false}, {64, 32, true, true, false},
       {16, 64, false, true, false}, {32, 64, true, true, false}, {64, 64, true, true, true}, {64, 128, true, true, true}, {1, 1, false, false, false}};
