@@ -43,7 +43,11 @@ __device__ __forceinline__ float qknorm_apply(float x, float r, float g) {
 // Float64 column sums of `rows` rows at `base`, over the 256 threads of a workgroup: thread t adds the rows
 // t / TPR, t / TPR + RPP, ... of its 8 channels 8 (t % TPR) .. into acc.
 // (bf16 data of ordinary range sum exactly in float64, so the result does not depend on the order.)
-template <int D>
+// NORMED: of the normalised rows, that many of a thread's rows at a time (0: of the rows as they are).  Kernels are instantiated for
+// each, since the normalising loop takes registers that the plain one's occupancy needs (quantiser with the mean inside at d = 128
+// 136 for 87, three waves per SIMD for five; forward calls, us, both loops in one kernel -> apart: 1000 heads of N = 64 31.6 -> 30.5,
+// 300 of 128 25.2 -> 23.7, blocks of 128, d = 64, 1000 of 64 21.2 -> 19.2).
+template <int D, int NORMED>
 __device__ __forceinline__ void column_sums(const unsigned short* __restrict__ base, const size_t row_stride, const int rows,
                                             const QkNorm& norm, double (&acc)[8]) {
   constexpr int TPR = D / 8;          // threads per row, 8 channels (16 bytes) each
@@ -52,26 +56,28 @@ __device__ __forceinline__ void column_sums(const unsigned short* __restrict__ b
 #pragma unroll
   for (int e = 0; e < 8; e++) acc[e] = 0.0;
   const int tr = t / TPR, tc = t % TPR;
-  int r = tr;
-  if (norm.gamma != nullptr) {
+  if constexpr (NORMED > 0) {
     // the mean is taken over the normalised keys: the TPR threads of a row share its sum of squares
+    static_assert(NORMED == 1 || NORMED == 4, "one row, or four");
     float g[8];
 #pragma unroll
     for (int e = 0; e < 8; e++) g[e] = norm.gamma[tc * 8 + e];
-    // Four rows at a time: their loads, sums and shuffles overlap, and a thread takes the float64 root and quotient of one of them for its neighbours.  (One row after the
-    // other, with every thread of a row taking its root, the loop was one chain.  Forward calls, us: 8 heads of N = 269 21.6 -> 19.0, 8 of 4163 79.3 -> 77.5, 64 of 8192 838
-    // -> 834; training step of 32 heads of 2048 187.1 -> 183.2.)
+    // Four rows at a time: their loads, sums and shuffles overlap, and a thread takes the float64 root and quotient of one of them
+    // for its neighbours.  (One row after the other, with every thread of a row taking its root, the loop is one chain, which heads
+    // of one block are as well off with, in two thirds of the registers.  Forward calls, us, one -> four: 8 heads of N = 269 21.6 -> 19.0, 8 of 4163 79.3
+    // -> 77.5, 64 of 8192 838 -> 834, 8 of 512 32.1 -> 25.6; training step of 32 heads of 2048 187.1 -> 183.2; but 1000 of 64 34.7 -> 37.3,
+    // blocks of 128, d = 64, 21.6 -> 25.1, 400 of 64 12.9 -> 14.1.)
     const int lane = t & 63;
-    for (int r0 = 0; r0 < rows; r0 += 4 * RPP) {  // whole passes: the shuffles need every lane
-      v8us v[4];
-      double ss[4];
+    for (int r0 = 0; r0 < rows; r0 += NORMED * RPP) {  // whole passes: the shuffles need every lane
+      v8us v[NORMED];
+      double ss[NORMED];
 #pragma unroll
-      for (int u = 0; u < 4; u++) {
+      for (int u = 0; u < NORMED; u++) {
         v[u] = v8us{0, 0, 0, 0, 0, 0, 0, 0};
         if (r0 + u * RPP + tr < rows) v[u] = *(const v8us*)(base + (size_t)(r0 + u * RPP + tr) * row_stride + tc * 8);
       }
 #pragma unroll
-      for (int u = 0; u < 4; u++) {
+      for (int u = 0; u < NORMED; u++) {
         ss[u] = 0.0;
 #pragma unroll
         for (int e = 0; e < 8; e++) {
@@ -82,40 +88,44 @@ __device__ __forceinline__ void column_sums(const unsigned short* __restrict__ b
 #pragma unroll
       for (int off = 1; off < TPR; off <<= 1)
 #pragma unroll
-        for (int u = 0; u < 4; u++) ss[u] += __shfl_xor(ss[u], off, 64);
-      const float mine = qknorm_rscale((tc & 2) ? ((tc & 1) ? ss[3] : ss[2]) : ((tc & 1) ? ss[1] : ss[0]), D, norm.eps);
+        for (int u = 0; u < NORMED; u++) ss[u] += __shfl_xor(ss[u], off, 64);
+      double own = ss[0];
+      if constexpr (NORMED == 4) own = (tc & 2) ? ((tc & 1) ? ss[3] : ss[2]) : ((tc & 1) ? ss[1] : ss[0]);
+      const float mine = qknorm_rscale(own, D, norm.eps);
 #pragma unroll
-      for (int u = 0; u < 4; u++) {
-        const float rs = __shfl(mine, (lane & ~(TPR - 1)) + u, 64);
+      for (int u = 0; u < NORMED; u++) {
+        __builtin_amdgcn_sched_barrier(0);      // (row after row: side by side they cost up to 22 registers)
+        const float rs = NORMED == 1 ? mine : __shfl(mine, (lane & ~(TPR - 1)) + u, 64);
         if (r0 + u * RPP + tr < rows) {
 #pragma unroll
           for (int e = 0; e < 8; e++) acc[e] += (double)qknorm_apply(bf16_bits_to_float(v[u][e]), rs, g[e]);
         }
       }
     }
-    return;
-  }
-  // four independent 16-byte loads in flight per thread
-  for (; r + 3 * RPP < rows; r += 4 * RPP) {
-    v8us v[4];
+  } else {
+    int r = tr;
+    // four independent 16-byte loads in flight per thread
+    for (; r + 3 * RPP < rows; r += 4 * RPP) {
+      v8us v[4];
 #pragma unroll
-    for (int u = 0; u < 4; u++) v[u] = *(const v8us*)(base + (size_t)(r + u * RPP) * row_stride + tc * 8);
+      for (int u = 0; u < 4; u++) v[u] = *(const v8us*)(base + (size_t)(r + u * RPP) * row_stride + tc * 8);
 #pragma unroll
-    for (int u = 0; u < 4; u++)
+      for (int u = 0; u < 4; u++)
 #pragma unroll
-      for (int e = 0; e < 8; e++) acc[e] += (double)bf16_bits_to_float(v[u][e]);
-  }
-  for (; r < rows; r += RPP) {
-    v8us v = *(const v8us*)(base + (size_t)r * row_stride + tc * 8);
+        for (int e = 0; e < 8; e++) acc[e] += (double)bf16_bits_to_float(v[u][e]);
+    }
+    for (; r < rows; r += RPP) {
+      v8us v = *(const v8us*)(base + (size_t)r * row_stride + tc * 8);
 #pragma unroll
-    for (int e = 0; e < 8; e++) acc[e] += (double)bf16_bits_to_float(v[e]);
+      for (int e = 0; e < 8; e++) acc[e] += (double)bf16_bits_to_float(v[e]);
+    }
   }
 }
 
 // ---- K mean, stage 1: float64 column sums of a chunk of rows -----------------------
 // Stage 2, the sum over the chunks, the division by N and the one rounding to
 // FP32, runs at the start of every workgroup that quantises a block of K (prepass_quant_kernel).
-template <int D>
+template <int D, int NORMED>
 __global__ void __launch_bounds__(256) kmean_partial_kernel(const unsigned short* __restrict__ K, RowView view,
                                                             double* __restrict__ kpart, int N,
                                                             int nchunk, int chunk_rows, QkNorm norm) {
@@ -126,7 +136,7 @@ __global__ void __launch_bounds__(256) kmean_partial_kernel(const unsigned short
   const int chunk = blockIdx.x, bh = blockIdx.y;
   const int row0 = chunk * chunk_rows;
   double acc[8];
-  column_sums<D>(K + view.row(bh, row0), view.row_stride, min(chunk_rows, N - row0), norm, acc);
+  column_sums<D, NORMED>(K + view.row(bh, row0), view.row_stride, min(chunk_rows, N - row0), norm, acc);
 #pragma unroll
   for (int e = 0; e < 8; e++) red[t][e] = acc[e];
   __syncthreads();
@@ -221,10 +231,16 @@ struct QuantJobs {
 // SUB = 64-row blocks per numerics block (Algorithm 1 leaves B_q, B_kv free): 1, or 2 for blocks of 128 rows.
 // A workgroup takes one numerics block; its scale (and block mean) is stored once per 64-row block: the
 // attention kernels index scales, means and bias rows by 64-row block whatever the numerics block is.
-// INLINE_MEAN: the K job sums its head itself (jobs of a short K; an instantiation of its own, since the summing loop costs
-// the registers that the long ones' occupancy needs).
-template <int D, int SUB, bool INLINE_MEAN>
-__global__ void __launch_bounds__(256) prepass_quant_kernel(QuantJobs jobs) {
+// MEAN: the K job adds chunk sums, or sums its head itself (jobs of a short K; instantiations of their own, since the summing
+// loops cost the registers that the others' occupancy needs), or sums the normalised rows of its head, of more than one block or of one.
+enum : int { kMeanOfChunks, kMeanInline, kMeanInlineNormed, kMeanInlineNormedBlock };
+// Waves per SIMD (left to itself the compiler takes 119 registers for plain keys where 87 do).
+constexpr int quantiser_waves(int D, int SUB, int mean) {
+  return mean == kMeanOfChunks ? 1 : mean == kMeanInlineNormed || SUB * D > 128 ? 3 : 5;
+}
+template <int D, int SUB, int MEAN>
+__global__ void __launch_bounds__(256, quantiser_waves(D, SUB, MEAN)) prepass_quant_kernel(QuantJobs jobs) {
+  constexpr bool INLINE_MEAN = MEAN != kMeanOfChunks;
   constexpr int ROWS = SUB * kBlock;
   constexpr int CPR = D / 16;            // 16-channel chunks per row
   constexpr int NCH = ROWS * CPR / 256;  // chunks per thread
@@ -353,7 +369,7 @@ __global__ void __launch_bounds__(256) prepass_quant_kernel(QuantJobs jobs) {
 
   if (INLINE_MEAN && jb.mean_inline) {
     double acc[8];
-    column_sums<D>(jb.src + view.row(bh, 0), view.row_stride, N, jb.norm, acc);
+    column_sums<D, MEAN == kMeanInlineNormed ? 4 : MEAN == kMeanInlineNormedBlock ? 1 : 0>(jb.src + view.row(bh, 0), view.row_stride, N, jb.norm, acc);
     // the rows of a wave meet in its first D / 8 lanes, the waves in colbuf
     double* red = (double*)colbuf;               // [wave][D]
     static_assert(4 * D * sizeof(double) <= sizeof(colbuf), "four waves' sums");

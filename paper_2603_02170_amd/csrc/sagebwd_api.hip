@@ -223,10 +223,17 @@ struct ScopedTimer {
 template <int D>
 int launch_kmean(const void* K, const RowView& kview, const sagebwd_params& p, char* ws, const Workspace& w, const QkNorm& norm,
                  hipStream_t st) {
-  kmean_partial_kernel<D><<<dim3(w.nchunk, p.B * p.H), 256, 0, st>>>((const unsigned short*)K, kview, (double*)(ws + w.kpart),
-                                                                     kv_len(p), w.nchunk, w.chunk_rows, norm);
+  const auto kernel = norm.gamma != nullptr ? kmean_partial_kernel<D, 4> : kmean_partial_kernel<D, 0>;
+  kernel<<<dim3(w.nchunk, p.B * p.H), 256, 0, st>>>((const unsigned short*)K, kview, (double*)(ws + w.kpart), kv_len(p), w.nchunk,
+                                                    w.chunk_rows, norm);
   SAGE_LAUNCH_CHECK();
   return SAGEBWD_OK;
+}
+
+template <int D, int SUB>
+auto quantiser(int mean) {
+  return mean == kMeanOfChunks ? prepass_quant_kernel<D, SUB, kMeanOfChunks> : mean == kMeanInline ? prepass_quant_kernel<D, SUB, kMeanInline>
+       : mean == kMeanInlineNormed ? prepass_quant_kernel<D, SUB, kMeanInlineNormed> : prepass_quant_kernel<D, SUB, kMeanInlineNormedBlock>;
 }
 
 // want_qk: smooth and quantise Q and K (F layouts; with want_tf also the backward's TF layouts);
@@ -312,13 +319,9 @@ int run_prepass(const void* Q, const void* K, const void* V, const void* dO, con
       }
       if (np == 0) continue;
       const dim3 grid((nblk_max + sub - 1) / sub, BH, np);
-      if (sub == 1) {
-        if (want_qk && inline_mean) prepass_quant_kernel<D, 1, true><<<grid, 256, 0, st>>>(part);
-        else prepass_quant_kernel<D, 1, false><<<grid, 256, 0, st>>>(part);
-      } else {
-        if (want_qk && inline_mean) prepass_quant_kernel<D, 2, true><<<grid, 256, 0, st>>>(part);
-        else prepass_quant_kernel<D, 2, false><<<grid, 256, 0, st>>>(part);
-      }
+      const int mean = !(want_qk && inline_mean) ? kMeanOfChunks : !qkn ? kMeanInline : Nk > kBlock ? kMeanInlineNormed : kMeanInlineNormedBlock;
+      const auto kernel = sub == 1 ? quantiser<D, 1>(mean) : quantiser<D, 2>(mean);
+      kernel<<<grid, 256, 0, st>>>(part);
       SAGE_LAUNCH_CHECK();
     }
   }

@@ -105,6 +105,14 @@ def test_workgroups_share_a_cu_as_the_order_of_their_launch_says(kernels):
         assert all(per_cu(k, 8) == n for k in _pick(kernels, "sage_bwd_single_kernel", bits))
 
 
+def test_the_sums_of_plain_keys_do_not_pay_for_the_normalising_ones(kernels):
+    # five waves per SIMD of the quantiser at d = 128 with the mean inside, seven of the chunk sums
+    for k in _pick(kernels, "prepass_quant_kernel", "ILi128ELi1ELi1E") + _pick(kernels, "prepass_quant_kernel", "ILi64ELi2ELi1E"):
+        assert k["scratch"] == 0 and k["vgpr"] <= 96, k
+    for k in _pick(kernels, "kmean_partial_kernel", "ELi0E"):
+        assert k["scratch"] == 0 and k["vgpr"] <= 72, k
+
+
 def test_two_workgroups_of_the_decoding_kernel_share_a_cu(kernels):
     for k in _pick(kernels, "sage_fwd_decode_kernel"):
         assert k["vgpr"] <= 256 and 2 * k["lds"] <= 160 * 1024, k

@@ -145,7 +145,9 @@ def _qk_norm_case(N, d, H, q_smooth, k_smooth, Nk=0, eps=1e-6, seed=0):
 
 
 @pytest.mark.parametrize("N,d,q_smooth,k_smooth,Nk", [(128, 64, False, True, 0), (300, 128, True, True, 0), (100, 128, False, False, 0),
-                                                      (64, 64, True, True, 256), (1000, 128, False, True, 0)])
+                                                      (64, 64, True, True, 256), (1000, 128, False, True, 0),
+                                                      # heads of one block of keys, whose sums are another instantiation
+                                                      (64, 128, False, True, 0), (37, 64, False, True, 0), (200, 128, True, True, 50)])
 def test_prepass_qk_norm_fused_is_bit_exact(N, d, q_smooth, k_smooth, Nk):
     """SAGEBWD_FLAG_QK_NORM: the pre-pass normalises Q and K (RMS norm with a gain per channel, Sec. 4) before
     smoothing and quantising them.  Codes, scales and means must equal the oracle's pre-pass run on the
