@@ -208,19 +208,32 @@ inline DsTraffic ds_traffic(long long heads, int nblk, int nqblk, int shift_bloc
   return {mb > 100, mb > 400};
 }
 
-// dQ with one Q block per workgroup and its waves on channel blocks (sage_bwd_dq_split_kernel; same bits): while the other form's workgroups, of two Q blocks each, leave
-// much of the machine idle, which walks of all lengths do longer than even ones.  On fuller machines this kernel is still the faster, but its copies and LDS reads cost power
-// that the kernels around it then lack (32 heads of N = 2048: 30.7 -> 26.9, but the backward before it, the same code, 127.5 -> 131.7), so the line lies where the
-// whole training step gains.  Q blocks of all heads: step / dQ kernel, us, two Q blocks per workgroup -> one.  With the mask, d = 128: 512 (N = 2048) 124 / 28 -> 114 / 17, 752
-// (3000) 206 / 38 -> 197 / 27, 768 (2048) 159 / 29 -> 155 / 22, 896 (4096) 279.7 / 52 -> 281.5 / 47, 960 (1500) 149.3 / 24 -> 150.5 / 22, 1024 (4096) 302 / 53 -> 305 / 45; longer
-// walks, 846 (9000) 555 / 105 -> 543 / 71, 1536 (8192) 760 / 152 -> 740 / 123, 2000 (16000) 1497 / 243 -> 1520 / 251; d = 64: 640 (2500) 125 / 23 -> 120 / 17, 768 (2048) 110.5 / 20 -> 109.5
-// / 16, 1008 (1777) 117 / 19 -> 119 / 18.  Without: 512 (2048) 153 / 28 -> 152 / 22.5, (4096) 264.5 / 49 -> 261.5 / 38.5, 640 (2048) 193 / 32 -> 199 / 31, (2500) 230.5 / 37 -> 236 / 36; d
-// = 64: 672 (1777) 135.3 / 20 -> 138 / 21.  One Q block a head leaves half of the other form idle at every size: 4000 heads of N = 64 329 / 40 -> 325 / 35.
+// dQ with one Q block per workgroup and its waves on channel blocks (sage_bwd_dq_split_kernel; same bits): while the other form's
+// workgroups, of two Q blocks each and three per CU, leave much of the machine idle, which walks of all lengths do longer than even
+// ones: as long as the longest walk has 3.85 times the stages that one of its slots has on average.  On fuller machines this kernel
+// is often still the faster, but the kernels around it in a training step get slower (32 heads of N = 2048: 30.7 -> 26.9, the
+// backward before it 127.5 -> 131.7; 46 of 1024 against 3072 keys: 43.7 -> 45.9, 126.5 -> 136.8, the forward 57.7 -> 63.4), so the
+// line lies where the whole step gains.  (Those run the same code with the same number of memory requests, and launched one at a
+// time they take the same time with either form: it is not what the caches hold, and the chip's power limit would explain it.)
+// Q blocks of all heads (N): step / dQ kernel, us, two Q blocks per workgroup -> one.
+// With the mask, as many keys as queries, d = 128: 512 (2048) 124 / 28 -> 114 / 17, 752 (3000) 205 / 38 -> 197 / 27, 768 (2048) 159 / 29
+// -> 155 / 22, 768 (6144) 369 / 72 -> 358 / 46; 799 (3000) 209.5 -> 210.3 (another time 211.8 -> 216.7), 880 (7000) 426 -> 422, 896 (4096) 279.7 -> 279.8, 923 (4500) 393 ->
+// 399, 960 (6144) 505 -> 512, 1024 (4096) 299 -> 304, 1136 (4500) 374 -> 379, 1248 (6144) 547 -> 550, 1312 (5200) 452 -> 458, 1476 (5200) 517
+// -> 506; d = 64: 640 (2500) 125 / 23 -> 120 / 17, 768 (2048) 110.5 / 20 -> 109.5 / 16, 1008 (1777) 117 -> 119, 1100 (7000) 407 -> 414, 1264 (5000) 306 -> 309.
+// Walks of 112 blocks and more, twice: d = 128: 968 (7700) 485 -> 492, 1024 (8192) 533 -> 534, 1128 (12000) 879 -> 871, 1280 (8192) 737 / 155 -> 697 / 111, 1392 (7400) 660
+// -> 652, 1410 (9000) 892 -> 879, 1500 (16000) 1363 -> 1350, 1536 (8192) 765 / 152 -> 742 / 124, 2000 (16000) 1497 -> 1520; d = 64: 1024 (8192) 375 -> 371,
+// 1280 (8192) 540 -> 511, 1504 (12000) 742 -> 746.
+// More keys than queries: 1.1 times 640 (1024) 111 -> 108, 752 (1024) 126.5 -> 127.4, 726 (4224) 370 -> 374; 1.25 times 704 (2048)
+// 194 -> 189.5; 1.5 times 544 (2048) 211 -> 200, 640 (2048) 213.5 -> 207.5, (1024) 131.8 -> 133.4 and at d = 64 95.3 -> 96.0, 726 (4224) 473 -> 490; twice 462 (4224) 481 -> 464, 496 (1024) 141 -> 136, 594 (4224) 531 -> 541, 896 (8192) 1292 -> 1279; three times 416
+// (1024) 199 -> 193, 528 (1024) 240 -> 243, 594 (4224) 782 -> 800, 736 (1024) 269 -> 284.
+// Without the mask: 512 (2048) 153 / 28 -> 152 / 22.5, (4096) 264.5 / 49 -> 261.5 / 38.5, 640 (2048) 193 -> 199, (2500) 230.5 -> 236; d = 64: 672 (1777) 135.3 ->
+// 138.  One Q block a head leaves half of the other form idle at every size: 4000 heads of N = 64 329 / 40 -> 325 / 35.
 inline bool use_dq_split(long long heads, int nblk, int nqblk, bool causal) {
   const long long blocks = heads * nqblk;
-  if (nqblk == 1) return true;
-  if (even_walks(nblk, nqblk, causal)) return blocks <= 2 * kCus;
-  return blocks <= (nqblk > 64 ? 6 : 3) * kCus;
+  if (nqblk == 1 || blocks <= 2 * kCus) return true;
+  if (even_walks(nblk, nqblk, causal)) return false;
+  const double slot = 0.5 * blocks * (nblk - 0.5 * nqblk) / (3 * kCus);
+  return nblk >= (nqblk >= 112 ? 2.0 : 3.85) * slot;
 }
 
 }  // namespace sage

@@ -59,7 +59,11 @@ int main() {
   // dQ with one Q block per workgroup: heads, key blocks, Q blocks, mask
   const struct { int heads, nblk, nqblk; bool causal, split; } kDq[] = {{1, 1, 1, true, true}, {5000, 3, 1, false, true}, {24, 32, 32, true, true}, {25, 32, 32, true, false},
       {12, 64, 64, true, true}, {13, 64, 64, true, false}, {12, 128, 128, true, true}, {13, 128, 128, true, false}, {16, 32, 32, false, true}, {17, 32, 32, false, false},
-      {64, 64, 8, true, true}, {65, 64, 8, true, false}};
+      {64, 64, 8, true, true}, {65, 64, 8, true, false},
+      // longer walks, and more keys than queries: where the whole step was measured
+      {8, 96, 96, true, true}, {16, 64, 64, true, false}, {16, 71, 71, true, false}, {13, 71, 71, true, false}, {16, 82, 82, true, false}, {10, 96, 96, true, false}, {10, 128, 128, true, true},
+      {12, 116, 116, true, true}, {10, 141, 141, true, true}, {8, 250, 250, true, false}, {40, 18, 16, true, true}, {40, 24, 16, true, false}, {17, 48, 32, true, true}, {17, 47, 47, true, false}, {11, 99, 66, true, false},
+      {31, 32, 16, true, true}, {9, 132, 66, true, false}, {7, 256, 128, true, true}, {26, 48, 16, true, true}, {33, 48, 16, true, false}, {46, 48, 16, true, false}};
   for (const auto& c : kDq)
     if (use_dq_split(c.heads, c.nblk, c.nqblk, c.causal) != c.split) return printf("use_dq_split: %d heads of %d x %d blocks, mask %d\n", c.heads, c.nqblk, c.nblk, c.causal), 1;
   // groups of heads: whole rounds where the walks are even (no mask, or few queries against many keys) and the workgroups have four
