@@ -32,6 +32,24 @@ inline bool fwd_quad_is_faster(long long heads, int nblk, int nqblk, int d, bool
   return d == 128 && (nblk == 11 || (wgs <= kCus / 2 && (nblk == 6 || nblk == 8 || nblk == 9)));
 }
 
+// ---- Q-smoothing's bias table for at most 16 Q blocks: qsmooth_bias_short_kernel or qsmooth_bias_kernel (same bits) ----
+// Workgroups (one per key block and head) with a CU to themselves are bound by latency, and the short kernel has no LDS and no
+// barrier; where they share one, its narrow loads, of Q's means for every 16 keys again, cost more than that.  Whole forward
+// calls that differ in this kernel only, us, qsmooth_bias_kernel -> the short one, by workgroups (heads of N):
+// d = 128: 1 (1 of 64) 14.2 -> 13.4, 40 (40 of 41) 14.6 -> 13.7, 64 (8 of 512) 23.2 -> 22.6, 128 (8 of 1000) 28.9 -> 29.0, 256 (16 of
+// 1024) 33.3 -> 33.0, (32 of 512) 28.0 -> 27.4, (2 of 1024 against 8192 keys) 73.9 -> 74.0; one Q block: 300 22.8 -> 22.7, 512 26.3 -> 25.8;
+// two: 300 26.0 -> 26.1, 500 29.0 -> 28.8; three: 300 26.4 -> 26.7; four: 280 27.4 -> 27.8; eight: 320 31.4 -> 32.4; 16: 288 36.4 ->
+// 38.7, 480 40.2 -> 42.1, the step 92.4 -> 94.2.
+// d = 64: 6 (2 of 130) 14.0 -> 13.2, 208 (13 of 1008) 27.4 -> 26.9, 256 (16 of 1024) 25.4 -> 25.0; one Q block: 500 18.3 -> 17.9, four: 280
+// 21.0 -> 20.9, 480 21.5 -> 21.2; eight: 320 23.12 -> 23.10, 384 24.2 -> 24.1; nine: 288 23.2 -> 23.4; 12: 264 26.9 -> 27.3; 16: 288 29.7 ->
+// 30.3, 480 33.3 -> 34.1.
+// From two workgroups per CU on (d = 128, 800 of four Q blocks 43.2 -> 44.2; d = 64, 748 of seven 31.0 -> 32.0) and from 17 Q blocks on,
+// where the larger products have rows for all their lanes, the other kernel.
+inline bool use_bias_short(long long heads, int nblk, int nqblk, int d) {
+  const long long wgs = heads * nblk;
+  return nqblk <= 16 && wgs <= (nqblk <= (d == 64 ? 8 : 2) ? 2 * kCus : kCus);
+}
+
 // ---- decoding: sage_fwd_decode_kernel -----------------------------------------------------------------
 // A query block of at most 32 rows that sees every key takes that kernel, which quantises K and V itself, instead of codes in the
 // workspace: with a long cache, or with many heads (its code is long, and with little work few workgroups share the cost of

@@ -600,14 +600,12 @@ __global__ void __launch_bounds__(256) qsmooth_bias_kernel(const unsigned short*
   }
 }
 
-// The same table for at most 16 Q blocks, where the kernel above has no Q blocks for two of its waves and half a tile of rows that do not exist for the others: wave w
-// forms 16 Q blocks x keys 16 w .. with 16x16x4 products, both operands straight from the tensors, without LDS or a barrier.  Step (v, p) contracts
-// channels 8 v + p + 0, 4, 2, 6 in the four lanes of a row, which is the order in which two steps of the kernel above do: the same bits, so that no logit falls to the other side of
-// a rounding.  The four lanes of a row read whole 16-byte pieces.  (Bound by latency, as the kernel
-// above is there.)  Whole calls, us, the kernel above -> this one: forward of 8 heads of N = 512 24.7 -> 23.6; training steps, 16 of
-// 1000 83.9 -> 74.5, d = 64, 13 of 1008 65.2 -> 59.9, 40 of 41 31.5 -> 29.4.  Its narrow loads cost more from two workgroups per CU on: forward of 200 heads of N = 256 (800
-// workgroups) 43.2 -> 44.2, d = 64, 34 of 448 against 1408 keys (748) 31.0 -> 32.0, the step of 54 of 648 (594) 101.3 -> 102.1; and from 17 Q blocks on the larger
-// products are the faster ones (32 heads of N = 2048 215.5 -> 216.4).
+// The same table for at most 16 Q blocks, where the kernel above has no Q blocks for two of its waves and half a tile of rows that do
+// not exist for the others: wave w forms 16 Q blocks x keys 16 w .. with 16x16x4 products, both operands straight from the tensors,
+// without LDS or a barrier.  Step (v, p) contracts channels 8 v + p + 0, 4, 2, 6 in the four lanes of a row, which is the order in
+// which two steps of the kernel above do: the same bits, so that no logit falls to the other side of a rounding.  The four lanes of
+// a row read whole 16-byte pieces.  Bound by latency, as the kernel above is there: 0.5 to 0.9 us less of a call (the forward of 8
+// heads of N = 512 23.2 -> 22.6, of 40 heads of 41 14.6 -> 13.7; see use_bias_short for where it is chosen).
 template <int D>
 __global__ void __launch_bounds__(256) qsmooth_bias_short_kernel(const unsigned short* __restrict__ K, RowView view,
                                                                  const float* __restrict__ muK, const float* __restrict__ muQ,

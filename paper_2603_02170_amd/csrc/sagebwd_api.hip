@@ -337,8 +337,8 @@ int run_prepass(const void* Q, const void* K, const void* V, const void* dO, con
     float* bias = (float*)(ws + w.bias);
     const int shift = p.causal ? (Nk - Nq) / 64 : -1;
     const dim3 bgrid(Nkp / 64, BH);
-    if (Nqp / 64 <= 16 && (long long)BH * (Nkp / 64) <= 2 * kCus) qsmooth_bias_short_kernel<D><<<bgrid, 256, 0, st>>>(keys, kv, muK, muQ, bias, Nk, Nkp, Nqp / 64, shift, sl2);
-    else qsmooth_bias_kernel<D><<<bgrid, 256, 0, st>>>(keys, kv, muK, muQ, bias, Nk, Nkp, Nqp / 64, shift, sl2);
+    const auto table = use_bias_short(BH, Nkp / 64, Nqp / 64, D) ? qsmooth_bias_short_kernel<D> : qsmooth_bias_kernel<D>;
+    table<<<bgrid, 256, 0, st>>>(keys, kv, muK, muQ, bias, Nk, Nkp, Nqp / 64, shift, sl2);
     SAGE_LAUNCH_CHECK();
   }
   return SAGEBWD_OK;

@@ -49,6 +49,12 @@ int main() {
       {10, 64, 128, true, false}, {5, 128, 128, true, true}, {6, 47, 128, false, false}, {24, 16, 64, true, false}};
   for (const auto& c : kQuad)
     if (fwd_quad_is_faster(c.heads, c.nblk, c.nblk, c.d, c.causal) != c.quad) return printf("fwd_quad_is_faster: %d heads of %d blocks, d %d, mask %d\n", c.heads, c.nblk, c.d, c.causal), 1;
+  // Q-smoothing's short table: heads, key blocks, Q blocks, d
+  const struct { int heads, nblk, nqblk, d; bool small; } kBias[] = {{1, 1, 1, 128, true}, {16, 16, 16, 128, true}, {32, 8, 8, 128, true}, {18, 16, 16, 128, false},
+      {30, 16, 16, 128, false}, {30, 16, 16, 64, false}, {40, 8, 8, 128, false}, {40, 8, 8, 64, true}, {32, 9, 9, 64, false}, {70, 4, 4, 128, false}, {120, 4, 4, 64, true}, {200, 4, 4, 64, false},
+      {512, 1, 1, 128, true}, {513, 1, 1, 64, false}, {250, 2, 2, 128, true}, {100, 3, 3, 128, false}, {4, 128, 16, 128, false}, {2, 128, 16, 64, true}, {1, 17, 17, 128, false}};
+  for (const auto& c : kBias)
+    if (use_bias_short(c.heads, c.nblk, c.nqblk, c.d) != c.small) return printf("use_bias_short: %d heads of %d x %d blocks, d %d\n", c.heads, c.nqblk, c.nblk, c.d), 1;
   // psi(dS) past the caches: heads, blocks, mask; loaded, stored
   const struct { int heads, nblk; bool causal, load, store; } kTraffic[] = {{36, 28, true, false, false}, {44, 32, true, false, false}, {64, 32, true, true, false},
       {16, 64, false, true, false}, {32, 64, true, true, false}, {64, 64, true, true, true}, {64, 128, true, true, true}, {1, 1, false, false, false}};
