@@ -209,21 +209,32 @@ inline int bwd_heads_of_group(int most, int left, int nblk, int nqblk, int shift
   return best;
 }
 
-// psi(dS) of a launch on its way from the backward to the dQ kernel.  Up to 100 MB it is left to the caches.  From there on the dQ kernel
-// loads it past them, and takes the last heads first, whose tiles were written last: the memory-side cache (256 MB) holds part of them.  Beyond 400 MB that is
-// little and displaces what the two kernels read again, so that sage_bwd_wide_kernel stores past the caches too (and the heads come in order).  Whole
-// steps / dQ kernel, us: all through the caches -> loaded past them, last heads first -> stored past them.  40 heads of N = 2048, d = 64, 86 MB: dQ 23.1 -> 26.2; d =
-// 128: 44 of 2048, 95 MB, 225 / 35.4 -> 224 / 37.2; 64 of 2048, 139 MB, 307 / 52.4 -> 300 / 49.7; 32 of 4096, 273 MB, 498 / 87 -> 488 / 74 -> 488.5 / 84; 20 of 6144,
-// 382 MB, 705 / 140 -> 698 / 124 -> 696 / 130; 24 of 6144 838 / 141.5 -> 819 / 124.6 -> 818 / 127; 64 of 4096, 545 MB, 989 / 167 -> 973 / 145 -> 973 / 144; 64 of 8192,
-// 2164 MB, 3515 / 518 -> 3514 / 510 -> 3485 / 494.5; d = 64, whose kernel always stores through, 64 of 4096 792 / 162 -> 773 / 132.
+// psi(dS) of a launch on its way from the backward to the dQ kernel.  While it fits the memory-side cache (256 MB) together with what the
+// two kernels read and write beside it (codes of Q and K in two layouts and of dO, V and dO in bf16, three gradients), it is left to the
+// caches.  From there on the dQ kernel loads it past them, and takes the last heads first, whose tiles were written last: the cache
+// holds part of them.  Beyond 400 MB of psi(dS) that is little and displaces what the two kernels read again, so that
+// sage_bwd_wide_kernel stores past the caches too (and the heads come in order).
+// Whole steps, us, all through the caches -> loaded past them, last heads first, by MB in all (of them psi(dS); heads of N).
+// d = 128, mask: 189 (129; 4 of 8192) 293 -> 294, 192 (42; 80 of 1024) 136 -> 140, 215 (28; 200 of 512) 146 -> 152, 218 (113; 14 of 4096)
+// 275.1 -> 274.9, 243 (86; 42 of 2048) 218.7 -> 217.1, 250 (130; 16 of 4096) 293.5 -> 291.9, 266 (94; 46 of 2048) 226.5 -> 225.4, 283 (193; 6 of
+// 8192) 448 -> 442, 288 (63; 120 of 1024) 215.7 -> 213.3, 302 (107; 52 of 2048) 251 -> 245, 360 (79; 150 of 1024) 264 -> 262.
+// d = 128, no mask: 188 (128; 8 of 4096) 250 -> 251, 206 (104; 26 of 2048) 207.6 -> 209.0, 230 (80; 80 of 1024) 220 -> 225, 237 (192; 3 of 8192)
+// 420 -> 423, 248 (128; 32 of 2048) 230.7 -> 233.2, 277 (128; 16 of 1024 against 8192 keys) 259.0 -> 259.8, 279 (144; 36 of 2048) 370 ->
+// 368, 282 (192; 12 of 4096) 356 -> 354, 287 (100; 100 of 1024) 256.6 -> 255.8, 376 (256; 16 of 4096) 420 -> 414, 496 (256; 64 of 2048) 477 -> 465.
+// d = 64: mask 198 (161; 5 of 8192) 292 -> 295, 219 (79; 150 of 1024) 184 -> 186, 237 (162; 20 of 4096) 268.5 -> 272.0, 252 (132; 64 of 2048)
+// 223 -> 221, 277 (225; 7 of 8192) 349 -> 343, 293 (106; 200 of 1024) 234 -> 230, 315 (165; 80 of 2048) 276 -> 269; no mask 193 (100; 100 of
+// 1024) 183 -> 185, 235 (160; 40 of 2048) 232.0 -> 232.7, 237 (192; 12 of 4096) 264 -> 272, 282 (192; 48 of 2048) 273 -> 268, 290 (150; 150 of 1024) 275 -> 273.
+// Stored past the caches as well, steps, us: mask, 273 MB (32 of 4096) 488 -> 488.5, 382 (20 of 6144) 698 -> 696, 24 of 6144 819 -> 818, 545 (64 of
+// 4096) 973 -> 973, 2164 (64 of 8192) 3514 -> 3485; no mask, 192 (12 of 4096) 354 -> 359, 256 (16 of 4096) 414 -> 420, 352 (22 of 4096) 697 ->
+// 699, 512 (32 of 4096) 846 -> 844, 768 (12 of 8192) 1380 -> 1382, 1024 (16 of 8192) 1589 -> 1567.
 struct DsTraffic {
   bool load_past, store_past;
 };
-inline DsTraffic ds_traffic(long long heads, int nblk, int nqblk, int shift_blocks, bool causal) {
+inline DsTraffic ds_traffic(long long heads, int nblk, int nqblk, int shift_blocks, int d, bool causal) {
   long long tiles = (long long)nblk * nqblk;      // of a head
   if (causal) tiles = (long long)nqblk * (shift_blocks + 1) + (long long)nqblk * (nqblk - 1) / 2;
-  const long long mb = heads * tiles * 4096 >> 20;
-  return {mb > 100, mb > 400};
+  const long long beside = 64ll * d * (7 * nqblk + 8 * nblk);
+  return {heads * (tiles * 4096 + beside) >> 20 >= 250, heads * tiles * 4096 >> 20 > 400};
 }
 
 // dQ with one Q block per workgroup and its waves on channel blocks (sage_bwd_dq_split_kernel; same bits): while the other form's

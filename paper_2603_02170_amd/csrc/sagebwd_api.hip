@@ -883,7 +883,7 @@ int sagebwd_bwd(const void* Q, const void* K, const void* V, const void* O, cons
     nh = bwd_heads_of_group(w.heads_per_group, BH - h0, Nkp / 64, Nqp / 64, shift_blocks, params->causal != 0, wide_form);
     a.bh0 = q.bh0 = h0;
     a.BH = q.BH = nh;
-    const DsTraffic ds = ds_traffic(nh, Nkp / 64, Nqp / 64, shift_blocks, params->causal != 0);
+    const DsTraffic ds = ds_traffic(nh, Nkp / 64, Nqp / 64, shift_blocks, d, params->causal != 0);
     const bool causal = params->causal != 0, wide = use_bwd_wide(a, d, causal, qs, big);
     a.stream_ds = ds.store_past;
     q.last_first = ds.load_past && !(wide && ds.store_past);

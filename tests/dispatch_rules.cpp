@@ -55,12 +55,16 @@ int main() {
       {512, 1, 1, 128, true}, {513, 1, 1, 64, false}, {250, 2, 2, 128, true}, {100, 3, 3, 128, false}, {4, 128, 16, 128, false}, {2, 128, 16, 64, true}, {1, 17, 17, 128, false}};
   for (const auto& c : kBias)
     if (use_bias_short(c.heads, c.nblk, c.nqblk, c.d) != c.small) return printf("use_bias_short: %d heads of %d x %d blocks, d %d\n", c.heads, c.nqblk, c.nblk, c.d), 1;
-  // psi(dS) past the caches: heads, blocks, mask; loaded, stored
-  const struct { int heads, nblk; bool causal, load, store; } kTraffic[] = {{36, 28, true, false, false}, {44, 32, true, false, false}, {64, 32, true, true, false},
-      {16, 64, false, true, false}, {32, 64, true, true, false}, {64, 64, true, true, true}, {64, 128, true, true, true}, {1, 1, false, false, false}};
+  // psi(dS) past the caches: heads, key blocks, Q blocks, d, mask; loaded, stored
+  const struct { int heads, nblk, nqblk, d; bool causal, load, store; } kTraffic[] = {{36, 28, 28, 128, true, false, false}, {46, 32, 32, 128, true, true, false},
+      {64, 32, 32, 128, true, true, false}, {16, 64, 64, 128, false, true, false}, {32, 64, 64, 128, true, true, false}, {64, 64, 64, 128, true, true, true},
+      {64, 128, 128, 128, true, true, true}, {1, 1, 1, 64, false, false, false}, {32, 32, 32, 128, false, false, false}, {36, 32, 32, 128, false, true, false},
+      {26, 32, 32, 128, false, false, false}, {3, 128, 128, 128, false, false, false}, {12, 64, 64, 64, false, false, false}, {48, 32, 32, 64, false, true, false},
+      {20, 64, 64, 64, true, false, false}, {5, 128, 128, 64, true, false, false}, {64, 32, 32, 64, true, true, false}, {120, 16, 16, 128, true, true, false},
+      {200, 8, 8, 128, true, false, false}, {40, 128, 16, 128, false, true, false}, {24, 16, 64, 128, false, false, false}, {1, 1040000, 1, 128, false, true, true}};
   for (const auto& c : kTraffic) {
-    const DsTraffic t = ds_traffic(c.heads, c.nblk, c.nblk, 0, c.causal);
-    if (t.load_past != c.load || t.store_past != c.store) return printf("ds_traffic: %d heads of %d blocks, mask %d\n", c.heads, c.nblk, c.causal), 1;
+    const DsTraffic t = ds_traffic(c.heads, c.nblk, c.nqblk, 0, c.d, c.causal);
+    if (t.load_past != c.load || t.store_past != c.store) return printf("ds_traffic: %d heads of %d x %d blocks, d %d, mask %d\n", c.heads, c.nqblk, c.nblk, c.d, c.causal), 1;
   }
   // dQ with one Q block per workgroup: heads, key blocks, Q blocks, mask
   const struct { int heads, nblk, nqblk; bool causal, split; } kDq[] = {{1, 1, 1, true, true}, {5000, 3, 1, false, true}, {24, 32, 32, true, true}, {25, 32, 32, true, false},

@@ -32,11 +32,11 @@ def test_one_q_block_per_workgroup_gives_the_same_bits(Nq, Nk, d, causal, token_
 
 
 def test_psi_ds_past_the_caches_and_one_stage():
-    """Tiles of more than 100 MB (12 heads of N = 6144 with the mask, and 8, which take the form with one Q block per workgroup: loaded past
-    the caches, the last heads first) against one head's; a walk of one stage."""
+    """Tiles that do not fit the caches beside the tensors (12 heads of N = 6144 with the mask, and 6 of 8192, which take the form with one Q block per
+    workgroup: loaded past them, the last heads first) against one head's; a walk of one stage."""
     d = 128
     g = torch.Generator(device="cuda").manual_seed(5)
-    for heads, N in ((12, 6144), (8, 6144), (3, 64)):
+    for heads, N in ((12, 6144), (6, 8192), (3, 64)):
         Q, K, V, dO = (torch.randn((1, heads, N, d), generator=g, device="cuda").to(torch.bfloat16) for _ in range(4))
         p = binding.SageParams(1, heads, N, d)
         O, L = binding.sagebwd_fwd(Q, K, V, p)
