@@ -563,7 +563,7 @@ __global__ void __launch_bounds__(512, MODE == kBwdMaxOnly ? 4 : 1) sage_bwd_ker
     if constexpr (!B_BEFORE_A) phase_b();
     barrier_all_memory();   // the interval's LDS traffic, copies and stores are complete
   };
-  // steady intervals: t >= 2 (all three tiles exist), tile t above the diagonal and not the last row
+  // steady intervals: t >= DRAIN (the tiles of all phases exist), tile t above the diagonal and not the last row
   // (a KV block with keys that do not exist masks them in every tile: no branch-free intervals for its group)
   // (under the mask: while Q block itop - ISTEP * t lies above the group's diagonal block j - sb)
   const int t_steady_end = (!gvalid || kvalid < 64) ? 0 : (CAUSAL ? min((itop + sb - j + ISTEP - 1) / ISTEP, T - 1) : T - 1);
@@ -632,6 +632,9 @@ struct BwdStageB1 {           // operands of phase B for one Q block
   float muq[D];               // Q-smoothing block mean
 };
 
+
+// Stage of the dQ kernels' loads: past the last one of a walk that one again (never used).  (Host code too, as below.)
+__host__ __device__ inline int dq_stage(int j, int n_j) { return j < n_j ? j : n_j - 1; }
 
 // The Q blocks such a workgroup walks, from the last one down: tile t = Q block itop - t, t = 0 .. T - 1.  Interval t
 // copies the operands of phase A of tile t + 2 and of phase B of tile t, past the last tile that one again (never used):
@@ -766,8 +769,9 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_single_kernel(BwdArgs args) {
     };
     auto read_A = [&](const int t) __attribute__((always_inline)) {
       const BwdStageA1<D>& st = L.stA[t % 3];
-      // (with Q-smoothing a CU holds one of these workgroups whatever the registers: -delta is read ahead as well, 3 %; at d = 64 behind the
-      // operands, which the first products wait for: 16 heads of N = 2048 69.1 -> 68.4 us, 4 of 4096 107.3 -> 106.1, d = 128 78.0 -> 79.6)
+      // (with Q-smoothing a CU holds one of these workgroups whatever the registers: -delta is read ahead as well, 3 %; at d = 64
+      // behind the operands, which the first products wait for: 16 heads of N = 2048 69.1 -> 68.4 us, 4 of 4096 107.3 -> 106.1, d =
+      // 128 78.0 -> 79.6)
       if constexpr (QSMOOTH && D == 128) read_delta(t);
 #pragma unroll
       for (int s = 0; s < KB; s++) {
@@ -1306,8 +1310,8 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_wide_kernel(BwdArgs args) {
           if (m % 2 == 0 && m / 2 + 1 < KB) read_V(m / 2 + 1);
           if (2 * m % LE == 0 && 2 * m + LE < 32) read_L(2 * m / LE + 1);
           dp[m & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(da[m % 3], vb[(m / 2) % 2], dp[m & 1], 0, 0, 0);
-          // (first through most of dP too: its operands are read under the older wave's dK.  Dropped at product 0, 3, 7, 11, 16: 64 heads of N = 8192
-          // with the mask 1997, 1991, 1986, 1965, 2000 us)
+          // (first through most of dP too: its operands are read under the older wave's dK.  Dropped at product 0, 3, 7, 11, 16: 64
+          // heads of N = 8192 with the mask 1997, 1991, 1986, 1965, 2000 us)
           if (m == 11) first_for_younger_waves<0>(wave);
           if (m >= 2) form_max(2 * m - 4);
           if (m >= 1) {
@@ -1361,8 +1365,8 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_wide_kernel(BwdArgs args) {
   // unmasked intervals: both tiles exist in full, tile t above the diagonal
   const int t_steady_end = !valid || kvalid < 64 ? 0 : CAUSAL ? min(itop + sb - j, T - 1) : T - 1;
   // the first interval, the unmasked ones, the others (written so that their masked form is there once), the last one.  The first and
-  // the last are half an interval each: in the masked form, as they were, each wasted the other half (64 heads of N = 2048 with the mask 136.3 -> 129.2
-  // us, 32 of 4096 236 -> 228.5, 64 of 8192 1970 -> 1900, 8 of 8192 without 438 -> 429, the dP priority included).
+  // the last are half an interval each: in the masked form, as they were, each wasted the other half (64 heads of N = 2048 with the
+  // mask 136.3 -> 129.2 us, 32 of 4096 236 -> 228.5, 64 of 8192 1970 -> 1900, 8 of 8192 without 438 -> 429, the dP priority included).
   interval(0, std::true_type{}, std::false_type{}, std::true_type{});
 #pragma clang loop unroll(disable)
   for (int t = 1; t < T;) {
@@ -1420,9 +1424,9 @@ struct DqArgs {
   float sm_scale;       // times 2^13
 };
 
-// The INT32 sums arrive as a 2^-26 (mfma_from_bias).  Half of that is made up in the weights (sm_scale), half at the end, so that gradients as
-// large and as small as FP32 holds come out as with converted sums: with all of it at the end the sums of gradients below 2^-100 were
-// denormal.
+// The INT32 sums arrive as a 2^-26 (mfma_from_bias).  Half of that is made up in the weights (sm_scale), half at the end: with all of it at
+// the end the sums of gradients below 2^-100 were denormal.  (A weight is then 2^13 times what a converted sum's would be: where
+// s_dS s_K scale is 2^115 and more it is infinite, though the gradient of small codes might not be.)
 constexpr float kDqWeight = 8192.0f;
 static_assert(kDqWeight * kDqWeight == kTwo26, "the two halves");
 
@@ -1441,11 +1445,11 @@ static_assert(kDqWeight * kDqWeight == kTwo26, "the two halves");
 // registers.  Three workgroups share a CU: about 96 KiB of psi(dS) in flight per CU.
 // (Every lane takes part in the scale copy: a memory operation under a lane mask sits behind a branch,
 // and with a path that skips it the compiler stops counting the loads in flight and waits for all of
-// them before each use.)  Measured: the kernel runs nearly at the speed of its psi(dS) stream alone (no
-// arithmetic, no K^ copies: 0.51 ms of 0.54 for 64 heads of N = 8192 with the mask, where a plain read
-// stream over the same bytes reaches 5.6 TB/s on this GPU); ring depths 3 to 7 and two or three workgroups
-// per CU change nothing.  What did: psi(dS) stored and loaded past the caches (see ds_traffic), 538 -> 520 us, dQ, dK and dV stored past
-// them (what a kernel leaves dirty in the L2 is written back at its end) -> 506, and a subtraction in place of the conversion -> 491.
+// them before each use.)  Measured, 64 heads of N = 8192 with the mask: with cached loads, conversions and cached stores the
+// kernel took 0.54 ms, its psi(dS) stream alone (no arithmetic, no K^ copies) 0.51, where a plain read stream over the same
+// bytes reaches 5.6 TB/s on this GPU; ring depths 3 to 7 and two or three workgroups per CU changed nothing.  What did: psi(dS)
+// stored and loaded past the caches (see ds_traffic), 538 -> 520 us, dQ, dK and dV stored past them (what a kernel leaves dirty in
+// the L2 is written back at its end) -> 506, and a subtraction in place of the conversion -> 491.
 // STREAM: psi(dS) is loaded past the caches.
 template <int D, bool CAUSAL, bool STREAM>
 __global__ void __launch_bounds__(256, 3) sage_bwd_dq_kernel(DqArgs args) {
@@ -1498,7 +1502,7 @@ __global__ void __launch_bounds__(256, 3) sage_bwd_dq_kernel(DqArgs args) {
     a[1] = STREAM ? stream_load((const v4i*)(p + 1024)) : *(const v4i*)(p + 1024);
   };
   auto load_k = [&](int j, int sl) __attribute__((always_inline)) {
-    const int jc = j < n_j ? j : n_j - 1;
+    const int jc = dq_stage(j, n_j);
     const int8_t* src = kth + (size_t)jc * TILE;
     int8_t* dst = lds + sl * KSLOT + wave * 1024;
     async_copy_16(src, dst);
@@ -1608,14 +1612,16 @@ __global__ void __launch_bounds__(256, 3) sage_bwd_dq_kernel(DqArgs args) {
   }
 }
 
-// dQ of calls whose launch of the kernel above does not fill the machine: it then takes as long as its longest chain of stages, at about 0.7 us a stage, most of
-// it the latency of one wave's transposition, products and updates in turn.  Here a workgroup owns ONE Q block and takes two stages (KV blocks) an
-// interval; wave (row half, channel block of 32) owns 32 x 32 of dQ, eight waves at d = 128 and four at d = 64, and a fragment of psi(dS) is
-// transposed by one wave only, an interval ahead, and handed on through LDS: 0.4 us a stage.  (An interval first issues all its LDS reads and the
-// transposing product, and the loads behind them; with the transposition hoisted over the barrier of the interval before by the compiler, which then waited for every load in flight, a stage took
-// 0.5.)  Twice the copies of K^ of the kernel above are what a full machine pays.  The order of the sums is that of the kernel above: the same bits.
-// us, kernel above -> this one, with the mask: 8 heads of N = 4096 48.5 -> 25.5, 24 of 2048 28.6 -> 21.5, 6 of 9000 104 -> 69, 2 of 1368 21.0 -> 12.0, 6 of 4467, d = 64, 35.0 ->
-// 24.1; without: 6 of 2297 29.8 -> 16.5, 12 of 768 14.5 -> 9.3 (the rule: use_dq_split).
+// dQ of calls whose launch of the kernel above does not fill the machine: it then takes as long as its longest chain of stages, at
+// about 0.7 us a stage, most of it the latency of one wave's transposition, products and updates in turn.  Here a workgroup owns ONE
+// Q block and takes two stages (KV blocks) an interval; wave (row half, channel block of 32) owns 32 x 32 of dQ, eight waves at d =
+// 128 and four at d = 64, and a fragment of psi(dS) is transposed by one wave only, an interval ahead, and handed on through LDS:
+// 0.4 us a stage.  (An interval first issues all its LDS reads and the transposing product, and the loads behind them; with the
+// transposition hoisted over the barrier of the interval before by the compiler, which then waited for every load in flight, a stage
+// took 0.5.)  Twice the copies of K^ of the kernel above are what a full machine pays.  The order of the sums is that of the kernel
+// above: the same bits. us, kernel above -> this one, with the mask: 8 heads of N = 4096 48.5 -> 25.5, 24 of 2048 28.6 -> 21.5, 6 of
+// 9000 104 -> 69, 2 of 1368 21.0 -> 12.0, 6 of 4467, d = 64, 35.0 -> 24.1; without: 6 of 2297 29.8 -> 16.5, 12 of 768 14.5 -> 9.3
+// (the rule: use_dq_split).
 template <int D, bool CAUSAL, bool STREAM>
 __global__ void __launch_bounds__(4 * D, D == 128 ? 4 : 2) sage_bwd_dq_split_kernel(DqArgs args) {
   constexpr int KS = D / 32;               // channel blocks
@@ -1654,7 +1660,7 @@ __global__ void __launch_bounds__(4 * D, D == 128 ? 4 : 2) sage_bwd_dq_split_ker
   const unsigned lane16 = lane * 16;
 
   // Stages past the end are clamped (see sage_bwd_dq_kernel).
-  auto stage = [&](int j) { return j < n_j ? j : n_j - 1; };
+  auto stage = [&](int j) { return dq_stage(j, n_j); };
   // fragment wave + NW f of the interval's eight: four a stage
   auto load_ds = [&](int m, v4i (&a)[FW]) __attribute__((always_inline)) {
 #pragma unroll

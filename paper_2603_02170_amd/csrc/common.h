@@ -85,9 +85,9 @@ __device__ __forceinline__ float wave_max_nonneg_f32(float v) {
   return __uint_as_float(u);
 }
 
-// Loads and stores of what passes through once and does not fit the caches: they are told to let go of it first.  For whole 16-byte pieces of
-// whole lines only: stores of 8 bytes that meet in the L2 otherwise, and loads of lines that another load takes the rest of, got slower (the
-// backward of 36 heads of N = 1777, d = 64, 55 -> 83 us, a decoding step 73 -> 95).
+// Loads and stores of what passes through once and does not fit the caches: they are told to let go of it first.  For whole 16-byte
+// pieces of whole lines only: stores of 8 bytes that meet in the L2 otherwise, and loads of lines that another load takes the rest
+// of, got slower (the backward of 36 heads of N = 1777, d = 64, 55 -> 83 us, a decoding step 73 -> 95).
 template <class T>
 __device__ __forceinline__ T stream_load(const T* p) {
   return __builtin_nontemporal_load(p);
@@ -104,12 +104,12 @@ constexpr float kBiasC0 = 0.15915494309189532f;
 constexpr float kTwo26 = 67108864.0f;
 
 // The product that starts a chain from B0.  As assembly, because the compiler folds the inline constant into one product
-// only and makes a splat of 16 registers for several: with it the loop of sage_fwd_kernel formed the splat anew in every tile (8 vector and 16 scalar
-// instructions) and had no register to spare (256 and 17 parked; now 251; 16 heads of N = 8192 350 -> 337 us).  The compiler does not see a matrix instruction here, so
-// the waits around one are written out: two states after a vector write of an operand, two before the next product of the chain
-// reads the result as its C, which must be the only thing that ever reads it (a copy or a spill in between would read an unfinished
-// result), and the result is kept off its operands' registers, as the compiler keeps those of its own products of this size.  A test reads
-// both from the assembly of the build.
+// only and makes a splat of 16 registers for several: with it the loop of sage_fwd_kernel formed the splat anew in every tile (8
+// vector and 16 scalar instructions) and had no register to spare (256 and 17 parked; now 251; 16 heads of N = 8192 350 -> 337 us).
+// The compiler does not see a matrix instruction here, so the waits around one are written out: two states after a vector write of
+// an operand, two before the next product of the chain reads the result as its C, which must be the only thing that ever reads it (a
+// copy or a spill in between would read an unfinished result), and the result is kept off its operands' registers, as the compiler
+// keeps those of its own products of this size.  A test reads both from the assembly of the build.
 __device__ __forceinline__ v16i mfma_from_bias(const v4i& a, const v4i& b) {
   v16i d;
   asm("s_nop 1\n\tv_mfma_i32_32x32x32_i8 %0, %1, %2, 0.15915494\n\ts_nop 1" : "=&v"(d) : "v"(a), "v"(b));
@@ -136,9 +136,10 @@ __device__ __forceinline__ gbytes_t uniform(const void* p) {
   asm("" : "+s"(g));
   return g;
 }
-// Two 16-byte pieces per lane to base + lane_offset and OFFSET behind it, past the caches (as stream_store does) where `stream` is not 0.  The branch is inside the
-// assembly, as below, and the compiler would make one plain store of both sides.  It does not see stores here: the wait states in front are
-// for a base that a vector instruction wrote, the one behind for an overwrite of the data, and a wait for them has to be written out.
+// Two 16-byte pieces per lane to base + lane_offset and OFFSET behind it, past the caches (as stream_store does) where `stream` is
+// not 0.  The branch is inside the assembly, as below, and the compiler would make one plain store of both sides.  It does not see
+// stores here: the wait states in front are for a base that a vector instruction wrote, the one behind for an overwrite of the data,
+// and a wait for them has to be written out.
 template <int OFFSET>
 __device__ __forceinline__ void store_pair(gbytes_t base, unsigned lane_offset, const v4i& a, const v4i& b, int stream) {
   asm volatile(
@@ -222,10 +223,11 @@ struct WorkItem {
 // > 0: that many heads of an XCD per set; < 0: the dense layout, sets of that many heads (on a machine of one XCD, so to
 // speak, so that the mapping below stays one formula).  A set divides the heads evenly; where four do not divide an XCD's heads,
 // short sequences take the largest number up to eight that does (five heads one at a time left the last head's heaviest items to the end:
-// calls with the mask, forward and backward in us, 40 heads of N = 1024 43 + 90 -> 39 + 65, of 2048 84 + 196 -> 73 + 167, 56 of 4096 276 + 808 -> 258 + 764;
-// nine heads have sets of three).  Where that is one or two, all of them, up to 31 heads and 768 items: 152 heads (19) of N = 512 55 + 100 -> 48 + 70, 248
-// (31) of 1024 163 + 381 -> 154 + 287; larger sets crowd the L2 (34 heads in sets of two -> all: N = 1024 164 + 323 -> 170 + 317, 2048 403 + 945 -> 421 + 980; 37 one at a
-// time -> all: 1024 190 + 407 -> 188 + 341, 2048 451 + 1084 -> 458 + 1064; 31 of 32 items, d = 64 and N = 2048, backward 667 -> 686).
+// calls with the mask, forward and backward in us, 40 heads of N = 1024 43 + 90 -> 39 + 65, of 2048 84 + 196 -> 73 + 167, 56 of 4096
+// 276 + 808 -> 258 + 764; nine heads have sets of three).  Where that is one or two, all of them, up to 31 heads and 768 items: 152
+// heads (19) of N = 512 55 + 100 -> 48 + 70, 248 (31) of 1024 163 + 381 -> 154 + 287; larger sets crowd the L2 (34 heads in sets of
+// two -> all: N = 1024 164 + 323 -> 170 + 317, 2048 403 + 945 -> 421 + 980; 37 one at a time -> all: 1024 190 + 407 -> 188 + 341,
+// 2048 451 + 1084 -> 458 + 1064; 31 of 32 items, d = 64 and N = 2048, backward 667 -> 686).
 __host__ __device__ inline int head_set_for(int items, int heads, bool always = false) {
   const bool dense = heads % 8 != 0;
   const int pool = dense ? heads : heads / 8;
@@ -272,11 +274,12 @@ __host__ __device__ inline int fold_end(int grid, int items, int rounds, int per
 
 // Both that order and a kernel with a CU to itself whose second round is to be the lighter one count on the heaviest items being the
 // first of the whole launch, which sets of heads do not give: where a set begins, its heaviest items follow the lightest of the one
-// before, and in the last round they end the launch.  Such launches take the items heaviest first over all heads (of an XCD, or of the call in
-// the dense layout); few as their workgroups are, their heads do not crowd the L2.  us, in sets -> over all heads: forward (four waves per 32 queries), 7
-// heads of N = 4096 77.0 -> 50.2 (two waves 59.2), 5 of 6144 91.4 -> 66.1 (79.2), 5 of 8192 133.4 -> 110.1 (127.3), 9 of 3000 49.5 -> 42.9 (48.3); forward,
-// 7 of 7000 131 -> 110.6 (not folded 127), 11 of 7000 157.6 -> 135.5 (152.8); d = 64, 11 of 7000 125 -> 97.5 (115.5); training steps, d =
-// 64, 5 of 5000 195 -> 161 (173), 10 of 4096 193 -> 165 (185), 7 of 7000 345 -> 275 (333).
+// before, and in the last round they end the launch.  Such launches take the items heaviest first over all heads (of an XCD, or of
+// the call in the dense layout); few as their workgroups are, their heads do not crowd the L2.  us, in sets -> over all heads:
+// forward (four waves per 32 queries), 7 heads of N = 4096 77.0 -> 50.2 (two waves 59.2), 5 of 6144 91.4 -> 66.1 (79.2), 5 of 8192
+// 133.4 -> 110.1 (127.3), 9 of 3000 49.5 -> 42.9 (48.3); forward, 7 of 7000 131 -> 110.6 (not folded 127), 11 of 7000 157.6 -> 135.5
+// (152.8); d = 64, 11 of 7000 125 -> 97.5 (115.5); training steps, d = 64, 5 of 5000 195 -> 161 (173), 10 of 4096 193 -> 165 (185),
+// 7 of 7000 345 -> 275 (333).
 __host__ __device__ inline int all_heads(int heads) { return heads % 8 != 0 ? -heads : heads / 8; }
 struct LaunchOrder {
   int head_set, fold_end;
@@ -290,10 +293,10 @@ __host__ __device__ inline int quad_head_set(int heads, int items) {
   return grid_for(heads, items) > 256 ? all_heads(heads) : head_set_for(items, heads);
 }
 
-// Row of K or V that a load of sage_fwd_decode_kernel for row `row` reads: a row that does not exist re-reads the last one that does (which changes no
-// maximum of its block), and all rows of a block that is not the wave's (`mine` false: the load ahead of a wave's last block) are one
-// row.  The loop stays without a branch, and no block is read twice (two sequences of 32 heads of 8192 keys, where that was an eighth of
-// all reads: 75.5 us a call -> 73.0 with Q's fragments in LDS).
+// Row of K or V that a load of sage_fwd_decode_kernel for row `row` reads: a row that does not exist re-reads the last one that does
+// (which changes no maximum of its block), and all rows of a block that is not the wave's (`mine` false: the load ahead of a wave's
+// last block) are one row.  The loop stays without a branch, and no block is read twice (two sequences of 32 heads of 8192 keys,
+// where that was an eighth of all reads: 75.5 us a call -> 73.0 with Q's fragments in LDS).
 __host__ __device__ inline int decode_row(int row, bool mine, int nk) {
   const int last = mine ? nk - 1 : 0;
   return row < last ? row : last;

@@ -37,12 +37,12 @@ inline bool fwd_quad_is_faster(long long heads, int nblk, int nqblk, int d, bool
 // barrier; where they share one, its narrow loads, of Q's means for every 16 keys again, cost more than that.  Whole forward
 // calls that differ in this kernel only, us, qsmooth_bias_kernel -> the short one, by workgroups (heads of N):
 // d = 128: 1 (1 of 64) 14.2 -> 13.4, 40 (40 of 41) 14.6 -> 13.7, 64 (8 of 512) 23.2 -> 22.6, 128 (8 of 1000) 28.9 -> 29.0, 256 (16 of
-// 1024) 33.3 -> 33.0, (32 of 512) 28.0 -> 27.4, (2 of 1024 against 8192 keys) 73.9 -> 74.0; one Q block: 300 22.8 -> 22.7, 512 26.3 -> 25.8;
-// two: 300 26.0 -> 26.1, 500 29.0 -> 28.8; three: 300 26.4 -> 26.7; four: 280 27.4 -> 27.8; eight: 320 31.4 -> 32.4; 16: 288 36.4 ->
-// 38.7, 480 40.2 -> 42.1, the step 92.4 -> 94.2.
+// 1024) 33.3 -> 33.0, (32 of 512) 28.0 -> 27.4, (2 of 1024 against 8192 keys) 73.9 -> 74.0; one Q block: 300 22.8 -> 22.7, 512 26.3
+// -> 25.8; two: 300 26.0 -> 26.1, 500 29.0 -> 28.8; three: 300 26.4 -> 26.7; four: 280 27.4 -> 27.8; eight: 320 31.4 -> 32.4; 16:
+// 288 36.4 -> 38.7, 480 40.2 -> 42.1, the step 92.4 -> 94.2.
 // d = 64: 6 (2 of 130) 14.0 -> 13.2, 208 (13 of 1008) 27.4 -> 26.9, 256 (16 of 1024) 25.4 -> 25.0; one Q block: 500 18.3 -> 17.9, four: 280
-// 21.0 -> 20.9, 480 21.5 -> 21.2; eight: 320 23.12 -> 23.10, 384 24.2 -> 24.1; nine: 288 23.2 -> 23.4; 12: 264 26.9 -> 27.3; 16: 288 29.7 ->
-// 30.3, 480 33.3 -> 34.1.
+// 21.0 -> 20.9, 480 21.5 -> 21.2; eight: 320 23.12 -> 23.10, 384 24.2 -> 24.1; nine: 288 23.2 -> 23.4; 12: 264 26.9 -> 27.3; 16: 288
+// 29.7 -> 30.3, 480 33.3 -> 34.1.
 // From two workgroups per CU on (d = 128, 800 of four Q blocks 43.2 -> 44.2; d = 64, 748 of seven 31.0 -> 32.0) and from 17 Q blocks on,
 // where the larger products have rows for all their lanes, the other kernel.
 inline bool use_bias_short(long long heads, int nblk, int nqblk, int d) {
@@ -53,13 +53,13 @@ inline bool use_bias_short(long long heads, int nblk, int nqblk, int d) {
 // ---- decoding: sage_fwd_decode_kernel -----------------------------------------------------------------
 // A query block of at most 32 rows that sees every key takes that kernel, which quantises K and V itself, instead of codes in the
 // workspace: with a long cache, or with many heads (its code is long, and with little work few workgroups share the cost of
-// fetching it).  Whole calls with one query row, us with codes -> this way.  d = 128: 1 head, 16 key blocks 18.6 -> 19.7, 20 20.6 -> 20.3; 16 heads, 20 23.1
-// -> 21.2; 64 of 12 24.6 -> 20.6; 128 of 4 20.4 -> 16.2, 86 of 6 20.7 -> 20.3, 48 of 14 25.1 -> 21.3.  With seven or eight blocks a head's
-// one workgroup walks two blocks with each wave: 64 heads of 8 19.7 -> 21.0 (without K-smoothing 16.9 -> 16.1), 80 of 8 22.4 -> 21.7.  d = 64: 16 heads of 12 15.1 -> 16.1,
-// 1 of 16 16.1 -> 15.0; 64 of 8 16.0 -> 14.1, 128 of 4 15.2 -> 11.9, 300 of 2 15.1 -> 13.1.
-// K-smoothing costs this way a launch for the mean, which the quantiser sums by itself in short heads: with one block a head 512 heads
-// of d = 128 13.0 -> 17.3, 4096 87.0 -> 89.1, 512 of d = 64 11.3 -> 13.3 (without K-smoothing 12.2 -> 10.1 at d = 128); with two, d =
-// 128, 300 heads 16.8 -> 17.6, 340 17.2 -> 17.7, 384 18.7 -> 17.7.
+// fetching it).  Whole calls with one query row, us with codes -> this way.  d = 128: 1 head, 16 key blocks 18.6 -> 19.7, 20 20.6 ->
+// 20.3; 16 heads, 20 23.1 -> 21.2; 64 of 12 24.6 -> 20.6; 128 of 4 20.4 -> 16.2, 86 of 6 20.7 -> 20.3, 48 of 14 25.1 -> 21.3.  With
+// seven or eight blocks a head's one workgroup walks two blocks with each wave: 64 heads of 8 19.7 -> 21.0 (without K-smoothing 16.9
+// -> 16.1), 80 of 8 22.4 -> 21.7.  d = 64: 16 heads of 12 15.1 -> 16.1, 1 of 16 16.1 -> 15.0; 64 of 8 16.0 -> 14.1, 128 of 4 15.2 ->
+// 11.9, 300 of 2 15.1 -> 13.1. K-smoothing costs this way a launch for the mean, which the quantiser sums by itself in short heads:
+// with one block a head 512 heads of d = 128 13.0 -> 17.3, 4096 87.0 -> 89.1, 512 of d = 64 11.3 -> 13.3 (without K-smoothing 12.2
+// -> 10.1 at d = 128); with two, d = 128, 300 heads 16.8 -> 17.6, 340 17.2 -> 17.7, 384 18.7 -> 17.7.
 inline bool decode_long_enough(long long heads, int nblk, int d, bool k_smooth) {
   if (nblk >= (d == 64 ? 16 : 20)) return true;
   const long long blocks = heads * nblk;
@@ -75,12 +75,12 @@ inline bool decode_long_enough(long long heads, int nblk, int d, bool k_smooth) 
 // (about 3 us, more with many query rows, whose partial results are FP32 rows).
 // Two workgroups fit a CU, so long caches take as many as fill one round of them.  A head keeps one workgroup where that alone is as good.
 // (a) Up to eight blocks, two for each wave.  us with the fewest blocks per wave -> with one workgroup, 1 and 32 query rows: d = 64, 128
-// heads of 8 16.8 -> 14.8, 20.2 -> 15.1, 64 of 8 14.6 -> 14.1, 16.1 -> 14.3; d = 128, 110 of 5 21.1 -> 20.3, 23.3 -> 20.6, 96 of 8 21.4 -> 21.9, 23.8 -> 22.4.
-// (b) Between one and two rounds of one workgroup per CU a second one per head fills no CU better: from 171 heads on if the walks are
-// short (180 heads of 12, d = 64, 25.1 -> 19.7; of 32, d = 128, 63.7 one, 59.6 two; 200 of 64, d = 64, 68.6 one, 63.4 two), from 241 on always (240 of 64, d =
-// 64, 73.1 one, 70.9 two; 256 of 12, d = 128, 38.4 -> 34.2, of 64, 16 query rows, 148.2 two, 146.6 one, 1 row 144.1 two, 146.3 one).
-// At d = 64 one workgroup per CU is enough while its waves have two blocks at most: 64 heads of 32 23.2 -> 20.0, 128 of 16 with 32 rows 25.9 -> 23.8;
-// 128 of 64 44.7 -> 43.2 with two per CU.
+// heads of 8 16.8 -> 14.8, 20.2 -> 15.1, 64 of 8 14.6 -> 14.1, 16.1 -> 14.3; d = 128, 110 of 5 21.1 -> 20.3, 23.3 -> 20.6, 96 of 8
+// 21.4 -> 21.9, 23.8 -> 22.4. (b) Between one and two rounds of one workgroup per CU a second one per head fills no CU better: from
+// 171 heads on if the walks are short (180 heads of 12, d = 64, 25.1 -> 19.7; of 32, d = 128, 63.7 one, 59.6 two; 200 of 64, d = 64,
+// 68.6 one, 63.4 two), from 241 on always (240 of 64, d = 64, 73.1 one, 70.9 two; 256 of 12, d = 128, 38.4 -> 34.2, of 64, 16 query
+// rows, 148.2 two, 146.6 one, 1 row 144.1 two, 146.3 one). At d = 64 one workgroup per CU is enough while its waves have two blocks
+// at most: 64 heads of 32 23.2 -> 20.0, 128 of 16 with 32 rows 25.9 -> 23.8; 128 of 64 44.7 -> 43.2 with two per CU.
 inline int decode_blocks_per_wave(long long heads, int nblk, int d) {
   auto blocks = [&](long long per_cu) {
     long long n = per_cu * kCus / heads;      // workgroups of a head
@@ -164,13 +164,14 @@ inline BwdEstimate bwd_estimate(long long heads, int nblk, int nqblk, int shift_
 }
 
 // Four KV blocks per workgroup?  Whole backward calls, us, two -> four.  Without
-// the mask: 32 heads of N = 1024 65.6 two (one round), 34 104 -> 85; 102 of 576 82.8 -> 92.5 (two rounds either way), 110 100.4 -> 97.2; 30 of 2112 206 -> 241, 16 of 4160 502 -> 470;
-// 520 of 64 38.1 -> 45.4, 140 of 256 51.5 -> 43.1, 170 of 320 62.5 -> 68.0.  With it: 34 of 2048 139.7 -> 143.8, 36 148.6 -> 145.6; 43 of 1344 92.3 -> 101.6, 60 121 -> 108; 20
-// of 3200 177 -> 202, 20 of 4096 284 -> 270; 520 of 64 40.4 -> 45.4, 216 of 192 45.0 -> 37.0.  Numerics blocks of 128 and Q-smoothing have the
-// same lines (34 of 2048, blocks of 64 x 128 140 -> 144, 128 x 64 179 -> 183, 128 x 128 180 -> 186; 36 151 -> 145, 189 -> 185, 191 -> 188).
+// the mask: 32 heads of N = 1024 65.6 two (one round), 34 104 -> 85; 102 of 576 82.8 -> 92.5 (two rounds either way), 110 100.4 ->
+// 97.2; 30 of 2112 206 -> 241, 16 of 4160 502 -> 470; 520 of 64 38.1 -> 45.4, 140 of 256 51.5 -> 43.1, 170 of 320 62.5 -> 68.0.
+// With it: 34 of 2048 139.7 -> 143.8, 36 148.6 -> 145.6; 43 of 1344 92.3 -> 101.6, 60 121 -> 108; 20 of 3200 177 -> 202, 20 of 4096
+// 284 -> 270; 520 of 64 40.4 -> 45.4, 216 of 192 45.0 -> 37.0.  Numerics blocks of 128 and Q-smoothing have the same lines (34 of
+// 2048, blocks of 64 x 128 140 -> 144, 128 x 64 179 -> 183, 128 x 128 180 -> 186; 36 151 -> 145, 189 -> 185, 191 -> 188).
 inline bool bwd_wide_is_faster(long long heads, int nblk, int nqblk, int shift_blocks, bool causal) {
-  // (one and two blocks leave half of the workgroup idle; one round of workgroups with two blocks each is never longer, nor a little more than
-  // one of short walks with the mask: 110 heads of 320 40.7 -> 42.8, 97 of 384 48.0 -> 46.5)
+  // (one and two blocks leave half of the workgroup idle; one round of workgroups with two blocks each is never longer, nor a little
+  // more than one of short walks with the mask: 110 heads of 320 40.7 -> 42.8, 97 of 384 48.0 -> 46.5)
   if (nblk <= 2 || heads * nblk <= (causal && nblk > 4 ? 9 * kCus / 4 : 2 * kCus)) return false;
   // three: 272 heads 49.3 -> 55.6 with the mask, 300 without 59.7 -> 60.6, 480 79.6 -> 71.6, 520 88.2 -> 92.7, 573 99.1 -> 95.2
   if (nblk == 3) return heads <= kCus || (heads - 1) % kCus >= 48;
@@ -180,15 +181,16 @@ inline bool bwd_wide_is_faster(long long heads, int nblk, int nqblk, int shift_b
   // (long walks of all lengths: the longest one decides; 272 workgroups of N = 4096 188 -> 207, 304 270 -> 270, 320 225 -> 214)
   if (!even && nblk > 64) return wgs > kCus * 6 / 5;
   const BwdEstimate t = bwd_estimate(heads, nblk, nqblk, shift_blocks, causal);
-  // (where both are near, the estimate is 2 % too good for two blocks with the mask, 35 heads of 2048 149 -> 146, 20 of 4096 284 -> 270, and 3 % for
-  // long walks without, 24 of 3776 528 -> 508, 16 of 4160 502 -> 470)
+  // (where both are near, the estimate is 2 % too good for two blocks with the mask, 35 heads of 2048 149 -> 146, 20 of 4096 284 ->
+  // 270, and 3 % for long walks without, 24 of 3776 528 -> 508, 16 of 4160 502 -> 470)
   return t.four < (!even ? 1.02 : nblk > 48 ? 1.03 : 1.0) * t.two;
 }
 
 // Heads of the next group of a backward whose psi(dS) does not fit the scratch at once: `most` do, `left` are left.  Where all
 // workgroups run for about the same time a group takes whole rounds of them, so the size is the one with the shortest estimate in all,
-// the largest of those (32 heads of N = 32768 without the mask: 7 heads fill three and a half rounds of workgroups with four KV blocks and take 7.11 ms,
-// 6 take 5.54; the training step 6 % faster).  Beyond 32 rounds a part of one is 3 %.  `wide`: the call may take that form.
+// the largest of those (32 heads of N = 32768 without the mask: 7 heads fill three and a half rounds of workgroups with four KV
+// blocks and take 7.11 ms, 6 take 5.54; the training step 6 % faster).  Beyond 32 rounds a part of one is 3 %.  `wide`: the call may
+// take that form.
 inline int bwd_heads_of_group(int most, int left, int nblk, int nqblk, int shift_blocks, bool causal, bool wide) {
   if (left <= most) return left;
   if (!wide || !even_walks(nblk, nqblk, causal) || (long long)most * ((nblk + 3) / 4) > 32 * kCus) return most;
@@ -216,16 +218,17 @@ inline int bwd_heads_of_group(int most, int left, int nblk, int nqblk, int shift
 // sage_bwd_wide_kernel stores past the caches too (and the heads come in order).
 // Whole steps, us, all through the caches -> loaded past them, last heads first, by MB in all (of them psi(dS); heads of N).
 // d = 128, mask: 189 (129; 4 of 8192) 293 -> 294, 192 (42; 80 of 1024) 136 -> 140, 215 (28; 200 of 512) 146 -> 152, 218 (113; 14 of 4096)
-// 275.1 -> 274.9, 243 (86; 42 of 2048) 218.7 -> 217.1, 250 (130; 16 of 4096) 293.5 -> 291.9, 266 (94; 46 of 2048) 226.5 -> 225.4, 283 (193; 6 of
-// 8192) 448 -> 442, 288 (63; 120 of 1024) 215.7 -> 213.3, 302 (107; 52 of 2048) 251 -> 245, 360 (79; 150 of 1024) 264 -> 262.
-// d = 128, no mask: 188 (128; 8 of 4096) 250 -> 251, 206 (104; 26 of 2048) 207.6 -> 209.0, 230 (80; 80 of 1024) 220 -> 225, 237 (192; 3 of 8192)
-// 420 -> 423, 248 (128; 32 of 2048) 230.7 -> 233.2, 277 (128; 16 of 1024 against 8192 keys) 259.0 -> 259.8, 279 (144; 36 of 2048) 370 ->
-// 368, 282 (192; 12 of 4096) 356 -> 354, 287 (100; 100 of 1024) 256.6 -> 255.8, 376 (256; 16 of 4096) 420 -> 414, 496 (256; 64 of 2048) 477 -> 465.
-// d = 64: mask 198 (161; 5 of 8192) 292 -> 295, 219 (79; 150 of 1024) 184 -> 186, 237 (162; 20 of 4096) 268.5 -> 272.0, 252 (132; 64 of 2048)
-// 223 -> 221, 277 (225; 7 of 8192) 349 -> 343, 293 (106; 200 of 1024) 234 -> 230, 315 (165; 80 of 2048) 276 -> 269; no mask 193 (100; 100 of
-// 1024) 183 -> 185, 235 (160; 40 of 2048) 232.0 -> 232.7, 237 (192; 12 of 4096) 264 -> 272, 282 (192; 48 of 2048) 273 -> 268, 290 (150; 150 of 1024) 275 -> 273.
-// Stored past the caches as well, steps, us: mask, 273 MB (32 of 4096) 488 -> 488.5, 382 (20 of 6144) 698 -> 696, 24 of 6144 819 -> 818, 545 (64 of
-// 4096) 973 -> 973, 2164 (64 of 8192) 3514 -> 3485; no mask, 192 (12 of 4096) 354 -> 359, 256 (16 of 4096) 414 -> 420, 352 (22 of 4096) 697 ->
+// 275.1 -> 274.9, 243 (86; 42 of 2048) 218.7 -> 217.1, 250 (130; 16 of 4096) 293.5 -> 291.9, 266 (94; 46 of 2048) 226.5 -> 225.4,
+// 283 (193; 6 of 8192) 448 -> 442, 288 (63; 120 of 1024) 215.7 -> 213.3, 302 (107; 52 of 2048) 251 -> 245, 360 (79; 150 of 1024) 264
+// -> 262. d = 128, no mask: 188 (128; 8 of 4096) 250 -> 251, 206 (104; 26 of 2048) 207.6 -> 209.0, 230 (80; 80 of 1024) 220 -> 225,
+// 237 (192; 3 of 8192) 420 -> 423, 248 (128; 32 of 2048) 230.7 -> 233.2, 277 (128; 16 of 1024 against 8192 keys) 259.0 -> 259.8, 279
+// (144; 36 of 2048) 370 -> 368, 282 (192; 12 of 4096) 356 -> 354, 287 (100; 100 of 1024) 256.6 -> 255.8, 376 (256; 16 of 4096) 420
+// -> 414, 496 (256; 64 of 2048) 477 -> 465. d = 64: mask 198 (161; 5 of 8192) 292 -> 295, 219 (79; 150 of 1024) 184 -> 186, 237
+// (162; 20 of 4096) 268.5 -> 272.0, 252 (132; 64 of 2048) 223 -> 221, 277 (225; 7 of 8192) 349 -> 343, 293 (106; 200 of 1024) 234 ->
+// 230, 315 (165; 80 of 2048) 276 -> 269; no mask 193 (100; 100 of 1024) 183 -> 185, 235 (160; 40 of 2048) 232.0 -> 232.7, 237 (192;
+// 12 of 4096) 264 -> 272, 282 (192; 48 of 2048) 273 -> 268, 290 (150; 150 of 1024) 275 -> 273. Stored past the caches as well,
+// steps, us: mask, 273 MB (32 of 4096) 488 -> 488.5, 382 (20 of 6144) 698 -> 696, 24 of 6144 819 -> 818, 545 (64 of 4096) 973 ->
+// 973, 2164 (64 of 8192) 3514 -> 3485; no mask, 192 (12 of 4096) 354 -> 359, 256 (16 of 4096) 414 -> 420, 352 (22 of 4096) 697 ->
 // 699, 512 (32 of 4096) 846 -> 844, 768 (12 of 8192) 1380 -> 1382, 1024 (16 of 8192) 1589 -> 1567.
 struct DsTraffic {
   bool load_past, store_past;
@@ -246,17 +249,19 @@ inline DsTraffic ds_traffic(long long heads, int nblk, int nqblk, int shift_bloc
 // time they take the same time with either form: it is not what the caches hold, and the chip's power limit would explain it.)
 // Q blocks of all heads (N): step / dQ kernel, us, two Q blocks per workgroup -> one.
 // With the mask, as many keys as queries, d = 128: 512 (2048) 124 / 28 -> 114 / 17, 752 (3000) 205 / 38 -> 197 / 27, 768 (2048) 159 / 29
-// -> 155 / 22, 768 (6144) 369 / 72 -> 358 / 46; 799 (3000) 209.5 -> 210.3 (another time 211.8 -> 216.7), 880 (7000) 426 -> 422, 896 (4096) 279.7 -> 279.8, 923 (4500) 393 ->
-// 399, 960 (6144) 505 -> 512, 1024 (4096) 299 -> 304, 1136 (4500) 374 -> 379, 1248 (6144) 547 -> 550, 1312 (5200) 452 -> 458, 1476 (5200) 517
-// -> 506; d = 64: 640 (2500) 125 / 23 -> 120 / 17, 768 (2048) 110.5 / 20 -> 109.5 / 16, 1008 (1777) 117 -> 119, 1100 (7000) 407 -> 414, 1264 (5000) 306 -> 309.
-// Walks of 112 blocks and more, twice: d = 128: 968 (7700) 485 -> 492, 1024 (8192) 533 -> 534, 1128 (12000) 879 -> 871, 1280 (8192) 737 / 155 -> 697 / 111, 1392 (7400) 660
-// -> 652, 1410 (9000) 892 -> 879, 1500 (16000) 1363 -> 1350, 1536 (8192) 765 / 152 -> 742 / 124, 2000 (16000) 1497 -> 1520; d = 64: 1024 (8192) 375 -> 371,
-// 1280 (8192) 540 -> 511, 1504 (12000) 742 -> 746.
+// -> 155 / 22, 768 (6144) 369 / 72 -> 358 / 46; 799 (3000) 209.5 -> 210.3 (another time 211.8 -> 216.7), 880 (7000) 426 -> 422, 896
+// (4096) 279.7 -> 279.8, 923 (4500) 393 -> 399, 960 (6144) 505 -> 512, 1024 (4096) 299 -> 304, 1136 (4500) 374 -> 379, 1248 (6144)
+// 547 -> 550, 1312 (5200) 452 -> 458, 1476 (5200) 517 -> 506; d = 64: 640 (2500) 125 / 23 -> 120 / 17, 768 (2048) 110.5 / 20 ->
+// 109.5 / 16, 1008 (1777) 117 -> 119, 1100 (7000) 407 -> 414, 1264 (5000) 306 -> 309. Walks of 112 blocks and more, twice: d = 128:
+// 968 (7700) 485 -> 492, 1024 (8192) 533 -> 534, 1128 (12000) 879 -> 871, 1280 (8192) 737 / 155 -> 697 / 111, 1392 (7400) 660 ->
+// 652, 1410 (9000) 892 -> 879, 1500 (16000) 1363 -> 1350, 1536 (8192) 765 / 152 -> 742 / 124, 2000 (16000) 1497 -> 1520; d = 64:
+// 1024 (8192) 375 -> 371, 1280 (8192) 540 -> 511, 1504 (12000) 742 -> 746.
 // More keys than queries: 1.1 times 640 (1024) 111 -> 108, 752 (1024) 126.5 -> 127.4, 726 (4224) 370 -> 374; 1.25 times 704 (2048)
-// 194 -> 189.5; 1.5 times 544 (2048) 211 -> 200, 640 (2048) 213.5 -> 207.5, (1024) 131.8 -> 133.4 and at d = 64 95.3 -> 96.0, 726 (4224) 473 -> 490; twice 462 (4224) 481 -> 464, 496 (1024) 141 -> 136, 594 (4224) 531 -> 541, 896 (8192) 1292 -> 1279; three times 416
-// (1024) 199 -> 193, 528 (1024) 240 -> 243, 594 (4224) 782 -> 800, 736 (1024) 269 -> 284.
-// Without the mask: 512 (2048) 153 / 28 -> 152 / 22.5, (4096) 264.5 / 49 -> 261.5 / 38.5, 640 (2048) 193 -> 199, (2500) 230.5 -> 236; d = 64: 672 (1777) 135.3 ->
-// 138.  One Q block a head leaves half of the other form idle at every size: 4000 heads of N = 64 329 / 40 -> 325 / 35.
+// 194 -> 189.5; 1.5 times 544 (2048) 211 -> 200, 640 (2048) 213.5 -> 207.5, (1024) 131.8 -> 133.4 and at d = 64 95.3 -> 96.0, 726
+// (4224) 473 -> 490; twice 462 (4224) 481 -> 464, 496 (1024) 141 -> 136, 594 (4224) 531 -> 541, 896 (8192) 1292 -> 1279; three times
+// 416 (1024) 199 -> 193, 528 (1024) 240 -> 243, 594 (4224) 782 -> 800, 736 (1024) 269 -> 284. Without the mask: 512 (2048) 153 / 28
+// -> 152 / 22.5, (4096) 264.5 / 49 -> 261.5 / 38.5, 640 (2048) 193 -> 199, (2500) 230.5 -> 236; d = 64: 672 (1777) 135.3 -> 138.
+// One Q block a head leaves half of the other form idle at every size: 4000 heads of N = 64 329 / 40 -> 325 / 35.
 inline bool use_dq_split(long long heads, int nblk, int nqblk, bool causal) {
   const long long blocks = heads * nqblk;
   if (nqblk == 1 || blocks <= 2 * kCus) return true;

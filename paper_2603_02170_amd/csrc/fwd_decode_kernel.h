@@ -7,9 +7,9 @@
 // wave takes whole 64-key blocks straight from the caller's tensors: it loads a block of K in the order of
 // the F fragments, finds the block's scale, quantises in registers, forms the logits, and does the same with V,
 // whose fragments one MFMA against the identity turns from (lane = key) to (lane = channel), the operand form of
-// P^V^.  No barrier and no traffic but K and V inside the loop (and at d = 128 two fragments of psi(Q) from LDS).  psi is the pre-pass's function (quantise_16, clamp
-// and factor included), so codes and scales are the same bits for every input, NaN and blocks whose 127 / max|x| overflows
-// among them; the logits are formed as in sage_fwd_kernel's converting path.
+// P^V^.  No barrier and no traffic but K and V inside the loop (and at d = 128 two fragments of psi(Q) from LDS).  psi is the
+// pre-pass's function (quantise_16, clamp and factor included), so codes and scales are the same bits for every input, NaN and
+// blocks whose 127 / max|x| overflows among them; the logits are formed as in sage_fwd_kernel's converting path.
 //
 // Keys are split over waves (four to a workgroup, which meet in LDS) and workgroups (whose partial O, m, l a second
 // small kernel joins).
@@ -18,8 +18,8 @@
 // wave per SIMD, with K and V both loaded a block ahead, was bound by issue as much as by memory (two sequences of 32 heads of
 // 8192 keys: 65 us of the call's 92).  For d = 128 two waves have room for one block of raw values each: V is loaded under the
 // logits into the registers that K has left, the next K under P^V^, values are formed twice (for the maximum and for
-// the codes) and not held, and lane-derived values are recomputed.  The call 92.4 -> 82.8 us (with the join below; 79.1 since no block is read twice); 8 sequences of 32 heads of 4096 159 -> 148;
-// 32 heads of 8192, d = 64, 16 queries, four sequences 87 -> 75.
+// the codes) and not held, and lane-derived values are recomputed.  The call 92.4 -> 82.8 us (with the join below; 79.1 since no
+// block is read twice); 8 sequences of 32 heads of 4096 159 -> 148; 32 heads of 8192, d = 64, 16 queries, four sequences 87 -> 75.
 #pragma once
 
 #include "common.h"

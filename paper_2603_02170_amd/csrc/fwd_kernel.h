@@ -25,8 +25,8 @@
 // result is unchanged because O/l and m + log l do not depend on the reference chosen.
 //
 // INT32 -> FP32 without a conversion instruction: the P^V^ accumulators start from the bit
-// pattern B0 of the float C0 = 1/(2 pi) (an inline constant of the ISA, see mfma_from_bias).  B0's mantissa leaves more than 2^20 codes to either end of its binade, so for
-// every possible sum |a| <= 64 * 127 * 127 the bits B0 + a read as the float C0 + a * 2^-26
+// pattern B0 of the float C0 = 1/(2 pi) (an inline constant of the ISA, see mfma_from_bias).  B0's mantissa leaves more than 2^20
+// codes to either end of its binade, so for every possible sum |a| <= 64 * 127 * 127 the bits B0 + a read as the float C0 + a * 2^-26
 // exactly.  The FP32 accumulators take w * 2^26 * (C0 + a * 2^-26) with ONE fused multiply-add
 // per value and so carry the bias C0 * 2^26 * sum(w), the same for every channel of a query;
 // it is subtracted every kBiasPeriod tiles and at the end.  Between corrections the bias stays
@@ -397,7 +397,8 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 3 : 2) sage_fwd_kernel(FwdA
   const int N = args.N;
   // First query of this wave.  The last workgroup of an odd number of Q blocks has two waves without queries: they take part in
   // the copies and the barriers, form nothing and store nothing (q0: rows that exist, for the loads of the prologue).  (Workgroups of 64
-  // queries served such calls before: half the waves to share a staged tile, and 6 heads of N = 22028, blocks of 128, took 998 us where N = 22016 took 677; now 705.)
+  // queries served such calls before: half the waves to share a staged tile, and 6 heads of N = 22028, blocks of 128, took 998 us
+  // where N = 22016 took 677; now 705.)
   const int q0w = qt * QT + 32 * wave;
   const bool has_rows = q0w < args.Nq;
   const int q0 = has_rows ? q0w : args.Nq - 32;
@@ -488,7 +489,8 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 3 : 2) sage_fwd_kernel(FwdA
   // An iteration after the wave's last tile.  From that tile on a copy is issued only where there is a tile, so the last wait of the
   // workgroup is for everything and short calls copy no tile twice (numerics blocks of 128 keys also lose the registers that the clamped
   // addresses held: 116 bytes of scratch -> 0).  With this and waves without queries that form nothing, forward calls in us: 2048 heads of
-  // N = 192, d = 64, 92.9 -> 90.3, 1100 of N = 40, d = 128, 31.7 -> 31.0, 4096 of N = 64 112.6 -> 111.2, 600 of N = 128 with blocks of 128 keys, d = 64, 27.6 -> 26.3.
+  // N = 192, d = 64, 92.9 -> 90.3, 1100 of N = 40, d = 128, 31.7 -> 31.0, 4096 of N = 64 112.6 -> 111.2, 600 of N = 128 with blocks
+  // of 128 keys, d = 64, 27.6 -> 26.3.
   auto keep_ring_moving = [&](const int j) {
     const bool issue = j + 3 < n_tiles;
     if (issue) stage_load(j + 3, nx3);
@@ -960,17 +962,31 @@ __global__ void __launch_bounds__(128 * NQ, 2) sage_fwd_pair_kernel(FwdArgs args
   if (kb == 0 && h == 0) args.LSE[(size_t)bh * args.nq_valid + q] = (m_ref + __builtin_amdgcn_logf(l_tot) - kLog2_127) * kLn2;
 }
 
+// What the copies of sage_fwd_quad_kernel read for slot p, in bytes from the head's codes: K^ of tile 0 or 1 of pair p + 2, V^ of pair p;
+// the head's last tile (at `last`) where there is no such tile.  (Host code too: a test goes through every copy.)
+__host__ __device__ inline int quad_k_offset(int p, int tile, int tile_bytes, int last) {
+  const int o = (2 * p + 4 + tile) * tile_bytes;
+  return o < last ? o : last;
+}
+__host__ __device__ inline int quad_v_offset(int p, int tile, int tile_bytes, int last) {
+  const int t = 2 * p + tile, o = (t > 0 ? t : 0) * tile_bytes;
+  return o < last ? o : last;
+}
+// Block whose scale interval t loads for tile 0 or 1 of pair t + 1: two blocks at a time, so the second may be one past the head's last.
+__host__ __device__ inline int quad_scale_block(int t) { return 2 * t + 2; }
+
 // ---- four waves per 32 queries -----------------------------------------------------------------------
-// sage_fwd_quad_kernel: the same for calls that leave half of the SIMDs idle even then.  A workgroup is one Q block, eight waves; the four waves of
-// 32 queries take TWO tiles at a time, wave (tile, key block) one 32-key block of the pair, and a quarter of O's channels each (d = 64: half of
-// them, twice over).  An interval is as long a chain as above and there are half as many.  The tiles of a pair are added to O one after the
-// other by every wave, and the sums of P of either key block in the order of the tiles, so the bits are those of the other two kernels: row maxima, P^ and
-// the sums of P go through LDS for that.
+// sage_fwd_quad_kernel: the same for calls that leave half of the SIMDs idle even then.  A workgroup is one Q block, eight waves;
+// the four waves of 32 queries take TWO tiles at a time, wave (tile, key block) one 32-key block of the pair, and a quarter of O's
+// channels each (d = 64: half of them, twice over).  An interval is as long a chain as above and there are half as many.  The tiles
+// of a pair are added to O one after the other by every wave, and the sums of P of either key block in the order of the tiles, so
+// the bits are those of the other two kernels: row maxima, P^ and the sums of P go through LDS for that.
 //
-// What an interval (0.85 us) takes is each wave's own instruction stream and its waits.  The steps, 1 and 4 heads of N = 4096, whole calls, two waves per 32
-// queries 51.8, 56.6 us: four waves 44.9, 48.7; copies whose addresses are one scalar minimum away and scales loaded behind the first waits for
-// LDS (85 -> 35 scalar instructions an interval, and such a wait no longer waits for all) 42.7, 47.0; the operands of the coming interval's products read under the end of
-// this one 41.3, 45.5.  Others: 8 heads of N = 1000 23.4 -> 21.5, 16 of 1024 25.8 -> 23.7, 8 of 2048 without the mask 35.2 -> 30.9.
+// What an interval (0.85 us) takes is each wave's own instruction stream and its waits.  The steps, 1 and 4 heads of N = 4096, whole
+// calls, two waves per 32 queries 51.8, 56.6 us: four waves 44.9, 48.7; copies whose addresses are one scalar minimum away and
+// scales loaded behind the first waits for LDS (85 -> 35 scalar instructions an interval, and such a wait no longer waits for all)
+// 42.7, 47.0; the operands of the coming interval's products read under the end of this one 41.3, 45.5.  Others: 8 heads of N = 1000
+// 23.4 -> 21.5, 16 of 1024 25.8 -> 23.7, 8 of 2048 without the mask 35.2 -> 30.9.
 template <int D, bool CAUSAL, bool QSMOOTH>
 __global__ void __launch_bounds__(512, 1) sage_fwd_quad_kernel(FwdArgs args) {
   constexpr int KS = D / 32;
@@ -1023,10 +1039,13 @@ __global__ void __launch_bounds__(512, 1) sage_fwd_quad_kernel(FwdArgs args) {
   const int last = n_tiles - 1;                                // (the diagonal block of every wave, with the mask)
   const int n_pairs = (n_tiles + 1) / 2;
 
-  // Copies of slot p: K^ of pair p + 2, V^ of pair p (from the last tile where there is no such tile: K^ is masked, V^ never used).  One lane offset serves
-  // all of a wave's copies, and a copy is a minimum and an addition of scalars away: the wave's own instruction stream is what such a call takes.
+  // Copies of slot p: K^ of pair p + 2, V^ of pair p (from the last tile where there is no such tile: K^ is masked, V^ never used).
+  // One lane offset serves all of a wave's copies, and a copy is a minimum and an addition of scalars away: the wave's own
+  // instruction stream is what such a call takes.
   constexpr int KC = NFRAG / 2 / NW;                           // copies of K^ per wave and slot, as many of V^
   static_assert(NFRAG / 2 % NW == 0 && (KC == 2 || TF == NW / 2), "a copy is of K^ for every wave, or of V^; of one tile");
+  // (raw buffers of the head's codes: the descriptor's last word has the 32-bit float format, no swizzle and no index; past N * D bytes
+  // they read zeros)
   const __amdgpu_buffer_rsrc_t krs = __builtin_amdgcn_make_buffer_rsrc((void*)KFh, 0, N * D, 0x27000);
   const __amdgpu_buffer_rsrc_t vrs = __builtin_amdgcn_make_buffer_rsrc((void*)VTh, 0, N * D, 0x27000);
   unsigned lane_off = lane * 16 + (wave % TF) * 1024;
@@ -1035,9 +1054,9 @@ __global__ void __launch_bounds__(512, 1) sage_fwd_quad_kernel(FwdArgs args) {
     const int o = wave + NW * k;                               // wave-uniform
     const int tile = KC == 2 ? k % KC : wave / TF;
     if (k < KC) {
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(krs, (lptr_t)(dst + o * 1024), 16, lane_off, min((2 * p + 4 + tile) * TILE_BYTES, last_off), 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(krs, (lptr_t)(dst + o * 1024), 16, lane_off, quad_k_offset(p, tile, TILE_BYTES, last_off), 0, 0);
     } else if (k < 2 * KC) {
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(vrs, (lptr_t)(dst + o * 1024), 16, lane_off, min(max(2 * p + tile, 0) * TILE_BYTES, last_off), 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(vrs, (lptr_t)(dst + o * 1024), 16, lane_off, quad_v_offset(p, tile, TILE_BYTES, last_off), 0, 0);
     } else if (QSMOOTH && k == 2 * KC) {
       // (every wave copies a row, so that all issue the same number)
       copy_4(uniform(args.bias + ((size_t)bh * nqblk + qblk) * N + min(max(2 * p + 2 + (wave & 1), 0), nblk - 1) * kBlock) + 4 * lane, dst + 2 * PAIR + (wave & 1) * 256);
@@ -1136,8 +1155,8 @@ __global__ void __launch_bounds__(512, 1) sage_fwd_quad_kernel(FwdArgs args) {
       w_bias += w;
       return w;
     };
-    // scales of the tiles of pairs t (sk, sv) and t - 1 (svp).  (Two at a time; past the head's last tile it is whatever lies behind them in the
-    // workspace, which has the codes behind the scales, and multiplies masked logits or nothing.)
+    // scales of the tiles of pairs t (sk, sv) and t - 1 (svp).  (Two at a time; past the head's last tile it is whatever lies behind
+    // them in the workspace, which has the codes behind the scales, and multiplies masked logits or nothing.)
     v2f sk = scalar_load2(sKh), sv = scalar_load2(sVh), svp = {0.f, 0.f};
     // K^ of pair t + 1 and V^ of pair t - 1 for interval t, read under the end of the interval before
     v4i ka[KS], va[2][2];
@@ -1235,8 +1254,8 @@ __global__ void __launch_bounds__(512, 1) sage_fwd_quad_kernel(FwdArgs args) {
         }
         // (behind the first waits for LDS: scalar loads come back out of order, and with one under way every such wait is for all)
         if (SN && sl == 1) {
-          skn = scalar_load2(sKh + 2 * t + 2);
-          svn = scalar_load2(sVh + 2 * t + 2);
+          skn = scalar_load2(sKh + quad_scale_block(t));
+          svn = scalar_load2(sVh + quad_scale_block(t));
         }
         if (sl < CPW) copy_piece(t + 2, wr, sl);
         if (SM && sl < 4) {

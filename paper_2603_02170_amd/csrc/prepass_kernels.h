@@ -64,9 +64,9 @@ __device__ __forceinline__ void column_sums(const unsigned short* __restrict__ b
     for (int e = 0; e < 8; e++) g[e] = norm.gamma[tc * 8 + e];
     // Four rows at a time: their loads, sums and shuffles overlap, and a thread takes the float64 root and quotient of one of them
     // for its neighbours.  (One row after the other, with every thread of a row taking its root, the loop is one chain, which heads
-    // of one block are as well off with, in two thirds of the registers.  Forward calls, us, one -> four: 8 heads of N = 269 21.6 -> 19.0, 8 of 4163 79.3
-    // -> 77.5, 64 of 8192 838 -> 834, 8 of 512 32.1 -> 25.6; training step of 32 heads of 2048 187.1 -> 183.2; but 1000 of 64 34.7 -> 37.3,
-    // blocks of 128, d = 64, 21.6 -> 25.1, 400 of 64 12.9 -> 14.1.)
+    // of one block are as well off with, in two thirds of the registers.  Forward calls, us, one -> four: 8 heads of N = 269 21.6 ->
+    // 19.0, 8 of 4163 79.3 -> 77.5, 64 of 8192 838 -> 834, 8 of 512 32.1 -> 25.6; training step of 32 heads of 2048 187.1 -> 183.2;
+    // but 1000 of 64 34.7 -> 37.3, blocks of 128, d = 64, 21.6 -> 25.1, 400 of 64 12.9 -> 14.1.)
     const int lane = t & 63;
     for (int r0 = 0; r0 < rows; r0 += NORMED * RPP) {  // whole passes: the shuffles need every lane
       v8us v[NORMED];
@@ -180,8 +180,8 @@ inline bool mean_inline(int heads, int N, int D) {
 }
 
 // The rounding of psi on 16 values held as FP32: q = rne(x * r) clamped to +-127 (which matters where r = 127 / max|x|
-// overflows, blocks of the smallest numbers, and for NaN: both become codes), packed into four registers.  x * r is rounded to FP32 before the addition that takes it to an integer, so the
-// codes are those of rintf.
+// overflows, blocks of the smallest numbers, and for NaN: both become codes), packed into four registers.  x * r is rounded to FP32
+// before the addition that takes it to an integer, so the codes are those of rintf.
 __device__ __forceinline__ v4i quantise_16(const float (&x)[16], const float r) {
   v4i o;
 #pragma unroll

@@ -399,9 +399,10 @@ int launch_fwd_small(const FwdArgs& a, FwdForm form, hipStream_t st) {
 
 // One Q block, or three under the mask: half or a quarter of the waves of such workgroups would have no queries.  Workgroups of two waves
 // then, at d = 64 (five fit a CU beside their rings, three of four waves; at d = 128 two of either) and once they are more than one round.
-// Whole calls, us, four waves -> two: 800 heads of N = 64 18.3 -> 16.1, 1100 22.7 -> 23.1, 1600 30.6 -> 28.8, 4096 60.4 -> 57.1; 300 heads of N = 192 with the mask
-// 22.7 -> 22.0, 350 24.8 -> 25.3, 400 29.2 -> 27.3, 2048 90.0 -> 85.5; blocks of 128 keys 4096 of 64 66.5 -> 63.1, 2048 of 192 94.6 -> 91.6.  Not with five blocks (1000
-// of N = 320 76.2 -> 78.4), more keys (2048 of 64 x 256 80.6 -> 81.3, 1300 55.3 -> 57.3) or Q-smoothing (2048 of 64 48.5 -> 50.0).
+// Whole calls, us, four waves -> two: 800 heads of N = 64 18.3 -> 16.1, 1100 22.7 -> 23.1, 1600 30.6 -> 28.8, 4096 60.4 -> 57.1; 300
+// heads of N = 192 with the mask 22.7 -> 22.0, 350 24.8 -> 25.3, 400 29.2 -> 27.3, 2048 90.0 -> 85.5; blocks of 128 keys 4096 of 64
+// 66.5 -> 63.1, 2048 of 192 94.6 -> 91.6.  Not with five blocks (1000 of N = 320 76.2 -> 78.4), more keys (2048 of 64 x 256 80.6 ->
+// 81.3, 1300 55.3 -> 57.3) or Q-smoothing (2048 of 64 48.5 -> 50.0).
 bool use_fwd_two_waves(const FwdArgs& a, bool causal) {
   return a.N == a.Nq && (a.Nq == 64 || (causal && a.Nq == 192)) && (long long)a.BH * ((a.Nq + 127) / 128) > 3 * kCus;
 }
@@ -503,8 +504,9 @@ int launch_bwd_wide(const BwdArgs& a, bool causal, hipStream_t st) {
   BwdArgs args = a;
   // Sets of heads at every length under the mask: four blocks of a head share what an XCD's L2 serves, so four heads' operands do not
   // crowd it, and the lightest workgroups of several heads end the launch.  Whole backward, us one head at a time -> in sets: 64 heads
-  // of N = 6144 1612 -> 1538, of 8192 2661 -> 2616, of 8256 2703 -> 2685, 24 of 10000 1527 -> 1472, 32 of 12288 2949 -> 2872, 16 of 16384 2482 -> 2490, 8 of
-  // 32768 6233 -> 6228.  Without the mask the rule of the other kernels (16 of 16384 4794 one at a time, 4820 in sets).
+  // of N = 6144 1612 -> 1538, of 8192 2661 -> 2616, of 8256 2703 -> 2685, 24 of 10000 1527 -> 1472, 32 of 12288 2949 -> 2872, 16 of
+  // 16384 2482 -> 2490, 8 of 32768 6233 -> 6228.  Without the mask the rule of the other kernels (16 of 16384 4794 one at a time,
+  // 4820 in sets).
   args.head_set = head_set_for(nquad, a.BH, causal);
   const int grid = grid_for(a.BH, nquad);
   if (causal) sage_bwd_wide_kernel<128, true, QSMOOTH, MODE, KV128><<<grid, 512, 0, st>>>(args);

@@ -1,6 +1,6 @@
 // Every row of dO and every Q block that the staging copies of sage_bwd_single_kernel and sage_bwd_wide_kernel read, over all small
-// shapes, the rows that a decoding step reads, and the
-// (head, item) of every workgroup, from the index functions the kernels themselves use.  Prints the first access that lies
+// shapes, the rows that a decoding step reads, the tiles and scales of sage_fwd_quad_kernel and the stages of
+// sage_bwd_dq_split_kernel, and the (head, item) of every workgroup, from the index functions the kernels themselves use.  Prints the first access that lies
 // outside the tensor, or the first workgroup without a (head, item) of its own, and returns 1.
 #include <stdio.h>
 
@@ -9,6 +9,7 @@
 
 #include "common.h"
 #include "bwd_kernel.h"
+#include "fwd_kernel.h"
 
 int every_workgroup_has_its_own_work() {
   // sets of the heads of an XCD: four, the largest divisor up to eight, all of a few short ones
@@ -69,7 +70,42 @@ int decoding_reads_every_block_once() {
   return 0;
 }
 
+// A workgroup of the forward with four waves per 32 queries: n_tiles of a head's nblk key blocks, two an interval.  Three slots are copied
+// before the first interval, slot t + 2 in interval t; interval t forms the logits of pair t + 1 from slot t - 1 and adds pair t - 1 to O from it.
+int quad_reads_the_tiles_of_its_pairs() {
+  const int tile_bytes = 8192;
+  for (int nblk = 1; nblk <= 40; nblk++)
+    for (int n_tiles = 1; n_tiles <= nblk; n_tiles++) {
+      const int last_off = (nblk - 1) * tile_bytes, pairs = (n_tiles + 1) / 2;
+      for (int p = -1; p <= pairs + 2; p++)      // intervals 0 .. pairs
+        for (int tile = 0; tile < 2; tile++) {
+          const int k = sage::quad_k_offset(p, tile, tile_bytes, last_off), v = sage::quad_v_offset(p, tile, tile_bytes, last_off);
+          const int want_k = 2 * (p + 2) + tile, want_v = 2 * p + tile;
+          const bool inside = k >= 0 && k <= last_off && k % tile_bytes == 0 && v >= 0 && v <= last_off && v % tile_bytes == 0;
+          const bool right = (want_k >= n_tiles || k == want_k * tile_bytes) && (want_v < 0 || want_v >= n_tiles || v == want_v * tile_bytes);
+          if (!inside || !right) return printf("four waves: %d of %d tiles, slot %d tile %d: K at %d, V at %d\n", n_tiles, nblk, p, tile, k, v), 1;
+        }
+      for (int t = 0; t + 1 < pairs; t++) {      // (intervals that form logits)
+        const int b = sage::quad_scale_block(t);
+        if (b != 2 * (t + 1) || b >= n_tiles || b + 1 > nblk) return printf("four waves: %d of %d tiles, interval %d: scales of block %d\n", n_tiles, nblk, t, b), 1;
+      }
+    }
+  return 0;
+}
+
+// dQ with one Q block per workgroup: two stages an interval, the loads of interval m + 3 and the copies of m + 2 in interval m.
+int dq_stages_exist() {
+  for (int n_j = 1; n_j <= 200; n_j++)
+    for (int m = 0; m <= n_j / 2 + 3; m++)
+      for (int k = 0; k < 2; k++) {
+        const int want = 2 * m + k, j = sage::dq_stage(want, n_j);
+        if (j < 0 || j >= n_j || (want < n_j && j != want)) return printf("dQ: %d stages, interval %d: stage %d\n", n_j, m, j), 1;
+      }
+  return 0;
+}
+
 int main() {
+  if (quad_reads_the_tiles_of_its_pairs() || dq_stages_exist()) return 1;
   if (every_workgroup_has_its_own_work()) return 1;
   if (decoding_reads_every_block_once()) return 1;
   long long copies = 0;

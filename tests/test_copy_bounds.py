@@ -1,5 +1,6 @@
 """The staging copies of the backward with one KV block per workgroup and with four stay inside the caller's tensors, for every small
-(N_q, N_kv) with and without the mask, and every workgroup of a launch has one (head, item) of its own: the kernels' own
+(N_q, N_kv) with and without the mask, those of the forward with four waves per 32 queries and of dQ with one Q block per workgroup take the
+tiles they are for, and every workgroup of a launch has one (head, item) of its own: the kernels' own
 index functions, run on the host (no GPU needed)."""
 import os
 import subprocess
