@@ -11,6 +11,18 @@ inline int fwd_per_cu(int d) { return d == 64 ? 3 : 2; }          // sage_fwd_ke
 constexpr int kMaxSweepPerCu = 2;                                 // sage_bwd_kernel, the sweep for the maxima
 inline int bwd_single_per_cu(int d, bool q_smooth) { return d == 64 && !q_smooth ? 2 : 1; }
 
+// Is the forward with four waves of 32 queries per workgroup folded?  The order takes a head's last query tile for its heaviest.  With an
+// odd number of Q blocks half of that tile's waves have no queries: it is the longest and yet light, and in short heads it is a
+// large part of all workgroups, which the order then pairs the wrong way.  Whole calls with the mask, us, folded -> not.  d = 128:
+// 107 heads of N = 420 32.6 -> 31.3, 100 of 448 30.8 -> 30.2, 86 of 540 34.2 -> 32.8, 98 of 576 37.0 -> 36.2, 163 of 320 33.0 ->
+// 32.5, 66 of 704 34.2 -> 33.8, 46 of 960 36.2 -> 35.8, but 57 of 960 40.1 -> 40.8; 34 of 1088 35.6 -> 35.3, 43 of 1216 41.3 ->
+// 41.6; d = 64: 113 of 320 18.9 -> 18.4, 143 of 320 21.7 -> 21.8, 92 of 420 23.0 -> 22.6, 86 of 540 26.1 -> 25.6, 71 of 704 27.4 ->
+// 26.9, 85 of 704 28.0 -> 28.5, 200 of 192 (two tiles) 17.1 -> 17.2, 245 19.3 -> 19.7.  Heads that divide over the XCDs gain all the
+// same, by the items being in order over all of them (80 of 576 31.0 -> 32.7, 64 of 960 39.9 -> 42.4; 48 of 832 33.1 -> 32.7).
+inline bool fwd_is_folded(long long heads, int n_qtiles, int nqblk) {
+  return nqblk == 2 * n_qtiles || heads % 8 == 0 || n_qtiles < 3 || n_qtiles > 8;
+}
+
 // ---- forward of few queries: two waves per 32 queries (sage_fwd_pair_kernel) or four (sage_fwd_quad_kernel) ----
 // Four while there is a CU for each workgroup of 64 queries, and at d = 128 for some more where the mask makes the second round
 // much the lighter.  An interval takes two key blocks: walks of few blocks gain with an even number of them and lose with an odd

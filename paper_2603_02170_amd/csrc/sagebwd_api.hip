@@ -416,7 +416,8 @@ int launch_fwd_full(const FwdArgs& a, bool kv128, hipStream_t st) {
   FwdArgs args = a;
   args.n_qtiles = (a.Nq + 32 * NW - 1) / (32 * NW);
   const int grid = grid_for(a.BH, args.n_qtiles);
-  const LaunchOrder order = folded_order(a.BH, args.n_qtiles, 2, CAUSAL ? fwd_per_cu(D) : 1);
+  const bool fold = CAUSAL && (NW == 2 || fwd_is_folded(a.BH, args.n_qtiles, a.Nq / kBlock));
+  const LaunchOrder order = folded_order(a.BH, args.n_qtiles, 2, fold ? fwd_per_cu(D) : 1);
   args.head_set = order.head_set;
   args.fold_end = order.fold_end;
   if (kv128) sage_fwd_kernel<D, CAUSAL, QS, NW, true><<<grid, 64 * NW, 0, st>>>(args);

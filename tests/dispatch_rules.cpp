@@ -49,6 +49,11 @@ int main() {
       {10, 64, 128, true, false}, {5, 128, 128, true, true}, {6, 47, 128, false, false}, {24, 16, 64, true, false}};
   for (const auto& c : kQuad)
     if (fwd_quad_is_faster(c.heads, c.nblk, c.nblk, c.d, c.causal) != c.quad) return printf("fwd_quad_is_faster: %d heads of %d blocks, d %d, mask %d\n", c.heads, c.nblk, c.d, c.causal), 1;
+  // order of the forward's workgroups: heads, query tiles, Q blocks
+  const struct { int heads, tiles, nqblk; bool folded; } kFold[] = {{107, 4, 7, false}, {107, 4, 8, true}, {98, 5, 9, false}, {98, 5, 10, true}, {163, 3, 5, false}, {46, 8, 15, false},
+      {64, 8, 15, true}, {80, 5, 9, true}, {245, 2, 3, true}, {51, 10, 19, true}, {36, 14, 28, true}};
+  for (const auto& c : kFold)
+    if (fwd_is_folded(c.heads, c.tiles, c.nqblk) != c.folded) return printf("fwd_is_folded: %d heads of %d Q blocks\n", c.heads, c.nqblk), 1;
   // Q-smoothing's short table: heads, key blocks, Q blocks, d
   const struct { int heads, nblk, nqblk, d; bool small; } kBias[] = {{1, 1, 1, 128, true}, {16, 16, 16, 128, true}, {32, 8, 8, 128, true}, {18, 16, 16, 128, false},
       {30, 16, 16, 128, false}, {30, 16, 16, 64, false}, {40, 8, 8, 128, false}, {40, 8, 8, 64, true}, {32, 9, 9, 64, false}, {70, 4, 4, 128, false}, {120, 4, 4, 64, true}, {200, 4, 4, 64, false},
