@@ -242,6 +242,14 @@ inline int bwd_heads_of_group(int most, int left, int nblk, int nqblk, int shift
 // steps, us: mask, 273 MB (32 of 4096) 488 -> 488.5, 382 (20 of 6144) 698 -> 696, 24 of 6144 819 -> 818, 545 (64 of 4096) 973 ->
 // 973, 2164 (64 of 8192) 3514 -> 3485; no mask, 192 (12 of 4096) 354 -> 359, 256 (16 of 4096) 414 -> 420, 352 (22 of 4096) 697 ->
 // 699, 512 (32 of 4096) 846 -> 844, 768 (12 of 8192) 1380 -> 1382, 1024 (16 of 8192) 1589 -> 1567.
+// Not with few key blocks, whose short walks wait for their first loads.  d = 128, mask: 355 (27; 700 of 256) 213 -> 217, 377 (49; 350
+// of 512) 254 -> 256, 415 (64; 300 of 640) 289 -> 292, 427 (76; 250 of 768) 298 -> 300, 410 (82; 200 of 896) 293.7 -> 293.1; no mask:
+// 371 (43; 700 of 256) 231 -> 233, 379 (63; 450 of 384) 276 -> 279, 780 (195; 500 of 640) 600 -> 604, 491 (140; 250 of 768) 388 -> 387,
+// 787 (225; 400 of 768) 586 -> 578; 628 (160; 64 of 8192 against 320 keys) 558 -> 567, 662 (250; 100 of 4096 against 640) 668 -> 676,
+// 512 (256; 32 of 8192 against 1024) 547 -> 542.  d = 64: 360 (128; 64 of 8192 against 256) 292 -> 295, 394 (160; 64 of 8192 against
+// 320) 354 -> 362, 412 (187; 300 of 1024 against 640) 370 -> 367, 400 (256; 64 of 4096 against 1024) 381 -> 364; 251 (87; 350 of 512)
+// 206 -> 207, 292 (117; 300 of 640) 249 -> 247, 315 (140; 250 of 768) 284 -> 280; mask 399 (107; 500 of 640) 306.3 -> 306.9, 402 (121;
+// 400 of 768) 312 -> 309.
 struct DsTraffic {
   bool load_past, store_past;
 };
@@ -249,7 +257,9 @@ inline DsTraffic ds_traffic(long long heads, int nblk, int nqblk, int shift_bloc
   long long tiles = (long long)nblk * nqblk;      // of a head
   if (causal) tiles = (long long)nqblk * (shift_blocks + 1) + (long long)nqblk * (nqblk - 1) / 2;
   const long long beside = 64ll * d * (7 * nqblk + 8 * nblk);
-  return {heads * (tiles * 4096 + beside) >> 20 >= 250, heads * tiles * 4096 >> 20 > 400};
+  const bool store_past = heads * tiles * 4096 >> 20 > 400;
+  const bool load_past = heads * (tiles * 4096 + beside) >> 20 >= 250 && nblk >= (d == 64 ? 10 : causal ? 14 : 12);
+  return {store_past || load_past, store_past};
 }
 
 // dQ with one Q block per workgroup and its waves on channel blocks (sage_bwd_dq_split_kernel; same bits): while the other form's

@@ -66,7 +66,9 @@ int main() {
       {64, 128, 128, 128, true, true, true}, {1, 1, 1, 64, false, false, false}, {32, 32, 32, 128, false, false, false}, {36, 32, 32, 128, false, true, false},
       {26, 32, 32, 128, false, false, false}, {3, 128, 128, 128, false, false, false}, {12, 64, 64, 64, false, false, false}, {48, 32, 32, 64, false, true, false},
       {20, 64, 64, 64, true, false, false}, {5, 128, 128, 64, true, false, false}, {64, 32, 32, 64, true, true, false}, {120, 16, 16, 128, true, true, false},
-      {200, 8, 8, 128, true, false, false}, {40, 128, 16, 128, false, true, false}, {24, 16, 64, 128, false, false, false}, {1, 1040000, 1, 128, false, true, true}};
+      {200, 8, 8, 128, true, false, false}, {40, 128, 16, 128, false, true, false}, {24, 16, 64, 128, false, false, false}, {1, 1040000, 1, 128, false, true, true},
+      {700, 4, 4, 128, true, false, false}, {300, 10, 10, 128, true, false, false}, {250, 12, 12, 128, true, false, false}, {400, 12, 12, 128, false, true, false},
+      {64, 5, 128, 64, false, false, false}, {74, 3, 132, 64, false, false, false}, {300, 10, 10, 64, false, true, false}, {300, 4, 128, 128, false, true, true}};
   for (const auto& c : kTraffic) {
     const DsTraffic t = ds_traffic(c.heads, c.nblk, c.nqblk, 0, c.d, c.causal);
     if (t.load_past != c.load || t.store_past != c.store) return printf("ds_traffic: %d heads of %d x %d blocks, d %d, mask %d\n", c.heads, c.nqblk, c.nblk, c.d, c.causal), 1;
