@@ -11,6 +11,9 @@ inline int fwd_per_cu(int d) { return d == 64 ? 3 : 2; }          // sage_fwd_ke
 constexpr int kMaxSweepPerCu = 2;                                 // sage_bwd_kernel, the sweep for the maxima
 inline int bwd_single_per_cu(int d, bool q_smooth) { return d == 64 && !q_smooth ? 2 : 1; }
 
+// Walks of about one length: no mask, or few queries against many keys.
+inline bool even_walks(int nblk, int nqblk, bool causal) { return !causal || nblk >= 4 * nqblk; }
+
 // Is the forward with four waves of 32 queries per workgroup folded?  The order takes a head's last query tile for its heaviest.  With an
 // odd number of Q blocks half of that tile's waves have no queries: it is the longest and yet light, and in short heads it is a
 // large part of all workgroups, which the order then pairs the wrong way.  Whole calls with the mask, us, folded -> not.  d = 128:
@@ -21,6 +24,14 @@ inline int bwd_single_per_cu(int d, bool q_smooth) { return d == 64 && !q_smooth
 // same, by the items being in order over all of them (80 of 576 31.0 -> 32.7, 64 of 960 39.9 -> 42.4; 48 of 832 33.1 -> 32.7).
 inline bool fwd_is_folded(long long heads, int n_qtiles, int nqblk) {
   return nqblk == 2 * n_qtiles || heads % 8 == 0 || n_qtiles < 3 || n_qtiles > 8;
+}
+// And the one with two waves per 32 queries?  Few queries against many keys have walks of about one length, of which no order is the
+// better one, and where the codes of an XCD's heads are many times its L2 a head's workgroups should not be as far apart as that
+// order has them.  Whole calls with the mask, us, folded -> not, d = 128: 224 heads of 128 queries against 2560 keys 174.0 -> 170.9,
+// 3264 209.6 -> 205.8, 3968 258.8 -> 253.6, 240 against 3008 207.6 -> 201.6, 208 against 3008 179.8 -> 180.0, 224 against 2048 144.0 ->
+// 144.0, 1536 103.6 -> 103.9, 512 45.6 -> 46.3; 112 of 256 against 2048 80.8 -> 82.1; d = 64, 224 of 128 against 3968 136.0 -> 136.8.
+inline bool fwd_pair_is_folded(long long heads, int nblk, int nqblk, int d) {
+  return !even_walks(nblk, nqblk, true) || heads * nblk * 64 * d <= (70ll << 20);
 }
 
 // ---- forward of few queries: two waves per 32 queries (sage_fwd_pair_kernel) or four (sage_fwd_quad_kernel) ----
@@ -148,9 +159,6 @@ class Queue {
   int levels_ = 1;
   double total_ = 0.0;
 };
-
-// Walks of about one length: no mask, or few queries against many keys.
-inline bool even_walks(int nblk, int nqblk, bool causal) { return !causal || nblk >= 4 * nqblk; }
 
 // Both kernels run one workgroup per CU, heaviest first.  In units of an interval with two KV blocks, a workgroup with two takes its
 // walk and 5 for filling and draining, one with four 1.65 times its walk and 3; with at most half of its blocks there it takes 0.8 of

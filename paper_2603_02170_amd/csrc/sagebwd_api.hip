@@ -387,7 +387,8 @@ int launch_fwd_small(const FwdArgs& a, FwdForm form, hipStream_t st) {
   args.n_qtiles = a.Nq / 64;
   const int grid = grid_for(a.BH, args.n_qtiles);
   // (the pair form's workgroups share a CU; the other two have one to themselves, the quad form's in up to three rounds under the mask)
-  const LaunchOrder order = folded_order(a.BH, args.n_qtiles, 2, CAUSAL && form == FwdForm::pair ? 2 : 1);
+  const bool fold = CAUSAL && form == FwdForm::pair && fwd_pair_is_folded(a.BH, a.N / kBlock, a.Nq / kBlock, D);
+  const LaunchOrder order = folded_order(a.BH, args.n_qtiles, 2, fold ? 2 : 1);
   args.fold_end = order.fold_end;
   args.head_set = CAUSAL && form == FwdForm::quad ? quad_head_set(a.BH, args.n_qtiles) : order.head_set;
   if (form == FwdForm::quad) sage_fwd_quad_kernel<D, CAUSAL, QS><<<grid, 512, 0, st>>>(args);

@@ -54,6 +54,9 @@ int main() {
       {64, 8, 15, true}, {80, 5, 9, true}, {245, 2, 3, true}, {51, 10, 19, true}, {36, 14, 28, true}};
   for (const auto& c : kFold)
     if (fwd_is_folded(c.heads, c.tiles, c.nqblk) != c.folded) return printf("fwd_is_folded: %d heads of %d Q blocks\n", c.heads, c.nqblk), 1;
+  if (fwd_pair_is_folded(224, 51, 2, 128) || fwd_pair_is_folded(240, 47, 2, 128) || !fwd_pair_is_folded(224, 24, 2, 128) || !fwd_pair_is_folded(224, 62, 2, 64) ||
+      !fwd_pair_is_folded(16, 64, 64, 128) || !fwd_pair_is_folded(128, 128, 33, 128))
+    return printf("fwd_pair_is_folded\n"), 1;
   // Q-smoothing's short table: heads, key blocks, Q blocks, d
   const struct { int heads, nblk, nqblk, d; bool small; } kBias[] = {{1, 1, 1, 128, true}, {16, 16, 16, 128, true}, {32, 8, 8, 128, true}, {18, 16, 16, 128, false},
       {30, 16, 16, 128, false}, {30, 16, 16, 64, false}, {40, 8, 8, 128, false}, {40, 8, 8, 64, true}, {32, 9, 9, 64, false}, {70, 4, 4, 128, false}, {120, 4, 4, 64, true}, {200, 4, 4, 64, false},
