@@ -55,6 +55,18 @@ inline bool fwd_quad_is_faster(long long heads, int nblk, int nqblk, int d, bool
   return d == 128 && (nblk == 11 || (wgs <= kCus / 2 && (nblk == 6 || nblk == 8 || nblk == 9)));
 }
 
+// ---- quantiser that sums QK-normed keys by itself: four rows at a time, or one at a time with fewer registers ----
+// `blocks` = row blocks of 64 of the longer of Q and K over all heads.  Every workgroup of the launch has the registers of those that
+// sum, so with many blocks the occupancy counts for more than the chain of a short sum.  Whole forward calls, us, four rows at a time
+// -> one, heads of queries x keys.  d = 128: 16 of 1024 x 128 (256 blocks) 15.6 -> 17.0, 32 22.9 -> 22.7, 64 38.1 -> 35.2, 128 of
+// 2048 x 128 (4096) 128 -> 113; 300 of 90 (600) 27.4 -> 26.5; 64 of 640 x 192 (640) 26.3 -> 29.8, 128 41.4 -> 41.2; 32 of 1024 x 256
+// (512) 27.6 -> 31.2, 64 45.6 -> 43.5, 64 of 2048 x 256 (2048) 83.2 -> 78.4; 16 of 4096 x 512 (1024) 47 -> 62.  d = 64: 32 of 1024 x
+// 128 (512) 15.3 -> 15.6, 64 23.7 -> 22.6; 500 of 128 (1000) 25.9 -> 25.3; 64 of 640 x 192 18.2 -> 18.5, 128 24.2 -> 23.0; 32 of
+// 1024 x 256 18.0 -> 19.4, 64 27.6 -> 26.8; 32 of 4096 x 512 (2048) 49 -> 55.
+inline bool normed_rows_by_fours(long long blocks, int nkblk) {
+  return nkblk > 4 || (nkblk > 1 && blocks < (nkblk == 2 ? 600 : 1024));
+}
+
 // ---- Q-smoothing's bias table for at most 16 Q blocks: qsmooth_bias_short_kernel or qsmooth_bias_kernel (same bits) ----
 // Workgroups (one per key block and head) with a CU to themselves are bound by latency, and the short kernel has no LDS and no
 // barrier; where they share one, its narrow loads, of Q's means for every 16 keys again, cost more than that.  Whole forward

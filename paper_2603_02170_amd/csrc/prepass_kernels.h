@@ -232,7 +232,8 @@ struct QuantJobs {
 // A workgroup takes one numerics block; its scale (and block mean) is stored once per 64-row block: the
 // attention kernels index scales, means and bias rows by 64-row block whatever the numerics block is.
 // MEAN: the K job adds chunk sums, or sums its head itself (jobs of a short K; instantiations of their own, since the summing
-// loops cost the registers that the others' occupancy needs), or sums the normalised rows of its head, of more than one block or of one.
+// loops cost the registers that the others' occupancy needs), or sums the normalised rows of its head, four at a time or
+// one (see normed_rows_by_fours).
 enum : int { kMeanOfChunks, kMeanInline, kMeanInlineNormed, kMeanInlineNormedBlock };
 // Waves per SIMD (left to itself the compiler takes 119 registers for plain keys where 87 do).
 constexpr int quantiser_waves(int D, int SUB, int mean) {

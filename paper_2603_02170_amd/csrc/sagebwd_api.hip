@@ -319,7 +319,9 @@ int run_prepass(const void* Q, const void* K, const void* V, const void* dO, con
       }
       if (np == 0) continue;
       const dim3 grid((nblk_max + sub - 1) / sub, BH, np);
-      const int mean = !(want_qk && inline_mean) ? kMeanOfChunks : !qkn ? kMeanInline : Nk > kBlock ? kMeanInlineNormed : kMeanInlineNormedBlock;
+      // (numerics blocks of 128 rows: fours unless a head has one block)
+      const bool fours = sub == 1 ? normed_rows_by_fours((long long)BH * nblk_max, Nkp / kBlock) : Nk > kBlock;
+      const int mean = !(want_qk && inline_mean) ? kMeanOfChunks : !qkn ? kMeanInline : fours ? kMeanInlineNormed : kMeanInlineNormedBlock;
       const auto kernel = sub == 1 ? quantiser<D, 1>(mean) : quantiser<D, 2>(mean);
       kernel<<<grid, 256, 0, st>>>(part);
       SAGE_LAUNCH_CHECK();

@@ -57,6 +57,11 @@ int main() {
   if (fwd_pair_is_folded(224, 51, 2, 128) || fwd_pair_is_folded(240, 47, 2, 128) || !fwd_pair_is_folded(224, 24, 2, 128) || !fwd_pair_is_folded(224, 62, 2, 64) ||
       !fwd_pair_is_folded(16, 64, 64, 128) || !fwd_pair_is_folded(128, 128, 33, 128))
     return printf("fwd_pair_is_folded\n"), 1;
+  // sums of QK-normed keys in the quantiser: row blocks, key blocks
+  const struct { int blocks, nkblk; bool fours; } kSums[] = {{1, 1, false}, {4000, 1, false}, {2, 2, true}, {512, 2, true}, {600, 2, false}, {1024, 2, false}, {640, 3, true}, {1280, 3, false},
+      {512, 4, true}, {1024, 4, false}, {1024, 8, true}, {2048, 8, true}};
+  for (const auto& c : kSums)
+    if (normed_rows_by_fours(c.blocks, c.nkblk) != c.fours) return printf("normed_rows_by_fours: %d blocks, %d of a head's keys\n", c.blocks, c.nkblk), 1;
   // Q-smoothing's short table: heads, key blocks, Q blocks, d
   const struct { int heads, nblk, nqblk, d; bool small; } kBias[] = {{1, 1, 1, 128, true}, {16, 16, 16, 128, true}, {32, 8, 8, 128, true}, {18, 16, 16, 128, false},
       {30, 16, 16, 128, false}, {30, 16, 16, 64, false}, {40, 8, 8, 128, false}, {40, 8, 8, 64, true}, {32, 9, 9, 64, false}, {70, 4, 4, 128, false}, {120, 4, 4, 64, true}, {200, 4, 4, 64, false},

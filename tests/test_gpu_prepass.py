@@ -218,3 +218,21 @@ def test_prepass_bit_exact_numerics_blocks_of_128_rows(bq, bkv, Nq, Nk, d, q_smo
     Q = (Q.float() * torch.linspace(0.5, 3, Nq)[:, None] + torch.linspace(-2, 2, d)).to(torch.bfloat16)   # blocks of different range
     _run_case(Q, K, V, dO, binding.SageParams(1, 2, Nq, d, causal=False, q_smooth=q_smooth, k_smooth=k_smooth,
                                               Nkv=0 if Nk == Nq else Nk, bq=bq, bkv=bkv))
+
+
+@pytest.mark.parametrize("Nq,Nk,heads,d", [(100, 100, 320, 128), (100, 100, 320, 64), (640, 192, 110, 128), (1024, 250, 70, 64)])
+def test_normed_keys_summed_four_rows_at_a_time_and_one_give_the_same_bits(Nq, Nk, heads, d):
+    """Calls of few and of many heads (normed_rows_by_fours): the first heads have the same means, O and LSE."""
+    g = torch.Generator(device="cuda").manual_seed(Nq + d)
+    Q, K, V = ((torch.randn((1, heads, n, d), generator=g, device="cuda") + 0.5).to(torch.bfloat16) for n in (Nq, Nk, Nk))
+    gains = [1.0 + 0.25 * torch.randn(d, generator=g, device="cuda") for _ in range(2)]
+    got = []
+    for n in (2, heads):
+        p = binding.SageParams(1, n, Nq, d, causal=False, Nkv=Nk, qk_gamma_q=gains[0], qk_gamma_k=gains[1])
+        ws = binding.alloc_workspace(p)
+        O, L = binding.sagebwd_fwd(*(t[:, :n].contiguous() for t in (Q, K, V)), p, ws)
+        got.append((binding.sagebwd_export_stats(p, ws)[0][:, :2], O[:, :2], L[:, :2]))
+    torch.cuda.synchronize()
+    assert got[0][0].abs().max() > 0.1
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
