@@ -293,6 +293,29 @@ __host__ __device__ inline int quad_head_set(int heads, int items) {
   return grid_for(heads, items) > 256 ? all_heads(heads) : head_set_for(items, heads);
 }
 
+// What a workgroup of a pre-pass launch takes: a job, a head, a block (or chunk) of its rows.  The grid is (blocks, heads, jobs), whose
+// ids, and so a head's blocks, go round the 8 XCDs; or, `own_xcd`, (8, blocks, jobs x heads / 8), in which a head's workgroups have
+// one XCD, the same in every launch and the one that the attention kernels give the head: what one launch has read or written is then
+// in the L2 that the next one reads through (see prepass_own_xcd).  The grid holds what a workgroup needs for it, so that it divides by
+// nothing, and the quantiser is instantiated for either: its job lies in the arguments at a place that waits for the number of heads,
+// one more trip to memory in front of all else (0.3 us a launch).
+struct PrepassItem {
+  int job, head, block;
+};
+__host__ __device__ inline PrepassItem prepass_item(int x, int y, int z, bool own_xcd, int heads) {
+  if (!own_xcd) return PrepassItem{z, y, x};
+  int job = 0, group = z;
+  for (; group >= heads / 8; group -= heads / 8) job++;
+  return PrepassItem{job, x + 8 * group, y};
+}
+// The last rows of the heads of each XCD first.
+__host__ __device__ inline PrepassItem last_rows_first(const PrepassItem& i, int blocks, int heads) {
+  return PrepassItem{i.job, heads - 8 + 2 * (i.head & 7) - i.head, blocks - 1 - i.block};
+}
+inline dim3 prepass_grid(int blocks, int heads, int jobs, bool own_xcd) {
+  return own_xcd ? dim3(8, blocks, jobs * (heads / 8)) : dim3(blocks, heads, jobs);
+}
+
 // Row of K or V that a load of sage_fwd_decode_kernel for row `row` reads: a row that does not exist re-reads the last one that does
 // (which changes no maximum of its block), and all rows of a block that is not the wave's (`mine` false: the load ahead of a wave's
 // last block) are one row.  The loop stays without a branch, and no block is read twice (two sequences of 32 heads of 8192 keys,

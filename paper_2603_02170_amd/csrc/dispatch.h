@@ -55,6 +55,19 @@ inline bool fwd_quad_is_faster(long long heads, int nblk, int nqblk, int d, bool
   return d == 128 && (nblk == 11 || (wgs <= kCus / 2 && (nblk == 6 || nblk == 8 || nblk == 9)));
 }
 
+// ---- launches of the forward's pre-pass, and decoding: does a head have an XCD of its own? (prepass_item; same bits) ----
+// With K-smoothing every row of K is read twice and more: by the launch that sums it (or by every workgroup that quantises a block of a
+// short head) and by the one that quantises it; and the forward reads the codes on the head's XCD.  Past the L2 all of it comes at 6.6
+// TB/s at most, from the memory-side cache too, out of it at 11 (a plain read of 128 MB and of 32).  Whole calls, us, ids as they
+// come -> own XCD: forward, 8 heads of N = 1000 22.1 -> 20.3, 8 of 512 17.8 -> 16.3, 64 of 256 16.2 -> 15.5, 128 of 640 49.0 -> 47.3, 200
+// of 300 40.3 -> 38.9, 32 of 512 against 4096 keys 60.6 -> 57.0; d = 64, 16 of 512 15.2 -> 14.3, 8 of 2000 25.8 -> 25.2; decoding, 64
+// heads of 8192 keys 78.6 -> 76.1; steps, 16 of 512 47.4 -> 45.7, 64 of 2048 and more the same.
+// One block a head has nothing to share (8 of 64 9.33 -> 9.38).  Without gain, or with a loss: QK-norm (its sums wait for their
+// chains; blocks of 128, 32 of 2048 235.4 -> 238.1), Q-smoothing (the bias kernel reads K in the order of ids, 16 of 1024 31.2 -> 31.9),
+// numerics blocks of 128 (32 of 2048 58.7 -> 60.0), and tensors read once (dO in the backward's pre-pass, 64 of 2048 17.2 -> 18.3).
+// (65535: the grid's y and z.)
+inline bool prepass_own_xcd(int heads, long long blocks) { return heads % 8 == 0 && blocks > 1 && blocks <= 65535; }
+
 // ---- quantiser that sums QK-normed keys by itself: four rows at a time, or one at a time with fewer registers ----
 // `blocks` = row blocks of 64 of the longer of Q and K over all heads.  Every workgroup of the launch has the registers of those that
 // sum, so with many blocks the occupancy counts for more than the chain of a short sum.  Whole forward calls, us, four rows at a time

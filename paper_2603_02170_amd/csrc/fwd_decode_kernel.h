@@ -35,10 +35,12 @@ struct DecodeArgs {
   int nchunk;
   unsigned short* O;
   float* LSE;                  // [BH, nq]
-  float* part;                 // partial O of every workgroup [BH, gridDim.x, 32, D] (rows < nq used), if more than one
-  v2f* part_ml;                // (m, l) [BH, gridDim.x, 32]
+  float* part;                 // partial O of every workgroup [BH, nsplit, 32, D] (rows < nq used), if more than one
+  v2f* part_ml;                // (m, l) [BH, nsplit, 32]
   int nq, nk, nblk;            // query rows (<= 32), keys, key blocks
   int blocks_per_wave;
+  int nsplit;                  // workgroups of a head
+  int heads, own_xcd;          // see prepass_item
   float scale_log2e;
 };
 
@@ -54,7 +56,8 @@ __global__ void __launch_bounds__(256, 2) sage_fwd_decode_kernel(DecodeArgs args
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int r32 = lane & 31, h = lane >> 5;
-  const int bh = blockIdx.y;
+  const PrepassItem item = prepass_item(blockIdx.x, blockIdx.y, blockIdx.z, args.own_xcd != 0, args.heads);
+  const int bh = item.head, split = item.block;
 
   // this wave's fragments of a block: row 32 rb + r32, channels 32 s + 16 h .. + 16 (two 16-byte pieces)
   struct Raw {
@@ -124,7 +127,7 @@ __global__ void __launch_bounds__(256, 2) sage_fwd_decode_kernel(DecodeArgs args
     return nz ? a / 127.0f : 0.f;
   };
 
-  const int first = (blockIdx.x * 4 + wave) * args.blocks_per_wave;
+  const int first = (split * 4 + wave) * args.blocks_per_wave;
   const int end = min(first + args.blocks_per_wave, args.nblk);
   Raw kr, vr_ahead;
   Raw& vr = V_AHEAD ? vr_ahead : kr;
@@ -342,7 +345,7 @@ __global__ void __launch_bounds__(256, 2) sage_fwd_decode_kernel(DecodeArgs args
     wgt[s] = __builtin_amdgcn_exp2f(mls[s][0] - m);          // 0 for a wave without blocks (the first wave always has one)
     l = __builtin_fmaf(mls[s][1], wgt[s], l);
   }
-  const bool whole = gridDim.x == 1;
+  const bool whole = args.nsplit == 1;
   const float inv_l = 1.0f / l;
   if (wave < KS) {
 #pragma unroll
@@ -361,13 +364,13 @@ __global__ void __launch_bounds__(256, 2) sage_fwd_decode_kernel(DecodeArgs args
         for (int e = 0; e < 4; e++) ob[e] = float_to_bf16_bits(o[e] * inv_l);
         *(v4us*)(args.O + args.qview.row(bh, row) + ch) = ob;
       } else {
-        *(v4f*)(args.part + (((size_t)bh * gridDim.x + blockIdx.x) * 32 + row) * D + ch) = o;
+        *(v4f*)(args.part + (((size_t)bh * args.nsplit + split) * 32 + row) * D + ch) = o;
       }
     }
   }
   if (wave == 0 && half == 0) {
     if (whole) args.LSE[(size_t)bh * args.nq + row] = (m + __builtin_amdgcn_logf(l) - kLog2_127) * kLn2;
-    else args.part_ml[((size_t)bh * gridDim.x + blockIdx.x) * 32 + row] = v2f{m, l};
+    else args.part_ml[((size_t)bh * args.nsplit + split) * 32 + row] = v2f{m, l};
   }
 }
 

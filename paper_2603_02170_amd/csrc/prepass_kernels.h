@@ -128,12 +128,13 @@ __device__ __forceinline__ void column_sums(const unsigned short* __restrict__ b
 template <int D, int NORMED>
 __global__ void __launch_bounds__(256) kmean_partial_kernel(const unsigned short* __restrict__ K, RowView view,
                                                             double* __restrict__ kpart, int N,
-                                                            int nchunk, int chunk_rows, QkNorm norm) {
+                                                            int nchunk, int chunk_rows, QkNorm norm, int heads, int own_xcd) {
   constexpr int TPR = D / 8;
   constexpr int RPP = 256 / TPR;
   __shared__ double red[256][8];
   const int t = threadIdx.x;
-  const int chunk = blockIdx.x, bh = blockIdx.y;
+  const PrepassItem item = prepass_item(blockIdx.x, blockIdx.y, blockIdx.z, own_xcd != 0, heads);
+  const int chunk = item.block, bh = item.head;
   const int row0 = chunk * chunk_rows;
   double acc[8];
   column_sums<D, NORMED>(K + view.row(bh, row0), view.row_stride, min(chunk_rows, N - row0), norm, acc);
@@ -220,6 +221,7 @@ struct QuantJob {
   unsigned short* norm_out;    // if set: the normalised rows as dense bf16 [BH, Np, D] (for the Q-smoothing bias)
 };
 struct QuantJobs {
+  int blocks, heads;           // of every job's workgroups
   QuantJob job[4];
 };
 
@@ -239,7 +241,7 @@ enum : int { kMeanOfChunks, kMeanInline, kMeanInlineNormed, kMeanInlineNormedBlo
 constexpr int quantiser_waves(int D, int SUB, int mean) {
   return mean == kMeanOfChunks ? 1 : mean == kMeanInlineNormed || SUB * D > 128 ? 3 : 5;
 }
-template <int D, int SUB, int MEAN>
+template <int D, int SUB, int MEAN, bool OWN_XCD = false>
 __global__ void __launch_bounds__(256, quantiser_waves(D, SUB, MEAN)) prepass_quant_kernel(QuantJobs jobs) {
   constexpr bool INLINE_MEAN = MEAN != kMeanOfChunks;
   constexpr int ROWS = SUB * kBlock;
@@ -253,9 +255,12 @@ __global__ void __launch_bounds__(256, quantiser_waves(D, SUB, MEAN)) prepass_qu
   __shared__ double sumsq[ROWS];         // QK-norm: the rows' sums of squares, then their factors
   __shared__ float wmax[4];
 
-  const QuantJob jb = jobs.job[blockIdx.z];
+  PrepassItem item = prepass_item(blockIdx.x, blockIdx.y, blockIdx.z, OWN_XCD, jobs.heads);
+  // (K in the order in which an L2 that does not hold all of it has kept what kmean_partial_kernel read)
+  if (OWN_XCD && MEAN == kMeanOfChunks && item.job == 0) item = last_rows_first(item, jobs.blocks, jobs.heads);
+  const QuantJob jb = jobs.job[item.job];
   const int t = threadIdx.x;
-  const int blk = blockIdx.x * SUB, bh = blockIdx.y;                        // first 64-row block
+  const int blk = item.block * SUB, bh = item.head;                         // first 64-row block
   const int N = jb.N, Np = jb.Np;
   const RowView view = jb.view;
   const int nblk = Np / kBlock;

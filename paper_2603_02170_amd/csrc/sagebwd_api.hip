@@ -222,10 +222,11 @@ struct ScopedTimer {
 // K-mean chunk sums (K-smoothing) into the workspace
 template <int D>
 int launch_kmean(const void* K, const RowView& kview, const sagebwd_params& p, char* ws, const Workspace& w, const QkNorm& norm,
-                 hipStream_t st) {
+                 bool own_xcd, hipStream_t st) {
   const auto kernel = norm.gamma != nullptr ? kmean_partial_kernel<D, 4> : kmean_partial_kernel<D, 0>;
-  kernel<<<dim3(w.nchunk, p.B * p.H), 256, 0, st>>>((const unsigned short*)K, kview, (double*)(ws + w.kpart), kv_len(p), w.nchunk,
-                                                    w.chunk_rows, norm);
+  const int heads = p.B * p.H;
+  kernel<<<prepass_grid(w.nchunk, heads, 1, own_xcd), 256, 0, st>>>((const unsigned short*)K, kview, (double*)(ws + w.kpart), kv_len(p), w.nchunk,
+                                                                   w.chunk_rows, norm, heads, own_xcd);
   SAGE_LAUNCH_CHECK();
   return SAGEBWD_OK;
 }
@@ -250,9 +251,11 @@ int run_prepass(const void* Q, const void* K, const void* V, const void* dO, con
   const bool qkn = (p.flags & SAGEBWD_FLAG_QK_NORM) != 0;
   const bool inline_mean = ks && mean_inline(BH, Nk, D);
   const QkNorm norm_q{qkn ? p.qk_gamma_q : nullptr, p.qk_norm_eps}, norm_k{qkn ? p.qk_gamma_k : nullptr, p.qk_norm_eps};
+  const int nblk_max = (Nqp > Nkp ? Nqp : Nkp) / 64;
+  const bool own_xcd = want_qk && ks && !qkn && !qs && !big_blocks(p) && prepass_own_xcd(BH, nblk_max);
   if (want_qk) {
     if (ks && !inline_mean) {
-      const int rc = launch_kmean<D>(K, kview, p, ws, w, norm_k, st);
+      const int rc = launch_kmean<D>(K, kview, p, ws, w, norm_k, own_xcd, st);
       if (rc != SAGEBWD_OK) return rc;
     }
   }
@@ -309,7 +312,6 @@ int run_prepass(const void* Q, const void* K, const void* V, const void* dO, con
   if (nj > 0) {
     // one launch per numerics block size in use (64-row blocks per numerics block: 1 or 2); Q-like jobs
     // quantise per B_q rows, K-like jobs per B_kv rows
-    const int nblk_max = (Nqp > Nkp ? Nqp : Nkp) / 64;
     for (int sub = 1; sub <= 2; sub++) {
       QuantJobs part;
       memset(&part, 0, sizeof(part));
@@ -318,11 +320,14 @@ int run_prepass(const void* Q, const void* K, const void* V, const void* dO, con
         if ((jobs.job[k].q_like ? block_q(p) : block_kv(p)) / 64 == sub) part.job[np++] = jobs.job[k];
       }
       if (np == 0) continue;
-      const dim3 grid((nblk_max + sub - 1) / sub, BH, np);
+      part.heads = BH;
+      part.blocks = (nblk_max + sub - 1) / sub;
+      const dim3 grid = prepass_grid(part.blocks, BH, np, own_xcd);
       // (numerics blocks of 128 rows: fours unless a head has one block)
       const bool fours = sub == 1 ? normed_rows_by_fours((long long)BH * nblk_max, Nkp / kBlock) : Nk > kBlock;
       const int mean = !(want_qk && inline_mean) ? kMeanOfChunks : !qkn ? kMeanInline : fours ? kMeanInlineNormed : kMeanInlineNormedBlock;
-      const auto kernel = sub == 1 ? quantiser<D, 1>(mean) : quantiser<D, 2>(mean);
+      const auto kernel = own_xcd ? (inline_mean ? prepass_quant_kernel<D, 1, kMeanInline, true> : prepass_quant_kernel<D, 1, kMeanOfChunks, true>)
+                          : sub == 1 ? quantiser<D, 1>(mean) : quantiser<D, 2>(mean);
       kernel<<<grid, 256, 0, st>>>(part);
       SAGE_LAUNCH_CHECK();
     }
@@ -584,14 +589,19 @@ int decode_impl(const void* Q, const void* K, const void* V, void* O, float* LSE
   // it is the last of its head, and leaves at most 32 * (4 D + 8)
   a.part_ml = (v2f*)(ws + w.KF);
   a.part = (float*)(ws + w.KF + align_up((size_t)BH * nsplit * 32 * sizeof(v2f)));
+  const bool own_xcd = ks && prepass_own_xcd(BH, a.nblk);
+  a.nsplit = nsplit;
+  a.heads = BH;
+  a.own_xcd = own_xcd;
+  const dim3 grid = prepass_grid(nsplit, BH, 1, own_xcd);
   if (ks) {
     ScopedTimer tm(SAGEBWD_KERNEL_PREPASS_FWD, st);
-    const int rc = launch_kmean<D>(K, a.kview, p, ws, w, QkNorm{nullptr, 0.f}, st);
+    const int rc = launch_kmean<D>(K, a.kview, p, ws, w, QkNorm{nullptr, 0.f}, own_xcd, st);
     if (rc != SAGEBWD_OK) return rc;
   }
   ScopedTimer tm(SAGEBWD_KERNEL_FWD, st);
-  if (ks) sage_fwd_decode_kernel<D, true><<<dim3(nsplit, BH), 256, 0, st>>>(a);
-  else sage_fwd_decode_kernel<D, false><<<dim3(nsplit, BH), 256, 0, st>>>(a);
+  if (ks) sage_fwd_decode_kernel<D, true><<<grid, 256, 0, st>>>(a);
+  else sage_fwd_decode_kernel<D, false><<<grid, 256, 0, st>>>(a);
   SAGE_LAUNCH_CHECK();
   if (nsplit > 1) {
     sage_fwd_decode_join_kernel<D><<<dim3(p.N, BH), 256, 0, st>>>(a, nsplit);
