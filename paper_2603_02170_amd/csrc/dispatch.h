@@ -64,9 +64,13 @@ inline bool fwd_quad_is_faster(long long heads, int nblk, int nqblk, int d, bool
 // heads of 8192 keys 78.6 -> 76.1; steps, 16 of 512 47.4 -> 45.7, 64 of 2048 and more the same.
 // One block a head has nothing to share (8 of 64 9.33 -> 9.38).  Without gain, or with a loss: QK-norm (its sums wait for their
 // chains; blocks of 128, 32 of 2048 235.4 -> 238.1), Q-smoothing (the bias kernel reads K in the order of ids, 16 of 1024 31.2 -> 31.9),
-// numerics blocks of 128 (32 of 2048 58.7 -> 60.0), and tensors read once (dO in the backward's pre-pass, 64 of 2048 17.2 -> 18.3).
-// (65535: the grid's y and z.)
+// numerics blocks of 128 (32 of 2048 58.7 -> 60.0).  (65535: the grid's y and z.)
 inline bool prepass_own_xcd(int heads, long long blocks) { return heads % 8 == 0 && blocks > 1 && blocks <= 65535; }
+// dO alone, in a backward that shares psi(Q) and psi(K): the forward has left O, and the backward finds the codes, in the L2 of the head's
+// XCD, while the 5 bytes an element of all heads are little more than the L2s hold (32 MB).  Steps, us, ids as they come -> own XCD: 8
+// heads of N = 128 29.2 -> 28.8, 128 of 256 55.7 -> 54.6, 32 of 1024 81.5 -> 80.6, 64 of 1024 134.4 -> 132.7, 32 of 2048 183.1 ->
+// 182.3; d = 64, 64 of 1024 90.8 -> 90.0; but this launch of 64 of 2048 17.2 -> 18.3.
+inline bool dO_own_xcd(long long elements) { return elements <= (8 << 20); }
 
 // ---- quantiser that sums QK-normed keys by itself: four rows at a time, or one at a time with fewer registers ----
 // `blocks` = row blocks of 64 of the longer of Q and K over all heads.  Every workgroup of the launch has the registers of those that
