@@ -55,6 +55,20 @@ inline bool fwd_quad_is_faster(long long heads, int nblk, int nqblk, int d, bool
   return d == 128 && (nblk == 11 || (wgs <= kCus / 2 && (nblk == 6 || nblk == 8 || nblk == 9)));
 }
 
+// ---- heads of one or two key blocks: psi and the forward in one launch (sage_fwd_short_kernel; same bits) or in two ----
+// One launch, and no codes written and read back where nobody wants them, against every Q block's workgroup quantising all of K and V.
+// Whole calls, us, two launches -> one.  One key block, d = 128: 8 heads of N = 64 9.4 -> 7.2, 256 12.6 -> 9.0, 1024 32.3 -> 20.0, 4096 120
+// -> 64; 2048 of 1 x 64 49.8 -> 26.9; 8 of 4096 x 64 13.6 -> 11.2, 32 32.8 -> 30.7; d = 64, 8 of 64 8.2 -> 5.8, 4096 63.3 -> 42.1, 16
+// of 4096 x 64 14.0 -> 13.0.  Two, d = 128: 8 of N = 128 10.4 -> 9.4, 128 13.4 -> 10.5, 512 34.0 -> 26.9, 2048 121 -> 92; 2048 of 1 x 128
+// 63 -> 46; d = 64, 64 of 128 9.7 -> 7.5, 2048 65.6 -> 58.5.  Two and many Q blocks: 8 of 2048 x 128, d = 64, 9.5 -> 7.7, 8 of 4096 x
+// 128 15.4 -> 15.0, but 16 of 4096 x 128 21.8 -> 26.4, d = 64 15.2 -> 18.0.  Training steps, whose codes are written all the same: 8 of
+// 64 25.7 -> 24.0, 512 52.1 -> 50.0, 8 of 128 28.9 -> 28.5, 256 of 128 49.2 -> 49.5.
+// Four key blocks: 8 of 256 12.6 -> 14.9, 128 20.6 -> 29.5, d = 64 64 of 256 12.0 -> 11.4, 128 14.6 -> 21.9; three 12.3 -> 13.8.
+inline bool fwd_short_is_faster(long long heads, int nkblk, int nqblk) {
+  if (nqblk >= 1 << 20) return false;      // (the grid counts threads in 32 bits)
+  return nkblk == 1 || (nkblk == 2 && (nqblk <= 2 || heads * nqblk <= 2 * kCus));
+}
+
 // ---- launches of the forward's pre-pass, and decoding: does a head have an XCD of its own? (prepass_item; same bits) ----
 // With K-smoothing every row of K is read twice and more: by the launch that sums it (or by every workgroup that quantises a block of a
 // short head) and by the one that quantises it; and the forward reads the codes on the head's XCD.  Past the L2 all of it comes at 6.6

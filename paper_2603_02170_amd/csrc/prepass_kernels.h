@@ -10,6 +10,8 @@
 // a = max|x|; s = a / 127 and r = 127 / a as IEEE FP32 divisions; q = rne(x * r).
 #pragma once
 
+#include <type_traits>
+
 #include "common.h"
 
 namespace sage {
@@ -180,21 +182,23 @@ inline bool mean_inline(int heads, int N, int D) {
   return (long long)N * D <= 65536 && (long long)heads * ((N + kBlock - 1) / kBlock) * N * D <= (14 << 20);
 }
 
-// The rounding of psi on 16 values held as FP32: q = rne(x * r) clamped to +-127 (which matters where r = 127 / max|x|
-// overflows, blocks of the smallest numbers, and for NaN: both become codes), packed into four registers.  x * r is rounded to FP32
+// The rounding of psi on values held as FP32: q = rne(x * r) clamped to +-127 (which matters where r = 127 / max|x|
+// overflows, blocks of the smallest numbers, and for NaN: both become codes), four packed into a register.  x * r is rounded to FP32
 // before the addition that takes it to an integer, so the codes are those of rintf.
+__device__ __forceinline__ int quantise_4(const float x0, const float x1, const float x2, const float x3, const float r) {
+  const float x[4] = {x0, x1, x2, x3};
+  unsigned u[4];
+#pragma unroll
+  for (int e = 0; e < 4; e++) {
+    const float y = __builtin_amdgcn_fmed3f(x[e] * r, -127.f, 127.f);
+    u[e] = __float_as_uint(y + 12582912.0f);               // 1.5 * 2^23: rne(y) in the low mantissa bits
+  }
+  return (int)(__builtin_amdgcn_perm(u[1], u[0], 0x0c0c0400u) | __builtin_amdgcn_perm(u[3], u[2], 0x04000c0cu));
+}
 __device__ __forceinline__ v4i quantise_16(const float (&x)[16], const float r) {
   v4i o;
 #pragma unroll
-  for (int w = 0; w < 4; w++) {
-    unsigned u[4];
-#pragma unroll
-    for (int e = 0; e < 4; e++) {
-      const float y = __builtin_amdgcn_fmed3f(x[4 * w + e] * r, -127.f, 127.f);
-      u[e] = __float_as_uint(y + 12582912.0f);               // 1.5 * 2^23: rne(y) in the low mantissa bits
-    }
-    o[w] = (int)(__builtin_amdgcn_perm(u[1], u[0], 0x0c0c0400u) | __builtin_amdgcn_perm(u[3], u[2], 0x04000c0cu));
-  }
+  for (int w = 0; w < 4; w++) o[w] = quantise_4(x[4 * w], x[4 * w + 1], x[4 * w + 2], x[4 * w + 3], r);
   return o;
 }
 
@@ -220,7 +224,13 @@ struct QuantJob {
   QkNorm norm;                 // QK-norm applied to src before anything else (Q and K jobs), or gamma == nullptr
   unsigned short* norm_out;    // if set: the normalised rows as dense bf16 [BH, Np, D] (for the Q-smoothing bias)
 };
+// Arguments of a launch, and of one with an XCD for every head, whose workgroups need the number of heads before anything else.  (In
+// front of the jobs there, with them not moved here: two queries against 320 keys of 54 heads, d = 64, 13.6 us, with eight bytes in front
+// 13.8; 64 heads of N = 256 15.3, with the numbers behind the jobs 15.6.)
 struct QuantJobs {
+  QuantJob job[4];
+};
+struct OwnXcdJobs {
   int blocks, heads;           // of every job's workgroups
   QuantJob job[4];
 };
@@ -242,7 +252,7 @@ constexpr int quantiser_waves(int D, int SUB, int mean) {
   return mean == kMeanOfChunks ? 1 : mean == kMeanInlineNormed || SUB * D > 128 ? 3 : 5;
 }
 template <int D, int SUB, int MEAN, bool OWN_XCD = false>
-__global__ void __launch_bounds__(256, quantiser_waves(D, SUB, MEAN)) prepass_quant_kernel(QuantJobs jobs) {
+__global__ void __launch_bounds__(256, quantiser_waves(D, SUB, MEAN)) prepass_quant_kernel(std::conditional_t<OWN_XCD, OwnXcdJobs, QuantJobs> jobs) {
   constexpr bool INLINE_MEAN = MEAN != kMeanOfChunks;
   constexpr int ROWS = SUB * kBlock;
   constexpr int CPR = D / 16;            // 16-channel chunks per row
@@ -255,9 +265,12 @@ __global__ void __launch_bounds__(256, quantiser_waves(D, SUB, MEAN)) prepass_qu
   __shared__ double sumsq[ROWS];         // QK-norm: the rows' sums of squares, then their factors
   __shared__ float wmax[4];
 
-  PrepassItem item = prepass_item(blockIdx.x, blockIdx.y, blockIdx.z, OWN_XCD, jobs.heads);
-  // (K in the order in which an L2 that does not hold all of it has kept what kmean_partial_kernel read)
-  if (OWN_XCD && MEAN == kMeanOfChunks && item.job == 0) item = last_rows_first(item, jobs.blocks, jobs.heads);
+  PrepassItem item{(int)blockIdx.z, (int)blockIdx.y, (int)blockIdx.x};
+  if constexpr (OWN_XCD) {
+    item = prepass_item(blockIdx.x, blockIdx.y, blockIdx.z, true, jobs.heads);
+    // (K in the order in which an L2 that does not hold all of it has kept what kmean_partial_kernel read)
+    if (MEAN == kMeanOfChunks && item.job == 0) item = last_rows_first(item, jobs.blocks, jobs.heads);
+  }
   const QuantJob jb = jobs.job[item.job];
   const int t = threadIdx.x;
   const int blk = item.block * SUB, bh = item.head;                         // first 64-row block

@@ -14,6 +14,7 @@
 #include "prepass_kernels.h"
 #include "fwd_kernel.h"
 #include "fwd_decode_kernel.h"
+#include "fwd_short_kernel.h"
 #include "bwd_kernel.h"
 #include "probe_kernels.h"
 
@@ -320,15 +321,22 @@ int run_prepass(const void* Q, const void* K, const void* V, const void* dO, con
         if ((jobs.job[k].q_like ? block_q(p) : block_kv(p)) / 64 == sub) part.job[np++] = jobs.job[k];
       }
       if (np == 0) continue;
-      part.heads = BH;
-      part.blocks = (nblk_max + sub - 1) / sub;
-      const dim3 grid = prepass_grid(part.blocks, BH, np, own_xcd);
+      const int blocks = (nblk_max + sub - 1) / sub;
+      const dim3 grid = prepass_grid(blocks, BH, np, own_xcd);
       // (numerics blocks of 128 rows: fours unless a head has one block)
       const bool fours = sub == 1 ? normed_rows_by_fours((long long)BH * nblk_max, Nkp / kBlock) : Nk > kBlock;
       const int mean = !(want_qk && inline_mean) ? kMeanOfChunks : !qkn ? kMeanInline : fours ? kMeanInlineNormed : kMeanInlineNormedBlock;
-      const auto kernel = own_xcd ? (inline_mean ? prepass_quant_kernel<D, 1, kMeanInline, true> : prepass_quant_kernel<D, 1, kMeanOfChunks, true>)
-                          : sub == 1 ? quantiser<D, 1>(mean) : quantiser<D, 2>(mean);
-      kernel<<<grid, 256, 0, st>>>(part);
+      if (own_xcd) {                    // (numerics blocks of 64, no QK-norm)
+        OwnXcdJobs own;
+        own.blocks = blocks;
+        own.heads = BH;
+        memcpy(own.job, part.job, sizeof(own.job));
+        const auto kernel = mean == kMeanInline ? prepass_quant_kernel<D, 1, kMeanInline, true> : prepass_quant_kernel<D, 1, kMeanOfChunks, true>;
+        kernel<<<grid, 256, 0, st>>>(own);
+      } else {
+        const auto kernel = sub == 1 ? quantiser<D, 1>(mean) : quantiser<D, 2>(mean);
+        kernel<<<grid, 256, 0, st>>>(part);
+      }
       SAGE_LAUNCH_CHECK();
     }
   }
@@ -610,10 +618,62 @@ int decode_impl(const void* Q, const void* K, const void* V, void* O, float* LSE
   return SAGEBWD_OK;
 }
 
+// Short heads: see fwd_short_kernel.h.
+bool use_fwd_short(const sagebwd_params& p) {
+  return fwd_short_is_faster((long long)p.B * p.H, padded_rows(kv_len(p)) / 64, padded_rows(p.N) / 64) && !(p.smooth & SAGEBWD_SMOOTH_Q) &&
+         !(p.flags & SAGEBWD_FLAG_QK_NORM) && !big_blocks(p);
+}
+template <int D>
+int fwd_short_impl(const void* Q, const void* K, const void* V, void* O, float* LSE, const sagebwd_params& p, char* ws, size_t ws_bytes,
+                   const Workspace& w, hipStream_t st) {
+  const bool share = (p.flags & SAGEBWD_FLAG_SHARE_QUANTIZED) != 0;
+  const int BH = p.B * p.H;
+  ShortArgs a;
+  memset(&a, 0, sizeof(a));
+  a.Q = (const unsigned short*)Q;
+  a.K = (const unsigned short*)K;
+  a.V = (const unsigned short*)V;
+  a.qview = caller_view(p, 1, p.N);
+  a.kview = caller_view(p, 1, kv_len(p));
+  a.O = (unsigned short*)O;
+  a.LSE = LSE;
+  a.nq = p.N;
+  a.nk = kv_len(p);
+  a.nqblk = padded_rows(a.nq) / 64;
+  a.nkblk = padded_rows(a.nk) / 64;
+  a.shift = p.causal ? a.nk - a.nq : 0;
+  a.heads = BH;
+  a.own_xcd = prepass_own_xcd(BH, a.nqblk);
+  a.k_smooth = (p.smooth & SAGEBWD_SMOOTH_K) != 0;
+  a.scale_log2e = logit_scale(p) * 1.4426950408889634f;
+  // the quantised tensors are wanted by a backward that shares them and by the inspection hooks, which take the workspace of sagebwd_bwd
+  if (share || ws_bytes >= w.total) {
+    a.QF = (int8_t*)(ws + w.QF);
+    a.KF = (int8_t*)(ws + w.KF);
+    a.VT = (int8_t*)(ws + w.VT);
+    a.QT = share ? (int8_t*)(ws + w.QT) : nullptr;
+    a.KT = share ? (int8_t*)(ws + w.KT) : nullptr;
+    a.sQ = (float*)(ws + w.sQ);
+    a.sK = (float*)(ws + w.sK);
+    a.sV = (float*)(ws + w.sV);
+    a.muK = (float*)(ws + w.muK);
+  }
+  const dim3 grid = prepass_grid(a.nqblk, BH, 1, a.own_xcd != 0);
+  ScopedTimer tm(SAGEBWD_KERNEL_FWD, st);
+  auto launch = [&](auto kernel) { kernel<<<grid, 512, 0, st>>>(a); };
+  if (p.causal) launch(a.nkblk == 1 ? sage_fwd_short_kernel<D, true, 1> : sage_fwd_short_kernel<D, true, 2>);
+  else launch(a.nkblk == 1 ? sage_fwd_short_kernel<D, false, 1> : sage_fwd_short_kernel<D, false, 2>);
+  SAGE_LAUNCH_CHECK();
+  return SAGEBWD_OK;
+}
+
 // The forward on a workspace of `ws_bytes` (at least w.fwd_total; arguments already validated).
 int forward_impl(const void* Q, const void* K, const void* V, void* O, float* LSE, const sagebwd_params& p,
                  char* ws, size_t ws_bytes, const Workspace& w, hipStream_t st) {
   int rc;
+  if (use_fwd_short(p)) {
+    return p.d == 64 ? fwd_short_impl<64>(Q, K, V, O, LSE, p, ws, ws_bytes, w, st) : fwd_short_impl<128>(Q, K, V, O, LSE, p, ws, ws_bytes, w, st);
+  }
   if (use_decode(p)) {
     rc = p.d == 64 ? decode_impl<64>(Q, K, V, O, LSE, p, ws, w, st) : decode_impl<128>(Q, K, V, O, LSE, p, ws, w, st);
     // the quantised tensors themselves are wanted only by a backward that shares them and by the inspection hooks, which
