@@ -69,6 +69,13 @@ inline bool fwd_short_is_faster(long long heads, int nkblk, int nqblk) {
   return nkblk == 1 || (nkblk == 2 && (nqblk <= 2 || heads * nqblk <= 2 * kCus));
 }
 
+// ---- backward of at most two blocks of queries and of keys: one launch (sage_bwd_short_kernel; same bits) or three ----
+// Whole training steps (with the forward in one launch), us, three launches -> one.  d = 128: 8 heads of N = 64 24.1 -> 16.8, 256 31.3 ->
+// 23.8, 512 49.7 -> 36.0, 4096 306 -> 218; 8 of N = 128 28.3 -> 24.8, 64 31.3 -> 27.4, 256 49.5 -> 41.1, 512 88.7 -> 78.3, 2048 300 -> 279;
+// 8 of 128 x 37 24.7 -> 20.0.  d = 64: 20 of N = 33 18.6 -> 13.4, 256 of 64 22.6 -> 16.6, 1024 57.1 -> 38.4; 8 of 128 22.0 -> 18.5, 512
+// 56.6 -> 50.8, 2048 188 -> 176.  (More blocks do not fit the LDS.)
+inline bool bwd_short_is_faster(int nkblk, int nqblk) { return nkblk <= 2 && nqblk <= 2; }
+
 // ---- launches of the forward's pre-pass, and decoding: does a head have an XCD of its own? (prepass_item; same bits) ----
 // With K-smoothing every row of K is read twice and more: by the launch that sums it (or by every workgroup that quantises a block of a
 // short head) and by the one that quantises it; and the forward reads the codes on the head's XCD.  Past the L2 all of it comes at 6.6

@@ -18,6 +18,111 @@
 
 namespace sage {
 
+// What the kernels for short heads share: 512 threads on a block of 64 rows, eight to a row.
+template <int D>
+struct ShortBlock {
+  static constexpr int KS = D / 32;
+  static constexpr int TILE = 64 * D;                  // bytes of a block's codes
+  static constexpr int EPT = TILE / 512;               // values per thread
+  static constexpr int PER = TILE / 64;                // threads that turn a block from the F to the TF layout
+  static constexpr int G = 1024 / D;                   // row groups of the column sums, a pair of channels per thread
+  typedef unsigned short Raw __attribute__((ext_vector_type(EPT)));
+  typedef int Codes __attribute__((ext_vector_type(EPT / 4)));
+  int row, ch0;                                        // this thread's row of every block, and its channels
+  __device__ __forceinline__ ShortBlock(int t) : row(t >> 3), ch0((t & 7) * EPT) {}
+  __device__ __forceinline__ Raw load(const unsigned short* src, const RowView& view, int bh, int blk, int rows) const {
+    Raw r = {};
+    const int n = 64 * blk + row;
+    if (n < rows) {
+      const unsigned short* p = src + view.row(bh, n) + ch0;
+#pragma unroll
+      for (int k = 0; k < EPT / 8; k++) {
+        const v8us v = *(const v8us*)(p + 8 * k);
+#pragma unroll
+        for (int e = 0; e < 8; e++) r[8 * k + e] = v[e];
+      }
+    }
+    return r;
+  }
+  // where the thread's codes lie in a block's F layout
+  __device__ __forceinline__ int f_at() const {
+    return (((row >> 5) * KS + ch0 / 32) * 64 + (row & 31) + 32 * ((ch0 >> 4) & 1)) * 16 + (ch0 & 15);
+  }
+  static __device__ __forceinline__ Codes quantise(const float (&x)[EPT], float r) {
+    Codes c;
+#pragma unroll
+    for (int w = 0; w < EPT / 4; w++) c[w] = quantise_4(x[4 * w], x[4 * w + 1], x[4 * w + 2], x[4 * w + 3], r);
+    return c;
+  }
+  // mu_K of the thread's channels: float64 sums, divided by N, rounded once to FP32 (rows that do not exist are zero in `raw`).  Barriers
+  // inside; `rows_lds` (a bf16 image of the blocks) is free again behind it.
+  template <int KB>
+  __device__ __forceinline__ void mean(const Raw* raw, int nkblk, int nk, unsigned* rows_lds, double (*red)[D], float* mu_lds, float* mu_out,
+                                       float (&mu)[EPT]) const {
+    const int t = threadIdx.x;
+#pragma unroll
+    for (int j = 0; j < KB; j++) *(Raw*)((unsigned short*)rows_lds + (size_t)(64 * j + row) * D + ch0) = raw[j];
+    __syncthreads();
+    const int pair = t % (D / 2), g = t / (D / 2);
+    double a0 = 0.0, a1 = 0.0;
+    for (int r = g; r < 64 * nkblk; r += G) {
+      const unsigned u = rows_lds[r * (D / 2) + pair];
+      a0 += (double)__uint_as_float(u << 16);
+      a1 += (double)__uint_as_float(u & 0xffff0000u);
+    }
+    red[g][2 * pair] = a0;
+    red[g][2 * pair + 1] = a1;
+    __syncthreads();
+    if (t < D) {
+      double s = red[0][t];
+#pragma unroll
+      for (int k = 1; k < G; k++) s += red[k][t];
+      const float m = (float)(s / (double)nk);
+      mu_lds[t] = m;
+      if (mu_out != nullptr) mu_out[t] = m;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < EPT; e += 4) {
+      const v4f m = *(const v4f*)(mu_lds + ch0 + e);
+#pragma unroll
+      for (int k = 0; k < 4; k++) mu[e + k] = m[k];
+    }
+  }
+  // F to TF layout: thread i of PER takes four channels of sixteen rows
+  static __device__ __forceinline__ void transpose(const int8_t* f, int i, int8_t* out) {
+    const int quad = i & 7, h = (i >> 3) & 1, cb = (i >> 4) % KS, rb = (i >> 4) / KS;
+    const int c = 4 * quad;                              // channel 32 cb + c
+    const int8_t* p = f + ((rb * KS + cb) * 64 + 32 * (c >> 4)) * 16 + (c & 15);
+    v4i o[4];
+#pragma unroll
+    for (int a = 0; a < 4; a++) {
+      unsigned r[4];
+#pragma unroll
+      for (int b = 0; b < 4; b++) r[b] = *(const unsigned*)(p + (8 * a + 4 * h + b) * 16);
+      const unsigned t0 = __builtin_amdgcn_perm(r[1], r[0], 0x05010400u), t1 = __builtin_amdgcn_perm(r[1], r[0], 0x07030602u);
+      const unsigned u0 = __builtin_amdgcn_perm(r[3], r[2], 0x05010400u), u1 = __builtin_amdgcn_perm(r[3], r[2], 0x07030602u);
+      o[0][a] = (int)__builtin_amdgcn_perm(u0, t0, 0x05040100u);
+      o[1][a] = (int)__builtin_amdgcn_perm(u0, t0, 0x07060302u);
+      o[2][a] = (int)__builtin_amdgcn_perm(u1, t1, 0x05040100u);
+      o[3][a] = (int)__builtin_amdgcn_perm(u1, t1, 0x07060302u);
+    }
+    int8_t* q = out + ((rb * KS + cb) * 64 + c + 32 * h) * 16;
+#pragma unroll
+    for (int k = 0; k < 4; k++) *(v4i*)(q + 16 * k) = o[k];
+  }
+};
+// Scale and factor of psi from the maxima of eight waves.
+__device__ __forceinline__ void short_factors(const float* p, float& scale, float& factor) {
+  float a = p[0];
+#pragma unroll
+  for (int k = 1; k < 8; k++) a = fmaxf(a, p[k]);
+  const bool nz = a > 0.f;
+  scale = nz ? a / 127.0f : 0.f;
+  factor = nz ? 127.0f / a : 0.f;
+}
+__device__ __forceinline__ float of_lane(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
+
 struct ShortArgs {
   const unsigned short *Q, *K, *V;
   RowView qview, kview;            // Q and O; K and V
@@ -36,11 +141,9 @@ struct ShortArgs {
 
 template <int D, bool CAUSAL, int KB>
 __global__ void __launch_bounds__(512, 1) sage_fwd_short_kernel(ShortArgs args) {
-  constexpr int KS = D / 32;
-  constexpr int TILE = 64 * D;             // bytes of a block's codes
-  constexpr int EPT = TILE / 512;          // values of a block per thread: 8 threads to a row
+  typedef ShortBlock<D> Block;
+  constexpr int KS = Block::KS, TILE = Block::TILE, EPT = Block::EPT, PER = Block::PER, G = Block::G;
   constexpr int NTASK = 2 * KB + 1;        // blocks of K, of V, the one of Q
-  constexpr int G = 1024 / D;              // row groups of the column sums, a pair of channels per thread
   struct Lds {
     int8_t kf[KB][TILE];                   // K^, F layout
     int8_t qf[TILE];                       // Q^, F layout
@@ -64,67 +167,22 @@ __global__ void __launch_bounds__(512, 1) sage_fwd_short_kernel(ShortArgs args) 
   const int bh = item.head, qb = item.block;
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int row = t >> 3, ch0 = (t & 7) * EPT;          // this thread's row of every block, and its channels
+  const Block own(t);
+  const int row = own.row;
 
-  typedef unsigned short Raw __attribute__((ext_vector_type(EPT)));
-  Raw raw[NTASK];
-  auto load = [&](const unsigned short* src, const RowView& view, int blk, int rows) __attribute__((always_inline)) {
-    Raw r = {};
-    const int n = 64 * blk + row;
-    if (n < rows) {
-      const unsigned short* p = src + view.row(bh, n) + ch0;
+  typename Block::Raw raw[NTASK];
 #pragma unroll
-      for (int k = 0; k < EPT / 8; k++) {
-        const v8us v = *(const v8us*)(p + 8 * k);
+  for (int j = 0; j < KB; j++) raw[j] = own.load(args.K, args.kview, bh, j, args.nk);
 #pragma unroll
-        for (int e = 0; e < 8; e++) r[8 * k + e] = v[e];
-      }
-    }
-    return r;
-  };
-#pragma unroll
-  for (int j = 0; j < KB; j++) raw[j] = load(args.K, args.kview, j, args.nk);
-#pragma unroll
-  for (int j = 0; j < KB; j++) raw[KB + j] = load(args.V, args.kview, j, args.nk);
-  raw[2 * KB] = load(args.Q, args.qview, qb, args.nq);
+  for (int j = 0; j < KB; j++) raw[KB + j] = own.load(args.V, args.kview, bh, j, args.nk);
+  raw[2 * KB] = own.load(args.Q, args.qview, bh, qb, args.nq);
 
-  // ---- mu_K: float64 sums of the channels, divided by N, rounded once to FP32 ----
   float mu[EPT];
 #pragma unroll
   for (int e = 0; e < EPT; e++) mu[e] = 0.f;
-  if (args.k_smooth) {
-#pragma unroll
-    for (int j = 0; j < KB; j++) *(Raw*)((unsigned short*)L.raw + (size_t)(64 * j + row) * D + ch0) = raw[j];
-    __syncthreads();
-    const int pair = t % (D / 2), g = t / (D / 2);
-    double a0 = 0.0, a1 = 0.0;
-    const int rows = 64 * args.nkblk;                    // (missing rows are zero)
-    for (int r = g; r < rows; r += G) {
-      const unsigned u = L.raw[r * (D / 2) + pair];
-      a0 += (double)__uint_as_float(u << 16);
-      a1 += (double)__uint_as_float(u & 0xffff0000u);
-    }
-    L.red[g][2 * pair] = a0;
-    L.red[g][2 * pair + 1] = a1;
-    __syncthreads();
-    if (t < D) {
-      double s = L.red[0][t];
-#pragma unroll
-      for (int k = 1; k < G; k++) s += L.red[k][t];
-      const float m = (float)(s / (double)args.nk);
-      L.mu[t] = m;
-      if (args.muK != nullptr && qb == 0) args.muK[(size_t)bh * D + t] = m;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < EPT; e += 4) {
-      const v4f m = *(const v4f*)(L.mu + ch0 + e);
-#pragma unroll
-      for (int k = 0; k < 4; k++) mu[e + k] = m[k];
-    }
-  } else if (args.muK != nullptr && qb == 0 && t < D) {
-    args.muK[(size_t)bh * D + t] = 0.f;
-  }
+  float* mu_out = args.muK != nullptr && qb == 0 ? args.muK + (size_t)bh * D : nullptr;
+  if (args.k_smooth) own.template mean<KB>(raw, args.nkblk, args.nk, L.raw, L.red, L.mu, mu_out, mu);
+  else if (mu_out != nullptr && t < D) mu_out[t] = 0.f;
 
   // ---- psi: block maxima, scales, codes ----
   auto values = [&](int task, float (&x)[EPT]) __attribute__((always_inline)) {
@@ -146,31 +204,17 @@ __global__ void __launch_bounds__(512, 1) sage_fwd_short_kernel(ShortArgs args) 
   __syncthreads();
   // lane k has the factors of task k
   float scale, factor;
-  {
-    const float* p = L.amax[lane < NTASK ? lane : 0];
-    float a = p[0];
-#pragma unroll
-    for (int k = 1; k < 8; k++) a = fmaxf(a, p[k]);
-    const bool nz = a > 0.f;
-    scale = nz ? a / 127.0f : 0.f;
-    factor = nz ? 127.0f / a : 0.f;
-  }
-  auto of_task = [](float v, int task) __attribute__((always_inline)) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), task));
-  };
-  // where this thread's codes lie in a block's F layout
-  const int f_at = (((row >> 5) * KS + ch0 / 32) * 64 + (row & 31) + 32 * ((ch0 >> 4) & 1)) * 16 + (ch0 & 15);
+  short_factors(L.amax[lane < NTASK ? lane : 0], scale, factor);
+  auto of_task = [](float v, int task) __attribute__((always_inline)) { return of_lane(v, task); };
+  const int f_at = own.f_at();
   const bool writes = args.QF != nullptr;
   auto my_turn = [&](int j) { return writes && j < args.nkblk && j % args.nqblk == qb; };
-  typedef int Codes __attribute__((ext_vector_type(EPT / 4)));
+  typedef typename Block::Codes Codes;
 #pragma unroll
   for (int k = 0; k < NTASK; k++) {
     float x[EPT];
     values(k, x);
-    const float r = of_task(factor, k);
-    Codes c;
-#pragma unroll
-    for (int w = 0; w < EPT / 4; w++) c[w] = quantise_4(x[4 * w], x[4 * w + 1], x[4 * w + 2], x[4 * w + 3], r);
+    const Codes c = Block::quantise(x, of_task(factor, k));
     int8_t* f = k < KB ? L.kf[k] : k < 2 * KB ? L.vf[k - KB] : L.qf;
     *(Codes*)(f + f_at) = c;
     if (k < KB && my_turn(k)) *(Codes*)(args.KF + ((size_t)bh * args.nkblk + k) * TILE + f_at) = c;
@@ -183,32 +227,9 @@ __global__ void __launch_bounds__(512, 1) sage_fwd_short_kernel(ShortArgs args) 
   }
   __syncthreads();
 
-  // ---- TF layouts: thread i of a block's TILE / 64 takes four channels of sixteen rows ----
-  auto transpose = [&](const int8_t* f, int i, int8_t* out) __attribute__((always_inline)) {
-    const int quad = i & 7, h = (i >> 3) & 1, cb = (i >> 4) % KS, rb = (i >> 4) / KS;
-    const int c = 4 * quad;                              // channel 32 cb + c
-    const int8_t* p = f + ((rb * KS + cb) * 64 + 32 * (c >> 4)) * 16 + (c & 15);
-    v4i o[4];
-#pragma unroll
-    for (int a = 0; a < 4; a++) {
-      unsigned r[4];
-#pragma unroll
-      for (int b = 0; b < 4; b++) r[b] = *(const unsigned*)(p + (8 * a + 4 * h + b) * 16);
-      const unsigned t0 = __builtin_amdgcn_perm(r[1], r[0], 0x05010400u), t1 = __builtin_amdgcn_perm(r[1], r[0], 0x07030602u);
-      const unsigned u0 = __builtin_amdgcn_perm(r[3], r[2], 0x05010400u), u1 = __builtin_amdgcn_perm(r[3], r[2], 0x07030602u);
-      o[0][a] = (int)__builtin_amdgcn_perm(u0, t0, 0x05040100u);
-      o[1][a] = (int)__builtin_amdgcn_perm(u0, t0, 0x07060302u);
-      o[2][a] = (int)__builtin_amdgcn_perm(u1, t1, 0x05040100u);
-      o[3][a] = (int)__builtin_amdgcn_perm(u1, t1, 0x07060302u);
-    }
-    int8_t* q = out + ((rb * KS + cb) * 64 + c + 32 * h) * 16;
-#pragma unroll
-    for (int k = 0; k < 4; k++) *(v4i*)(q + 16 * k) = o[k];
-  };
-  constexpr int PER = TILE / 64;           // threads of a block
   for (int i = t; i < KB * PER; i += 512) {
     const int j = i / PER;
-    if (j < args.nkblk) transpose(L.vf[j], i % PER, L.vt[j]);
+    if (j < args.nkblk) Block::transpose(L.vf[j], i % PER, L.vt[j]);
   }
   // ---- the attention.  Four waves share 32 queries: wave (jj, kb) has 32-key block kb of the tiles jj, jj + 2, ... for the logits and P,
   // and channel block 2 jj + kb for O.  Row maxima, P^ and the sums of P go through LDS; every value is formed as in fwd_tile, and
@@ -334,11 +355,11 @@ __global__ void __launch_bounds__(512, 1) sage_fwd_short_kernel(ShortArgs args) 
   if (!writes) return;
   for (int j = 0; j < args.nkblk; j++) {
     if (!my_turn(j)) continue;
-    if (args.KT != nullptr && t < PER) transpose(L.kf[j], t, args.KT + ((size_t)bh * args.nkblk + j) * TILE);
+    if (args.KT != nullptr && t < PER) Block::transpose(L.kf[j], t, args.KT + ((size_t)bh * args.nkblk + j) * TILE);
     int8_t* out = args.VT + ((size_t)bh * args.nkblk + j) * TILE;
     for (int i = t; i < TILE / 16; i += 512) *(v4i*)(out + 16 * i) = *(const v4i*)(L.vt[j] + 16 * i);
   }
-  if (args.QT != nullptr && t >= 512 - PER) transpose(L.qf, t - (512 - PER), args.QT + ((size_t)bh * args.nqblk + qb) * TILE);
+  if (args.QT != nullptr && t >= 512 - PER) Block::transpose(L.qf, t - (512 - PER), args.QT + ((size_t)bh * args.nqblk + qb) * TILE);
 }
 
 }  // namespace sage

@@ -16,6 +16,7 @@
 #include "fwd_decode_kernel.h"
 #include "fwd_short_kernel.h"
 #include "bwd_kernel.h"
+#include "bwd_short_kernel.h"
 #include "probe_kernels.h"
 
 // Workspace of sagebwd_fwd_static: one array per GPU, held until the process ends.  In host code the
@@ -715,6 +716,63 @@ int forward_impl(const void* Q, const void* K, const void* V, void* O, float* LS
   return rc;
 }
 
+// Short heads: see bwd_short_kernel.h.  (All heads in one group: the launch leaves psi(dS) of every head in the scratch.)
+bool use_bwd_short(const sagebwd_params& p, const Workspace& w) {
+  return bwd_short_is_faster(padded_rows(kv_len(p)) / 64, padded_rows(p.N) / 64) && !(p.smooth & SAGEBWD_SMOOTH_Q) && !big_blocks(p) &&
+         (!(p.flags & SAGEBWD_FLAG_QK_NORM) || (p.flags & SAGEBWD_FLAG_SHARE_QUANTIZED)) && w.heads_per_group >= p.B * p.H;
+}
+template <int D>
+int bwd_short_impl(const void* Q, const void* K, const void* V, const void* O, const void* dO, const float* LSE, void* dQ, void* dK, void* dV,
+                   const sagebwd_params& p, char* ws, const Workspace& w, hipStream_t st) {
+  ShortBwdArgs a;
+  memset(&a, 0, sizeof(a));
+  a.Q = (const unsigned short*)Q;
+  a.K = (const unsigned short*)K;
+  a.V = (const unsigned short*)V;
+  a.O = (const unsigned short*)O;
+  a.dO = (const unsigned short*)dO;
+  a.nq = p.N;
+  a.nk = kv_len(p);
+  a.qview = caller_view(p, 1, a.nq);
+  a.kview = caller_view(p, 1, a.nk);
+  a.LSE = LSE;
+  a.dQ = (unsigned short*)dQ;
+  a.dK = (unsigned short*)dK;
+  a.dV = (unsigned short*)dV;
+  a.nqblk = padded_rows(a.nq) / 64;
+  a.nkblk = padded_rows(a.nk) / 64;
+  a.shift_blocks = p.causal ? (a.nk - a.nq) / 64 : 0;
+  a.k_smooth = (p.smooth & SAGEBWD_SMOOTH_K) != 0;
+  a.sm_scale = logit_scale(p);
+  a.scale_log2e = a.sm_scale * 1.4426950408889634f;
+  a.QF = (int8_t*)(ws + w.QF);
+  a.QT = (int8_t*)(ws + w.QT);
+  a.KF = (int8_t*)(ws + w.KF);
+  a.KT = (int8_t*)(ws + w.KT);
+  a.dOT = (int8_t*)(ws + w.dOT);
+  a.sQ = (float*)(ws + w.sQ);
+  a.sK = (float*)(ws + w.sK);
+  a.sdO = (float*)(ws + w.sdO);
+  a.delta = (float*)(ws + w.delta);
+  a.nl2 = (float*)(ws + w.nl2);
+  a.muK = (float*)(ws + w.muK);
+  a.dSq = (int8_t*)(ws + w.dSq);
+  a.ds_pitch = w.ds_pitch;
+  a.sdS = (float*)(ws + w.sdS);
+  const bool one = a.nqblk == 1 && a.nkblk == 1, share = (p.flags & SAGEBWD_FLAG_SHARE_QUANTIZED) != 0;
+  ScopedTimer tm(SAGEBWD_KERNEL_BWD, st);
+  auto launch = [&](auto kernel) { kernel<<<p.B * p.H, 512, 0, st>>>(a); };
+  auto pick = [&](auto causal) {
+    constexpr bool C = decltype(causal)::value;
+    if (one) launch(share ? sage_bwd_short_kernel<D, C, 1, true> : sage_bwd_short_kernel<D, C, 1, false>);
+    else launch(share ? sage_bwd_short_kernel<D, C, 2, true> : sage_bwd_short_kernel<D, C, 2, false>);
+  };
+  if (p.causal) pick(std::true_type{});
+  else pick(std::false_type{});
+  SAGE_LAUNCH_CHECK();
+  return SAGEBWD_OK;
+}
+
 // Times `reps` launches of `launch` on `st` with one pair of events around them, after one untimed launch;
 // waits for them.  Returns the mean milliseconds per launch through *ms.
 template <class F>
@@ -904,6 +962,8 @@ int sagebwd_bwd(const void* Q, const void* K, const void* V, const void* O, cons
   const int Nk = kv_len(*params), Nkp = padded_rows(Nk), Nqp = padded_rows(params->N);
   const int shift_blocks = params->causal ? (Nk - params->N) / 64 : 0;
   const bool qs = (params->smooth & SAGEBWD_SMOOTH_Q) != 0;
+  if (use_bwd_short(*params, w))
+    return d == 64 ? bwd_short_impl<64>(Q, K, V, O, dO, LSE, dQ, dK, dV, *params, ws, w, st) : bwd_short_impl<128>(Q, K, V, O, dO, LSE, dQ, dK, dV, *params, ws, w, st);
   {
     ScopedTimer tm(SAGEBWD_KERNEL_PREPASS_BWD, st);
     const bool reuse = (params->flags & SAGEBWD_FLAG_SHARE_QUANTIZED) != 0;   // Q^, K^ as the forward left them
