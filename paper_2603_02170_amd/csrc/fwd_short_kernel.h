@@ -257,10 +257,13 @@ __global__ void __launch_bounds__(512, 1) sage_fwd_short_kernel(ShortArgs args) 
         const int j = jj + 2 * o;
         if (j > last) continue;
         const int8_t* k = L.kf[j] + kb * KS * 1024 + lane * 16;
+        v16i zero;
 #pragma unroll
-        for (int r = 0; r < 16; r++) sacc[o][r] = SBIAS ? kBiasBits : 0;
+        for (int r = 0; r < 16; r++) zero[r] = 0;
+        if constexpr (SBIAS) sacc[o] = mfma_from_bias(*(const v4i*)k, qf[0]);
+        else sacc[o] = __builtin_amdgcn_mfma_i32_32x32x32_i8(*(const v4i*)k, qf[0], zero, 0, 0, 0);
 #pragma unroll
-        for (int s = 0; s < KS; s++) sacc[o] = __builtin_amdgcn_mfma_i32_32x32x32_i8(*(const v4i*)(k + s * 1024), qf[s], sacc[o], 0, 0, 0);
+        for (int s = 1; s < KS; s++) sacc[o] = __builtin_amdgcn_mfma_i32_32x32x32_i8(*(const v4i*)(k + s * 1024), qf[s], sacc[o], 0, 0, 0);
         int m = INT_MIN;
 #pragma unroll
         for (int r = 0; r < 16; r++) {

@@ -146,3 +146,12 @@ def test_products_that_start_from_the_inline_constant_are_read_by_their_chain_on
             if any(overlaps(dst, r) for r in _registers(line)):
                 assert line.startswith("v_mfma_i32_32x32x32_i8") and _registers(line)[3:] == [dst], (code[n], line)
                 break
+
+
+def test_kernels_of_short_heads(kernels):
+    # nothing in scratch; with one block at d = 128 two workgroups of eight waves per CU, of the forward with two blocks as well
+    for stem in ("sage_fwd_short_kernel", "sage_bwd_short_kernel"):
+        for k in _pick(kernels, stem):
+            assert k["scratch"] == 0 and k["vgpr"] <= 256 and k["lds"] <= 160 * 1024, k
+    for k in _pick(kernels, "sage_bwd_short_kernel", "ILi128E", "ELi1ELb") + _pick(kernels, "sage_fwd_short_kernel", "ILi128E"):
+        assert k["vgpr"] <= 128 and 2 * k["lds"] <= 160 * 1024, k
