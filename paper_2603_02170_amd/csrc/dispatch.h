@@ -144,6 +144,15 @@ inline bool decode_long_enough(long long heads, int nblk, int d, bool k_smooth) 
   return blocks >= 512;
 }
 
+// A head's workgroups on one XCD (prepass_item), by the elements of K: while K fits the L2s (32 MB in all) the second read of it comes from
+// there, and where it is several times that the ids as they come leave as little; in between those were the better order.  Whole calls with
+// one query row, us, ids as they come -> own XCD, MB of K: d = 128: 4 (8 heads of 2048 keys) 18.7 -> 17.5, 17 (8 of 8192) 23.2 ->
+// 21.9, 25 (24 of 4096) 26.7 -> 26.2, 33 (16 of 8192) 29.6 -> 29.9, 33 (64 of 2048) 28.3 -> 28.5, 50 (48 of 4096) 39.2 -> 39.4, 67 (64 of
+// 4096) 44.6 -> 45.3, 67 (128 of 2048) 45.7 -> 47.8, 100 (96 of 4096) 65.2 -> 64.1, 134 (64 of 8192) 78.4 -> 76.2; d = 64: 8 (32 of 2048) 16.8
+// -> 16.0, 17 (32 of 4096) 20.2 -> 19.6, 25 (24 of 8192) 26.7 -> 26.0, 33 (64 of 4096) 29.3 -> 30.3, 33 (32 of 8192) 27.9 -> 26.8, 50
+// (96 of 4096) 40.0 -> 41.7, 67 (128 of 4096) 44.6 -> 48.5, 100 (96 of 8192) 63.0 -> 62.5, 134 (128 of 8192) 78.5 -> 77.4.
+inline bool decode_own_xcd(long long elements) { return elements <= (14ll << 20) || elements >= (48ll << 20); }
+
 // Key blocks of a wave; a workgroup has four waves, and where a head has several workgroups a second kernel joins their results
 // (about 3 us, more with many query rows, whose partial results are FP32 rows).
 // Two workgroups fit a CU, so long caches take as many as fill one round of them.  A head keeps one workgroup where that alone is as good.

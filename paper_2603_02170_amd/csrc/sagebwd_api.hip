@@ -598,7 +598,7 @@ int decode_impl(const void* Q, const void* K, const void* V, void* O, float* LSE
   // it is the last of its head, and leaves at most 32 * (4 D + 8)
   a.part_ml = (v2f*)(ws + w.KF);
   a.part = (float*)(ws + w.KF + align_up((size_t)BH * nsplit * 32 * sizeof(v2f)));
-  const bool own_xcd = ks && prepass_own_xcd(BH, a.nblk);
+  const bool own_xcd = ks && decode_own_xcd((long long)BH * a.nk * D) && prepass_own_xcd(BH, a.nblk);
   a.nsplit = nsplit;
   a.heads = BH;
   a.own_xcd = own_xcd;
