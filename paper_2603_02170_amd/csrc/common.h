@@ -297,8 +297,9 @@ __host__ __device__ inline int quad_head_set(int heads, int items) {
 // ids, and so a head's blocks, go round the 8 XCDs; or, `own_xcd`, (8, blocks, jobs x heads / 8), in which a head's workgroups have
 // one XCD, the same in every launch and the one that the attention kernels give the head: what one launch has read or written is then
 // in the L2 that the next one reads through (see prepass_own_xcd).  The grid holds what a workgroup needs for it, so that it divides by
-// nothing, and the quantiser is instantiated for either: its job lies in the arguments at a place that waits for the number of heads,
-// one more trip to memory in front of all else (0.3 us a launch).
+// nothing, and the kernels are instantiated for either: a workgroup that has to look in the arguments which of the two it is begins to
+// load that much later (0.3 us a launch of the quantiser, whose job lies at a place that waits for the number of heads; decoding, 32
+// heads of 4096 keys, 28.6 us, with the choice at run time 29.2).
 struct PrepassItem {
   int job, head, block;
 };

@@ -40,11 +40,11 @@ struct DecodeArgs {
   int nq, nk, nblk;            // query rows (<= 32), keys, key blocks
   int blocks_per_wave;
   int nsplit;                  // workgroups of a head
-  int heads, own_xcd;          // see prepass_item
+  int heads;
   float scale_log2e;
 };
 
-template <int D, bool KSMOOTH>
+template <int D, bool KSMOOTH, bool OWN_XCD = false>
 __global__ void __launch_bounds__(256, 2) sage_fwd_decode_kernel(DecodeArgs args) {
   constexpr int KS = D / 32;
   constexpr int Q_LDS = D == 128 ? 2 : 0;    // fragments of psi(Q), the same for all four waves, that lie in LDS: nothing is in scratch then
@@ -56,7 +56,7 @@ __global__ void __launch_bounds__(256, 2) sage_fwd_decode_kernel(DecodeArgs args
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int r32 = lane & 31, h = lane >> 5;
-  const PrepassItem item = prepass_item(blockIdx.x, blockIdx.y, blockIdx.z, args.own_xcd != 0, args.heads);
+  const PrepassItem item = prepass_item(blockIdx.x, blockIdx.y, blockIdx.z, OWN_XCD, args.heads);
   const int bh = item.head, split = item.block;
 
   // this wave's fragments of a block: row 32 rb + r32, channels 32 s + 16 h .. + 16 (two 16-byte pieces)

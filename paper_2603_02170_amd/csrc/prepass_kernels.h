@@ -127,15 +127,15 @@ __device__ __forceinline__ void column_sums(const unsigned short* __restrict__ b
 // ---- K mean, stage 1: float64 column sums of a chunk of rows -----------------------
 // Stage 2, the sum over the chunks, the division by N and the one rounding to
 // FP32, runs at the start of every workgroup that quantises a block of K (prepass_quant_kernel).
-template <int D, int NORMED>
+template <int D, int NORMED, bool OWN_XCD = false>
 __global__ void __launch_bounds__(256) kmean_partial_kernel(const unsigned short* __restrict__ K, RowView view,
                                                             double* __restrict__ kpart, int N,
-                                                            int nchunk, int chunk_rows, QkNorm norm, int heads, int own_xcd) {
+                                                            int nchunk, int chunk_rows, QkNorm norm, int heads) {
   constexpr int TPR = D / 8;
   constexpr int RPP = 256 / TPR;
   __shared__ double red[256][8];
   const int t = threadIdx.x;
-  const PrepassItem item = prepass_item(blockIdx.x, blockIdx.y, blockIdx.z, own_xcd != 0, heads);
+  const PrepassItem item = prepass_item(blockIdx.x, blockIdx.y, blockIdx.z, OWN_XCD, heads);
   const int chunk = item.block, bh = item.head;
   const int row0 = chunk * chunk_rows;
   double acc[8];

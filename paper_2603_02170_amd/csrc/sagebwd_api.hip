@@ -225,10 +225,10 @@ struct ScopedTimer {
 template <int D>
 int launch_kmean(const void* K, const RowView& kview, const sagebwd_params& p, char* ws, const Workspace& w, const QkNorm& norm,
                  bool own_xcd, hipStream_t st) {
-  const auto kernel = norm.gamma != nullptr ? kmean_partial_kernel<D, 4> : kmean_partial_kernel<D, 0>;
+  const auto kernel = norm.gamma != nullptr ? kmean_partial_kernel<D, 4> : own_xcd ? kmean_partial_kernel<D, 0, true> : kmean_partial_kernel<D, 0>;
   const int heads = p.B * p.H;
   kernel<<<prepass_grid(w.nchunk, heads, 1, own_xcd), 256, 0, st>>>((const unsigned short*)K, kview, (double*)(ws + w.kpart), kv_len(p), w.nchunk,
-                                                                   w.chunk_rows, norm, heads, own_xcd);
+                                                                   w.chunk_rows, norm, heads);
   SAGE_LAUNCH_CHECK();
   return SAGEBWD_OK;
 }
@@ -601,7 +601,6 @@ int decode_impl(const void* Q, const void* K, const void* V, void* O, float* LSE
   const bool own_xcd = ks && decode_own_xcd((long long)BH * a.nk * D) && prepass_own_xcd(BH, a.nblk);
   a.nsplit = nsplit;
   a.heads = BH;
-  a.own_xcd = own_xcd;
   const dim3 grid = prepass_grid(nsplit, BH, 1, own_xcd);
   if (ks) {
     ScopedTimer tm(SAGEBWD_KERNEL_PREPASS_FWD, st);
@@ -609,7 +608,8 @@ int decode_impl(const void* Q, const void* K, const void* V, void* O, float* LSE
     if (rc != SAGEBWD_OK) return rc;
   }
   ScopedTimer tm(SAGEBWD_KERNEL_FWD, st);
-  if (ks) sage_fwd_decode_kernel<D, true><<<grid, 256, 0, st>>>(a);
+  if (own_xcd) sage_fwd_decode_kernel<D, true, true><<<grid, 256, 0, st>>>(a);
+  else if (ks) sage_fwd_decode_kernel<D, true><<<grid, 256, 0, st>>>(a);
   else sage_fwd_decode_kernel<D, false><<<grid, 256, 0, st>>>(a);
   SAGE_LAUNCH_CHECK();
   if (nsplit > 1) {
