@@ -184,21 +184,24 @@ inline bool mean_inline(int heads, int N, int D) {
 
 // The rounding of psi on values held as FP32: q = rne(x * r) clamped to +-127 (which matters where r = 127 / max|x|
 // overflows, blocks of the smallest numbers, and for NaN: both become codes), four packed into a register.  x * r is rounded to FP32
-// before the addition that takes it to an integer, so the codes are those of rintf.
+// before the addition that takes it to an integer, so the codes are those of rintf.  Without CLAMP: where neither can be.
+template <bool CLAMP = true>
 __device__ __forceinline__ int quantise_4(const float x0, const float x1, const float x2, const float x3, const float r) {
+#pragma clang fp contract(off)
   const float x[4] = {x0, x1, x2, x3};
   unsigned u[4];
 #pragma unroll
   for (int e = 0; e < 4; e++) {
-    const float y = __builtin_amdgcn_fmed3f(x[e] * r, -127.f, 127.f);
+    const float y = CLAMP ? __builtin_amdgcn_fmed3f(x[e] * r, -127.f, 127.f) : x[e] * r;
     u[e] = __float_as_uint(y + 12582912.0f);               // 1.5 * 2^23: rne(y) in the low mantissa bits
   }
   return (int)(__builtin_amdgcn_perm(u[1], u[0], 0x0c0c0400u) | __builtin_amdgcn_perm(u[3], u[2], 0x04000c0cu));
 }
+template <bool CLAMP = true>
 __device__ __forceinline__ v4i quantise_16(const float (&x)[16], const float r) {
   v4i o;
 #pragma unroll
-  for (int w = 0; w < 4; w++) o[w] = quantise_4(x[4 * w], x[4 * w + 1], x[4 * w + 2], x[4 * w + 3], r);
+  for (int w = 0; w < 4; w++) o[w] = quantise_4<CLAMP>(x[4 * w], x[4 * w + 1], x[4 * w + 2], x[4 * w + 3], r);
   return o;
 }
 
