@@ -133,6 +133,7 @@ struct ShortArgs {
   int shift;                       // causal: query i sees keys k <= i + shift
   int heads, own_xcd;              // see prepass_item
   int k_smooth;
+  int converting;                  // the logits by the converting path whatever their scales (see fwd_short_impl)
   float scale_log2e;
   // the workspace's tensors, or nullptr (TF layouts of Q and K: where a backward shares them)
   int8_t *QF, *QT, *KF, *KT, *VT;
@@ -353,7 +354,7 @@ __global__ void __launch_bounds__(512, 1) sage_fwd_short_kernel(ShortArgs args) 
   };
   static_assert(KB < kBiasPeriod, "the bias is subtracted once, at the end");
   // (see sage_fwd_kernel for the line)
-  if (__builtin_amdgcn_readfirstlane((int)(cq * smax < 1e-3f))) attend(std::true_type{});
+  if (__builtin_amdgcn_readfirstlane((int)(!args.converting && cq * smax < 1e-3f))) attend(std::true_type{});
   else attend(std::false_type{});
   if (!writes) return;
   for (int j = 0; j < args.nkblk; j++) {

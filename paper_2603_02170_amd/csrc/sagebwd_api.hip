@@ -646,6 +646,8 @@ int fwd_short_impl(const void* Q, const void* K, const void* V, void* O, float* 
   a.heads = BH;
   a.own_xcd = prepass_own_xcd(BH, a.nqblk);
   a.k_smooth = (p.smooth & SAGEBWD_SMOOTH_K) != 0;
+  // (few queries of many heads that see all keys have the decoding form's logits here too: by the biased path their LSE would be off by 2e-5)
+  a.converting = use_decode(p);
   a.scale_log2e = logit_scale(p) * 1.4426950408889634f;
   // the quantised tensors are wanted by a backward that shares them and by the inspection hooks, which take the workspace of sagebwd_bwd
   if (share || ws_bytes >= w.total) {

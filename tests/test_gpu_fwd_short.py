@@ -75,3 +75,25 @@ def test_rows_have_the_bits_of_a_call_with_more_queries(heads, Nk, d, k_smooth):
         o, l = binding.sagebwd_fwd(Q[:, :, first:first + n].contiguous(), K, V, binding.SageParams(1, heads, n, d, causal=False, k_smooth=k_smooth, Nkv=Nk))
         torch.cuda.synchronize()
         assert torch.equal(O[:, :, first:first + n], o) and torch.equal(L[:, :, first:first + n], l)
+
+
+# Few queries of many heads, no mask: the decoding form's calls where their heads are longer.  Its LSE is within a few roundings of the
+# log-sum-exp of the stored codes: FP32 exponents of at most 16 are rounded by 2^-20 (and by 2^-15 on the biased path, which is not
+# taken here), their sum, its logarithm and an LSE of at most 8 by less than that together.
+@pytest.mark.parametrize("heads,Nq,Nk,d,k_smooth", [(1368, 4, 13, 128, False), (921, 26, 102, 128, True), (600, 32, 128, 64, True), (549, 1, 65, 128, True)])
+def test_lse_of_few_queries_of_many_heads(heads, Nq, Nk, d, k_smooth):
+    g = torch.Generator(device="cuda").manual_seed(5)
+    Q, K, V = (torch.randn((1, heads, n, d), generator=g, device="cuda") for n in (Nq, Nk, Nk))
+    Q, K = (x * torch.rsqrt(x.square().mean(-1, keepdim=True)) for x in (Q, K))
+    Q, K, V = (x.to(torch.bfloat16) for x in (Q, K, V))
+    p = binding.SageParams(1, heads, Nq, d, causal=False, k_smooth=k_smooth, Nkv=Nk)
+    ws = binding.alloc_workspace(p)
+    _, L = binding.sagebwd_fwd(Q, K, V, p, ws)
+
+    def stored(which, n):
+        codes, scale = binding.sagebwd_export_quantized(p, ws, which)[:2]
+        scale = scale.double().cpu().reshape(heads, -1).repeat_interleave(64, 1)[:, :n, None]
+        return codes.double().cpu().reshape(heads, -1, d)[:, :n] * scale
+
+    ref = torch.logsumexp(stored(binding.TENSOR_Q, Nq) @ stored(binding.TENSOR_K, Nk).transpose(1, 2) / d ** 0.5, -1)
+    assert (L.double().cpu().reshape(heads, Nq) - ref).abs().max() <= 4 * 2.0 ** -20
