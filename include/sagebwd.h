@@ -209,7 +209,7 @@ int sagebwd_export_ds(const sagebwd_params* params, const void* workspace, size_
  * biased or by the converting path), so that O agrees between calls of different B*H to its bf16 rounding and LSE to
  * about 1e-4.  sagebwd_bwd, given the same O and LSE, returns the same bits in every case.
  *
- * Heads of one or two blocks of keys (no Q-smoothing, QK-norm or larger blocks; with two, few blocks of queries) need none either, and
+ * Heads of one or two blocks of keys (no Q-smoothing, QK-norm or larger blocks, not too many blocks of queries) need none either, and
  * leave them where a later call could read them.
  *
  * A decoding step (at most 32 queries, no mask, numerics blocks of 64, neither Q-smoothing nor QK-norm, more than a

@@ -64,9 +64,16 @@ inline bool fwd_quad_is_faster(long long heads, int nblk, int nqblk, int d, bool
 // 128 15.4 -> 15.0, but 16 of 4096 x 128 21.8 -> 26.4, d = 64 15.2 -> 18.0.  Training steps, whose codes are written all the same: 8 of
 // 64 25.7 -> 24.0, 512 52.1 -> 50.0, 8 of 128 28.9 -> 28.5, 256 of 128 49.2 -> 49.5.
 // Four key blocks: 8 of 256 12.6 -> 14.9, 128 20.6 -> 29.5, d = 64 64 of 256 12.0 -> 11.4, 128 14.6 -> 21.9; three 12.3 -> 13.8.
-inline bool fwd_short_is_faster(long long heads, int nkblk, int nqblk) {
-  if (nqblk >= 1 << 20) return false;      // (the grid counts threads in 32 bits)
-  return nkblk == 1 || (nkblk == 2 && (nqblk <= 2 || heads * nqblk <= 2 * kCus));
+// One key block: up to 32 Q blocks a head always (64 heads of 2048 x 64 40.3 -> 30.8, d = 64 28.9 -> 22.0; 384 216 -> 164, 126 -> 104);
+// beyond, the Q blocks of a head follow each other in the two launches, which are the faster ones with many heads: d = 64, 8 of 8192 x 64
+// 14.3 -> 12.9, but 32 35.2 -> 38.6, 256 255 -> 280, 16 of 6144 16.9 -> 17.7, 12 of 16384 26.8 -> 30.3; d = 128, 64 of 4096 60.5 -> 55.2, 256 of
+// 8192 437 -> 426, 6 of 32768 42.4 -> 42.6, but 16 of 16384 53.3 -> 55.2, 24 of 32768 154 -> 166.  Where the backward's layouts are written too
+// (`share`): 64 of 4096 x 64 64.0 -> 60.3, 32 of 8192 58.9 -> 60.2, 4 of 8192 x 128 15.8 -> 17.1.
+inline bool fwd_short_is_faster(long long heads, int nkblk, int nqblk, int d, bool share) {
+  if (nqblk >= 1 << 20 || (share && nqblk > 64)) return false;      // (the grid counts threads in 32 bits)
+  const long long wgs = heads * nqblk;
+  if (nkblk == 1) return nqblk <= 32 || (d == 64 ? wgs <= 4 * kCus : nqblk <= 128 || wgs <= 12 * kCus);
+  return nkblk == 2 && (nqblk <= 2 || wgs <= 2 * kCus);
 }
 
 // ---- backward of at most two blocks of queries and of keys: one launch (sage_bwd_short_kernel; same bits) or three ----

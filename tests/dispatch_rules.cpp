@@ -49,6 +49,12 @@ int main() {
       {10, 64, 128, true, false}, {5, 128, 128, true, true}, {6, 47, 128, false, false}, {24, 16, 64, true, false}};
   for (const auto& c : kQuad)
     if (fwd_quad_is_faster(c.heads, c.nblk, c.nblk, c.d, c.causal) != c.quad) return printf("fwd_quad_is_faster: %d heads of %d blocks, d %d, mask %d\n", c.heads, c.nblk, c.d, c.causal), 1;
+  // psi and the forward in one launch: heads, key blocks, Q blocks, d, the backward's layouts written too
+  const struct { int heads, nkblk, nqblk, d; bool share, one; } kShort[] = {{8, 1, 1, 128, true, true}, {4096, 1, 1, 64, false, true}, {384, 1, 32, 64, false, true}, {16, 1, 96, 64, false, false},
+      {8, 1, 128, 64, false, true}, {12, 1, 256, 64, false, false}, {256, 1, 128, 128, false, true}, {16, 1, 256, 128, false, false}, {6, 1, 512, 128, false, true}, {64, 1, 64, 128, true, true},
+      {32, 1, 128, 128, true, false}, {4, 2, 128, 128, true, false}, {8, 2, 32, 64, false, true}, {16, 2, 64, 128, false, false}, {2048, 2, 2, 128, false, true}, {8, 3, 3, 128, false, false}};
+  for (const auto& c : kShort)
+    if (fwd_short_is_faster(c.heads, c.nkblk, c.nqblk, c.d, c.share) != c.one) return printf("fwd_short_is_faster: %d heads of %d x %d blocks, d %d\n", c.heads, c.nqblk, c.nkblk, c.d), 1;
   // order of the forward's workgroups: heads, query tiles, Q blocks
   const struct { int heads, tiles, nqblk; bool folded; } kFold[] = {{107, 4, 7, false}, {107, 4, 8, true}, {98, 5, 9, false}, {98, 5, 10, true}, {163, 3, 5, false}, {46, 8, 15, false},
       {64, 8, 15, true}, {80, 5, 9, true}, {245, 2, 3, true}, {51, 10, 19, true}, {36, 14, 28, true}};
