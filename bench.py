@@ -189,15 +189,17 @@ def main():
         torch.cuda.synchronize()
         for name, kid in names:
             tot, n = binding.read_timing(kid)
-            kern.setdefault(name, tot / max(n, 1))
+            if n:
+                kern.setdefault(name, tot / n)
     binding.set_timing(False)
-    kern = {k: kern[k] for k in ("prepass_fwd", "fwd", "prepass_bwd", "bwd", "bwd_dq")}
+    # (heads of one or two blocks have neither pre-passes nor a dQ kernel of their own)
+    kern = {k: kern[k] for k in ("prepass_fwd", "fwd", "prepass_bwd", "bwd", "bwd_dq") if k in kern}
 
     peaks = measured_peaks(torch, binding)
     tops = work_ops(w) / (ms * 1e-3) / 1e12
     # the backward kernel (sage_bwd_wide_kernel at the headline shape) runs four of the five backward matmuls (S recompute, dV, dP, dK); the fifth (dQ)
     # runs in sage_bwd_dq_kernel from the staged psi(dS) tiles
-    bwd_ops = work_ops(w, matmuls=4)
+    bwd_ops = work_ops(w, matmuls=4 if "bwd_dq" in kern else 5)
     # (four rounds of its workgroups and more always take that kernel; below, the rule on sizes decides)
     wide = w.d == 128 and w.B * w.H * -(-w.N // 256) >= 1024
     bwd_kernel = "sage_bwd_wide_kernel" if wide else "backward kernel (by shape)"
@@ -248,20 +250,22 @@ def main():
         "roofline_fwd": {"bound": "mfma", "kernel": "sage_fwd_kernel", "achieved": fwd_tops, "peak": INT8_PEAK_TOPS,
                          "unit": "TOP/s", "frac": fwd_tops / INT8_PEAK_TOPS, "traffic": traffic.get("fwd"),
                          "frac_of_measured_peak": fwd_tops / peaks["int8_mfma"]["value"]},
-        "roofline_bwd_dq": {"bound": "hbm", "kernel": dq_kernel,
-                            "achieved": dq_bytes / (kern["bwd_dq"] * 1e-3) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                            "frac": dq_bytes / (kern["bwd_dq"] * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                            "traffic": traffic.get("bwd_dq"),
-                            "frac_of_measured_read": dq_bytes / (kern["bwd_dq"] * 1e-3) / 1e9 / peaks["hbm_read"]["value"],
-                            "note": "bytes = staged psi(dS) tiles + K^ + dQ; the tiles are this design's staging "
-                                    "of dS between the two backward kernels, not traffic the method itself requires"},
-        "roofline_prepass": {"bound": "hbm", "kernel": "prepass (forward)",
-                             "achieved": pre_fwd_bytes / (kern["prepass_fwd"] * 1e-3) / 1e9, "peak": HBM_PEAK_GBS,
-                             "unit": "GB/s", "frac": pre_fwd_bytes / (kern["prepass_fwd"] * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                             "bytes_per_element": pre_fwd_bytes / elems,
-                             "frac_of_measured_copy": pre_fwd_bytes / (kern["prepass_fwd"] * 1e-3) / 1e9 / peaks["hbm_copy"]["value"],
-                             "note": "K is read twice (mean, then psi); the second read is not counted"},
     }
+    if "bwd_dq" in kern:
+        out["roofline_bwd_dq"] = {"bound": "hbm", "kernel": dq_kernel,
+                                  "achieved": dq_bytes / (kern["bwd_dq"] * 1e-3) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                                  "frac": dq_bytes / (kern["bwd_dq"] * 1e-3) / 1e9 / HBM_PEAK_GBS,
+                                  "traffic": traffic.get("bwd_dq"),
+                                  "frac_of_measured_read": dq_bytes / (kern["bwd_dq"] * 1e-3) / 1e9 / peaks["hbm_read"]["value"],
+                                  "note": "bytes = staged psi(dS) tiles + K^ + dQ; the tiles are this design's staging "
+                                          "of dS between the two backward kernels, not traffic the method itself requires"}
+    if "prepass_fwd" in kern:
+        out["roofline_prepass"] = {"bound": "hbm", "kernel": "prepass (forward)",
+                                   "achieved": pre_fwd_bytes / (kern["prepass_fwd"] * 1e-3) / 1e9, "peak": HBM_PEAK_GBS,
+                                   "unit": "GB/s", "frac": pre_fwd_bytes / (kern["prepass_fwd"] * 1e-3) / 1e9 / HBM_PEAK_GBS,
+                                   "bytes_per_element": pre_fwd_bytes / elems,
+                                   "frac_of_measured_copy": pre_fwd_bytes / (kern["prepass_fwd"] * 1e-3) / 1e9 / peaks["hbm_copy"]["value"],
+                                   "note": "K is read twice (mean, then psi); the second read is not counted"}
     if not a.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(w)
     print(json.dumps(out))
