@@ -3,7 +3,8 @@
 // A call of a few short heads takes the time of its launches (about 4 us each, with the trips to memory that each begins and ends
 // with), not of its work.  Here a workgroup of eight waves takes one Q block of a head with ALL keys of the head (at most KB blocks of
 // 64): it sums K, quantises its Q block and every block of K and V, all 512 threads on a block together, and forms O from what lies in
-// LDS then, with the arithmetic of sage_fwd_kernel, so that the bits are its.  The blocks of a head are quantised by
+// LDS then, with the arithmetic of sage_fwd_kernel, so that the bits are its (`converting`: with the converting path for all logits, as
+// the decoding form has it; the sums in this form's order).  The blocks of a head are quantised by
 // each of its Q blocks' workgroups; the one whose turn it is writes the codes to the workspace, where a backward or an inspection hook
 // wants them.
 //

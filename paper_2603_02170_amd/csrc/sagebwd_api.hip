@@ -622,8 +622,7 @@ int decode_impl(const void* Q, const void* K, const void* V, void* O, float* LSE
 // Short heads: see fwd_short_kernel.h.
 bool use_fwd_short(const sagebwd_params& p) {
   return fwd_short_is_faster((long long)p.B * p.H, padded_rows(kv_len(p)) / 64, padded_rows(p.N) / 64, p.d, (p.flags & SAGEBWD_FLAG_SHARE_QUANTIZED) != 0) &&
-         !(p.smooth & SAGEBWD_SMOOTH_Q) &&
-         !(p.flags & SAGEBWD_FLAG_QK_NORM) && !big_blocks(p);
+         !(p.smooth & SAGEBWD_SMOOTH_Q) && !(p.flags & SAGEBWD_FLAG_QK_NORM) && !big_blocks(p);
 }
 template <int D>
 int fwd_short_impl(const void* Q, const void* K, const void* V, void* O, float* LSE, const sagebwd_params& p, char* ws, size_t ws_bytes,
