@@ -17,6 +17,9 @@
  *     [B, H, Nkv, d] (or [B, N, H, d] / [B, Nkv, H, d], see sagebwd_params.layout); LSE is float32
  *     [B, H, N].  Nkv = N unless sagebwd_params.Nkv says otherwise (cross attention, chunked prefill,
  *     decoding against a cache: the paper states the method for one length, nothing in it couples the two).
+ *   - Outputs in the memory of inputs: sagebwd_fwd reads Q, K and V before it writes O and LSE, which may lie there;
+ *     sagebwd_bwd reads Q, K, O and LSE before it writes the gradients, which may lie there, but V and dO until the
+ *     last of dK and dV is written.  (Calls whose outputs do are not given to the kernels that read and write at once.)
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  Work
  *     is enqueued on it and the call returns without synchronising.  The entry points
  *     only launch kernels (no allocation, no memset, no host synchronisation), so

@@ -1,6 +1,8 @@
 // Rules on sizes that choose between forms of a kernel and divide its work: plain host functions, which a test calls as well.
 #pragma once
 
+#include <stddef.h>
+
 namespace sage {
 
 // CUs of the machine: what a launch has to fill (four SIMDs each).
@@ -74,6 +76,32 @@ inline bool fwd_short_is_faster(long long heads, int nkblk, int nqblk, int d, bo
   const long long wgs = heads * nqblk;
   if (nkblk == 1) return nqblk <= 32 || (d == 64 ? wgs <= 4 * kCus : nqblk <= 128 || wgs <= 12 * kCus);
   return nkblk == 2 && (nqblk <= 2 || wgs <= 2 * kCus);
+}
+
+// ---- outputs that lie in the memory of inputs ----
+// In the separate launches of a forward K and V, and Q, are quantised before O and LSE are written, and a backward has read Q, K, O and
+// LSE before the gradients are: a caller may have O written over K, say.  The forms of one launch write the rows of one workgroup while
+// others still read.  What one workgroup alone reads and writes may be the same memory there: O in the place of Q, row for row, and in
+// the backward, of which a workgroup has read a whole head before it writes, a gradient in the place of an input of as many rows.
+struct Memory {
+  const void* at;
+  size_t bytes;
+};
+inline bool meet(const Memory& a, const Memory& b) {
+  const size_t x = (size_t)a.at, y = (size_t)b.at;
+  return x < y + b.bytes && y < x + a.bytes;
+}
+inline bool same(const Memory& a, const Memory& b) { return a.at == b.at && a.bytes == b.bytes; }
+inline bool fwd_outputs_apart(const Memory& Q, const Memory& K, const Memory& V, const Memory& O, const Memory& LSE) {
+  return !meet(O, K) && !meet(O, V) && (!meet(O, Q) || same(O, Q)) && !meet(LSE, Q) && !meet(LSE, K) && !meet(LSE, V);
+}
+inline bool bwd_outputs_apart(const Memory (&inputs)[5], const Memory& LSE, const Memory (&gradients)[3]) {
+  for (const Memory& g : gradients) {
+    if (meet(g, LSE)) return false;
+    for (const Memory& x : inputs)
+      if (meet(g, x) && !same(g, x)) return false;
+  }
+  return true;
 }
 
 // ---- backward of at most two blocks of queries and of keys: one launch (sage_bwd_short_kernel; same bits) or three ----

@@ -75,7 +75,8 @@ inline RowView caller_view(const sagebwd_params& p, size_t scale, int rows) {
   }
   return v;
 }
-
+// Bytes of one of the caller's bf16 tensors of `rows` rows.
+inline size_t tensor_bytes(const sagebwd_params& p, int rows) { return (size_t)p.B * p.H * rows * p.d * 2; }
 
 // Byte offsets of every buffer inside the caller's workspace.  What the forward needs comes first
 // (`fwd_total` bytes), so that a forward-only caller can pass a much smaller buffer.
@@ -674,14 +675,19 @@ int fwd_short_impl(const void* Q, const void* K, const void* V, void* O, float* 
 int forward_impl(const void* Q, const void* K, const void* V, void* O, float* LSE, const sagebwd_params& p,
                  char* ws, size_t ws_bytes, const Workspace& w, hipStream_t st) {
   int rc;
-  if (use_fwd_short(p)) {
+  // outputs in the memory of inputs: the forms that read K and V while they write O are not taken
+  const Memory q{Q, tensor_bytes(p, p.N)}, k{K, tensor_bytes(p, kv_len(p))}, v{V, k.bytes}, o{O, q.bytes};
+  const bool apart = fwd_outputs_apart(q, k, v, o, Memory{LSE, (size_t)p.B * p.H * p.N * sizeof(float)});
+  const bool leaves_codes = ws_bytes >= ((p.flags & SAGEBWD_FLAG_SHARE_QUANTIZED) ? w.fwd_total : w.total);
+  if (apart && use_fwd_short(p)) {
     return p.d == 64 ? fwd_short_impl<64>(Q, K, V, O, LSE, p, ws, ws_bytes, w, st) : fwd_short_impl<128>(Q, K, V, O, LSE, p, ws, ws_bytes, w, st);
   }
-  if (use_decode(p)) {
+  // (a decoding step quantises Q again behind itself where the codes are left)
+  if (apart && use_decode(p) && !(leaves_codes && same(o, q))) {
     rc = p.d == 64 ? decode_impl<64>(Q, K, V, O, LSE, p, ws, w, st) : decode_impl<128>(Q, K, V, O, LSE, p, ws, w, st);
     // the quantised tensors themselves are wanted only by a backward that shares them and by the inspection hooks, which
     // take the workspace of sagebwd_bwd
-    if (rc != SAGEBWD_OK || ws_bytes < ((p.flags & SAGEBWD_FLAG_SHARE_QUANTIZED) ? w.fwd_total : w.total)) return rc;
+    if (rc != SAGEBWD_OK || !leaves_codes) return rc;
     ScopedTimer tm(SAGEBWD_KERNEL_PREPASS_FWD, st);
     return p.d == 64 ? prepass_for_forward<64>(Q, K, V, p, ws, w, st) : prepass_for_forward<128>(Q, K, V, p, ws, w, st);
   }
@@ -964,7 +970,9 @@ int sagebwd_bwd(const void* Q, const void* K, const void* V, const void* O, cons
   const int Nk = kv_len(*params), Nkp = padded_rows(Nk), Nqp = padded_rows(params->N);
   const int shift_blocks = params->causal ? (Nk - params->N) / 64 : 0;
   const bool qs = (params->smooth & SAGEBWD_SMOOTH_Q) != 0;
-  if (use_bwd_short(*params, w))
+  const Memory mq{Q, tensor_bytes(*params, params->N)}, mk{K, tensor_bytes(*params, Nk)};
+  const Memory read[5] = {mq, mk, {V, mk.bytes}, {O, mq.bytes}, {dO, mq.bytes}}, written[3] = {{dQ, mq.bytes}, {dK, mk.bytes}, {dV, mk.bytes}};
+  if (use_bwd_short(*params, w) && bwd_outputs_apart(read, Memory{LSE, (size_t)BH * params->N * sizeof(float)}, written))
     return d == 64 ? bwd_short_impl<64>(Q, K, V, O, dO, LSE, dQ, dK, dV, *params, ws, w, st) : bwd_short_impl<128>(Q, K, V, O, dO, LSE, dQ, dK, dV, *params, ws, w, st);
   {
     ScopedTimer tm(SAGEBWD_KERNEL_PREPASS_BWD, st);

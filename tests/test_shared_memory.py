@@ -1,0 +1,17 @@
+"""Outputs in the memory of inputs (no GPU needed): the rule that keeps such calls from the forms of one launch."""
+import os
+import subprocess
+
+from paper_2603_02170_amd import build
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def test_calls_whose_outputs_lie_in_their_inputs(tmp_path):
+    exe = str(tmp_path / "shared_memory")
+    cmd = [build.hipcc_path(), "-x", "hip", "--cuda-host-only", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "paper_2603_02170_amd", "csrc"),
+           os.path.join(ROOT, "tests", "shared_memory.cpp"), "-o", exe]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-2000:]
+    run = subprocess.run([exe], capture_output=True, text=True)
+    assert run.returncode == 0, run.stdout
