@@ -168,6 +168,8 @@ inline bool use_bias_short(long long heads, int nblk, int nqblk, int d) {
 // 11.9, 300 of 2 15.1 -> 13.1. K-smoothing costs this way a launch for the mean, which the quantiser sums by itself in short heads:
 // with one block a head 512 heads of d = 128 13.0 -> 17.3, 4096 87.0 -> 89.1, 512 of d = 64 11.3 -> 13.3 (without K-smoothing 12.2
 // -> 10.1 at d = 128); with two, d = 128, 300 heads 16.8 -> 17.6, 340 17.2 -> 17.7, 384 18.7 -> 17.7.
+// (Heads of one or two key blocks have a form of one launch now, which is asked first and takes every such call: what stands here of them
+// compares the two that it replaced, and decides nothing.)
 inline bool decode_long_enough(long long heads, int nblk, int d, bool k_smooth) {
   if (nblk >= (d == 64 ? 16 : 20)) return true;
   const long long blocks = heads * nblk;
