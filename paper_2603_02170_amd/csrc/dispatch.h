@@ -66,16 +66,51 @@ inline bool fwd_quad_is_faster(long long heads, int nblk, int nqblk, int d, bool
 // 128 15.4 -> 15.0, but 16 of 4096 x 128 21.8 -> 26.4, d = 64 15.2 -> 18.0.  Training steps, whose codes are written all the same: 8 of
 // 64 25.7 -> 24.0, 512 52.1 -> 50.0, 8 of 128 28.9 -> 28.5, 256 of 128 49.2 -> 49.5.
 // Four key blocks: 8 of 256 12.6 -> 14.9, 128 20.6 -> 29.5, d = 64 64 of 256 12.0 -> 11.4, 128 14.6 -> 21.9; three 12.3 -> 13.8.
-// One key block: up to 32 Q blocks a head always (64 heads of 2048 x 64 40.3 -> 30.8, d = 64 28.9 -> 22.0; 384 216 -> 164, 126 -> 104);
-// beyond, the Q blocks of a head follow each other in the two launches, which are the faster ones with many heads: d = 64, 8 of 8192 x 64
-// 14.3 -> 12.9, but 32 35.2 -> 38.6, 256 255 -> 280, 16 of 6144 16.9 -> 17.7, 12 of 16384 26.8 -> 30.3; d = 128, 64 of 4096 60.5 -> 55.2, 256 of
-// 8192 437 -> 426, 6 of 32768 42.4 -> 42.6, but 16 of 16384 53.3 -> 55.2, 24 of 32768 154 -> 166.  Where the backward's layouts are written too
-// (`share`): 64 of 4096 x 64 64.0 -> 60.3, 32 of 8192 58.9 -> 60.2, 4 of 8192 x 128 15.8 -> 17.1.
-inline bool fwd_short_is_faster(long long heads, int nkblk, int nqblk, int d, bool share) {
-  if (nqblk >= 1 << 20 || (share && nqblk > 64)) return false;      // (the grid counts threads in 32 bits)
+// One key block and many Q blocks: 64 heads of 2048 x 64 40.3 -> 30.8, d = 64 28.9 -> 22.0; 384 216 -> 164, 126 -> 104; beyond 32 the Q blocks
+// of a head follow each other in the two launches: d = 64, 8 of 8192 x 64 14.3 -> 12.9, but 32 35.2 -> 38.6, 256 255 -> 280, 16 of 6144
+// 16.9 -> 17.7, 12 of 16384 26.8 -> 30.3; d = 128, 64 of 4096 60.5 -> 55.2, 256 of 8192 437 -> 426, 6 of 32768 42.4 -> 42.6, but 16 of 16384 53.3 ->
+// 55.2, 24 of 32768 154 -> 166; with codes 64 of 4096 x 64 64.0 -> 60.3, 32 of 8192 58.9 -> 60.2, 4 of 8192 x 128 15.8 -> 17.1.
+//
+// With many heads the two launches are the faster ones again, all the more where the codes are written (`codes`: for a backward, or on a
+// workspace of the full size).  Each line lies where both were timed, tensors warm and (in brackets) not seen for 700 MB.
+// One key block, d = 64.  Up to 32 Q blocks a head, a power of two of them, one launch always (2048 heads of 128 x 64 52 -> 42, with codes 54 ->
+// 44; 512 of 2048 183 -> 141): the two launches read such heads' codes, a power of two apart, at three quarters of the rate of others.  Three
+// Q blocks: 1365 heads of 192 42 -> 39 (47 -> 45), with codes 45 -> 44 (51 -> 54), 5461 170 -> 172 (4666: 162 -> 173).  More: 153 of 320 13.6 -> 10.9,
+// 819 40 -> 39 (45 -> 45), but 1638 68 -> 72, 2000 of 448 (114 -> 144), 1820 of 576 120 -> 142; with codes 131 of 384 12.5 -> 13.3, 256 of 320 16.6 ->
+// 18.0, 1638 72 -> 78, (2800 130 -> 168), 102 of 640 14.6 -> 15.3, 1820 of 576 131 -> 165.
+// d = 128, with codes: just over three workgroups per CU 387 of 78 x 30 19.9 -> 21.1, 131 of 384 19.1 -> 20.6, 67 of 768 18.6 -> 20.1.  341 of 576 (53 -> 52), but 568 77 -> 76 (77 -> 82), 744 of 704 (115 -> 127), 1555 of 576 (223 -> 210); with codes 204 of 320 25.1 -> 23.3, but
+// 1024 83 -> 90 (92 -> 98), 1170 of 448 (145 -> 149), 568 of 576 77 -> 88 (85 -> 97), 910 (142 -> 156), 236 of 832 (57 -> 60).
+// Two key blocks and two Q blocks, d = 64: 1024 heads of 65 33 -> 30, 3000 64 -> 76 (72 -> 83), 20000 with codes 450 -> 605; 3000 of 100 76 -> 80 (87 ->
+// 94), of 128 85 -> 81 (96 -> 103), 15000 of 128 x 65 365 -> 374; with codes 387 of 128 17.0 -> 19.0, 1024 39 -> 35, 3000 94 -> 105 (104 -> 118).  d = 128: 256 heads, a round of two workgroups
+// per CU, 18.6 -> 15.5, 387 22.6 -> 23.7, 512 34 -> 28; 3000 of 65 119 -> 124 (126 -> 137), with codes 512 28.8 -> 29.4, 1500 70 -> 79; 1500 of 80
+// with codes 75 -> 80 (81 -> 88).  More Q blocks, d = 128: 24 of 1024 (a CU and a half for each) 14.1 -> 14.4, 12 of 2048 13.6 -> 14.1, 8 of 4096 15.1 ->
+// 15.7; with codes 24 of 1024 14.6 -> 16.5, 96 of 256 16.4 -> 17.2, 8 of 4096 15.4 -> 17.0, but 170 of 192 x 70 21.8 -> 19.2.
+inline bool fwd_short_is_faster(long long heads, int nkblk, int nqblk, int d, bool codes, int nq = 0, int nk = 0) {
+  if (nqblk >= 1 << 20 || (codes && nqblk > 64)) return false;      // (the grid counts threads in 32 bits)
+  if (nq == 0) nq = 64 * nqblk;
+  if (nk == 0) nk = 64 * nkblk;
   const long long wgs = heads * nqblk;
-  if (nkblk == 1) return nqblk <= 32 || (d == 64 ? wgs <= 4 * kCus : nqblk <= 128 || wgs <= 12 * kCus);
-  return nkblk == 2 && (nqblk <= 2 || wgs <= 2 * kCus);
+  const bool power_of_two = (nqblk & (nqblk - 1)) == 0;
+  if (nkblk == 1 && d == 64) {
+    if (nqblk > 32) return wgs <= (codes ? 3 : 4) * kCus;
+    if (power_of_two) return true;
+    if (nqblk == 3) return !codes || wgs <= 12 * kCus;
+    return wgs <= (codes ? 3 : 8) * kCus;
+  }
+  if (nkblk == 1) {
+    if (nqblk > 128) return wgs <= 12 * kCus;
+    if (codes && nqblk > 1 && wgs > 3 * kCus && wgs < 1000) return false;
+    if (power_of_two || nqblk == 3) return true;
+    if (codes) return wgs <= 10 * kCus;
+    return nqblk < 7 || heads % 8 != 0 || wgs <= 16 * kCus || wgs > 40 * kCus;
+  }
+  if (nkblk != 2) return false;
+  if (nqblk == 1) return true;
+  if (nqblk == 2 && heads > kCus && (codes ? heads < 500 : d == 128 && heads < 430)) return false;
+  if (nqblk == 2 && d == 64) return codes ? heads <= 4 * kCus : heads <= (nq >= 112 ? 4000 : 1300);
+  if (nqblk == 2) return heads <= (codes ? kCus : 1300) || nq + nk >= 170;
+  if (d == 64) return wgs <= 2 * kCus;
+  return wgs <= kCus || (wgs <= 2 * kCus && (codes ? nqblk < 8 && wgs > 448 : nqblk < 16));
 }
 
 // ---- outputs that lie in the memory of inputs ----

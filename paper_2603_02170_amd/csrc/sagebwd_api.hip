@@ -621,8 +621,8 @@ int decode_impl(const void* Q, const void* K, const void* V, void* O, float* LSE
 }
 
 // Short heads: see fwd_short_kernel.h.
-bool use_fwd_short(const sagebwd_params& p) {
-  return fwd_short_is_faster((long long)p.B * p.H, padded_rows(kv_len(p)) / 64, padded_rows(p.N) / 64, p.d, (p.flags & SAGEBWD_FLAG_SHARE_QUANTIZED) != 0) &&
+bool use_fwd_short(const sagebwd_params& p, bool codes) {
+  return fwd_short_is_faster((long long)p.B * p.H, padded_rows(kv_len(p)) / 64, padded_rows(p.N) / 64, p.d, codes, p.N, kv_len(p)) &&
          !(p.smooth & SAGEBWD_SMOOTH_Q) && !(p.flags & SAGEBWD_FLAG_QK_NORM) && !big_blocks(p);
 }
 template <int D>
@@ -680,7 +680,7 @@ int forward_impl(const void* Q, const void* K, const void* V, void* O, float* LS
   const Memory q{Q, tensor_bytes(p, p.N)}, k{K, tensor_bytes(p, kv_len(p))}, v{V, k.bytes}, o{O, q.bytes};
   const bool apart = fwd_outputs_apart(q, k, v, o, Memory{LSE, (size_t)p.B * p.H * p.N * sizeof(float)});
   const bool leaves_codes = ws_bytes >= ((p.flags & SAGEBWD_FLAG_SHARE_QUANTIZED) ? w.fwd_total : w.total);
-  if (apart && use_fwd_short(p)) {
+  if (apart && use_fwd_short(p, leaves_codes)) {
     return p.d == 64 ? fwd_short_impl<64>(Q, K, V, O, LSE, p, ws, ws_bytes, w, st) : fwd_short_impl<128>(Q, K, V, O, LSE, p, ws, ws_bytes, w, st);
   }
   // (a decoding step quantises Q again behind itself where the codes are left)
