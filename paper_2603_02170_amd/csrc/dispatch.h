@@ -144,7 +144,20 @@ inline bool bwd_outputs_apart(const Memory (&inputs)[5], const Memory& LSE, cons
 // 23.8, 512 49.7 -> 36.0, 4096 306 -> 218; 8 of N = 128 28.3 -> 24.8, 64 31.3 -> 27.4, 256 49.5 -> 41.1, 512 88.7 -> 78.3, 2048 300 -> 279;
 // 8 of 128 x 37 24.7 -> 20.0.  d = 64: 20 of N = 33 18.6 -> 13.4, 256 of 64 22.6 -> 16.6, 1024 57.1 -> 38.4; 8 of 128 22.0 -> 18.5, 512
 // 56.6 -> 50.8, 2048 188 -> 176.  (More blocks do not fit the LDS.)
-inline bool bwd_short_is_faster(int nkblk, int nqblk) { return nkblk <= 2 && nqblk <= 2; }
+//
+// A head whose second block of queries or keys has few rows costs the one launch as much as whole blocks do, and the others' workgroups less:
+// with many heads they are the faster ones.  Backward alone, us, three -> one, with the codes shared and (without).  Two Q blocks and one of keys:
+// d = 64 (a CU has two workgroups), 512 heads of 128 x 64 24.5 -> 23.5 (31 -> 29), 768 33 -> 34 (42 -> 42), 1024 39 -> 44 (51 -> 55), 2048 68 -> 84 (95 ->
+// 108), 8192 of 100 x 33 247 -> 308 (327 -> 381); d = 128, 768 of 65 x 10 40 -> 40, 1400 69 -> 74, 2048 97 -> 104, 2048 of 100 x 33 118 -> 126, but of
+// 128 x 64 138 -> 139, 4096 275 -> 260 (without 360 -> 317; 308 -> 288 of 100 x 33).  Two of each, d = 128: 1024 of 65 70 -> 67, 2048 135 -> 144, 8192 492 -> 534
+// (669 -> 633), 2048 of 80 143 -> 152, of 96 155 -> 160, 4096 299 -> 299, of 112 327 -> 308; d = 64, 2048 of 65 87 -> 86.
+inline bool bwd_short_is_faster(long long heads, int nq, int nk, int d, bool share) {
+  if (nq > 128 || nk > 128) return false;
+  if (nq <= 64) return true;
+  if (d == 64) return nk > 64 || heads <= (share ? 2 : 3) * kCus;
+  if (!share) return true;
+  return nk <= 64 ? nk >= 48 || heads <= 900 : nq + nk >= 170 || heads <= 1200;
+}
 
 // ---- launches of the forward's pre-pass, and decoding: does a head have an XCD of its own? (prepass_item; same bits) ----
 // With K-smoothing every row of K is read twice and more: by the launch that sums it (or by every workgroup that quantises a block of a

@@ -727,8 +727,9 @@ int forward_impl(const void* Q, const void* K, const void* V, void* O, float* LS
 
 // Short heads: see bwd_short_kernel.h.  (All heads in one group: the launch leaves psi(dS) of every head in the scratch.)
 bool use_bwd_short(const sagebwd_params& p, const Workspace& w) {
-  return bwd_short_is_faster(padded_rows(kv_len(p)) / 64, padded_rows(p.N) / 64) && !(p.smooth & SAGEBWD_SMOOTH_Q) && !big_blocks(p) &&
-         (!(p.flags & SAGEBWD_FLAG_QK_NORM) || (p.flags & SAGEBWD_FLAG_SHARE_QUANTIZED)) && w.heads_per_group >= p.B * p.H;
+  const bool share = (p.flags & SAGEBWD_FLAG_SHARE_QUANTIZED) != 0;
+  return bwd_short_is_faster((long long)p.B * p.H, p.N, kv_len(p), p.d, share) && !(p.smooth & SAGEBWD_SMOOTH_Q) && !big_blocks(p) &&
+         (!(p.flags & SAGEBWD_FLAG_QK_NORM) || share) && w.heads_per_group >= p.B * p.H;
 }
 template <int D>
 int bwd_short_impl(const void* Q, const void* K, const void* V, const void* O, const void* dO, const float* LSE, void* dQ, void* dK, void* dV,

@@ -20,5 +20,13 @@ int main() {
   for (const auto& c : kFwd)
     if (fwd_short_is_faster(c.heads, (c.nk + 63) / 64, (c.nq + 63) / 64, c.d, c.codes, c.nq, c.nk) != c.one)
       return printf("fwd_short_is_faster: %d heads of %d x %d, d %d, codes %d\n", c.heads, c.nq, c.nk, c.d, c.codes), 1;
+  // heads, queries, keys, d, codes shared; one launch
+  const struct { int heads, nq, nk, d; bool share, one; } kBwd[] = {
+      {8192, 64, 64, 64, true, true}, {8192, 1, 128, 128, true, true}, {512, 128, 64, 64, true, true}, {1024, 128, 64, 64, true, false}, {2048, 100, 33, 64, false, false},
+      {768, 100, 33, 64, false, true}, {8192, 128, 128, 64, true, true}, {2048, 65, 10, 128, true, false}, {512, 65, 10, 128, true, true}, {4096, 128, 64, 128, true, true},
+      {4096, 100, 33, 128, false, true}, {2048, 65, 65, 128, true, false}, {8192, 65, 65, 128, false, true}, {4096, 112, 112, 128, true, true}, {2048, 65, 128, 128, true, true},
+      {8, 129, 64, 128, true, false}};
+  for (const auto& c : kBwd)
+    if (bwd_short_is_faster(c.heads, c.nq, c.nk, c.d, c.share) != c.one) return printf("bwd_short_is_faster: %d heads of %d x %d, d %d, share %d\n", c.heads, c.nq, c.nk, c.d, c.share), 1;
   return 0;
 }
