@@ -39,7 +39,7 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_short_kernel(ShortBwdArgs arg
   typedef ShortBlock<D> Block;
   typedef typename Block::Raw Raw;
   typedef typename Block::Codes Codes;
-  constexpr int KS = Block::KS, TILE = Block::TILE, EPT = Block::EPT, PER = Block::PER, G = Block::G;
+  constexpr int KS = Block::KS, TILE = Block::TILE, EPT = Block::EPT, PER = Block::PER, SUMS = Block::SUMS;
   constexpr int PPR = D / 8;               // 16-byte pieces of a bf16 row
   constexpr int NTASK = SHARE ? NB : 3 * NB;       // blocks of dO, then of Q, of K
   struct Frags {                           // of the tiles [Q block][KV block]
@@ -52,6 +52,7 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_short_kernel(ShortBwdArgs arg
       struct {
         int8_t qf[NB][TILE], kf[NB][TILE]; // F layouts
       };
+      double sums[SHARE ? 1 : SUMS][D];       // (before them: of K)
       int8_t dq_rows[NB][2 * TILE];        // at the end: rows of a gradient, pieces as in dO
     };
     union {
@@ -73,7 +74,6 @@ __global__ void __launch_bounds__(512, 1) sage_bwd_short_kernel(ShortBwdArgs arg
     float nl2[64 * NB], dl[64 * NB];       // -L log2(e), -delta
     float red[NB][NB][4][2];               // [Q block][KV block][wave]: max P, max |dS|
     float amax[NTASK][8];
-    double sums[SHARE ? 1 : G][D];
     float mu[D];
   };
   __shared__ __attribute__((aligned(16))) Lds L;

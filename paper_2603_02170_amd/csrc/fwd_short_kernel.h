@@ -19,6 +19,13 @@
 
 namespace sage {
 
+// In lane i of 32: a of lane i plus a of lane i + 32; in lane i + 32 the same of b.
+__device__ __forceinline__ double sum_of_halves(double a, double b) {
+  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+
 // What the kernels for short heads share: 512 threads on a block of 64 rows, eight to a row.
 template <int D>
 struct ShortBlock {
@@ -26,7 +33,8 @@ struct ShortBlock {
   static constexpr int TILE = 64 * D;                  // bytes of a block's codes
   static constexpr int EPT = TILE / 512;               // values per thread
   static constexpr int PER = TILE / 64;                // threads that turn a block from the F to the TF layout
-  static constexpr int G = 1024 / D;                   // row groups of the column sums, a pair of channels per thread
+  static constexpr int G = 2048 / D;                   // row groups of the column sums: a pair of channels of two of them per thread
+  static constexpr int SUMS = 16;                      // of them or of pairs of them in LDS, four of a wave of the pre-pass
   typedef unsigned short Raw __attribute__((ext_vector_type(EPT)));
   typedef int Codes __attribute__((ext_vector_type(EPT / 4)));
   int row, ch0;                                        // this thread's row of every block, and its channels
@@ -56,7 +64,10 @@ struct ShortBlock {
     return c;
   }
   // mu_K of the thread's channels: float64 sums, divided by N, rounded once to FP32 (rows that do not exist are zero in `raw`).  Barriers
-  // inside; `rows_lds` (a bf16 image of the blocks) is free again behind it.
+  // inside; `rows_lds` (a bf16 image of the blocks) is free again behind it.  The sums are added in the order of the pre-pass: row groups as
+  // the threads of column_sums have them, a wave's groups in pairs and pairs of pairs, then the waves in turn.  Sums of ordinary
+  // data are exact in any order; where they are not (1e30 beside 1 in a channel), a forward and a backward of other forms still have
+  // the same mean.
   template <int KB>
   __device__ __forceinline__ void mean(const Raw* raw, int nkblk, int nk, unsigned* rows_lds, double (*red)[D], float* mu_lds, float* mu_out,
                                        float (&mu)[EPT]) const {
@@ -65,19 +76,34 @@ struct ShortBlock {
     for (int j = 0; j < KB; j++) *(Raw*)((unsigned short*)rows_lds + (size_t)(64 * j + row) * D + ch0) = raw[j];
     __syncthreads();
     const int pair = t % (D / 2), g = t / (D / 2);
-    double a0 = 0.0, a1 = 0.0;
+    double a0 = 0.0, a1 = 0.0, b0 = 0.0, b1 = 0.0;       // groups g and g + G / 2
     for (int r = g; r < 64 * nkblk; r += G) {
-      const unsigned u = rows_lds[r * (D / 2) + pair];
+      const unsigned u = rows_lds[r * (D / 2) + pair], v = rows_lds[(r + G / 2) * (D / 2) + pair];
       a0 += (double)__uint_as_float(u << 16);
       a1 += (double)__uint_as_float(u & 0xffff0000u);
+      b0 += (double)__uint_as_float(v << 16);
+      b1 += (double)__uint_as_float(v & 0xffff0000u);
     }
-    red[g][2 * pair] = a0;
-    red[g][2 * pair + 1] = a1;
+    if constexpr (D == 64) {
+      // (the halves of a wave hold a pair of groups: each adds one of its two pairs, so that half as many values go through LDS.  All 32 of
+      // them there took registers that a fourth workgroup of a CU needs: 4096 heads of 64 39.0 -> 43.3 us)
+      const int p = (g >> 1) + (t & 32 ? SUMS / 2 : 0);
+      red[p][2 * pair] = sum_of_halves(a0, b0);
+      red[p][2 * pair + 1] = sum_of_halves(a1, b1);
+    } else {
+      red[g][2 * pair] = a0;
+      red[g][2 * pair + 1] = a1;
+      red[g + G / 2][2 * pair] = b0;
+      red[g + G / 2][2 * pair + 1] = b1;
+    }
     __syncthreads();
     if (t < D) {
-      double s = red[0][t];
+      double s = 0.0;
 #pragma unroll
-      for (int k = 1; k < G; k++) s += red[k][t];
+      for (int k = 0; k < SUMS; k += 4) {
+        const double w = (red[k][t] + red[k + 1][t]) + (red[k + 2][t] + red[k + 3][t]);
+        s = k == 0 ? w : s + w;
+      }
       const float m = (float)(s / (double)nk);
       mu_lds[t] = m;
       if (mu_out != nullptr) mu_out[t] = m;
@@ -144,7 +170,7 @@ struct ShortArgs {
 template <int D, bool CAUSAL, int KB>
 __global__ void __launch_bounds__(512, 1) sage_fwd_short_kernel(ShortArgs args) {
   typedef ShortBlock<D> Block;
-  constexpr int KS = Block::KS, TILE = Block::TILE, EPT = Block::EPT, PER = Block::PER, G = Block::G;
+  constexpr int KS = Block::KS, TILE = Block::TILE, EPT = Block::EPT, PER = Block::PER, SUMS = Block::SUMS;
   constexpr int NTASK = 2 * KB + 1;        // blocks of K, of V, the one of Q
   struct Lds {
     int8_t kf[KB][TILE];                   // K^, F layout
@@ -156,12 +182,16 @@ __global__ void __launch_bounds__(512, 1) sage_fwd_short_kernel(ShortArgs args) 
       };
       unsigned raw[KB * TILE / 2];         // K as it came, for the sums
     };
-    double red[G][D];
     float mu[D];
     float amax[NTASK][8];                  // maxima of the eight waves
-    int8_t p[2][KB][2][1024];              // [32 queries][tile][32 keys]: P^, the operand of P^V^
-    float psum[2][KB][2][64];              // sums of P
-    int rmax[2][KB][2][32];                // row maxima of the logits
+    union {
+      double red[SUMS][D];
+      struct {
+        int8_t p[2][KB][2][1024];          // [32 queries][tile][32 keys]: P^, the operand of P^V^
+        float psum[2][KB][2][64];          // sums of P
+        int rmax[2][KB][2][32];            // row maxima of the logits
+      };
+    };
   };
   __shared__ __attribute__((aligned(16))) Lds L;
 

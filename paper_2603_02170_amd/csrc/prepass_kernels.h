@@ -145,7 +145,22 @@ __global__ void __launch_bounds__(256) kmean_partial_kernel(const unsigned short
   __syncthreads();
   if (t < D) {
     double s = 0.0;
-    for (int g = 0; g < RPP; g++) s += red[g * TPR + t / 8][t % 8];
+    if (N <= 2 * kBlock) {
+      // (in the order in which the quantiser adds the groups of a head that it sums itself: short heads have one mean in all forms, also
+      // where their sums are not exact)
+      for (int g = 0; g < RPP; g += RPP / 4) {
+        double w[RPP / 4];
+#pragma unroll
+        for (int k = 0; k < RPP / 4; k++) w[k] = red[(g + k) * TPR + t / 8][t % 8];
+#pragma unroll
+        for (int off = 1; off < RPP / 4; off <<= 1)
+#pragma unroll
+          for (int k = 0; k < RPP / 4; k += 2 * off) w[k] += w[k + off];
+        s += w[0];
+      }
+    } else {
+      for (int g = 0; g < RPP; g++) s += red[g * TPR + t / 8][t % 8];
+    }
     kpart[((size_t)bh * nchunk + chunk) * D + t] = s;
   }
 }
