@@ -17,6 +17,9 @@
 
 namespace sage {
 
+// (products and sums are rounded apart, as in the other forms, but where an FMA is written)
+#pragma clang fp contract(off)
+
 struct ShortBwdArgs {
   const unsigned short *Q, *K, *V, *O, *dO;
   RowView qview, kview;            // Q, O, dO, dQ; K, V, dK, dV

@@ -19,6 +19,9 @@
 
 namespace sage {
 
+// (products and sums are rounded apart, as in the other forms, but where an FMA is written)
+#pragma clang fp contract(off)
+
 // In lane i of 32: a of lane i plus a of lane i + 32; in lane i + 32 the same of b.
 __device__ __forceinline__ double sum_of_halves(double a, double b) {
   const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
