@@ -170,6 +170,9 @@ inline bool bwd_short_is_faster(long long heads, int nq, int nk, int d, bool sha
 // chains; blocks of 128, 32 of 2048 235.4 -> 238.1), Q-smoothing (the bias kernel reads K in the order of ids, 16 of 1024 31.2 -> 31.9),
 // numerics blocks of 128 (32 of 2048 58.7 -> 60.0).  (65535: the grid's y and z.)
 inline bool prepass_own_xcd(int heads, long long blocks) { return heads % 8 == 0 && blocks > 1 && blocks <= 65535; }
+// One block of K and one or two of the others are no more: backwards that quantise Q and K themselves, d = 64, ids as they come -> own XCD,
+// 1000 heads of 128 x 64 49.1 -> 50.3, 2000 90.6 -> 93.8; three blocks and more 1000 of 512 x 64 with 7 % less.
+inline bool prepass_rows_shared(int nqblk, int nkblk) { return nkblk > 1 || nqblk > 2; }
 // dO alone, in a backward that shares psi(Q) and psi(K): the forward has left O, and the backward finds the codes, in the L2 of the head's
 // XCD, while the 5 bytes an element of all heads are little more than the L2s hold (32 MB).  Steps, us, ids as they come -> own XCD: 8
 // heads of N = 128 29.2 -> 28.8, 128 of 256 55.7 -> 54.6, 32 of 1024 81.5 -> 80.6, 64 of 1024 134.4 -> 132.7, 32 of 2048 183.1 ->

@@ -255,7 +255,7 @@ int run_prepass(const void* Q, const void* K, const void* V, const void* dO, con
   const bool inline_mean = ks && mean_inline(BH, Nk, D);
   const QkNorm norm_q{qkn ? p.qk_gamma_q : nullptr, p.qk_norm_eps}, norm_k{qkn ? p.qk_gamma_k : nullptr, p.qk_norm_eps};
   const int nblk_max = (Nqp > Nkp ? Nqp : Nkp) / 64;
-  const bool own_xcd = (want_qk ? ks && !qkn && !qs : dO_own_xcd((long long)BH * Nqp * D)) && !big_blocks(p) && prepass_own_xcd(BH, nblk_max);
+  const bool own_xcd = (want_qk ? ks && !qkn && !qs && prepass_rows_shared(Nqp / 64, Nkp / 64) : dO_own_xcd((long long)BH * Nqp * D)) && !big_blocks(p) && prepass_own_xcd(BH, nblk_max);
   if (want_qk) {
     if (ks && !inline_mean) {
       const int rc = launch_kmean<D>(K, kview, p, ws, w, norm_k, own_xcd, st);

@@ -28,5 +28,7 @@ int main() {
       {8, 129, 64, 128, true, false}};
   for (const auto& c : kBwd)
     if (bwd_short_is_faster(c.heads, c.nq, c.nk, c.d, c.share) != c.one) return printf("bwd_short_is_faster: %d heads of %d x %d, d %d, share %d\n", c.heads, c.nq, c.nk, c.d, c.share), 1;
+  // an XCD for every head in the pre-pass: not where a head has one block of keys and at most two of queries
+  if (prepass_rows_shared(2, 1) || prepass_rows_shared(1, 1) || !prepass_rows_shared(3, 1) || !prepass_rows_shared(1, 2)) return printf("prepass_rows_shared\n"), 1;
   return 0;
 }
