@@ -200,9 +200,12 @@ def main():
     # the backward kernel (sage_bwd_wide_kernel at the headline shape) runs four of the five backward matmuls (S recompute, dV, dP, dK); the fifth (dQ)
     # runs in sage_bwd_dq_kernel from the staged psi(dS) tiles
     bwd_ops = work_ops(w, matmuls=4 if "bwd_dq" in kern else 5)
+    # (dP, on bf16 MFMA at half rate, counts twice)
+    mixed = 4 / 5 if "bwd_dq" in kern else 5 / 6
     # (four rounds of its workgroups and more always take that kernel; below, the rule on sizes decides)
     wide = w.d == 128 and w.B * w.H * -(-w.N // 256) >= 1024
-    bwd_kernel = "sage_bwd_wide_kernel" if wide else "backward kernel (by shape)"
+    bwd_kernel = "sage_bwd_wide_kernel" if wide else "backward kernel (by shape)" if "bwd_dq" in kern else "sage_bwd_short_kernel (the pre-pass and dQ included)"
+    fwd_kernel = "sage_fwd_kernel" if "prepass_fwd" in kern else "sage_fwd_short_kernel (the pre-pass included)"
     # (and more than 1536 Q blocks, more than one a head, the two-block form of dQ)
     dq_kernel = "sage_bwd_dq_kernel" if w.N > 64 and w.B * w.H * -(-w.N // 64) > 1536 else "dQ kernel (by shape)"
     fwd_ops = work_ops(w, bwd=False)
@@ -241,13 +244,14 @@ def main():
         "roofline": {"bound": "mfma", "kernel": bwd_kernel, "achieved": bwd_tops, "peak": INT8_PEAK_TOPS,
                      "unit": "TOP/s", "frac": bwd_tops / INT8_PEAK_TOPS,
                      "traffic": traffic.get("bwd"),
-                     "frac_of_mixed_roof": bwd_tops / (INT8_PEAK_TOPS * 0.8),
+                     "frac_of_mixed_roof": bwd_tops / (INT8_PEAK_TOPS * mixed),
                      "frac_of_measured_peak": bwd_tops / peaks["int8_mfma"]["value"],
-                     "note": "algorithmic ops of the four matmuls this kernel runs (8*N^2*d per head, x0.5 causal) "
-                             "over its mean HIP-event duration, against the INT8 MFMA peak; one of the four (dP) "
-                             "runs on bf16 MFMA at half rate, so the kernel's own mixed roof is 4/5 of that peak "
+                     "note": ("algorithmic ops of the four matmuls this kernel runs (8*N^2*d per head, x0.5 causal) " if "bwd_dq" in kern else
+                              "algorithmic ops of the five matmuls this launch runs (10*N^2*d per head, x0.5 causal) ") +
+                             "over its mean HIP-event duration, against the INT8 MFMA peak; one of them (dP) "
+                             f"runs on bf16 MFMA at half rate, so the kernel's own mixed roof is {'4/5' if 'bwd_dq' in kern else '5/6'} of that peak "
                              "(frac_of_mixed_roof).  traffic: from profiles/, not measured in this run"},
-        "roofline_fwd": {"bound": "mfma", "kernel": "sage_fwd_kernel", "achieved": fwd_tops, "peak": INT8_PEAK_TOPS,
+        "roofline_fwd": {"bound": "mfma", "kernel": fwd_kernel, "achieved": fwd_tops, "peak": INT8_PEAK_TOPS,
                          "unit": "TOP/s", "frac": fwd_tops / INT8_PEAK_TOPS, "traffic": traffic.get("fwd"),
                          "frac_of_measured_peak": fwd_tops / peaks["int8_mfma"]["value"]},
     }
