@@ -127,6 +127,7 @@ typedef enum sagebwd_tensor {
 } sagebwd_tensor;
 
 /* Kernels whose device time sagebwd_read_timing() reports. */
+/* (Short heads: a forward of one launch counts as FWD alone, a backward of one launch as BWD alone.) */
 typedef enum sagebwd_kernel {
   SAGEBWD_KERNEL_PREPASS_FWD = 0, /* smoothing + psi(Q), psi(K), psi(V)            */
   SAGEBWD_KERNEL_FWD = 1,         /* fused forward (Algorithm 1 loop)              */
@@ -212,15 +213,16 @@ int sagebwd_export_ds(const sagebwd_params* params, const void* workspace, size_
  * biased or by the converting path), so that O agrees between calls of different B*H to its bf16 rounding and LSE to
  * about 1e-4.  sagebwd_bwd, given the same O and LSE, returns the same bits in every case.
  *
- * Heads of one or two blocks of keys (no Q-smoothing, QK-norm or larger blocks, not too many blocks of queries) need none either, and
- * leave them where a later call could read them.
- *
  * A decoding step (at most 32 queries, no mask, numerics blocks of 64, neither Q-smoothing nor QK-norm, more than a
- * thousand keys or enough heads) needs no quantised tensors in memory, and writes none where no later call could
+ * thousand keys, or more than 128 and enough heads) needs no quantised tensors in memory, and writes none where no later call could
  * read them: that is, where workspace_bytes is below *bwd_bytes of sagebwd_workspace_bytes (with
  * SAGEBWD_FLAG_SHARE_QUANTIZED, where the forward's own need holds what the backward reads, it always writes them).
  * On a workspace of the full size it runs the whole pre-pass behind itself, for the export hooks, which about doubles
  * its time: a caller that only decodes passes a workspace of *fwd_bytes.
+ *
+ * Most calls of at most 128 keys (the same numerics and options; the number of heads and of query blocks decides) quantise and attend
+ * in one launch.  They too write the quantised tensors only with SAGEBWD_FLAG_SHARE_QUANTIZED or on a workspace of at least *bwd_bytes,
+ * and in the same launch, at a small cost.
  */
 int sagebwd_fwd(const void* Q, const void* K, const void* V, void* O, float* LSE,
                 const sagebwd_params* params, void* workspace, size_t workspace_bytes,
