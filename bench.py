@@ -24,7 +24,7 @@ HBM_PEAK_GBS = 8000.0       # MI355X HBM3E peak (published)
 # HBM bytes per launch at the headline workload.  NOT measured in this run: taken from the committed
 # rocprofv3 FETCH_SIZE / WRITE_SIZE runs summarised in profiles/hbm_traffic_cases.txt
 # (scaled by the copy-kernel calibration stated there).
-PROFILED_TRAFFIC_BYTES = {"headline": {"bwd": 5.0164e9, "fwd": 3.381e8, "bwd_dq": 2.4924e9}}
+PROFILED_TRAFFIC_BYTES = {"headline": {"bwd": 5.0230e9, "fwd": 3.381e8, "bwd_dq": 2.4932e9}}
 
 
 def work_ops(w, fwd=True, bwd=True, matmuls=None):

@@ -299,7 +299,7 @@ __host__ __device__ inline int quad_head_set(int heads, int items) {
 // in the L2 that the next one reads through (see prepass_own_xcd).  The grid holds what a workgroup needs for it, so that it divides by
 // nothing, and the kernels are instantiated for either: a workgroup that has to look in the arguments which of the two it is begins to
 // load that much later (0.3 us a launch of the quantiser, whose job lies at a place that waits for the number of heads; decoding, 32
-// heads of 4096 keys, 28.6 us, with the choice at run time 29.2).
+// heads of 4096 keys, 28.6 us, with the choice at run time 29.2; sage_fwd_short_kernel has it at run time all the same).
 struct PrepassItem {
   int job, head, block;
 };
@@ -309,7 +309,8 @@ __host__ __device__ inline PrepassItem prepass_item(int x, int y, int z, bool ow
   for (; group >= heads / 8; group -= heads / 8) job++;
   return PrepassItem{job, x + 8 * group, y};
 }
-// The last rows of the heads of each XCD first.
+// The last rows of the heads of each XCD first: the order in which an L2 that does not hold all of it has kept what the launch before has
+// read of K (kmean_partial_kernel), or written of O (the forward, where the backward's pre-pass quantises dO alone).
 __host__ __device__ inline PrepassItem last_rows_first(const PrepassItem& i, int blocks, int heads) {
   return PrepassItem{i.job, heads - 8 + 2 * (i.head & 7) - i.head, blocks - 1 - i.block};
 }

@@ -151,6 +151,8 @@ inline bool bwd_outputs_apart(const Memory (&inputs)[5], const Memory& LSE, cons
 // 108), 8192 of 100 x 33 247 -> 308 (327 -> 381); d = 128, 768 of 65 x 10 40 -> 40, 1400 69 -> 74, 2048 97 -> 104, 2048 of 100 x 33 118 -> 126, but of
 // 128 x 64 138 -> 139, 4096 275 -> 260 (without 360 -> 317; 308 -> 288 of 100 x 33).  Two of each, d = 128: 1024 of 65 70 -> 67, 2048 135 -> 144, 8192 492 -> 534
 // (669 -> 633), 2048 of 80 143 -> 152, of 96 155 -> 160, 4096 299 -> 299, of 112 327 -> 308; d = 64, 2048 of 65 87 -> 86.
+// On tensors not seen for 700 MB, shared: d = 64, 1024 of 128 x 64 44 -> 49, 2400 of 100 x 33 80 -> 101; d = 128, 2400 of 65 x 10 127 -> 135, of 65 172
+// -> 183, of 100 x 33 154 -> 157, of 128 x 64 185 -> 175.
 inline bool bwd_short_is_faster(long long heads, int nq, int nk, int d, bool share) {
   if (nq > 128 || nk > 128) return false;
   if (nq <= 64) return true;
@@ -161,14 +163,19 @@ inline bool bwd_short_is_faster(long long heads, int nq, int nk, int d, bool sha
 
 // ---- launches of the forward's pre-pass, and decoding: does a head have an XCD of its own? (prepass_item; same bits) ----
 // With K-smoothing every row of K is read twice and more: by the launch that sums it (or by every workgroup that quantises a block of a
-// short head) and by the one that quantises it; and the forward reads the codes on the head's XCD.  Past the L2 all of it comes at 6.6
-// TB/s at most, from the memory-side cache too, out of it at 11 (a plain read of 128 MB and of 32).  Whole calls, us, ids as they
-// come -> own XCD: forward, 8 heads of N = 1000 22.1 -> 20.3, 8 of 512 17.8 -> 16.3, 64 of 256 16.2 -> 15.5, 128 of 640 49.0 -> 47.3, 200
+// short head) and by the one that quantises it; the chunk sums are read by every workgroup that quantises a block of the head (eight XCDs
+// had fetched them all, one does: 7.3 of 79.8 MB past the L2s with 512 queries against 4096 keys); and the forward reads the codes on the head's XCD.
+// What a launch has read or written is still in the L2 of its XCD for the next one, as far as it fits: a plain read of 32 MB by one launch after
+// the other takes 2.5 us with every workgroup on the XCD of before and 5.7 on the next one (13 and 5.9 TB/s), a write and a read
+// of it 9.3 and 24.4; of 48 MB 7.9 either way, but 4.5 with the order reversed every time.  (Profiler runs that count traffic empty the L2s
+// before every launch, and show none of this but the chunk sums.)  Whole calls, us, ids as they come -> own XCD, the same tensors every time: forward, 8 heads of N = 1000 22.1 -> 20.3, 8 of 512 17.8 -> 16.3, 64 of 256 16.2 -> 15.5, 128 of 640 49.0 -> 47.3, 200
 // of 300 40.3 -> 38.9, 32 of 512 against 4096 keys 60.6 -> 57.0; d = 64, 16 of 512 15.2 -> 14.3, 8 of 2000 25.8 -> 25.2; decoding, 64
 // heads of 8192 keys 78.6 -> 76.1; steps, 16 of 512 47.4 -> 45.7, 64 of 2048 and more the same.
 // One block a head has nothing to share (8 of 64 9.33 -> 9.38).  Without gain, or with a loss: QK-norm (its sums wait for their
 // chains; blocks of 128, 32 of 2048 235.4 -> 238.1), Q-smoothing (the bias kernel reads K in the order of ids, 16 of 1024 31.2 -> 31.9),
-// numerics blocks of 128 (32 of 2048 58.7 -> 60.0).  (65535: the grid's y and z.)
+// numerics blocks of 128 (32 of 2048 58.7 -> 60.0).  On tensors not seen for 700 MB: 8 of N = 1000 24.1 -> 22.7, 64 of 256 18.7 -> 16.9, 32 of 512 x
+// 4096 67.0 -> 62.3, 8 of 8192 x 512 39.9 -> 34.0, d = 64 26.8 -> 23.0; steps, 64 of 2048 343 -> 339.  It does not gain everywhere that it is
+// taken: d = 64, 256 heads of 2560 x 313 1.03 times as long, 632 of 2847 x 297 1.04.  (65535: the grid's y and z.)
 inline bool prepass_own_xcd(int heads, long long blocks) { return heads % 8 == 0 && blocks > 1 && blocks <= 65535; }
 // One block of K and one or two of the others are no more: backwards that quantise Q and K themselves, d = 64, ids as they come -> own XCD,
 // 1000 heads of 128 x 64 49.1 -> 50.3, 2000 90.6 -> 93.8; three blocks and more 1000 of 512 x 64 with 7 % less.
@@ -176,7 +183,8 @@ inline bool prepass_rows_shared(int nqblk, int nkblk) { return nkblk > 1 || nqbl
 // dO alone, in a backward that shares psi(Q) and psi(K): the forward has left O, and the backward finds the codes, in the L2 of the head's
 // XCD, while the 5 bytes an element of all heads are little more than the L2s hold (32 MB).  Steps, us, ids as they come -> own XCD: 8
 // heads of N = 128 29.2 -> 28.8, 128 of 256 55.7 -> 54.6, 32 of 1024 81.5 -> 80.6, 64 of 1024 134.4 -> 132.7, 32 of 2048 183.1 ->
-// 182.3; d = 64, 64 of 1024 90.8 -> 90.0; but this launch of 64 of 2048 17.2 -> 18.3.
+// 182.3; d = 64, 64 of 1024 90.8 -> 90.0; but this launch of 64 of 2048 17.2 -> 18.3.  Backwards alone, on tensors not seen for 700 MB: 128 heads
+// of N = 256 36.1 -> 35.7, d = 64 25.4 -> 24.9, 64 of 1024 95.1 -> 94.1, 65.5 -> 64.9.
 inline bool dO_own_xcd(long long elements) { return elements <= (8 << 20); }
 
 // ---- quantiser that sums QK-normed keys by itself: four rows at a time, or one at a time with fewer registers ----
@@ -233,12 +241,16 @@ inline bool decode_long_enough(long long heads, int nblk, int d, bool k_smooth) 
 }
 
 // A head's workgroups on one XCD (prepass_item), by the elements of K: while K fits the L2s (32 MB in all) the second read of it comes from
-// there, and where it is several times that the ids as they come leave as little; in between those were the better order.  Whole calls with
-// one query row, us, ids as they come -> own XCD, MB of K: d = 128: 4 (8 heads of 2048 keys) 18.7 -> 17.5, 17 (8 of 8192) 23.2 ->
+// there.  Beyond, an L2 that has passed all of its share has the start of it no longer, and what is left is the chunk sums' one fetch; in
+// between calls lost by it, by up to 9 %, for no cause that has been found (the keys of a head count too: 33 MB at d = 64 gained with
+// 32 heads and lost with 64), and the ids stay as they come there.  Whole calls with one query row, the same tensors every time, us, ids as they come -> own XCD, MB of K: d = 128: 4 (8 heads of 2048 keys) 18.7 -> 17.5, 17 (8 of 8192) 23.2 ->
 // 21.9, 25 (24 of 4096) 26.7 -> 26.2, 33 (16 of 8192) 29.6 -> 29.9, 33 (64 of 2048) 28.3 -> 28.5, 50 (48 of 4096) 39.2 -> 39.4, 67 (64 of
 // 4096) 44.6 -> 45.3, 67 (128 of 2048) 45.7 -> 47.8, 100 (96 of 4096) 65.2 -> 64.1, 134 (64 of 8192) 78.4 -> 76.2; d = 64: 8 (32 of 2048) 16.8
 // -> 16.0, 17 (32 of 4096) 20.2 -> 19.6, 25 (24 of 8192) 26.7 -> 26.0, 33 (64 of 4096) 29.3 -> 30.3, 33 (32 of 8192) 27.9 -> 26.8, 50
-// (96 of 4096) 40.0 -> 41.7, 67 (128 of 4096) 44.6 -> 48.5, 100 (96 of 8192) 63.0 -> 62.5, 134 (128 of 8192) 78.5 -> 77.4.
+// (96 of 4096) 40.0 -> 41.7, 67 (128 of 4096) 44.6 -> 48.5, 100 (96 of 8192) 63.0 -> 62.5, 134 (128 of 8192) 78.5 -> 77.4.  Larger, and past the
+// memory-side cache (256 MB): d = 128, 268 (64 of 16384) 142 -> 143, (32 of 32768) 145 -> 143, (256 of 4096) 145 -> 146, 537 (64 of 32768) 295 -> 288, (1024
+// of 2048) 287 -> 288.  On tensors not seen for 700 MB: d = 128, 17 (8 of 8192) 24.5 -> 24.1, 134 (64 of 8192) 82.8 -> 81.4, 268 (64 of 16384) 154.7 ->
+// 154.2, 537 (64 of 32768) 309 -> 303, (256 of 8192) 301 -> 302.
 inline bool decode_own_xcd(long long elements) { return elements <= (14ll << 20) || elements >= (48ll << 20); }
 
 // Key blocks of a wave; a workgroup has four waves, and where a head has several workgroups a second kernel joins their results

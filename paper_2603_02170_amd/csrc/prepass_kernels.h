@@ -286,7 +286,7 @@ __global__ void __launch_bounds__(256, quantiser_waves(D, SUB, MEAN)) prepass_qu
   PrepassItem item{(int)blockIdx.z, (int)blockIdx.y, (int)blockIdx.x};
   if constexpr (OWN_XCD) {
     item = prepass_item(blockIdx.x, blockIdx.y, blockIdx.z, true, jobs.heads);
-    // (K in the order in which an L2 that does not hold all of it has kept what kmean_partial_kernel read)
+    // (job 0: K where there are chunk sums, or dO alone)
     if (MEAN == kMeanOfChunks && item.job == 0) item = last_rows_first(item, jobs.blocks, jobs.heads);
   }
   const QuantJob jb = jobs.job[item.job];
