@@ -73,18 +73,21 @@ inline bool fwd_quad_is_faster(long long heads, int nblk, int nqblk, int d, bool
 //
 // With many heads the two launches are the faster ones again, all the more where the codes are written (`codes`: for a backward, or on a
 // workspace of the full size).  Each line lies where both were timed, tensors warm and (in brackets) not seen for 700 MB.
-// One key block, d = 64.  Up to 32 Q blocks a head, a power of two of them, one launch always (2048 heads of 128 x 64 52 -> 42, with codes 54 ->
-// 44; 512 of 2048 183 -> 141): the two launches read such heads' codes, a power of two apart, at three quarters of the rate of others.  Three
-// Q blocks: 1365 heads of 192 42 -> 39 (47 -> 45), with codes 45 -> 44 (51 -> 54), 5461 170 -> 172 (4666: 162 -> 173).  More: 153 of 320 13.6 -> 10.9,
-// 819 40 -> 39 (45 -> 45), but 1638 68 -> 72, 2000 of 448 (114 -> 144), 1820 of 576 120 -> 142; with codes 131 of 384 12.5 -> 13.3, 256 of 320 16.6 ->
-// 18.0, 1638 72 -> 78, (2800 130 -> 168), 102 of 640 14.6 -> 15.3, 1820 of 576 131 -> 165.
-// d = 128, with codes: just over three workgroups per CU 387 of 78 x 30 19.9 -> 21.1, 131 of 384 19.1 -> 20.6, 67 of 768 18.6 -> 20.1.  341 of 576 (53 -> 52), but 568 77 -> 76 (77 -> 82), 744 of 704 (115 -> 127), 1555 of 576 (223 -> 210); with codes 204 of 320 25.1 -> 23.3, but
-// 1024 83 -> 90 (92 -> 98), 1170 of 448 (145 -> 149), 568 of 576 77 -> 88 (85 -> 97), 910 (142 -> 156), 236 of 832 (57 -> 60).
-// Two key blocks and two Q blocks, d = 64: 1024 heads of 65 33 -> 30, 3000 64 -> 76 (72 -> 83), 20000 with codes 450 -> 605; 3000 of 100 76 -> 80 (87 ->
-// 94), of 128 85 -> 81 (96 -> 103), 15000 of 128 x 65 365 -> 374; with codes 387 of 128 17.0 -> 19.0, 1024 39 -> 35, 3000 94 -> 105 (104 -> 118).  d = 128: 256 heads, a round of two workgroups
-// per CU, 18.6 -> 15.5, 387 22.6 -> 23.7, 512 34 -> 28; 3000 of 65 119 -> 124 (126 -> 137), with codes 512 28.8 -> 29.4, 1500 70 -> 79; 1500 of 80
-// with codes 75 -> 80 (81 -> 88).  More Q blocks, d = 128: 24 of 1024 (a CU and a half for each) 14.1 -> 14.4, 12 of 2048 13.6 -> 14.1, 8 of 4096 15.1 ->
-// 15.7; with codes 24 of 1024 14.6 -> 16.5, 96 of 256 16.4 -> 17.2, 8 of 4096 15.4 -> 17.0, but 170 of 192 x 70 21.8 -> 19.2.
+// One key block, d = 64.  Up to 32 Q blocks a head, a power of two of them, one launch always (2048 heads of 128 x 64 52 -> 42, with
+// codes 54 -> 44; 512 of 2048 183 -> 141): the two launches read such heads' codes, a power of two apart, at three quarters of the rate
+// of others.  Three Q blocks: 1365 heads of 192 42 -> 39 (47 -> 45), with codes 45 -> 44 (51 -> 54), 5461 170 -> 172 (4666: 162 -> 173).
+// More: 153 of 320 13.6 -> 10.9, 819 40 -> 39 (45 -> 45), but 1638 68 -> 72, 2000 of 448 (114 -> 144), 1820 of 576 120 -> 142; with
+// codes 131 of 384 12.5 -> 13.3, 256 of 320 16.6 -> 18.0, 1638 72 -> 78, (2800 130 -> 168), 102 of 640 14.6 -> 15.3, 1820 of 576 131 ->
+// 165.
+// d = 128, with codes: just over three workgroups per CU 387 of 78 x 30 19.9 -> 21.1, 131 of 384 19.1 -> 20.6, 67 of 768 18.6 -> 20.1.
+// 341 of 576 (53 -> 52), but 568 77 -> 76 (77 -> 82), 744 of 704 (115 -> 127), 1555 of 576 (223 -> 210); with codes 204 of 320 25.1 ->
+// 23.3, but 1024 83 -> 90 (92 -> 98), 1170 of 448 (145 -> 149), 568 of 576 77 -> 88 (85 -> 97), 910 (142 -> 156), 236 of 832 (57 -> 60).
+// Two key blocks and two Q blocks, d = 64: 1024 heads of 65 33 -> 30, 3000 64 -> 76 (72 -> 83), 20000 with codes 450 -> 605; 3000 of 100
+// 76 -> 80 (87 -> 94), of 128 85 -> 81 (96 -> 103), 15000 of 128 x 65 365 -> 374; with codes 387 of 128 17.0 -> 19.0, 1024 39 -> 35,
+// 3000 94 -> 105 (104 -> 118).  d = 128: 256 heads, a round of two workgroups per CU, 18.6 -> 15.5, 387 22.6 -> 23.7, 512 34 -> 28; 3000
+// of 65 119 -> 124 (126 -> 137), with codes 512 28.8 -> 29.4, 1500 70 -> 79; 1500 of 80 with codes 75 -> 80 (81 -> 88).  More Q blocks,
+// d = 128: 24 of 1024 (a CU and a half for each) 14.1 -> 14.4, 12 of 2048 13.6 -> 14.1, 8 of 4096 15.1 -> 15.7; with codes 24 of 1024
+// 14.6 -> 16.5, 96 of 256 16.4 -> 17.2, 8 of 4096 15.4 -> 17.0, but 170 of 192 x 70 21.8 -> 19.2.
 inline bool fwd_short_is_faster(long long heads, int nkblk, int nqblk, int d, bool codes, int nq = 0, int nk = 0) {
   if (nqblk >= 1 << 20 || (codes && nqblk > 64)) return false;      // (the grid counts threads in 32 bits)
   if (nq == 0) nq = 64 * nqblk;
